@@ -104,7 +104,7 @@ TRON_API int tron_dataset_shape(const tron_dataset *ds, int64_t *n, int64_t *d, 
  *   "fwd_head_nnz"             of fwd_csr_nnz, the nonzeros of the head partition (the most frequent columns)
  *   "bwd_tile_nnz", "bwd_tile_rows", "bwd_tiles"  nonzeros, features and tiles of the hot-row tiles
  *   "fwd_lds_columns"          columns served from LDS tables in the forward pass
- *   "dense_grid"               workgroups of the dense kernels
+ *   "dense_grid"               groups of four wave tiles of the matrix, at most 2048 (the unit of tron_hv_static's limit)
  *   "dense_compact_rows"       rows of the compacted copy of the active rows the next tron_hv would run over (0: none)
  *   "unit_values"              1 when the sparse layouts keep no values (every instance's entries share one value)
  *   "fwd_bytes_gather", "fwd_bytes_head", "fwd_bytes_ranges", "fwd_bytes_combine",
@@ -150,7 +150,7 @@ TRON_API int tron_hv(tron_dataset *ds, double C, const double *v_dev, double *Hv
  * TRON_HV_STATIC_MAX_DOUBLES doubles (2 MiB, held by every GPU the library runs on until the process ends) instead of
  * the handle's allocation, and the call itself allocates nothing and never synchronises: it only enqueues on the
  * handle's stream.  vHv_dev: DEVICE pointer to one double that receives v.Hv, or NULL.
- * Dense handles only.  TRON_EINVAL when d * (workgroups of the dense kernels, at most 2048; tron_dataset_stat
+ * Dense handles only.  TRON_EINVAL when d * (groups of four wave tiles, at most 2048; tron_dataset_stat
  * "dense_grid") + d + 1 exceeds TRON_HV_STATIC_MAX_DOUBLES (any n for d <= 127), when the handle is sparse, or when
  * the current device is not the handle's; TRON_ESTATE if no D is cached.
  * All calls on one GPU share the one array: calls that overlap in time on the same GPU (different streams or

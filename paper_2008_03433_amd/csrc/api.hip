@@ -477,7 +477,7 @@ int tron_dataset_stat(const tron_dataset *ds, const char *name, int64_t *value)
         {"bwd_tile_rows", ds->dense ? 0 : ds->bwd.hot.nhot},
         {"bwd_tiles", ds->dense ? 0 : ds->bwd.hot.ntiles_total},
         {"fwd_lds_columns", ds->dense ? 0 : [&] { int64_t t = 0; for (int x = 0; x < kMaxParts; ++x) t += ds->fwd.part_nhot[x]; return t; }()},
-        {"dense_grid", ds->dense_grid},
+        {"dense_grid", ds->dense ? dense_work_units(ds->n, ds->d) : 0},
         {"dense_compact_rows", (ds->dense && ds->have_D && ds->hat_slot == ds->Dcur) ? ds->hat_rows : 0},
         {"unit_values", (!ds->dense && ds->fwd.unit) ? 1 : 0},
     };

@@ -50,7 +50,7 @@ struct Tuning {
     int64_t fuse_reductions = -1;  // second reduction stage inside the producing kernel (last workgroup): 0 never, 1 always,
                                    //   -1 automatic (launches of few workgroups, where the extra launch costs more than it does)
     int64_t dense_device_driver = -1;   // tron_solve on dense d <= 32 without preconditioner driven from the device:
-                                        //   0 never, 1 always, -1 automatic (the L2-SVM on matrices up to 1 GB)
+                                        //   0 never, 1 always, -1 automatic (all but L2-SVM matrices above 1 GB)
     int64_t batch_grid = 0;  // workgroups of the multi-problem pass: 0 = as many as are resident at once
     int64_t batch_mfma = -1; // multi-problem pass on the matrix units: 1 = yes, 0 = no, -1 = the library decides
     int64_t batch_lean = 1;         // matrix-unit pass: rounds without function / gradient requests run a kernel compiled without those steps
@@ -251,7 +251,7 @@ struct CsrPlan {
 }  // namespace tron
 
 // ---------------------------------------------------------------- the handle
-struct tron_batch;
+namespace tron { struct DriverState; struct SolveParams; }
 struct tron_dataset {
     int64_t n = 0, d = 0;
     bool dense = false;
@@ -296,7 +296,7 @@ struct tron_dataset {
     int hat_slot = -1;
     int64_t active_count[2] = {0, 0};   // rows with D != 0 in each buffer
 
-    tron_batch *self_batch = nullptr;   // dense: one problem over all rows, for solves driven from the device
+    tron::DriverState *driver = nullptr;   // dense: solves driven from the device
 
     // solver vectors (d each), allocated on first tron_solve
     double *sv[9] = {nullptr};
@@ -417,7 +417,8 @@ PlanBytes plan_bytes(const CsrPlan &A);
 
 // ---- kernels_dense.hip
 bool dense_supported(int64_t d);
-int dense_grid_for(int64_t n, int64_t d);
+int dense_grid_for(int64_t n, int64_t d);     // workgroups of a pass
+int dense_work_units(int64_t n, int64_t d);   // what tron_hv_static's limit counts: groups of four wave tiles, at most 2048
 int64_t dense_partials_needed(int64_t n, int64_t d);
 // fused pass: z = X w, loss terms, D -> Dout, partial sums of X^T zhat and of the loss;
 // then g = w + C (column sums) (if g != null), scalars[0] = sum loss, [1] = w.w, [2] = g.g, [3] = rows with D != 0
@@ -437,6 +438,9 @@ int dense_compact_build(tron_dataset *ds, int Dslot);
 // whether the knob asks for the copy, given how many Hessian-vector products the last inner solve took
 bool dense_compact_wanted(const tron_dataset *ds, int Dslot, int recent_cg_iters);
 void dense_compact_release(tron_dataset *ds);
+
+// one round of a solve driven from the device (d <= 32): the pass that serves the problem's pending request, and its next step
+int dense_round(tron_dataset *ds, const SolveParams &P, DriverState &drv, int64_t stamp);
 
 // ---- batch.hip
 int dense_device_solve(tron_dataset *ds, const tron_params &P, double *w_dev, tron_result *res);

@@ -24,6 +24,51 @@ __device__ __forceinline__ double read_lane(double v, int lane)
     return __hiloint2double(hi, lo);
 }
 
+// A zero that the compiler takes for lane-dependent: an address formed with it is read with a vector load.  A scalar load
+// would be counted by the same counter as the LDS operations, so the next wait for LDS would also wait for memory.
+__device__ __forceinline__ int lane_zero()
+{
+    int zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+    return zero;
+}
+
+// Two values to add over pairs of lanes, of which each lane of a pair keeps one: lanes with `odd` clear return a summed over
+// the pair, the others b.  CTRL moves each lane's partner to it (0xB1: lane ^ 1, 0x4E: lane ^ 2).
+template <int CTRL>
+__device__ __forceinline__ double fold(double a, double b, int odd)
+{
+    const double keep = odd ? b : a, give = odd ? a : b;
+    return keep + dpp_move<CTRL>(give);
+}
+
+// v of lane ^ 4: row_shr:4 into the upper quad of every eight lanes, row_shl:4 into the lower one
+__device__ __forceinline__ double other_quad_of_8(double v)
+{
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    int a = __builtin_amdgcn_update_dpp(lo, lo, 0x114, 0xf, 0xa, false);
+    a = __builtin_amdgcn_update_dpp(a, lo, 0x104, 0xf, 0x5, false);
+    int b = __builtin_amdgcn_update_dpp(hi, hi, 0x114, 0xf, 0xa, false);
+    b = __builtin_amdgcn_update_dpp(b, hi, 0x104, 0xf, 0x5, false);
+    return __hiloint2double(b, a);
+}
+
+// v + (v of lane ^ 16), v + (v of lane ^ 32): permlane16_swap / permlane32_swap of a value with itself give both operands
+__device__ __forceinline__ double add_row_pairs(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double add_halves(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
 // Sum over aligned groups of 2 / 4 / 8 / 16 consecutive lanes; every lane of a group receives its total.
 __device__ __forceinline__ double sum2(double v) { return v + dpp_move<0xB1>(v); }
 __device__ __forceinline__ double sum4(double v) { v = sum2(v); return v + dpp_move<0x4E>(v); }
@@ -129,6 +174,27 @@ __device__ __forceinline__ double block_sum(double v, double *lds)
     }
     __syncthreads();
     return t;
+}
+
+// ---- sums that one workgroup leaves for the workgroup that finishes last
+// They are written through to where every XCD sees them (a relaxed store of device scope), and the wavefront that wrote
+// them waits for the stores before it draws the ticket; the reader uses loads of device scope.  A fence of device scope
+// (__threadfence) would do as well, but it writes back the XCD's whole L2 for every workgroup: a pass over 1M x 24 rows by 512
+// workgroups took 59 us that way, by 2048 workgroups 119 us.
+__device__ __forceinline__ void store_shared(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double load_shared(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// True in every thread of the workgroup that draws the last of the launch's tickets.  Called by all threads; the workgroup's
+// sums were stored by wavefront 0.  The counter is the only thing touched by a read-modify-write; the caller clears it.
+__device__ __forceinline__ bool last_workgroup(unsigned *ticket)
+{
+    __shared__ int is_last;
+    if (threadIdx.x < kWave) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores of this wavefront have arrived
+        if (threadIdx.x == 0) is_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    }
+    __syncthreads();
+    return is_last;
 }
 
 // Second reduction stage inside the producing kernel (see Finish in common.h).  Every thread of every workgroup calls it

@@ -912,9 +912,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_hot(int n, const int32_t *__r
 // a full memory latency in every iteration of the persistent loops, which prefetch these entries two chunks ahead.
 __device__ __forceinline__ int4 load_uniform(const int4 *__restrict__ p)
 {
-    int zero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));   // a lane-dependent zero as far as the compiler can tell
-    return p[zero];
+    return p[lane_zero()];
 }
 
 struct PartPtrs {   // device arrays of one partitioned plan (or of its head partition, pre-offset where noted)

@@ -5,25 +5,140 @@
 // so each element of X is read from HBM exactly once per call.
 //
 // Layout of the work inside a wavefront (64 lanes): a row is covered by L consecutive lanes, each
-// holding E consecutive columns (E*L >= d); one "step" therefore covers 64/L rows and a wave tile of
+// holding E of its columns (E*L >= d; see Tile); one "step" covers 64/L rows and a wave tile of
 // U steps covers RT = U*64/L consecutive rows.  For d = 24: E = 6, L = 4, U = 4 -- 64 rows = 12 KiB per
 // tile, each lane issuing three 16-byte loads per step, twelve per tile, all in flight together.
-//   1. partial dot products x.v per lane, butterfly over the L lanes of the row;
-//   2. the RT row results are moved so that lane i owns row i of the tile: the per-row scalar work
-//      (sigmoid / log1p for the logistic loss, D scaling) runs once per row, and D, y are read/written
-//      as one coalesced 8-byte-per-lane access;
-//   3. the per-row coefficient is broadcast back to the row's lanes and accumulated into E private
-//      column accumulators, which are reduced over the wavefront / workgroup once, at the end.
-// Workgroup partial column sums go to `partials[col * grid + block]`; a second kernel adds them in a
-// fixed order (no atomics) and applies  out = add + C * sum  together with the dot products the
-// trust-region driver needs.
+//   1. partial dot products x.v per lane, summed over the L lanes of the row and folded on the way, so that a
+//      row's total ends up in the lanes that own the row;
+//   2. the per-row scalar work (sigmoid / log1p for the logistic loss, D scaling) runs in the owners, and D, y
+//      are read / written as one coalesced access;
+//   3. the per-row coefficient goes back to the row's lanes (moves inside a quad of lanes) and is accumulated into E
+//      private column accumulators, which are reduced over the wavefront / workgroup once, at the end.
+// Every workgroup leaves its column sums at `partials[block * d ...]`.  For d <= 32 the workgroup that finishes last adds
+// them in a fixed order and forms the outputs (dense_finish); the separate launch this replaces took 9.7 us for 2048
+// workgroups of 24 columns.  Wider matrices take a launch of k_dense_columns, one workgroup per 16 columns.  Nothing is added
+// in an order that depends on timing.
 #include <cmath>
 
 #include "dense_tile.h"
+#include "device_driver.h"
 
 namespace tron {
 
 namespace {
+
+// What the second stage of a pass forms from the per-workgroup column sums:
+//   out = add + C * sums (add == null: add 1);  scal null: no scalars;
+//   fun_grad: scal[0] = sum of the losses, [1] = add.add (add = w), [2] = out.out, [3] = rows with D != 0;
+//   otherwise: scal[0] = scal_copy[0] = out.dotw (the CG step kernel continues from the copy).
+struct DenseFinish {
+    unsigned *ticket;      // counter of finished workgroups (zero between kernels)
+    const double *add;
+    double C;
+    double *out;           // may be null
+    const double *dotw;    // null: out itself
+    double *scal, *scal_copy;
+    bool fun_grad;
+};
+
+// d <= 32 (at most four lanes per row): the last workgroup completes the sums
+constexpr bool dense_finishes(int L) { return L <= 4; }
+constexpr int kFinishMaxD = 32;
+// Eight wavefronts per CU, whatever the shape: with twelve loads of 16 bytes per lane in flight they keep HBM busy, and every
+// workgroup more costs its ticket (10 ns, one after the other) and its sums.  1M x 24, a Hessian-vector call with 256 / 512 /
+// 1024 / 2048 workgroups: 43 / 44 / 52 / 64 us; 20M x 24: 629 / 640 / 652 / 663 us.  Twelve wavefronts: 44 and 633 us.
+constexpr int dense_block(int L) { return dense_finishes(L) ? 512 : kBlock; }
+constexpr int kFinishGrid = 256, kWideGrid = 512;
+// doubles of LDS: the column sums of the wavefronts, then one per thread for the workgroup that finishes last
+constexpr int dense_lds(int E, int L) { return dense_block(L) / kWave * E * L > dense_block(L) ? dense_block(L) / kWave * E * L : dense_block(L); }
+constexpr int kColumnsBlock = 1024, kColumnsPer = 16;
+
+__device__ __forceinline__ void store_dense_scalars(const DenseFinish &fin, double loss, double ww, double cp, double active)
+{
+    if (fin.fun_grad) {
+        fin.scal[0] = loss;
+        fin.scal[1] = ww;
+        fin.scal[2] = cp;
+        fin.scal[3] = active;
+    } else {
+        fin.scal[0] = cp;
+        fin.scal_copy[0] = cp;
+    }
+}
+
+// Every thread of every workgroup calls it; wavefront 0 has written the workgroup's d <= 32 column sums (and its two
+// other sums) last.  The workgroup that draws the last ticket adds the rows of partial sums: thread t the elements t,
+// t + T, ... of the d x grid array, T a multiple of d, so all of them belong to column t % d; then over the threads of a
+// column in LDS (col_sum: a double per thread; its earlier contents have been read by wavefront 0 only).  True in wavefront 0
+// of that workgroup: lane c < d then has column c's sum, every lane the loss sum and the number of active rows (zero without
+// loss_partials); the caller clears the counter.
+template <int kWaves>
+__device__ __forceinline__ bool dense_last_sums(double *col_sum, unsigned *ticket, int d, const double *partials, const double *loss_partials,
+                                                const double *active_partials, double &col, double &loss, double &active)
+{
+    constexpr int kThreads = kWaves * kWave, kAtOnce = 8;
+    __shared__ double red[2][kWaves];
+    if (!last_workgroup(ticket)) return false;
+    const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
+    const int groups = kThreads / d, T = groups * d, total = d * (int)gridDim.x;
+    double s = 0.0;
+    if (t < T)
+        for (int i0 = t; i0 < total; i0 += kAtOnce * T) {
+            double v[kAtOnce];
+#pragma unroll
+            for (int k = 0; k < kAtOnce; ++k) v[k] = (i0 + k * T < total) ? load_shared(partials + i0 + k * T) : 0.0;
+#pragma unroll
+            for (int k = 0; k < kAtOnce; ++k) s += v[k];
+        }
+    col_sum[t] = s;
+    double a = 0.0, e = 0.0;
+    if (loss_partials) {
+        for (int b = t; b < (int)gridDim.x; b += kThreads) {
+            a += load_shared(loss_partials + b);
+            e += load_shared(active_partials + b);
+        }
+        a = wave_sum(a);
+        e = wave_sum(e);
+    }
+    if (lane == 0) {
+        red[0][wv] = a;
+        red[1][wv] = e;
+    }
+    __syncthreads();
+    if (wv != 0) return false;
+    col = loss = active = 0.0;
+    if (lane < d)
+        for (int k = 0; k < groups; ++k) col += col_sum[k * d + lane];
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        loss += red[0][k];
+        active += red[1][k];
+    }
+    return true;
+}
+
+template <int kWaves>
+__device__ __forceinline__ void dense_finish(double *lds, const DenseFinish &fin, int d, const double *partials, const double *loss_partials,
+                                             const double *active_partials)
+{
+    double sum, loss, active;
+    if (!dense_last_sums<kWaves>(lds, fin.ticket, d, partials, loss_partials, active_partials, sum, loss, active)) return;
+    const int lane = threadIdx.x;
+    double cp = 0.0, ww = 0.0;
+    if (lane < d) {
+        const double add = fin.add ? fin.add[lane] : 1.0;
+        const double o = fma(fin.C, sum, add);
+        cp = o * (fin.dotw ? fin.dotw[lane] : o);
+        ww = add * add;
+        if (fin.out) fin.out[lane] = o;
+    }
+    cp = wave_sum(cp);
+    ww = wave_sum(ww);
+    if (lane == 0) {
+        if (fin.scal) store_dense_scalars(fin, loss, ww, cp, active);
+        *fin.ticket = 0u;
+    }
+}
 
 // ------------------------------------------------------------------ Hessian-vector pass
 // MASK: D is the active set of the L2-SVM (D_ii = 2 on it, else 0) instead of an fp64 value per row: one bit per row,
@@ -31,35 +146,35 @@ namespace {
 // DIAG: column sums of D_i x_ij^2 instead (the diagonal of X^T D X; v is not read).
 // SKIP (with the bit words only): rows outside the active set are not read.  Chosen by the host when a noticeable
 // part of the rows is inactive; with (almost) every row active the plain loop is about 1% faster.
+// lds: E * L doubles per wavefront
 template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP>
-__global__ __launch_bounds__(kBlock) void k_dense_hv(int64_t n, int64_t d, const double *__restrict__ X,
-                                                     const void *__restrict__ Dv, const double *__restrict__ v,
-                                                     double *__restrict__ partials)
+__device__ __forceinline__ void hv_pass(double *lds, int64_t n, int64_t d, const double *__restrict__ X, const void *__restrict__ Dv,
+                                        const double *__restrict__ v, double *__restrict__ partials)
 {
+    constexpr int kWaves = dense_block(L) / kWave;
     const double *D = static_cast<const double *>(Dv);
     const uint8_t *Dm = static_cast<const uint8_t *>(Dv);
     using T = Tile<E, L, U, VEC>;
-    __shared__ double lds[kWavesPerBlock * E * L];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    const int q = lane % L;
+    const int q = lane % L, own = T::own_row(lane);
     double vreg[E], acc[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        vreg[e] = (!DIAG && q * E + e < d) ? v[q * E + e] : 0.0;
+        vreg[e] = (!DIAG && T::col(q, e) < d) ? v[T::col(q, e)] : 0.0;
         acc[e] = 0.0;
     }
     const int64_t ntiles = (n + T::RT - 1) / T::RT;
-    const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
+    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
     // With the active set as one 64-bit word per tile (bit i = row row0 + i is active; rows past n are never set)
     // the rows outside it are not read: the pass moves 8 |I| d bytes, the saving the paper gets from a compacted
     // copy X_I (Section 5) without the copy.  The word of the next tile is fetched one iteration ahead.
     constexpr bool kBits = MASK && T::RT == kWave;
     const uint64_t *Dbits = static_cast<const uint64_t *>(Dv);
-    const int64_t tile0 = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+    const int64_t tile0 = (int64_t)blockIdx.x * kWaves + wv;
     uint64_t bits_next = (kBits && SKIP && tile0 < ntiles) ? Dbits[tile0] : 0;
     for (int64_t tile = tile0; tile < ntiles; tile += nwaves) {
         const int64_t row0 = tile * T::RT;
-        double x[U][E], t[U], c[U];
+        double x[U][E], c[U];
         uint64_t bits = 0;
         if (kBits && SKIP) {
             bits = bits_next;
@@ -70,21 +185,19 @@ __global__ __launch_bounds__(kBlock) void k_dense_hv(int64_t n, int64_t d, const
         if (kBits && !SKIP) bits = Dbits[tile];
         double Drow = 0.0;
         if (kBits) {
-            Drow = ((bits >> lane) & 1u) ? 2.0 : 0.0;
-        } else if (lane < T::RT && row0 + lane < n) {
-            Drow = MASK ? (Dm[row0 + lane] ? 2.0 : 0.0) : D[row0 + lane];
+            Drow = ((bits >> own) & 1u) ? 2.0 : 0.0;
+        } else if (row0 + own < n) {
+            Drow = MASK ? (Dm[row0 + own] ? 2.0 : 0.0) : D[row0 + own];
         }
         if (DIAG) {
-            T::from_row_owner(Drow, lane, c);
+            T::from_row_owner(Drow, c);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
 #pragma unroll
                 for (int e = 0; e < E; ++e) acc[e] = fma(c[u] * x[u][e], x[u][e], acc[e]);
             }
         } else {
-            T::row_dots(x, vreg, t);
-            const double a1 = Drow * T::to_row_owner(t, lane);   // a1 = D (X v)
-            T::from_row_owner(a1, lane, c);
+            T::from_row_owner(Drow * T::row_sum(x, vreg, lane), c);   // a1 = D (X v)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
 #pragma unroll
@@ -92,27 +205,38 @@ __global__ __launch_bounds__(kBlock) void k_dense_hv(int64_t n, int64_t d, const
             }
         }
     }
-    T::flush(acc, d, lane, wv, lds, partials);
+    T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
+}
+
+template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP>
+__global__ __launch_bounds__(dense_block(L)) void k_dense_hv(int64_t n, int64_t d, const double *__restrict__ X,
+                                                                const void *__restrict__ Dv, const double *__restrict__ v,
+                                                                double *__restrict__ partials, DenseFinish fin)
+{
+    constexpr int kWaves = dense_block(L) / kWave;
+    __shared__ double lds[dense_lds(E, L)];
+    hv_pass<E, L, U, VEC, MASK, DIAG, SKIP>(lds, n, d, X, Dv, v, partials);
+    if constexpr (dense_finishes(L)) dense_finish<kWaves>(lds, fin, (int)d, partials, nullptr, nullptr);
 }
 
 // ------------------------------------------------------------------ function / gradient pass
+// lds as in hv_pass, lds_red: two rows of one double per wavefront
 template <int E, int L, int U, bool VEC, int LOSS>
-__global__ __launch_bounds__(kBlock) void k_dense_fun_grad(int64_t n, int64_t d, const double *__restrict__ X,
-                                                           const int8_t *__restrict__ y, const double *__restrict__ w,
-                                                           void *__restrict__ Dv, double *__restrict__ partials,
-                                                           double *__restrict__ loss_partials, double *__restrict__ active_partials)
+__device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[dense_block(L) / kWave], int64_t n, int64_t d,
+                                              const double *__restrict__ X, const int8_t *__restrict__ y, const double *__restrict__ w,
+                                              void *__restrict__ Dv, double *__restrict__ partials,
+                                              double *__restrict__ loss_partials, double *__restrict__ active_partials)
 {
+    using T = Tile<E, L, U, VEC>;
+    constexpr int kWaves = dense_block(L) / kWave;
     double *Dout = static_cast<double *>(Dv);       // logistic loss: fp64 D
     uint8_t *Dmask = static_cast<uint8_t *>(Dv);    // L2-SVM: active-set mask
-    using T = Tile<E, L, U, VEC>;
-    __shared__ double lds[kWavesPerBlock * E * L];
-    __shared__ double lds_red[kWavesPerBlock];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    const int q = lane % L;
+    const int q = lane % L, own = T::own_row(lane);
     double wreg[E], acc[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        wreg[e] = (q * E + e < d) ? w[q * E + e] : 0.0;
+        wreg[e] = (T::col(q, e) < d) ? w[T::col(q, e)] : 0.0;
         acc[e] = 0.0;
     }
     double loss_acc = 0.0, active_acc = 0.0;   // sum of the losses; number of rows with D != 0
@@ -126,8 +250,8 @@ __global__ __launch_bounds__(kBlock) void k_dense_fun_grad(int64_t n, int64_t d,
     uint64_t held_bits = 0;
     int64_t held_tile = -1;
     const int64_t ntiles = (n + T::RT - 1) / T::RT;
-    const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
-    const int64_t wave_id = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+    const int64_t wave_id = (int64_t)blockIdx.x * kWaves + wv;
     const int64_t per_wave = (ntiles + nwaves - 1) / nwaves;
     // kBits: tiles [first, last) one after the other; otherwise tiles wave_id, wave_id + nwaves, ...
     const int64_t first = kBits ? wave_id * per_wave : wave_id;
@@ -136,33 +260,33 @@ __global__ __launch_bounds__(kBlock) void k_dense_fun_grad(int64_t n, int64_t d,
     int it = 0;
     for (int64_t tile = first; tile < last; tile += step, ++it) {
         const int64_t row0 = tile * T::RT;
-        double x[U][E], t[U], c[U];
+        double x[U][E], c[U];
         T::load(X, n, d, row0, lane, x);
-        const bool mine = lane < T::RT && row0 + lane < n;
-        const double yrow = mine ? (double)y[row0 + lane] : 1.0;
-        T::row_dots(x, wreg, t);
-        const double z = T::to_row_owner(t, lane);            // z = X w
+        const bool in = row0 + own < n, mine = in && T::first_owner(lane);
+        const double yrow = in ? (double)y[row0 + own] : 1.0;
+        const double z = T::row_sum(x, wreg, lane);           // z = X w
         double alpha, zhat, Di;
         loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
         if (mine) {
             loss_acc += alpha;
             active_acc += (Di != 0.0) ? 1.0 : 0.0;
-        } else {
+        }
+        if (!in) {
             Di = 0.0;
             zhat = 0.0;
         }
         if (kBits) {
-            const uint64_t bits = __ballot(Di != 0.0);
+            const uint64_t bits = T::ballot_rows(Di != 0.0, lane);
             if (lane == (it & (kWave - 1))) { held_bits = bits; held_tile = tile; }
             if ((it & (kWave - 1)) == kWave - 1) {
                 Dbits[held_tile] = held_bits;   // every lane holds one: 64 consecutive words
                 held_tile = -1;
             }
         } else if (mine) {
-            if (LOSS == TRON_LOSS_L2SVM) Dmask[row0 + lane] = (Di != 0.0) ? 1 : 0;
-            else Dout[row0 + lane] = Di;
+            if (LOSS == TRON_LOSS_L2SVM) Dmask[row0 + own] = (Di != 0.0) ? 1 : 0;
+            else Dout[row0 + own] = Di;
         }
-        T::from_row_owner(zhat, lane, c);
+        T::from_row_owner(zhat, c);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
 #pragma unroll
@@ -170,130 +294,144 @@ __global__ __launch_bounds__(kBlock) void k_dense_fun_grad(int64_t n, int64_t d,
         }
     }
     if (kBits && held_tile >= 0) Dbits[held_tile] = held_bits;
-    T::flush(acc, d, lane, wv, lds, partials);
-    loss_acc = block_sum(loss_acc, lds_red);
-    if (threadIdx.x == 0) loss_partials[blockIdx.x] = loss_acc;
-    active_acc = block_sum(active_acc, lds_red);
-    if (threadIdx.x == 0) active_partials[blockIdx.x] = active_acc;
-}
-
-// ------------------------------------------------------------------ second stage
-// One wavefront per column: out[c] = add[c] + C * sum_b partials[c*grid + b]; colprod[c] = out[c]*dotw[c]
-// (dotw = v for the Hessian-vector product, out itself for the gradient norm).
-__global__ __launch_bounds__(kBlock) void k_dense_columns(int64_t d, int grid, const double *__restrict__ partials,
-                                                          const double *__restrict__ add, double C, double *__restrict__ out,
-                                                          const double *__restrict__ dotw, double *__restrict__ colprod)
-{
-    const int c = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-    if (c >= d) return;
-    const int lane = threadIdx.x & (kWave - 1);
-    const double *p = partials + (int64_t)c * grid;
-    double s = 0.0;
-    for (int b = lane; b < grid; b += kWave) s += p[b];
-    s = wave_sum(s);
+    loss_acc = wave_sum(loss_acc);
+    active_acc = wave_sum(active_acc);
     if (lane == 0) {
-        const double o = fma(C, s, add ? add[c] : 1.0);
-        if (out) out[c] = o;
-        colprod[c] = o * (dotw ? dotw[c] : o);
+        lds_red[0][wv] = loss_acc;
+        lds_red[1][wv] = active_acc;
+    }
+    T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) t += lds_red[threadIdx.x][k];
+        store_shared((threadIdx.x ? active_partials : loss_partials) + blockIdx.x, t);
     }
 }
 
-// scal[0] = sum loss partials (or v.Hv when nloss == 0: then scal[0] = sum colprod), scal[1] = w.w, scal[2] = sum colprod,
-// scal[3] = sum of the active-row counts
-__global__ __launch_bounds__(kBlock) void k_dense_scalars(int64_t d, int nloss, const double *__restrict__ loss_partials,
-                                                          const double *__restrict__ active_partials,
-                                                          const double *__restrict__ w, const double *__restrict__ colprod,
-                                                          double *__restrict__ scal, double *__restrict__ scal_copy)
+template <int E, int L, int U, bool VEC, int LOSS>
+__global__ __launch_bounds__(dense_block(L)) void k_dense_fun_grad(int64_t n, int64_t d, const double *__restrict__ X,
+                                                                      const int8_t *__restrict__ y, const double *__restrict__ w,
+                                                                      void *__restrict__ Dv, double *__restrict__ partials,
+                                                                      double *__restrict__ loss_partials, double *__restrict__ active_partials,
+                                                                      DenseFinish fin)
 {
-    __shared__ double lds[kWavesPerBlock];
-    double a = 0.0, b = 0.0, c = 0.0, e = 0.0;
-    for (int i = threadIdx.x; i < nloss; i += kBlock) {
-        a += loss_partials[i];
-        e += active_partials[i];
-    }
-    for (int64_t j = threadIdx.x; j < d; j += kBlock) {
-        if (w) b += w[j] * w[j];
-        c += colprod[j];
-    }
-    a = block_sum(a, lds);
-    b = block_sum(b, lds);
-    c = block_sum(c, lds);
-    e = block_sum(e, lds);
-    if (threadIdx.x == 0) {
-        if (nloss > 0) {
-            scal[0] = a;
-            scal[1] = b;
-            scal[2] = c;
-            scal[3] = e;
-        } else {
-            scal[0] = c;
-            scal_copy[0] = c;   // p.Hp: the CG step kernel continues from it
-        }
-    }
+    constexpr int kWaves = dense_block(L) / kWave;
+    __shared__ double lds[dense_lds(E, L)];
+    __shared__ double lds_red[2][kWaves];
+    fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, y, w, Dv, partials, loss_partials, active_partials);
+    if constexpr (dense_finishes(L)) dense_finish<kWaves>(lds, fin, (int)d, partials, loss_partials, active_partials);
 }
 
-// Both second-stage kernels in one launch, for d <= kFinishMaxD: a single workgroup of 16 wavefronts; wavefront w adds the
-// per-workgroup partial sums of columns w, w + 16, ... (sixteen loads per lane in flight at a time, added in index
-// order), then the workgroup adds the column products and the other scalars.  Same outputs as k_dense_columns followed
-// by k_dense_scalars; the launch and the wait between the two are saved, which is a third of a Hessian-vector call on a
-// matrix of a million rows.
-constexpr int kFinishMaxD = 64;
-constexpr int kFinishWaves = 16;
-__global__ __launch_bounds__(kFinishWaves * kWave) void k_dense_finish(int64_t d, int grid, const double *__restrict__ partials,
-                                                                       const double *__restrict__ add, double C, double *__restrict__ out,
-                                                                       const double *__restrict__ dotw, int nloss,
-                                                                       const double *__restrict__ loss_partials,
-                                                                       const double *__restrict__ active_partials,
-                                                                       const double *__restrict__ w, double *__restrict__ scal,
-                                                                       double *__restrict__ scal_copy)
+// ------------------------------------------------------------------ a round of a solve driven from the device
+// The pass that serves the problem's pending request -- function / gradient at a trial point or a Hessian-vector product -- and,
+// in the workgroup that finishes last, the step of Algorithm 1 or of the CG iteration that was waiting for it: one launch
+// per product, no vector kernels and no host in between.  d <= 32, tiles of 64 rows.
+struct RoundArgs {
+    const double *X;
+    const int8_t *y;
+    void *D[2];
+    double *partials, *loss_partials, *active_partials;
+    unsigned *ticket;
+    BatchCtl *ctl;
+    ProbState *st;
+    tron_trace_rec *trace;
+    BatchHost *host;
+};
+
+template <int E, int L, int U, bool VEC, int LOSS>
+__global__ __launch_bounds__(dense_block(L)) void k_dense_round(int64_t n, int64_t d, RoundArgs A, SolveParams P, int64_t stamp)
 {
-    __shared__ double colprod[kFinishMaxD];
-    __shared__ double red[4][kFinishWaves];
+    constexpr int kWaves = dense_block(L) / kWave;
+    constexpr bool svm = LOSS == TRON_LOSS_L2SVM;
+    __shared__ double lds[dense_lds(E, L)];
+    __shared__ double lds_red[2][kWaves];
+    const int mode = __builtin_amdgcn_readfirstlane(A.ctl->mode[0]);
+    if (mode == MODE_IDLE) {   // the solve ended in an earlier round
+        if (blockIdx.x == 0 && threadIdx.x < kWave) advance_problem(0, mode, d, 0.0, 0.0, A.ctl, A.st, P, A.trace, A.host, stamp);
+        return;
+    }
+    void *D = __builtin_amdgcn_readfirstlane(A.ctl->dslot[0]) ? A.D[1] : A.D[0];
+    const double *vec = A.ctl->vec[0];
+    if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, A.X, A.y, vec, D, A.partials, A.loss_partials, A.active_partials);
+    else hv_pass<E, L, U, VEC, svm, false, svm>(lds, n, d, A.X, D, vec, A.partials);
+    double col, loss, active;
+    if (!dense_last_sums<kWaves>(lds, A.ticket, (int)d, A.partials, mode == MODE_FG ? A.loss_partials : nullptr, A.active_partials, col, loss, active)) return;
+    if (threadIdx.x == 0) *A.ticket = 0u;
+    advance_problem(0, mode, d, col, loss, A.ctl, A.st, P, A.trace, A.host, stamp);
+}
+
+// ------------------------------------------------------------------ second stage of the wide matrices
+// out[c] = add[c] + C * sum_b partials[b * d + c] and the scalars (see DenseFinish) for d > 32.  A workgroup takes 16
+// columns; a wavefront reads four rows of partial sums (128 bytes each) per load, sixteen loads in flight, wavefront k the
+// rows 4 k .. 4 k + 3 of every 64.  The scalars are sums over the columns, so the workgroup that finishes last adds up
+// what the others left; it replaces a launch.  With one wavefront per column and its loads not batched this took 10 us for
+// 2048 workgroups of 257 columns, and the scalars another 4 us.
+__global__ __launch_bounds__(kColumnsBlock) void k_dense_columns(int d, int grid, const double *__restrict__ partials, double *__restrict__ col_partials,
+                                                               const double *__restrict__ loss_partials, const double *__restrict__ active_partials,
+                                                               DenseFinish fin)
+{
+    constexpr int kWaves = kColumnsBlock / kWave, kAtOnce = 16, kRows = kColumnsBlock / kColumnsPer;
+    __shared__ double part[kWaves][kColumnsPer];
+    __shared__ double red[4][kWaves];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    for (int c = wv; c < d; c += kFinishWaves) {
-        const double *p = partials + (int64_t)c * grid;
-        double s = 0.0;
-        for (int b0 = 0; b0 < grid; b0 += 16 * kWave) {
-            double t[16];
+    const int c = blockIdx.x * kColumnsPer + lane % kColumnsPer;
+    double s = 0.0;
+    for (int b0 = threadIdx.x / kColumnsPer; b0 < grid; b0 += kAtOnce * kRows) {
+        double t[kAtOnce];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int b = b0 + k * kWave + lane;
-                t[k] = (b < grid) ? p[b] : 0.0;
-            }
+        for (int k = 0; k < kAtOnce; ++k) {
+            const int b = b0 + k * kRows;
+            t[k] = (b < grid && c < d) ? partials[(int64_t)b * d + c] : 0.0;
+        }
 #pragma unroll
-            for (int k = 0; k < 16; ++k) s += t[k];
-        }
-        s = wave_sum(s);
-        if (lane == 0) {
-            const double o = fma(C, s, add ? add[c] : 1.0);
-            if (out) out[c] = o;
-            colprod[c] = o * (dotw ? dotw[c] : o);
-        }
+        for (int k = 0; k < kAtOnce; ++k) s += t[k];
     }
-    double a = 0.0, e = 0.0, ww = 0.0;
-    for (int i = threadIdx.x; i < nloss; i += kFinishWaves * kWave) {
-        a += loss_partials[i];
-        e += active_partials[i];
-    }
-    if (w && threadIdx.x < d) ww = w[threadIdx.x] * w[threadIdx.x];
+    s = add_halves(add_row_pairs(s));   // the four rows of a load
+    if (lane < kColumnsPer) part[wv][lane] = s;
     __syncthreads();
-    double cp = (threadIdx.x < d) ? colprod[threadIdx.x] : 0.0;   // d <= 64: all in wavefront 0
-    a = wave_sum(a); e = wave_sum(e); ww = wave_sum(ww); cp = wave_sum(cp);
-    if (lane == 0) { red[0][wv] = a; red[1][wv] = e; red[2][wv] = ww; red[3][wv] = cp; }
+    if (wv == 0) {   // the outputs of the 16 columns, and what they add to the scalars
+        double cp = 0.0, ww = 0.0;
+        if (lane < kColumnsPer && c < d) {
+            double t = 0.0;
+#pragma unroll
+            for (int k = 0; k < kWaves; ++k) t += part[k][lane];
+            const double add = fin.add ? fin.add[c] : 1.0;
+            const double o = fma(fin.C, t, add);
+            cp = o * (fin.dotw ? fin.dotw[c] : o);
+            ww = add * add;
+            if (fin.out) fin.out[c] = o;
+        }
+        cp = wave_sum(cp);
+        ww = wave_sum(ww);
+        if (fin.scal && lane == 0) {
+            store_shared(col_partials + 2 * blockIdx.x, cp);
+            store_shared(col_partials + 2 * blockIdx.x + 1, ww);
+        }
+    }
+    if (!fin.scal || !last_workgroup(fin.ticket)) return;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};   // loss, w.w, sum of the column products, active rows
+    if (fin.fun_grad)
+        for (int b = threadIdx.x; b < grid; b += kColumnsBlock) {
+            v[0] += loss_partials[b];
+            v[3] += active_partials[b];
+        }
+    if (threadIdx.x < gridDim.x) {
+        v[2] = load_shared(col_partials + 2 * threadIdx.x);
+        v[1] = load_shared(col_partials + 2 * threadIdx.x + 1);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = wave_sum(v[k]);
+        if (lane == 0) red[k][wv] = v[k];
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double ta = 0.0, te = 0.0, tw = 0.0, tc = 0.0;
-#pragma unroll
-        for (int k = 0; k < kFinishWaves; ++k) { ta += red[0][k]; te += red[1][k]; tw += red[2][k]; tc += red[3][k]; }
-        if (nloss > 0) {
-            scal[0] = ta;
-            scal[1] = tw;
-            scal[2] = tc;
-            scal[3] = te;
-        } else {
-            scal[0] = tc;
-            scal_copy[0] = tc;   // p.Hp: the CG step kernel continues from it
-        }
+        double t[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int k = 0; k < 4; ++k)
+            for (int m = 0; m < kWaves; ++m) t[k] += red[k][m];
+        store_dense_scalars(fin, t[0], t[1], t[2], t[3]);
+        *fin.ticket = 0u;
     }
 }
 
@@ -319,7 +457,7 @@ HvInput hv_input(const tron_dataset *ds, int Dslot)
 }
 
 template <int E, int L>
-int launch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *partials)
+int launch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *partials, const DenseFinish &fin)
 {
     constexpr int U = pick_U(E, L);
     const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
@@ -327,7 +465,7 @@ int launch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *part
     const void *D = in.D;
     const bool mask = in.mask, skip = in.skip;
 #define TRON_HV(V, M, G, S) \
-    hipLaunchKernelGGL((k_dense_hv<E, L, U, V, M, G, S>), dim3(grid), dim3(kBlock), 0, ds->stream, in.n, ds->d, in.X, D, v, partials)
+    hipLaunchKernelGGL((k_dense_hv<E, L, U, V, M, G, S>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, in.n, ds->d, in.X, D, v, partials, fin)
 #define TRON_HV_V(M, G, S) do { if (vec) TRON_HV((E % 2 == 0), M, G, S); else TRON_HV(false, M, G, S); } while (0)
     if (v) {
         if (!mask) TRON_HV_V(false, false, false);
@@ -344,13 +482,13 @@ int launch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *part
 }
 
 template <int E, int L>
-int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *loss_partials, double *active_partials)
+int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *loss_partials, double *active_partials, const DenseFinish &fin)
 {
     constexpr int U = pick_U(E, L);
     const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
     const int grid = ds->dense_grid;
 #define TRON_FG(V, LS) \
-    hipLaunchKernelGGL((k_dense_fun_grad<E, L, U, V, LS>), dim3(grid), dim3(kBlock), 0, ds->stream, ds->n, ds->d, ds->X, ds->y8, w, Dout, ds->partials, loss_partials, active_partials)
+    hipLaunchKernelGGL((k_dense_fun_grad<E, L, U, V, LS>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, ds->X, ds->y8, w, Dout, ds->partials, loss_partials, active_partials, fin)
     if (loss == TRON_LOSS_LR) {
         if (vec) TRON_FG((E % 2 == 0), TRON_LOSS_LR); else TRON_FG(false, TRON_LOSS_LR);
     } else {
@@ -358,6 +496,28 @@ int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *l
     }
 #undef TRON_FG
     return TRON_OK;
+}
+
+template <int E, int L>
+int launch_round(tron_dataset *ds, const SolveParams &P, const RoundArgs &A, int64_t stamp)
+{
+    if constexpr (dense_finishes(L)) {
+        constexpr int U = pick_U(E, L);
+        const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
+#define TRON_ROUND(V, LS) \
+    hipLaunchKernelGGL((k_dense_round<E, L, U, V, LS>), dim3(ds->dense_grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp)
+        if (P.loss == TRON_LOSS_LR) {
+            if (vec) TRON_ROUND((E % 2 == 0), TRON_LOSS_LR); else TRON_ROUND(false, TRON_LOSS_LR);
+        } else {
+            if (vec) TRON_ROUND((E % 2 == 0), TRON_LOSS_L2SVM); else TRON_ROUND(false, TRON_LOSS_L2SVM);
+        }
+#undef TRON_ROUND
+        TRON_HIP(hipGetLastError());
+        return TRON_OK;
+    } else {
+        set_error("internal: a solve driven from the device needs d <= %d", kFinishMaxD);
+        return TRON_EINVAL;
+    }
 }
 
 // E in 1..8 for L = 1, E in 5..8 for L >= 2 (smaller d picks a smaller L)
@@ -394,8 +554,20 @@ int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *l
     set_error("internal: no dense kernel for E=%d L=%d", s.E, s.L);              \
     return TRON_EINVAL;
 
-int dispatch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *partials) { TRON_DISPATCH(launch_hv, ds, in, v, partials) }
-int dispatch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *lp, double *ap) { TRON_DISPATCH(launch_fg, ds, loss, w, Dout, lp, ap) }
+int dispatch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *partials, const DenseFinish &fin) { TRON_DISPATCH(launch_hv, ds, in, v, partials, fin) }
+int dispatch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *lp, double *ap, const DenseFinish &fin) { TRON_DISPATCH(launch_fg, ds, loss, w, Dout, lp, ap, fin) }
+int dispatch_round(tron_dataset *ds, const SolveParams &P, const RoundArgs &A, int64_t stamp) { TRON_DISPATCH(launch_round, ds, P, A, stamp) }
+
+// the second stage of a wide matrix; the others have completed it in the pass
+int launch_columns(tron_dataset *ds, int grid, const double *partials, double *col_partials, const double *loss_partials, const double *active_partials,
+                   const DenseFinish &fin)
+{
+    if (ds->d <= kFinishMaxD) return TRON_OK;
+    hipLaunchKernelGGL(k_dense_columns, dim3((unsigned)((ds->d + kColumnsPer - 1) / kColumnsPer)), dim3(kColumnsBlock), 0, ds->stream, (int)ds->d, grid,
+                       partials, col_partials, loss_partials, active_partials, fin);
+    TRON_HIP(hipGetLastError());
+    return TRON_OK;
+}
 
 }  // namespace
 
@@ -588,9 +760,9 @@ int dense_compact_build(tron_dataset *ds, int Dslot)
     if (g > kMaxGrid) g = kMaxGrid;
     const uint64_t inv_d = ((1ull << 32) + (uint64_t)ds->d - 1) / (uint64_t)ds->d;
     if (ds->d % 2 == 0)
-        hipLaunchKernelGGL(k_compact_rows<true>, dim3((int)g), dim3(kBlock), 0, ds->stream, ds->n, (int)ds->d, inv_d, ds->X, bits, ds->tile_off, ds->Xhat);
+        hipLaunchKernelGGL(k_compact_rows<true>, dim3((int)g), dim3(kBlock), 0, ds->stream, ds->n, ds->d, inv_d, ds->X, bits, ds->tile_off, ds->Xhat);
     else
-        hipLaunchKernelGGL(k_compact_rows<false>, dim3((int)g), dim3(kBlock), 0, ds->stream, ds->n, (int)ds->d, inv_d, ds->X, bits, ds->tile_off, ds->Xhat);
+        hipLaunchKernelGGL(k_compact_rows<false>, dim3((int)g), dim3(kBlock), 0, ds->stream, ds->n, ds->d, inv_d, ds->X, bits, ds->tile_off, ds->Xhat);
     const int64_t words = (rows + kWave - 1) / kWave;
     int64_t gb = (words + kBlock - 1) / kBlock;
     if (gb < 1) gb = 1;
@@ -620,16 +792,21 @@ int dense_grid_for(int64_t n, int64_t d)
 {
     Shape s;
     if (!pick_shape(d, s)) return 1;
-    const int U = pick_U(s.E, s.L);
-    const int64_t RT = (int64_t)U * (kWave / s.L);
-    const int64_t tiles = (n + RT - 1) / RT;
-    int64_t g = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (g < 1) g = 1;
-    if (g > kMaxGrid) g = kMaxGrid;
-    return (int)g;
+    const int64_t rows = (int64_t)pick_U(s.E, s.L) * (kWave / s.L) * (dense_block(s.L) / kWave);
+    const int64_t g = (n + rows - 1) / rows, most = dense_finishes(s.L) ? kFinishGrid : kWideGrid;
+    return (int)(g < most ? g : most);
 }
 
-// column partials (d * grid) followed by loss partials (grid), column products (d) and active-row counts (grid)
+int dense_work_units(int64_t n, int64_t d)
+{
+    Shape s;
+    if (!pick_shape(d, s)) return 1;
+    const int64_t rows = (int64_t)pick_U(s.E, s.L) * (kWave / s.L) * kWavesPerBlock;
+    const int64_t g = (n + rows - 1) / rows;
+    return (int)(g > kMaxGrid ? kMaxGrid : g);
+}
+
+// column sums (grid * d) followed by loss partials (grid), the column workgroups' sums (d) and active-row counts (grid)
 int64_t dense_partials_needed(int64_t n, int64_t d)
 {
     const int64_t g = dense_grid_for(n, d);
@@ -639,44 +816,37 @@ int64_t dense_partials_needed(int64_t n, int64_t d)
 int dense_hv(tron_dataset *ds, double C, int Dslot, const double *v, double *Hv)
 {
     const HvInput in = hv_input(ds, Dslot);
-    const int grid = in.grid;
-    double *colprod = ds->partials + ds->d * ds->dense_grid + ds->dense_grid;
+    const DenseFinish fin{ds->ticket, v, C, Hv, v, ds->scal_dev, ds->scal_copy, false};
     {
         ProfScope ps(ds, SLOT_DENSE_HV);
-        TRON_TRY(dispatch_hv(ds, in, v, ds->partials));
+        TRON_TRY(dispatch_hv(ds, in, v, ds->partials, fin));
         TRON_HIP(hipGetLastError());
     }
     ProfScope ps(ds, SLOT_DENSE_FINALIZE);
-    if (ds->d <= kFinishMaxD) {
-        hipLaunchKernelGGL(k_dense_finish, dim3(1), dim3(kFinishWaves * kWave), 0, ds->stream, ds->d, grid, ds->partials, v, C, Hv, v, 0,
-                           (const double *)nullptr, (const double *)nullptr, (const double *)nullptr, ds->scal_dev, ds->scal_copy);
-    } else {
-        const int cg = (int)((ds->d + kWavesPerBlock - 1) / kWavesPerBlock);
-        hipLaunchKernelGGL(k_dense_columns, dim3(cg), dim3(kBlock), 0, ds->stream, ds->d, grid, ds->partials, v, C, Hv, v, colprod);
-        hipLaunchKernelGGL(k_dense_scalars, dim3(1), dim3(kBlock), 0, ds->stream, ds->d, 0, (const double *)nullptr,
-                           (const double *)nullptr, (const double *)nullptr, colprod, ds->scal_dev, ds->scal_copy);
-    }
-    TRON_HIP(hipGetLastError());
-    return TRON_OK;
+    return launch_columns(ds, in.grid, ds->partials, ds->partials + (ds->d + 1) * ds->dense_grid, nullptr, nullptr, fin);
 }
 
 // out = 1 + C diag(X^T D X): the same pass as dense_hv with squared entries
 int dense_hess_diag(tron_dataset *ds, double C, int Dslot, double *out)
 {
     const HvInput in = hv_input(ds, Dslot);
-    const int grid = in.grid;
-    double *colprod = ds->partials + ds->d * ds->dense_grid + ds->dense_grid;
+    const DenseFinish fin{ds->ticket, nullptr, C, out, nullptr, nullptr, nullptr, false};
     {
         ProfScope ps(ds, SLOT_DENSE_HV);
-        TRON_TRY(dispatch_hv(ds, in, nullptr, ds->partials));
+        TRON_TRY(dispatch_hv(ds, in, nullptr, ds->partials, fin));
         TRON_HIP(hipGetLastError());
     }
     ProfScope ps(ds, SLOT_DENSE_FINALIZE);
-    const int cg = (int)((ds->d + kWavesPerBlock - 1) / kWavesPerBlock);
-    hipLaunchKernelGGL(k_dense_columns, dim3(cg), dim3(kBlock), 0, ds->stream, ds->d, grid, ds->partials, (const double *)nullptr, C,
-                       out, (const double *)nullptr, colprod);
-    TRON_HIP(hipGetLastError());
-    return TRON_OK;
+    return launch_columns(ds, in.grid, ds->partials, ds->partials + (ds->d + 1) * ds->dense_grid, nullptr, nullptr, fin);
+}
+
+int dense_round(tron_dataset *ds, const SolveParams &P, DriverState &drv, int64_t stamp)
+{
+    double *loss_partials = ds->partials + ds->d * ds->dense_grid;
+    const RoundArgs A{ds->X, ds->y8, {ds->Dbuf[0], ds->Dbuf[1]}, ds->partials, loss_partials, loss_partials + ds->dense_grid + ds->d,
+                      ds->ticket, drv.ctl, drv.st, P.trace_cap > 0 ? drv.trace_dev : nullptr, drv.host_dev};
+    ProfScope ps(ds, SLOT_BATCH_PASS);
+    return dispatch_round(ds, P, A, stamp);
 }
 
 int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Dslot, double *g)
@@ -686,32 +856,22 @@ int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Ds
     ds->D_is_mask[Dslot] = (loss == TRON_LOSS_L2SVM);
     const int grid = ds->dense_grid;
     double *loss_partials = ds->partials + ds->d * grid;
-    double *colprod = loss_partials + grid;
-    double *active_partials = colprod + ds->d;
+    double *col_partials = loss_partials + grid;
+    double *active_partials = col_partials + ds->d;
+    const DenseFinish fin{ds->ticket, w, C, g, nullptr, ds->scal_dev, ds->scal_copy, true};
     {
         ProfScope ps(ds, SLOT_DENSE_FUN_GRAD);
-        TRON_TRY(dispatch_fg(ds, loss, w, Dout, loss_partials, active_partials));
+        TRON_TRY(dispatch_fg(ds, loss, w, Dout, loss_partials, active_partials, fin));
         TRON_HIP(hipGetLastError());
     }
     ProfScope ps(ds, SLOT_DENSE_FINALIZE);
-    if (ds->d <= kFinishMaxD) {
-        hipLaunchKernelGGL(k_dense_finish, dim3(1), dim3(kFinishWaves * kWave), 0, ds->stream, ds->d, grid, ds->partials, w, C, g,
-                           (const double *)nullptr, grid, loss_partials, active_partials, w, ds->scal_dev, ds->scal_copy);
-    } else {
-        const int cg = (int)((ds->d + kWavesPerBlock - 1) / kWavesPerBlock);
-        hipLaunchKernelGGL(k_dense_columns, dim3(cg), dim3(kBlock), 0, ds->stream, ds->d, grid, ds->partials, w, C, g,
-                           (const double *)nullptr, colprod);
-        hipLaunchKernelGGL(k_dense_scalars, dim3(1), dim3(kBlock), 0, ds->stream, ds->d, grid, loss_partials, active_partials, w, colprod,
-                           ds->scal_dev, ds->scal_copy);
-    }
-    TRON_HIP(hipGetLastError());
-    return TRON_OK;
+    return launch_columns(ds, grid, ds->partials, col_partials, loss_partials, active_partials, fin);
 }
 
 }  // namespace tron
 
 // ------------------------------------------------------------------ Hessian-vector product without any allocation
-// The work space of the dense Hessian-vector product -- per-workgroup column sums (d * grid), the d column products
+// The work space of the dense Hessian-vector product -- per-workgroup column sums (d * grid), the column workgroups' sums (d)
 // and the curvature scalar -- in a file-scope device array instead of the handle's allocation.  Every GPU the
 // library runs on holds its own copy of the array, at its own address, until the process ends.
 namespace {
@@ -733,10 +893,13 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
     const int Dslot = ds->Dcur;
     const HvInput in = hv_input(ds, Dslot);
     const int grid = in.grid;
-    const int64_t need = ds->d * grid + ds->d + 1;
+    // The limit is stated in groups of four wave tiles (dense_work_units); the sums of the workgroups that are launched, at most
+    // 256 for d <= 32 and 512 otherwise, and never more than those groups, fit wherever it holds.
+    const int units = dense_work_units(in.n, ds->d);
+    const int64_t need = ds->d * units + ds->d + 1;
     if (need > kStaticScratchDoubles) {
         set_error("tron_hv_static: n = %lld, d = %lld needs %lld doubles of work space (d * %d workgroups + d + 1); the static "
-                  "work space holds %lld: use tron_hv", (long long)ds->n, (long long)ds->d, (long long)need, grid,
+                  "work space holds %lld: use tron_hv", (long long)ds->n, (long long)ds->d, (long long)need, units,
                   (long long)kStaticScratchDoubles);
         return TRON_EINVAL;
     }
@@ -757,18 +920,10 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
     double *partials = g_scratch_ptr[dev];
     double *colprod = partials + ds->d * grid;
     double *scalar = colprod + ds->d;
-    // Nothing has to start at zero: every workgroup of the pass writes all d of its column sums, the second stage
-    // writes all d column products, the third the scalar.
-    TRON_TRY(dispatch_hv(ds, in, v_dev, partials));
-    if (ds->d <= kFinishMaxD) {
-        hipLaunchKernelGGL(k_dense_finish, dim3(1), dim3(kFinishWaves * kWave), 0, ds->stream, ds->d, grid, partials, v_dev, C, Hv_dev, v_dev, 0,
-                           (const double *)nullptr, (const double *)nullptr, (const double *)nullptr, vHv_dev ? vHv_dev : scalar, scalar);
-    } else {
-        const int cg = (int)((ds->d + kWavesPerBlock - 1) / kWavesPerBlock);
-        hipLaunchKernelGGL(k_dense_columns, dim3(cg), dim3(kBlock), 0, ds->stream, ds->d, grid, partials, v_dev, C, Hv_dev, v_dev, colprod);
-        hipLaunchKernelGGL(k_dense_scalars, dim3(1), dim3(kBlock), 0, ds->stream, ds->d, 0, (const double *)nullptr,
-                           (const double *)nullptr, (const double *)nullptr, colprod, vHv_dev ? vHv_dev : scalar, scalar);
-    }
+    // Nothing has to start at zero: every workgroup of the pass writes all d of its column sums, the second stage the rest.
+    // The counter of finished workgroups is the handle's own.
+    const DenseFinish fin{ds->ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false};
+    TRON_TRY(dispatch_hv(ds, in, v_dev, partials, fin));
     TRON_HIP(hipGetLastError());
-    return TRON_OK;
+    return launch_columns(ds, grid, partials, colprod, nullptr, nullptr, fin);
 }

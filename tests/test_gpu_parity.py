@@ -580,6 +580,35 @@ def test_solve_dense_lr_tight(rng, dense_driver):
     compare_solves(p, LOSS_L2SVM, 0.5, 1e-6)
 
 
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("n,d", [(1, 3), (63, 1), (65, 2), (513, 8), (4097, 9), (511, 16), (4095, 17), (131_137, 25), (70_001, 32)])
+def test_dense_solve_then_calls_at_tile_and_workgroup_edges(rng, dense_driver, loss, n, d):
+    """A tile has 64 rows, a workgroup eight tiles, a launch at most 256 workgroups; one to four lanes per row.  A solve from
+    w = 0 and one from elsewhere on the same handle, then the calls that continue from the D the solve left."""
+    import paper_2008_03433_amd as tron
+    from oracle import Oracle
+    torch = torch_mod()
+    p = _dense(rng, n, d)
+    compare_solves(p, loss, 0.3, 1e-3)
+    compare_solves(p, loss, 0.3, 1e-3, w0=0.3 * rng.standard_normal(d))
+    ds = tron.Dataset.from_problem(p)
+    try:
+        w = torch.zeros(d, dtype=torch.float64, device="cuda")
+        for _ in range(2):   # the second from the solution of the first
+            r = ds.solve(loss, 0.3, 1e-3, w)
+        assert r.outer_iters == 0 and r.converged
+        o = Oracle.from_problem(p)
+        f, _, D = o.fun_grad(loss, 0.3, w.cpu().numpy())
+        assert abs(r.f - f) <= 1e-10 * abs(f)
+        v = dev(rng.standard_normal(d))
+        Hv = torch.empty_like(v)
+        ds.hv(0.3, v, Hv)
+        want = o.hv(0.3, D, v.cpu().numpy())
+        assert np.linalg.norm(Hv.cpu().numpy() - want) <= 1e-10 * np.linalg.norm(want)
+    finally:
+        ds.close()
+
+
 def test_solve_hits_trust_region_boundary(rng):
     # far-away start with saturated sigmoids: the quadratic model is poor, steps get rejected, the
     # radius shrinks and CG ends on the boundary (H >= I means the very first step from Delta_0 = |g|
