@@ -5,8 +5,8 @@
 // Work is split by nonzeros, not by rows, because row lengths are heavily skewed (Zipf-distributed
 // features give the transposed copy rows of length ~n next to millions of length 0/1): a workgroup
 // streams one chunk of kChunk nonzeros with 16-byte non-temporal loads that cover whole cache lines,
-// multiplies them by the gathered vector entries and parks the products in LDS; the sums of the row
-// pieces ("segments") of the chunk come out of a segmented scan (see chunk_runs).  Rows and segments that fit
+// multiplies them by the gathered vector entries; the sums of the row
+// pieces ("segments") of the chunk come out of a segmented scan (see runs_from_regs).  Rows and segments that fit
 // into a chunk are stored so that they never cross a chunk boundary; one longer than a chunk receives the rest
 // from the `carry` of the following chunks in a small fix-up kernel, in a fixed order -- nothing is ever added in
 // an order that depends on timing, so results are bit-reproducible (the one atomic instruction in use, the LDS
@@ -133,6 +133,12 @@ static void parallel_ranges(int64_t n, F &&fn)
     for (unsigned t = 1 + started; t < T; ++t) fn(std::min<int64_t>(n, (int64_t)t * per), std::min<int64_t>(n, (int64_t)(t + 1) * per));
     for (std::thread &w : workers) w.join();
 }
+
+// Where entry e of a chunk is stored.  Thread t of a kernel owns entries 8t .. 8t+7 of a chunk, and its loads cover whole
+// cache lines: the columns come as two pieces of four (16 bytes), the values as four pieces of two, piece m of all threads
+// together.  The 16-bit slots of a head partition or a tile are 16 bytes per thread and stay in order.
+static inline int64_t col_pos(int64_t q) { const int64_t e = q % kChunk; return q - e + (e / 4 % 2) * (kChunk / 2) + e / 8 * 4 + e % 4; }
+static inline int64_t val_pos(int64_t q) { const int64_t e = q % kChunk; return q - e + (e / 2 % 4) * (kChunk / 4) + e / 8 * 2 + e % 2; }
 
 int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowptr, const int32_t *h_col,
                    const double *h_val, int parts, bool hot, bool unit, hipStream_t st)
@@ -353,8 +359,8 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
                         continue;
                     }
                     const int64_t q = cursor[x]++;
-                    pcol[q] = slot1 ? ~(slot1 - 1) : h_col[k];   // the head's become 16-bit slots below
-                    if (!A.unit) pval[q] = h_val[k];
+                    pcol[x < P ? col_pos(q) : q] = slot1 ? ~(slot1 - 1) : h_col[k];   // the head's become 16-bit slots below
+                    if (!A.unit) pval[val_pos(q)] = h_val[k];
                 }
             }
         });
@@ -714,92 +720,69 @@ struct PartArgs {
 // chunk is being reduced, so HBM latency is paid once per workgroup, not once per chunk.
 // With HOT the partition's most frequent columns are first copied from x into an LDS table; entries of those
 // columns are stored as ~slot and never touch the vector cache.
-// Stream registers of one chunk: thread t holds entries m*512 + 2t, m*512 + 2t + 1 (m = 0..3), so that every load
-// instruction of a wavefront covers whole consecutive cache lines (a wavefront that reads 16 of every 32 bytes is
-// served in 64-byte requests, twice as many, and the number of requests a CU keeps in flight is what bounds it).
+// Stream registers of one chunk: thread t holds its own entries 8t .. 8t+7 (see col_pos / val_pos).  Every load instruction of
+// a wavefront covers whole consecutive cache lines: one that reads 16 of every 32 bytes is served in 64-byte requests, twice
+// as many, and the number of requests a CU keeps in flight is what bounds it.
 constexpr int kQuarter = kChunk / 4;
 
-template <bool HEAD>
-struct StreamRegs {
-    v2i c[4];
-    v2d v[4];
-};
-template <>
-struct StreamRegs<true> {
-    uint32_t c[4];   // two 16-bit LDS slots each
-    v2d v[4];
-};
-
-// UNIT: the entries carry no values (see CsrPlan::unit); v stays unset and unused
 template <bool HEAD, bool UNIT>
-__device__ __forceinline__ StreamRegs<HEAD> load_stream(const void *__restrict__ col, const double *__restrict__ val, int64_t start)
-{
-    StreamRegs<HEAD> s;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const int64_t k = start + m * kQuarter + threadIdx.x * 2;
-        if constexpr (HEAD)
-            s.c[m] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(static_cast<const uint16_t *>(col) + k));
-        else
-            s.c[m] = __builtin_nontemporal_load(reinterpret_cast<const v2i *>(static_cast<const int32_t *>(col) + k));
-        if constexpr (!UNIT) s.v[m] = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(val + k));
-    }
-    return s;
-}
+struct StreamRegs {
+    v4i c[HEAD ? 1 : 2];        // HEAD: eight 16-bit LDS slots
+    v2d v[UNIT ? 1 : 4];        // UNIT: the entries carry no values (see CsrPlan::unit)
+};
 
-// the two gathered vector entries of quarter m
-template <bool HOT, bool HEAD>
-__device__ __forceinline__ void gather2(const StreamRegs<HEAD> &r, int m, const double *__restrict__ x, const double *table, double *out)
+template <bool HEAD, bool UNIT>
+__device__ __forceinline__ void load_stream(StreamRegs<HEAD, UNIT> &s, const void *__restrict__ col, const double *__restrict__ val, int64_t start)
 {
     if constexpr (HEAD) {
-        out[0] = table[r.c[m] & 0xffffu];
-        out[1] = table[r.c[m] >> 16];
+        s.c[0] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(static_cast<const uint16_t *>(col) + start + threadIdx.x * 8));
     } else {
-        out[0] = gather<HOT>(x, table, r.c[m].x);
-        out[1] = gather<HOT>(x, table, r.c[m].y);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            s.c[m] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(static_cast<const int32_t *>(col) + start + m * (kChunk / 2) + threadIdx.x * 4));
+    }
+    if constexpr (!UNIT) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) s.v[m] = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(val + start + m * kQuarter + threadIdx.x * 2));
+    }
+}
+
+// the products of the thread's eight entries
+template <bool HOT, bool HEAD, bool SQ, bool UNIT>
+__device__ __forceinline__ void products(const StreamRegs<HEAD, UNIT> &r, const double *__restrict__ x, const double *table, double (&p)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if constexpr (HEAD) {
+            const unsigned two = (unsigned)r.c[0][e / 2];
+            p[e] = table[e % 2 ? two >> 16 : two & 0xffffu];
+        } else {
+            p[e] = gather<HOT>(x, table, r.c[e / 4][e % 4]);
+        }
+    }
+    if constexpr (!UNIT) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double v = r.v[e / 2][e % 2];
+            p[e] *= SQ ? v * v : v;
+        }
     }
 }
 
 // ------------------------------------------------------------------ segment sums of a chunk
 // The entries of a chunk are in segment order (a segment = the entries of one row inside the chunk) and a flag bit
-// marks the last entry of every segment.  Products are written to LDS in load order and read back so that thread
-// t owns entries 8t .. 8t+7; the thread sums its own runs in registers, the open run at its end is carried to the
-// following threads by a segmented scan over the wavefront (DPP) and across the four wavefronts through LDS.
-// No loop depends on how long the segments are.
-//
-// LDS layout of the products: blocks of 8 entries padded to 10 doubles, so that the 128-bit reads of a wavefront
-// (80-byte lane stride) fall into distinct banks; the padding of the first four blocks holds the wavefront totals.
-constexpr int kProdDoubles = kChunk / 8 * 10;   // 2560 doubles = 20 KiB
-constexpr int kOutOffset = 40;                  // segment sums are parked at prod[kOutOffset ...] (behind the totals)
+// marks the last entry of every segment.  Thread t owns entries 8t .. 8t+7: it sums its own runs in registers, the open run
+// at its end is carried to the following threads by a segmented scan over the wavefront (DPP) and across the four
+// wavefronts through LDS.  No loop depends on how long the segments are.  (With the entries stored in order the products were
+// passed through LDS, from load order to thread order: a barrier more and, 500,000 x 750,000 with values, 52.6 instead of 47.6 us
+// in the tiles, 45.7 / 43.8 in the head partition, 45.1 / 42.9 and 41.7 / 40.3 in the ranges.)
+constexpr int kOutOffset = 16;                  // segment sums are parked at prod[kOutOffset ...] (behind the wavefront totals)
 constexpr int kSegPasses = kChunk / kBlock;     // a chunk holds at most kChunk segments: 8 passes of 256
+constexpr int kProdDoubles = kOutOffset + kChunk;
 
-__device__ __forceinline__ int prod_pos(int e) { return e + 2 * (e >> 3); }
-
-// products of the chunk in `r` into LDS
-template <bool HOT, bool HEAD, bool SQ, bool UNIT>
-__device__ __forceinline__ void products_to_lds(const StreamRegs<HEAD> &r, const double *__restrict__ x, const double *table, double *prod)
-{
-    double xg[4][2];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) gather2<HOT, HEAD>(r, m, x, table, xg[m]);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        double2 p;
-        if constexpr (UNIT) {
-            p.x = xg[m][0];
-            p.y = xg[m][1];
-        } else {
-            p.x = (SQ ? r.v[m].x * r.v[m].x : r.v[m].x) * xg[m][0];
-            p.y = (SQ ? r.v[m].y * r.v[m].y : r.v[m].y) * xg[m][1];
-        }
-        *reinterpret_cast<double2 *>(prod + prod_pos(m * kQuarter + threadIdx.x * 2)) = p;   // an even entry: the pair stays together
-    }
-}
-
-// Call after the barrier that follows the product writes.  f = the thread's 8 flag bits.
-// p[e] in: the product of entry 8 * tid + e.  On return p[e] = sum of the thread's entries from the start of the run
+// f = the thread's 8 flag bits.  p[e] in: the product of entry 8 * tid + e.  On return p[e] = sum of the thread's entries from the start of the run
 // containing e up to e, cin = what the entries before the thread add to its first run, idx0 = number of flags in the
-// threads before it.  Uses prod[8..39] for the wavefront totals; contains one barrier.
+// threads before it.  Uses prod[0..7] for the wavefront totals; contains one barrier.
 __device__ __forceinline__ void runs_from_regs(double *prod, const unsigned f, double (&p)[8], double &cin, int &idx0)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -820,8 +803,8 @@ __device__ __forceinline__ void runs_from_regs(double *prod, const unsigned f, d
     const double ext = lane_before(t);
     const int exh = lane_before(h);
     if (lane == kWave - 1) {
-        prod[10 * wv + 8] = t;
-        *reinterpret_cast<int2 *>(prod + 10 * wv + 9) = make_int2(h, ci);
+        prod[2 * wv] = t;
+        *reinterpret_cast<int2 *>(prod + 2 * wv + 1) = make_int2(h, ci);
     }
     __syncthreads();
     double ct = 0.0;
@@ -829,8 +812,8 @@ __device__ __forceinline__ void runs_from_regs(double *prod, const unsigned f, d
 #pragma unroll
     for (int w = 0; w < kWavesPerBlock - 1; ++w) {
         if (w < wv) {
-            const double wt = prod[10 * w + 8];
-            const int2 hc = *reinterpret_cast<const int2 *>(prod + 10 * w + 9);
+            const double wt = prod[2 * w];
+            const int2 hc = *reinterpret_cast<const int2 *>(prod + 2 * w + 1);
             ct = hc.x ? wt : ct + wt;
             cb += hc.y;
         }
@@ -839,44 +822,22 @@ __device__ __forceinline__ void runs_from_regs(double *prod, const unsigned f, d
     idx0 = cb + ci - cnt;
 }
 
-// The same with the products taken from LDS (call after the barrier that follows the product writes).  After the barrier
-// inside, the product area may be overwritten (the totals at prod[8..39] may not).
-__device__ __forceinline__ void chunk_runs(double *prod, const unsigned f, double (&p)[8], double &cin, int &idx0)
-{
-    const double2 *src = reinterpret_cast<const double2 *>(prod + 10 * threadIdx.x);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double2 d = src[q];
-        p[2 * q] = d.x;
-        p[2 * q + 1] = d.y;
-    }
-    runs_from_regs(prod, f, p, cin, idx0);
-}
-
 // flag byte of the calling thread: bit e = entry 8*tid + e is the last of its segment
 __device__ __forceinline__ unsigned load_flags(const uint8_t *__restrict__ flags /* of this chunk */)
 {
     return flags[threadIdx.x];
 }
 
-// Segment sums of the chunk whose products are in LDS: the sums of the owned segments go to out[0 .. nseg) in segment
-// order (one coalesced store per 64 segments; the partial sums of a plan are stored segment by segment, not by row:
-// see sum_parts), the piece of a row that started in an earlier chunk to *carry_slot.  Three barriers; the caller
+// Segment sums of the chunk whose products are p (the thread's eight): the sums of the owned segments go to out[0 .. nseg) in
+// segment order (one coalesced store per 64 segments; the partial sums of a plan are stored segment by segment, not by row:
+// see sum_parts), the piece of a row that started in an earlier chunk to *carry_slot.  Two barriers; the caller
 // adds one before it reuses `prod`.
-// FROM_REGS: p holds the products of the thread's own 8 entries (nothing is read from the product area)
-template <bool FROM_REGS = false>
 __device__ __forceinline__ void chunk_segments(double *prod, const unsigned flags, const int nseg, const bool continued,
-                                               double *__restrict__ out, double *__restrict__ carry_slot, double *regs = nullptr)
+                                               double *__restrict__ out, double *__restrict__ carry_slot, double (&p)[8])
 {
-    double p[8], cin;
+    double cin;
     int idx0;
-    if constexpr (FROM_REGS) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = regs[e];
-        runs_from_regs(prod, flags, p, cin, idx0);
-    } else {
-        chunk_runs(prod, flags, p, cin, idx0);
-    }
+    runs_from_regs(prod, flags, p, cin, idx0);
     double *outv = prod + kOutOffset;
     int i = idx0 - (continued ? 1 : 0);
     bool first = true;
@@ -955,86 +916,31 @@ __device__ __forceinline__ void part_body(double *prod, double *table, const Par
     int c = q;
     int4 tab = load_uniform(tabs + c);
     int4 tab_n = load_uniform(tabs + ((c + Q < nchunks) ? c + Q : c));
-    StreamRegs<HEAD> cur = load_stream<HEAD, UNIT>(col, val, (int64_t)c * kChunk);
+    StreamRegs<HEAD, UNIT> cur;
+    load_stream(cur, col, val, (int64_t)c * kChunk);
     unsigned fl = load_flags(flags + (int64_t)c * kBlock);
 
     for (; c < nchunks; c += Q) {
-        products_to_lds<HOT, HEAD, SQ, UNIT>(cur, x, table, prod);
+        double p[8];
+        products<HOT, HEAD, SQ, UNIT>(cur, x, table, p);
         // Only now fetch the next chunk (clamped index: always the same loads): nothing below waits for these
         // registers, so they stay in flight during the segment sums and are waited for at the top of the next
         // iteration.
         __builtin_amdgcn_sched_barrier(0);
         const int cn = (c + Q < nchunks) ? c + Q : c;
         const int cnn = (cn + Q < nchunks) ? cn + Q : cn;
-        const StreamRegs<HEAD> nxt = load_stream<HEAD, UNIT>(col, val, (int64_t)cn * kChunk);
+        StreamRegs<HEAD, UNIT> nxt;
+        load_stream(nxt, col, val, (int64_t)cn * kChunk);
         const unsigned fl_n = load_flags(flags + (int64_t)cn * kBlock);
         const int4 tab_nn = load_uniform(tabs + cnn);
         __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        chunk_segments(prod, fl, tab.y, tab.z > 0, partial + tab.x, carry + c);
-        __syncthreads();  // prod is reused by the next chunk
-        cur = nxt;
-        fl = fl_n;
-        tab = tab_n;
-        tab_n = tab_nn;
-    }
-}
-
-// The head partition of a unit plan: an entry is a 16-bit slot of the LDS table and nothing else, so thread t loads the
-// slots of entries 8t .. 8t+7 with one 16-byte load and gathers their table values straight into the registers the
-// segment sums start from -- no trip of the products through LDS.
-__device__ __forceinline__ void head_unit_body(double *prod, double *table, const PartArgs &pa, const int q, const int Q,
-                                               const PartPtrs &pp)
-{
-    const int tid = threadIdx.x;
-    const int nchunks = pa.nchunks[0];
-    if (q >= nchunks) return;
-    {
-        const double2 *__restrict__ src = reinterpret_cast<const double2 *>(pp.hot_x);
-        for (int k = tid; k < pa.slots / 2; k += kBlock) reinterpret_cast<double2 *>(table)[k] = src[k];
-        __syncthreads();
-    }
-    const uint16_t *col = static_cast<const uint16_t *>(pp.col) + pa.base[0];
-    const int4 *__restrict__ tabs = pp.chunk_tab + pa.chunk0[0];
-    const uint8_t *__restrict__ flags = pp.flags + (int64_t)pa.chunk0[0] * kBlock;
-    double *partial = pp.partial + pa.seg0[0];
-    double *carry = pp.carry + pa.chunk0[0];
-    auto load8 = [&](int c) { return __builtin_nontemporal_load(reinterpret_cast<const v4i *>(col + (int64_t)c * kChunk + 8 * tid)); };
-
-    int c = q;
-    int4 tab = load_uniform(tabs + c);
-    int4 tab_n = load_uniform(tabs + ((c + Q < nchunks) ? c + Q : c));
-    v4i cur = load8(c);
-    unsigned fl = load_flags(flags + (int64_t)c * kBlock);
-    for (; c < nchunks; c += Q) {
-        double p[8];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const unsigned two = (unsigned)cur[m];
-            p[2 * m] = table[two & 0xffffu];
-            p[2 * m + 1] = table[two >> 16];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        const int cn = (c + Q < nchunks) ? c + Q : c;
-        const int cnn = (cn + Q < nchunks) ? cn + Q : cn;
-        const v4i nxt = load8(cn);
-        const unsigned fl_n = load_flags(flags + (int64_t)cn * kBlock);
-        const int4 tab_nn = load_uniform(tabs + cnn);
-        __builtin_amdgcn_sched_barrier(0);
-        chunk_segments<true>(prod, fl, tab.y, tab.z > 0, partial + tab.x, carry + c, p);
+        chunk_segments(prod, fl, tab.y, tab.z > 0, partial + tab.x, carry + c, p);
         __syncthreads();  // the totals and the parked sums are reused by the next chunk
         cur = nxt;
         fl = fl_n;
         tab = tab_n;
         tab_n = tab_nn;
     }
-}
-
-__global__ __launch_bounds__(kBlock) void k_csr_head_unit(PartArgs pa, PartPtrs pp)
-{
-    __shared__ __align__(16) double prod[kOutOffset + kChunk];
-    extern __shared__ __align__(16) double table[];   // pa.slots doubles
-    head_unit_body(prod, table, pa, blockIdx.x, gridDim.x, pp);
 }
 
 // Head partition of a unit plan stored as sorted slices (see SellHead).  A wavefront reads its own contiguous stream of
@@ -1145,11 +1051,11 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
         }
         int4 h = make_int4((int)base[s], 0, 0, (int)sslot[s].size());
         const size_t off = tiloc[s].size();
-        if (!unit) tval[s].resize(off + kChunk, 0.0);
+        if (!unit) tval[s].resize(off + kChunk, 0.0);   // off: a multiple of kChunk
         tiloc[s].resize(off + kChunk, 0);
         tflags[s].resize((off + kChunk) / 8, 0);
         for (size_t k = 0; k < e.size(); ++k) {
-            if (!unit) tval[s][off + k] = e[k].val;
+            if (!unit) tval[s][val_pos(off + k)] = e[k].val;
             tiloc[s][off + k] = e[k].iloc;
             if (k + 1 == e.size() || e[k + 1].slot != e[k].slot) {
                 tflags[s][(off + k) / 8] |= (uint8_t)(1u << (k % 8));
@@ -1272,15 +1178,6 @@ struct TileArgs {
     int64_t ntiles[kTileSlices];
 };
 
-struct TileRegs {
-    v2d v[4];
-    uint32_t il[4];     // two 16-bit local column offsets each
-    uint4 slots;        // slots of the segments 8*tid .. 8*tid+7 (16 bits each)
-    unsigned flags;     // bit e: entry 8*tid + e is the last of its segment
-    double w[2];        // the two columns of the tile that the thread copies into LDS
-    int4 hdr;
-};
-
 struct TilePtrs {
     const double *val;
     const uint16_t *iloc;
@@ -1290,115 +1187,23 @@ struct TilePtrs {
     double *wg_acc;
 };
 
-// data of tile T whose header h is already in registers; columns clamped to the tile's last one
-__device__ __forceinline__ TileRegs load_tile(const TilePtrs &tp, const double *__restrict__ x, int4 h, int64_t T)
-{
-    TileRegs r;
-    r.hdr = h;
-    {
-        const int tid = threadIdx.x, lastc = h.z - 1;
-        const double *xt = x + h.x;
-        r.w[0] = xt[tid < lastc ? tid : lastc];
-        r.w[1] = xt[tid + kBlock < lastc ? tid + kBlock : lastc];
-    }
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const int64_t k = T * kChunk + m * kQuarter + threadIdx.x * 2;
-        r.v[m] = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(tp.val + k));
-        r.il[m] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(tp.iloc + k));
-    }
-    r.flags = tp.flags[T * kBlock + threadIdx.x];
-    // slot blocks are padded to a multiple of 8; threads beyond the tile's segments re-read its first block
-    const int nseg = h.y;
-    const int64_t d0 = (int64_t)h.w + ((8 * (int)threadIdx.x < nseg) ? 8 * (int)threadIdx.x : 0);
-    r.slots = *reinterpret_cast<const uint4 *>(tp.seg_slot + d0);
-    return r;
-}
-
-// Persistent workgroup (slice s, q): tiles q, q + B, ... of the slice; LDS accumulators for the slice's hot rows.
-// Software pipeline: while tile t is reduced, the data of tiles t + B and t + 2B and the header of tile t + 3B are
-// in flight (all indices clamped to the last tile, so every iteration issues the same loads).
-// Slots inside a tile are distinct, so the accumulator updates of different segments never collide.
-template <bool SQ>
-__device__ __forceinline__ void tiles_body(double *prod, uint16_t *slots, double *acc, double (*window)[kTileWindow], const TileArgs &ta,
-                                           const int s, const int q, const int B, const TilePtrs &tp, const double *__restrict__ x)
-{
-    const int tid = threadIdx.x;
-    for (int k = tid; k < kTileSlots; k += kBlock) acc[k] = 0.0;
-    const int64_t nt = ta.ntiles[s];
-    if (q < nt) {
-        const int64_t T0 = ta.tile0[s];
-        const int64_t last = nt - 1;
-        auto clampt = [&](int64_t t) { return T0 + (t < last ? t : last); };
-        TileRegs cur = load_tile(tp, x, load_uniform(tp.hdr + clampt(q)), clampt(q));
-        TileRegs nxt = load_tile(tp, x, load_uniform(tp.hdr + clampt(q + B)), clampt(q + B));
-        int4 hdr2 = load_uniform(tp.hdr + clampt(q + 2 * (int64_t)B));
-        window[0][tid] = cur.w[0];
-        window[0][tid + kBlock] = cur.w[1];
-        __syncthreads();
-        int buf = 0;
-        for (int64_t t = q; t < nt; t += B) {
-            const int nseg = cur.hdr.y;
-            // gathers from the copy of the tile's columns (at most kTileWindow of them) in LDS: see k_hot_tiles_unit
-            const double *xt = window[buf];
-            double xg[4][2];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                xg[m][0] = xt[cur.il[m] & 0xffffu];
-                xg[m][1] = xt[cur.il[m] >> 16];
-            }
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                double2 p;
-                p.x = (SQ ? cur.v[m].x * cur.v[m].x : cur.v[m].x) * xg[m][0];
-                p.y = (SQ ? cur.v[m].y * cur.v[m].y : cur.v[m].y) * xg[m][1];
-                *reinterpret_cast<double2 *>(prod + prod_pos(m * kQuarter + tid * 2)) = p;
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            const TileRegs nn = load_tile(tp, x, hdr2, clampt(t + 2 * (int64_t)B));
-            const int4 hdr3 = load_uniform(tp.hdr + clampt(t + 3 * (int64_t)B));
-            __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();
-            // every thread is past the accumulator updates of the tile before: its slots may be replaced; and past the
-            // gathers of the tile before that one, which were the last to read the other window buffer
-            if (8 * tid < nseg) *reinterpret_cast<uint4 *>(slots + 8 * tid) = cur.slots;
-            window[buf ^ 1][tid] = nxt.w[0];
-            window[buf ^ 1][tid + kBlock] = nxt.w[1];
-            buf ^= 1;
-            double p[8], cin;
-            int idx0;
-            chunk_runs(prod, cur.flags, p, cin, idx0);   // barrier inside: the slots and the next tile's columns are visible after it
-            int i = idx0;
-            bool first = true;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if ((cur.flags >> e) & 1u) {
-                    acc[slots[i]] += first ? p[e] + cin : p[e];
-                    first = false;
-                    ++i;
-                }
-            }
-            // no barrier here: the next tile's products do not touch acc or slots, and its wavefront totals are
-            // written after its first barrier
-            cur = nxt;
-            nxt = nn;
-            hdr2 = hdr3;
-        }
-    }
-    __syncthreads();
-    double *out = tp.wg_acc + ((int64_t)s * B + q) * kTileSlots;
-    for (int k = tid; k < kTileSlots; k += kBlock) out[k] = acc[k];
-}
-
-// The tiles of a unit plan: an entry is a 16-bit column offset and nothing else; thread t loads the offsets of entries
-// 8t .. 8t+7 with one 16-byte load.  A tile spans at most kTileWindow columns: the workgroup copies them from x into
+// An entry of a tile is a 16-bit column offset, and a value unless the plan is a unit plan; thread t loads those of entries
+// 8t .. 8t+7 (see val_pos).  A tile spans at most kTileWindow columns: the workgroup copies them from x into
 // LDS with two coalesced loads per thread and gathers from the copy -- the gathers of a tile go to a few hundred
 // consecutive doubles, and the vector memory pipeline, which handles about one lane of such a gather per clock, was
 // what bound this kernel when they went to x itself.
-struct TileRegsU {
+template <bool UNIT>
+struct TileValues {
+    v2d v[4];
+};
+template <>
+struct TileValues<true> {};
+
+template <bool UNIT>
+struct TileRegs : TileValues<UNIT> {
     v4i il;             // eight 16-bit local column offsets
-    uint4 slots;
-    unsigned flags;
+    uint4 slots;        // slots of the segments 8*tid .. 8*tid+7 (16 bits each)
+    unsigned flags;     // bit e: entry 8*tid + e is the last of its segment
     double w[2];        // the two columns of the tile that the thread copies into LDS
     int4 hdr;
 };
@@ -1412,12 +1217,18 @@ __device__ __forceinline__ void lds_add(double *a, double v)
 }
 
 // the data of tile T, whose header is h; columns clamped to the tile's last one
-__device__ __forceinline__ void load_tile_unit(TileRegsU &r, const TilePtrs &tp, const double *__restrict__ x, int4 h, int64_t T)
+template <bool UNIT>
+__device__ __forceinline__ void load_tile(TileRegs<UNIT> &r, const TilePtrs &tp, const double *__restrict__ x, int4 h, int64_t T)
 {
     const int tid = threadIdx.x;
     r.hdr = h;
     r.il = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(tp.iloc + T * kChunk + 8 * tid));
+    if constexpr (!UNIT) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) r.v[m] = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(tp.val + T * kChunk + m * kQuarter + tid * 2));
+    }
     r.flags = tp.flags[T * kBlock + tid];
+    // slot blocks are padded to a multiple of 8; threads beyond the tile's segments re-read its first block
     const int nseg = h.y;
     const int64_t d0 = (int64_t)h.w + ((8 * tid < nseg) ? 8 * tid : 0);
     r.slots = *reinterpret_cast<const uint4 *>(tp.seg_slot + d0);
@@ -1427,7 +1238,8 @@ __device__ __forceinline__ void load_tile_unit(TileRegsU &r, const TilePtrs &tp,
     r.w[1] = xt[tid + kBlock < lastc ? tid + kBlock : lastc];
 }
 
-__device__ __forceinline__ void store_window(double *window, const TileRegsU &r)
+template <bool UNIT>
+__device__ __forceinline__ void store_window(double *window, const TileRegs<UNIT> &r)
 {
     window[threadIdx.x] = r.w[0];
     window[threadIdx.x + kBlock] = r.w[1];
@@ -1436,15 +1248,15 @@ __device__ __forceinline__ void store_window(double *window, const TileRegsU &r)
 // One tile: cur is reduced (its columns are in window[BUF]) while the data of the next tile of the workgroup, whose
 // header is ahead, are loaded into nxt; they are not waited for before the end of the step, where the columns go to
 // the other window buffer.  ahead becomes the header of the tile after that.
-template <int BUF>
-__device__ __forceinline__ void tile_step_unit(double *prod, uint16_t *slots, double *acc, double (*window)[kTileWindow], TileRegsU &cur,
-                                               TileRegsU &nxt, int4 &ahead, const TilePtrs &tp, const double *__restrict__ x,
-                                               const int64_t Tn, const int64_t Tnn)
+template <int BUF, bool SQ, bool UNIT>
+__device__ __forceinline__ void tile_step(double *prod, uint16_t *slots, double *acc, double (*window)[kTileWindow], TileRegs<UNIT> &cur,
+                                          TileRegs<UNIT> &nxt, int4 &ahead, const TilePtrs &tp, const double *__restrict__ x,
+                                          const int64_t Tn, const int64_t Tnn)
 {
     const int tid = threadIdx.x;
     const int nseg = cur.hdr.y;
     __builtin_amdgcn_sched_barrier(0);
-    load_tile_unit(nxt, tp, x, ahead, Tn);
+    load_tile(nxt, tp, x, ahead, Tn);
     ahead = load_uniform(tp.hdr + Tnn);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
@@ -1456,6 +1268,13 @@ __device__ __forceinline__ void tile_step_unit(double *prod, uint16_t *slots, do
         const unsigned two = (unsigned)cur.il[m];
         p[2 * m] = window[BUF][two & 0xffffu];
         p[2 * m + 1] = window[BUF][two >> 16];
+    }
+    if constexpr (!UNIT) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double v = cur.v[e / 2][e % 2];
+            p[e] *= SQ ? v * v : v;
+        }
     }
     if (8 * tid < nseg) *reinterpret_cast<uint4 *>(slots + 8 * tid) = cur.slots;
     int idx0;
@@ -1476,13 +1295,18 @@ __device__ __forceinline__ void tile_step_unit(double *prod, uint16_t *slots, do
     store_window(window[BUF ^ 1], nxt);
 }
 
-// Persistent workgroup (slice s, q): tiles q, q + B, ... of the slice, two steps per iteration so that the two sets of
-// tile registers and the two window buffers swap roles without copies (indices clamped to the last tile, so every
-// step issues the same loads).
-__device__ __forceinline__ void tiles_unit_body(double *prod, uint16_t *slots, double *acc, double (*window)[kTileWindow],
-                                                const TileArgs &ta, const int s, const int q, const int B, const TilePtrs &tp,
-                                                const double *__restrict__ x)
+// Persistent workgroup (slice s, q): tiles q, q + B, ... of the slice, LDS accumulators for the slice's hot rows; two steps per
+// iteration so that the two sets of tile registers and the two window buffers swap roles without copies (indices clamped to
+// the last tile, so every step issues the same loads).  SQ: the values are squared.
+template <bool SQ, bool UNIT>
+__global__ __launch_bounds__(kBlock) void k_hot_tiles(TileArgs ta, int B, TilePtrs tp, const double *__restrict__ x)
 {
+    __shared__ __align__(16) double prod[kOutOffset];   // the wavefront totals only
+    __shared__ __align__(16) uint16_t slots[kChunk];
+    __shared__ double acc[kTileSlots];
+    __shared__ double window[2][kTileWindow];
+    static_assert(kTileWindow == 2 * kBlock, "two columns per thread");
+    const int s = blockIdx.x % kTileSlices, q = blockIdx.x / kTileSlices;
     const int tid = threadIdx.x;
     for (int k = tid; k < kTileSlots; k += kBlock) acc[k] = 0.0;
     const int64_t nt = ta.ntiles[s];
@@ -1490,39 +1314,19 @@ __device__ __forceinline__ void tiles_unit_body(double *prod, uint16_t *slots, d
         const int64_t T0 = ta.tile0[s];
         const int64_t last = nt - 1;
         auto clampt = [&](int64_t t) { return T0 + (t < last ? t : last); };
-        TileRegsU r0, r1;
-        load_tile_unit(r0, tp, x, load_uniform(tp.hdr + clampt(q)), clampt(q));
+        TileRegs<UNIT> r0, r1;
+        load_tile(r0, tp, x, load_uniform(tp.hdr + clampt(q)), clampt(q));
         int4 ahead = load_uniform(tp.hdr + clampt(q + B));
         store_window(window[0], r0);
         for (int64_t t = q; t < nt; t += 2 * (int64_t)B) {
-            tile_step_unit<0>(prod, slots, acc, window, r0, r1, ahead, tp, x, clampt(t + B), clampt(t + 2 * (int64_t)B));
+            tile_step<0, SQ, UNIT>(prod, slots, acc, window, r0, r1, ahead, tp, x, clampt(t + B), clampt(t + 2 * (int64_t)B));
             if (t + B >= nt) break;
-            tile_step_unit<1>(prod, slots, acc, window, r1, r0, ahead, tp, x, clampt(t + 2 * (int64_t)B), clampt(t + 3 * (int64_t)B));
+            tile_step<1, SQ, UNIT>(prod, slots, acc, window, r1, r0, ahead, tp, x, clampt(t + 2 * (int64_t)B), clampt(t + 3 * (int64_t)B));
         }
     }
     __syncthreads();
     double *out = tp.wg_acc + ((int64_t)s * B + q) * kTileSlots;
     for (int k = tid; k < kTileSlots; k += kBlock) out[k] = acc[k];
-}
-
-__global__ __launch_bounds__(kBlock) void k_hot_tiles_unit(TileArgs ta, int B, TilePtrs tp, const double *__restrict__ x)
-{
-    __shared__ __align__(16) double prod[kOutOffset];   // the wavefront totals only
-    __shared__ __align__(16) uint16_t slots[kChunk];
-    __shared__ double acc[kTileSlots];
-    __shared__ double window[2][kTileWindow];
-    static_assert(kTileWindow == 2 * kBlock, "two columns per thread");
-    tiles_unit_body(prod, slots, acc, window, ta, blockIdx.x % kTileSlices, blockIdx.x / kTileSlices, B, tp, x);
-}
-
-template <bool SQ>
-__global__ __launch_bounds__(kBlock) void k_hot_tiles(TileArgs ta, int B, TilePtrs tp, const double *__restrict__ x)
-{
-    __shared__ __align__(16) double prod[kProdDoubles];
-    __shared__ __align__(16) uint16_t slots[kChunk];
-    __shared__ double acc[kTileSlots];
-    __shared__ double window[2][kTileWindow];
-    tiles_body<SQ>(prod, slots, acc, window, ta, blockIdx.x % kTileSlices, blockIdx.x / kTileSlices, B, tp, x);
 }
 
 // sums[s*K + k] = sum over the B workgroups of slice s: sixteen partial sums (workgroup order inside each), added in
@@ -1567,13 +1371,13 @@ static int launch_hot_tiles(tron_dataset *ds, const CsrPlan &A, const double *x,
     {
         ProfScope ps(ds, SLOT_SPMV_TILES, st);
         if (A.unit)   // squares, if any, are in the scaled vector
-            hipLaunchKernelGGL(k_hot_tiles_unit, dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
+            hipLaunchKernelGGL((k_hot_tiles<false, true>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
                                H.blocks_per_slice, tile_ptrs(H), x);
         else if (square)
-            hipLaunchKernelGGL((k_hot_tiles<true>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
+            hipLaunchKernelGGL((k_hot_tiles<true, false>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
                                H.blocks_per_slice, tile_ptrs(H), x);
         else
-            hipLaunchKernelGGL((k_hot_tiles<false>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
+            hipLaunchKernelGGL((k_hot_tiles<false, false>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
                                H.blocks_per_slice, tile_ptrs(H), x);
         TRON_HIP(hipGetLastError());
     }
@@ -1834,8 +1638,8 @@ static int launch_partials(tron_dataset *ds, const CsrPlan &A, int slot, const d
             hipLaunchKernelGGL(k_head_sell, dim3((S.nwaves + kSellBlock / kWave - 1) / (kSellBlock / kWave)), dim3(kSellBlock), 0, ds->stream, S.nwaves, S.wave_off, S.data,
                                A.hot_x + (size_t)A.head * kHotSlots, S.sums);
         } else if (A.unit)
-            hipLaunchKernelGGL(k_csr_head_unit, dim3(grid), dim3(kBlock), kHotSlots * sizeof(double), ds->stream, head_args(A),
-                               head_ptrs(ds, A));
+            hipLaunchKernelGGL((k_csr_spmv_part<true, true, false, true>), dim3(grid), dim3(kBlock), kHotSlots * sizeof(double), ds->stream,
+                               head_args(A), A.rows, head_ptrs(ds, A), x);
         else
             hipLaunchKernelGGL((k_csr_spmv_part<true, true, false, false>), dim3(grid), dim3(kBlock), kHotSlots * sizeof(double), ds->stream,
                                head_args(A), A.rows, head_ptrs(ds, A), x);
