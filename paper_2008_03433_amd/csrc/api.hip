@@ -178,8 +178,6 @@ void tron_dataset_destroy(tron_dataset *ds)
     hipFree(ds->partials); hipFree(ds->row_partials); hipFree(ds->unit_scale); hipFree(ds->scal_copy); hipFree(ds->ticket);
     if (ds->scal_host) hipHostFree(ds->scal_host);
     for (double *p : ds->sv) hipFree(p);
-    for (hipEvent_t e : ds->cg_event)
-        if (e) hipEventDestroy(e);
     hipFree(ds->cg_partials);
     ds->prof.destroy();
     delete ds;

@@ -193,6 +193,8 @@ struct SellHead {
     void release();
 };
 
+constexpr int kDirectMaxSums = 2560;   // per-workgroup sums that a kernel with the epilogue in it may leave (see hv_enqueue)
+
 struct CsrPlan {
     int64_t rows = 0, cols = 0, nnz = 0;
     SellHead sell;                       // optional (head partition of a unit plan)
@@ -245,6 +247,13 @@ struct CsrPlan {
     uint8_t *flags = nullptr;            // device, nblocks * 256: bit e of byte t of a chunk = its entry 8t + e is the last
                                          //   entry of a row inside the chunk
     uint16_t *row_mask = nullptr;        // device, rows: bit x set iff the row has entries in partition x
+    // ---- P == 1 as segments, the epilogue applied by the kernel itself (k_csr_direct; row_lo as for plain CSR)
+    bool direct = false;
+    int32_t *row_seg = nullptr;          // device, rows: the row's segment, or -1
+    int2 *chunk_long = nullptr;          // device, nblocks: long row continuing into the chunk, long row starting in it (-1: none)
+    int4 *long_row = nullptr;            // device, nfix: {row, first chunk it continues into, number of those, unused}
+    double *long_first = nullptr;        // device, nfix
+    unsigned *long_ticket = nullptr;     // device, nfix
     void release();
 };
 
@@ -300,7 +309,6 @@ struct tron_dataset {
 
     // solver vectors (d each), allocated on first tron_solve
     double *sv[9] = {nullptr};
-    hipEvent_t cg_event[2] = {nullptr, nullptr};   // end of a CG iteration's kernels, by iteration parity
     double *cg_partials = nullptr;   // kCgRegions x kMaxGrid: per-workgroup sums that the next CG kernel adds up itself
 
     tron::Profiler prof;
@@ -345,36 +353,38 @@ int read_scalars(tron_dataset *ds, int count);  // stream sync; then scal_host[0
 // trust-region boundary is in kScalFlag + it % 2).  Two slots each, so that the kernels of iteration it + 1 can be
 // enqueued before the host has read what iteration it left.
 constexpr int kScalRR = 6, kScalFlag = 8;
-// The step and direction kernels leave per-workgroup partial sums in regions of cg_partials, kMaxGrid doubles each.  With
-// at most kCgDirectGrid workgroups the consumer adds them up itself (every workgroup, in the order of the second-stage
-// kernel, so all get the same bits), which saves the two launches that would do nothing else; above that every workgroup
-// re-reading every partial sum costs more than those launches, and the second-stage kernel runs in between.
+// The step and direction kernels leave per-workgroup partial sums in regions of cg_partials, kMaxGrid doubles each.  They have
+// at most kCgDirectGrid workgroups, and the consumer adds them up itself (every workgroup, in the order of the second-stage
+// kernel, so all get the same bits), which saves the two launches that would do nothing else.
 enum { CGP_RR = 0, CGP_PP, CGP_SP, CGP_SS, kCgRegions };
 constexpr int kCgDirectGrid = 512;
 // rr0 >= 0: also starts a CG run (scalar kScalRR = rr0, both flags cleared)
 int cg_init(tron_dataset *ds, const double *g, const double *M, double *s, double *r, double *p, int first = -1, double rr0 = -1.0);  // M: slot0 = g.(g/M); returns #partials
 // What the CG step kernel needs to form the step length itself from the device copy of the scalars (slot 0 = p.Hp,
 // slots 1..3 = p.p, s.p, s.s unless it == 0, r.r as above): alpha = rr / p.Hp, or the step to the trust-region boundary
-// if |s + alpha p| >= delta.  The kernel leaves the step taken in scalar 4 and the boundary flag in its slot.
+// if |s + alpha p| >= delta.  The kernel leaves the boundary flag in its slot.
 // An iteration that was enqueued ahead although the run had ended -- the iteration before it went to the boundary, or
 // left sqrt(r.r) <= tol -- changes nothing: both kernels test for that themselves, with the host's own comparison.
 struct CgStepCtl {
     double tol, delta;   // tol = xi times the length of the gradient the run started from
     int it;              // iteration number, from 0 (then s = 0 and p.p = r.r)
+    bool last;           // the last iteration allowed: no direction after it
 };
-// n_dir: workgroups of the direction kernel before (its partial sums of p.p, s.p, s.s; unused when it == 0), 0 = take the
-// sums from scalars 1..3.  n_php: partial sums of p.Hp at the start of ds->partials, 0 = take p.Hp from scalar 0.
+// the step and direction kernels in one launch, d <= kCgSmallD (a few elements per thread of one workgroup)
+constexpr int64_t kCgSmallD = 8192;
+int cg_small(tron_dataset *ds, const CgStepCtl &ctl, int n_php, const double *Hp, const double *M, double *s, double *r, double *p);
+// n_dir: workgroups of the direction kernel before (its partial sums of p.p, s.p, s.s; unused when it == 0).  n_php: partial
+// sums of p.Hp at the start of ds->partials, 0 = take p.Hp from scalar 0.
 // Returns its own number of workgroups: the partial sums of r.r | r.(r/M) in region CGP_RR.
 int cg_step(tron_dataset *ds, const CgStepCtl &ctl, int n_dir, int n_php, const double *p, const double *Hp, const double *M, double *s, double *r);
 int vec_workgroups(int64_t m);   // workgroups of the vector kernels (and of the sparse combine kernels) over m elements
-// n_step: workgroups of the step kernel before: adds up the new r.r and leaves it in its scalar slot (host and device copy);
-// 0 = the slot holds it already.  beta = (new r.r) / (old r.r); partial sums of p.p, s.p, s.s (M-weighted) in their regions.
+// n_step: workgroups of the step kernel before: adds up the new r.r and leaves it in its scalar slot (for the host with the
+// boundary flag as its sign).  beta = (new r.r) / (old r.r); partial sums of p.p, s.p, s.s (M-weighted) in their regions.
 // Returns its number of workgroups.
 int cg_dir(tron_dataset *ds, const CgStepCtl &ctl, int n_step, const double *r, const double *s, const double *M, double *p);
-// the second stage as a launch of its own, for `count` partial sums in each of nregions regions of cg_partials from `region` on
-int reduce_cg_regions(tron_dataset *ds, int region, int nregions, int count, int first_scalar);
 int trial_point(tron_dataset *ds, const double *w, const double *s, const double *g, const double *r, const double *M,
-                double *wnew, int first = -1);  // wnew = w+s; slots: g.s, s.r, s.s | s.Ms
+                double *wnew, int first = -1);  // wnew = w+s; slots: g.s, s.r, s.s | s.Ms, wnew.wnew
+int copy_norm(tron_dataset *ds, int64_t m, const double *src, double *dst, int first = -1);   // dst = src; slot0 = src.src
 int probe_read(const double *src, int64_t count, int reps, hipStream_t st, double *ms, double *checksum);
 int probe_copy(double *dst, const double *src, int64_t count, int reps, hipStream_t st, double *ms);
 
@@ -395,6 +405,7 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
 //   post (spmv_loss: applied to zhat; spmv_scale: to out), when not null: the stored vector is multiplied by it
 //   elementwise -- the column scale of the unit plan that will gather from it (then passed with x_prescaled = true)
 // Each returns the number of first-stage partials in slot 0 (0 if none), or a negative error.
+bool single_sums(const CsrPlan &A);   // whether one launch does all of it (then at most kDirectMaxSums partials)
 int spmv_loss(tron_dataset *ds, const CsrPlan &A, int slot, int loss, const double *x, double *zwork, double *zhat, double *D,
               const double *post = nullptr, int first = -1);
 int spmv_scale(tron_dataset *ds, const CsrPlan &A, int slot, const double *x, const double *scale, double *out,
@@ -447,7 +458,7 @@ int dense_device_solve(tron_dataset *ds, const tron_params &P, double *w_dev, tr
 void dense_device_release(tron_dataset *ds);
 
 // ---- solver.hip
-int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot);                        // scalars[0]=sum of loss terms, [1]=w.w, no sync
+int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot, bool ww);               // scalars[0]=sum of loss terms, [1]=w.w if ww, no sync
 int fun_eval(tron_dataset *ds, int loss, double C, const double *w, int Dslot, double *f_out);  // syncs
 int grad_enqueue(tron_dataset *ds, double C, const double *w, double *g, int scalar);           // scalars[scalar]=g.g, no sync
 // out = 1 + C sum_i D_i x_ij^2 with D = Dbuf[Dslot] (the diagonal of the Hessian; C scaled by the caller for a blend). Enqueue only.

@@ -198,28 +198,20 @@ __device__ __forceinline__ bool last_workgroup(unsigned *ticket)
 }
 
 // Second reduction stage inside the producing kernel (see Finish in common.h).  Every thread of every workgroup calls it
-// after thread 0 has written the workgroup's partial sums (NSLOTS of them, `stride` apart).  The workgroup that draws
-// the last ticket adds the partial sums of all workgroups -- in the order and with the arithmetic of k_reduce_final, so
-// the result does not depend on which workgroup that is -- writes the scalars and clears the counter for the next
-// kernel on the stream.  The counter is the only thing touched atomically; no sum goes through an atomic.
+// after thread 0 has stored the workgroup's partial sums (NSLOTS of them, `stride` apart; store_shared).  The workgroup that
+// draws the last ticket adds the partial sums of all workgroups (and `extra` more behind them) -- in the order and with the
+// arithmetic of k_reduce_final, so the result does not depend on which workgroup that is -- writes the scalars and clears the
+// counter for the next kernel on the stream.
 template <int NSLOTS>
-__device__ __forceinline__ void finish_partials(const Finish &f, const double *partials, int stride, double *lds)
+__device__ __forceinline__ void finish_partials(const Finish &f, const double *partials, int stride, double *lds, int extra = 0)
 {
-    if (!f.ticket) return;
-    __shared__ int is_last;
-    if (threadIdx.x == 0) {
-        __threadfence();   // the partial sums above are visible device-wide before the ticket is
-        is_last = (atomicAdd(f.ticket, 1u) == gridDim.x - 1) ? 1 : 0;
-    }
-    __syncthreads();
-    if (!is_last) return;
-    __threadfence();       // and the other workgroups' partial sums are visible here
-    const int count = (int)gridDim.x;
+    if (!f.ticket || !last_workgroup(f.ticket)) return;
+    const int count = (int)gridDim.x + extra;
 #pragma unroll
     for (int s = 0; s < NSLOTS; ++s) {
         const double *p = partials + (int64_t)s * stride;
         double acc = 0.0;
-        for (int b = threadIdx.x; b < count; b += kBlock) acc += __builtin_nontemporal_load(p + b);
+        for (int b = threadIdx.x; b < count; b += kBlock) acc += load_shared(p + b);
         acc = block_sum(acc, lds);
         if (threadIdx.x == 0) {
             f.scal[f.first + s] = acc;

@@ -60,6 +60,7 @@ void CsrPlan::release()
     sell.release();
     hipFree(rowptr); hipFree(col); hipFree(col16); hipFree(val); hipFree(row_lo); hipFree(carry);
     hipFree(xs); hipFree(hot_ids); hipFree(hot_x); hipFree(group_base); hipFree(chunk_tab); hipFree(flags); hipFree(row_mask);
+    hipFree(row_seg); hipFree(chunk_long); hipFree(long_row); hipFree(long_first); hipFree(long_ticket);
     hipFree(fix_row); hipFree(fix_part); hipFree(fix_b0); hipFree(fix_cnt);
     *this = CsrPlan();
 }
@@ -137,8 +138,8 @@ static void parallel_ranges(int64_t n, F &&fn)
 // Where entry e of a chunk is stored.  Thread t of a kernel owns entries 8t .. 8t+7 of a chunk, and its loads cover whole
 // cache lines: the columns come as two pieces of four (16 bytes), the values as four pieces of two, piece m of all threads
 // together.  The 16-bit slots of a head partition or a tile are 16 bytes per thread and stay in order.
-static inline int64_t col_pos(int64_t q) { const int64_t e = q % kChunk; return q - e + (e / 4 % 2) * (kChunk / 2) + e / 8 * 4 + e % 4; }
-static inline int64_t val_pos(int64_t q) { const int64_t e = q % kChunk; return q - e + (e / 2 % 4) * (kChunk / 4) + e / 8 * 2 + e % 2; }
+static inline int64_t col_pos(int64_t q) { const uint32_t e = (uint32_t)q & (kChunk - 1); return q - e + ((e >> 2 & 1) * (kChunk / 2) + (e >> 3) * 4 + (e & 3)); }
+static inline int64_t val_pos(int64_t q) { const uint32_t e = (uint32_t)q & (kChunk - 1); return q - e + ((e >> 1 & 3) * (kChunk / 4) + (e >> 3) * 2 + (e & 1)); }
 
 int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowptr, const int32_t *h_col,
                    const double *h_val, int parts, bool hot, bool unit, hipStream_t st)
@@ -529,6 +530,39 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
                 gbase[(size_t)G].first[x] = (int32_t)m;
             }
         }
+        // A single range: the kernel applies the epilogue itself where every chunk has a bounded number of rows (the empty ones
+        // among them) and the sums it leaves are few enough to be added up by the kernel after it.
+        if (P == 1) {
+            const int nlong = (int)fix_row.size();
+            std::vector<int32_t> rl((size_t)chunk + 1), row_seg((size_t)rows, -1);
+            int64_t r = 0, most = 0;
+            for (int c = 0; c < chunk; ++c) {
+                while (r < rows && rp32[r] < (int64_t)c * kChunk) ++r;
+                rl[c] = c ? (int32_t)r : 0;
+                if (c) most = std::max<int64_t>(most, rl[c] - rl[c - 1]);
+            }
+            rl[chunk] = (int32_t)rows;
+            most = std::max<int64_t>(most, rows - rl[chunk - 1]);
+            if (most <= 4 * kChunk && chunk + nlong <= kDirectMaxSums) {
+                for (int64_t m = 0; m < nseg_total; ++m) row_seg[seg_row[m]] = (int32_t)m;
+                std::vector<int2> chunk_long((size_t)chunk, make_int2(-1, -1));
+                std::vector<int4> long_row((size_t)std::max(nlong, 1));
+                for (int l = 0; l < nlong; ++l) {
+                    long_row[l] = make_int4(seg_row[fix_row[l]], fix_b0[l], fix_cnt[l], 0);
+                    chunk_long[fix_b0[l] - 1].y = l;
+                    for (int k = 0; k < fix_cnt[l]; ++k) chunk_long[fix_b0[l] + k].x = l;
+                }
+                TRON_TRY(upload(&A.row_lo, rl.data(), rl.size(), st));
+                TRON_TRY(upload(&A.row_seg, row_seg.data(), row_seg.size(), st));
+                TRON_TRY(upload(&A.chunk_long, chunk_long.data(), chunk_long.size(), st));
+                TRON_TRY(upload(&A.long_row, long_row.data(), long_row.size(), st));
+                TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.long_first), sizeof(double) * std::max(nlong, 1)));
+                TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.long_ticket), sizeof(unsigned) * std::max(nlong, 1)));
+                TRON_HIP(hipMemsetAsync(A.long_ticket, 0, sizeof(unsigned) * std::max(nlong, 1), st));
+                TRON_HIP(hipStreamSynchronize(st));
+                A.direct = true;
+            }
+        }
         TRON_TRY(upload(&A.group_base, gbase.data(), gbase.size(), st));
         TRON_TRY(upload(&A.chunk_tab, tab.data(), tab.size(), st));
         TRON_TRY(upload(&A.flags, flags.data(), flags.size(), st));
@@ -550,18 +584,48 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
 }
 
 // ------------------------------------------------------------------ chunk kernel
-enum { EPI_PLAIN = 0, EPI_SCALE = 1, EPI_AXPY = 2 };
+// What happens to a row's sum z:
+//   PLAIN  out = z;   SCALE  out = aux z;   AXPY  out = aux + alpha z (no aux: 1 + alpha z), and the row's share of out . (self ?
+//   out : aux);   LR / SVM  the loss terms at z with aux = the labels: out = zhat, D, and the row's loss.
+enum { EPI_PLAIN = 0, EPI_SCALE = 1, EPI_AXPY = 2, EPI_LR = 3, EPI_SVM = 4 };
+struct EpiArgs {
+    double *out;
+    const double *aux;
+    double alpha;
+    bool self;
+    double *D;
+    double *red;   // per-workgroup sums of the shares; null: not wanted
+    Finish fin;
+};
 
 template <int EPI>
-__device__ __forceinline__ double epilogue(double sum, int64_t r, const double *__restrict__ aux, double alpha)
+__device__ __forceinline__ double row_aux(const EpiArgs &A, int64_t r)
 {
-    if (EPI == EPI_PLAIN) return sum;
-    if (EPI == EPI_SCALE) return aux[r] * sum;
-    return fma(alpha, sum, aux ? aux[r] : 1.0);   // no addend vector: add 1 (the Hessian diagonal)
+    if (EPI == EPI_PLAIN) return 0.0;
+    if (EPI == EPI_AXPY) return A.aux ? A.aux[r] : 1.0;
+    return A.aux[r];
 }
 
-// One chunk: nonzeros [start, end) of a (sub)matrix whose row offsets are rp (relative to col/val),
-// chunk-local tables row_lo[0..1] and carry slot *carry_out.
+// returns the row's share of the sum
+template <int EPI>
+__device__ __forceinline__ double finish_row(const EpiArgs &A, int64_t r, double z, double aux)
+{
+    if constexpr (EPI == EPI_LR || EPI == EPI_SVM) {
+        double a, zh, Di;
+        loss_terms_dev<EPI == EPI_LR ? TRON_LOSS_LR : TRON_LOSS_L2SVM>(z, aux, a, zh, Di);
+        A.out[r] = zh;
+        A.D[r] = Di;
+        return a;
+    } else if constexpr (EPI == EPI_AXPY) {
+        const double o = fma(A.alpha, z, aux);
+        A.out[r] = o;
+        return o * (A.self ? o : aux);
+    } else {
+        A.out[r] = EPI == EPI_SCALE ? aux * z : z;
+        return 0.0;
+    }
+}
+
 // With HOT, a negative stored column c means "entry ~c of the workgroup's LDS table" (the most frequent
 // columns of the partition, copied from x once per workgroup).
 // x[c] through a 32-bit byte offset (tron_dataset_create_csr accepts n, d < 2^29 only)
@@ -581,30 +645,56 @@ __device__ __forceinline__ double gather(const double *__restrict__ x, const dou
     return (c < 0) ? hot : cold;
 }
 
-template <int EPI, typename RP, bool HOT = false, bool SQ = false>
-__device__ __forceinline__ void chunk_body(double *prod, const double *table, int64_t start, int64_t end, bool first_chunk,
-                                           const RP *__restrict__ rp, const int32_t *__restrict__ col,
-                                           const double *__restrict__ val, const int32_t *__restrict__ row_lo,
-                                           const double *__restrict__ x, double *__restrict__ yout,
-                                           const double *__restrict__ aux, double alpha, double *__restrict__ carry_out)
+// Plain CSR: one workgroup per chunk of nonzeros, the epilogue applied directly.  The chunk's row range, and the offsets and
+// the addends of the rows a thread starts with, are asked for before the gathers: asked for where they are used, after the
+// products are in LDS, they added three memory latencies to a kernel that is little else (9.6 us for the 1.05M nonzeros of
+// the rcv1-shaped matrix).
+template <int EPI, bool SQ>
+__global__ __launch_bounds__(kBlock) void k_csr_spmv(int64_t nnz, const int64_t *__restrict__ rowptr,
+                                                     const int32_t *__restrict__ col, const double *__restrict__ val,
+                                                     const int32_t *__restrict__ row_lo, const double *__restrict__ x, EpiArgs A,
+                                                     double *__restrict__ carry)
 {
+    __shared__ __align__(16) double prod[kChunk];
+    __shared__ double lds[kWavesPerBlock];
     const int tid = threadIdx.x;
-    // ---- phase 1: products into LDS (two passes of 1024 nonzeros, 4 per thread per pass)
-    if (end - start == kChunk) {
-        // thread t takes entries m*512 + 2t, m*512 + 2t + 1: every load instruction covers whole cache lines
-        v2i c[4];
-        v2d v[4];
+    const int64_t start = (int64_t)blockIdx.x * kChunk;
+    const int64_t end = (start + kChunk < nnz) ? start + kChunk : nnz;
+    const int64_t *__restrict__ rp = rowptr;
+    const int lo = row_lo[blockIdx.x], nrows = row_lo[blockIdx.x + 1] - lo;
+    const bool full = end - start == kChunk;
+    // thread t takes entries m*512 + 2t, m*512 + 2t + 1: every load instruction covers whole cache lines
+    v2i c[4];
+    v2d v[4];
+    if (full) {
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const int64_t k = start + m * (kChunk / 4) + tid * 2;
             c[m] = __builtin_nontemporal_load(reinterpret_cast<const v2i *>(col + k));
             v[m] = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(val + k));
         }
+    }
+    // rows that start in this chunk: groups of g lanes per row, g = 256 / (number of rows) rounded
+    // down to a power of two (so one pass covers them whenever there are at most 256 rows)
+    int g = 1;
+    while (g < kWave && nrows * (g * 2) <= kBlock) g *= 2;
+    const int sub = tid & (g - 1);
+    const int rows_per_pass = kBlock / g;
+    const int ri0 = tid / g;
+    int64_t rs0 = 0, re0 = 0;
+    double aux0 = 0.0;
+    if (ri0 < nrows) {
+        rs0 = rp[lo + ri0];
+        re0 = rp[lo + ri0 + 1];
+        aux0 = row_aux<EPI>(A, lo + ri0);
+    }
+    const int64_t next_start = (blockIdx.x > 0) ? rp[lo] : start;   // rp[rows] == nnz
+    if (full) {
         double xg[4][2];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
-            xg[m][0] = gather<HOT>(x, table, c[m].x);
-            xg[m][1] = gather<HOT>(x, table, c[m].y);
+            xg[m][0] = load_elem(x, c[m].x);
+            xg[m][1] = load_elem(x, c[m].y);
         }
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
@@ -616,31 +706,21 @@ __device__ __forceinline__ void chunk_body(double *prod, const double *table, in
     } else {
         for (int k = tid; k < kChunk; k += kBlock) {
             const int64_t kk = start + k;
-            prod[k] = (kk < end) ? (SQ ? val[kk] * val[kk] : val[kk]) * gather<HOT>(x, table, col[kk]) : 0.0;
+            prod[k] = (kk < end) ? (SQ ? val[kk] * val[kk] : val[kk]) * load_elem(x, col[kk]) : 0.0;
         }
     }
     __syncthreads();
 
-    const int lo = row_lo[0], hi = row_lo[1];
-
-    // ---- carry: the part of row lo-1 that lies in this chunk (wavefront 0)
-    if (!first_chunk && tid < kWave) {
-        const int64_t next_start = (int64_t)rp[lo];  // rp[rows] == nnz of this (sub)matrix
-        if (next_start > start) {
-            const int len = (int)(((next_start < end) ? next_start : end) - start);
-            double s = 0.0;
-            for (int k = tid; k < len; k += kWave) s += prod[k];
-            s = wave_sum(s);
-            if (tid == 0) *carry_out = s;
-        }
+    // carry: the part of row lo-1 that lies in this chunk (wavefront 0)
+    if (next_start > start && tid < kWave) {
+        const int len = (int)(((next_start < end) ? next_start : end) - start);
+        double s = 0.0;
+        for (int k = tid; k < len; k += kWave) s += prod[k];
+        s = wave_sum(s);
+        if (tid == 0) carry[blockIdx.x] = s;
     }
 
-    // ---- rows that start in this chunk: groups of g lanes per row, g = 256 / (number of rows) rounded
-    //      down to a power of two (so one pass covers them whenever there are at most 256 rows)
-    const int nrows = hi - lo;
-    if (nrows <= 0) return;
-    int g = 1;
-    while (g < kWave && nrows * (g * 2) <= kBlock) g *= 2;
+    double acc = 0.0;
     if (g == 1 && nrows > kBlock) {
         // Many short rows (the tail of a Zipf-distributed transposed copy: a thousand rows of one or two entries in a
         // chunk): one thread per row, and the row offsets of eight passes are fetched together -- a pass that waited
@@ -648,59 +728,50 @@ __device__ __forceinline__ void chunk_body(double *prod, const double *table, in
         constexpr int kBatch = 8;
         for (int base = 0; base < nrows; base += kBatch * kBlock) {
             int64_t rs[kBatch], re[kBatch];
+            double aux[kBatch];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const int ri = base + j * kBlock + tid;
                 const int64_t r = (int64_t)lo + (ri < nrows ? ri : nrows - 1);
-                rs[j] = (int64_t)rp[r];
-                re[j] = (int64_t)rp[r + 1];
+                rs[j] = rp[r];
+                re[j] = rp[r + 1];
+                aux[j] = row_aux<EPI>(A, r);
             }
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const int ri = base + j * kBlock + tid;
                 if (ri < nrows) {
-                    const int64_t r = (int64_t)lo + ri;
                     const int k0 = (int)(rs[j] - start);
                     const int k1 = (int)(((re[j] < end) ? re[j] : end) - start);
                     double s = 0.0;
                     for (int k = k0; k < k1; ++k) s += prod[k];
-                    yout[r] = epilogue<EPI>(s, r, aux, alpha);
+                    acc += finish_row<EPI>(A, (int64_t)lo + ri, s, aux[j]);
                 }
             }
         }
-        return;
-    }
-    const int sub = tid & (g - 1);
-    const int rows_per_pass = kBlock / g;
-    for (int base = 0; base < nrows; base += rows_per_pass) {
-        const int ri = base + tid / g;
-        double s = 0.0;
-        int64_t r = 0;
-        if (ri < nrows) {
-            r = (int64_t)lo + ri;
-            const int64_t rs = (int64_t)rp[r], re = (int64_t)rp[r + 1];
-            const int k0 = (int)(rs - start);
-            const int k1 = (int)(((re < end) ? re : end) - start);
-            for (int k = k0 + sub; k < k1; k += g) s += prod[k];
+    } else {
+        for (int base = 0; base < nrows; base += rows_per_pass) {
+            const int ri = base + ri0;
+            if (base > 0 && ri < nrows) {
+                rs0 = rp[lo + ri];
+                re0 = rp[lo + ri + 1];
+                aux0 = row_aux<EPI>(A, lo + ri);
+            }
+            double s = 0.0;
+            if (ri < nrows) {
+                const int k0 = (int)(rs0 - start);
+                const int k1 = (int)(((re0 < end) ? re0 : end) - start);
+                for (int k = k0 + sub; k < k1; k += g) s += prod[k];
+            }
+            s = group_sum(s, g);
+            if (ri < nrows && sub == 0) acc += finish_row<EPI>(A, (int64_t)lo + ri, s, aux0);
         }
-        s = group_sum(s, g);
-        if (ri < nrows && sub == 0) yout[r] = epilogue<EPI>(s, r, aux, alpha);
     }
-}
-
-// unpartitioned: y = epilogue(A x) directly
-template <int EPI, bool SQ>
-__global__ __launch_bounds__(kBlock) void k_csr_spmv(int64_t nnz, const int64_t *__restrict__ rowptr,
-                                                     const int32_t *__restrict__ col, const double *__restrict__ val,
-                                                     const int32_t *__restrict__ row_lo, const double *__restrict__ x,
-                                                     double *__restrict__ yout, const double *__restrict__ aux,
-                                                     double alpha, double *__restrict__ carry)
-{
-    __shared__ __align__(16) double prod[kChunk];
-    const int b = blockIdx.x;
-    const int64_t start = (int64_t)b * kChunk;
-    const int64_t end = (start + kChunk < nnz) ? start + kChunk : nnz;
-    chunk_body<EPI, int64_t, false, SQ>(prod, nullptr, start, end, b == 0, rowptr, col, val, row_lo + b, x, yout, aux, alpha, carry + b);
+    if (A.red) {
+        acc = block_sum(acc, lds);
+        if (tid == 0) store_shared(A.red + blockIdx.x, acc);
+        finish_partials<1>(A.fin, A.red, 0, lds);
+    }
 }
 
 struct PartArgs {
@@ -856,6 +927,121 @@ __device__ __forceinline__ void chunk_segments(double *prod, const unsigned flag
     for (int j = 0; j < kSegPasses; ++j) {
         const int sidx = (int)threadIdx.x + kBlock * j;
         if (j * kBlock < nseg && sidx < nseg) out[sidx] = outv[sidx];
+    }
+}
+
+// A single range of segments whose kernel applies the epilogue itself (see CsrPlan::direct): one workgroup per chunk.  A chunk's
+// rows (the empty ones among them) are row_lo[c] .. row_lo[c + 1]; row_seg says which segment a row is, or -1.  A row longer
+// than a chunk is added up by the workgroup that finishes last among its chunks, in a fixed order; its share of the sum
+// goes to a slot of its own (red[workgroups + row's index among the long ones]), so no sum depends on timing.  The launches
+// this saves -- the fix-up of the long rows and the combine kernel -- took 4.0 and 6.2 us of the 22 us of a product with the
+// transposed copy of the rcv1-shaped matrix.
+struct DirectPtrs {
+    const int32_t *col;
+    const double *val;
+    const int4 *chunk_tab;
+    const uint8_t *flags;
+    const int32_t *row_lo, *row_seg;
+    const int2 *chunk_long;    // per chunk: index of the long row that continues into it / that starts in it, or -1
+    const int4 *long_row;      // {row, first chunk it continues into, number of those, unused}
+    double *carry;             // per chunk: the piece of the long row that continues into it
+    double *long_first;        // per long row: its piece in the chunk it starts in
+    unsigned *long_ticket;     // per long row (zero between launches)
+};
+
+template <int EPI, bool SQ>
+__global__ __launch_bounds__(kBlock) void k_csr_direct(DirectPtrs P, int nlong, const double *__restrict__ x, EpiArgs A)
+{
+    constexpr int kAhead = 8;   // a chunk of short rows has up to 2048, and empty ones
+    __shared__ __align__(16) double prod[kProdDoubles];
+    __shared__ double lds[kWavesPerBlock];
+    __shared__ double piece;
+    __shared__ int last_of[2];
+    const int tid = threadIdx.x, c = blockIdx.x;
+    StreamRegs<false, false> s;
+    load_stream(s, P.col, P.val, (int64_t)c * kChunk);
+    const unsigned flags = P.flags[(int64_t)c * kBlock + tid];
+    const int lo = P.row_lo[c], hi = P.row_lo[c + 1];
+    const int4 tab = P.chunk_tab[c];
+    const int2 lr = P.chunk_long[c];
+    int seg[kAhead];
+    double aux[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+        const int r = lo + j * kBlock + tid;
+        seg[j] = r < hi ? P.row_seg[r] : -1;
+        aux[j] = r < hi ? row_aux<EPI>(A, r) : 0.0;
+    }
+    double p[8], cin;
+    products<false, false, SQ, false>(s, x, nullptr, p);
+    int idx0;
+    runs_from_regs(prod, flags, p, cin, idx0);
+    double *outv = prod + kOutOffset;
+    {
+        int i = idx0 - (tab.z > 0 ? 1 : 0);
+        bool first = true;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if ((flags >> e) & 1u) {
+                const double v = first ? p[e] + cin : p[e];
+                if (i < 0) piece = v;
+                else outv[i] = v;
+                first = false;
+                ++i;
+            }
+        }
+    }
+    __syncthreads();
+    const int starts_long = lr.y >= 0 ? tab.x + tab.y - 1 : -1;   // the segment that is only a long row's first piece
+    double acc = 0.0;
+    for (int base = lo; base < hi; base += kAhead * kBlock) {
+        if (base > lo) {
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
+                const int r = base + j * kBlock + tid;
+                seg[j] = r < hi ? P.row_seg[r] : -1;
+                aux[j] = r < hi ? row_aux<EPI>(A, r) : 0.0;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const int r = base + j * kBlock + tid;
+            if (r < hi && !(starts_long >= 0 && seg[j] == starts_long)) acc += finish_row<EPI>(A, r, seg[j] >= 0 ? outv[seg[j] - tab.x] : 0.0, aux[j]);
+        }
+    }
+    if (lr.x >= 0 || lr.y >= 0) {   // uniform
+        if (tid == 0) {
+            if (lr.x >= 0) store_shared(P.carry + c, piece);
+            if (lr.y >= 0) store_shared(P.long_first + lr.y, outv[tab.y - 1]);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the pieces have arrived
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int l = q ? lr.y : lr.x;
+                last_of[q] = l >= 0 && __hip_atomic_fetch_add(P.long_ticket + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)P.long_row[l].z;
+            }
+        }
+        __syncthreads();
+        if (tid < kWave) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (!last_of[q]) continue;
+                const int l = q ? lr.y : lr.x;
+                const int4 R = P.long_row[l];
+                double z = 0.0;
+                for (int k = tid; k < R.z; k += kWave) z += load_shared(P.carry + R.y + k);
+                z = wave_sum(z) + load_shared(P.long_first + l);
+                if (tid == 0) {
+                    const double share = finish_row<EPI>(A, R.x, z, row_aux<EPI>(A, R.x));
+                    if (A.red) store_shared(A.red + gridDim.x + l, share);
+                    P.long_ticket[l] = 0u;
+                }
+            }
+        }
+    }
+    if (A.red) {
+        acc = block_sum(acc, lds);
+        if (tid == 0) store_shared(A.red + c, acc);
+        finish_partials<1>(A.fin, A.red, 0, lds, nlong);
     }
 }
 
@@ -1504,7 +1690,7 @@ __global__ __launch_bounds__(kBlock) void k_combine_loss(int64_t n, PartialRef P
         }
     }
     acc = block_sum(acc, lds);
-    if (threadIdx.x == 0) red[blockIdx.x] = acc;
+    if (threadIdx.x == 0) store_shared(red + blockIdx.x, acc);
     finish_partials<1>(fin, red, 0, lds);
 }
 
@@ -1538,7 +1724,7 @@ __global__ __launch_bounds__(kBlock) void k_combine_axpy(int64_t rows, PartialRe
         }
     }
     acc = block_sum(acc, lds);
-    if (threadIdx.x == 0) red[blockIdx.x] = acc;
+    if (threadIdx.x == 0) store_shared(red + blockIdx.x, acc);
     finish_partials<1>(fin, red, 0, lds);
 }
 
@@ -1551,22 +1737,38 @@ static inline int vec_grid(int64_t m)
     return (int)g;
 }
 
+// one launch with the epilogue in it: plain CSR or a single range of segments.  Returns the number of sums in E.red.
+template <int EPI>
+static int launch_single(tron_dataset *ds, const CsrPlan &A, int slot, const double *x, const EpiArgs &E, bool square = false)
+{
+    ProfScope ps(ds, slot);
+    if (A.direct) {
+        const DirectPtrs P{A.col, A.val, A.chunk_tab, A.flags, A.row_lo, A.row_seg, A.chunk_long, A.long_row, A.carry, A.long_first, A.long_ticket};
+        if (square) hipLaunchKernelGGL((k_csr_direct<EPI, true>), dim3(A.nblocks), dim3(kBlock), 0, ds->stream, P, A.nfix, x, E);
+        else hipLaunchKernelGGL((k_csr_direct<EPI, false>), dim3(A.nblocks), dim3(kBlock), 0, ds->stream, P, A.nfix, x, E);
+        TRON_HIP(hipGetLastError());
+        return A.nblocks + A.nfix;
+    }
+    if (square)
+        hipLaunchKernelGGL((k_csr_spmv<EPI, true>), dim3(A.nblocks), dim3(kBlock), 0, ds->stream, A.part_nnz[0], A.rowptr, A.col, A.val, A.row_lo, x, E, A.carry);
+    else
+        hipLaunchKernelGGL((k_csr_spmv<EPI, false>), dim3(A.nblocks), dim3(kBlock), 0, ds->stream, A.part_nnz[0], A.rowptr, A.col, A.val, A.row_lo, x, E, A.carry);
+    TRON_HIP(hipGetLastError());
+    return A.nblocks;
+}
+
+// Whether launch_single can form the sum over the rows as well (no row is completed by the fix-up kernel, and the sums are few)
+bool single_sums(const CsrPlan &A) { return A.direct || (A.plain && A.nfix == 0 && A.nblocks <= kDirectMaxSums); }
+
+static Finish no_finish(tron_dataset *ds) { return finish_for(ds, -1, 1); }
+
+// plain CSR with the rows longer than a chunk completed by the fix-up kernel
 template <int EPI>
 static int launch_plain(tron_dataset *ds, const CsrPlan &A, int slot, const double *x, double *yout, const double *aux,
                         double alpha, bool square = false)
 {
-    {
-        ProfScope ps(ds, slot);
-        if (square)
-            hipLaunchKernelGGL((k_csr_spmv<EPI, true>), dim3(A.nblocks), dim3(kBlock), 0, ds->stream, A.part_nnz[0], A.rowptr, A.col, A.val,
-                               A.row_lo, x, yout, aux, alpha, A.carry);
-        else
-            hipLaunchKernelGGL((k_csr_spmv<EPI, false>), dim3(A.nblocks), dim3(kBlock), 0, ds->stream, A.part_nnz[0], A.rowptr, A.col, A.val,
-                               A.row_lo, x, yout, aux, alpha, A.carry);
-        TRON_HIP(hipGetLastError());
-    }
-    TRON_TRY(launch_fixup<EPI>(ds, A, yout, aux, alpha));
-    return TRON_OK;
+    TRON_TRY(launch_single<EPI>(ds, A, slot, x, EpiArgs{yout, aux, alpha, false, nullptr, nullptr, no_finish(ds)}, square));
+    return launch_fixup<EPI>(ds, A, yout, aux, alpha);
 }
 
 static PartArgs part_args(const CsrPlan &A)
@@ -1674,6 +1876,10 @@ static int launch_partials(tron_dataset *ds, const CsrPlan &A, int slot, const d
 int spmv_loss(tron_dataset *ds, const CsrPlan &A, int slot, int loss, const double *x, double *zwork, double *zhat, double *D,
               const double *post, int first)
 {
+    if (single_sums(A) && !post) {
+        const EpiArgs E{zhat, ds->y, 0.0, false, D, ds->partials, finish_for(ds, first, A.nblocks)};
+        return loss == TRON_LOSS_LR ? launch_single<EPI_LR>(ds, A, slot, x, E) : launch_single<EPI_SVM>(ds, A, slot, x, E);
+    }
     if (A.plain) {
         if (post) { set_error("internal: post-scaling on an unpartitioned plan"); return TRON_EINVAL; }
         TRON_TRY(launch_plain<EPI_PLAIN>(ds, A, slot, x, zwork, nullptr, 0.0));
@@ -1693,6 +1899,10 @@ int spmv_loss(tron_dataset *ds, const CsrPlan &A, int slot, int loss, const doub
 
 int spmv_scale(tron_dataset *ds, const CsrPlan &A, int slot, const double *x, const double *scale, double *out, const double *post)
 {
+    if (A.direct && !post) {
+        const int g = launch_single<EPI_SCALE>(ds, A, slot, x, EpiArgs{out, scale, 0.0, false, nullptr, nullptr, no_finish(ds)});
+        return g < 0 ? g : TRON_OK;
+    }
     if (A.plain) {
         if (post) { set_error("internal: post-scaling on an unpartitioned plan"); return TRON_EINVAL; }
         return launch_plain<EPI_SCALE>(ds, A, slot, x, out, scale, 0.0);
@@ -1727,6 +1937,10 @@ int spmv_axpy(tron_dataset *ds, const CsrPlan &A, int slot, const double *x, con
     } else if (x_prescaled && !(A.unit && A.col_scale)) {
         set_error("internal: pre-scaled vector for a plan without column scale");
         return TRON_EINVAL;
+    }
+    if (single_sums(A)) {
+        const int g = launch_single<EPI_AXPY>(ds, A, slot, x, EpiArgs{out, add, alpha, dot_self, nullptr, add ? ds->partials : nullptr, finish_for(ds, add ? first : -1, A.nblocks)}, square);
+        return (g < 0 || add) ? g : 0;
     }
     if (A.plain) {
         TRON_TRY(launch_plain<EPI_AXPY>(ds, A, slot, x, out, add, alpha, square));
@@ -1784,6 +1998,10 @@ PlanBytes plan_bytes(const CsrPlan &A)
         const int64_t acc = 8 * (int64_t)kTileSlices * H.blocks_per_slice * kTileSlots;
         b.tiles = H.ntiles_total * (kChunk * (2 + vbytes) + kBlock + (int64_t)sizeof(int4)) + 2 * H.nseg_padded + 8 * H.span_total + acc;
         b.tile_reduce = acc + 8 * (int64_t)kTileSlices * kTileSlots;
+    }
+    if (A.direct) {   // row ranges and segment numbers, addend and result, no partial sums
+        b.ranges += 4 * A.rows + 16 * A.rows - 8 * nseg_ranges;
+        return b;
     }
     // combine: every partial sum once, the row mask, the group table, the result; plus what the plan's extras need per row
     b.combine = 8 * A.nseg_total + 2 * A.rows + (int64_t)sizeof(GroupBase) * A.ngroups + 8 * A.rows;

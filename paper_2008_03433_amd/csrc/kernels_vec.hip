@@ -24,11 +24,9 @@ __global__ __launch_bounds__(kBlock) void k_reduce_final(const double *__restric
     }
 }
 
-// Automatic rule: only launches of up to kFuseMaxGrid workgroups complete their own reduction.  Every workgroup pays a
-// device-wide fence and a ticket (a few microseconds, overlapped only if there are few of them); measured: with 5
-// workgroups a solve of the smallest sparse configuration takes 0.42 instead of 0.49 ms, with 47 nothing is gained, with
-// 2048 a combine kernel takes 65 instead of 36 us.
-constexpr int kFuseMaxGrid = 32;
+// Automatic rule: launches of up to kFuseMaxGrid workgroups complete their own reduction.  The tickets are drawn one after the
+// other, about 10 ns each, against the 4 to 5 us of a launch that adds the sums.
+constexpr int kFuseMaxGrid = 256;
 Finish finish_for(tron_dataset *ds, int first_scalar, int grid)
 {
     const bool fuse = ds->ticket && first_scalar >= 0 &&
@@ -45,15 +43,6 @@ int reduce_final(tron_dataset *ds, int nslots, int count, int stride, int first_
     }
     ProfScope ps(ds, SLOT_REDUCE_FINAL);
     hipLaunchKernelGGL(k_reduce_final, dim3(nslots), dim3(kBlock), 0, ds->stream, ds->partials, count, stride,
-                       ds->scal_dev, ds->scal_copy, first_scalar);
-    TRON_HIP(hipGetLastError());
-    return TRON_OK;
-}
-
-int reduce_cg_regions(tron_dataset *ds, int region, int nregions, int count, int first_scalar)
-{
-    ProfScope ps(ds, SLOT_REDUCE_FINAL);
-    hipLaunchKernelGGL(k_reduce_final, dim3(nregions), dim3(kBlock), 0, ds->stream, ds->cg_partials + (size_t)region * kMaxGrid, count, kMaxGrid,
                        ds->scal_dev, ds->scal_copy, first_scalar);
     TRON_HIP(hipGetLastError());
     return TRON_OK;
@@ -89,14 +78,14 @@ __global__ __launch_bounds__(kBlock) void k_dots(int64_t m, const double *__rest
         if (K > 2) s2 += a2[i] * b2[i];
     }
     s0 = block_sum(s0, lds);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s0;
+    if (threadIdx.x == 0) store_shared(partials + blockIdx.x, s0);
     if (K > 1) {
         s1 = block_sum(s1, lds);
-        if (threadIdx.x == 0) partials[stride + blockIdx.x] = s1;
+        if (threadIdx.x == 0) store_shared(partials + stride + blockIdx.x, s1);
     }
     if (K > 2) {
         s2 = block_sum(s2, lds);
-        if (threadIdx.x == 0) partials[2 * stride + blockIdx.x] = s2;
+        if (threadIdx.x == 0) store_shared(partials + 2 * stride + blockIdx.x, s2);
     }
     finish_partials<K>(fin, partials, stride, lds);
 }
@@ -113,6 +102,32 @@ int dot_partials(tron_dataset *ds, int64_t m, const double *a0, const double *b0
         hipLaunchKernelGGL(k_dots<2>, dim3(g), dim3(kBlock), 0, ds->stream, m, a0, b0, a1, b1, a2, b2, ds->partials, kMaxGrid, fin);
     else
         hipLaunchKernelGGL(k_dots<1>, dim3(g), dim3(kBlock), 0, ds->stream, m, a0, b0, a1, b1, a2, b2, ds->partials, kMaxGrid, fin);
+    TRON_HIP(hipGetLastError());
+    return g;
+}
+
+// dst = src;  partial slot 0 = src.src
+__global__ __launch_bounds__(kBlock) void k_copy_norm(int64_t m, const double *__restrict__ src, double *__restrict__ dst,
+                                                      double *__restrict__ partials, Finish fin)
+{
+    __shared__ double lds[kWavesPerBlock];
+    double acc = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < m; i += (int64_t)gridDim.x * kBlock) {
+        const double x = src[i];
+        dst[i] = x;
+        acc += x * x;
+    }
+    acc = block_sum(acc, lds);
+    if (threadIdx.x == 0) store_shared(partials + blockIdx.x, acc);
+    finish_partials<1>(fin, partials, 0, lds);
+}
+
+int copy_norm(tron_dataset *ds, int64_t m, const double *src, double *dst, int first)
+{
+    ProfScope ps(ds, SLOT_DOT);
+    const int g = vec_grid(m);
+    const Finish fin = finish_for(ds, first, g);
+    hipLaunchKernelGGL(k_copy_norm, dim3(g), dim3(kBlock), 0, ds->stream, m, src, dst, ds->partials, fin);
     TRON_HIP(hipGetLastError());
     return g;
 }
@@ -134,7 +149,7 @@ __global__ __launch_bounds__(kBlock) void k_loss_terms(int64_t n, const double *
         acc += a;
     }
     acc = block_sum(acc, lds);
-    if (threadIdx.x == 0) partials[blockIdx.x] = acc;
+    if (threadIdx.x == 0) store_shared(partials + blockIdx.x, acc);
     finish_partials<1>(fin, partials, 0, lds);
 }
 
@@ -160,17 +175,12 @@ int loss_terms(tron_dataset *ds, int loss, const double *z, double *zhat, double
 template <bool PRE>
 __global__ __launch_bounds__(kBlock) void k_cg_init(int64_t d, const double *__restrict__ g, const double *__restrict__ M,
                                                     double *__restrict__ s, double *__restrict__ r, double *__restrict__ p,
-                                                    double *__restrict__ partials, Finish fin, double rr0, double *__restrict__ scal,
-                                                    double *__restrict__ scal_copy)
+                                                    double *__restrict__ partials, Finish fin, double rr0, double *__restrict__ scal_copy)
 {
     __shared__ double lds[kWavesPerBlock];
     if (rr0 >= 0.0 && blockIdx.x == 0 && threadIdx.x == 0) {
-        scal[kScalRR] = rr0;
-        scal_copy[kScalRR] = rr0;
-        for (int q = 0; q < 2; ++q) {
-            scal[kScalFlag + q] = 0.0;
-            scal_copy[kScalFlag + q] = 0.0;
-        }
+        scal_copy[kScalRR] = rr0;   // not the host's copies: it waits for what the iterations write there
+        for (int q = 0; q < 2; ++q) scal_copy[kScalFlag + q] = 0.0;
     }
     double acc = 0.0;
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < d; j += (int64_t)gridDim.x * kBlock) {
@@ -183,7 +193,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(int64_t d, const double *__r
     }
     if (PRE) {
         acc = block_sum(acc, lds);
-        if (threadIdx.x == 0) partials[blockIdx.x] = acc;
+        if (threadIdx.x == 0) store_shared(partials + blockIdx.x, acc);
         finish_partials<1>(fin, partials, 0, lds);
     }
 }
@@ -193,8 +203,8 @@ int cg_init(tron_dataset *ds, const double *g, const double *M, double *s, doubl
     ProfScope ps(ds, SLOT_CG_VEC);
     const int gr = vec_grid(ds->d);
     const Finish fin = finish_for(ds, M ? first : -1, gr);   // without M the kernel produces no sum
-    if (M) hipLaunchKernelGGL(k_cg_init<true>, dim3(gr), dim3(kBlock), 0, ds->stream, ds->d, g, M, s, r, p, ds->partials, fin, rr0, ds->scal_dev, ds->scal_copy);
-    else hipLaunchKernelGGL(k_cg_init<false>, dim3(gr), dim3(kBlock), 0, ds->stream, ds->d, g, M, s, r, p, ds->partials, fin, rr0, ds->scal_dev, ds->scal_copy);
+    if (M) hipLaunchKernelGGL(k_cg_init<true>, dim3(gr), dim3(kBlock), 0, ds->stream, ds->d, g, M, s, r, p, ds->partials, fin, rr0, ds->scal_copy);
+    else hipLaunchKernelGGL(k_cg_init<false>, dim3(gr), dim3(kBlock), 0, ds->stream, ds->d, g, M, s, r, p, ds->partials, fin, rr0, ds->scal_copy);
     TRON_HIP(hipGetLastError());
     return gr;
 }
@@ -223,60 +233,98 @@ __device__ __forceinline__ double cg_step_length(const CgStepCtl &c, const doubl
     return (sp >= 0.0) ? gap / __dadd_rn(sp, rad) : __dadd_rn(rad, -sp) / pp;
 }
 
-// The sum of `count` <= kCgDirectGrid per-workgroup partial sums with the order and arithmetic of k_reduce_final, formed
-// by every wavefront on its own: each lane plays its thread of each of that kernel's wavefronts in turn.  No barrier, no
-// LDS, and the loads of several such sums can be in flight together.
-static_assert(kCgDirectGrid <= 2 * kBlock, "two partial sums per thread of the second-stage kernel at most");
+// The sum of `count` per-workgroup partial sums with the order and arithmetic of k_reduce_final, formed
+// by every wavefront on its own: each lane plays its thread of each of that kernel's wavefronts in turn (those that have
+// anything to add).  No barrier, no LDS, and the loads of several such sums can be in flight together.
 __device__ __forceinline__ double sum_of_partials(const double *__restrict__ p, int count)
 {
+    constexpr int kAtOnce = 3;
     const int lane = threadIdx.x & (kWave - 1);
-    double a[kWavesPerBlock];
-#pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) {
-        const int b = w * kWave + lane;
-        const double x = p[b < count ? b : 0], y = p[b + kBlock < count ? b + kBlock : 0];
-        a[w] = (0.0 + (b < count ? x : 0.0)) + (b + kBlock < count ? y : 0.0);
-    }
     double t = 0.0;
+    if (count <= kWave) return wave_sum(lane < count ? p[lane] : 0.0);   // the other wavefronts add zeros
+    double a[kWavesPerBlock] = {0.0, 0.0, 0.0, 0.0};
+    for (int b0 = 0; b0 < count; b0 += kAtOnce * kBlock) {
+        double x[kAtOnce][kWavesPerBlock];
+#pragma unroll
+        for (int k = 0; k < kAtOnce; ++k) {
+#pragma unroll
+            for (int w = 0; w < kWavesPerBlock; ++w) {
+                const int b = b0 + k * kBlock + w * kWave + lane;
+                x[k][w] = b < count ? p[b] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kAtOnce; ++k) {
+#pragma unroll
+            for (int w = 0; w < kWavesPerBlock; ++w) a[w] += x[k][w];
+        }
+    }
 #pragma unroll
     for (int w = 0; w < kWavesPerBlock; ++w) t += wave_sum(a[w]);
     return t;
 }
 
-// s += a p;  r -= a Hp with a = the step length above;  region CGP_RR = partial sums of r.r (PRE: r.(r / M));  scalar 4 = a,
-// the iteration's flag slot = whether the step went to the boundary.  Nothing at all if the run had ended.
+// Elements a thread of the step and direction kernels holds at a time.  The first are asked for before the scalars the kernel
+// starts from, so that the two latencies overlap.
+constexpr int kCgAtOnce = 4;
+
+// The new r.r of iteration c.it to its slot, for the kernels after this one, and with the boundary flag as its sign bit for the
+// host, which waits for that word (see cg_solve).
+__device__ __forceinline__ void post_rr(const CgStepCtl &c, double *scal, double *scal_copy, double rr, bool boundary)
+{
+    const int slot = kScalRR + ((c.it + 1) & 1);
+    scal_copy[slot] = rr;
+    __hip_atomic_store(scal + slot, boundary ? -rr : rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// s += a p;  r -= a Hp with a = the step length above;  region CGP_RR = partial sums of r.r (PRE: r.(r / M));  the iteration's flag slot = whether the step went to the boundary.  Nothing at all if the run had ended.
 template <bool PRE>
 __global__ __launch_bounds__(kBlock) void k_cg_step(int64_t d, CgStepCtl ctl, int n_dir, int n_php, const double *__restrict__ php, const double *__restrict__ sc, const double *__restrict__ p,
                                                     const double *__restrict__ Hp, const double *__restrict__ M,
                                                     double *__restrict__ s, double *__restrict__ r, double *__restrict__ cgp,
-                                                    double *__restrict__ scal, double *__restrict__ scal_copy)
+                                                    double *__restrict__ scal_copy)
 {
     __shared__ double lds[kWavesPerBlock];
+    const int64_t j0 = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    double vp[kCgAtOnce], vh[kCgAtOnce], vs[kCgAtOnce], vr[kCgAtOnce], vm[kCgAtOnce];
+    auto fetch = [&](int64_t from) {
+#pragma unroll
+        for (int k = 0; k < kCgAtOnce; ++k) {
+            const int64_t j = from + k * stride;
+            const int64_t at = j < d ? j : 0;
+            vp[k] = p[at];
+            vh[k] = Hp[at];
+            vs[k] = s[at];
+            vr[k] = r[at];
+            if (PRE) vm[k] = M[at];
+        }
+    };
+    fetch(j0);
     if (cg_run_ended(ctl, sc)) return;
     double pp = 0.0, sp = 0.0, ss = 0.0;
-    if (ctl.it > 0 && n_dir > 0) {   // what the direction kernel before left, one partial sum per workgroup
+    if (ctl.it > 0) {   // what the direction kernel before left, one partial sum per workgroup
         pp = sum_of_partials(cgp + (size_t)CGP_PP * kMaxGrid, n_dir);
         sp = sum_of_partials(cgp + (size_t)CGP_SP * kMaxGrid, n_dir);
         ss = sum_of_partials(cgp + (size_t)CGP_SS * kMaxGrid, n_dir);
-    } else if (ctl.it > 0) {   // added up by a launch in between
-        pp = sc[1];
-        sp = sc[2];
-        ss = sc[3];
     }
     const double pHp = n_php > 0 ? sum_of_partials(php, n_php) : sc[0];   // left by the product's last kernel, or added up by a launch
     bool boundary;
     const double alpha = cg_step_length(ctl, sc, pHp, pp, sp, ss, boundary);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        scal[4] = alpha;
-        scal[kScalFlag + (ctl.it & 1)] = boundary ? 1.0 : 0.0;
         scal_copy[kScalFlag + (ctl.it & 1)] = boundary ? 1.0 : 0.0;   // read by the kernels after this one only
     }
     double acc = 0.0;
-    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < d; j += (int64_t)gridDim.x * kBlock) {
-        s[j] = fma(alpha, p[j], s[j]);
-        const double rj = fma(-alpha, Hp[j], r[j]);
-        r[j] = rj;
-        acc += rj * (PRE ? rj / M[j] : rj);
+    for (int64_t from = j0; from < d; from += kCgAtOnce * stride) {
+        if (from > j0) fetch(from);
+#pragma unroll
+        for (int k = 0; k < kCgAtOnce; ++k) {
+            const int64_t j = from + k * stride;
+            if (j >= d) break;
+            s[j] = fma(alpha, vp[k], vs[k]);
+            const double rj = fma(-alpha, vh[k], vr[k]);
+            r[j] = rj;
+            acc += rj * (PRE ? rj / vm[k] : rj);
+        }
     }
     acc = block_sum(acc, lds);
     if (threadIdx.x == 0) cgp[(size_t)CGP_RR * kMaxGrid + blockIdx.x] = acc;
@@ -296,8 +344,8 @@ int cg_step(tron_dataset *ds, const CgStepCtl &ctl, int n_dir, int n_php, const 
 {
     ProfScope ps(ds, SLOT_CG_VEC);
     const int g = cg_grid(ds->d);
-    if (M) hipLaunchKernelGGL(k_cg_step<true>, dim3(g), dim3(kBlock), 0, ds->stream, ds->d, ctl, n_dir, n_php, ds->partials, ds->scal_copy, p, Hp, M, s, r, ds->cg_partials, ds->scal_dev, ds->scal_copy);
-    else hipLaunchKernelGGL(k_cg_step<false>, dim3(g), dim3(kBlock), 0, ds->stream, ds->d, ctl, n_dir, n_php, ds->partials, ds->scal_copy, p, Hp, M, s, r, ds->cg_partials, ds->scal_dev, ds->scal_copy);
+    if (M) hipLaunchKernelGGL(k_cg_step<true>, dim3(g), dim3(kBlock), 0, ds->stream, ds->d, ctl, n_dir, n_php, ds->partials, ds->scal_copy, p, Hp, M, s, r, ds->cg_partials, ds->scal_copy);
+    else hipLaunchKernelGGL(k_cg_step<false>, dim3(g), dim3(kBlock), 0, ds->stream, ds->d, ctl, n_dir, n_php, ds->partials, ds->scal_copy, p, Hp, M, s, r, ds->cg_partials, ds->scal_copy);
     TRON_HIP(hipGetLastError());
     return g;
 }
@@ -313,29 +361,48 @@ __global__ __launch_bounds__(kBlock) void k_cg_dir(int64_t d, CgStepCtl ctl, int
                                                    double *__restrict__ scal_copy)
 {
     __shared__ double lds[kWavesPerBlock];
+    const int64_t j0 = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    double vp[kCgAtOnce], vr[kCgAtOnce], vs[kCgAtOnce], vm[kCgAtOnce];
+    auto fetch = [&](int64_t from) {
+#pragma unroll
+        for (int k = 0; k < kCgAtOnce; ++k) {
+            const int64_t j = from + k * stride;
+            const int64_t at = j < d ? j : 0;
+            vp[k] = p[at];
+            vr[k] = r[at];
+            vs[k] = s[at];
+            if (PRE) vm[k] = M[at];
+        }
+    };
+    fetch(j0);
     if (cg_run_ended(ctl, sc)) return;
     const double rr_old = sc[kScalRR + (ctl.it & 1)];
-    const double rr_new = n_step > 0 ? sum_of_partials(cgp + (size_t)CGP_RR * kMaxGrid, n_step) : sc[kScalRR + ((ctl.it + 1) & 1)];
-    if (n_step > 0 && blockIdx.x == 0 && threadIdx.x == 0) {   // read by the kernels after this one only (this one reads the other slot)
-        scal[kScalRR + ((ctl.it + 1) & 1)] = rr_new;
-        scal_copy[kScalRR + ((ctl.it + 1) & 1)] = rr_new;
+    const double rr_new = sum_of_partials(cgp + (size_t)CGP_RR * kMaxGrid, n_step);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {   // read by the kernels after this one only (this one reads the other slot)
+        post_rr(ctl, scal, scal_copy, rr_new, sc[kScalFlag + (ctl.it & 1)] != 0.0);
     }
-    if (sc[kScalFlag + (ctl.it & 1)] != 0.0 || sqrt(rr_new) <= ctl.tol) return;
+    if (ctl.last || sc[kScalFlag + (ctl.it & 1)] != 0.0 || sqrt(rr_new) <= ctl.tol) return;
     const double beta = rr_new / rr_old;
     double pp = 0.0, sp = 0.0, ss = 0.0;
-    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < d; j += (int64_t)gridDim.x * kBlock) {
-        const double m = PRE ? M[j] : 1.0;
-        const double pj = fma(beta, p[j], PRE ? r[j] / m : r[j]);
-        const double sj = s[j];
-        p[j] = pj;
-        if (PRE) {
-            pp += m * pj * pj;
-            sp += m * sj * pj;
-            ss += m * sj * sj;
-        } else {
-            pp += pj * pj;
-            sp += sj * pj;
-            ss += sj * sj;
+    for (int64_t from = j0; from < d; from += kCgAtOnce * stride) {
+        if (from > j0) fetch(from);
+#pragma unroll
+        for (int k = 0; k < kCgAtOnce; ++k) {
+            const int64_t j = from + k * stride;
+            if (j >= d) break;
+            const double m = PRE ? vm[k] : 1.0;
+            const double pj = fma(beta, vp[k], PRE ? vr[k] / m : vr[k]);
+            const double sj = vs[k];
+            p[j] = pj;
+            if (PRE) {
+                pp += m * pj * pj;
+                sp += m * sj * pj;
+                ss += m * sj * sj;
+            } else {
+                pp += pj * pj;
+                sp += sj * pj;
+                ss += sj * sj;
+            }
         }
     }
     pp = block_sum(pp, lds);
@@ -356,7 +423,106 @@ int cg_dir(tron_dataset *ds, const CgStepCtl &ctl, int n_step, const double *r, 
     return g;
 }
 
-// wnew = w + s;  partial slots: 0 = g.s, 1 = s.r, 2 = s.s (PRE: s.Ms)
+// Both of the above in one launch for d <= kCgSmallD: a single workgroup holds the vectors in registers, so nothing has to be
+// exchanged between workgroups.  The sums p.p, s.p, s.s stay in scalars 1..3.  2,000 x 5,000: the two launches took 4.0 and
+// 3.0 us, one after the other with the products.
+constexpr int kCgSmallBlock = 1024, kCgSmallPer = 8;
+static_assert(kCgSmallD == kCgSmallBlock * kCgSmallPer, "eight elements of each vector per thread");
+template <int N>
+__device__ __forceinline__ void small_sums(double (&v)[N], double (*lds)[kCgSmallBlock / kWave])
+{
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    __syncthreads();   // lds may still be read from the sums before
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        v[k] = wave_sum(v[k]);
+        if (lane == 0) lds[k][wv] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = sum16(lds[k][lane & 15]);
+}
+
+template <bool PRE>
+__global__ __launch_bounds__(kCgSmallBlock) void k_cg_small(int d, CgStepCtl ctl, int n_php, const double *__restrict__ php, double *scal, double *scal_copy,
+                                                            const double *__restrict__ Hp, const double *__restrict__ M, double *__restrict__ s,
+                                                            double *__restrict__ r, double *__restrict__ p)
+{
+    __shared__ double lds[3][kCgSmallBlock / kWave];
+    const int tid = threadIdx.x;
+    double vp[kCgSmallPer], vh[kCgSmallPer], vs[kCgSmallPer], vr[kCgSmallPer], vm[kCgSmallPer];
+#pragma unroll
+    for (int k = 0; k < kCgSmallPer; ++k) {
+        const int j = tid + k * kCgSmallBlock;
+        if (k * kCgSmallBlock >= d) break;   // uniform
+        const int at = j < d ? j : 0;
+        vp[k] = p[at];
+        vh[k] = Hp[at];
+        vs[k] = s[at];
+        vr[k] = r[at];
+        if (PRE) vm[k] = M[at];
+    }
+    if (cg_run_ended(ctl, scal_copy)) return;
+    double one[1] = {0.0};
+    for (int b = tid; b < n_php; b += kCgSmallBlock) one[0] += php[b];
+    small_sums(one, lds);
+    const double pHp = n_php > 0 ? one[0] : scal_copy[0];
+    bool boundary;
+    const double alpha = cg_step_length(ctl, scal_copy, pHp, scal_copy[1], scal_copy[2], scal_copy[3], boundary);
+    const double rr_old = scal_copy[kScalRR + (ctl.it & 1)];
+    one[0] = 0.0;
+#pragma unroll
+    for (int k = 0; k < kCgSmallPer; ++k) {
+        const int j = tid + k * kCgSmallBlock;
+        if (k * kCgSmallBlock >= d) break;
+        if (j < d) {
+            vs[k] = fma(alpha, vp[k], vs[k]);
+            s[j] = vs[k];
+            vr[k] = fma(-alpha, vh[k], vr[k]);
+            r[j] = vr[k];
+            one[0] += vr[k] * (PRE ? vr[k] / vm[k] : vr[k]);
+        }
+    }
+    small_sums(one, lds);
+    const double rr = one[0];
+    if (tid == 0) {
+        scal_copy[kScalFlag + (ctl.it & 1)] = boundary ? 1.0 : 0.0;
+        post_rr(ctl, scal, scal_copy, rr, boundary);
+    }
+    if (ctl.last || boundary || sqrt(rr) <= ctl.tol) return;
+    const double beta = rr / rr_old;
+    double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kCgSmallPer; ++k) {
+        const int j = tid + k * kCgSmallBlock;
+        if (k * kCgSmallBlock >= d) break;
+        if (j < d) {
+            const double m = PRE ? vm[k] : 1.0;
+            const double pj = fma(beta, vp[k], PRE ? vr[k] / m : vr[k]);
+            p[j] = pj;
+            v[0] += m * pj * pj;
+            v[1] += m * vs[k] * pj;
+            v[2] += m * vs[k] * vs[k];
+        }
+    }
+    small_sums(v, lds);
+    if (tid == 0) {
+        scal_copy[1] = v[0];
+        scal_copy[2] = v[1];
+        scal_copy[3] = v[2];
+    }
+}
+
+int cg_small(tron_dataset *ds, const CgStepCtl &ctl, int n_php, const double *Hp, const double *M, double *s, double *r, double *p)
+{
+    ProfScope ps(ds, SLOT_CG_VEC);
+    if (M) hipLaunchKernelGGL(k_cg_small<true>, dim3(1), dim3(kCgSmallBlock), 0, ds->stream, (int)ds->d, ctl, n_php, ds->partials, ds->scal_dev, ds->scal_copy, Hp, M, s, r, p);
+    else hipLaunchKernelGGL(k_cg_small<false>, dim3(1), dim3(kCgSmallBlock), 0, ds->stream, (int)ds->d, ctl, n_php, ds->partials, ds->scal_dev, ds->scal_copy, Hp, M, s, r, p);
+    TRON_HIP(hipGetLastError());
+    return TRON_OK;
+}
+
+// wnew = w + s;  partial slots: 0 = g.s, 1 = s.r, 2 = s.s (PRE: s.Ms), 3 = wnew.wnew
 template <bool PRE>
 __global__ __launch_bounds__(kBlock) void k_trial_point(int64_t d, const double *__restrict__ w, const double *__restrict__ s,
                                                         const double *__restrict__ g, const double *__restrict__ r,
@@ -364,21 +530,25 @@ __global__ __launch_bounds__(kBlock) void k_trial_point(int64_t d, const double 
                                                         double *__restrict__ partials, int stride, Finish fin)
 {
     __shared__ double lds[kWavesPerBlock];
-    double gs = 0.0, sr = 0.0, ss = 0.0;
+    double gs = 0.0, sr = 0.0, ss = 0.0, ww = 0.0;
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < d; j += (int64_t)gridDim.x * kBlock) {
         const double sj = s[j];
-        wnew[j] = w[j] + sj;
+        const double wj = w[j] + sj;
+        wnew[j] = wj;
+        ww += wj * wj;
         gs += g[j] * sj;
         sr += sj * r[j];
         ss += PRE ? M[j] * sj * sj : sj * sj;
     }
     gs = block_sum(gs, lds);
-    if (threadIdx.x == 0) partials[blockIdx.x] = gs;
+    if (threadIdx.x == 0) store_shared(partials + blockIdx.x, gs);
     sr = block_sum(sr, lds);
-    if (threadIdx.x == 0) partials[stride + blockIdx.x] = sr;
+    if (threadIdx.x == 0) store_shared(partials + stride + blockIdx.x, sr);
     ss = block_sum(ss, lds);
-    if (threadIdx.x == 0) partials[2 * stride + blockIdx.x] = ss;
-    finish_partials<3>(fin, partials, stride, lds);
+    if (threadIdx.x == 0) store_shared(partials + 2 * stride + blockIdx.x, ss);
+    ww = block_sum(ww, lds);
+    if (threadIdx.x == 0) store_shared(partials + 3 * stride + blockIdx.x, ww);
+    finish_partials<4>(fin, partials, stride, lds);
 }
 
 int trial_point(tron_dataset *ds, const double *w, const double *s, const double *g, const double *r, const double *M,

@@ -3,6 +3,7 @@
 // All vectors stay in device memory; per CG iteration the host reads back a handful of scalars.
 #include <cmath>
 #include <cstring>
+#include <thread>
 
 #include "common.h"
 
@@ -10,12 +11,13 @@ namespace tron {
 
 // f(w) for the sparse layout: z = X w, loss terms (zhat, D into Dbuf[Dslot]), f = 1/2 w.w + C sum loss.
 // The dense layout computes the same together with the gradient sums in one fused pass.
-int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot)   // scalar 0 = sum of the loss terms, scalar 1 = w.w
+int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot, bool ww)   // scalar 0 = sum of the loss terms, scalar 1 = w.w if ww
 {
     // with unit plans zhat is stored already multiplied by the instances' values, as the transposed plan gathers it
     const int gl = spmv_loss(ds, ds->fwd, SLOT_SPMV_FWD, loss, w, ds->z, ds->zhat, ds->Dbuf[Dslot], ds->bwd.col_scale, 0);
     TRON_TRY(gl);
     TRON_TRY(reduce_final(ds, 1, gl, 0, 0));
+    if (!ww) return TRON_OK;
     const int gw = dot_partials(ds, ds->d, w, w, nullptr, nullptr, nullptr, nullptr, 1);
     TRON_TRY(gw);
     TRON_TRY(reduce_final(ds, 1, gw, 0, 1));
@@ -24,7 +26,7 @@ int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot)   // sca
 
 int fun_eval(tron_dataset *ds, int loss, double C, const double *w, int Dslot, double *f_out)
 {
-    TRON_TRY(fun_enqueue(ds, loss, w, Dslot));
+    TRON_TRY(fun_enqueue(ds, loss, w, Dslot, true));
     TRON_TRY(read_scalars(ds, 2));
     *f_out = 0.5 * ds->scal_host[1] + C * ds->scal_host[0];
     return TRON_OK;
@@ -57,10 +59,11 @@ int hv_enqueue(tron_dataset *ds, double C, const double *v, double *Hv, int *vhv
     if (ds->dense) return dense_hv(ds, C, ds->Dcur, v, Hv);
     const double *D = ds->Dbuf[ds->Dcur];
     TRON_TRY(spmv_scale(ds, ds->fwd, SLOT_SPMV_FWD, v, D, ds->z, ds->bwd.col_scale));   // a1 = D (X v)
-    const bool direct = vhv_partials && vec_workgroups(ds->d) <= kCgDirectGrid;
+    const bool one = single_sums(ds->bwd);   // at most kDirectMaxSums of them
+    const bool direct = vhv_partials && (one || vec_workgroups(ds->d) <= kCgDirectGrid);
     const int g = spmv_axpy(ds, ds->bwd, SLOT_SPMV_BWD, ds->z, v, C, false, Hv, false, ds->bwd.col_scale != nullptr, direct ? -1 : 0);  // Hv = v + C X^T a1
     TRON_TRY(g);
-    if (direct && g <= kCgDirectGrid) {
+    if (direct && (one || g <= kCgDirectGrid)) {
         *vhv_partials = g;
         return TRON_OK;
     }
@@ -91,7 +94,7 @@ int ensure_solver_vectors(tron_dataset *ds, bool precond)
 // Scalar slots of the outer loop, apart from 0..3 of the evaluation: what one wait of the host brings back together.
 constexpr int kScalGG = 2;      // g.g of the sparse gradient (the dense pass leaves it there as well)
 constexpr int kScalTrial = 10;  // g.s, s.r, s.s of the trial point
-constexpr int kScalW0 = 13;     // w0.w0
+constexpr int kScalWW = 13;     // w.w at the trial point (the fourth of those sums); w0.w0 at the start
 
 // Whether a product with X is cheap enough to be spent on a guess (kernels enqueued before the host knows that their
 // result is wanted), as against one idle gap of the device per wait of the host.
@@ -105,7 +108,7 @@ bool products_cheap(const tron_dataset *ds)
 int eval_enqueue(tron_dataset *ds, const tron_params &P, const double *w, int Dslot, double *gout, bool with_grad)
 {
     if (ds->dense) return dense_fun_grad(ds, P.loss, P.C, w, Dslot, gout);
-    TRON_TRY(fun_enqueue(ds, P.loss, w, Dslot));
+    TRON_TRY(fun_enqueue(ds, P.loss, w, Dslot, false));   // w.w is in kScalWW already
     if (with_grad) TRON_TRY(grad_enqueue(ds, P.C, w, gout, kScalGG));
     return TRON_OK;
 }
@@ -113,7 +116,7 @@ int eval_enqueue(tron_dataset *ds, const tron_params &P, const double *w, int Ds
 // What eval_enqueue's kernels left, after a wait; *gnorm only where the gradient was formed.
 void eval_result(tron_dataset *ds, const tron_params &P, int Dslot, bool with_grad, double *f, double *gnorm)
 {
-    *f = 0.5 * ds->scal_host[1] + P.C * ds->scal_host[0];
+    *f = 0.5 * ds->scal_host[ds->dense ? 1 : kScalWW] + P.C * ds->scal_host[0];
     if (ds->dense) {
         ds->active_frac[Dslot] = ds->scal_host[3] / (double)ds->n;
         ds->active_count[Dslot] = (int64_t)ds->scal_host[3];
@@ -127,10 +130,36 @@ void eval_result(tron_dataset *ds, const tron_params &P, int Dslot, bool with_gr
 // With a diagonal preconditioner M (not null): z = r / M replaces r in p and in the dot products r.r, and the lengths
 // are M-norms (the iteration is plain CG in the variables M^(1/2) s); gscaled = sqrt(g.M^-1 g) takes the place of |g|.
 // One wait per iteration: the step kernel forms alpha (or the step to the boundary) from the scalars the device keeps,
-// the direction kernel forms beta, and the host reads the new r.r and the boundary flag of iteration k once its kernels
-// have run.  Where a product is cheap the kernels of iteration k + 1 are enqueued before that wait, so the device never
+// the direction kernel forms beta and posts the new r.r, with the boundary flag as its sign, to the iteration's word in
+// pinned memory, for which the host polls (an event recorded behind every iteration costs the device a gap of 2 us).  Where a
+// product is cheap the kernels of iteration k + 1 are enqueued before that wait, so the device never
 // idles while the host decides; if iteration k turns out to be the last, those kernels find that out by themselves and
 // leave s and r alone (see CgStepCtl) -- one product computed for nothing per run, against one idle gap per iteration.
+// The word of an iteration is marked before its kernels are enqueued; nothing else writes it.
+constexpr uint64_t kUnset = 0x7ff4dead00c0ffeeull;   // a NaN that no arithmetic returns
+
+int wait_for_word(tron_dataset *ds, const double *word, double *value)
+{
+    const uint64_t *w = reinterpret_cast<const uint64_t *>(word);
+    for (unsigned spins = 1;; ++spins) {
+        const uint64_t v = __atomic_load_n(w, __ATOMIC_ACQUIRE);
+        if (v != kUnset) {
+            std::memcpy(value, &v, sizeof(v));
+            return TRON_OK;
+        }
+        if ((spins & 1023u) != 0) { __builtin_ia32_pause(); continue; }
+        // nothing for a while: make sure that the kernels are still running
+        const hipError_t e = hipStreamQuery(ds->stream);
+        (void)hipGetLastError();
+        if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(e, "hipStreamQuery", __FILE__, __LINE__);
+        if (e == hipSuccess && __atomic_load_n(w, __ATOMIC_ACQUIRE) == kUnset) {
+            set_error("internal: a CG iteration has ended without its result");
+            return TRON_ESTATE;
+        }
+        std::this_thread::yield();
+    }
+}
+
 int cg_solve(tron_dataset *ds, const tron_params &P, const double *M, double delta, double gscaled, int *n_hv, int *on_boundary)
 {
     double *g = ds->sv[V_G], *s = ds->sv[V_S], *r = ds->sv[V_R], *p = ds->sv[V_P], *Hp = ds->sv[V_HP];
@@ -138,41 +167,33 @@ int cg_solve(tron_dataset *ds, const tron_params &P, const double *M, double del
     const double tol = P.cg_xi * gscaled;
     *on_boundary = 0;
     *n_hv = 0;
-    for (hipEvent_t &e : ds->cg_event)
-        if (!e) TRON_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     TRON_TRY(cg_init(ds, g, M, s, r, p, -1, rr0));
     if (std::sqrt(rr0) <= tol) return TRON_OK;
     const bool ahead = g_tuning.cg_speculate > 0 || (g_tuning.cg_speculate < 0 && products_cheap(ds));
     int n_dir = 0;   // workgroups of the direction kernel enqueued last
     auto enqueue = [&](int it) -> int {
+        const uint64_t unset = kUnset;
+        __atomic_store_n(reinterpret_cast<uint64_t *>(ds->scal_host + kScalRR + ((it + 1) & 1)), unset, __ATOMIC_RELEASE);
         int n_php = 0;   // per-workgroup partial sums of p.Hp left for the step kernel (0: the sum is in scalar 0)
         TRON_TRY(hv_enqueue(ds, P.C, p, Hp, &n_php));
-        const CgStepCtl ctl{tol, delta, it};
+        const CgStepCtl ctl{tol, delta, it, it + 1 >= P.max_cg};
+        if (ds->d <= kCgSmallD) return cg_small(ds, ctl, n_php, Hp, M, s, r, p);
         const int g1 = cg_step(ds, ctl, n_dir, n_php, p, Hp, M, s, r);
         TRON_TRY(g1);
-        const bool direct = g1 <= kCgDirectGrid;   // the consumer adds up the partial sums itself
-        const bool last = it + 1 >= P.max_cg;      // the last iteration allowed: no direction after it
-        if (!direct || last) TRON_TRY(reduce_cg_regions(ds, CGP_RR, 1, g1, kScalRR + ((it + 1) & 1)));
-        if (!last) {
-            const int g2 = cg_dir(ds, ctl, direct ? g1 : 0, r, s, M, p);
-            TRON_TRY(g2);
-            if (!direct) TRON_TRY(reduce_cg_regions(ds, CGP_PP, 3, g2, 1));
-            n_dir = direct ? g2 : 0;
-        }
-        TRON_HIP(hipEventRecord(ds->cg_event[it & 1], ds->stream));
-        return TRON_OK;
+        n_dir = cg_dir(ds, ctl, g1, r, s, M, p);
+        return n_dir < 0 ? n_dir : TRON_OK;
     };
     TRON_TRY(enqueue(0));
     for (int it = 0;; ++it) {
         const bool more = it + 1 < P.max_cg;
         if (ahead && more) TRON_TRY(enqueue(it + 1));
-        TRON_HIP(hipEventSynchronize(ds->cg_event[it & 1]));
+        double rr;
+        TRON_TRY(wait_for_word(ds, ds->scal_host + kScalRR + ((it + 1) & 1), &rr));
         *n_hv = it + 1;
-        if (ds->scal_host[kScalFlag + (it & 1)] != 0.0) {
+        if (std::signbit(rr) && !std::isnan(rr)) {
             *on_boundary = 1;
             break;
         }
-        const double rr = ds->scal_host[kScalRR + ((it + 1) & 1)];
         if (!more || std::sqrt(rr) <= tol) break;
         if (!ahead) TRON_TRY(enqueue(it + 1));
     }
@@ -229,16 +250,15 @@ extern "C" int tron_solve(tron_dataset *ds, const tron_params *params, double *w
     const size_t dbytes = sizeof(double) * ds->d;
     double *&w = ds->sv[V_W], *&wnew = ds->sv[V_WNEW], *&g = ds->sv[V_G], *&gnew = ds->sv[V_GNEW];
     double *s = ds->sv[V_S], *r = ds->sv[V_R];
-    TRON_HIP(hipMemcpyAsync(w, w_dev, dbytes, hipMemcpyDeviceToDevice, ds->stream));
 
-    // f and the gradient at w0, and whether w0 = 0, behind one wait
+    // w = w0, f and the gradient at w0, and whether w0 = 0, behind one wait
     ds->Dcur = 0;
     ds->have_D = false;
     double f, gnorm = 0.0;
     {
-        const int gz = dot_partials(ds, ds->d, w, w, nullptr, nullptr, nullptr, nullptr, kScalW0);
+        const int gz = copy_norm(ds, ds->d, w_dev, w, kScalWW);
         TRON_TRY(gz);
-        TRON_TRY(reduce_final(ds, 1, gz, 0, kScalW0));
+        TRON_TRY(reduce_final(ds, 1, gz, 0, kScalWW));
     }
     TRON_TRY(eval_enqueue(ds, P, w, ds->Dcur, g, true));
     TRON_TRY(read_scalars(ds, kScalars));
@@ -248,7 +268,7 @@ extern "C" int tron_solve(tron_dataset *ds, const tron_params *params, double *w
     res->n_grad++;
     // |grad f(0)|: the reference of the stopping test.  When w0 = 0 it is the first gradient itself; otherwise one more
     // evaluation, whose D goes to the buffer of the trial points.
-    if (ds->scal_host[kScalW0] != 0.0) {
+    if (ds->scal_host[kScalWW] != 0.0) {
         double f0, gn0 = 0.0;
         TRON_HIP(hipMemsetAsync(wnew, 0, dbytes, ds->stream));
         TRON_TRY(eval_enqueue(ds, P, wnew, 1 - ds->Dcur, gnew, true));
@@ -278,7 +298,7 @@ extern "C" int tron_solve(tron_dataset *ds, const tron_params *params, double *w
         // accepted (a rejected step leaves it unused; n_grad counts the gradients of accepted steps either way).
         const int gt = trial_point(ds, w, s, g, r, M, wnew, kScalTrial);
         TRON_TRY(gt);
-        TRON_TRY(reduce_final(ds, 3, gt, kMaxGrid, kScalTrial));
+        TRON_TRY(reduce_final(ds, 4, gt, kMaxGrid, kScalTrial));
         const int trial_slot = 1 - ds->Dcur;   // D of the trial point goes to the other buffer
         const bool grad_ahead = !ds->dense && g_tuning.cg_speculate != 0 && (g_tuning.cg_speculate > 0 || products_cheap(ds));
         TRON_TRY(eval_enqueue(ds, P, wnew, trial_slot, gnew, grad_ahead));
