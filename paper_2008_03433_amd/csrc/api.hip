@@ -9,6 +9,7 @@
 #include <thread>
 
 #include "common.h"
+#include "host_util.h"
 
 namespace tron {
 
@@ -138,9 +139,9 @@ static int check_labels(const double *y, int64_t n)
     return TRON_OK;
 }
 
-// host copies of caller arrays (from host or device memory)
+// host copy of a caller's array in device memory
 template <typename T>
-static int fetch(std::vector<T> &dst, const T *src, size_t count, int mem)
+static int fetch(std::vector<T> &dst, const T *src, size_t count)
 {
     try {
         dst.resize(count);
@@ -148,12 +149,20 @@ static int fetch(std::vector<T> &dst, const T *src, size_t count, int mem)
         set_error("out of host memory staging %zu elements", count);
         return TRON_ENOMEM;
     }
-    if (!count) return TRON_OK;
-    if (mem == TRON_MEM_DEVICE)
-        TRON_HIP(hipMemcpy(dst.data(), src, sizeof(T) * count, hipMemcpyDeviceToHost));
-    else
-        memcpy(dst.data(), src, sizeof(T) * count);
+    if (count) TRON_HIP(hipMemcpy(dst.data(), src, sizeof(T) * count, hipMemcpyDeviceToHost));
     return TRON_OK;
+}
+
+// csr_plan_build for either thread: running out of host memory is an error code
+static int plan_build(CsrPlan &P, int64_t rows, int64_t cols, const int64_t *rowptr, const int32_t *col, const double *val, int parts, bool hot,
+                      bool unit, int64_t cols_used, hipStream_t st)
+{
+    try {
+        return csr_plan_build(P, rows, cols, rowptr, col, val, parts, hot, unit, cols_used, st);
+    } catch (const std::bad_alloc &) {
+        set_error("out of host memory building the sparse layout");
+        return TRON_ENOMEM;
+    }
 }
 
 }  // namespace tron
@@ -194,37 +203,75 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         return TRON_EINVAL;
     }
     TRON_TRY(check_device());
-    std::vector<int64_t> h_rowptr;
-    TRON_TRY(fetch(h_rowptr, rowptr, (size_t)n + 1, mem));
+    // host arrays are read in place
+    std::vector<int64_t> rowptr_copy;
+    std::vector<int32_t> col_copy;
+    std::vector<double> val_copy, y_copy;
+    const int64_t *h_rowptr = rowptr;
+    const int32_t *h_col = col;
+    const double *h_val = val, *h_y = y;
+    if (mem == TRON_MEM_DEVICE) {
+        TRON_TRY(fetch(rowptr_copy, rowptr, (size_t)n + 1));
+        h_rowptr = rowptr_copy.data();
+    }
     if (h_rowptr[0] != 0) { set_error("rowptr[0] = %lld, expected 0", (long long)h_rowptr[0]); return TRON_EINVAL; }
     for (int64_t i = 0; i < n; ++i)
         if (h_rowptr[i + 1] < h_rowptr[i]) { set_error("rowptr decreases at row %lld", (long long)i); return TRON_EINVAL; }
     const int64_t nnz = h_rowptr[n];
     if (nnz > 0 && (!col || !val)) { set_error("col/val are null but nnz = %lld", (long long)nnz); return TRON_EINVAL; }
-    std::vector<int32_t> h_col;
-    std::vector<double> h_val, h_y;
-    TRON_TRY(fetch(h_col, col, (size_t)nnz, mem));
-    TRON_TRY(fetch(h_val, val, (size_t)nnz, mem));
-    TRON_TRY(fetch(h_y, y, (size_t)n, mem));
-    TRON_TRY(check_labels(h_y.data(), n));
-    // columns strictly increasing inside each row and in range; values finite; count per column
+    if (mem == TRON_MEM_DEVICE) {
+        TRON_TRY(fetch(col_copy, col, (size_t)nnz));
+        TRON_TRY(fetch(val_copy, val, (size_t)nnz));
+        TRON_TRY(fetch(y_copy, y, (size_t)n));
+        h_col = col_copy.data();
+        h_val = val_copy.data();
+        h_y = y_copy.data();
+    }
+    TRON_TRY(check_labels(h_y, n));
+    // Columns strictly increasing inside each row and in range; values finite; count per column.  Matrices whose counts fit a
+    // cache per thread are walked by several threads, each a block of rows with equal shares of the entries: the blocks' own
+    // counts say where each of them places its entries in the transposed copy, instances in ascending order.
     std::vector<int64_t> t_rowptr;
+    const unsigned T = (nnz < INT32_MAX && d <= (1 << 19)) ? host_threads(nnz) : 1;
+    HostArray<int32_t> block_count;
+    std::vector<int64_t> block_row(T + 1, n);
     try {
         t_rowptr.assign((size_t)d + 1, 0);
+        if (T > 1) block_count = HostArray<int32_t>((size_t)T * (size_t)d);
     } catch (const std::bad_alloc &) { set_error("out of host memory"); return TRON_ENOMEM; }
-    for (int64_t i = 0; i < n; ++i) {
-        int64_t prev = -1;
-        for (int64_t k = h_rowptr[i]; k < h_rowptr[i + 1]; ++k) {
-            const int64_t c = h_col[k];
-            if (c <= prev || c >= d) {
-                set_error("row %lld: column index %lld out of order or out of range [0,%lld)", (long long)i, (long long)c, (long long)d);
-                return TRON_EINVAL;
+    block_row[0] = 0;
+    for (unsigned t = 1; t < T; ++t) block_row[t] = std::lower_bound(h_rowptr, h_rowptr + n, nnz / T * t) - h_rowptr;
+    struct Fault { int64_t row = -1, col = 0; };   // col < 0: a value that is not finite
+    std::vector<Fault> fault(T);
+    on_threads(T, [&](unsigned t, unsigned) {
+        int32_t *cnt = T > 1 ? block_count.data() + (size_t)t * (size_t)d : nullptr;
+        if (cnt) std::fill(cnt, cnt + d, 0);
+        for (int64_t i = block_row[t]; i < block_row[t + 1]; ++i) {
+            int64_t prev = -1;
+            for (int64_t k = h_rowptr[i]; k < h_rowptr[i + 1]; ++k) {
+                const int64_t c = h_col[k];
+                if (c <= prev || c >= d) { fault[t].row = i; fault[t].col = c; return; }
+                if (!std::isfinite(h_val[k])) { fault[t].row = i; fault[t].col = INT64_MIN; return; }
+                prev = c;
+                if (cnt) cnt[c] += 1;
+                else t_rowptr[c + 1] += 1;
             }
-            if (!std::isfinite(h_val[k])) { set_error("row %lld: non-finite value", (long long)i); return TRON_EINVAL; }
-            prev = c;
-            t_rowptr[c + 1] += 1;
         }
+    });
+    for (const Fault &f : fault) {   // the first in row order
+        if (f.row < 0) continue;
+        if (f.col == INT64_MIN) set_error("row %lld: non-finite value", (long long)f.row);
+        else set_error("row %lld: column index %lld out of order or out of range [0,%lld)", (long long)f.row, (long long)f.col, (long long)d);
+        return TRON_EINVAL;
     }
+    if (T > 1)
+        parallel_ranges(d, (int64_t)T * d, [&](int64_t c0, int64_t c1) {
+            for (unsigned t = 0; t < T; ++t)
+                for (int64_t c = c0; c < c1; ++c) t_rowptr[c + 1] += block_count[(size_t)t * (size_t)d + c];
+        });
+    int64_t cols_used = 0, rows_used = 0;
+    for (int64_t c = 0; c < d; ++c) cols_used += t_rowptr[c + 1] > 0;
+    for (int64_t i = 0; i < n; ++i) rows_used += h_rowptr[i + 1] > h_rowptr[i];
     // Unit plans: when both layouts are partitioned and every instance's entries share one value r_i (binary features,
     // optionally scaled per instance, e.g. normalised to unit length), X = diag(r) B with B binary: the layouts keep no
     // values, the row sums of X are multiplied by r afterwards and X^T gathers from r .* (its vector).
@@ -277,27 +324,49 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
     // explicit transposed copy (d x n): counting sort by column keeps rows ascending inside each column
     for (int64_t j = 0; j < d; ++j) t_rowptr[j + 1] += t_rowptr[j];
     const int64_t t_nnz = t_rowptr[d];
-    std::vector<int32_t> t_col;
-    std::vector<double> t_val;
+    HostArray<int32_t> t_col;
+    HostArray<double> t_val;
     std::vector<int64_t> cursor;
     try {
-        t_col.resize((size_t)t_nnz);
-        if (!unit) t_val.resize((size_t)t_nnz);
-        cursor.assign(t_rowptr.begin(), t_rowptr.end() - 1);
+        t_col = HostArray<int32_t>((size_t)t_nnz);
+        if (!unit) t_val = HostArray<double>((size_t)t_nnz);
+        if (T == 1) cursor.assign(t_rowptr.begin(), t_rowptr.end() - 1);
     } catch (const std::bad_alloc &) { set_error("out of host memory building the transposed copy"); return TRON_ENOMEM; }
-    {
+    if (T > 1) {
+        parallel_ranges(d, (int64_t)T * d, [&](int64_t c0, int64_t c1) {   // the blocks' counts become their first places
+            std::vector<int32_t> at(t_rowptr.begin() + c0, t_rowptr.begin() + c1);
+            for (unsigned t = 0; t < T; ++t)
+                for (int64_t c = c0; c < c1; ++c) {
+                    int32_t &cnt = block_count[(size_t)t * (size_t)d + c];
+                    const int32_t first = at[c - c0];
+                    at[c - c0] += cnt;
+                    cnt = first;
+                }
+        });
+        on_threads(T, [&](unsigned t, unsigned) {
+            int32_t *at = block_count.data() + (size_t)t * (size_t)d;
+            for (int64_t i = block_row[t]; i < block_row[t + 1]; ++i)
+                for (int64_t k = h_rowptr[i]; k < h_rowptr[i + 1]; ++k) {
+                    const int64_t c = h_col[k];
+                    if (nhot && slot_code[c] >= 0) continue;
+                    const int64_t pos = at[c]++;
+                    t_col[pos] = (int32_t)i;
+                    if (!unit) t_val[pos] = h_val[k];
+                }
+        });
+    } else {
         // One host thread per range of features (equal shares of the copy's entries): every thread walks the whole matrix
         // and places the entries of its own features, so the instances stay in ascending order inside a feature and no
         // two threads touch the same cursor.
-        unsigned T = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
-        if (t_nnz < (1 << 20)) T = 1;
-        std::vector<int64_t> bound(T + 1, d);
+        const unsigned F = host_threads(t_nnz);
+        std::vector<int64_t> bound(F + 1, d);
         bound[0] = 0;
-        for (unsigned t = 1; t < T; ++t)
-            bound[t] = std::lower_bound(t_rowptr.begin(), t_rowptr.end(), t_nnz / T * t) - t_rowptr.begin();
-        for (unsigned t = 1; t <= T; ++t) bound[t] = std::min<int64_t>(d, std::max(bound[t], bound[t - 1]));
-        bound[T] = d;
-        auto place = [&](int64_t c0, int64_t c1) {
+        for (unsigned t = 1; t < F; ++t)
+            bound[t] = std::lower_bound(t_rowptr.begin(), t_rowptr.end(), t_nnz / F * t) - t_rowptr.begin();
+        for (unsigned t = 1; t <= F; ++t) bound[t] = std::min<int64_t>(d, std::max(bound[t], bound[t - 1]));
+        bound[F] = d;
+        on_threads(F, [&](unsigned t, unsigned) {
+            const int64_t c0 = bound[t], c1 = bound[t + 1];
             if (c0 >= c1) return;
             for (int64_t i = 0; i < n; ++i)
                 for (int64_t k = h_rowptr[i]; k < h_rowptr[i + 1]; ++k) {
@@ -309,28 +378,40 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
                     t_col[pos] = (int32_t)i;
                     if (!unit) t_val[pos] = h_val[k];
                 }
-        };
-        std::vector<std::thread> workers;
-        unsigned started = 0;
-        try {
-            for (unsigned t = 1; t < T; ++t) { workers.emplace_back(place, bound[t], bound[t + 1]); ++started; }
-        } catch (const std::exception &) {
-            // no more threads to be had: the remaining ranges run below
-        }
-        place(bound[0], bound[1]);
-        for (unsigned t = 1 + started; t < T; ++t) place(bound[t], bound[t + 1]);
-        for (std::thread &w : workers) w.join();
+        });
     }
 
     tron_dataset *ds = new (std::nothrow) tron_dataset();
     if (!ds) { set_error("out of host memory"); return TRON_ENOMEM; }
     ds->n = n; ds->d = d; ds->dense = false; ds->stream = reinterpret_cast<hipStream_t>(hip_stream);
     int rc = alloc_common(ds);
-    if (rc >= 0) rc = csr_plan_build(ds->fwd, n, d, h_rowptr.data(), h_col.data(), unit ? nullptr : h_val.data(),
-                                     fwd_partitioned ? kColParts : 1, g_tuning.csr_hot != 0, unit, ds->stream);
-    if (rc >= 0) rc = csr_plan_build(ds->bwd, d, n, t_rowptr.data(), t_col.data(), unit ? nullptr : t_val.data(), partitioned ? kColParts : 1,
-                                     false, unit, ds->stream);
-    if (rc >= 0 && nhot) rc = hot_tiles_build(ds->bwd, h_rowptr.data(), h_col.data(), h_val.data(), slot_code, nhot, ds->stream);
+    if (rc >= 0) {
+        // the two layouts are independent of each other: the first is built beside the second where a thread can be had
+        int rc_fwd = TRON_OK;
+        std::string err_fwd;
+        auto build_fwd = [&] {
+            hipError_t e = hipSetDevice(ds->device);   // a new thread starts on device 0
+            rc_fwd = e != hipSuccess ? hip_fail(e, "hipSetDevice", __FILE__, __LINE__)
+                                     : plan_build(ds->fwd, n, d, h_rowptr, h_col, unit ? nullptr : h_val, fwd_partitioned ? kColParts : 1,
+                                                  g_tuning.csr_hot != 0, unit, cols_used, ds->stream);
+            if (rc_fwd < 0) err_fwd = tron_last_error();
+        };
+        std::thread beside;
+        bool threaded = false;
+        try {
+            if (nnz >= (1 << 17)) { beside = std::thread(build_fwd); threaded = true; }
+        } catch (const std::exception &) {
+        }
+        if (!threaded) build_fwd();
+        rc = plan_build(ds->bwd, d, n, t_rowptr.data(), t_col.data(), unit ? nullptr : t_val.data(), partitioned ? kColParts : 1, false, unit, rows_used,
+                        ds->stream);
+        if (threaded) beside.join();
+        if (rc_fwd < 0) {
+            rc = rc_fwd;
+            set_error("%s", err_fwd.c_str());
+        }
+    }
+    if (rc >= 0 && nhot) rc = hot_tiles_build(ds->bwd, h_rowptr, h_col, h_val, slot_code, nhot, ds->stream);
     if (rc >= 0 && unit) {
         hipError_t e = hipMalloc(reinterpret_cast<void **>(&ds->unit_scale), sizeof(double) * (size_t)n);
         if (e == hipSuccess) e = hipMemcpyAsync(ds->unit_scale, row_value.data(), sizeof(double) * (size_t)n, hipMemcpyHostToDevice, ds->stream);
@@ -349,7 +430,7 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         }
     }
     if (rc >= 0) {
-        hipError_t e = hipMemcpyAsync(ds->y, h_y.data(), sizeof(double) * n, hipMemcpyHostToDevice, ds->stream);
+        hipError_t e = hipMemcpyAsync(ds->y, h_y, sizeof(double) * n, hipMemcpyHostToDevice, ds->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ds->stream);
         if (e != hipSuccess) rc = hip_fail(e, "copy y", __FILE__, __LINE__);
     }

@@ -392,7 +392,7 @@ int probe_copy(double *dst, const double *src, int64_t count, int reps, hipStrea
 // parts: 1 = plain CSR, 0 = choose from the size of the gathered vector
 // unit: build a unit plan (see CsrPlan::unit; partitioned layouts only; h_val is not read)
 int csr_plan_build(CsrPlan &P, int64_t rows, int64_t cols, const int64_t *h_rowptr, const int32_t *h_col,
-                   const double *h_val, int parts, bool hot, bool unit, hipStream_t st);
+                   const double *h_val, int parts, bool hot, bool unit, int64_t cols_used, hipStream_t st);   // cols_used: columns with entries
 // Hot-row tiles for plan A (rows x cols) from the *other* orientation's CSR (cols x rows: t_rowptr over A's columns,
 // t_col = A's row ids).  slot_code[row] = slice * kTileSlots + slot for hot rows, -1 otherwise.
 int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, const double *t_val,

@@ -29,6 +29,7 @@
 #include <thread>
 
 #include "device_util.h"
+#include "host_util.h"
 
 namespace tron {
 
@@ -111,30 +112,6 @@ static void plan_chunks(const RP *rp, int64_t rows, int64_t nnz_x, int nchunks, 
     (void)nnz_x;
 }
 
-// fn(first, last) over [0, n) cut into equal ranges, one host thread per range (at most eight; small n: the caller's
-// thread alone).  fn must not throw and must write only what belongs to its own range.
-template <class F>
-static void parallel_ranges(int64_t n, F &&fn)
-{
-    unsigned T = std::thread::hardware_concurrency();
-    T = std::max(1u, std::min(8u, T));
-    if (n < (1 << 16)) T = 1;
-    const int64_t per = (n + T - 1) / T;
-    std::vector<std::thread> workers;
-    unsigned started = 0;
-    try {
-        for (unsigned t = 1; t < T; ++t) {
-            workers.emplace_back(fn, std::min<int64_t>(n, (int64_t)t * per), std::min<int64_t>(n, (int64_t)(t + 1) * per));
-            ++started;
-        }
-    } catch (const std::exception &) {
-        // no more threads to be had: the remaining ranges run below
-    }
-    fn((int64_t)0, std::min<int64_t>(n, per));
-    for (unsigned t = 1 + started; t < T; ++t) fn(std::min<int64_t>(n, (int64_t)t * per), std::min<int64_t>(n, (int64_t)(t + 1) * per));
-    for (std::thread &w : workers) w.join();
-}
-
 // Where entry e of a chunk is stored.  Thread t of a kernel owns entries 8t .. 8t+7 of a chunk, and its loads cover whole
 // cache lines: the columns come as two pieces of four (16 bytes), the values as four pieces of two, piece m of all threads
 // together.  The 16-bit slots of a head partition or a tile are 16 bytes per thread and stay in order.
@@ -142,7 +119,7 @@ static inline int64_t col_pos(int64_t q) { const uint32_t e = (uint32_t)q & (kCh
 static inline int64_t val_pos(int64_t q) { const uint32_t e = (uint32_t)q & (kChunk - 1); return q - e + ((e >> 1 & 3) * (kChunk / 4) + (e >> 3) * 2 + (e & 1)); }
 
 int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowptr, const int32_t *h_col,
-                   const double *h_val, int parts, bool hot, bool unit, hipStream_t st)
+                   const double *h_val, int parts, bool hot, bool unit, int64_t cols_used, hipStream_t st)
 {
     A.rows = rows;
     A.cols = cols;
@@ -194,17 +171,18 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         }
         rp[rows] = at;
         const int64_t stored = at;
-        std::vector<int32_t> pcol((size_t)stored);
-        std::vector<double> pval((size_t)stored);
-        {
-            int64_t filled = 0;
-            int32_t last_col = 0;
-            for (int64_t r = 0; r < rows; ++r) {
-                for (; filled < rp[r]; ++filled) { pcol[filled] = last_col; pval[filled] = 0.0; }
-                for (int64_t k = h_rowptr[r]; k < h_rowptr[r + 1]; ++k, ++filled) { pcol[filled] = h_col[k]; pval[filled] = h_val[k]; }
-                if (h_rowptr[r + 1] > h_rowptr[r]) last_col = h_col[h_rowptr[r + 1] - 1];
+        const HostArray<int32_t> pcol((size_t)stored);
+        const HostArray<double> pval((size_t)stored);
+        parallel_ranges(rows, stored, [&](int64_t r0, int64_t r1) {
+            for (int64_t r = r0; r < r1; ++r) {
+                const int64_t k0 = h_rowptr[r], k1 = h_rowptr[r + 1];
+                int64_t q = rp[r];
+                for (int64_t k = k0; k < k1; ++k, ++q) { pcol[q] = h_col[k]; pval[q] = h_val[k]; }
+                if (q == rp[r + 1]) continue;
+                const int32_t last_col = k1 > 0 ? h_col[k1 - 1] : 0;   // of the last row with entries up to here
+                for (; q < rp[r + 1]; ++q) { pcol[q] = last_col; pval[q] = 0.0; }
             }
-        }
+        });
         const int64_t nb64 = std::max<int64_t>(1, (stored + kChunk - 1) / kChunk);
         if (nb64 > 0x7ffffff0) { set_error("matrix too large: %lld chunks", (long long)nb64); return TRON_EINVAL; }
         A.nblocks = (int)nb64;
@@ -214,11 +192,12 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         TRON_TRY(upload(&A.rowptr, rp.data(), (size_t)rows + 1, st));
         TRON_TRY(upload(&A.col, pcol.data(), (size_t)stored, st));
         TRON_TRY(upload(&A.val, pval.data(), (size_t)stored, st));
-        TRON_HIP(hipStreamSynchronize(st));   // the staging vectors go out of scope
+        TRON_HIP(hipStreamSynchronize(st));   // the staging arrays go out of scope
     } else {
         const int P = A.P;
         std::vector<int64_t> colcount((size_t)cols + 1, 0);
-        for (int64_t k = 0; k < A.nnz; ++k) colcount[h_col[k] + 1]++;
+        if (P > 1)   // a single range needs no counts
+            for (int64_t k = 0; k < A.nnz; ++k) colcount[h_col[k] + 1]++;
         // Head partition: the kHotSlots most frequent columns of the whole matrix, when they hold a good part of
         // the nonzeros.  Their entries need no locality in L2 (one LDS table serves them all), so they are not
         // split by column range: one segment per row instead of one per row and range.
@@ -268,7 +247,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         for (int x = 0; x < P; ++x)
             for (int64_t j = bound[x]; j < bound[x + 1]; ++j)
                 if (part_of[j] != P || A.head < 0) part_of[j] = (uint8_t)x;
-        for (int x = 0; x < P; ++x) A.part_nnz[x] = colcount[bound[x + 1]] - colcount[bound[x]];
+        for (int x = 0; x < P; ++x) A.part_nnz[x] = P > 1 ? colcount[bound[x + 1]] - colcount[bound[x]] : A.nnz;
         for (int x = 0; x < NP; ++x)
             if (A.part_nnz[x] > 0x7ffffff0) { set_error("partition too large for 32-bit offsets"); return TRON_EINVAL; }
         // LDS-resident columns of a range: its kHotSlots most frequent columns with at least kHotMinCount entries
@@ -288,6 +267,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
                 }
             }
         }
+        if (P == 1) A.cold_cols = cols_used;
         for (int64_t j = 0; j < cols; ++j)   // head columns have count 0 here
             if (colcount[j + 1] > colcount[j] && !(hot && slot_of[j] >= 0)) A.cold_cols++;
         std::vector<int64_t>().swap(colcount);
@@ -301,7 +281,11 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         // one table for the passes over the entries below: partition in the upper half, LDS slot + 1 (0: none) in the lower
         std::vector<int32_t> code_of((size_t)cols);
         for (int64_t j = 0; j < cols; ++j) code_of[j] = ((int32_t)part_of[j] << 16) | ((hot && slot_of[j] >= 0) ? slot_of[j] + 1 : 0);
-        parallel_ranges(rows, [&](int64_t r0, int64_t r1) {
+        parallel_ranges(rows, A.nnz, [&](int64_t r0, int64_t r1) {
+            if (P == 1) {
+                for (int64_t r = r0; r < r1; ++r) len32[(size_t)r] = (int32_t)(h_rowptr[r + 1] - h_rowptr[r]);
+                return;
+            }
             for (int64_t r = r0; r < r1; ++r)
                 for (int64_t k = h_rowptr[r]; k < h_rowptr[r + 1]; ++k) {
                     const int x = code_of[h_col[k]] >> 16;
@@ -345,10 +329,25 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         A.nblocks = chunk;
         if (nseg_total > 0x7ffffff0) { set_error("too many row segments for 32-bit indexing"); return TRON_EINVAL; }
         // entries partition-major; inside a row the entries of one range are contiguous and stay ordered
-        std::vector<int32_t> pcol((size_t)pos, 0);
-        std::vector<double> pval(A.unit ? 0 : (size_t)pos, 0.0);
-        parallel_ranges(rows, [&](int64_t r0, int64_t r1) {   // a row's places belong to that row alone
+        size_t stored_cols = (size_t)pos;
+        HostArray<int32_t> pcol((size_t)pos);
+        HostArray<double> pval(A.unit ? 0 : (size_t)pos);
+        parallel_ranges(pos, pos, [&](int64_t q0, int64_t q1) {
+            std::fill(pcol.data() + q0, pcol.data() + q1, 0);
+            if (!A.unit) std::fill(pval.data() + q0, pval.data() + q1, 0.0);
+        });
+        parallel_ranges(rows, A.nnz, [&](int64_t r0, int64_t r1) {   // a row's places belong to that row alone
             int64_t cursor[kMaxParts + 1];
+            if (P == 1) {
+                for (int64_t r = r0; r < r1; ++r) {
+                    int64_t q = rp32[(size_t)r];
+                    for (int64_t k = h_rowptr[r]; k < h_rowptr[r + 1]; ++k, ++q) {
+                        pcol[col_pos(q)] = h_col[k];
+                        pval[val_pos(q)] = h_val[k];
+                    }
+                }
+                return;
+            }
             for (int64_t r = r0; r < r1; ++r) {
                 for (int x = 0; x < NP; ++x) cursor[x] = A.part_base[x] + rp32[(size_t)x * (rows + 1) + r];
                 int64_t hq = sell ? head_off[r] : 0;
@@ -474,7 +473,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
                     const int32_t hdr[4] = {-1, 0, 0, 0};   // a header of a slice without groups
                     std::memcpy(&data[((size_t)gpad * kWave + l) * 8], hdr, sizeof(hdr));
                 }
-            parallel_ranges((int64_t)slices.size(), [&](int64_t p0, int64_t p1) {   // a slice's groups belong to it alone
+            parallel_ranges((int64_t)slices.size(), groups * kWave, [&](int64_t p0, int64_t p1) {   // a slice's groups belong to it alone
             for (int64_t p = p0; p < p1; ++p) {
                 const Slice &sc = slices[stored[p]];
                 const int64_t w1 = std::min<int64_t>(rows, (sc.first / kSellWindow + 1) * (int64_t)kSellWindow);
@@ -506,16 +505,16 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         } else if (A.head >= 0) {
             // the head partition is the last one: its columns go to col16, the ranges' stay in col
             const size_t h0 = (size_t)A.part_base[A.head];
-            std::vector<uint16_t> c16(pcol.size() - h0, 0);
+            std::vector<uint16_t> c16((size_t)pos - h0, 0);
             // padding: slot 0 (value 0; in a unit plan the padding lies behind the last flagged entry of the partition, and
             // what follows the last flag of a chunk never reaches a sum)
-            for (size_t k = h0; k < pcol.size(); ++k) c16[k - h0] = (uint16_t)(pcol[k] < 0 ? ~pcol[k] : 0);
+            for (size_t k = h0; k < (size_t)pos; ++k) c16[k - h0] = (uint16_t)(pcol[k] < 0 ? ~pcol[k] : 0);
             TRON_TRY(upload(&A.col16, c16.data(), c16.size(), st));
             TRON_HIP(hipStreamSynchronize(st));
-            pcol.resize(h0);
+            stored_cols = h0;
         }
-        TRON_TRY(upload(&A.col, pcol.data(), pcol.size(), st));
-        if (!A.unit) TRON_TRY(upload(&A.val, pval.data(), pval.size(), st));
+        TRON_TRY(upload(&A.col, pcol.data(), stored_cols, st));
+        if (!A.unit) TRON_TRY(upload(&A.val, pval.data(), (size_t)pos, st));
         else TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.xs), sizeof(double) * (size_t)(cols + 1)));
         // group_base[G].first[x] = first segment of partition x whose row is >= 64 G (see sum_parts)
         A.ngroups = (rows + kWave - 1) / kWave;
@@ -956,7 +955,6 @@ __global__ __launch_bounds__(kBlock) void k_csr_direct(DirectPtrs P, int nlong, 
     __shared__ __align__(16) double prod[kProdDoubles];
     __shared__ double lds[kWavesPerBlock];
     __shared__ double piece;
-    __shared__ int last_of[2];
     const int tid = threadIdx.x, c = blockIdx.x;
     StreamRegs<false, false> s;
     load_stream(s, P.col, P.val, (int64_t)c * kChunk);
@@ -994,6 +992,33 @@ __global__ __launch_bounds__(kBlock) void k_csr_direct(DirectPtrs P, int nlong, 
     __syncthreads();
     const int starts_long = lr.y >= 0 ? tab.x + tab.y - 1 : -1;   // the segment that is only a long row's first piece
     double acc = 0.0;
+    // the last wavefront sees to the long rows while the others start on the chunk's own
+    if ((lr.x >= 0 || lr.y >= 0) && tid >= kBlock - kWave) {
+        const int lane = tid & (kWave - 1);
+        if (lane == 0) {
+            if (lr.x >= 0) store_shared(P.carry + c, piece);
+            if (lr.y >= 0) store_shared(P.long_first + lr.y, outv[tab.y - 1]);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the pieces have arrived
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int l = q ? lr.y : lr.x;
+            if (l < 0) continue;   // uniform
+            const int4 R = P.long_row[l];
+            unsigned ticket = 0;
+            if (lane == 0) ticket = __hip_atomic_fetch_add(P.long_ticket + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((int)__builtin_amdgcn_readfirstlane(ticket) != R.z) continue;
+            double z = 0.0;
+            for (int k = lane; k < R.z; k += kWave) z += load_shared(P.carry + R.y + k);
+            z = wave_sum(z) + load_shared(P.long_first + l);
+            if (lane == 0) {
+                const double share = finish_row<EPI>(A, R.x, z, row_aux<EPI>(A, R.x));
+                if (A.red) store_shared(A.red + gridDim.x + l, share);
+                P.long_ticket[l] = 0u;
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // before this workgroup's own ticket, if there is one
+    }
     for (int base = lo; base < hi; base += kAhead * kBlock) {
         if (base > lo) {
 #pragma unroll
@@ -1007,35 +1032,6 @@ __global__ __launch_bounds__(kBlock) void k_csr_direct(DirectPtrs P, int nlong, 
         for (int j = 0; j < kAhead; ++j) {
             const int r = base + j * kBlock + tid;
             if (r < hi && !(starts_long >= 0 && seg[j] == starts_long)) acc += finish_row<EPI>(A, r, seg[j] >= 0 ? outv[seg[j] - tab.x] : 0.0, aux[j]);
-        }
-    }
-    if (lr.x >= 0 || lr.y >= 0) {   // uniform
-        if (tid == 0) {
-            if (lr.x >= 0) store_shared(P.carry + c, piece);
-            if (lr.y >= 0) store_shared(P.long_first + lr.y, outv[tab.y - 1]);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the pieces have arrived
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int l = q ? lr.y : lr.x;
-                last_of[q] = l >= 0 && __hip_atomic_fetch_add(P.long_ticket + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)P.long_row[l].z;
-            }
-        }
-        __syncthreads();
-        if (tid < kWave) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                if (!last_of[q]) continue;
-                const int l = q ? lr.y : lr.x;
-                const int4 R = P.long_row[l];
-                double z = 0.0;
-                for (int k = tid; k < R.z; k += kWave) z += load_shared(P.carry + R.y + k);
-                z = wave_sum(z) + load_shared(P.long_first + l);
-                if (tid == 0) {
-                    const double share = finish_row<EPI>(A, R.x, z, row_aux<EPI>(A, R.x));
-                    if (A.red) store_shared(A.red + gridDim.x + l, share);
-                    P.long_ticket[l] = 0u;
-                }
-            }
         }
     }
     if (A.red) {
@@ -1269,7 +1265,7 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
     try {
         ecode.resize((size_t)t_rowptr[A.cols]);
     } catch (const std::exception &) { set_error("out of host memory building the hot-row tiles"); return TRON_ENOMEM; }
-    parallel_ranges(A.cols, [&](int64_t i0, int64_t i1) {
+    parallel_ranges(A.cols, t_rowptr[A.cols], [&](int64_t i0, int64_t i1) {
         for (int64_t k = t_rowptr[i0]; k < t_rowptr[i1]; ++k) {
             const int32_t code = slot_code[t_col[k]];
             ecode[k] = code >= 0 ? (uint16_t)code : kNoCode;
