@@ -326,20 +326,22 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
     const int64_t t_nnz = t_rowptr[d];
     HostArray<int32_t> t_col;
     HostArray<double> t_val;
+    HostArray<int32_t> place;
     std::vector<int64_t> cursor;
     try {
+        if (T > 1) place = HostArray<int32_t>((size_t)d);   // here, where running out of memory is an error code, not in the threads
         t_col = HostArray<int32_t>((size_t)t_nnz);
         if (!unit) t_val = HostArray<double>((size_t)t_nnz);
         if (T == 1) cursor.assign(t_rowptr.begin(), t_rowptr.end() - 1);
     } catch (const std::bad_alloc &) { set_error("out of host memory building the transposed copy"); return TRON_ENOMEM; }
     if (T > 1) {
         parallel_ranges(d, (int64_t)T * d, [&](int64_t c0, int64_t c1) {   // the blocks' counts become their first places
-            std::vector<int32_t> at(t_rowptr.begin() + c0, t_rowptr.begin() + c1);
+            for (int64_t c = c0; c < c1; ++c) place[c] = (int32_t)t_rowptr[c];
             for (unsigned t = 0; t < T; ++t)
                 for (int64_t c = c0; c < c1; ++c) {
                     int32_t &cnt = block_count[(size_t)t * (size_t)d + c];
-                    const int32_t first = at[c - c0];
-                    at[c - c0] += cnt;
+                    const int32_t first = place[c];
+                    place[c] += cnt;
                     cnt = first;
                 }
         });

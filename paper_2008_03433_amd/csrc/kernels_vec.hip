@@ -268,13 +268,13 @@ __device__ __forceinline__ double sum_of_partials(const double *__restrict__ p, 
 // starts from, so that the two latencies overlap.
 constexpr int kCgAtOnce = 4;
 
-// The new r.r of iteration c.it to its slot, for the kernels after this one, and with the boundary flag as its sign bit for the
-// host, which waits for that word (see cg_solve).
+// The new r.r of iteration c.it to its slot, for the kernels after this one, and with the boundary flag as its sign bit (also
+// of a zero or a NaN) for the host, which waits for that word (see cg_solve).
 __device__ __forceinline__ void post_rr(const CgStepCtl &c, double *scal, double *scal_copy, double rr, bool boundary)
 {
     const int slot = kScalRR + ((c.it + 1) & 1);
     scal_copy[slot] = rr;
-    __hip_atomic_store(scal + slot, boundary ? -rr : rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(scal + slot, copysign(rr, boundary ? -1.0 : 1.0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // s += a p;  r -= a Hp with a = the step length above;  region CGP_RR = partial sums of r.r (PRE: r.(r / M));  the iteration's flag slot = whether the step went to the boundary.  Nothing at all if the run had ended.

@@ -190,7 +190,7 @@ int cg_solve(tron_dataset *ds, const tron_params &P, const double *M, double del
         double rr;
         TRON_TRY(wait_for_word(ds, ds->scal_host + kScalRR + ((it + 1) & 1), &rr));
         *n_hv = it + 1;
-        if (std::signbit(rr) && !std::isnan(rr)) {
+        if (std::signbit(rr)) {
             *on_boundary = 1;
             break;
         }

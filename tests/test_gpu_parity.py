@@ -436,6 +436,56 @@ def test_hv_requires_fun_grad(rng):
     ds.close()
 
 
+def _csr_rows(rng, lengths, d):
+    """Rows of the given lengths at random columns, standard normal values."""
+    rowptr = np.zeros(len(lengths) + 1, dtype=np.int64)
+    rowptr[1:] = np.cumsum(lengths)
+    col = np.concatenate([np.sort(rng.choice(d, size=m, replace=False)) for m in lengths if m] or [np.zeros(0)]).astype(np.int32)
+    y = np.where(rng.random(len(lengths)) < 0.5, 1.0, -1.0)
+    return SparseProblem("rows", len(lengths), d, rowptr, col, rng.standard_normal(col.size) / 30.0, y)
+
+
+@pytest.mark.parametrize("segmented", [0, 1])
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("lengths", [
+    [2047, 1, 2048, 2049, 1, 4096, 4097, 3],                # rows around one and two chunks of 2048 entries
+    [6200, 6200, 5, 2050] + [0] * 3000 + [9, 2500],         # a long row that begins where another ends; more empty rows than a chunk has threads
+    [0] * 300 + [1] * 2048 + [7000] + [0] * 257,            # a chunk of single entries before a long row, empty rows at both ends
+], ids=["around-chunks", "long-after-long", "single-entries"])
+def test_csr_rows_longer_than_a_chunk(rng, loss, segmented, lengths):
+    """The rows completed by the workgroup that finishes last among their chunks, twice on one handle (its counters start
+    from zero again), and the empty rows a chunk looks after."""
+    import paper_2008_03433_amd as tron
+    tron.tron_tuning_set("csr_segmented", segmented)
+    try:
+        check_calls(_csr_rows(rng, lengths, 8000), loss, 0.5, rng, w_scale=0.3, n_hv=3)
+    finally:
+        tron.tron_tuning_set("csr_segmented", -1)
+
+
+@pytest.mark.parametrize("blend", [0.0, 0.01])
+@pytest.mark.parametrize("d", [8191, 8192, 8193])
+def test_solve_sparse_around_the_limit_of_the_single_workgroup_step(rng, d, blend):
+    p = _csr_rows(rng, [20] * 1200, d)
+    p.val *= 30.0
+    compare_solves(p, LOSS_LR, 1.0, 1e-3, precond_blend=blend)
+
+
+@pytest.mark.parametrize("d", [700, (1 << 19) + 1])
+def test_csr_creation_on_several_threads(rng, d):
+    """200,000 nonzeros are split over threads by blocks of rows, above 524,288 features by ranges of features; the error
+    reported for an invalid matrix is the first in row order whichever thread met it."""
+    import paper_2008_03433_amd as tron
+    p = _csr_rows(rng, [0] * 11 + [100] * 1990 + [500, 500], d)
+    check_calls(p, LOSS_LR, 1.0, rng, n_hv=1)
+    for late in (1600, 1989):
+        col, val = p.col.copy(), p.val.copy()
+        val[p.rowptr[late]] = np.nan
+        col[p.rowptr[900] + 5] = d
+        with pytest.raises(tron.TronError, match="row 900: column index"):
+            tron.tron_dataset_create_csr(p.n, d, p.rowptr, col, val, p.y)
+
+
 def test_invalid_inputs_are_rejected(rng):
     import paper_2008_03433_amd as tron
     y = np.array([1.0, -1.0])
