@@ -37,7 +37,7 @@ ROCPROF_NAMES = {
     ("c3", "spmv_head"): ("k_head_sell", "csr_spmv_c3.md"),
     ("c3", "spmv_fwd"): ("k_csr_spmv_part<true, false, false, true>", "csr_spmv_c3.md"),
     ("c3", "spmv_bwd"): ("k_csr_spmv_part<false, false, false, true>", "csr_spmv_c3.md"),
-    ("c3", "spmv_tiles"): ("k_hot_tiles_unit", "csr_spmv_c3.md"),
+    ("c3", "spmv_tiles"): ("k_hot_tiles<false, true>", "csr_spmv_c3.md"),
     # the same matrix with the general layout forced (csr_unit = 0: 32-bit / 16-bit indices + fp64 values)
     ("c3_values", "spmv_head"): ("k_csr_spmv_part<true, true, false, false>", "csr_spmv_c3_values.md"),
     ("c3_values", "spmv_fwd"): ("k_csr_spmv_part<true, false, false, false>", "csr_spmv_c3_values.md"),
