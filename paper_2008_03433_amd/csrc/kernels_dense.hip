@@ -48,7 +48,7 @@ constexpr int kFinishMaxD = 32;
 // workgroup more costs its ticket (10 ns, one after the other) and its sums.  1M x 24, a Hessian-vector call with 256 / 512 /
 // 1024 / 2048 workgroups: 43 / 44 / 52 / 64 us; 20M x 24: 629 / 640 / 652 / 663 us.  Twelve wavefronts: 44 and 633 us.
 constexpr int dense_block(int L) { return dense_finishes(L) ? 512 : kBlock; }
-constexpr int kFinishGrid = 256, kWideGrid = 512;
+constexpr int kFinishGrid = 256, kWideGrid = 512, kFewGrid = 512;
 // doubles of LDS: the column sums of the wavefronts, then one per thread for the workgroup that finishes last
 constexpr int dense_lds(int E, int L) { return dense_block(L) / kWave * E * L > dense_block(L) ? dense_block(L) / kWave * E * L : dense_block(L); }
 constexpr int kColumnsBlock = 1024, kColumnsPer = 16;
@@ -438,6 +438,11 @@ __global__ __launch_bounds__(kColumnsBlock) void k_dense_columns(int d, int grid
 // ------------------------------------------------------------------ dispatch
 constexpr double kSkipBelow = 0.95;   // active fraction under which the Hessian-vector pass skips the inactive rows
 
+// Where about half of the rows or fewer are read, the loads that are left out no longer fill the queue to HBM with eight
+// wavefronts per CU: d <= 32 then runs two workgroups per CU.  20M x 24, 256 / 512 workgroups: 0.72 of the rows active 490 / 503
+// us, 0.47 364 / 358, 0.38 335 / 294, 0.36 330 / 281.
+constexpr double kFewBelow = 0.5;
+
 // What a Hessian-vector pass runs over: the matrix itself with D of one buffer, or the compacted copy of its active rows
 // (then every row is active: the bit words are all ones).
 struct HvInput {
@@ -452,8 +457,9 @@ HvInput hv_input(const tron_dataset *ds, int Dslot)
 {
     if (ds->hat_slot == Dslot && ds->Xhat)
         return HvInput{ds->Xhat, ds->hat_rows, ds->hat_bits, true, false, dense_grid_for(ds->hat_rows, ds->d)};
-    const bool mask = ds->D_is_mask[Dslot];
-    return HvInput{ds->X, ds->n, ds->Dbuf[Dslot], mask, mask && ds->active_frac[Dslot] < kSkipBelow, ds->dense_grid};
+    const bool mask = ds->D_is_mask[Dslot], skip = mask && ds->active_frac[Dslot] < kSkipBelow;
+    const bool few = skip && ds->d <= kFinishMaxD && ds->active_frac[Dslot] < kFewBelow;
+    return HvInput{ds->X, ds->n, ds->Dbuf[Dslot], mask, skip, few ? dense_grid_few(ds->n, ds->d) : ds->dense_grid};
 }
 
 template <int E, int L>
@@ -788,14 +794,17 @@ bool dense_supported(int64_t d)
     return d >= 1 && pick_shape(d, s);
 }
 
-int dense_grid_for(int64_t n, int64_t d)
+static int grid_up_to(int64_t n, int64_t d, int64_t most)
 {
     Shape s;
     if (!pick_shape(d, s)) return 1;
     const int64_t rows = (int64_t)pick_U(s.E, s.L) * (kWave / s.L) * (dense_block(s.L) / kWave);
-    const int64_t g = (n + rows - 1) / rows, most = dense_finishes(s.L) ? kFinishGrid : kWideGrid;
+    const int64_t g = (n + rows - 1) / rows;
     return (int)(g < most ? g : most);
 }
+
+int dense_grid_for(int64_t n, int64_t d) { return grid_up_to(n, d, d <= kFinishMaxD ? kFinishGrid : kWideGrid); }
+int dense_grid_few(int64_t n, int64_t d) { return grid_up_to(n, d, kFewGrid); }
 
 int dense_work_units(int64_t n, int64_t d)
 {
@@ -809,7 +818,7 @@ int dense_work_units(int64_t n, int64_t d)
 // column sums (grid * d) followed by loss partials (grid), the column workgroups' sums (d) and active-row counts (grid)
 int64_t dense_partials_needed(int64_t n, int64_t d)
 {
-    const int64_t g = dense_grid_for(n, d);
+    const int64_t g = d <= kFinishMaxD ? dense_grid_few(n, d) : dense_grid_for(n, d);   // the largest grid of a pass
     return d * g + g + d + g;
 }
 
@@ -894,7 +903,7 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
     const HvInput in = hv_input(ds, Dslot);
     const int grid = in.grid;
     // The limit is stated in groups of four wave tiles (dense_work_units); the sums of the workgroups that are launched, at most
-    // 256 for d <= 32 and 512 otherwise, and never more than those groups, fit wherever it holds.
+    // 512 and never more than those groups, fit wherever it holds.
     const int units = dense_work_units(in.n, ds->d);
     const int64_t need = ds->d * units + ds->d + 1;
     if (need > kStaticScratchDoubles) {
