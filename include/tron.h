@@ -155,7 +155,8 @@ TRON_API int tron_hv(tron_dataset *ds, double C, const double *v_dev, double *Hv
  * the current device is not the handle's; TRON_ESTATE if no D is cached.
  * All calls on one GPU share the one array: calls that overlap in time on the same GPU (different streams or
  * threads) race; calls on one stream are ordered and safe.  The array keeps the last call's contents; no call relies
- * on them.
+ * on them.  Nothing of the handle is written: a captured call may be replayed on another stream beside the handle's own
+ * calls, as long as none of those replaces the cached D it reads (tron_fun_grad, tron_solve).
  */
 #define TRON_HV_STATIC_MAX_DOUBLES 262144
 TRON_API int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, double *Hv_dev, double *vHv_dev);

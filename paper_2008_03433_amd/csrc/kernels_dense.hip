@@ -880,14 +880,27 @@ int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Ds
 }  // namespace tron
 
 // ------------------------------------------------------------------ Hessian-vector product without any allocation
-// The work space of the dense Hessian-vector product -- per-workgroup column sums (d * grid), the column workgroups' sums (d)
-// and the curvature scalar -- in a file-scope device array instead of the handle's allocation.  Every GPU the
-// library runs on holds its own copy of the array, at its own address, until the process ends.
+// The work space of the dense Hessian-vector product -- per-workgroup column sums (d * grid), the column workgroups' sums (d),
+// the curvature scalar and the counter of finished workgroups -- in a file-scope device object instead of the handle's
+// allocation: a product enqueued here shares nothing that is written with the handle's own calls, so a captured one may be
+// replayed beside them.  Every GPU the library runs on holds its own copy of the object, at its own address, until the
+// process ends.
 namespace {
 constexpr int64_t kStaticScratchDoubles = TRON_HV_STATIC_MAX_DOUBLES;
-__device__ __align__(256) double scratch[kStaticScratchDoubles];
+struct StaticWork {
+    double sums[kStaticScratchDoubles];
+    unsigned ticket;
+};
+__device__ __align__(256) StaticWork static_work;
 constexpr int kStaticMaxDevices = 64;
-double *g_scratch_ptr[kStaticMaxDevices] = {nullptr};   // device address of `scratch` on each GPU, looked up once
+StaticWork *g_static_work[kStaticMaxDevices] = {nullptr};   // device address of `static_work` on each GPU, looked up once
+
+// The counter starts every call at zero whatever an earlier one left: calls that overlapped (they race for the sums) spoil
+// their own results and no later ones.
+__global__ __launch_bounds__(tron::kWave) void k_clear_counter(unsigned *counter)
+{
+    if (threadIdx.x == 0) *counter = 0u;
+}
 }  // namespace
 
 extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, double *Hv_dev, double *vHv_dev)
@@ -919,19 +932,22 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
                   kStaticMaxDevices);
         return TRON_EINVAL;
     }
-    if (!g_scratch_ptr[dev]) {
-        // in host code the array's name is only a stand-in: its address on this GPU comes from the runtime
-        double *p = nullptr;
-        TRON_HIP(hipGetSymbolAddress(reinterpret_cast<void **>(&p), HIP_SYMBOL(scratch)));
+    if (!g_static_work[dev]) {
+        // in host code the object's name is only a stand-in: its address on this GPU comes from the runtime
+        StaticWork *p = nullptr;
+        TRON_HIP(hipGetSymbolAddress(reinterpret_cast<void **>(&p), HIP_SYMBOL(static_work)));
         if (!p) { set_error("tron_hv_static: the static work space has no device address"); return TRON_EDEVICE; }
-        g_scratch_ptr[dev] = p;
+        g_static_work[dev] = p;
     }
-    double *partials = g_scratch_ptr[dev];
+    double *partials = g_static_work[dev]->sums;
     double *colprod = partials + ds->d * grid;
     double *scalar = colprod + ds->d;
-    // Nothing has to start at zero: every workgroup of the pass writes all d of its column sums, the second stage the rest.
-    // The counter of finished workgroups is the handle's own.
-    const DenseFinish fin{ds->ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false};
+    // Of the sums nothing has to start at zero: every workgroup of the pass writes all d of its column sums, the second stage
+    // the rest.
+    unsigned *ticket = &g_static_work[dev]->ticket;
+    hipLaunchKernelGGL(k_clear_counter, dim3(1), dim3(kWave), 0, ds->stream, ticket);
+    TRON_HIP(hipGetLastError());
+    const DenseFinish fin{ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false};
     TRON_TRY(dispatch_hv(ds, in, v_dev, partials, fin));
     TRON_HIP(hipGetLastError());
     return launch_columns(ds, grid, partials, colprod, nullptr, nullptr, fin);

@@ -113,3 +113,48 @@ def test_static_hv_rejects_what_does_not_fit_and_wrong_state():
         assert e.value.code == -1
     finally:
         sp.close()
+
+
+@pytest.mark.parametrize("d", [24, 40])
+def test_captured_static_hv_runs_beside_the_handles_own_calls(d):
+    """A captured tron_hv_static replayed on a second stream while tron_hv runs on the handle's stream: the two share no work
+    space and no counter, so every result has the bits of the call made alone -- during the overlap and afterwards.  d <= 32
+    and d > 32 finish their sums in different kernels."""
+    torch = torch_mod()
+    rng = np.random.default_rng(31 + d)
+    n, C = 1_000_003, 0.3
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+    X = dev(rng.standard_normal((n, d)))
+    y = dev(np.where(rng.random(n) < 0.5, 1.0, -1.0))
+    torch.cuda.synchronize()
+    ds = tron.Dataset.from_dense(X, y, stream=own)
+    try:
+        ds.fun_grad(LOSS_LR, C, dev(0.3 * rng.standard_normal(d)))
+        v, u = dev(rng.standard_normal(d)), dev(rng.standard_normal(d))
+        Hv, Hu, Gu = torch.empty_like(v), torch.empty_like(u), torch.empty_like(u)
+        s = torch.empty(1, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        ds.hv(C, v, Hv)
+        ds.hv_static(C, u, Hu, s)
+        torch.cuda.synchronize()
+        Hv_alone, Hu_alone, s_alone = Hv.cpu().numpy(), Hu.cpu().numpy(), s.item()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=own):
+            ds.hv_static(C, u, Gu, s)
+        for _ in range(30):
+            Hv.zero_(); Gu.zero_(); s.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(other):
+                graph.replay()
+            for _ in range(3):
+                ds.hv(C, v, Hv, want_vHv=False)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(Hv.cpu().numpy(), Hv_alone)
+            np.testing.assert_array_equal(Gu.cpu().numpy(), Hu_alone)
+            assert s.item() == s_alone
+        g = torch.empty_like(v)
+        f1 = ds.fun_grad(LOSS_LR, C, u, g)
+        assert ds.fun_grad(LOSS_LR, C, u, None) == f1
+    finally:
+        torch.cuda.synchronize()
+        ds.close()
