@@ -106,9 +106,15 @@ __device__ __forceinline__ bool dense_last_sums(double *col_sum, unsigned *ticke
     }
     __syncthreads();
     if (wv != 0) return false;
+    // m lanes share a column's groups, m the largest power of two with d m <= 64: eight to sixteen additions one after the
+    // other whatever d is.  With one lane per column they were 512 / d: a Hessian-vector call over 100,000 rows
+    // took 11.9 us at d = 1 (6.9 now), 9.0 at d = 4 (7.9), 9.4 at d = 24 (9.3).
+    const int m = kWave >> (d > 1 ? 32 - __clz(d - 1) : 0), c = lane / m;
     col = loss = active = 0.0;
-    if (lane < d)
-        for (int k = 0; k < groups; ++k) col += col_sum[k * d + lane];
+    if (c < d)
+        for (int k = lane % m; k < groups; k += m) col += col_sum[k * d + c];
+    col = __shfl(group_sum(col, m), lane * m, kWave);
+    if (lane >= d) col = 0.0;
 #pragma unroll
     for (int k = 0; k < kWaves; ++k) {
         loss += red[0][k];

@@ -35,6 +35,14 @@ def test_dense_calls(rng, loss, n, d):
 
 
 @pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("n,d", [(131_071, 1), (200_003, 2), (131_137, 3), (700_001, 4), (300_001, 5), (131_073, 7)])
+def test_dense_calls_narrow_rows(rng, loss, n, d):
+    """Up to 512 column sums a workgroup adds per column (64 to 8 lanes share them), and wavefronts with one tile more or less
+    than others."""
+    check_calls(_dense(rng, n, d), loss, 0.5, rng, w_scale=0.5)
+
+
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
 def test_dense_many_tiles_ragged_tail(rng, loss):
     # more wave tiles than resident wavefronts (grid-stride loop taken several times) + ragged tail
     p = dg.config4(n=700_001)
