@@ -18,6 +18,7 @@
 // them in a fixed order and forms the outputs (dense_finish); the separate launch this replaces took 9.7 us for 2048
 // workgroups of 24 columns.  Wider matrices take a launch of k_dense_columns, one workgroup per 16 columns.  Nothing is added
 // in an order that depends on timing.
+#include <algorithm>
 #include <cmath>
 
 #include "dense_tile.h"
@@ -44,9 +45,9 @@ struct DenseFinish {
 // d <= 32 (at most four lanes per row): the last workgroup completes the sums
 constexpr bool dense_finishes(int L) { return L <= 4; }
 constexpr int kFinishMaxD = 32;
-// Eight wavefronts per CU, whatever the shape: with twelve loads of 16 bytes per lane in flight they keep HBM busy, and every
-// workgroup more costs its ticket (10 ns, one after the other) and its sums.  1M x 24, a Hessian-vector call with 256 / 512 /
-// 1024 / 2048 workgroups: 43 / 44 / 52 / 64 us; 20M x 24: 629 / 640 / 652 / 663 us.  Twelve wavefronts: 44 and 633 us.
+// Eight wavefronts per CU: with twelve loads of 16 bytes per lane in flight they keep HBM busy, and every workgroup more costs its
+// ticket (10 ns, one after the other) and its sums.  More only for narrow rows (tiles_at_once, dense_fun_grad_grid) and for few
+// active ones (kFewBelow).  1M x 24, a Hessian-vector call with 256 / 512 / 1024 / 2048 workgroups: 43 / 44 / 52 / 64 us; 20M x 24: 629 / 640 / 652 / 663 us.  Twelve wavefronts: 44 and 633 us.
 constexpr int dense_block(int L) { return dense_finishes(L) ? 512 : kBlock; }
 constexpr int kFinishGrid = 256, kWideGrid = 512, kFewGrid = 512;
 // doubles of LDS: the column sums of the wavefronts, then one per thread for the workgroup that finishes last
@@ -146,6 +147,13 @@ __device__ __forceinline__ void dense_finish(double *lds, const DenseFinish &fin
     }
 }
 
+// Tiles whose loads a wavefront of the Hessian-vector pass issues together: a tile of narrow rows is only 512 d bytes, and eight
+// wavefronts per CU with one such tile each do not keep HBM busy.  Up to d = 4 those in flight on a CU still fit its 32 KB L1,
+// which serves a lane's loads of the same line (d <= 8: a lane holds a whole row); two tiles at d = 5 gain nothing, and at d = 4
+// only where D is one bit a row (mask).  20M rows, one tile / several, L2-SVM: d = 1 57 / 30 us, 2 92 / 51, 3 108 / 81,
+// 4 117 / 104; logistic: 94 / 55, 103 / 81, 116 / 105, 126 / 132.
+constexpr int tiles_at_once(int E, int L, bool mask) { return L > 1 ? 1 : E == 1 ? 8 : E == 2 ? 4 : E == 3 || (E == 4 && mask) ? 2 : 1; }
+
 // ------------------------------------------------------------------ Hessian-vector pass
 // MASK: D is the active set of the L2-SVM (D_ii = 2 on it, else 0) instead of an fp64 value per row: one bit per row,
 // a 64-bit word per wave tile, when a tile has 64 rows (d <= 32); one byte per row otherwise.
@@ -177,37 +185,53 @@ __device__ __forceinline__ void hv_pass(double *lds, int64_t n, int64_t d, const
     constexpr bool kBits = MASK && T::RT == kWave;
     const uint64_t *Dbits = static_cast<const uint64_t *>(Dv);
     const int64_t tile0 = (int64_t)blockIdx.x * kWaves + wv;
-    uint64_t bits_next = (kBits && SKIP && tile0 < ntiles) ? Dbits[tile0] : 0;
-    for (int64_t tile = tile0; tile < ntiles; tile += nwaves) {
-        const int64_t row0 = tile * T::RT;
-        double x[U][E], c[U];
-        uint64_t bits = 0;
+    constexpr int G = tiles_at_once(E, L, MASK);
+    uint64_t bits_next[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) bits_next[g] = (kBits && SKIP && tile0 + g * nwaves < ntiles) ? Dbits[tile0 + g * nwaves] : 0;
+    for (int64_t tile = tile0; tile < ntiles; tile += G * nwaves) {
+        double x[G][U][E], Drow[G], c[U];
+        uint64_t bits[G], any = 0;
         if (kBits && SKIP) {
-            bits = bits_next;
-            bits_next = (tile + nwaves < ntiles) ? Dbits[tile + nwaves] : 0;
-            if (bits == 0) continue;   // no active row in the tile
-        }
-        T::load(X, n, d, row0, lane, x, (kBits && SKIP) ? bits : ~0ull);
-        if (kBits && !SKIP) bits = Dbits[tile];
-        double Drow = 0.0;
-        if (kBits) {
-            Drow = ((bits >> own) & 1u) ? 2.0 : 0.0;
-        } else if (row0 + own < n) {
-            Drow = MASK ? (Dm[row0 + own] ? 2.0 : 0.0) : D[row0 + own];
-        }
-        if (DIAG) {
-            T::from_row_owner(Drow, c);
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) acc[e] = fma(c[u] * x[u][e], x[u][e], acc[e]);
+            for (int g = 0; g < G; ++g) {
+                const int64_t ahead = tile + (G + g) * nwaves;
+                bits[g] = bits_next[g];
+                any |= bits[g];
+                bits_next[g] = (ahead < ntiles) ? Dbits[ahead] : 0;
             }
-        } else {
-            T::from_row_owner(Drow * T::row_sum(x, vreg, lane), c);   // a1 = D (X v)
+            if (any == 0) continue;   // no active row in the tiles
+        }
+        // tiles past the last one: every row is past n
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+        for (int g = 0; g < G; ++g) T::load(X, n, d, (tile + g * nwaves) * T::RT, lane, x[g], (kBits && SKIP) ? bits[g] : ~0ull);
 #pragma unroll
-                for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[u][e], acc[e]);
+        for (int g = 0; g < G; ++g) {
+            const int64_t t = tile + g * nwaves, row = t * T::RT + own;
+            if (kBits && !SKIP) bits[g] = (t < ntiles) ? Dbits[t] : 0;
+            Drow[g] = 0.0;
+            if (kBits) {
+                Drow[g] = ((bits[g] >> own) & 1u) ? 2.0 : 0.0;
+            } else if (row < n) {
+                Drow[g] = MASK ? (Dm[row] ? 2.0 : 0.0) : D[row];
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (DIAG) {
+                T::from_row_owner(Drow[g], c);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) acc[e] = fma(c[u] * x[g][u][e], x[g][u][e], acc[e]);
+                }
+            } else {
+                T::from_row_owner(Drow[g] * T::row_sum(x[g], vreg, lane), c);   // a1 = D (X v)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[g][u][e], acc[e]);
+                }
             }
         }
     }
@@ -498,7 +522,7 @@ int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *l
 {
     constexpr int U = pick_U(E, L);
     const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
-    const int grid = ds->dense_grid;
+    const int grid = dense_fun_grad_grid(ds->n, ds->d, loss);
 #define TRON_FG(V, LS) \
     hipLaunchKernelGGL((k_dense_fun_grad<E, L, U, V, LS>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, ds->X, ds->y8, w, Dout, ds->partials, loss_partials, active_partials, fin)
     if (loss == TRON_LOSS_LR) {
@@ -517,7 +541,7 @@ int launch_round(tron_dataset *ds, const SolveParams &P, const RoundArgs &A, int
         constexpr int U = pick_U(E, L);
         const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
 #define TRON_ROUND(V, LS) \
-    hipLaunchKernelGGL((k_dense_round<E, L, U, V, LS>), dim3(ds->dense_grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp)
+    hipLaunchKernelGGL((k_dense_round<E, L, U, V, LS>), dim3(dense_round_grid(ds->n, ds->d, P.loss)), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp)
         if (P.loss == TRON_LOSS_LR) {
             if (vec) TRON_ROUND((E % 2 == 0), TRON_LOSS_LR); else TRON_ROUND(false, TRON_LOSS_LR);
         } else {
@@ -812,6 +836,28 @@ static int grid_up_to(int64_t n, int64_t d, int64_t most)
 int dense_grid_for(int64_t n, int64_t d) { return grid_up_to(n, d, d <= kFinishMaxD ? kFinishGrid : kWideGrid); }
 int dense_grid_few(int64_t n, int64_t d) { return grid_up_to(n, d, kFewGrid); }
 
+// A function/gradient pass over narrow rows is bound by the chain of operations of a tile, not by its bytes, so what helps is
+// more wavefronts; their tickets (10 ns each) pay from some millions of rows on, in the rounds of a solve, where the Hessian-vector
+// passes pay them too, later than in calls.  Calls with 256 / 512 workgroups: 20M rows, d = 1 L2-SVM 88 / 58 us, logistic
+// 169 / 121; d = 4 155 / 133 and 192 / 174; d = 5 L2-SVM 187 / 161, logistic 214 / 212 (the rounds lose by it: 1007 / 1032 a
+// solve); 4M x 3 37 / 36 and 45 / 41, 4M x 4 38 / 40 and 45 / 42; 2M x 2 25 / 26 and 32 / 31.  512 / 1024, 20M rows, L2-SVM: d = 1
+// 58 / 52, d = 2 86 / 77, d = 3 105 / 114; a solve's rounds, 40M x 2: 450 / 472.
+constexpr int64_t kNarrowRows = 6'000'000, kNarrowCallRows = 3'000'000, kNarrowestRows = 16'000'000;
+constexpr int kNarrowGrid = 512, kNarrowestGrid = 1024;
+
+int dense_round_grid(int64_t n, int64_t d, int loss)
+{
+    const bool narrow = d <= 4 || (d == 5 && loss == TRON_LOSS_L2SVM);
+    return narrow && n >= kNarrowRows ? grid_up_to(n, d, kNarrowGrid) : dense_grid_for(n, d);
+}
+
+int dense_fun_grad_grid(int64_t n, int64_t d, int loss)
+{
+    if (d <= 2 && n >= kNarrowestRows) return grid_up_to(n, d, kNarrowestGrid);
+    if (d <= 3 && n >= kNarrowCallRows) return grid_up_to(n, d, kNarrowGrid);
+    return dense_round_grid(n, d, loss);
+}
+
 int dense_work_units(int64_t n, int64_t d)
 {
     Shape s;
@@ -824,7 +870,8 @@ int dense_work_units(int64_t n, int64_t d)
 // column sums (grid * d) followed by loss partials (grid), the column workgroups' sums (d) and active-row counts (grid)
 int64_t dense_partials_needed(int64_t n, int64_t d)
 {
-    const int64_t g = d <= kFinishMaxD ? dense_grid_few(n, d) : dense_grid_for(n, d);   // the largest grid of a pass
+    int64_t g = d <= kFinishMaxD ? dense_grid_few(n, d) : dense_grid_for(n, d);   // the largest grid of a pass
+    for (int loss : {TRON_LOSS_LR, TRON_LOSS_L2SVM}) g = std::max<int64_t>(g, dense_fun_grad_grid(n, d, loss));
     return d * g + g + d + g;
 }
 
@@ -857,8 +904,9 @@ int dense_hess_diag(tron_dataset *ds, double C, int Dslot, double *out)
 
 int dense_round(tron_dataset *ds, const SolveParams &P, DriverState &drv, int64_t stamp)
 {
-    double *loss_partials = ds->partials + ds->d * ds->dense_grid;
-    const RoundArgs A{ds->X, ds->y8, {ds->Dbuf[0], ds->Dbuf[1]}, ds->partials, loss_partials, loss_partials + ds->dense_grid + ds->d,
+    const int grid = dense_round_grid(ds->n, ds->d, P.loss);
+    double *loss_partials = ds->partials + ds->d * grid;
+    const RoundArgs A{ds->X, ds->y8, {ds->Dbuf[0], ds->Dbuf[1]}, ds->partials, loss_partials, loss_partials + grid + ds->d,
                       ds->ticket, drv.ctl, drv.st, P.trace_cap > 0 ? drv.trace_dev : nullptr, drv.host_dev};
     ProfScope ps(ds, SLOT_BATCH_PASS);
     return dispatch_round(ds, P, A, stamp);
@@ -869,7 +917,7 @@ int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Ds
     void *Dout = ds->Dbuf[Dslot];
     if (ds->hat_slot == Dslot) ds->hat_slot = -1;   // the compacted copy belonged to the D that is overwritten now
     ds->D_is_mask[Dslot] = (loss == TRON_LOSS_L2SVM);
-    const int grid = ds->dense_grid;
+    const int grid = dense_fun_grad_grid(ds->n, ds->d, loss);
     double *loss_partials = ds->partials + ds->d * grid;
     double *col_partials = loss_partials + grid;
     double *active_partials = col_partials + ds->d;
