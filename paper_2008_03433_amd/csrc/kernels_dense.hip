@@ -839,9 +839,9 @@ int dense_grid_few(int64_t n, int64_t d) { return grid_up_to(n, d, kFewGrid); }
 // A function/gradient pass over narrow rows is bound by the chain of operations of a tile, not by its bytes, so what helps is
 // more wavefronts; their tickets (10 ns each) pay from some millions of rows on, in the rounds of a solve, where the Hessian-vector
 // passes pay them too, later than in calls.  Calls with 256 / 512 workgroups: 20M rows, d = 1 L2-SVM 88 / 58 us, logistic
-// 169 / 121; d = 4 155 / 133 and 192 / 174; d = 5 L2-SVM 187 / 161, logistic 214 / 212 (the rounds lose by it: 1007 / 1032 a
-// solve); 4M x 3 37 / 36 and 45 / 41, 4M x 4 38 / 40 and 45 / 42; 2M x 2 25 / 26 and 32 / 31.  512 / 1024, 20M rows, L2-SVM: d = 1
-// 58 / 52, d = 2 86 / 77, d = 3 105 / 114; a solve's rounds, 40M x 2: 450 / 472.
+// 169 / 121; d = 4 155 / 133 and 192 / 174; d = 5 L2-SVM 187 / 161, logistic 214 / 212, 6M rows 74 / 64 (the logistic rounds
+// lose by it: 20M x 5 1007 / 1032 us a solve); 4M x 3 37 / 36 and 45 / 41, 4M x 4 38 / 40 and 45 / 42; 2M x 2 25 / 26 and
+// 32 / 31.  512 / 1024, 20M rows, L2-SVM: d = 1 58 / 52, d = 2 86 / 77, d = 3 105 / 114; a solve's rounds, 40M x 2: 450 / 472.
 constexpr int64_t kNarrowRows = 6'000'000, kNarrowCallRows = 3'000'000, kNarrowestRows = 16'000'000;
 constexpr int kNarrowGrid = 512, kNarrowestGrid = 1024;
 
@@ -854,7 +854,7 @@ int dense_round_grid(int64_t n, int64_t d, int loss)
 int dense_fun_grad_grid(int64_t n, int64_t d, int loss)
 {
     if (d <= 2 && n >= kNarrowestRows) return grid_up_to(n, d, kNarrowestGrid);
-    if (d <= 3 && n >= kNarrowCallRows) return grid_up_to(n, d, kNarrowGrid);
+    if ((d <= 3 && n >= kNarrowCallRows) || (d <= 5 && n >= kNarrowRows)) return grid_up_to(n, d, kNarrowGrid);
     return dense_round_grid(n, d, loss);
 }
 
