@@ -215,8 +215,11 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         h_rowptr = rowptr_copy.data();
     }
     if (h_rowptr[0] != 0) { set_error("rowptr[0] = %lld, expected 0", (long long)h_rowptr[0]); return TRON_EINVAL; }
-    for (int64_t i = 0; i < n; ++i)
+    int64_t rows_used = 0, cols_used = 0;   // rows and columns with entries
+    for (int64_t i = 0; i < n; ++i) {
         if (h_rowptr[i + 1] < h_rowptr[i]) { set_error("rowptr decreases at row %lld", (long long)i); return TRON_EINVAL; }
+        rows_used += h_rowptr[i + 1] > h_rowptr[i];
+    }
     const int64_t nnz = h_rowptr[n];
     if (nnz > 0 && (!col || !val)) { set_error("col/val are null but nnz = %lld", (long long)nnz); return TRON_EINVAL; }
     if (mem == TRON_MEM_DEVICE) {
@@ -269,9 +272,6 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
             for (unsigned t = 0; t < T; ++t)
                 for (int64_t c = c0; c < c1; ++c) t_rowptr[c + 1] += block_count[(size_t)t * (size_t)d + c];
         });
-    int64_t cols_used = 0, rows_used = 0;
-    for (int64_t c = 0; c < d; ++c) cols_used += t_rowptr[c + 1] > 0;
-    for (int64_t i = 0; i < n; ++i) rows_used += h_rowptr[i + 1] > h_rowptr[i];
     // Unit plans: when both layouts are partitioned and every instance's entries share one value r_i (binary features,
     // optionally scaled per instance, e.g. normalised to unit length), X = diag(r) B with B binary: the layouts keep no
     // values, the row sums of X are multiplied by r afterwards and X^T gathers from r .* (its vector).
@@ -322,7 +322,11 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         }
     }
     // explicit transposed copy (d x n): counting sort by column keeps rows ascending inside each column
-    for (int64_t j = 0; j < d; ++j) t_rowptr[j + 1] += t_rowptr[j];
+    cols_used = nhot;
+    for (int64_t j = 0; j < d; ++j) {
+        cols_used += t_rowptr[j + 1] > 0;
+        t_rowptr[j + 1] += t_rowptr[j];
+    }
     const int64_t t_nnz = t_rowptr[d];
     HostArray<int32_t> t_col;
     HostArray<double> t_val;
@@ -424,8 +428,8 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
     }
     if (rc >= 0) {
         int64_t need = 0;
-        if (!ds->fwd.plain) need = std::max<int64_t>(need, ds->fwd.nseg_total);   // one partial sum per segment
-        if (!ds->bwd.plain) need = std::max<int64_t>(need, ds->bwd.nseg_total);
+        if (!ds->fwd.plain && !ds->fwd.direct) need = std::max<int64_t>(need, ds->fwd.nseg_total);   // one partial sum per segment
+        if (!ds->bwd.plain && !ds->bwd.direct) need = std::max<int64_t>(need, ds->bwd.nseg_total);
         if (need > 0) {
             hipError_t e = hipMalloc(reinterpret_cast<void **>(&ds->row_partials), sizeof(double) * need);
             if (e != hipSuccess) rc = hip_fail(e, "allocate row partials", __FILE__, __LINE__);

@@ -279,8 +279,8 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         std::vector<int32_t> len32((size_t)NP * rows, 0);         // its number of entries
         std::vector<int32_t> head_cnt(sell ? (size_t)rows : 0, 0);   // entries of the row in a head kept as sorted slices
         // one table for the passes over the entries below: partition in the upper half, LDS slot + 1 (0: none) in the lower
-        std::vector<int32_t> code_of((size_t)cols);
-        for (int64_t j = 0; j < cols; ++j) code_of[j] = ((int32_t)part_of[j] << 16) | ((hot && slot_of[j] >= 0) ? slot_of[j] + 1 : 0);
+        std::vector<int32_t> code_of(P > 1 ? (size_t)cols : 0);
+        for (int64_t j = 0; P > 1 && j < cols; ++j) code_of[j] = ((int32_t)part_of[j] << 16) | ((hot && slot_of[j] >= 0) ? slot_of[j] + 1 : 0);
         parallel_ranges(rows, A.nnz, [&](int64_t r0, int64_t r1) {
             if (P == 1) {
                 for (int64_t r = r0; r < r1; ++r) len32[(size_t)r] = (int32_t)(h_rowptr[r + 1] - h_rowptr[r]);
@@ -516,24 +516,12 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         TRON_TRY(upload(&A.col, pcol.data(), stored_cols, st));
         if (!A.unit) TRON_TRY(upload(&A.val, pval.data(), (size_t)pos, st));
         else TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.xs), sizeof(double) * (size_t)(cols + 1)));
-        // group_base[G].first[x] = first segment of partition x whose row is >= 64 G (see sum_parts)
-        A.ngroups = (rows + kWave - 1) / kWave;
         A.nseg_total = nseg_total;
-        std::vector<GroupBase> gbase((size_t)A.ngroups);
-        std::memset(gbase.data(), 0, sizeof(GroupBase) * gbase.size());
-        for (int x = 0; x < NP; ++x) {
-            const int64_t s0 = A.part_seg0[x], s1 = (x + 1 < NP) ? A.part_seg0[x + 1] : nseg_total;
-            int64_t m = s0;
-            for (int64_t G = 0; G < A.ngroups; ++G) {
-                while (m < s1 && seg_row[m] < G * kWave) ++m;
-                gbase[(size_t)G].first[x] = (int32_t)m;
-            }
-        }
         // A single range: the kernel applies the epilogue itself where every chunk has a bounded number of rows (the empty ones
         // among them) and the sums it leaves are few enough to be added up by the kernel after it.
         if (P == 1) {
             const int nlong = (int)fix_row.size();
-            std::vector<int32_t> rl((size_t)chunk + 1), row_seg((size_t)rows, -1);
+            std::vector<int32_t> rl((size_t)chunk + 1);
             int64_t r = 0, most = 0;
             for (int c = 0; c < chunk; ++c) {
                 while (r < rows && rp32[r] < (int64_t)c * kChunk) ++r;
@@ -543,9 +531,10 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
             rl[chunk] = (int32_t)rows;
             most = std::max<int64_t>(most, rows - rl[chunk - 1]);
             if (most <= 4 * kChunk && chunk + nlong <= kDirectMaxSums) {
+                std::vector<int32_t> row_seg((size_t)rows, -1);
                 for (int64_t m = 0; m < nseg_total; ++m) row_seg[seg_row[m]] = (int32_t)m;
                 std::vector<int2> chunk_long((size_t)chunk, make_int2(-1, -1));
-                std::vector<int4> long_row((size_t)std::max(nlong, 1));
+                std::vector<int4> long_row((size_t)nlong);
                 for (int l = 0; l < nlong; ++l) {
                     long_row[l] = make_int4(seg_row[fix_row[l]], fix_b0[l], fix_cnt[l], 0);
                     chunk_long[fix_b0[l] - 1].y = l;
@@ -554,28 +543,47 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
                 TRON_TRY(upload(&A.row_lo, rl.data(), rl.size(), st));
                 TRON_TRY(upload(&A.row_seg, row_seg.data(), row_seg.size(), st));
                 TRON_TRY(upload(&A.chunk_long, chunk_long.data(), chunk_long.size(), st));
-                TRON_TRY(upload(&A.long_row, long_row.data(), long_row.size(), st));
-                TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.long_first), sizeof(double) * std::max(nlong, 1)));
-                TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.long_ticket), sizeof(unsigned) * std::max(nlong, 1)));
-                TRON_HIP(hipMemsetAsync(A.long_ticket, 0, sizeof(unsigned) * std::max(nlong, 1), st));
+                if (nlong) {
+                    TRON_TRY(upload(&A.long_row, long_row.data(), long_row.size(), st));
+                    TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.long_first), sizeof(double) * nlong));
+                    TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.long_ticket), sizeof(unsigned) * nlong));
+                    TRON_HIP(hipMemsetAsync(A.long_ticket, 0, sizeof(unsigned) * nlong, st));
+                }
                 TRON_HIP(hipStreamSynchronize(st));
                 A.direct = true;
             }
         }
-        TRON_TRY(upload(&A.group_base, gbase.data(), gbase.size(), st));
+        if (!A.direct) {   // what the combine kernels read
+            // group_base[G].first[x] = first segment of partition x whose row is >= 64 G (see sum_parts)
+            A.ngroups = (rows + kWave - 1) / kWave;
+            std::vector<GroupBase> gbase((size_t)A.ngroups);
+            std::memset(gbase.data(), 0, sizeof(GroupBase) * gbase.size());
+            for (int x = 0; x < NP; ++x) {
+                const int64_t s0 = A.part_seg0[x], s1 = (x + 1 < NP) ? A.part_seg0[x + 1] : nseg_total;
+                int64_t m = s0;
+                for (int64_t G = 0; G < A.ngroups; ++G) {
+                    while (m < s1 && seg_row[m] < G * kWave) ++m;
+                    gbase[(size_t)G].first[x] = (int32_t)m;
+                }
+            }
+            TRON_TRY(upload(&A.group_base, gbase.data(), gbase.size(), st));
+            TRON_TRY(upload(&A.row_mask, mask.data(), mask.size(), st));
+            TRON_HIP(hipStreamSynchronize(st));   // gbase goes out of scope
+        }
         TRON_TRY(upload(&A.chunk_tab, tab.data(), tab.size(), st));
         TRON_TRY(upload(&A.flags, flags.data(), flags.size(), st));
-        TRON_TRY(upload(&A.row_mask, mask.data(), mask.size(), st));
         TRON_HIP(hipStreamSynchronize(st));
     }
     A.nfix = (int)fix_row.size();
     A.fix_max_cnt = 0;
     for (int32_t c : fix_cnt) A.fix_max_cnt = std::max(A.fix_max_cnt, (int)c);
     if (A.plain) TRON_TRY(upload(&A.row_lo, row_lo.data(), row_lo.size(), st));
-    TRON_TRY(upload(&A.fix_row, fix_row.data(), fix_row.size(), st));
-    TRON_TRY(upload(&A.fix_part, fix_part.data(), fix_part.size(), st));
-    TRON_TRY(upload(&A.fix_b0, fix_b0.data(), fix_b0.size(), st));
-    TRON_TRY(upload(&A.fix_cnt, fix_cnt.data(), fix_cnt.size(), st));
+    if (!A.direct) {   // (its long rows are in long_row)
+        TRON_TRY(upload(&A.fix_row, fix_row.data(), fix_row.size(), st));
+        TRON_TRY(upload(&A.fix_part, fix_part.data(), fix_part.size(), st));
+        TRON_TRY(upload(&A.fix_b0, fix_b0.data(), fix_b0.size(), st));
+        TRON_TRY(upload(&A.fix_cnt, fix_cnt.data(), fix_cnt.size(), st));
+    }
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.carry), sizeof(double) * A.nblocks));
     TRON_HIP(hipMemsetAsync(A.carry, 0, sizeof(double) * A.nblocks, st));
     TRON_HIP(hipStreamSynchronize(st));  // the host vectors above go out of scope
