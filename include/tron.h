@@ -100,6 +100,9 @@ TRON_API int tron_dataset_shape(const tron_dataset *ds, int64_t *n, int64_t *d, 
  *   "fwd_parts", "bwd_parts"   column partitions of the forward / transposed CSR layouts (0 for dense)
  *   "fwd_segmented", "bwd_segmented"  1 when that layout stores row segments + flag bits (every partitioned layout, and
  *                              unpartitioned ones whose chunks mix long and short rows), 0 for plain CSR
+ *   "fwd_single_launch", "bwd_single_launch"  1 when one launch forms a product with that layout, its epilogue and its share
+ *                              of the scalars (unpartitioned layouts that leave at most 2560 sums; plain CSR: no row longer
+ *                              than a chunk of 2048 entries, segments: at most 8192 rows, empty ones included, a chunk)
  *   "fwd_csr_nnz", "bwd_csr_nnz"  nonzeros held in those CSR layouts
  *   "fwd_head_nnz"             of fwd_csr_nnz, the nonzeros of the head partition (the most frequent columns)
  *   "bwd_tile_nnz", "bwd_tile_rows", "bwd_tiles"  nonzeros, features and tiles of the hot-row tiles

@@ -555,6 +555,8 @@ int tron_dataset_stat(const tron_dataset *ds, const char *name, int64_t *value)
         {"bwd_parts", ds->dense ? 0 : ds->bwd.P},
         {"fwd_segmented", (ds->dense || ds->fwd.plain) ? 0 : 1},
         {"bwd_segmented", (ds->dense || ds->bwd.plain) ? 0 : 1},
+        {"fwd_single_launch", (!ds->dense && single_sums(ds->fwd)) ? 1 : 0},
+        {"bwd_single_launch", (!ds->dense && single_sums(ds->bwd)) ? 1 : 0},
         {"fwd_csr_nnz", ds->dense ? 0 : ds->fwd.nnz},
         {"fwd_head_nnz", (ds->dense || ds->fwd.head < 0) ? 0 : ds->fwd.part_nnz[ds->fwd.head]},
         {"bwd_csr_nnz", ds->dense ? 0 : ds->bwd.nnz},

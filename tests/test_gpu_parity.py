@@ -9,7 +9,7 @@ from oracle import LOSS_LR, LOSS_L2SVM
 
 pytestmark = pytest.mark.gpu
 
-from util import check_calls, compare_solves, dev, torch_mod  # noqa: E402
+from util import assert_vec_close, check_calls, compare_solves, dev, torch_mod  # noqa: E402
 
 
 def _dense(rng, n, d, name="rand"):
@@ -480,6 +480,57 @@ def test_csr_rows_longer_than_a_chunk(rng, loss, segmented, lengths):
         check_calls(_csr_rows(rng, lengths, 8000), loss, 0.5, rng, w_scale=0.3, n_hv=3)
     finally:
         tron.tron_tuning_set("csr_segmented", -1)
+
+
+def _check_single_range(p, loss, rng, segmented, single):
+    """Calls, the Hessian diagonal and a preconditioned solve on an unpartitioned matrix; single: whether each of the two layouts
+    is one whose products take one launch."""
+    import paper_2008_03433_amd as tron
+    from oracle import Oracle
+    torch = torch_mod()
+    tron.tron_tuning_set("csr_segmented", segmented)
+    try:
+        ds = tron.Dataset.from_problem(p)
+        try:
+            for name, want in (("fwd_parts", 1), ("bwd_parts", 1), ("fwd_segmented", segmented), ("bwd_segmented", segmented),
+                               ("fwd_single_launch", int(single[0])), ("bwd_single_launch", int(single[1]))):
+                assert tron.tron_dataset_stat(ds.handle, name) == want, name
+            w = 0.3 * rng.standard_normal(p.d)
+            ds.fun_grad(loss, 0.5, dev(w), None)
+            hd = torch.empty(p.d, dtype=torch.float64, device="cuda")
+            ds.hess_diag(0.5, hd)
+            o = Oracle.from_problem(p)
+            assert_vec_close(hd.cpu().numpy(), o.hess_diag(0.5, o.fun_grad(loss, 0.5, w)[2]), what="diag(H)")
+        finally:
+            ds.close()
+        check_calls(p, loss, 0.5, rng, w_scale=0.3, n_hv=2)
+        compare_solves(p, loss, 0.1, 1e-2, precond_blend=0.01)
+    finally:
+        tron.tron_tuning_set("csr_segmented", -1)
+
+
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("rows,cols,single", [(8100, 7000, True), (8300, 8300, False)])
+def test_csr_segments_with_empty_rows_around_the_limit(rng, loss, rows, cols, single):
+    """A chunk that looks after up to 8192 rows, and one that looks after more (the sums then go through the fix-up and combine
+    kernels): runs of empty rows and columns, the columns' beside a thousand with two entries each; and long rows."""
+    p = _csr_rows(rng, [6200, 5] + [0] * rows + [2050, 7, 4097, 300], 6300)
+    p.col[p.col >= 3000] += cols
+    p = SparseProblem("gap", p.n, 6300 + cols, p.rowptr, p.col, p.val, p.y)
+    _check_single_range(p, loss, rng, 1, (single, single))
+
+
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("segmented", [0, 1])
+@pytest.mark.parametrize("n,single", [(48_000, True), (60_000, False)])
+def test_csr_single_range_around_the_limit_of_its_sums(rng, loss, segmented, n, single):
+    """4.8M and 6M entries in rows of 100: 2400 and 3000 chunks, either side of the 2560 sums that the kernel after a product
+    adds up.  The columns are longer than a chunk: the plain layout completes them by the fix-up kernel."""
+    d, per = 150, 100
+    col = np.sort(np.argpartition(rng.random((n, d), dtype=np.float32), per, axis=1)[:, :per], axis=1).astype(np.int32).ravel()
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0)
+    p = SparseProblem("short-wide", n, d, np.arange(0, n * per + 1, per, dtype=np.int64), col, rng.standard_normal(n * per) / 30.0, y)
+    _check_single_range(p, loss, rng, segmented, (single, single and segmented == 1))
 
 
 @pytest.mark.parametrize("blend", [0.0, 0.01])
