@@ -599,6 +599,7 @@ int launch_columns(tron_dataset *ds, int grid, const double *partials, double *c
                    const DenseFinish &fin)
 {
     if (ds->d <= kFinishMaxD) return TRON_OK;
+    ProfScope ps(ds, SLOT_DENSE_FINALIZE);
     hipLaunchKernelGGL(k_dense_columns, dim3((unsigned)((ds->d + kColumnsPer - 1) / kColumnsPer)), dim3(kColumnsBlock), 0, ds->stream, (int)ds->d, grid,
                        partials, col_partials, loss_partials, active_partials, fin);
     TRON_HIP(hipGetLastError());
@@ -884,7 +885,6 @@ int dense_hv(tron_dataset *ds, double C, int Dslot, const double *v, double *Hv)
         TRON_TRY(dispatch_hv(ds, in, v, ds->partials, fin));
         TRON_HIP(hipGetLastError());
     }
-    ProfScope ps(ds, SLOT_DENSE_FINALIZE);
     return launch_columns(ds, in.grid, ds->partials, ds->partials + (ds->d + 1) * ds->dense_grid, nullptr, nullptr, fin);
 }
 
@@ -898,7 +898,6 @@ int dense_hess_diag(tron_dataset *ds, double C, int Dslot, double *out)
         TRON_TRY(dispatch_hv(ds, in, nullptr, ds->partials, fin));
         TRON_HIP(hipGetLastError());
     }
-    ProfScope ps(ds, SLOT_DENSE_FINALIZE);
     return launch_columns(ds, in.grid, ds->partials, ds->partials + (ds->d + 1) * ds->dense_grid, nullptr, nullptr, fin);
 }
 
@@ -927,7 +926,6 @@ int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Ds
         TRON_TRY(dispatch_fg(ds, loss, w, Dout, loss_partials, active_partials, fin));
         TRON_HIP(hipGetLastError());
     }
-    ProfScope ps(ds, SLOT_DENSE_FINALIZE);
     return launch_columns(ds, grid, ds->partials, col_partials, loss_partials, active_partials, fin);
 }
 

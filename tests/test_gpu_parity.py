@@ -441,6 +441,23 @@ def test_repeated_calls_are_bitwise_identical(rng):
         ds.close()
 
 
+def test_profile_counts_what_was_launched(rng):
+    """Up to 32 columns a dense pass completes its own sums; above, a second kernel does."""
+    import paper_2008_03433_amd as tron
+    for d, kernels in ((24, {"dense_fun_grad": 2, "dense_hv": 3}), (40, {"dense_fun_grad": 2, "dense_hv": 3, "dense_finalize": 5})):
+        ds = tron.Dataset.from_problem(_dense(rng, 300, d))
+        try:
+            w = dev(rng.standard_normal(d))
+            tron.tron_profile_enable(ds.handle, True)
+            for _ in range(2):
+                ds.fun_grad(LOSS_LR, 0.5, w, None)
+            for _ in range(3):
+                ds.hv(0.5, w, dev(np.zeros(d)))
+            assert {k: r["calls"] for k, r in tron.tron_profile_read(ds.handle).items()} == kernels
+        finally:
+            ds.close()
+
+
 def test_hv_requires_fun_grad(rng):
     torch = torch_mod()
     import paper_2008_03433_amd as tron
