@@ -531,15 +531,8 @@ int tron_dataset_stat(const tron_dataset *ds, const char *name, int64_t *value)
     PlanBytes fb{0, 0, 0, 0, 0, 0}, bb{0, 0, 0, 0, 0, 0};
     int64_t hv_bytes = 0, fun_grad_bytes = 0;
     if (ds->dense) {
-        // X once (the active rows only when the pass skips the others), D or the active-set bits / bytes, per-workgroup sums
-        const int slot = ds->Dcur;
-        const bool mask = ds->have_D && ds->D_is_mask[slot];
-        const double frac = (mask && ds->active_frac[slot] < 0.95) ? ds->active_frac[slot] : 1.0;
-        const int64_t dbytes = !mask ? 8 * ds->n : (ds->d <= 32 ? ds->n / 8 : ds->n);
-        hv_bytes = (int64_t)(8.0 * frac * (double)ds->n * (double)ds->d) + dbytes + 8 * ds->d * ds->dense_grid;
-        if (ds->have_D && ds->hat_slot == slot)   // the pass runs over the compacted copy
-            hv_bytes = 8 * ds->hat_rows * ds->d + ds->hat_rows / 8 + 8 * ds->d * dense_grid_for(ds->hat_rows, ds->d);
-        fun_grad_bytes = 8 * ds->n * ds->d + ds->n /* labels */ + dbytes + 8 * ds->d * ds->dense_grid;
+        hv_bytes = dense_hv_bytes(ds);
+        fun_grad_bytes = dense_fun_grad_bytes(ds);
     } else {
         fb = plan_bytes(ds->fwd);
         bb = plan_bytes(ds->bwd);

@@ -434,6 +434,10 @@ int dense_fun_grad_grid(int64_t n, int64_t d, int loss);   // of a function/grad
 int dense_round_grid(int64_t n, int64_t d, int loss);      // of a round of a solve driven from the device
 int dense_work_units(int64_t n, int64_t d);   // what tron_hv_static's limit counts: groups of four wave tiles, at most 2048
 int64_t dense_partials_needed(int64_t n, int64_t d);
+// bytes of a tron_hv / tron_fun_grad call with the D cached now (none: fp64): X -- of the rows the pass reads --, labels, D or the
+// active set, per-workgroup sums
+int64_t dense_hv_bytes(const tron_dataset *ds);
+int64_t dense_fun_grad_bytes(const tron_dataset *ds);
 // fused pass: z = X w, loss terms, D -> Dout, partial sums of X^T zhat and of the loss;
 // then g = w + C (column sums) (if g != null), scalars[0] = sum loss, [1] = w.w, [2] = g.g, [3] = rows with D != 0
 // (the caller reads the four scalars and records scalars[3] / n in active_frac[Dslot])

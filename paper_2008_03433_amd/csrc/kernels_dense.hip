@@ -876,6 +876,24 @@ int64_t dense_partials_needed(int64_t n, int64_t d)
     return d * g + g + d + g;
 }
 
+// D of n rows as a pass keeps it: fp64, or the active set as one bit (d <= 32) or one byte a row
+static int64_t d_bytes(int64_t n, int64_t d, bool mask) { return !mask ? 8 * n : (d <= kFinishMaxD ? n / 8 : n); }
+
+int64_t dense_hv_bytes(const tron_dataset *ds)
+{
+    if (!ds->have_D) return 8 * ds->n * ds->d + d_bytes(ds->n, ds->d, false) + 8 * ds->d * ds->dense_grid;
+    const HvInput in = hv_input(ds, ds->Dcur);
+    const double frac = (in.skip && ds->d <= kFinishMaxD) ? ds->active_frac[ds->Dcur] : 1.0;   // the bytes of wider rows are all read
+    return (int64_t)(8.0 * frac * (double)in.n * (double)ds->d) + d_bytes(in.n, ds->d, in.mask) + 8 * ds->d * in.grid;
+}
+
+int64_t dense_fun_grad_bytes(const tron_dataset *ds)
+{
+    const bool mask = ds->have_D && ds->D_is_mask[ds->Dcur];
+    const int grid = dense_fun_grad_grid(ds->n, ds->d, mask ? TRON_LOSS_L2SVM : TRON_LOSS_LR);
+    return 8 * ds->n * ds->d + ds->n + d_bytes(ds->n, ds->d, mask) + 8 * ds->d * grid;
+}
+
 int dense_hv(tron_dataset *ds, double C, int Dslot, const double *v, double *Hv)
 {
     const HvInput in = hv_input(ds, Dslot);
@@ -972,7 +990,7 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
     const int units = dense_work_units(in.n, ds->d);
     const int64_t need = ds->d * units + ds->d + 1;
     if (need > kStaticScratchDoubles) {
-        set_error("tron_hv_static: n = %lld, d = %lld needs %lld doubles of work space (d * %d workgroups + d + 1); the static "
+        set_error("tron_hv_static: n = %lld, d = %lld needs %lld doubles of work space (d * %d groups of four wave tiles + d + 1); the static "
                   "work space holds %lld: use tron_hv", (long long)ds->n, (long long)ds->d, (long long)need, units,
                   (long long)kStaticScratchDoubles);
         return TRON_EINVAL;

@@ -458,6 +458,30 @@ def test_profile_counts_what_was_launched(rng):
             ds.close()
 
 
+@pytest.mark.parametrize("d,workgroups", [(24, 512), (40, 512)])
+def test_byte_counts_follow_the_pass(rng, d, workgroups):
+    """tron_dataset_stat counts what the next pass reads: the active rows where it skips the others (d <= 32, then 512 workgroups
+    below one half), every row otherwise; the set as a bit or a byte a row; the sums of the workgroups launched."""
+    import paper_2008_03433_amd as tron
+    n = 400_000
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0)
+    X = rng.standard_normal((n, d))
+    X[:, 0] += 4.0 * y
+    ds = tron.Dataset.from_problem(DenseProblem("separable", n, d, X, y))
+    try:
+        w = np.zeros(d)
+        w[0] = 0.4
+        ds.fun_grad(LOSS_L2SVM, 0.5, dev(w), None)
+        active = int(np.sum(1.0 - y * (X @ w) > 0.0))
+        assert 0 < active < 0.5 * n
+        read, bits = (active, n // 8) if d <= 32 else (n, n)
+        assert abs(tron.tron_dataset_stat(ds.handle, "hv_bytes") - (8 * read * d + bits + 8 * d * workgroups)) <= 1
+        grid = 256 if d <= 32 else 512
+        assert tron.tron_dataset_stat(ds.handle, "fun_grad_bytes") == 8 * n * d + n + bits + 8 * d * grid
+    finally:
+        ds.close()
+
+
 def test_hv_requires_fun_grad(rng):
     torch = torch_mod()
     import paper_2008_03433_amd as tron
