@@ -89,14 +89,6 @@ static int check_device()
     return TRON_OK;
 }
 
-static int vec_grid_for(int64_t m)
-{
-    int64_t g = (m + kBlock * 4 - 1) / (kBlock * 4);
-    if (g < 1) g = 1;
-    if (g > kMaxGrid) g = kMaxGrid;
-    return (int)g;
-}
-
 static int alloc_common(tron_dataset *ds)
 {
     const int64_t n = ds->n;
@@ -124,8 +116,6 @@ static int alloc_common(tron_dataset *ds)
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->scal_copy), sizeof(double) * kScalars));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->ticket), 64));
     TRON_HIP(hipMemset(ds->ticket, 0, 64));
-    ds->vec_grid_n = vec_grid_for(ds->n);
-    ds->vec_grid_d = vec_grid_for(ds->d);
     return TRON_OK;
 }
 

@@ -220,7 +220,6 @@ struct CsrPlan {
     int nfix = 0;                        // number of (partition, split row) pairs
     int fix_max_cnt = 0;                 // largest fix_cnt
     int32_t *fix_row = nullptr;          // device, nfix: the split row (P > 1: its segment's slot in the partial sums)
-    int32_t *fix_part = nullptr;         // device, nfix: 0 (kept for the address arithmetic shared by both layouts)
     int32_t *fix_b0 = nullptr;           // device, nfix: first chunk id holding a continuation of it
     int32_t *fix_cnt = nullptr;          // device, nfix: number of consecutive chunks that do
     // ---- P == 1
@@ -292,7 +291,6 @@ struct tron_dataset {
     unsigned *ticket = nullptr;  // counter of finished workgroups for reductions completed inside the producing kernel (zero between kernels)
     bool finish_done = false;    // the last producing kernel did: the next reduce_final call is a no-op
     int dense_grid = 0;          // workgroups of the dense kernels
-    int vec_grid_n = 0, vec_grid_d = 0;  // workgroups of elementwise kernels over n / d
 
     double *unit_scale = nullptr;  // sparse, unit plans: r (n), the value shared by the entries of instance i
 

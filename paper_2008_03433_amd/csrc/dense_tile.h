@@ -5,8 +5,6 @@
 
 namespace tron {
 
-constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
-
 // A wave tile of RT = U * 64 / L rows.  A row is covered by L consecutive lanes; lane q of them holds the columns
 // col(q, 0) .. col(q, E - 1): pieces of one or two columns (8 or 16 bytes) dealt to the L lanes in turn, so that one
 // load instruction reads L consecutive pieces of a row and the next one the pieces behind them.  (With E consecutive columns
@@ -24,10 +22,10 @@ struct Tile {
     static_assert(U == (L < 4 ? L : 4), "row_sum folds the rows of a step over lanes of one quad");
 
     // column of entry e of lane q of a row
-    __device__ static __forceinline__ constexpr int col(int q, int e) {  return VEC ? (e / 2) * 2 * L + 2 * q + (e & 1) : e * L + q; }
+    __device__ static __forceinline__ constexpr int col(int q, int e) { return VEC ? (e / 2) * 2 * L + 2 * q + (e & 1) : e * L + q; }
     // the tile row a lane owns, and whether it is the first of the lanes that own it (L > 4: every quad of a row's lanes
     // owns the same U rows)
-    __device__ static __forceinline__ int own_row(int lane) {  return (lane % U) * RW + lane / L; }
+    __device__ static __forceinline__ int own_row(int lane) { return (lane % U) * RW + lane / L; }
     __device__ static __forceinline__ bool first_owner(int lane) { return lane % L < U; }
 
     // bit i of the result = the owner of tile row i passes true (tiles of 64 rows)

@@ -62,7 +62,7 @@ void CsrPlan::release()
     hipFree(rowptr); hipFree(col); hipFree(col16); hipFree(val); hipFree(row_lo); hipFree(carry);
     hipFree(xs); hipFree(hot_ids); hipFree(hot_x); hipFree(group_base); hipFree(chunk_tab); hipFree(flags); hipFree(row_mask);
     hipFree(row_seg); hipFree(chunk_long); hipFree(long_row); hipFree(long_first); hipFree(long_ticket);
-    hipFree(fix_row); hipFree(fix_part); hipFree(fix_b0); hipFree(fix_cnt);
+    hipFree(fix_row); hipFree(fix_b0); hipFree(fix_cnt);
     *this = CsrPlan();
 }
 
@@ -75,41 +75,35 @@ static int upload(T **dst, const T *src, size_t count, hipStream_t st)
     return TRON_OK;
 }
 
-// row_lo / fix-up lists of one partition (or of the whole matrix when P == 1).
-// rp[r] = position of row r's first entry relative to the partition start; rp[rows] = nnz_x.
-template <typename RP>
-static void plan_chunks(const RP *rp, int64_t rows, int64_t nnz_x, int nchunks, int chunk0, int part,
-                        std::vector<int32_t> &row_lo, std::vector<int32_t> &fix_row, std::vector<int32_t> &fix_part,
+// row_lo / fix-up lists of the plain layout.  rp[r] = position of row r's first entry, rp[rows] = entries stored.
+static void plan_chunks(const int64_t *rp, int64_t rows, int nchunks, std::vector<int32_t> &row_lo, std::vector<int32_t> &fix_row,
                         std::vector<int32_t> &fix_b0, std::vector<int32_t> &fix_cnt)
 {
     // row_lo[c] = first row r with rp[r] >= c*kChunk; row_lo[nchunks] = rows
-    const size_t off = row_lo.size();
-    row_lo.resize(off + nchunks + 1);
+    row_lo.resize((size_t)nchunks + 1);
     int64_t r = 0;
     for (int c = 0; c < nchunks; ++c) {
         const int64_t start = (int64_t)c * kChunk;
-        while (r < rows && (int64_t)rp[r] < start) ++r;
-        row_lo[off + c] = (int32_t)r;
+        while (r < rows && rp[r] < start) ++r;
+        row_lo[c] = (int32_t)r;
     }
-    row_lo[off] = 0;
-    row_lo[off + nchunks] = (int32_t)rows;
-    // chunk c >= 1 begins inside row row_lo[c]-1 iff rp[row_lo[c]] > c*kChunk  (rp[rows] = nnz_x)
+    row_lo[0] = 0;
+    row_lo[nchunks] = (int32_t)rows;
+    // chunk c >= 1 begins inside row row_lo[c]-1 iff rp[row_lo[c]] > c*kChunk  (rp[rows] = entries stored)
     for (int c = 1; c < nchunks; ++c) {
         const int64_t start = (int64_t)c * kChunk;
-        const int32_t lo = row_lo[off + c];
-        if (lo >= 1 && (int64_t)rp[lo] > start) {
+        const int32_t lo = row_lo[c];
+        if (lo >= 1 && rp[lo] > start) {
             const int32_t row = lo - 1;
-            if (!fix_row.empty() && fix_row.back() == row && fix_part.back() == part) {
+            if (!fix_row.empty() && fix_row.back() == row) {
                 fix_cnt.back() += 1;
             } else {
                 fix_row.push_back(row);
-                fix_part.push_back(part);
-                fix_b0.push_back(chunk0 + c);
+                fix_b0.push_back(c);
                 fix_cnt.push_back(1);
             }
         }
     }
-    (void)nnz_x;
 }
 
 // Where entry e of a chunk is stored.  Thread t of a kernel owns entries 8t .. 8t+7 of a chunk, and its loads cover whole
@@ -130,7 +124,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
     if (parts > kColParts) parts = kColParts;
     A.P = parts;
     A.plain = (parts == 1);
-    std::vector<int32_t> row_lo, fix_row, fix_part, fix_b0, fix_cnt;
+    std::vector<int32_t> row_lo, fix_row, fix_b0, fix_cnt;
 
     if (A.unit && A.P == 1) { set_error("internal: unit plan without partitions"); return TRON_EINVAL; }
     if (A.plain && g_tuning.csr_segmented != 0) {
@@ -188,7 +182,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         A.nblocks = (int)nb64;
         A.part_base[0] = 0; A.part_nnz[0] = stored; A.part_chunk0[0] = 0; A.part_nchunks[0] = A.nblocks;
         A.max_chunks = A.nblocks;
-        plan_chunks(rp.data(), rows, stored, A.nblocks, 0, 0, row_lo, fix_row, fix_part, fix_b0, fix_cnt);
+        plan_chunks(rp.data(), rows, A.nblocks, row_lo, fix_row, fix_b0, fix_cnt);
         TRON_TRY(upload(&A.rowptr, rp.data(), (size_t)rows + 1, st));
         TRON_TRY(upload(&A.col, pcol.data(), (size_t)stored, st));
         TRON_TRY(upload(&A.val, pval.data(), (size_t)stored, st));
@@ -397,7 +391,6 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
                 }
                 if (c_last > c) {
                     fix_row.push_back((int32_t)(A.part_seg0[x] + m));   // partitioned plans: the segment's slot in the partial sums
-                    fix_part.push_back(0);
                     fix_b0.push_back(A.part_chunk0[x] + c + 1);
                     fix_cnt.push_back(c_last - c);
                 }
@@ -580,7 +573,6 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
     if (A.plain) TRON_TRY(upload(&A.row_lo, row_lo.data(), row_lo.size(), st));
     if (!A.direct) {   // (its long rows are in long_row)
         TRON_TRY(upload(&A.fix_row, fix_row.data(), fix_row.size(), st));
-        TRON_TRY(upload(&A.fix_part, fix_part.data(), fix_part.size(), st));
         TRON_TRY(upload(&A.fix_b0, fix_b0.data(), fix_b0.size(), st));
         TRON_TRY(upload(&A.fix_cnt, fix_cnt.data(), fix_cnt.size(), st));
     }
@@ -1584,9 +1576,8 @@ static int launch_hot_tiles(tron_dataset *ds, const CsrPlan &A, const double *x,
 // G lanes per split row: y[row] += factor * (carry[b0] + ... + carry[b0+cnt-1]).  G = 8 when no row spans more than
 // 64 chunks (one workgroup then fixes 32 rows), else a whole wavefront per row.
 template <int EPI, int G>
-__global__ __launch_bounds__(kBlock) void k_csr_fixup(int nfix, int64_t rows, const int32_t *__restrict__ fix_row,
-                                                      const int32_t *__restrict__ fix_part, const int32_t *__restrict__ fix_b0,
-                                                      const int32_t *__restrict__ fix_cnt, const double *__restrict__ carry,
+__global__ __launch_bounds__(kBlock) void k_csr_fixup(int nfix, const int32_t *__restrict__ fix_row,
+                                                      const int32_t *__restrict__ fix_b0, const int32_t *__restrict__ fix_cnt, const double *__restrict__ carry,
                                                       double *__restrict__ yout, const double *__restrict__ aux, double alpha)
 {
     const int m = blockIdx.x * (kBlock / G) + threadIdx.x / G;
@@ -1601,7 +1592,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_fixup(int nfix, int64_t rows, co
         double factor = 1.0;
         if (EPI == EPI_SCALE) factor = aux[r];
         if (EPI == EPI_AXPY) factor = alpha;
-        double *dst = yout + (int64_t)fix_part[m] * rows + r;   // fix_part is 0 when unpartitioned
+        double *dst = yout + r;
         *dst = fma(factor, s, *dst);
     }
 }
@@ -1613,12 +1604,12 @@ static int launch_fixup(tron_dataset *ds, const CsrPlan &A, double *yout, const 
     ProfScope ps(ds, SLOT_SPMV_FIXUP);
     if (A.fix_max_cnt <= 64) {
         const int per = kBlock / 8;
-        hipLaunchKernelGGL((k_csr_fixup<EPI, 8>), dim3((A.nfix + per - 1) / per), dim3(kBlock), 0, ds->stream, A.nfix, A.rows, A.fix_row,
-                           A.fix_part, A.fix_b0, A.fix_cnt, A.carry, yout, aux, alpha);
+        hipLaunchKernelGGL((k_csr_fixup<EPI, 8>), dim3((A.nfix + per - 1) / per), dim3(kBlock), 0, ds->stream, A.nfix, A.fix_row,
+                           A.fix_b0, A.fix_cnt, A.carry, yout, aux, alpha);
     } else {
         const int per = kBlock / kWave;
-        hipLaunchKernelGGL((k_csr_fixup<EPI, kWave>), dim3((A.nfix + per - 1) / per), dim3(kBlock), 0, ds->stream, A.nfix, A.rows,
-                           A.fix_row, A.fix_part, A.fix_b0, A.fix_cnt, A.carry, yout, aux, alpha);
+        hipLaunchKernelGGL((k_csr_fixup<EPI, kWave>), dim3((A.nfix + per - 1) / per), dim3(kBlock), 0, ds->stream, A.nfix,
+                           A.fix_row, A.fix_b0, A.fix_cnt, A.carry, yout, aux, alpha);
     }
     TRON_HIP(hipGetLastError());
     return TRON_OK;
