@@ -219,8 +219,9 @@ typedef struct {
  * giving it; this is the diagonal one of the work it cites, a = 0.01 being that work's choice.)
  * Returns TRON_OK when converged, TRON_EMAXITER when max_outer was reached or progress stalled.
  * On return the handle caches D at the final iterate (so tron_hv may follow).
- * Small dense L2-SVM problems (d <= 32, no preconditioner) are driven from the device, like tron_batch_solve with one
- * problem over all rows: same rules, same results up to summation order (knob "dense_device_driver").
+ * Dense problems with d <= 32 and no preconditioner -- logistic loss: of any size; L2-SVM: matrices up to 1 GB -- are driven
+ * from the device, like tron_batch_solve with one problem over all rows: same rules, same results up to summation order
+ * (knob "dense_device_driver").
  */
 TRON_API int tron_solve(tron_dataset *ds, const tron_params *params, double *w_dev, tron_result *res_host);
 
@@ -348,14 +349,15 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  *   tron_hv calls that follow), -1 (default) inside tron_solve when at most 60% of the rows are active and the last inner
  *   solve took at least ten products.  Read at call time, not at creation.
  * "dense_device_driver" (-1/0/1): tron_solve on a dense matrix with d <= 32 and no preconditioner runs its trust-region and
- *   CG steps on the device (as tron_batch_solve does): 0 never, 1 always, -1 (default) for the L2-SVM on matrices up to 1 GB.
+ *   CG steps on the device (as tron_batch_solve does): 0 never, 1 always, -1 (default) for the logistic loss, and for the
+ *   L2-SVM on matrices up to 1 GB (larger ones may put their products on a compacted copy, see above).
  * "batch_grid" (0..4096): workgroups of the multi-problem pass (0 = as many as are resident at once).
  * "batch_mfma_rows" (0/32/64): rows of X a wavefront of the matrix-unit pass keeps in LDS at a time (0: 32, except 64
  *                in the L2-SVM's rounds without function / gradient requests).
  * "batch_lean" (0/1, default 1): batches created afterwards run a round of the matrix-unit pass in which no problem asks
- *                for function and gradient (the Hessian-vector calls; inside tron_batch_solve the rounds right after the
- *                host has looked at the problems' requests) with a kernel compiled without the loss terms of such
- *                requests: fewer registers, so more wavefronts per SIMD.
+ *                for function and gradient (the Hessian-vector calls; inside tron_batch_solve, for matrices of 400 MB
+ *                or more, where the host waits for the requests of every round) with a kernel compiled without the loss
+ *                terms of such requests: fewer registers, so more wavefronts per SIMD.
  * "batch_mfma" (-1/0/1): batches created afterwards run the multi-problem pass on the fp64 matrix units (1), or on the
  *                vector units where those can hold the batch, i.e. up to eight problems (0); -1 (default): per loss,
  *                the matrix units from eight problems on for the L2-SVM and from five on for the logistic loss.
