@@ -6,13 +6,14 @@ exercises every stage of the path (z = Xw, loss terms, f reduction, gradient, th
 products of the CG loop, the CG vector updates and the host driver).  `value` is the number of
 Hessian-vector products completed per second of solve wall-clock (all stages included); the
 stand-alone tron_hv and tron_fun_grad rates, the solve seconds and the HBM roofline of the dominant
-kernel are reported next to it.  One JSON line is printed on stdout; progress goes to stderr.
+kernel are reported next to it.  One JSON line of a few hundred characters is printed on stdout; progress and the whole
+record (every kernel, call and workload measured; also written to --detail FILE) go to stderr.
 
     python bench.py [--workload c3|c5|c4|c2|c1] [--also c5|none] [--steps K] [--warmup W] [--gpus 1]
 
 The primary workload (default c3, the large sparse config) fills the top-level fields; the workload
 named by --also (default c5, the large dense config) is measured the same way and reported under
-"also".
+"also" of the whole record.
 """
 from __future__ import annotations
 
@@ -657,6 +658,30 @@ def stream_probe() -> dict:
             "copy_GB/s": 2 * half * 8 / (ms_copy * 1e-3) / 1e9, "copy_bytes_read": half * 8, "copy_bytes_written": half * 8}
 
 
+def short(x):
+    """Floats to six significant digits, inside lists and dicts too."""
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: short(v) for k, v in x.items()}
+    return [short(v) for v in x] if isinstance(x, (list, tuple)) else x
+
+
+def headline(out: dict) -> dict:
+    """What the line on stdout says of the whole record.  It stays below 2000 characters: a caller that keeps only the end of
+    the output still has all of it."""
+    keys = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config")
+    line = {k: out[k] for k in keys}
+    line["solve"] = {k: out["solve"][k] for k in ("outer_iters", "cg_iters", "f", "converged", "min_seconds")}
+    line["hv_call"] = {k: out["hv_call"][k] for k in ("ms", "frac_hbm_peak")}
+    line["roofline"] = {k: v for k, v in out["roofline"].items() if k not in ("also", "note", "in", "workload")}
+    if out.get("cpu_baseline"):
+        line["cpu_baseline"] = {k: out["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind", "sample")}
+    for w, sub in out.get("also", {}).items():
+        line["also"] = {"workload": w, "solve_ms": sub["ms_per_step"], "hv_call_ms": sub["hv_call"]["ms"], "hv_frac_hbm_peak": sub["hv_call"]["frac_hbm_peak"]}
+    return short(line)
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -672,6 +697,7 @@ def main() -> int:
     ap.add_argument("--only-cv", nargs="?", const="all", default=None, choices=["all", "c4", "20M"],
                     help="run the cross-validation (multi-problem) measurements only (optionally one of the two sizes)")
     ap.add_argument("--only-active-set", action="store_true", help="run the active-set sweep (dense L2-SVM, 20M x 24) only")
+    ap.add_argument("--detail", default=None, metavar="FILE", help="write the whole record there as well")
     ap.add_argument("--tune", action="append", default=[], metavar="KNOB=VALUE", help="library tuning knob (see tron_tuning_set)")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -726,7 +752,11 @@ def main() -> int:
         finally:
             tron.tron_tuning_set("csr_unit", 1)
         out["cross_validation"] = cross_validation_configs()
-    print(json.dumps(out), flush=True)
+    log("whole record: " + json.dumps(out))
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(headline(out)), flush=True)
     return 0
 
 

@@ -1,5 +1,6 @@
 """Host logic of bench.py that needs no GPU: the committed rocprofv3 summaries are read back as bytes per launch."""
 import importlib.util
+import json
 import os
 import subprocess
 import sys
@@ -33,3 +34,24 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_the_line_on_stdout_is_short_whatever_the_record_holds():
+    b = _bench()
+    x = 1234567.890123456
+    roofline = {"kernel": "spmv_tiles", "in": "kernels_hv", "bound": "hbm", "achieved": x, "peak": 8000.0, "unit": "GB/s", "frac": x, "traffic": x,
+                "ms_per_launch": x, "format_bytes_per_launch": x, "work_GB/s": x, "workload": "w" * 40, "note": "n" * 400, "also": [{"kernel": "k"}] * 30}
+    call = {"per_s": x, "ms": x, "GB/s": x, "frac_hbm_peak": x}
+    out = {"metric": "m" * 107, "value": x, "unit": "Hv/s", "n_gpus": 1, "steps": 20, "warmup": 5, "ms_per_step": x, "higher_is_better": True,
+           "scaling": "weak", "vs_baseline": None, "dtype": "f64", "data": "synthetic", "config": {f"key{i}": x for i in range(12)},
+           "solve": {"outer_iters": 5, "cg_iters": 22, "f": x, "converged": True, "min_seconds": x, "gnorm": x}, "hv_call": call, "roofline": roofline,
+           "cpu_baseline": {"value": x, "unit": "Hv/s", "cores": 1, "kind": "oracle", "sample": "s" * 250, "host_cpu": "c" * 50},
+           "also": {"c5": {"ms_per_step": x, "hv_call": call, "roofline": roofline}}, "others": {"c1": [x] * 1000}}
+    line = b.headline(out)
+    assert len(json.dumps(line)) < 2000
+    for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config"):
+        assert line[key] == b.short(out[key]), key
+    assert line["roofline"]["kernel"] == "spmv_tiles" and "also" not in line["roofline"]
+    assert abs(line["value"] / x - 1) < 1e-5
+    out["cpu_baseline"] = None
+    assert "cpu_baseline" not in b.headline(out)
