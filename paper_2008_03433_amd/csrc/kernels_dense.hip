@@ -33,7 +33,7 @@ namespace {
 //   fun_grad: scal[0] = sum of the losses, [1] = add.add (add = w), [2] = out.out, [3] = rows with D != 0;
 //   otherwise: scal[0] = scal_copy[0] = out.dotw (the CG step kernel continues from the copy).
 struct DenseFinish {
-    unsigned *ticket;      // counter of finished workgroups (zero between kernels)
+    unsigned *ticket;      // counter of finished workgroups (zero between kernels); d <= 32: null = the pass leaves its sums alone
     const double *add;
     double C;
     double *out;           // may be null
@@ -67,21 +67,18 @@ __device__ __forceinline__ void store_dense_scalars(const DenseFinish &fin, doub
     }
 }
 
-// Every thread of every workgroup calls it; wavefront 0 has written the workgroup's d <= 32 column sums (and its two
-// other sums) last.  The workgroup that draws the last ticket adds the rows of partial sums: thread t the elements t,
-// t + T, ... of the d x grid array, T a multiple of d, so all of them belong to column t % d; then over the threads of a
-// column in LDS (col_sum: a double per thread; its earlier contents have been read by wavefront 0 only).  True in wavefront 0
-// of that workgroup: lane c < d then has column c's sum, every lane the loss sum and the number of active rows (zero without
-// loss_partials); the caller clears the counter.
+// One workgroup adds the rows of partial sums of `grid` workgroups, d <= 32: thread t the elements t, t + T, ... of the
+// d x grid array, T a multiple of d, so all of them belong to column t % d; then over the threads of a column in LDS (col_sum:
+// a double per thread; its earlier contents have been read by wavefront 0 only).  True in wavefront 0: lane c < d then has
+// column c's sum, every lane the loss sum and the number of active rows (zero without loss_partials).
 template <int kWaves>
-__device__ __forceinline__ bool dense_last_sums(double *col_sum, unsigned *ticket, int d, const double *partials, const double *loss_partials,
-                                                const double *active_partials, double &col, double &loss, double &active)
+__device__ __forceinline__ bool dense_add_rows(double *col_sum, int grid, int d, const double *partials, const double *loss_partials,
+                                               const double *active_partials, double &col, double &loss, double &active)
 {
     constexpr int kThreads = kWaves * kWave, kAtOnce = 8;
     __shared__ double red[2][kWaves];
-    if (!last_workgroup(ticket)) return false;
     const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
-    const int groups = kThreads / d, T = groups * d, total = d * (int)gridDim.x;
+    const int groups = kThreads / d, T = groups * d, total = d * grid;
     double s = 0.0;
     if (t < T)
         for (int i0 = t; i0 < total; i0 += kAtOnce * T) {
@@ -94,7 +91,7 @@ __device__ __forceinline__ bool dense_last_sums(double *col_sum, unsigned *ticke
     col_sum[t] = s;
     double a = 0.0, e = 0.0;
     if (loss_partials) {
-        for (int b = t; b < (int)gridDim.x; b += kThreads) {
+        for (int b = t; b < grid; b += kThreads) {
             a += load_shared(loss_partials + b);
             e += load_shared(active_partials + b);
         }
@@ -124,12 +121,18 @@ __device__ __forceinline__ bool dense_last_sums(double *col_sum, unsigned *ticke
     return true;
 }
 
+// Every thread of every workgroup calls it; wavefront 0 has written the workgroup's column sums (and its two other sums) last.
+// The workgroup that draws the last ticket adds the rows; the caller clears the counter.
 template <int kWaves>
-__device__ __forceinline__ void dense_finish(double *lds, const DenseFinish &fin, int d, const double *partials, const double *loss_partials,
-                                             const double *active_partials)
+__device__ __forceinline__ bool dense_last_sums(double *col_sum, unsigned *ticket, int d, const double *partials, const double *loss_partials,
+                                                const double *active_partials, double &col, double &loss, double &active)
 {
-    double sum, loss, active;
-    if (!dense_last_sums<kWaves>(lds, fin.ticket, d, partials, loss_partials, active_partials, sum, loss, active)) return;
+    return last_workgroup(ticket) && dense_add_rows<kWaves>(col_sum, (int)gridDim.x, d, partials, loss_partials, active_partials, col, loss, active);
+}
+
+// what wavefront 0 forms from the sums: the outputs and the scalars
+__device__ __forceinline__ void dense_outputs(const DenseFinish &fin, int d, double sum, double loss, double active)
+{
     const int lane = threadIdx.x;
     double cp = 0.0, ww = 0.0;
     if (lane < d) {
@@ -141,10 +144,26 @@ __device__ __forceinline__ void dense_finish(double *lds, const DenseFinish &fin
     }
     cp = wave_sum(cp);
     ww = wave_sum(ww);
-    if (lane == 0) {
-        if (fin.scal) store_dense_scalars(fin, loss, ww, cp, active);
-        *fin.ticket = 0u;
-    }
+    if (lane == 0 && fin.scal) store_dense_scalars(fin, loss, ww, cp, active);
+}
+
+template <int kWaves>
+__device__ __forceinline__ void dense_finish(double *lds, const DenseFinish &fin, int d, const double *partials, const double *loss_partials,
+                                             const double *active_partials)
+{
+    double sum, loss, active;
+    if (!dense_last_sums<kWaves>(lds, fin.ticket, d, partials, loss_partials, active_partials, sum, loss, active)) return;
+    dense_outputs(fin, d, sum, loss, active);
+    if (threadIdx.x == 0) *fin.ticket = 0u;
+}
+
+// The same as a launch of its own behind a pass without a counter (tron_hv_static): the same sums in the same order.
+constexpr int kFinishBlock = dense_block(1);
+__global__ __launch_bounds__(kFinishBlock) void k_dense_finish(int d, int grid, const double *__restrict__ partials, DenseFinish fin)
+{
+    __shared__ double lds[kFinishBlock];
+    double sum, loss, active;
+    if (dense_add_rows<kFinishBlock / kWave>(lds, grid, d, partials, nullptr, nullptr, sum, loss, active)) dense_outputs(fin, d, sum, loss, active);
 }
 
 // Tiles whose loads a wavefront of the Hessian-vector pass issues together: a tile of narrow rows is only 512 d bytes, and eight
@@ -245,8 +264,10 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_hv(int64_t n, int64_t 
 {
     constexpr int kWaves = dense_block(L) / kWave;
     __shared__ double lds[dense_lds(E, L)];
+    // the counter of k_dense_columns starts at zero whatever an earlier call left in it
+    if constexpr (!dense_finishes(L)) { if (blockIdx.x == 0 && threadIdx.x == 0) *fin.ticket = 0u; }
     hv_pass<E, L, U, VEC, MASK, DIAG, SKIP>(lds, n, d, X, Dv, v, partials);
-    if constexpr (dense_finishes(L)) dense_finish<kWaves>(lds, fin, (int)d, partials, nullptr, nullptr);
+    if constexpr (dense_finishes(L)) { if (fin.ticket) dense_finish<kWaves>(lds, fin, (int)d, partials, nullptr, nullptr); }
 }
 
 // ------------------------------------------------------------------ function / gradient pass
@@ -964,13 +985,6 @@ struct StaticWork {
 __device__ __align__(256) StaticWork static_work;
 constexpr int kStaticMaxDevices = 64;
 StaticWork *g_static_work[kStaticMaxDevices] = {nullptr};   // device address of `static_work` on each GPU, looked up once
-
-// The counter starts every call at zero whatever an earlier one left: calls that overlapped (they race for the sums) spoil
-// their own results and no later ones.
-__global__ __launch_bounds__(tron::kWave) void k_clear_counter(unsigned *counter)
-{
-    if (threadIdx.x == 0) *counter = 0u;
-}
 }  // namespace
 
 extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, double *Hv_dev, double *vHv_dev)
@@ -1012,13 +1026,14 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
     double *partials = g_static_work[dev]->sums;
     double *colprod = partials + ds->d * grid;
     double *scalar = colprod + ds->d;
-    // Of the sums nothing has to start at zero: every workgroup of the pass writes all d of its column sums, the second stage
-    // the rest.
-    unsigned *ticket = &g_static_work[dev]->ticket;
-    hipLaunchKernelGGL(k_clear_counter, dim3(1), dim3(kWave), 0, ds->stream, ticket);
-    TRON_HIP(hipGetLastError());
-    const DenseFinish fin{ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false};
+    // Nothing has to start at zero: every workgroup of the pass writes all d of its column sums, the second stage the rest.  Calls
+    // that overlapped (they race for the sums) spoil their own results and no later ones: for d <= 32 the sums are added by a
+    // launch of its own, without a counter, for wider rows the pass clears the counter of k_dense_columns first.  (A counter in
+    // the pass needs a launch that clears it: 20,003 x 8 then takes 21.1 us a call, this way 18.8.)
+    const bool narrow = ds->d <= kFinishMaxD;
+    const DenseFinish fin{narrow ? nullptr : &g_static_work[dev]->ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false};
     TRON_TRY(dispatch_hv(ds, in, v_dev, partials, fin));
+    if (narrow) hipLaunchKernelGGL(k_dense_finish, dim3(1), dim3(kFinishBlock), 0, ds->stream, (int)ds->d, grid, partials, fin);
     TRON_HIP(hipGetLastError());
     return launch_columns(ds, grid, partials, colprod, nullptr, nullptr, fin);
 }
