@@ -489,10 +489,32 @@ __global__ __launch_bounds__(kColumnsBlock) void k_dense_columns(int d, int grid
 // ------------------------------------------------------------------ dispatch
 constexpr double kSkipBelow = 0.95;   // active fraction under which the Hessian-vector pass skips the inactive rows
 
+// A row that is left out saves bytes only if nothing else of its 128-byte lines is read.  For rows shorter than a line the pass
+// skips where at least a tenth of the lines is free of active rows, (1 - active)^(rows per line) >= 0.1.  L2-SVM calls, every
+// row read by 256 workgroups / the better of skipping with 256 and 512: 20M x 1, 0.2 of the rows active 40 / 43 us, 0.05
+// 40 / 38; 20M x 3, 0.5 91 / 91 (256: 125), 0.2 91 / 84; 16M x 5, 0.5 116 / 118 (256: 173), 0.2 116 / 108; 10M x 8, 0.85
+// 120 / 118 (256: 133), 0.5 115 / 95; 8M x 12, 0.94 141 / 142, 0.7 139 / 128; 6M x 16, 0.85 143 / 129.
+constexpr int kLineDoubles = 16;
+constexpr double kFreeLines = 0.1;
+
 // Where about half of the rows or fewer are read, the loads that are left out no longer fill the queue to HBM with eight
 // wavefronts per CU: d <= 32 then runs two workgroups per CU.  20M x 24, 256 / 512 workgroups: 0.72 of the rows active 490 / 503
-// us, 0.47 364 / 358, 0.38 335 / 294, 0.36 330 / 281.
+// us, 0.47 364 / 358, 0.38 335 / 294, 0.36 330 / 281.  Rows of a line or less gain at any fraction that is skipped once the
+// pass is long: 10M x 8, 0.7 active 127 / 112, 6M x 16, 0.85 133 / 129, 0.5 97 / 82; but 3M x 12, 0.5 48 / 49.  Below 2M rows the
+// additional tickets cost more: 1M x 24, 0.35 31 / 34, 1M x 8, 0.2 25 / 27, 200,000 x 4, 0.2 20 / 22 (2M x 24, 0.2 40 / 37).
 constexpr double kFewBelow = 0.5;
+constexpr int64_t kFewRows = 2'000'000, kFewShortRows = 6'000'000;
+
+bool skip_pays(int64_t d, double active)
+{
+    if (d >= kLineDoubles) return active < kSkipBelow;
+    return std::pow(std::max(0.0, 1.0 - active), (double)kLineDoubles / (double)d) >= kFreeLines;
+}
+
+bool few_active(int64_t n, int64_t d, double active)
+{
+    return d <= kFinishMaxD && n >= kFewRows && (active < kFewBelow || (d <= kLineDoubles && n >= kFewShortRows));
+}
 
 // What a Hessian-vector pass runs over: the matrix itself with D of one buffer, or the compacted copy of its active rows
 // (then every row is active: the bit words are all ones).
@@ -508,8 +530,9 @@ HvInput hv_input(const tron_dataset *ds, int Dslot)
 {
     if (ds->hat_slot == Dslot && ds->Xhat)
         return HvInput{ds->Xhat, ds->hat_rows, ds->hat_bits, true, false, dense_grid_for(ds->hat_rows, ds->d)};
-    const bool mask = ds->D_is_mask[Dslot], skip = mask && ds->active_frac[Dslot] < kSkipBelow;
-    const bool few = skip && ds->d <= kFinishMaxD && ds->active_frac[Dslot] < kFewBelow;
+    const double active = ds->active_frac[Dslot];
+    const bool mask = ds->D_is_mask[Dslot], skip = mask && skip_pays(ds->d, active);
+    const bool few = skip && few_active(ds->n, ds->d, active);
     return HvInput{ds->X, ds->n, ds->Dbuf[Dslot], mask, skip, few ? dense_grid_few(ds->n, ds->d) : ds->dense_grid};
 }
 

@@ -458,12 +458,11 @@ def test_profile_counts_what_was_launched(rng):
             ds.close()
 
 
-@pytest.mark.parametrize("d,workgroups", [(24, 512), (40, 512)])
-def test_byte_counts_follow_the_pass(rng, d, workgroups):
+@pytest.mark.parametrize("n,d,workgroups", [(400_000, 24, 256), (2_000_000, 8, 512), (400_000, 40, 512)])
+def test_byte_counts_follow_the_pass(rng, n, d, workgroups):
     """tron_dataset_stat counts what the next pass reads: the active rows where it skips the others (d <= 32, then 512 workgroups
-    below one half), every row otherwise; the set as a bit or a byte a row; the sums of the workgroups launched."""
+    below one half from 2M rows on), every row otherwise; the set as a bit or a byte a row; the sums of the workgroups launched."""
     import paper_2008_03433_amd as tron
-    n = 400_000
     y = np.where(rng.random(n) < 0.5, 1.0, -1.0)
     X = rng.standard_normal((n, d))
     X[:, 0] += 4.0 * y
@@ -478,6 +477,43 @@ def test_byte_counts_follow_the_pass(rng, d, workgroups):
         assert abs(tron.tron_dataset_stat(ds.handle, "hv_bytes") - (8 * read * d + bits + 8 * d * workgroups)) <= 1
         grid = 256 if d <= 32 else 512
         assert tron.tron_dataset_stat(ds.handle, "fun_grad_bytes") == 8 * n * d + n + bits + 8 * d * grid
+    finally:
+        ds.close()
+
+
+@pytest.mark.parametrize("n,d,share,skips", [
+    (70_001, 1, 0.3, False), (70_001, 1, 0.05, True), (70_001, 3, 0.5, False), (70_001, 3, 0.2, True), (70_001, 8, 0.75, False),
+    (70_001, 8, 0.6, True), (70_001, 12, 0.9, False), (70_001, 12, 0.7, True), (70_001, 16, 0.9, True), (70_001, 16, 0.97, False),
+    (70_001, 4, 0.0, True), (2_000_003, 8, 0.3, True), (6_000_011, 5, 0.45, True), (6_000_011, 5, 0.6, False)])
+def test_passes_over_part_of_the_rows(rng, n, d, share, skips):
+    """L2-SVM products with a share of the rows active, on both sides of the line from which the inactive rows are left out
+    (short rows: where a tenth of the 128-byte lines has no active row) and in the long passes with 512 workgroups; the
+    tolerance is that of fp64 sums in another order."""
+    import paper_2008_03433_amd as tron
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0)
+    X = rng.standard_normal((n, d))
+    u = rng.random(n)
+    X[:, 0] = y * (u + 1e-3)          # y z = w_0 (u + 1e-3) >= 1 where the row is inactive
+    w = np.zeros(d)
+    w[0] = 1.0 / (share + 1e-3) if share > 0.0 else 2000.0
+    C = 0.7
+    active = 1.0 - y * (X @ w) > 0.0
+    assert abs(active.mean() - share) < 0.02
+    ds = tron.Dataset.from_problem(DenseProblem("share", n, d, X, y))
+    try:
+        ds.fun_grad(LOSS_L2SVM, C, dev(w), None)
+        read = int(active.sum()) if skips else n
+        grid = tron.tron_dataset_stat(ds.handle, "hv_bytes") - 8 * read * d - n // 8
+        assert -1 <= grid <= 8 * d * 512 + 1
+        v = rng.standard_normal(d)
+        Hv, diag = dev(np.zeros(d)), dev(np.zeros(d))
+        vHv = ds.hv(C, dev(v), Hv)
+        ds.hess_diag(C, diag)
+        XI = X[active]
+        ref = v + 2.0 * C * (XI.T @ (XI @ v))
+        np.testing.assert_allclose(Hv.cpu().numpy(), ref, rtol=1e-10, atol=1e-10 * np.abs(ref).max())
+        assert abs(vHv - v @ ref) <= 1e-10 * abs(v @ ref)
+        np.testing.assert_allclose(diag.cpu().numpy(), 1.0 + 2.0 * C * (XI * XI).sum(axis=0), rtol=1e-10)
     finally:
         ds.close()
 
