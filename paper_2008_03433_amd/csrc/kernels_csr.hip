@@ -723,21 +723,25 @@ __global__ __launch_bounds__(kBlock) void k_csr_spmv(int64_t nnz, const int64_t 
     if (g == 1 && nrows > kBlock) {
         // Many short rows (the tail of a Zipf-distributed transposed copy: a thousand rows of one or two entries in a
         // chunk): one thread per row, and the row offsets of eight passes are fetched together -- a pass that waited
-        // for its own two offsets first cost a memory round trip each, eight or more per chunk.
+        // for its own two offsets first cost a memory round trip each, eight or more per chunk.  Passes that no row needs are
+        // left out: half of the chunks of a matrix with eight entries a row have a few more than 256 rows (1.5M x 60, the forward product:
+        // 34 us, with all eight passes of offsets and addends 41).
         constexpr int kBatch = 8;
         for (int base = 0; base < nrows; base += kBatch * kBlock) {
             int64_t rs[kBatch], re[kBatch];
             double aux[kBatch];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
+                if (base + j * kBlock >= nrows) break;   // uniform
                 const int ri = base + j * kBlock + tid;
                 const int64_t r = (int64_t)lo + (ri < nrows ? ri : nrows - 1);
-                rs[j] = rp[r];
-                re[j] = rp[r + 1];
-                aux[j] = row_aux<EPI>(A, r);
+                rs[j] = (base + j == 0) ? rs0 : rp[r];
+                re[j] = (base + j == 0) ? re0 : rp[r + 1];
+                aux[j] = (base + j == 0) ? aux0 : row_aux<EPI>(A, r);
             }
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
+                if (base + j * kBlock >= nrows) break;
                 const int ri = base + j * kBlock + tid;
                 if (ri < nrows) {
                     const int k0 = (int)(rs[j] - start);
