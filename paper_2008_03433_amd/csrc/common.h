@@ -428,7 +428,7 @@ PlanBytes plan_bytes(const CsrPlan &A);
 bool dense_supported(int64_t d);
 int dense_grid_for(int64_t n, int64_t d);     // workgroups of a pass
 int dense_grid_few(int64_t n, int64_t d);     // of a Hessian-vector pass with few active rows, d <= 32
-int dense_fun_grad_grid(int64_t n, int64_t d, int loss);   // of a function/gradient pass
+int dense_fun_grad_grid(int64_t n, int64_t d);   // of a function/gradient pass
 int dense_round_grid(int64_t n, int64_t d, int loss);      // of a round of a solve driven from the device
 int dense_work_units(int64_t n, int64_t d);   // what tron_hv_static's limit counts: groups of four wave tiles, at most 2048
 int64_t dense_partials_needed(int64_t n, int64_t d);

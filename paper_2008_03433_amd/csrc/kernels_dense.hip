@@ -566,7 +566,7 @@ int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *l
 {
     constexpr int U = pick_U(E, L);
     const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
-    const int grid = dense_fun_grad_grid(ds->n, ds->d, loss);
+    const int grid = dense_fun_grad_grid(ds->n, ds->d);
 #define TRON_FG(V, LS) \
     hipLaunchKernelGGL((k_dense_fun_grad<E, L, U, V, LS>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, ds->X, ds->y8, w, Dout, ds->partials, loss_partials, active_partials, fin)
     if (loss == TRON_LOSS_LR) {
@@ -887,20 +887,24 @@ int dense_grid_few(int64_t n, int64_t d) { return grid_up_to(n, d, kFewGrid); }
 // 169 / 121; d = 4 155 / 133 and 192 / 174; d = 5 L2-SVM 187 / 161, logistic 214 / 212, 6M rows 74 / 64 (the logistic rounds
 // lose by it: 20M x 5 1007 / 1032 us a solve); 4M x 3 37 / 36 and 45 / 41, 4M x 4 38 / 40 and 45 / 42; 2M x 2 25 / 26 and
 // 32 / 31.  512 / 1024, 20M rows, L2-SVM: d = 1 58 / 52, d = 2 86 / 77, d = 3 105 / 114; a solve's rounds, 40M x 2: 450 / 472.
+// The Hessian-vector rounds of the L2-SVM leave out inactive rows whatever their number, whose loads want 512 workgroups up to
+// d = 8: solves with 256 / 512, (nearly) all rows active and few, 20M x 6 1020 / 872 and 1804 / 1450 us, 6M x 6 320 / 302
+// and 543 / 493, 16M x 7 953 / 922 and 1655 / 1600, 15M x 8 932 / 929 and 1597 / 1495; 6M x 9 466 / 478 and 763 / 757, 8M x 13
+// 827 / 1007 and 1335 / 1550.
 constexpr int64_t kNarrowRows = 6'000'000, kNarrowCallRows = 3'000'000, kNarrowestRows = 16'000'000;
 constexpr int kNarrowGrid = 512, kNarrowestGrid = 1024;
 
 int dense_round_grid(int64_t n, int64_t d, int loss)
 {
-    const bool narrow = d <= 4 || (d == 5 && loss == TRON_LOSS_L2SVM);
+    const bool narrow = d <= 4 || (d <= 8 && loss == TRON_LOSS_L2SVM);
     return narrow && n >= kNarrowRows ? grid_up_to(n, d, kNarrowGrid) : dense_grid_for(n, d);
 }
 
-int dense_fun_grad_grid(int64_t n, int64_t d, int loss)
+int dense_fun_grad_grid(int64_t n, int64_t d)
 {
     if (d <= 2 && n >= kNarrowestRows) return grid_up_to(n, d, kNarrowestGrid);
     if ((d <= 3 && n >= kNarrowCallRows) || (d <= 5 && n >= kNarrowRows)) return grid_up_to(n, d, kNarrowGrid);
-    return dense_round_grid(n, d, loss);
+    return dense_grid_for(n, d);
 }
 
 int dense_work_units(int64_t n, int64_t d)
@@ -916,7 +920,8 @@ int dense_work_units(int64_t n, int64_t d)
 int64_t dense_partials_needed(int64_t n, int64_t d)
 {
     int64_t g = d <= kFinishMaxD ? dense_grid_few(n, d) : dense_grid_for(n, d);   // the largest grid of a pass
-    for (int loss : {TRON_LOSS_LR, TRON_LOSS_L2SVM}) g = std::max<int64_t>(g, dense_fun_grad_grid(n, d, loss));
+    g = std::max<int64_t>(g, dense_fun_grad_grid(n, d));
+    for (int loss : {TRON_LOSS_LR, TRON_LOSS_L2SVM}) g = std::max<int64_t>(g, dense_round_grid(n, d, loss));
     return d * g + g + d + g;
 }
 
@@ -934,7 +939,7 @@ int64_t dense_hv_bytes(const tron_dataset *ds)
 int64_t dense_fun_grad_bytes(const tron_dataset *ds)
 {
     const bool mask = ds->have_D && ds->D_is_mask[ds->Dcur];
-    const int grid = dense_fun_grad_grid(ds->n, ds->d, mask ? TRON_LOSS_L2SVM : TRON_LOSS_LR);
+    const int grid = dense_fun_grad_grid(ds->n, ds->d);
     return 8 * ds->n * ds->d + ds->n + d_bytes(ds->n, ds->d, mask) + 8 * ds->d * grid;
 }
 
@@ -978,7 +983,7 @@ int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Ds
     void *Dout = ds->Dbuf[Dslot];
     if (ds->hat_slot == Dslot) ds->hat_slot = -1;   // the compacted copy belonged to the D that is overwritten now
     ds->D_is_mask[Dslot] = (loss == TRON_LOSS_L2SVM);
-    const int grid = dense_fun_grad_grid(ds->n, ds->d, loss);
+    const int grid = dense_fun_grad_grid(ds->n, ds->d);
     double *loss_partials = ds->partials + ds->d * grid;
     double *col_partials = loss_partials + grid;
     double *active_partials = col_partials + ds->d;
@@ -1052,7 +1057,7 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
     // Nothing has to start at zero: every workgroup of the pass writes all d of its column sums, the second stage the rest.  Calls
     // that overlapped (they race for the sums) spoil their own results and no later ones: for d <= 32 the sums are added by a
     // launch of its own, without a counter, for wider rows the pass clears the counter of k_dense_columns first.  (A counter in
-    // the pass needs a launch that clears it: 20,003 x 8 then takes 21.1 us a call, this way 18.8.)
+    // the pass needs a launch that clears it: 20,003 x 8 then takes 21.1 us a call, this way 19.1.)
     const bool narrow = ds->d <= kFinishMaxD;
     const DenseFinish fin{narrow ? nullptr : &g_static_work[dev]->ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false};
     TRON_TRY(dispatch_hv(ds, in, v_dev, partials, fin));

@@ -43,10 +43,10 @@ def test_dense_calls_narrow_rows(rng, loss, n, d):
 
 
 @pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
-@pytest.mark.parametrize("n,d", [(3_000_001, 3), (6_000_001, 4), (6_000_065, 5), (16_000_001, 1)])
+@pytest.mark.parametrize("n,d", [(3_000_001, 3), (6_000_001, 4), (6_000_065, 5), (6_000_001, 7), (16_000_001, 1)])
 def test_dense_narrow_rows_with_the_larger_grids(rng, loss, n, d):
-    """Function/gradient passes over narrow rows run 512 workgroups from 3M (d <= 3) or 6M rows (d <= 4, L2-SVM 5) on, the rounds of
-    a solve from 6M; over one or two columns and 16M rows 1024.  The work space holds their sums."""
+    """Function/gradient passes over narrow rows run 512 workgroups from 3M (d <= 3) or 6M rows (d <= 5) on, the rounds of a solve
+    from 6M (d <= 4, L2-SVM 8); over one or two columns and 16M rows 1024.  The work space holds their sums."""
     p = _dense(rng, n, d)
     check_calls(p, loss, 0.5, rng, w_scale=0.5, n_hv=1)
     if n < 10_000_000:
