@@ -43,7 +43,7 @@ ROCPROF_NAMES = {
     ("c3_values", "spmv_head"): ("k_csr_spmv_part<true, true, false, false>", "csr_spmv_c3_values.md"),
     ("c3_values", "spmv_fwd"): ("k_csr_spmv_part<true, false, false, false>", "csr_spmv_c3_values.md"),
     ("c3_values", "spmv_bwd"): ("k_csr_spmv_part<false, false, false, false>", "csr_spmv_c3_values.md"),
-    ("c3_values", "spmv_tiles"): ("k_hot_tiles<false>", "csr_spmv_c3_values.md"),
+    ("c3_values", "spmv_tiles"): ("k_hot_tiles<false, false>", "csr_spmv_c3_values.md"),
 }
 
 

@@ -805,8 +805,9 @@ bool dense_compact_wanted(const tron_dataset *ds, int Dslot, int recent_cg_iters
     if (!ds->dense || ds->d > 32 || !ds->D_is_mask[Dslot] || g_tuning.dense_compact == 0) return false;
     if (ds->active_count[Dslot] <= 0 || ds->active_frac[Dslot] >= kSkipBelow) return false;
     if (g_tuning.dense_compact > 0) return true;
-    // Building the copy costs about as much as 2.5 products over it and a product over it saves about a quarter of the
-    // row-skipping one: worth it from about ten products per iterate on, with no more than 60% of the rows active.
+    // Building the copy costs as much as 2.8 products over it, and a product over it saves about a fifth of the row-skipping
+    // one: paid for after 11 to 13 products per iterate at 0.36 to 0.47 of the rows active, 26 at 0.72 (20M x 24).  The
+    // inner solve before had ten or more: the next one, nearer the solution, tends to be longer.
     return ds->active_frac[Dslot] <= 0.6 && recent_cg_iters >= 10;
 }
 
