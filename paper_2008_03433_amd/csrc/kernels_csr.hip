@@ -644,6 +644,37 @@ __device__ __forceinline__ double gather(const double *__restrict__ x, const dou
     return (c < 0) ? hot : cold;
 }
 
+// Rows lo + base, lo + base + 1, ... below lo + nrows, kPasses passes of one row a thread; returns acc with their epilogue's sums
+// added.  Everything the passes need is asked for at once, without a branch between the loads (with one, each pass waits for
+// its own, and the 1.05M nonzeros of the rcv1-shaped matrix, whose chunks do not come here, take 10.3 us instead of 8.9).
+template <int EPI, int kPasses>
+__device__ __forceinline__ double short_rows(const EpiArgs &A, const int64_t *__restrict__ rp, const double *prod, int lo, int nrows, int base,
+                                             int64_t start, int64_t end, double acc)
+{
+    int64_t rs[kPasses], re[kPasses];
+    double aux[kPasses];
+#pragma unroll
+    for (int j = 0; j < kPasses; ++j) {
+        const int ri = base + j * kBlock + threadIdx.x;
+        const int64_t r = (int64_t)lo + (ri < nrows ? ri : nrows - 1);
+        rs[j] = rp[r];
+        re[j] = rp[r + 1];
+        aux[j] = row_aux<EPI>(A, r);
+    }
+#pragma unroll
+    for (int j = 0; j < kPasses; ++j) {
+        const int ri = base + j * kBlock + threadIdx.x;
+        if (ri < nrows) {
+            const int k0 = (int)(rs[j] - start);
+            const int k1 = (int)(((re[j] < end) ? re[j] : end) - start);
+            double s = 0.0;
+            for (int k = k0; k < k1; ++k) s += prod[k];
+            acc += finish_row<EPI>(A, (int64_t)lo + ri, s, aux[j]);
+        }
+    }
+    return acc;
+}
+
 // Plain CSR: one workgroup per chunk of nonzeros, the epilogue applied directly.  The chunk's row range, and the offsets and
 // the addends of the rows a thread starts with, are asked for before the gathers: asked for where they are used, after the
 // products are in LDS, they added three memory latencies to a kernel that is little else (9.6 us for the 1.05M nonzeros of
@@ -723,35 +754,14 @@ __global__ __launch_bounds__(kBlock) void k_csr_spmv(int64_t nnz, const int64_t 
     if (g == 1 && nrows > kBlock) {
         // Many short rows (the tail of a Zipf-distributed transposed copy: a thousand rows of one or two entries in a
         // chunk): one thread per row, and the row offsets of eight passes are fetched together -- a pass that waited
-        // for its own two offsets first cost a memory round trip each, eight or more per chunk.  Passes that no row needs are
-        // left out: half of the chunks of a matrix with eight entries a row have a few more than 256 rows (1.5M x 60, the forward product:
-        // 34 us, with all eight passes of offsets and addends 41).
-        constexpr int kBatch = 8;
-        for (int base = 0; base < nrows; base += kBatch * kBlock) {
-            int64_t rs[kBatch], re[kBatch];
-            double aux[kBatch];
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                if (base + j * kBlock >= nrows) break;   // uniform
-                const int ri = base + j * kBlock + tid;
-                const int64_t r = (int64_t)lo + (ri < nrows ? ri : nrows - 1);
-                rs[j] = (base + j == 0) ? rs0 : rp[r];
-                re[j] = (base + j == 0) ? re0 : rp[r + 1];
-                aux[j] = (base + j == 0) ? aux0 : row_aux<EPI>(A, r);
-            }
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                if (base + j * kBlock >= nrows) break;
-                const int ri = base + j * kBlock + tid;
-                if (ri < nrows) {
-                    const int k0 = (int)(rs[j] - start);
-                    const int k1 = (int)(((re[j] < end) ? re[j] : end) - start);
-                    double s = 0.0;
-                    for (int k = k0; k < k1; ++k) s += prod[k];
-                    acc += finish_row<EPI>(A, (int64_t)lo + ri, s, aux[j]);
-                }
-            }
-        }
+        // for its own two offsets first cost a memory round trip each, eight or more per chunk.  Four or two where no more
+        // are left: chunks of rows with five to eight entries have not many more than 256.  Forward products, always eight passes /
+        // this: 1.5M rows of 5 entries 29.5 / 24.7 us, 1M of about 6 26.2 / 22.5, 1.5M of about 8 37.4 / 34.3, of 2 18.2 / 17.2,
+        // 800,000 of 3 17.7 / 16.6, 1M of one 15.1 / 15.2.
+        int base = 0;
+        for (; nrows - base > 4 * kBlock; base += 8 * kBlock) acc = short_rows<EPI, 8>(A, rp, prod, lo, nrows, base, start, end, acc);
+        if (nrows - base > 2 * kBlock) acc = short_rows<EPI, 4>(A, rp, prod, lo, nrows, base, start, end, acc);
+        else if (base < nrows) acc = short_rows<EPI, 2>(A, rp, prod, lo, nrows, base, start, end, acc);
     } else {
         for (int base = 0; base < nrows; base += rows_per_pass) {
             const int ri = base + ri0;

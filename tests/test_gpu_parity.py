@@ -559,6 +559,24 @@ def test_csr_rows_longer_than_a_chunk(rng, loss, segmented, lengths):
         tron.tron_tuning_set("csr_segmented", -1)
 
 
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("lengths", [
+    [8] * 256 + [7] * 400,                          # 256 rows in a chunk; 292, two passes of 256
+    [4] * 600 + [3, 5] * 256,                       # 512 rows, two full passes
+    [4, 4, 3] * 300 + [3] * 700,                    # from 512 to 683 rows, four passes
+    [2] * 1024 + [2] * 1023 + [1, 1] + [2] * 300,   # 1024 rows, four full passes; 1025, eight
+    [1] * 2048 + [1, 0] * 2100 + [3],               # 2048 rows, eight full passes; about 4095, twice
+    ([1, 0, 0, 0] * 530 + [0] * 60 + [2] * 200)])
+def test_csr_plain_chunks_of_many_short_rows(rng, loss, lengths):
+    """Plain CSR: the rows of a chunk are added up in groups of two, four or eight passes of 256 rows."""
+    import paper_2008_03433_amd as tron
+    tron.tron_tuning_set("csr_segmented", 0)
+    try:
+        check_calls(_csr_rows(rng, lengths, 40), loss, 0.5, rng, w_scale=0.5)
+    finally:
+        tron.tron_tuning_set("csr_segmented", -1)
+
+
 def _check_single_range(p, loss, rng, segmented, single):
     """Calls, the Hessian diagonal and a preconditioned solve on an unpartitioned matrix; single: whether each of the two layouts
     is one whose products take one launch."""
