@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
+import threading
 from dataclasses import dataclass
 from typing import List, Optional, Tuple
 
@@ -37,7 +39,41 @@ class TraceRec(ctypes.Structure):
 class _Result(ctypes.Structure):
     _fields_ = [("f", _dbl), ("gnorm", _dbl), ("gnorm0", _dbl), ("outer_iters", _int), ("cg_iters_total", _int),
                 ("n_fun", _int), ("n_grad", _int), ("n_hv", _int), ("converged", _int), ("trace_cap", _int),
-                ("trace_len", _int), ("trace", ctypes.POINTER(TraceRec))]
+                ("trace_len", _int), ("trace", _vp)]
+
+
+# Records of a solve's outer iterations, as the library writes them, become dicts through one unpacking per record.  The array
+# they are written to is a thread's own and stays with it: a ctypes array made for each call (64 KB at the default
+# trace_cap), its cast to a pointer -- a reference cycle, so the arrays of a loop of solves lie about until the garbage collector runs --
+# and a getattr per field took 20 us of a call that spends 38 us on the GPU.
+_RECORD = struct.Struct("4i6d")
+_RESULT = struct.Struct("3d8iP")
+_RECORD_NAMES = tuple(name for name, _ in TraceRec._fields_)
+assert _RECORD.size == ctypes.sizeof(TraceRec) and _RESULT.size == ctypes.sizeof(_Result)
+_TRACE_KEPT = 16 * 1024   # records, 1 MB; a larger array is made for its call
+
+
+class _TraceSpace(threading.local):
+    array = None
+
+    def records(self, count: int):
+        """An array of at least `count` records that this thread may use until its next call."""
+        if count > _TRACE_KEPT:
+            return (TraceRec * count)()
+        if self.array is None or len(self.array) < count:
+            self.array = (TraceRec * count)()
+        return self.array
+
+
+_trace_space = _TraceSpace()
+
+
+def _solve_result(res, k: int, status: int, traces, first: int) -> "SolveResult":
+    """Problem k's result out of an array of _Result, its records from `first` on."""
+    *head, converged, _, count, _ = _RESULT.unpack_from(res, k * _RESULT.size)
+    size = _RECORD.size
+    return SolveResult(*head, bool(converged), status,
+                       [dict(zip(_RECORD_NAMES, _RECORD.unpack_from(traces, i * size))) for i in range(first, first + count)])
 
 
 # every symbol include/tron.h declares, with its signature
@@ -219,14 +255,12 @@ class SolveResult:
 def tron_solve(ds, loss, C, eps, w, max_outer=1000, max_cg=1000, cg_xi=0.1, trace_cap=1024, precond_blend=0.0) -> SolveResult:
     """Runs the solve in place on the CUDA tensor w (in: w0, out: final iterate)."""
     params = _Params(loss, C, eps, max_outer, max_cg, cg_xi, precond_blend)
-    trace = (TraceRec * max(trace_cap, 1))()
+    trace = _trace_space.records(max(trace_cap, 1))
     res = _Result()
     res.trace_cap = trace_cap
-    res.trace = ctypes.cast(trace, ctypes.POINTER(TraceRec)) if trace_cap > 0 else None
+    res.trace = ctypes.addressof(trace) if trace_cap > 0 else None
     rc = _check(load_library().tron_solve(ds, ctypes.byref(params), _ptr(w), ctypes.byref(res)))
-    recs = [{k: getattr(trace[i], k) for k, _ in TraceRec._fields_} for i in range(res.trace_len)]
-    return SolveResult(res.f, res.gnorm, res.gnorm0, res.outer_iters, res.cg_iters_total, res.n_fun, res.n_grad,
-                       res.n_hv, bool(res.converged), rc, recs)
+    return _solve_result(res, 0, rc, trace, 0)
 
 
 BATCH_MAX = 16
@@ -268,20 +302,15 @@ def tron_batch_solve(b, loss, C, eps, W, max_outer=1000, max_cg=1000, cg_xi=0.1,
     """Solves the K problems in place on the CUDA tensor W (K*d doubles); one SolveResult per problem."""
     K = len(C)
     params = _Params(loss, 0.0, eps, max_outer, max_cg, cg_xi, precond_blend)
-    traces = [(TraceRec * max(trace_cap, 1))() for _ in range(K)]
+    per = max(trace_cap, 1)
+    traces = _trace_space.records(per * max(K, 1))
+    address = ctypes.addressof(traces)
     res = (_Result * K)()
     for k in range(K):
-        res[k].trace_cap = trace_cap
-        res[k].trace = ctypes.cast(traces[k], ctypes.POINTER(TraceRec)) if trace_cap > 0 else None
+        _RESULT.pack_into(res, k * _RESULT.size, *([0] * 9), trace_cap, 0, address + k * per * _RECORD.size if trace_cap > 0 else 0)
     status = (_int * K)()
     _check(load_library().tron_batch_solve(b, ctypes.byref(params), _dbl_array(C), _ptr(W), res, status))
-    out = []
-    for k in range(K):
-        r = res[k]
-        recs = [{f: getattr(traces[k][i], f) for f, _ in TraceRec._fields_} for i in range(r.trace_len)]
-        out.append(SolveResult(r.f, r.gnorm, r.gnorm0, r.outer_iters, r.cg_iters_total, r.n_fun, r.n_grad, r.n_hv,
-                               bool(r.converged), status[k], recs))
-    return out
+    return [_solve_result(res, k, status[k], traces, k * per) for k in range(K)]
 
 
 def tron_profile_enable(ds, on: bool) -> None:
