@@ -351,6 +351,10 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  * "dense_device_driver" (-1/0/1): tron_solve on a dense matrix with d <= 32 and no preconditioner runs its trust-region and
  *   CG steps on the device (as tron_batch_solve does): 0 never, 1 always, -1 (default) for the logistic loss, and for the
  *   L2-SVM on matrices up to 1 GB (larger ones may put their products on a compacted copy, see above).
+ * "solve_resident" (-1/0): a tron_solve driven from the device runs as one launch whose workgroups wait for each other between
+ *   the steps, where all of them can be resident at once (-1, default), or as a launch per product (0).
+ * "solve_wait_us" (-1..10000000): how long a workgroup of such a launch waits for the others before it gives up and the
+ *   solve starts again with a launch per product: microseconds, 0 not at all, -1 (default) a tenth of a second.
  * "batch_grid" (0..4096): workgroups of the multi-problem pass (0 = as many as are resident at once).
  * "batch_mfma_rows" (0/32/64): rows of X a wavefront of the matrix-unit pass keeps in LDS at a time (0: 32, except 64
  *                in the L2-SVM's rounds without function / gradient requests).

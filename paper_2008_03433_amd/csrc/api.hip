@@ -1,14 +1,17 @@
 // C ABI entry points: dataset handles, argument checking, profiling, error text.
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <mutex>
 #include <new>
 #include <thread>
 
 #include "common.h"
+#include "grid_sync.h"
 #include "host_util.h"
 
 namespace tron {
@@ -116,7 +119,53 @@ static int alloc_common(tron_dataset *ds)
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->scal_copy), sizeof(double) * kScalars));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->ticket), 64));
     TRON_HIP(hipMemset(ds->ticket, 0, 64));
+    TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->sync_words), sizeof(unsigned) * kSyncWords));
+    TRON_HIP(hipMemset(ds->sync_words, 0, sizeof(unsigned) * kSyncWords));
+    TRON_HIP(hipDeviceGetAttribute(&ds->cus, hipDeviceAttributeMultiprocessorCount, ds->device));
     return TRON_OK;
+}
+
+// ------------------------------------------------------------------ launches whose workgroups wait for each other
+// 100 ms: far longer than the workgroups of a pass over the largest matrix are apart, and what a solve loses when another process
+// holds a part of the GPU
+constexpr long long kResidentWaitUs = 100'000, kTicksPerUs = 100;
+
+GridSync grid_sync(const tron_dataset *ds)
+{
+    const long long us = g_tuning.solve_wait_us;
+    return GridSync{ds->sync_words, us < 0 ? kResidentWaitUs * kTicksPerUs : us == 0 ? -1 : us * kTicksPerUs};
+}
+
+bool resident_possible(const tron_dataset *ds, int grid) { return g_tuning.solve_resident != 0 && grid <= ds->cus; }
+
+namespace {
+struct ResidentPool {
+    std::mutex m;
+    std::condition_variable freed;
+    int used = 0;   // workgroups of the launches under way
+};
+constexpr int kPools = 64;
+ResidentPool g_resident[kPools];
+}  // namespace
+
+ResidentShare::ResidentShare(int device, int grid) : device_(device), grid_(grid)
+{
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 0;
+    ResidentPool &p = g_resident[device_ % kPools];
+    std::unique_lock<std::mutex> lock(p.m);
+    p.freed.wait(lock, [&] { return p.used == 0 || p.used + grid_ <= cus; });
+    p.used += grid_;
+}
+
+ResidentShare::~ResidentShare()
+{
+    ResidentPool &p = g_resident[device_ % kPools];
+    {
+        std::lock_guard<std::mutex> lock(p.m);
+        p.used -= grid_;
+    }
+    p.freed.notify_all();
 }
 
 static int check_labels(const double *y, int64_t n)
@@ -174,7 +223,7 @@ void tron_dataset_destroy(tron_dataset *ds)
     ds->fwd.release();
     ds->bwd.release();
     hipFree(ds->y); hipFree(ds->y8); hipFree(ds->z); hipFree(ds->zhat); hipFree(ds->Dbuf[0]); hipFree(ds->Dbuf[1]);
-    hipFree(ds->partials); hipFree(ds->row_partials); hipFree(ds->unit_scale); hipFree(ds->scal_copy); hipFree(ds->ticket);
+    hipFree(ds->partials); hipFree(ds->row_partials); hipFree(ds->unit_scale); hipFree(ds->scal_copy); hipFree(ds->ticket); hipFree(ds->sync_words);
     if (ds->scal_host) hipHostFree(ds->scal_host);
     for (double *p : ds->sv) hipFree(p);
     hipFree(ds->cg_partials);
@@ -715,6 +764,14 @@ int tron_tuning_set(const char *name, int64_t value)
     }
     if (name && strcmp(name, "dense_device_driver") == 0 && value >= -1 && value <= 1) {
         g_tuning.dense_device_driver = value;
+        return TRON_OK;
+    }
+    if (name && strcmp(name, "solve_resident") == 0 && value >= -1 && value <= 0) {
+        g_tuning.solve_resident = value;
+        return TRON_OK;
+    }
+    if (name && strcmp(name, "solve_wait_us") == 0 && value >= -1 && value <= 10'000'000) {
+        g_tuning.solve_wait_us = value;
         return TRON_OK;
     }
     if (name && strcmp(name, "batch_grid") == 0 && value >= 0 && value <= 4096) {

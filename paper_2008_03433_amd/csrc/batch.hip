@@ -1065,9 +1065,8 @@ extern "C" int tron_batch_solve(tron_batch *b, const tron_params *params, const 
 }
 
 // ------------------------------------------------------------------ one problem, driven from the device
-// tron_solve for a dense matrix with d <= 32 in rounds of one launch each (k_dense_round: the pass over X, and the step of
-// the solve in the workgroup that finishes last), so that no scalar is waited for by the host inside an iteration and no
-// vector kernels run between the passes.
+// tron_solve for a dense matrix with d <= 32 in one launch (k_dense_solve), or where its workgroups cannot all be resident in a
+// launch per round, so that no scalar is waited for by the host inside an iteration and no vector kernels run between the passes.
 namespace tron {
 
 int DriverState::create(int K, hipStream_t stream)
@@ -1119,9 +1118,29 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     ds->have_D = false;
     ds->hat_slot = -1;   // both D buffers are overwritten
     const double C = Q.C;
-    TRON_TRY(launch_begin(ds, drv, 1, BEGIN_SOLVE, w_dev, &C));
-    TRON_TRY(drive_rounds(ds, drv, 1, round_limit(Q), false, [&](int64_t stamp, bool) -> int { return dense_round(ds, P, drv, stamp); }));
-    TRON_HIP(hipStreamSynchronize(ds->stream));
+    bool done = false;
+    const int grid = dense_round_grid(ds->n, ds->d, Q.loss);
+    if (resident_possible(ds, grid)) {
+        const ResidentShare share(ds->device, grid);
+        drv.host->stamp[0] = 0;
+        TRON_TRY(dense_solve_launch(ds, P, drv, 0, w_dev, C));
+        // the stream's own wait takes some microseconds more to notice the end than the first workgroup's last word
+        for (unsigned spins = 1;; ++spins) {
+            const int64_t v = __atomic_load_n(&drv.host->stamp[0], __ATOMIC_ACQUIRE);
+            if ((v != 0 && (v & 3) == MODE_IDLE) || ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady)) break;
+            __builtin_ia32_pause();
+        }
+        (void)hipGetLastError();
+        TRON_HIP(hipStreamSynchronize(ds->stream));
+        // otherwise workgroups gave up waiting for others before the first of them had the result; w0 is as it was
+        const int64_t v = __atomic_load_n(&drv.host->stamp[0], __ATOMIC_ACQUIRE);
+        done = v != 0 && (v & 3) == MODE_IDLE;
+    }
+    if (!done) {
+        TRON_TRY(launch_begin(ds, drv, 1, BEGIN_SOLVE, w_dev, &C));
+        TRON_TRY(drive_rounds(ds, drv, 1, round_limit(Q), false, [&](int64_t stamp, bool) -> int { return dense_solve_launch(ds, P, drv, stamp, nullptr, C); }));
+        TRON_HIP(hipStreamSynchronize(ds->stream));
+    }
     fill_result(drv, 0, cap, *res);
     // D at the final iterate, in the layout of the single-problem calls (one bit per row in 64-bit words for the L2-SVM, fp64 per
     // row for the logistic loss)

@@ -51,6 +51,8 @@ struct Tuning {
                                    //   -1 automatic (launches of few workgroups, where the extra launch costs more than it does)
     int64_t dense_device_driver = -1;   // tron_solve on dense d <= 32 without preconditioner driven from the device:
                                         //   0 never, 1 always, -1 automatic (all but L2-SVM matrices above 1 GB)
+    int64_t solve_resident = -1;   // solves in one launch whose workgroups wait for each other: 0 never, -1 where they can all be resident
+    int64_t solve_wait_us = -1;    // how long such a workgroup waits for the others: -1 automatic, 0 not at all (the launches then end at once)
     int64_t batch_grid = 0;  // workgroups of the multi-problem pass: 0 = as many as are resident at once
     int64_t batch_mfma = -1; // multi-problem pass on the matrix units: 1 = yes, 0 = no, -1 = the library decides
     int64_t batch_lean = 1;         // matrix-unit pass: rounds without function / gradient requests run a kernel compiled without those steps
@@ -289,6 +291,8 @@ struct tron_dataset {
     double *scal_dev = nullptr;  // the device address of scal_host (kernels write the scalars there)
     double *scal_copy = nullptr; // the same scalars in device memory, for kernels that continue from them without the host
     unsigned *ticket = nullptr;  // counter of finished workgroups for reductions completed inside the producing kernel (zero between kernels)
+    unsigned *sync_words = nullptr;  // counters of the launches whose workgroups wait for each other (zero between kernels)
+    int cus = 0;                 // compute units of the device
     bool finish_done = false;    // the last producing kernel did: the next reduce_final call is a no-op
     int dense_grid = 0;          // workgroups of the dense kernels
 
@@ -326,6 +330,23 @@ struct Finish {
 // the launch is small enough for that to pay (then the reduce_final call that follows does nothing), without otherwise or
 // when first_scalar < 0.
 Finish finish_for(tron_dataset *ds, int first_scalar, int grid);
+
+// Launches whose workgroups wait for each other (grid_sync.h).  resident_possible: whether `grid` workgroups can be resident
+// together, one per compute unit.  ResidentShare: the call's place among those of this process that run on one device at a time; it
+// waits until its workgroups and theirs are no more than the compute units, so that two solves on two streams cannot each hold a
+// part of the GPU and wait for the rest.
+struct GridSync;
+GridSync grid_sync(const tron_dataset *ds);
+bool resident_possible(const tron_dataset *ds, int grid);
+class ResidentShare {
+public:
+    ResidentShare(int device, int grid);
+    ~ResidentShare();
+    ResidentShare(const ResidentShare &) = delete;
+    ResidentShare &operator=(const ResidentShare &) = delete;
+private:
+    int device_, grid_;
+};
 
 // RAII bracket used by the launch helpers
 struct ProfScope {
@@ -455,8 +476,9 @@ int dense_compact_build(tron_dataset *ds, int Dslot);
 bool dense_compact_wanted(const tron_dataset *ds, int Dslot, int recent_cg_iters);
 void dense_compact_release(tron_dataset *ds);
 
-// one round of a solve driven from the device (d <= 32): the pass that serves the problem's pending request, and its next step
-int dense_round(tron_dataset *ds, const SolveParams &P, DriverState &drv, int64_t stamp);
+// a solve driven from the device (d <= 32) from w0, or with stamp > 0 one round of it: the pass that serves the problem's pending
+// request, and its next step
+int dense_solve_launch(tron_dataset *ds, const SolveParams &P, DriverState &drv, int64_t stamp, const double *w0, double C);
 
 // ---- batch.hip
 int dense_device_solve(tron_dataset *ds, const tron_params &P, double *w_dev, tron_result *res);

@@ -1,6 +1,6 @@
 // Algorithm 1 of the paper on the device: the state of problems that advance without the host, and the step a problem
 // takes when the product it was waiting for is there.  Used by the multi-problem pass (batch.hip) and by solves of one dense
-// problem (k_dense_round).  The vectors have d <= 32 entries, one lane each.
+// problem (k_dense_solve).  The vectors have d <= 32 entries, one lane each.
 #pragma once
 
 #include "device_util.h"
@@ -112,7 +112,7 @@ __device__ __forceinline__ void finish(ProbScalars &sc, int status)
 }
 
 // Problem k's step, by one wavefront.  mode = the request the pass just served, cj its column sum of this lane's column,
-// loss_sum the loss sum; stamp = the number of the round.  The rules are those of the single-problem driver (Algorithm 1
+// loss_sum the loss sum; stamp = the number of the round.  host, trace, P.out null: nothing is reported there.  The rules are those of the single-problem driver (Algorithm 1
 // with Steihaug's truncated CG), lane j holding entry j of every vector.
 __device__ __forceinline__ void advance_problem(const int k, const int mode, const int64_t d, const double cj, const double loss_sum, BatchCtl *ctl, ProbState *st,
                                                 const SolveParams &P, tron_trace_rec *trace, BatchHost *host, const int64_t stamp)
@@ -260,10 +260,10 @@ __device__ __forceinline__ void advance_problem(const int k, const int mode, con
         ctl->mode[k] = next.mode;
         ctl->dslot[k] = next.slot;
         S.sc = sc;
-        if (sc.phase == PH_DONE) host->sc[k] = sc;
+        if (host && sc.phase == PH_DONE) host->sc[k] = sc;
         // running or not, for the host that enqueues rounds meanwhile (see drive_rounds); the results above are read after
         // the stream has drained
-        __hip_atomic_store(&host->stamp[k], (stamp << 2) | next.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (host) __hip_atomic_store(&host->stamp[k], (stamp << 2) | next.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     if (sc.phase == PH_DONE && in && P.out) P.out[(int64_t)k * d + j] = one_shot ? o : S.w[j];
 }

@@ -1,0 +1,94 @@
+// Waiting for the other workgroups inside a kernel whose workgroups are all resident at once.
+#pragma once
+
+#include "device_util.h"
+
+namespace tron {
+
+// A barrier over the grid costs a round trip to where every XCD sees the same memory for each step of its chain, and the
+// additions to one counter, and the polls of it, go one after the other.  Up to kSyncFlat workgroups one counter does: 1.1 us with 40
+// workgroups, 1.4 with 64, but 2.1 with 128 and 3.7 with 256.  Beyond, eight groups with a counter and a word to poll each,
+// and a counter over the groups: 1.6 us with 128, 1.8 with 256 (sixteen groups: the same; a flag per workgroup, all of them
+// polled by everyone: 4.1).  A launch that depends on the one before it costs 4 to 6 us.
+constexpr int kSyncGroups = 8;
+constexpr unsigned kSyncFlat = 64;
+constexpr int kSyncLine = 32;   // 128 bytes apart
+constexpr int kSyncWords = (3 + 2 * kSyncGroups) * kSyncLine;
+
+// words: kSyncWords of device memory, zero between kernels (the workgroup that leaves last clears them)
+struct GridSync {
+    unsigned *words;
+    long long ticks;   // how long a workgroup waits for the others (100 MHz); below zero: not at all
+};
+
+// Every thread of every workgroup makes the same calls.  What one workgroup reads of another's has to be written by store_shared before
+// arrive() and read by load_shared after wait().  A workgroup that has waited for too long -- part of the grid is not
+// resident -- gives up: wait() then returns false there and, soon, in every other workgroup; the caller leaves and the host takes
+// another way.  So no wait is without an end, whatever else runs on the GPU.
+class GridBarrier {
+public:
+    __device__ explicit GridBarrier(const GridSync &s) : w_(s.words), ticks_(s.ticks), round_(0) {}
+
+    __device__ __forceinline__ void arrive()
+    {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // every wavefront's own stores have arrived
+        __syncthreads();
+        ++round_;
+        if (threadIdx.x != 0) return;
+        const unsigned G = gridDim.x;
+        if (G <= kSyncFlat) {
+            add(root());
+        } else {
+            const unsigned g = blockIdx.x % kSyncGroups, members = (G - g + kSyncGroups - 1) / kSyncGroups;
+            if (add(counter(g)) == round_ * members - 1 && add(root()) == round_ * kSyncGroups - 1)
+                for (int k = 0; k < kSyncGroups; ++k) put(release(k), round_);
+        }
+    }
+
+    __device__ __forceinline__ bool wait()
+    {
+        __shared__ int ok;
+        if (threadIdx.x < kWave) {
+            const bool flat = gridDim.x <= kSyncFlat;
+            const unsigned *word = flat ? root() : release(blockIdx.x % kSyncGroups);
+            const unsigned want = flat ? round_ * gridDim.x : round_;
+            bool good = false;
+            if (ticks_ >= 0) {
+                const long long from = wall_clock64();
+                for (unsigned polls = 1;; ++polls) {
+                    if ((int)(get(word) - want) >= 0) { good = true; break; }
+                    if ((polls & 15u) == 0 && (get(given_up()) != 0 || wall_clock64() - from > ticks_)) break;
+                }
+            }
+            if (threadIdx.x == 0) {
+                ok = good;
+                if (!good) put(given_up(), 1u);
+            }
+        }
+        __syncthreads();
+        return ok;
+    }
+
+    // the last thing a workgroup does, whether it gave up or not
+    __device__ __forceinline__ void leave()
+    {
+        if (threadIdx.x == 0 && add(left()) == gridDim.x - 1)
+            for (int k = 0; k < kSyncWords / kSyncLine; ++k) put(w_ + k * kSyncLine, 0u);
+    }
+
+private:
+    __device__ unsigned *root() const { return w_; }
+    __device__ unsigned *left() const { return w_ + kSyncLine; }
+    __device__ unsigned *given_up() const { return w_ + 2 * kSyncLine; }
+    __device__ unsigned *counter(int g) const { return w_ + (3 + g) * kSyncLine; }
+    __device__ unsigned *release(int g) const { return w_ + (3 + kSyncGroups + g) * kSyncLine; }
+    __device__ static unsigned add(unsigned *p) { return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ static unsigned get(const unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ static void put(unsigned *p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+    unsigned *w_;
+    long long ticks_;
+    unsigned round_;
+};
+
+}  // namespace tron

@@ -23,6 +23,7 @@
 
 #include "dense_tile.h"
 #include "device_driver.h"
+#include "grid_sync.h"
 
 namespace tron {
 
@@ -110,7 +111,13 @@ __device__ __forceinline__ bool dense_add_rows(double *col_sum, int grid, int d,
     const int m = kWave >> (d > 1 ? 32 - __clz(d - 1) : 0), c = lane / m;
     col = loss = active = 0.0;
     if (c < d)
-        for (int k = lane % m; k < groups; k += m) col += col_sum[k * d + c];
+        for (int k0 = lane % m; k0 < groups; k0 += kAtOnce * m) {
+            double v[kAtOnce];
+#pragma unroll
+            for (int k = 0; k < kAtOnce; ++k) v[k] = (k0 + k * m < groups) ? col_sum[(k0 + k * m) * d + c] : 0.0;
+#pragma unroll
+            for (int k = 0; k < kAtOnce; ++k) col += v[k];
+        }
     col = __shfl(group_sum(col, m), lane * m, kWave);
     if (lane >= d) col = 0.0;
 #pragma unroll
@@ -173,14 +180,30 @@ __global__ __launch_bounds__(kFinishBlock) void k_dense_finish(int d, int grid, 
 // 4 117 / 104; logistic: 94 / 55, 103 / 81, 116 / 105, 126 / 132.
 constexpr int tiles_at_once(int E, int L, bool mask) { return L > 1 ? 1 : E == 1 ? 8 : E == 2 ? 4 : E == 3 || (E == 4 && mask) ? 2 : 1; }
 
+// The tiles of a wavefront: first, first + step, ... below last.  A contiguous range, or every tile whose number leaves the
+// wavefront's as remainder.
+struct TileWalk {
+    int64_t first, last, step;
+    __device__ __forceinline__ TileWalk(int64_t ntiles, int waves, bool contiguous)
+    {
+        const int64_t nwaves = (int64_t)gridDim.x * waves, id = (int64_t)blockIdx.x * waves + threadIdx.x / kWave;
+        const int64_t per = (ntiles + nwaves - 1) / nwaves;
+        first = contiguous ? id * per : id;
+        last = contiguous && first + per < ntiles ? first + per : ntiles;
+        step = contiguous ? 1 : nwaves;
+    }
+};
+
 // ------------------------------------------------------------------ Hessian-vector pass
 // MASK: D is the active set of the L2-SVM (D_ii = 2 on it, else 0) instead of an fp64 value per row: one bit per row,
 // a 64-bit word per wave tile, when a tile has 64 rows (d <= 32); one byte per row otherwise.
 // DIAG: column sums of D_i x_ij^2 instead (the diagonal of X^T D X; v is not read).
 // SKIP (with the bit words only): rows outside the active set are not read.  Chosen by the host when a noticeable
 // part of the rows is inactive; with (almost) every row active the plain loop is about 1% faster.
+// SOLVE: the pass is one of several in a launch.  All of them then deal the tiles out alike, so that a wavefront reads the D that
+// it wrote itself.
 // lds: E * L doubles per wavefront
-template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP>
+template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP, bool SOLVE = false>
 __device__ __forceinline__ void hv_pass(double *lds, int64_t n, int64_t d, const double *__restrict__ X, const void *__restrict__ Dv,
                                         const double *__restrict__ v, double *__restrict__ partials)
 {
@@ -197,18 +220,18 @@ __device__ __forceinline__ void hv_pass(double *lds, int64_t n, int64_t d, const
         acc[e] = 0.0;
     }
     const int64_t ntiles = (n + T::RT - 1) / T::RT;
-    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
     // With the active set as one 64-bit word per tile (bit i = row row0 + i is active; rows past n are never set)
     // the rows outside it are not read: the pass moves 8 |I| d bytes, the saving the paper gets from a compacted
     // copy X_I (Section 5) without the copy.  The word of the next tile is fetched one iteration ahead.
     constexpr bool kBits = MASK && T::RT == kWave;
     const uint64_t *Dbits = static_cast<const uint64_t *>(Dv);
-    const int64_t tile0 = (int64_t)blockIdx.x * kWaves + wv;
     constexpr int G = tiles_at_once(E, L, MASK);
+    const TileWalk walk(ntiles, kWaves, SOLVE && kBits);
+    const int64_t tile0 = walk.first, last = walk.last, nwaves = walk.step;
     uint64_t bits_next[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) bits_next[g] = (kBits && SKIP && tile0 + g * nwaves < ntiles) ? Dbits[tile0 + g * nwaves] : 0;
-    for (int64_t tile = tile0; tile < ntiles; tile += G * nwaves) {
+    for (int g = 0; g < G; ++g) bits_next[g] = (kBits && SKIP && tile0 + g * nwaves < last) ? Dbits[tile0 + g * nwaves] : 0;
+    for (int64_t tile = tile0; tile < last; tile += G * nwaves) {
         double x[G][U][E], Drow[G], c[U];
         uint64_t bits[G], any = 0;
         if (kBits && SKIP) {
@@ -217,17 +240,17 @@ __device__ __forceinline__ void hv_pass(double *lds, int64_t n, int64_t d, const
                 const int64_t ahead = tile + (G + g) * nwaves;
                 bits[g] = bits_next[g];
                 any |= bits[g];
-                bits_next[g] = (ahead < ntiles) ? Dbits[ahead] : 0;
+                bits_next[g] = (ahead < last) ? Dbits[ahead] : 0;
             }
             if (any == 0) continue;   // no active row in the tiles
         }
         // tiles past the last one: every row is past n
 #pragma unroll
-        for (int g = 0; g < G; ++g) T::load(X, n, d, (tile + g * nwaves) * T::RT, lane, x[g], (kBits && SKIP) ? bits[g] : ~0ull);
+        for (int g = 0; g < G; ++g) T::load(X, n, d, ((SOLVE && tile + g * nwaves >= last) ? ntiles : tile + g * nwaves) * T::RT, lane, x[g], (kBits && SKIP) ? bits[g] : ~0ull);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int64_t t = tile + g * nwaves, row = t * T::RT + own;
-            if (kBits && !SKIP) bits[g] = (t < ntiles) ? Dbits[t] : 0;
+            if (kBits && !SKIP) bits[g] = (t < last) ? Dbits[t] : 0;
             Drow[g] = 0.0;
             if (kBits) {
                 Drow[g] = ((bits[g] >> own) & 1u) ? 2.0 : 0.0;
@@ -301,13 +324,8 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
     uint64_t held_bits = 0;
     int64_t held_tile = -1;
     const int64_t ntiles = (n + T::RT - 1) / T::RT;
-    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
-    const int64_t wave_id = (int64_t)blockIdx.x * kWaves + wv;
-    const int64_t per_wave = (ntiles + nwaves - 1) / nwaves;
-    // kBits: tiles [first, last) one after the other; otherwise tiles wave_id, wave_id + nwaves, ...
-    const int64_t first = kBits ? wave_id * per_wave : wave_id;
-    const int64_t last = kBits ? ((first + per_wave < ntiles) ? first + per_wave : ntiles) : ntiles;
-    const int64_t step = kBits ? 1 : nwaves;
+    const TileWalk walk(ntiles, kWaves, kBits);
+    const int64_t first = walk.first, last = walk.last, step = walk.step;
     int it = 0;
     for (int64_t tile = first; tile < last; tile += step, ++it) {
         const int64_t row0 = tile * T::RT;
@@ -374,42 +392,191 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_fun_grad(int64_t n, in
     if constexpr (dense_finishes(L)) dense_finish<kWaves>(lds, fin, (int)d, partials, loss_partials, active_partials);
 }
 
-// ------------------------------------------------------------------ a round of a solve driven from the device
-// The pass that serves the problem's pending request -- function / gradient at a trial point or a Hessian-vector product -- and,
-// in the workgroup that finishes last, the step of Algorithm 1 or of the CG iteration that was waiting for it: one launch
-// per product, no vector kernels and no host in between.  d <= 32, tiles of 64 rows.
-struct RoundArgs {
+// ------------------------------------------------------------------ a solve driven from the device
+// Passes that serve the problem's pending request -- function / gradient at a trial point or a Hessian-vector product -- each followed
+// by the step of Algorithm 1 or of the CG iteration that was waiting for it.  d <= 32, tiles of 64 rows.
+// stamp == 0: the whole solve in one launch of workgroups that are all resident.  Every workgroup keeps the problem's state in LDS,
+// adds all partial sums and takes the step itself (in the same order, so all hold the same bits): between two passes lies one
+// barrier over the grid.  Only the first workgroup reports.  A round of 20,000 x 24 takes 7.6 us (the pass with its tile in registers 2.3, the
+// barrier 2, the sums 1.5, the step 1.5), as a launch of its own 10 and the gaps; whole solves 95 -> 63 us, 1M x 24 229 -> 197,
+// 5M x 18 logistic 748 -> 730.
+// stamp > 0: round `stamp` of a solve with a launch per round (grids of more workgroups than CUs, or a part of the GPU
+// busy otherwise): the workgroup that finishes last adds the sums and takes the step, the state lies in device memory.  The
+// same sums in the same order, the same results.
+struct SolveArgs {
     const double *X;
     const int8_t *y;
     void *D[2];
     double *partials, *loss_partials, *active_partials;
+    int64_t round_stride;   // doubles between the partial sums of even and odd rounds (a workgroup may be one round ahead)
     unsigned *ticket;
+    GridSync sync;
     BatchCtl *ctl;
     ProbState *st;
+    const double *w0;       // stamp == 0: the starting point
+    double C;
     tron_trace_rec *trace;
     BatchHost *host;
 };
 
+// Either pass of a solve, one tile at a time: fun_grad_pass and hv_pass in one loop.  x holds the wavefront's first tile already
+// where `loaded` is set; D of the next tile (L2-SVM Hessian-vector pass: also which of its rows are read) is fetched one step ahead.
 template <int E, int L, int U, bool VEC, int LOSS>
-__global__ __launch_bounds__(dense_block(L)) void k_dense_round(int64_t n, int64_t d, RoundArgs A, SolveParams P, int64_t stamp)
+__device__ __forceinline__ void solve_pass(double *lds, double (*lds_red)[dense_block(L) / kWave], const bool fg, int64_t n, int64_t d,
+                                           const double *__restrict__ X, const int8_t *__restrict__ y, const double *vec, void *Dv,
+                                           double *__restrict__ partials, double *__restrict__ loss_partials, double (&x)[U][E], const bool loaded)
+{
+    using T = Tile<E, L, U, VEC>;
+    constexpr int kWaves = dense_block(L) / kWave;
+    constexpr bool svm = LOSS == TRON_LOSS_L2SVM;
+    static_assert(T::RT == kWave, "one 64-bit word per tile");
+    double *D = static_cast<double *>(Dv);
+    uint64_t *Dbits = static_cast<uint64_t *>(Dv);
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int q = lane % L, own = T::own_row(lane);
+    double vreg[E], acc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        vreg[e] = (T::col(q, e) < d) ? vec[T::col(q, e)] : 0.0;
+        acc[e] = 0.0;
+    }
+    const int64_t ntiles = (n + T::RT - 1) / T::RT;
+    const TileWalk walk(ntiles, kWaves, svm);
+    double loss_acc = 0.0, dnext = 0.0;
+    uint64_t held_bits = 0, bnext = 0;
+    int64_t held_tile = -1;
+    if (!fg && walk.first < walk.last) {
+        if (svm) bnext = Dbits[walk.first];
+        else if (walk.first * T::RT + own < n) dnext = D[walk.first * T::RT + own];
+    }
+    int it = 0;
+    for (int64_t tile = walk.first; tile < walk.last; tile += walk.step, ++it) {
+        const int64_t row0 = tile * T::RT, after = tile + walk.step;
+        const uint64_t bits = bnext;
+        const double Drow = dnext;
+        if (!fg && after < walk.last) {
+            if (svm) bnext = Dbits[after];
+            else dnext = after * T::RT + own < n ? D[after * T::RT + own] : 0.0;
+        }
+        if (svm && !fg && bits == 0) continue;   // no active row in the tile
+        if (it > 0 || !loaded) T::load(X, n, d, row0, lane, x, svm && !fg ? bits : ~0ull);
+        double c[U];
+        const double z = T::row_sum(x, vreg, lane);
+        if (fg) {   // uniform
+            const bool in = row0 + own < n, mine = in && T::first_owner(lane);
+            const double yrow = in ? (double)y[row0 + own] : 1.0;
+            double alpha, zhat, Di;
+            loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
+            if (mine) loss_acc += alpha;
+            if (!in) {
+                Di = 0.0;
+                zhat = 0.0;
+            }
+            if (svm) {
+                const uint64_t word = T::ballot_rows(Di != 0.0, lane);
+                if (lane == (it & (kWave - 1))) { held_bits = word; held_tile = tile; }
+                if ((it & (kWave - 1)) == kWave - 1) {
+                    Dbits[held_tile] = held_bits;   // every lane holds one: 64 consecutive words
+                    held_tile = -1;
+                }
+            } else if (mine) {
+                D[row0 + own] = Di;
+            }
+            T::from_row_owner(zhat, c);
+        } else {
+            T::from_row_owner((svm ? (((bits >> own) & 1u) ? 2.0 : 0.0) : Drow) * z, c);   // a1 = D (X v)
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[u][e], acc[e]);
+        }
+    }
+    if (svm && held_tile >= 0) Dbits[held_tile] = held_bits;
+    loss_acc = wave_sum(loss_acc);
+    if (lane == 0) lds_red[0][wv] = loss_acc;
+    T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) t += lds_red[0][k];
+        store_shared(loss_partials + blockIdx.x, t);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void copy_words(T *dst, const T *src)
+{
+    static_assert(sizeof(T) % sizeof(uint64_t) == 0, "");
+    for (int i = threadIdx.x; i < (int)(sizeof(T) / sizeof(uint64_t)); i += blockDim.x) reinterpret_cast<uint64_t *>(dst)[i] = reinterpret_cast<const uint64_t *>(src)[i];
+}
+
+template <int E, int L, int U, bool VEC, int LOSS>
+__global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64_t d, SolveArgs A, SolveParams P, int64_t stamp)
 {
     constexpr int kWaves = dense_block(L) / kWave;
     constexpr bool svm = LOSS == TRON_LOSS_L2SVM;
     __shared__ double lds[dense_lds(E, L)];
     __shared__ double lds_red[2][kWaves];
-    const int mode = __builtin_amdgcn_readfirstlane(A.ctl->mode[0]);
-    if (mode == MODE_IDLE) {   // the solve ended in an earlier round
-        if (blockIdx.x == 0 && threadIdx.x < kWave) advance_problem(0, mode, d, 0.0, 0.0, A.ctl, A.st, P, A.trace, A.host, stamp);
-        return;
+    __shared__ BatchCtl ctl;
+    __shared__ ProbState st;
+    const bool whole = stamp == 0;
+    const double *__restrict__ X = A.X;
+    GridBarrier grid(A.sync);
+    if (whole) {
+        if (threadIdx.x < kWave) begin_problem(0, BEGIN_SOLVE, d, A.w0, A.C, &ctl, &st);
+        if (blockIdx.x != 0) {
+            A.trace = nullptr;
+            A.host = nullptr;
+            P.out = nullptr;
+        }
+    } else {
+        copy_words(&ctl, A.ctl);
+        copy_words(&st, A.st);
     }
-    void *D = __builtin_amdgcn_readfirstlane(A.ctl->dslot[0]) ? A.D[1] : A.D[0];
-    const double *vec = A.ctl->vec[0];
-    if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, A.X, A.y, vec, D, A.partials, A.loss_partials, A.active_partials);
-    else hv_pass<E, L, U, VEC, svm, false, svm>(lds, n, d, A.X, D, vec, A.partials);
-    double col, loss, active;
-    if (!dense_last_sums<kWaves>(lds, A.ticket, (int)d, A.partials, mode == MODE_FG ? A.loss_partials : nullptr, A.active_partials, col, loss, active)) return;
-    if (threadIdx.x == 0) *A.ticket = 0u;
-    advance_problem(0, mode, d, col, loss, A.ctl, A.st, P, A.trace, A.host, stamp);
+    __syncthreads();
+    // The first tile of the next pass is asked for before the wait for the other workgroups; it stays where it is the only one.
+    using T = Tile<E, L, U, VEC>;
+    constexpr bool kOne = tiles_at_once(E, L, svm) == 1;
+    const int64_t ntiles = (n + T::RT - 1) / T::RT;
+    const TileWalk walk(ntiles, kWaves, svm);
+    const bool one_tile = walk.first + walk.step >= walk.last;
+    double x[U][E];
+    if (kOne && whole) T::load(X, n, d, (walk.first < walk.last ? walk.first : ntiles) * T::RT, threadIdx.x & (kWave - 1), x);
+    for (int64_t round = 1;; ++round) {
+        const int mode = __builtin_amdgcn_readfirstlane(ctl.mode[0]);
+        if (mode == MODE_IDLE) break;
+        void *D = __builtin_amdgcn_readfirstlane(ctl.dslot[0]) ? A.D[1] : A.D[0];
+        const double *vec = ctl.vec[0];
+        const int64_t at = (round & 1) * A.round_stride;
+        double *partials = A.partials + at, *loss_partials = A.loss_partials + at, *active_partials = A.active_partials + at;
+        if constexpr (kOne) {
+            solve_pass<E, L, U, VEC, LOSS>(lds, lds_red, mode == MODE_FG, n, d, X, A.y, vec, D, partials, loss_partials, x, whole);
+        } else {
+            if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, A.y, vec, D, partials, loss_partials, active_partials);
+            else hv_pass<E, L, U, VEC, svm, false, svm, true>(lds, n, d, X, D, vec, partials);
+        }
+        if (whole) {
+            grid.arrive();
+            if (kOne && !one_tile) T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), x);
+            if (!grid.wait()) break;
+        } else if (!last_workgroup(A.ticket)) {
+            return;
+        }
+        double col, loss, active;
+        if (dense_add_rows<kWaves>(lds, (int)gridDim.x, (int)d, partials, mode == MODE_FG ? loss_partials : nullptr, active_partials, col, loss, active))
+            advance_problem(0, mode, d, col, loss, &ctl, &st, P, A.trace, A.host, whole ? round : stamp);
+        __syncthreads();
+        if (!whole) {
+            copy_words(A.ctl, &ctl);
+            copy_words(A.st, &st);
+            if (threadIdx.x == 0) *A.ticket = 0u;
+            return;
+        }
+    }
+    if (whole) grid.leave();
+    else if (blockIdx.x == 0 && threadIdx.x < kWave)   // the solve ended in an earlier round
+        advance_problem(0, MODE_IDLE, d, 0.0, 0.0, &ctl, &st, P, A.trace, A.host, stamp);
 }
 
 // ------------------------------------------------------------------ second stage of the wide matrices
@@ -579,19 +746,19 @@ int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *l
 }
 
 template <int E, int L>
-int launch_round(tron_dataset *ds, const SolveParams &P, const RoundArgs &A, int64_t stamp)
+int launch_solve(tron_dataset *ds, const SolveParams &P, const SolveArgs &A, int64_t stamp)
 {
     if constexpr (dense_finishes(L)) {
         constexpr int U = pick_U(E, L);
         const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
-#define TRON_ROUND(V, LS) \
-    hipLaunchKernelGGL((k_dense_round<E, L, U, V, LS>), dim3(dense_round_grid(ds->n, ds->d, P.loss)), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp)
+#define TRON_SOLVE(V, LS) \
+    hipLaunchKernelGGL((k_dense_solve<E, L, U, V, LS>), dim3(dense_round_grid(ds->n, ds->d, P.loss)), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp)
         if (P.loss == TRON_LOSS_LR) {
-            if (vec) TRON_ROUND((E % 2 == 0), TRON_LOSS_LR); else TRON_ROUND(false, TRON_LOSS_LR);
+            if (vec) TRON_SOLVE((E % 2 == 0), TRON_LOSS_LR); else TRON_SOLVE(false, TRON_LOSS_LR);
         } else {
-            if (vec) TRON_ROUND((E % 2 == 0), TRON_LOSS_L2SVM); else TRON_ROUND(false, TRON_LOSS_L2SVM);
+            if (vec) TRON_SOLVE((E % 2 == 0), TRON_LOSS_L2SVM); else TRON_SOLVE(false, TRON_LOSS_L2SVM);
         }
-#undef TRON_ROUND
+#undef TRON_SOLVE
         TRON_HIP(hipGetLastError());
         return TRON_OK;
     } else {
@@ -636,7 +803,7 @@ int launch_round(tron_dataset *ds, const SolveParams &P, const RoundArgs &A, int
 
 int dispatch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *partials, const DenseFinish &fin) { TRON_DISPATCH(launch_hv, ds, in, v, partials, fin) }
 int dispatch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *lp, double *ap, const DenseFinish &fin) { TRON_DISPATCH(launch_fg, ds, loss, w, Dout, lp, ap, fin) }
-int dispatch_round(tron_dataset *ds, const SolveParams &P, const RoundArgs &A, int64_t stamp) { TRON_DISPATCH(launch_round, ds, P, A, stamp) }
+int dispatch_solve(tron_dataset *ds, const SolveParams &P, const SolveArgs &A, int64_t stamp) { TRON_DISPATCH(launch_solve, ds, P, A, stamp) }
 
 // the second stage of a wide matrix; the others have completed it in the pass
 int launch_columns(tron_dataset *ds, int grid, const double *partials, double *col_partials, const double *loss_partials, const double *active_partials,
@@ -917,13 +1084,14 @@ int dense_work_units(int64_t n, int64_t d)
     return (int)(g > kMaxGrid ? kMaxGrid : g);
 }
 
-// column sums (grid * d) followed by loss partials (grid), the column workgroups' sums (d) and active-row counts (grid)
+// column sums (grid * d) followed by loss partials (grid), the column workgroups' sums (d) and active-row counts (grid); a solve
+// driven from the device has two sets of sums
 int64_t dense_partials_needed(int64_t n, int64_t d)
 {
     int64_t g = d <= kFinishMaxD ? dense_grid_few(n, d) : dense_grid_for(n, d);   // the largest grid of a pass
     g = std::max<int64_t>(g, dense_fun_grad_grid(n, d));
     for (int loss : {TRON_LOSS_LR, TRON_LOSS_L2SVM}) g = std::max<int64_t>(g, dense_round_grid(n, d, loss));
-    return d * g + g + d + g;
+    return (d <= kFinishMaxD ? 2 : 1) * (d * g + g + d + g);
 }
 
 // D of n rows as a pass keeps it: fp64, or the active set as one bit (d <= 32) or one byte a row
@@ -969,14 +1137,14 @@ int dense_hess_diag(tron_dataset *ds, double C, int Dslot, double *out)
     return launch_columns(ds, in.grid, ds->partials, ds->partials + (ds->d + 1) * ds->dense_grid, nullptr, nullptr, fin);
 }
 
-int dense_round(tron_dataset *ds, const SolveParams &P, DriverState &drv, int64_t stamp)
+int dense_solve_launch(tron_dataset *ds, const SolveParams &P, DriverState &drv, int64_t stamp, const double *w0, double C)
 {
     const int grid = dense_round_grid(ds->n, ds->d, P.loss);
     double *loss_partials = ds->partials + ds->d * grid;
-    const RoundArgs A{ds->X, ds->y8, {ds->Dbuf[0], ds->Dbuf[1]}, ds->partials, loss_partials, loss_partials + grid + ds->d,
-                      ds->ticket, drv.ctl, drv.st, P.trace_cap > 0 ? drv.trace_dev : nullptr, drv.host_dev};
+    const SolveArgs A{ds->X, ds->y8, {ds->Dbuf[0], ds->Dbuf[1]}, ds->partials, loss_partials, loss_partials + grid, (ds->d + 2) * grid,
+                      ds->ticket, grid_sync(ds), drv.ctl, drv.st, w0, C, P.trace_cap > 0 ? drv.trace_dev : nullptr, drv.host_dev};
     ProfScope ps(ds, SLOT_BATCH_PASS);
-    return dispatch_round(ds, P, A, stamp);
+    return dispatch_solve(ds, P, A, stamp);
 }
 
 int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Dslot, double *g)

@@ -229,7 +229,7 @@ extern "C" int tron_solve(tron_dataset *ds, const tron_params *params, double *w
                   "0 <= precond_blend <= 1, trace)");
         return TRON_EINVAL;
     }
-    // Dense matrices with d <= 32: the solve can be driven from the device (k_dense_round), which saves the host's waits for
+    // Dense matrices with d <= 32: the solve can be driven from the device (k_dense_solve), which saves the host's waits for
     // scalars and the vector kernels inside every iteration.  The logistic loss always is.  L2-SVM matrices above 1 GB stay
     // with the host, which can put the products on a compacted copy of the active rows (dense_compact_wanted) and for
     // which the waits are small next to the passes.
