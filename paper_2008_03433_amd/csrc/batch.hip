@@ -47,6 +47,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
     // function/gradient pass only, kept out of the registers: per wavefront and problem the loss sum of every lane's rows
     // and the new active-set words of up to 64 tiles
     __shared__ double lloss[kWavesPerBlock][KT][kWave];
+    __shared__ double lprod[LOSS == TRON_LOSS_LR ? kWavesPerBlock : 1][KT][kWave];   // and their product, see LossSum
     __shared__ uint64_t lheld[kWavesPerBlock][KT][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -82,6 +83,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
 #pragma unroll
     for (int k = 0; k < KT; ++k) {
         lloss[wv][k][lane] = 0.0;
+        if (!svm) lprod[wv][k][lane] = 0.0;
         lheld[wv][k][lane] = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[k][e] = 0.0;
@@ -146,10 +148,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
                     T::from_row_owner(svm ? (mine ? z : 0.0) : Drow[k] * z, c);
                 } else {
                     // the per-row terms of Table 1 run once per row
-                    double alpha, zhat, Di;
+                    LossTerm alpha;
+                    double zhat, Di;
                     loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
-                    if (!mine) { alpha = 0.0; zhat = 0.0; Di = 0.0; }
-                    lloss[wv][k][lane] += alpha;
+                    if (!mine) { alpha = LossTerm{0.0, 0.0}; zhat = 0.0; Di = 0.0; }
+                    LossSum<LOSS> losses{lloss[wv][k][lane], svm ? 0.0 : lprod[svm ? 0 : wv][k][lane]};
+                    losses.add(alpha);
+                    if ((it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) losses.scale();
+                    lloss[wv][k][lane] = losses.lin;
+                    if (!svm) lprod[wv][k][lane] = losses.p;
                     if (svm) {
                         const uint64_t nb = T::ballot_rows(Di != 0.0, lane);
                         if (lane == 0) lheld[wv][k][slotl] = nb;
@@ -181,7 +188,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
         if (mode[k] == MODE_IDLE) continue;   // uniform over the workgroup
         double *pk = partials + (int64_t)k * cols * gridDim.x;
         T::flush(acc[k], d, lane, wv, kWavesPerBlock, lds, pk + blockIdx.x, gridDim.x);
-        const double ls = block_sum(lloss[wv][k][lane], lds_red);   // its barriers also order the reuse of lds
+        const double ls = block_sum(LossSum<LOSS>{lloss[wv][k][lane], svm ? 0.0 : lprod[svm ? 0 : wv][k][lane]}.value(), lds_red);   // its barriers also order the reuse of lds
         if (threadIdx.x == 0) pk[d * (int64_t)gridDim.x + blockIdx.x] = ls;
     }
 }
@@ -329,9 +336,8 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
 
     double xr[NP][PW];
     double lossM = 0.0;   // L2-SVM: loss terms of this lane's rows of its problem
-    double lossK[KT];     // logistic: loss terms of this lane's row, by problem
-#pragma unroll
-    for (int k = 0; k < KT; ++k) lossK[k] = 0.0;
+    LossSum<LOSS> lossK[KT / PP];   // logistic: losses of this lane's row, by problem (PP k + sub)
+    int adds = 0;
     uint64_t nbM = 0;     // this lane's rows' bits of its problem's new active-set word for the current tile
     mfma4 G1 = {0.0, 0.0, 0.0, 0.0}, G2 = {0.0, 0.0, 0.0, 0.0};
 
@@ -467,13 +473,17 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
                         const bool act = by_sub_i(mk) == MODE_FG && kk < K;
                         const double z = Ex[(kk < K ? kk : 0) * kExRow + rowl];
                         const bool mine = act && ((by_sub_u(wq) >> (RT * h + rowl)) & 1u);
-                        double alpha, zhat, Di;
+                        LossTerm alpha;
+                        double zhat, Di;
                         loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
-                        if (!mine) { alpha = 0.0; zhat = 0.0; Di = 0.0; }
-#pragma unroll
-                        for (int j = 0; j < PP; ++j) lossK[k + j] += (sub == j) ? alpha : 0.0;
+                        if (!mine) { alpha = LossTerm{0.0, 0.0}; zhat = 0.0; Di = 0.0; }
+                        lossK[k / PP].add(alpha);
                         if (mine) Dval[((int64_t)kk * 2 + by_sub_i(dk)) * n + tile * kWave + RT * h + rowl] = Di;
                         if (act) Ex[kk * kExRow + rowl] = zhat;
+                    }
+                    if ((++adds & (LossSum<LOSS>::kAdds - 1)) == 0) {
+#pragma unroll
+                        for (int k = 0; k < KT / PP; ++k) lossK[k].scale();
                     }
                     wave_lds_fence();
                 }
@@ -516,7 +526,7 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
                         if (kHasEx) cfg = (modeM == MODE_FG) ? ex[v] : 0.0;
                         if (svm && any_fg) {   // uniform
                             const double yv = ((ybits >> (4 * v)) & 1u) ? 1.0 : -1.0;
-                            double alpha, zhat, Di;
+                            double alpha, zhat, Di;   // L2-SVM only
                             loss_terms_dev<LOSS>(z[v], yv, alpha, zhat, Di);
                             const bool mine = modeM == MODE_FG && bit;   // a row of this lane's problem (rows past n have no bit)
                             lossM += mine ? alpha : 0.0;
@@ -579,7 +589,7 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
 #pragma unroll
     for (int k = 0; k < KT; ++k) {
         if (mode[k] == MODE_IDLE) continue;   // uniform over the workgroup
-        const double ls = FG ? block_sum(svm ? (p == k ? lossM : 0.0) : lossK[k], lds_red) : 0.0;
+        const double ls = FG ? block_sum(svm ? (p == k ? lossM : 0.0) : (sub == k % PP ? lossK[k / PP].value() : 0.0), lds_red) : 0.0;
         if (threadIdx.x == 0) partials[((int64_t)k * cols + d) * gridDim.x + blockIdx.x] = ls;
     }
 }

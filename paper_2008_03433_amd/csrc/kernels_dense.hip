@@ -313,7 +313,8 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
         wreg[e] = (T::col(q, e) < d) ? w[T::col(q, e)] : 0.0;
         acc[e] = 0.0;
     }
-    double loss_acc = 0.0, active_acc = 0.0;   // sum of the losses; number of rows with D != 0
+    LossSum<LOSS> losses;
+    double active_acc = 0.0;   // number of rows with D != 0
     // D of a tile is stored only after the loads of the next tile have been issued: the memory counter retires in
     // order, so a store issued before them would have to complete before their data could be used.
     // Active set of the L2-SVM when a tile has 64 rows: one 64-bit word per tile.  A wavefront then walks a
@@ -334,10 +335,11 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
         const bool in = row0 + own < n, mine = in && T::first_owner(lane);
         const double yrow = in ? (double)y[row0 + own] : 1.0;
         const double z = T::row_sum(x, wreg, lane);           // z = X w
-        double alpha, zhat, Di;
+        LossTerm alpha;
+        double zhat, Di;
         loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
         if (mine) {
-            loss_acc += alpha;
+            losses.add(alpha);
             active_acc += (Di != 0.0) ? 1.0 : 0.0;
         }
         if (!in) {
@@ -355,6 +357,7 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
             if (LOSS == TRON_LOSS_L2SVM) Dmask[row0 + own] = (Di != 0.0) ? 1 : 0;
             else Dout[row0 + own] = Di;
         }
+        if ((it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) losses.scale();
         T::from_row_owner(zhat, c);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -363,7 +366,7 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
         }
     }
     if (kBits && held_tile >= 0) Dbits[held_tile] = held_bits;
-    loss_acc = wave_sum(loss_acc);
+    const double loss_acc = wave_sum(losses.value());
     active_acc = wave_sum(active_acc);
     if (lane == 0) {
         lds_red[0][wv] = loss_acc;
@@ -442,7 +445,8 @@ __device__ __forceinline__ void solve_pass(double *lds, double (*lds_red)[dense_
     }
     const int64_t ntiles = (n + T::RT - 1) / T::RT;
     const TileWalk walk(ntiles, kWaves, svm);
-    double loss_acc = 0.0, dnext = 0.0;
+    LossSum<LOSS> losses;
+    double dnext = 0.0;
     uint64_t held_bits = 0, bnext = 0;
     int64_t held_tile = -1;
     if (!fg && walk.first < walk.last) {
@@ -465,9 +469,11 @@ __device__ __forceinline__ void solve_pass(double *lds, double (*lds_red)[dense_
         if (fg) {   // uniform
             const bool in = row0 + own < n, mine = in && T::first_owner(lane);
             const double yrow = in ? (double)y[row0 + own] : 1.0;
-            double alpha, zhat, Di;
+            LossTerm alpha;
+            double zhat, Di;
             loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
-            if (mine) loss_acc += alpha;
+            if (mine) losses.add(alpha);
+            if ((it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) losses.scale();
             if (!in) {
                 Di = 0.0;
                 zhat = 0.0;
@@ -493,7 +499,7 @@ __device__ __forceinline__ void solve_pass(double *lds, double (*lds_red)[dense_
         }
     }
     if (svm && held_tile >= 0) Dbits[held_tile] = held_bits;
-    loss_acc = wave_sum(loss_acc);
+    const double loss_acc = wave_sum(losses.value());
     if (lane == 0) lds_red[0][wv] = loss_acc;
     T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
     if (threadIdx.x == 0) {
