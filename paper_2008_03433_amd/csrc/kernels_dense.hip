@@ -315,8 +315,6 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
     }
     LossSum<LOSS> losses;
     double active_acc = 0.0;   // number of rows with D != 0
-    // D of a tile is stored only after the loads of the next tile have been issued: the memory counter retires in
-    // order, so a store issued before them would have to complete before their data could be used.
     // Active set of the L2-SVM when a tile has 64 rows: one 64-bit word per tile.  A wavefront then walks a
     // contiguous range of tiles, lane i keeps the word of its i-th, 64+i-th, ... tile, and every 64 tiles the words
     // go out as one 512-byte store: small stores between the reads cost far more than their bytes.
@@ -403,6 +401,7 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_fun_grad(int64_t n, in
 // barrier over the grid.  Only the first workgroup reports.  A round of 20,000 x 24 takes 7.6 us (the pass with its tile in registers 2.3, the
 // barrier 2, the sums 1.5, the step 1.5), as a launch of its own 10 and the gaps; whole solves 95 -> 63 us, 1M x 24 229 -> 197,
 // 5M x 18 logistic 748 -> 730.
+// ONE: no wavefront has more than one tile (stamp == 0 only).
 // stamp > 0: round `stamp` of a solve with a launch per round (grids of more workgroups than CUs, or a part of the GPU
 // busy otherwise): the workgroup that finishes last adds the sums and takes the step, the state lies in device memory.  The
 // same sums in the same order, the same results.
@@ -422,19 +421,87 @@ struct SolveArgs {
     BatchHost *host;
 };
 
-// Either pass of a solve, one tile at a time: fun_grad_pass and hv_pass in one loop.  x holds the wavefront's first tile already
-// where `loaded` is set; D of the next tile (L2-SVM Hessian-vector pass: also which of its rows are read) is fetched one step ahead.
+// Either pass of a solve over so few rows that a wavefront has one tile at most: the tile, its labels and the two D buffers' entries
+// of the lane's row stay in registers for the whole solve (D goes to memory as well, for the calls after the solve).  The same
+// operations in the same order as fun_grad_pass and hv_pass.  20,000 x 24: 1.2 us a pass instead of 3.
 template <int E, int L, int U, bool VEC, int LOSS>
-__device__ __forceinline__ void solve_pass(double *lds, double (*lds_red)[dense_block(L) / kWave], const bool fg, int64_t n, int64_t d,
-                                           const double *__restrict__ X, const int8_t *__restrict__ y, const double *vec, void *Dv,
-                                           double *__restrict__ partials, double *__restrict__ loss_partials, double (&x)[U][E], const bool loaded)
+struct OneTile {
+    using T = Tile<E, L, U, VEC>;
+    static constexpr int kWaves = dense_block(L) / kWave;
+    static constexpr bool svm = LOSS == TRON_LOSS_L2SVM;
+    double x[U][E], y, Dreg[2];
+    bool in;
+
+    __device__ __forceinline__ void load(int64_t n, int64_t d, const double *__restrict__ X, const int8_t *__restrict__ y8)
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        const int64_t row0 = ((int64_t)blockIdx.x * kWaves + threadIdx.x / kWave) * T::RT, row = row0 + T::own_row(lane);
+        in = row < n;
+        T::load(X, n, d, row0, lane, x);
+        y = in ? (double)y8[row] : 1.0;
+        Dreg[0] = Dreg[1] = 0.0;
+    }
+
+    __device__ __forceinline__ void pass(double *lds, double (*lds_red)[kWaves], const bool fg, const int slot, int64_t d, const double *vec, void *Dv,
+                                         double *__restrict__ partials, double *__restrict__ loss_partials)
+    {
+        const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, q = lane % L;
+        const int64_t tile = (int64_t)blockIdx.x * kWaves + wv;
+        double vreg[E], acc[E], c[U], coef;
+#pragma unroll
+        for (int e = 0; e < E; ++e) vreg[e] = (T::col(q, e) < d) ? vec[T::col(q, e)] : 0.0;
+        const double z = T::row_sum(x, vreg, lane);
+        LossSum<LOSS> losses;
+        if (fg) {   // uniform
+            LossTerm alpha;
+            double zhat, Di;
+            loss_terms_dev<LOSS>(z, y, alpha, zhat, Di);
+            if (in && T::first_owner(lane)) losses.add(alpha);
+            Di = in ? Di : 0.0;
+            coef = in ? zhat : 0.0;
+            if (svm) {
+                const uint64_t word = T::ballot_rows(Di != 0.0, lane);
+                if (lane == 0 && __ballot(in) != 0) static_cast<uint64_t *>(Dv)[tile] = word;
+            } else if (in && T::first_owner(lane)) {
+                static_cast<double *>(Dv)[tile * T::RT + T::own_row(lane)] = Di;
+            }
+            Dreg[0] = slot ? Dreg[0] : Di;
+            Dreg[1] = slot ? Di : Dreg[1];
+        } else {
+            coef = (slot ? Dreg[1] : Dreg[0]) * z;   // a1 = D (X v)
+        }
+        T::from_row_owner(coef, c);
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[u][e], acc[e]);
+        }
+        const double loss_acc = fg ? wave_sum(losses.value()) : 0.0;
+        if (lane == 0) lds_red[0][wv] = loss_acc;
+        T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
+        if (threadIdx.x == 0) {
+            double t = 0.0;
+#pragma unroll
+            for (int k = 0; k < kWaves; ++k) t += lds_red[0][k];
+            store_shared(loss_partials + blockIdx.x, t);
+        }
+    }
+};
+
+// Either pass of an L2-SVM solve over more rows, one tile at a time: fun_grad_pass and hv_pass in one loop, the same operations in the
+// same order.  x holds the wavefront's first tile already where `loaded` is set: it was asked for before the wait for the other
+// workgroups, which saves 2 us of a pass of 27 (1M x 24).  The logistic loss keeps its two loops: one for both took 730 us a solve of
+// 5M x 18 instead of 718.
+template <int E, int L, int U, bool VEC>
+__device__ __forceinline__ void svm_solve_pass(double *lds, double (*lds_red)[dense_block(L) / kWave], const bool fg, int64_t n, int64_t d,
+                                               const double *__restrict__ X, const int8_t *__restrict__ y, const double *vec, uint64_t *Dbits,
+                                               double *__restrict__ partials, double *__restrict__ loss_partials, double (&x)[U][E], const bool loaded)
 {
     using T = Tile<E, L, U, VEC>;
     constexpr int kWaves = dense_block(L) / kWave;
-    constexpr bool svm = LOSS == TRON_LOSS_L2SVM;
     static_assert(T::RT == kWave, "one 64-bit word per tile");
-    double *D = static_cast<double *>(Dv);
-    uint64_t *Dbits = static_cast<uint64_t *>(Dv);
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int q = lane % L, own = T::own_row(lane);
     double vreg[E], acc[E];
@@ -444,53 +511,34 @@ __device__ __forceinline__ void solve_pass(double *lds, double (*lds_red)[dense_
         acc[e] = 0.0;
     }
     const int64_t ntiles = (n + T::RT - 1) / T::RT;
-    const TileWalk walk(ntiles, kWaves, svm);
-    LossSum<LOSS> losses;
-    double dnext = 0.0;
-    uint64_t held_bits = 0, bnext = 0;
+    const TileWalk walk(ntiles, kWaves, true);
+    LossSum<TRON_LOSS_L2SVM> losses;
+    uint64_t held_bits = 0, bnext = (!fg && walk.first < walk.last) ? Dbits[walk.first] : 0;
     int64_t held_tile = -1;
-    if (!fg && walk.first < walk.last) {
-        if (svm) bnext = Dbits[walk.first];
-        else if (walk.first * T::RT + own < n) dnext = D[walk.first * T::RT + own];
-    }
     int it = 0;
-    for (int64_t tile = walk.first; tile < walk.last; tile += walk.step, ++it) {
-        const int64_t row0 = tile * T::RT, after = tile + walk.step;
-        const uint64_t bits = bnext;
-        const double Drow = dnext;
-        if (!fg && after < walk.last) {
-            if (svm) bnext = Dbits[after];
-            else dnext = after * T::RT + own < n ? D[after * T::RT + own] : 0.0;
-        }
-        if (svm && !fg && bits == 0) continue;   // no active row in the tile
-        if (it > 0 || !loaded) T::load(X, n, d, row0, lane, x, svm && !fg ? bits : ~0ull);
+    for (int64_t tile = walk.first; tile < walk.last; ++tile, ++it) {
+        const int64_t row0 = tile * T::RT;
+        const uint64_t bits = bnext;   // fetched one step ahead
+        bnext = (!fg && tile + 1 < walk.last) ? Dbits[tile + 1] : 0;
+        if (!fg && bits == 0) continue;   // no active row in the tile
+        if (it > 0 || !loaded) T::load(X, n, d, row0, lane, x, fg ? ~0ull : bits);
         double c[U];
         const double z = T::row_sum(x, vreg, lane);
         if (fg) {   // uniform
-            const bool in = row0 + own < n, mine = in && T::first_owner(lane);
-            const double yrow = in ? (double)y[row0 + own] : 1.0;
+            const bool in = row0 + own < n;
             LossTerm alpha;
             double zhat, Di;
-            loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
-            if (mine) losses.add(alpha);
-            if ((it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) losses.scale();
-            if (!in) {
-                Di = 0.0;
-                zhat = 0.0;
+            loss_terms_dev<TRON_LOSS_L2SVM>(z, in ? (double)y[row0 + own] : 1.0, alpha, zhat, Di);
+            if (in && T::first_owner(lane)) losses.add(alpha);
+            const uint64_t word = T::ballot_rows(in && Di != 0.0, lane);
+            if (lane == (it & (kWave - 1))) { held_bits = word; held_tile = tile; }
+            if ((it & (kWave - 1)) == kWave - 1) {
+                Dbits[held_tile] = held_bits;   // every lane holds one: 64 consecutive words
+                held_tile = -1;
             }
-            if (svm) {
-                const uint64_t word = T::ballot_rows(Di != 0.0, lane);
-                if (lane == (it & (kWave - 1))) { held_bits = word; held_tile = tile; }
-                if ((it & (kWave - 1)) == kWave - 1) {
-                    Dbits[held_tile] = held_bits;   // every lane holds one: 64 consecutive words
-                    held_tile = -1;
-                }
-            } else if (mine) {
-                D[row0 + own] = Di;
-            }
-            T::from_row_owner(zhat, c);
+            T::from_row_owner(in ? zhat : 0.0, c);
         } else {
-            T::from_row_owner((svm ? (((bits >> own) & 1u) ? 2.0 : 0.0) : Drow) * z, c);   // a1 = D (X v)
+            T::from_row_owner((((bits >> own) & 1u) ? 2.0 : 0.0) * z, c);   // a1 = D (X v)
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -498,7 +546,7 @@ __device__ __forceinline__ void solve_pass(double *lds, double (*lds_red)[dense_
             for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[u][e], acc[e]);
         }
     }
-    if (svm && held_tile >= 0) Dbits[held_tile] = held_bits;
+    if (held_tile >= 0) Dbits[held_tile] = held_bits;
     const double loss_acc = wave_sum(losses.value());
     if (lane == 0) lds_red[0][wv] = loss_acc;
     T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
@@ -517,7 +565,7 @@ __device__ __forceinline__ void copy_words(T *dst, const T *src)
     for (int i = threadIdx.x; i < (int)(sizeof(T) / sizeof(uint64_t)); i += blockDim.x) reinterpret_cast<uint64_t *>(dst)[i] = reinterpret_cast<const uint64_t *>(src)[i];
 }
 
-template <int E, int L, int U, bool VEC, int LOSS>
+template <int E, int L, int U, bool VEC, int LOSS, bool ONE>
 __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64_t d, SolveArgs A, SolveParams P, int64_t stamp)
 {
     constexpr int kWaves = dense_block(L) / kWave;
@@ -526,7 +574,7 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
     __shared__ double lds_red[2][kWaves];
     __shared__ BatchCtl ctl;
     __shared__ ProbState st;
-    const bool whole = stamp == 0;
+    const bool whole = ONE || stamp == 0;
     const double *__restrict__ X = A.X;
     GridBarrier grid(A.sync);
     if (whole) {
@@ -541,14 +589,12 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
         copy_words(&st, A.st);
     }
     __syncthreads();
-    // The first tile of the next pass is asked for before the wait for the other workgroups; it stays where it is the only one.
     using T = Tile<E, L, U, VEC>;
-    constexpr bool kOne = tiles_at_once(E, L, svm) == 1;
-    const int64_t ntiles = (n + T::RT - 1) / T::RT;
-    const TileWalk walk(ntiles, kWaves, svm);
-    const bool one_tile = walk.first + walk.step >= walk.last;
-    double x[U][E];
-    if (kOne && whole) T::load(X, n, d, (walk.first < walk.last ? walk.first : ntiles) * T::RT, threadIdx.x & (kWave - 1), x);
+    constexpr bool kAhead = !ONE && svm && tiles_at_once(E, L, true) == 1;
+    const TileWalk walk((n + T::RT - 1) / T::RT, kWaves, true);
+    OneTile<E, L, U, VEC, LOSS> mine;
+    if constexpr (ONE) mine.load(n, d, X, A.y);
+    if (kAhead && whole && walk.first < walk.last) T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), mine.x);
     for (int64_t round = 1;; ++round) {
         const int mode = __builtin_amdgcn_readfirstlane(ctl.mode[0]);
         if (mode == MODE_IDLE) break;
@@ -556,15 +602,13 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
         const double *vec = ctl.vec[0];
         const int64_t at = (round & 1) * A.round_stride;
         double *partials = A.partials + at, *loss_partials = A.loss_partials + at, *active_partials = A.active_partials + at;
-        if constexpr (kOne) {
-            solve_pass<E, L, U, VEC, LOSS>(lds, lds_red, mode == MODE_FG, n, d, X, A.y, vec, D, partials, loss_partials, x, whole);
-        } else {
-            if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, A.y, vec, D, partials, loss_partials, active_partials);
-            else hv_pass<E, L, U, VEC, svm, false, svm, true>(lds, n, d, X, D, vec, partials);
-        }
+        if constexpr (ONE) mine.pass(lds, lds_red, mode == MODE_FG, ctl.dslot[0], d, vec, D, partials, loss_partials);
+        else if constexpr (kAhead) svm_solve_pass<E, L, U, VEC>(lds, lds_red, mode == MODE_FG, n, d, X, A.y, vec, static_cast<uint64_t *>(D), partials, loss_partials, mine.x, whole);
+        else if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, A.y, vec, D, partials, loss_partials, active_partials);
+        else hv_pass<E, L, U, VEC, svm, false, svm, true>(lds, n, d, X, D, vec, partials);
         if (whole) {
             grid.arrive();
-            if (kOne && !one_tile) T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), x);
+            if (kAhead && walk.first < walk.last) T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), mine.x);
             if (!grid.wait()) break;
         } else if (!last_workgroup(A.ticket)) {
             return;
@@ -757,8 +801,12 @@ int launch_solve(tron_dataset *ds, const SolveParams &P, const SolveArgs &A, int
     if constexpr (dense_finishes(L)) {
         constexpr int U = pick_U(E, L);
         const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
-#define TRON_SOLVE(V, LS) \
-    hipLaunchKernelGGL((k_dense_solve<E, L, U, V, LS>), dim3(dense_round_grid(ds->n, ds->d, P.loss)), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp)
+        const int grid = dense_round_grid(ds->n, ds->d, P.loss);
+        const bool one = stamp == 0 && (ds->n + kWave - 1) / kWave <= (int64_t)grid * (dense_block(L) / kWave);
+#define TRON_SOLVE(V, LS) do { \
+        if (one) hipLaunchKernelGGL((k_dense_solve<E, L, U, V, LS, true>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp); \
+        else hipLaunchKernelGGL((k_dense_solve<E, L, U, V, LS, false>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp); \
+    } while (0)
         if (P.loss == TRON_LOSS_LR) {
             if (vec) TRON_SOLVE((E % 2 == 0), TRON_LOSS_LR); else TRON_SOLVE(false, TRON_LOSS_LR);
         } else {
