@@ -221,7 +221,9 @@ typedef struct {
  * On return the handle caches D at the final iterate (so tron_hv may follow).
  * Dense problems with d <= 32 and no preconditioner -- logistic loss: of any size; L2-SVM: matrices up to 1 GB -- are driven
  * from the device, like tron_batch_solve with one problem over all rows: same rules, same results up to summation order
- * (knob "dense_device_driver").
+ * (knob "dense_device_driver").  Sparse problems of up to some four million entries (not partitioned by columns, up to 2048 chunks
+ * of 2048 entries in either orientation) are solved in one launch, unless the profiler is on: same rules, same results up to
+ * summation order (knob "solve_resident").
  */
 TRON_API int tron_solve(tron_dataset *ds, const tron_params *params, double *w_dev, tron_result *res_host);
 
@@ -351,8 +353,9 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  * "dense_device_driver" (-1/0/1): tron_solve on a dense matrix with d <= 32 and no preconditioner runs its trust-region and
  *   CG steps on the device (as tron_batch_solve does): 0 never, 1 always, -1 (default) for the logistic loss, and for the
  *   L2-SVM on matrices up to 1 GB (larger ones may put their products on a compacted copy, see above).
- * "solve_resident" (-1/0): a tron_solve driven from the device runs as one launch whose workgroups wait for each other between
- *   the steps, where all of them can be resident at once (-1, default), or as a launch per product (0).
+ * "solve_resident" (-1/0): a tron_solve driven from the device, and that of a small sparse problem, runs as one launch whose
+ *   workgroups wait for each other between the steps, where all of them can be resident at once (-1, default), or as a launch per
+ *   product (0; sparse problems: driven by the host).
  * "solve_wait_us" (-1..10000000): how long a workgroup of such a launch waits for the others before it gives up and the
  *   solve starts again with a launch per product: microseconds, 0 not at all, -1 (default) a tenth of a second.
  * "batch_grid" (0..4096): workgroups of the multi-problem pass (0 = as many as are resident at once).

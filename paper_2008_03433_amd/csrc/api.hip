@@ -114,7 +114,7 @@ static int alloc_common(tron_dataset *ds)
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->partials), sizeof(double) * need));
     // The scalars the host steers by live in pinned host memory that the kernels write directly: they are there when
     // the stream has drained, without a copy operation between the last kernel and the host's wait.
-    TRON_HIP(hipHostMalloc(reinterpret_cast<void **>(&ds->scal_host), sizeof(double) * kScalars, hipHostMallocMapped));
+    TRON_HIP(hipHostMalloc(reinterpret_cast<void **>(&ds->scal_host), sizeof(double) * kScalars + (ds->dense ? 0 : kSolveHostBytes), hipHostMallocMapped));
     TRON_HIP(hipHostGetDevicePointer(reinterpret_cast<void **>(&ds->scal_dev), ds->scal_host, 0));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->scal_copy), sizeof(double) * kScalars));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->ticket), 64));
@@ -218,6 +218,7 @@ void tron_dataset_destroy(tron_dataset *ds)
     if (!ds) return;
     hipStreamSynchronize(ds->stream);
     dense_device_release(ds);
+    csr_resident_release(ds);
     dense_compact_release(ds);
     hipFree(ds->X);
     ds->fwd.release();

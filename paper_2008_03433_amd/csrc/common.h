@@ -67,6 +67,7 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxGrid = 2048;       // 256 CUs x 8 resident workgroups: grid-stride kernels use at most this
 constexpr int kChunk = 2048;         // nonzeros per workgroup in the CSR kernels (256 threads x 8)
 constexpr int kScalars = 16;         // scalar slots shared by the reductions
+constexpr int kSolveHostBytes = 3072;   // pinned memory behind the scalars: what a solve in one launch reports
 
 // ---------------------------------------------------------------- profiling slots
 enum Slot {
@@ -218,6 +219,7 @@ struct CsrPlan {
     const double *col_scale = nullptr;   // device, cols (not owned) or null
     double *xs = nullptr;                // device, cols: work space for x .* col_scale
     int nblocks = 0;                     // total number of chunks
+    int max_rows = 0;                    // P == 1, plain or direct: most rows of a chunk, empty ones among them
     double *carry = nullptr;             // device, nblocks: sum of the part of a row entering chunk c from before
     int nfix = 0;                        // number of (partition, split row) pairs
     int fix_max_cnt = 0;                 // largest fix_cnt
@@ -261,7 +263,7 @@ struct CsrPlan {
 }  // namespace tron
 
 // ---------------------------------------------------------------- the handle
-namespace tron { struct DriverState; struct SolveParams; }
+namespace tron { struct DriverState; struct SolveParams; struct CsrSolver; }
 struct tron_dataset {
     int64_t n = 0, d = 0;
     bool dense = false;
@@ -308,6 +310,7 @@ struct tron_dataset {
     int64_t active_count[2] = {0, 0};   // rows with D != 0 in each buffer
 
     tron::DriverState *driver = nullptr;   // dense: solves driven from the device
+    tron::CsrSolver *csr_solver = nullptr;   // sparse: work space of solves in one launch
 
     // solver vectors (d each), allocated on first tron_solve
     double *sv[9] = {nullptr};
@@ -483,6 +486,12 @@ int dense_solve_launch(tron_dataset *ds, const SolveParams &P, DriverState &drv,
 // ---- batch.hip
 int dense_device_solve(tron_dataset *ds, const tron_params &P, double *w_dev, tron_result *res);
 void dense_device_release(tron_dataset *ds);
+
+// ---- csr_solve.hip
+// tron_solve in one launch, where the layouts and the tuning allow it: 1 = done (*status is what tron_solve returns), 0 = not
+// possible or given up (w_dev is untouched), < 0 = an error
+int csr_resident_solve(tron_dataset *ds, const tron_params &P, double *w_dev, tron_result *res, int *status);
+void csr_resident_release(tron_dataset *ds);
 
 // ---- solver.hip
 int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot, bool ww);               // scalars[0]=sum of loss terms, [1]=w.w if ww, no sync

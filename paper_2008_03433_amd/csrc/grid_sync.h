@@ -52,14 +52,7 @@ public:
             const bool flat = gridDim.x <= kSyncFlat;
             const unsigned *word = flat ? root() : release(blockIdx.x % kSyncGroups);
             const unsigned want = flat ? round_ * gridDim.x : round_;
-            bool good = false;
-            if (ticks_ >= 0) {
-                const long long from = wall_clock64();
-                for (unsigned polls = 1;; ++polls) {
-                    if ((int)(get(word) - want) >= 0) { good = true; break; }
-                    if ((polls & 15u) == 0 && (get(given_up()) != 0 || wall_clock64() - from > ticks_)) break;
-                }
-            }
+            const bool good = poll(word, want);
             if (threadIdx.x == 0) {
                 ok = good;
                 if (!good) put(given_up(), 1u);
@@ -67,6 +60,26 @@ public:
         }
         __syncthreads();
         return ok;
+    }
+
+    // A lane waits until *place is no longer `empty`, adds what is there to sum and makes the place empty again.  False: given up, like
+    // wait(); the workgroup must not arrive any more.
+    __device__ __forceinline__ bool take(uint64_t *place, uint64_t empty, double &sum)
+    {
+        if (ticks_ >= 0) {
+            const long long from = wall_clock64();
+            for (unsigned polls = 1;; ++polls) {
+                const uint64_t v = __hip_atomic_load(place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (v != empty) {
+                    sum += __longlong_as_double((long long)v);
+                    __hip_atomic_store(place, empty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    return true;
+                }
+                if ((polls & 15u) == 0 && (get(given_up()) != 0 || wall_clock64() - from > ticks_)) break;
+            }
+        }
+        put(given_up(), 1u);
+        return false;
     }
 
     // the last thing a workgroup does, whether it gave up or not
@@ -77,6 +90,15 @@ public:
     }
 
 private:
+    __device__ __forceinline__ bool poll(const unsigned *word, unsigned want)
+    {
+        if (ticks_ < 0) return false;
+        const long long from = wall_clock64();
+        for (unsigned polls = 1;; ++polls) {
+            if ((int)(get(word) - want) >= 0) return true;
+            if ((polls & 15u) == 0 && (get(given_up()) != 0 || wall_clock64() - from > ticks_)) return false;
+        }
+    }
     __device__ unsigned *root() const { return w_; }
     __device__ unsigned *left() const { return w_ + kSyncLine; }
     __device__ unsigned *given_up() const { return w_ + 2 * kSyncLine; }

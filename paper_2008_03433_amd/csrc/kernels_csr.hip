@@ -28,15 +28,10 @@
 #include <exception>
 #include <thread>
 
-#include "device_util.h"
+#include "csr_chunk.h"
 #include "host_util.h"
 
 namespace tron {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef double v2d __attribute__((ext_vector_type(2)));
-typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
 constexpr int64_t kGatherBytesForPartitioning = 3 << 19;  // 1.5 MiB: larger gather vectors get partitioned
 constexpr int64_t kMinNnzForPartitioning = 1 << 22;
@@ -183,6 +178,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         A.part_base[0] = 0; A.part_nnz[0] = stored; A.part_chunk0[0] = 0; A.part_nchunks[0] = A.nblocks;
         A.max_chunks = A.nblocks;
         plan_chunks(rp.data(), rows, A.nblocks, row_lo, fix_row, fix_b0, fix_cnt);
+        for (int c = 0; c < A.nblocks; ++c) A.max_rows = std::max(A.max_rows, row_lo[c + 1] - row_lo[c]);
         TRON_TRY(upload(&A.rowptr, rp.data(), (size_t)rows + 1, st));
         TRON_TRY(upload(&A.col, pcol.data(), (size_t)stored, st));
         TRON_TRY(upload(&A.val, pval.data(), (size_t)stored, st));
@@ -523,6 +519,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
             }
             rl[chunk] = (int32_t)rows;
             most = std::max<int64_t>(most, rows - rl[chunk - 1]);
+            A.max_rows = (int)std::min<int64_t>(most, 0x7fffffff);
             if (most <= 4 * kChunk && chunk + nlong <= kDirectMaxSums) {
                 std::vector<int32_t> row_seg((size_t)rows, -1);
                 for (int64_t m = 0; m < nseg_total; ++m) row_seg[seg_row[m]] = (int32_t)m;
@@ -627,12 +624,6 @@ __device__ __forceinline__ double finish_row(const EpiArgs &A, int64_t r, double
 
 // With HOT, a negative stored column c means "entry ~c of the workgroup's LDS table" (the most frequent
 // columns of the partition, copied from x once per workgroup).
-// x[c] through a 32-bit byte offset (tron_dataset_create_csr accepts n, d < 2^29 only)
-__device__ __forceinline__ double load_elem(const double *__restrict__ x, int c)
-{
-    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(x) + (size_t)((uint32_t)c << 3));
-}
-
 template <bool HOT>
 __device__ __forceinline__ double gather(const double *__restrict__ x, const double *table, int c)
 {
@@ -807,8 +798,6 @@ struct PartArgs {
 // Stream registers of one chunk: thread t holds its own entries 8t .. 8t+7 (see col_pos / val_pos).  Every load instruction of
 // a wavefront covers whole consecutive cache lines: one that reads 16 of every 32 bytes is served in 64-byte requests, twice
 // as many, and the number of requests a CU keeps in flight is what bounds it.
-constexpr int kQuarter = kChunk / 4;
-
 template <bool HEAD, bool UNIT>
 struct StreamRegs {
     v4i c[HEAD ? 1 : 2];        // HEAD: eight 16-bit LDS slots
@@ -853,59 +842,6 @@ __device__ __forceinline__ void products(const StreamRegs<HEAD, UNIT> &r, const 
     }
 }
 
-// ------------------------------------------------------------------ segment sums of a chunk
-// The entries of a chunk are in segment order (a segment = the entries of one row inside the chunk) and a flag bit
-// marks the last entry of every segment.  Thread t owns entries 8t .. 8t+7: it sums its own runs in registers, the open run
-// at its end is carried to the following threads by a segmented scan over the wavefront (DPP) and across the four
-// wavefronts through LDS.  No loop depends on how long the segments are.  (With the entries stored in order the products were
-// passed through LDS, from load order to thread order: a barrier more and, 500,000 x 750,000 with values, 52.6 instead of 47.6 us
-// in the tiles, 45.7 / 43.8 in the head partition, 45.1 / 42.9 and 41.7 / 40.3 in the ranges.)
-constexpr int kOutOffset = 16;                  // segment sums are parked at prod[kOutOffset ...] (behind the wavefront totals)
-constexpr int kSegPasses = kChunk / kBlock;     // a chunk holds at most kChunk segments: 8 passes of 256
-constexpr int kProdDoubles = kOutOffset + kChunk;
-
-// f = the thread's 8 flag bits.  p[e] in: the product of entry 8 * tid + e.  On return p[e] = sum of the thread's entries from the start of the run
-// containing e up to e, cin = what the entries before the thread add to its first run, idx0 = number of flags in the
-// threads before it.  Uses prod[0..7] for the wavefront totals; contains one barrier.
-__device__ __forceinline__ void runs_from_regs(double *prod, const unsigned f, double (&p)[8], double &cin, int &idx0)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    double run = 0.0;
-    const unsigned nf = ~f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        run += p[e];
-        p[e] = run;
-        const int keep = (int)(nf << (31 - e)) >> 31;   // all ones unless entry e ends a segment
-        run = __hiloint2double(__double2hiint(run) & keep, __double2loint(run) & keep);
-    }
-    const int cnt = __popc(f);
-    double t = run;
-    int h = (f != 0u);
-    wave_seg_scan(t, h);
-    const int ci = wave_scan_add(cnt);
-    const double ext = lane_before(t);
-    const int exh = lane_before(h);
-    if (lane == kWave - 1) {
-        prod[2 * wv] = t;
-        *reinterpret_cast<int2 *>(prod + 2 * wv + 1) = make_int2(h, ci);
-    }
-    __syncthreads();
-    double ct = 0.0;
-    int cb = 0;
-#pragma unroll
-    for (int w = 0; w < kWavesPerBlock - 1; ++w) {
-        if (w < wv) {
-            const double wt = prod[2 * w];
-            const int2 hc = *reinterpret_cast<const int2 *>(prod + 2 * w + 1);
-            ct = hc.x ? wt : ct + wt;
-            cb += hc.y;
-        }
-    }
-    cin = exh ? ext : ct + ext;
-    idx0 = cb + ci - cnt;
-}
-
 // flag byte of the calling thread: bit e = entry 8*tid + e is the last of its segment
 __device__ __forceinline__ unsigned load_flags(const uint8_t *__restrict__ flags /* of this chunk */)
 {
@@ -921,7 +857,7 @@ __device__ __forceinline__ void chunk_segments(double *prod, const unsigned flag
 {
     double cin;
     int idx0;
-    runs_from_regs(prod, flags, p, cin, idx0);
+    runs_from_regs(prod, threadIdx.x, flags, p, cin, idx0);
     double *outv = prod + kOutOffset;
     int i = idx0 - (continued ? 1 : 0);
     bool first = true;
@@ -987,7 +923,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_direct(DirectPtrs P, int nlong, 
     double p[8], cin;
     products<false, false, SQ, false>(s, x, nullptr, p);
     int idx0;
-    runs_from_regs(prod, flags, p, cin, idx0);
+    runs_from_regs(prod, threadIdx.x, flags, p, cin, idx0);
     double *outv = prod + kOutOffset;
     {
         int i = idx0 - (tab.z > 0 ? 1 : 0);
@@ -1474,7 +1410,7 @@ __device__ __forceinline__ void tile_step(double *prod, uint16_t *slots, double 
     }
     if (8 * tid < nseg) *reinterpret_cast<uint4 *>(slots + 8 * tid) = cur.slots;
     int idx0;
-    runs_from_regs(prod, cur.flags, p, cin, idx0);   // barrier inside: the slots are visible after it
+    runs_from_regs(prod, threadIdx.x, cur.flags, p, cin, idx0);   // barrier inside: the slots are visible after it
     // What the threads before add to the thread's first segment goes in on its own, before the segment's own sum.
     int sl[8];
     int i = idx0;

@@ -237,6 +237,12 @@ extern "C" int tron_solve(tron_dataset *ds, const tron_params *params, double *w
         const double bytes = (double)ds->n * (double)ds->d * 8.0;
         if (g_tuning.dense_device_driver > 0 || P.loss == TRON_LOSS_LR || bytes <= 1e9) return dense_device_solve(ds, P, w_dev, res);
     }
+    if (!ds->dense) {
+        int status = TRON_OK;
+        const int rc = csr_resident_solve(ds, P, w_dev, res, &status);
+        if (rc < 0) return rc;
+        if (rc > 0) return status;
+    }
     const double eta0 = 1e-4, eta1 = 0.25, eta2 = 0.75, sig2 = 0.5, sig3 = 4.0;
     tron_trace_rec *trace = res->trace;
     const int trace_cap = res->trace_cap;

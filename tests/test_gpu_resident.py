@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import paper_2008_03433_amd as tron
-from datagen import DenseProblem
+from datagen import DenseProblem, SparseProblem
 from oracle import LOSS_LR, LOSS_L2SVM
 from util import torch_mod
 
@@ -69,6 +69,147 @@ def test_solves_of_several_threads_on_streams_of_their_own(rng):
             ds = tron.Dataset.from_problem(problems[k])
             w0 = torch.zeros(24, dtype=torch.float64, device="cuda")
             out[k] = [_solve(ds, LOSS_L2SVM, 0.3, w0) for _ in range(5)]
+            ds.close()
+
+    for k in range(len(problems)):
+        work(k, alone)
+    threads = [threading.Thread(target=work, args=(k, together)) for k in range(len(problems))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert together == alone
+
+
+# ------------------------------------------------------------------ sparse
+def _sparse(rng, n, d, mean, common=(), long_rows=(), zipf=0.0):
+    """Rows of about `mean` entries; columns `common` are in every row, the rows `long_rows` have two thirds of all columns, every
+    seventh row and the columns after 0.9 d are empty (but for those)."""
+    p = np.arange(1, d + 1, dtype=np.float64) ** -zipf
+    p[int(0.9 * d) + 1:] = 0.0
+    p = np.cumsum(p / p.sum())
+    rows, cols = [], []
+    for i in range(n):
+        k = 0 if i % 7 == 6 else rng.poisson(mean)
+        c = np.minimum(np.searchsorted(p, rng.random(k)), d - 1)
+        if i in long_rows:
+            c = rng.permutation(d)[:2 * d // 3]
+        c = np.unique(np.concatenate([c, np.asarray(common, dtype=c.dtype)])).astype(np.int32)
+        rows.append(c.size)
+        cols.append(c)
+    rowptr = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    col = np.concatenate(cols) if cols else np.zeros(0, np.int32)
+    val = rng.lognormal(size=col.size) / np.sqrt(np.repeat(np.maximum(rows, 1), rows))
+    score = np.zeros(n)
+    np.add.at(score, np.repeat(np.arange(n), rows), val * rng.standard_normal(d)[col])
+    y = np.where(score + 0.3 * rng.standard_normal(n) >= 0.0, 1.0, -1.0)
+    return SparseProblem("resident", n, d, rowptr, col, val, y)
+
+
+# one entry; fewer entries than a chunk of 2048; rows and columns of several lengths with many short ones in a chunk; columns
+# longer than a chunk (the transposed copy as segments) and rows longer than a chunk (the other one); more chunks than the
+# workgroups hold at once (512); more rows in a chunk than the launch takes (the other path, in both cases)
+SPARSE = {
+    "one": dict(n=1, d=1, mean=0, common=(0,)),
+    "tiny": dict(n=9, d=13, mean=3),
+    "chunk": dict(n=60, d=41, mean=30),
+    "short": dict(n=2500, d=2000, mean=4),
+    "columns": dict(n=6000, d=3000, mean=12, common=(5, 1700), zipf=1.05),
+    "rows": dict(n=300, d=9000, mean=60, long_rows=(0, 17, 18, 299)),
+    "both": dict(n=5000, d=5000, mean=10, common=(0, 2600), long_rows=(3, 4000)),
+    "rounds": dict(n=30_000, d=20_000, mean=55, zipf=0.8),
+    "wide": dict(n=400, d=60_000, mean=12),
+}
+
+
+def _same_solve(a, b, rel):
+    """The same trajectory, the numbers within rel.  (Rounding of 1e-16 per sum, which the inner iterations amplify: up to 5e-9 in w
+    over forty problems of this kind.)"""
+    wa, wb = np.frombuffer(a[0]), np.frombuffer(b[0])
+    assert np.linalg.norm(wa - wb) <= rel * max(np.linalg.norm(wb), 1e-300)
+    assert abs(a[1] - b[1]) <= rel * abs(b[1])
+    assert (a[3], a[4], a[5]) == (b[3], b[4], b[5])
+    for s, t in zip(a[6], b[6]):
+        assert [s[k] for k in ("iter", "cg_iters", "accepted", "on_boundary")] == [t[k] for k in ("iter", "cg_iters", "accepted", "on_boundary")]
+        assert abs(s["f"] - t["f"]) <= rel * abs(t["f"]) and abs(s["delta"] - t["delta"]) <= 1e3 * rel * abs(t["delta"])
+
+
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("name", SPARSE)
+def test_sparse_solve_in_one_launch_follows_the_solve_driven_by_the_host(rng, knob, loss, name):
+    torch = torch_mod()
+    q = _sparse(rng, **SPARSE[name])
+    ds = tron.Dataset.from_problem(q)
+    zero = torch.zeros(q.d, dtype=torch.float64, device="cuda")
+    far = torch.from_numpy(3.0 * rng.standard_normal(q.d)).cuda()
+    try:
+        # C so small, and from far away the inner solves so short, that rounding stays small: with C = 1 the L2-SVM solve of "columns"
+        # takes 78 products, and the host-driven solve itself moves by 5e-2 in w when its start moves by one part in 1e15.
+        # Not preconditioned by the whole diagonal: of one column that is the Hessian, and the step then ends exactly at the radius.
+        far_kw = dict(max_cg=12, max_outer=4)
+        for start, C, kw in ((zero, 0.02, {}), (far, 0.02, far_kw), (zero, 0.02, dict(precond_blend=0.3)), (far, 0.02, dict(precond_blend=0.9, **far_kw)),
+                             (zero, 0.02, dict(max_outer=1)), (zero, 0.02, dict(max_cg=2, trace_cap=1))):
+            def solve():
+                w = start.clone()
+                r = ds.solve(loss, C, 0.01, w, **kw)
+                hv = torch.empty_like(w)
+                ds.hv(C, far, hv)   # with the D that the solve leaves
+                return w.cpu().numpy().tobytes(), r.f, r.gnorm, r.outer_iters, r.cg_iters_total, r.status, r.trace, hv.cpu().numpy()
+
+            one = solve()
+            again = solve()
+            assert one[:7] == again[:7]
+            knob("solve_wait_us", 0)    # every workgroup gives up at once, the host drives the solve
+            given_up = solve()
+            knob("solve_wait_us", -1)
+            assert solve()[:7] == one[:7]
+            knob("solve_resident", 0)
+            host = solve()
+            knob("solve_resident", -1)
+            assert given_up[:7] == host[:7]
+            _same_solve(one, host, 5e-9)
+            assert np.linalg.norm(one[7] - host[7]) <= 1e-7 * np.linalg.norm(host[7])
+    finally:
+        ds.close()
+
+
+def test_sparse_solve_of_many_steps_goes_on_in_further_launches(rng, knob):
+    """More than 512 products, the most of one launch, and more records than the pinned ones (32)."""
+    torch = torch_mod()
+    q = _sparse(rng, 1500, 400, 20, common=(3,))
+    ds = tron.Dataset.from_problem(q)
+    w0 = torch.zeros(q.d, dtype=torch.float64, device="cuda")
+    try:
+        for kw in (dict(cg_xi=1e-9), dict(max_cg=2, max_outer=60)):
+            def solve():
+                w = w0.clone()
+                return ds.solve(LOSS_LR, 1e3, 1e-7, w, **kw), w
+
+            one, w = solve()
+            knob("solve_resident", 0)
+            host, v = solve()
+            knob("solve_resident", -1)
+            if "cg_xi" in kw:   # the same minimiser: the gradient is 1e-7 of the first one, H >= I
+                assert one.n_hv > 256 and one.status == host.status == 0
+                assert abs(one.f - host.f) <= 1e-9 * host.f
+            else:
+                assert one.outer_iters == host.outer_iters > 32 and len(one.trace) == len(host.trace)
+                assert [t["iter"] for t in one.trace] == list(range(1, one.outer_iters + 1))
+                assert abs(one.f - host.f) <= 1e-6 * host.f
+    finally:
+        ds.close()
+
+
+def test_sparse_solves_of_several_threads_on_streams_of_their_own(rng):
+    torch = torch_mod()
+    problems = [_sparse(rng, **SPARSE[k]) for k in ("columns", "rounds", "both", "short")]
+    alone, together = {}, {}
+
+    def work(k, out):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            ds = tron.Dataset.from_problem(problems[k])
+            w0 = torch.zeros(problems[k].d, dtype=torch.float64, device="cuda")
+            out[k] = [_solve(ds, LOSS_LR, 0.3, w0) for _ in range(5)]
             ds.close()
 
     for k in range(len(problems)):
