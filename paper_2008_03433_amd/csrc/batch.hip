@@ -1134,17 +1134,17 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
         const ResidentShare share(ds->device, grid);
         drv.host->stamp[0] = 0;
         TRON_TRY(dense_solve_launch(ds, P, drv, 0, w_dev, C));
-        // the stream's own wait takes some microseconds more to notice the end than the first workgroup's last word
-        for (unsigned spins = 1;; ++spins) {
-            const int64_t v = __atomic_load_n(&drv.host->stamp[0], __ATOMIC_ACQUIRE);
-            if ((v != 0 && (v & 3) == MODE_IDLE) || ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady)) break;
+        // With the stamp everything is there that the call returns; the stream's own wait would take some microseconds more.
+        auto ended = [&]() { return __atomic_load_n(&drv.host->stamp[0], __ATOMIC_ACQUIRE) != 0; };
+        for (unsigned spins = 1; !ended(); ++spins) {
+            if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
             __builtin_ia32_pause();
         }
-        (void)hipGetLastError();
-        TRON_HIP(hipStreamSynchronize(ds->stream));
-        // otherwise workgroups gave up waiting for others before the first of them had the result; w0 is as it was
-        const int64_t v = __atomic_load_n(&drv.host->stamp[0], __ATOMIC_ACQUIRE);
-        done = v != 0 && (v & 3) == MODE_IDLE;
+        if (!ended()) {
+            (void)hipGetLastError();
+            TRON_HIP(hipStreamSynchronize(ds->stream));
+        }
+        done = ended();   // otherwise workgroups gave up waiting for others before the first of them had the result; w0 is as it was
     }
     if (!done) {
         TRON_TRY(launch_begin(ds, drv, 1, BEGIN_SOLVE, w_dev, &C));

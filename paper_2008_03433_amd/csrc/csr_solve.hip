@@ -529,7 +529,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
     __shared__ double pieces[kMaxTeams];
     __shared__ int bad;
     int tid = threadIdx.x & (kTeam - 1);
-    const int team = __builtin_amdgcn_readfirstlane(threadIdx.x / kTeam), teams = blockDim.x / kTeam;
+    const int team = __builtin_amdgcn_readfirstlane(threadIdx.x / kTeam);
     int first = team * (int)gridDim.x + (int)blockIdx.x;
     double *lds = lds_all + team * kTeamLds, *piece = pieces + team;
     GridBarrier grid(args.sync);

@@ -576,14 +576,12 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
     __shared__ ProbState st;
     const bool whole = ONE || stamp == 0;
     const double *__restrict__ X = A.X;
+    double *out = P.out;
+    if (whole) P.out = nullptr;   // stored at the end
     GridBarrier grid(A.sync);
     if (whole) {
         if (threadIdx.x < kWave) begin_problem(0, BEGIN_SOLVE, d, A.w0, A.C, &ctl, &st);
-        if (blockIdx.x != 0) {
-            A.trace = nullptr;
-            A.host = nullptr;
-            P.out = nullptr;
-        }
+        if (blockIdx.x != 0) A.trace = nullptr;
     } else {
         copy_words(&ctl, A.ctl);
         copy_words(&st, A.st);
@@ -595,9 +593,13 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
     OneTile<E, L, U, VEC, LOSS> mine;
     if constexpr (ONE) mine.load(n, d, X, A.y);
     if (kAhead && whole && walk.first < walk.last) T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), mine.x);
+    bool done = false;
     for (int64_t round = 1;; ++round) {
         const int mode = __builtin_amdgcn_readfirstlane(ctl.mode[0]);
-        if (mode == MODE_IDLE) break;
+        if (mode == MODE_IDLE) {
+            done = true;
+            break;
+        }
         void *D = __builtin_amdgcn_readfirstlane(ctl.dslot[0]) ? A.D[1] : A.D[0];
         const double *vec = ctl.vec[0];
         const int64_t at = (round & 1) * A.round_stride;
@@ -615,7 +617,7 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
         }
         double col, loss, active;
         if (dense_add_rows<kWaves>(lds, (int)gridDim.x, (int)d, partials, mode == MODE_FG ? loss_partials : nullptr, active_partials, col, loss, active))
-            advance_problem(0, mode, d, col, loss, &ctl, &st, P, A.trace, A.host, whole ? round : stamp);
+            advance_problem(0, mode, d, col, loss, &ctl, &st, P, A.trace, whole ? nullptr : A.host, stamp);
         __syncthreads();
         if (!whole) {
             copy_words(A.ctl, &ctl);
@@ -624,8 +626,17 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
             return;
         }
     }
-    if (whole) grid.leave();
-    else if (blockIdx.x == 0 && threadIdx.x < kWave)   // the solve ended in an earlier round
+    if (whole) {
+        if (done && blockIdx.x == 0 && threadIdx.x < kWave) {
+            // the host goes on when it sees the stamp: everything that the call returns has arrived by then
+            const int lane = threadIdx.x;
+            if (lane < d) store_shared(out + lane, st.w[lane]);
+            if (lane == 0) A.host->sc[0] = st.sc;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0) __hip_atomic_store(&A.host->stamp[0], (int64_t)1 << 2 | MODE_IDLE, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        grid.leave();
+    } else if (blockIdx.x == 0 && threadIdx.x < kWave)   // the solve ended in an earlier round
         advance_problem(0, MODE_IDLE, d, 0.0, 0.0, &ctl, &st, P, A.trace, A.host, stamp);
 }
 
