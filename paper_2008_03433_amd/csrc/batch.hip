@@ -615,7 +615,8 @@ __global__ __launch_bounds__(kBlock) void k_member_planes(int64_t n, int K, cons
 constexpr int kAdvanceBlock = 1024;
 
 // One workgroup per problem.  All sixteen wavefronts add up the pass's partial sums (fixed order); the first one then runs
-// the step that was waiting for them.
+// the step that was waiting for them.  A wavefront's loads are asked for together, eight of each of its columns (two with d = 24,
+// three at most): latency is all there is to it.  One load after the other it took 9.1 us for 512 workgroups of six problems, 17 for 1024 of twelve.
 __global__ __launch_bounds__(kAdvanceBlock) void k_batch_advance(int64_t d, int grid, const double *__restrict__ partials,
                                                           BatchCtl *ctl, ProbState *st, SolveParams P,
                                                           tron_trace_rec *trace, BatchHost *host, int64_t stamp)
@@ -625,12 +626,29 @@ __global__ __launch_bounds__(kAdvanceBlock) void k_batch_advance(int64_t d, int 
     __shared__ double cs[kVecPad + 1];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     if (mode != MODE_IDLE) {   // uniform
-        for (int c = wv; c <= d; c += kAdvanceBlock / kWave) {
-            const double *p = partials + ((int64_t)k * (d + 1) + c) * grid;
-            double s = 0.0;
-            for (int b = lane; b < grid; b += kWave) s += p[b];
-            s = wave_sum(s);
-            if (lane == 0) cs[c] = s;
+        constexpr int kWaves = kAdvanceBlock / kWave, kColumns = kVecPad / kWaves + 1, kAtOnce = 8;
+        const double *p = partials + ((int64_t)k * (d + 1) + wv) * grid;
+        double s[kColumns];
+#pragma unroll
+        for (int j = 0; j < kColumns; ++j) s[j] = 0.0;
+        for (int b0 = lane; b0 < grid; b0 += kAtOnce * kWave) {
+            double v[kColumns][kAtOnce];
+#pragma unroll
+            for (int j = 0; j < kColumns; ++j)
+#pragma unroll
+                for (int i = 0; i < kAtOnce; ++i) {
+                    const int b = b0 + i * kWave;
+                    v[j][i] = (wv + j * kWaves <= d && b < grid) ? p[(int64_t)j * kWaves * grid + b] : 0.0;
+                }
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i)
+#pragma unroll
+                for (int j = 0; j < kColumns; ++j) s[j] += v[j][i];
+        }
+#pragma unroll
+        for (int j = 0; j < kColumns; ++j) {
+            const double t = wave_sum(s[j]);
+            if (lane == 0 && wv + j * kWaves <= d) cs[wv + j * kWaves] = t;
         }
         __syncthreads();
     }
@@ -771,7 +789,6 @@ int launch_begin(tron_dataset *ds, DriverState &drv, int K, int what, const doub
 {
     BatchC Cs;
     for (int k = 0; k < kBatchMax; ++k) Cs.v[k] = (k < K) ? C_host[k] : 1.0;
-    for (int k = 0; k < kBatchMax; ++k) drv.host->stamp[k] = 0;   // the stream is drained between calls
     ProfScope ps(ds, SLOT_BATCH_ADVANCE);
     hipLaunchKernelGGL(k_batch_begin, dim3(K), dim3(kWave), 0, ds->stream, what, ds->d, IN, Cs, drv.ctl, drv.st);
     TRON_HIP(hipGetLastError());
@@ -779,29 +796,35 @@ int launch_begin(tron_dataset *ds, DriverState &drv, int K, int what, const doub
 }
 
 // Enqueues rounds until every problem is idle: launch(stamp, no_fg), stamp = 1, 2, ...  The kernels write every problem's
-// stamp and next mode into pinned memory, which the host polls while the device works: it keeps kAhead rounds enqueued behind
+// stamp and next mode into pinned memory, which the host polls while the device works: it keeps some rounds enqueued behind
 // the last one it has seen (a round that finds every problem idle takes 2 us).  Copying the modes to the host and waiting for
 // the stream every fourth round, as this replaces, took 40 us of a solve's 170 (20,000 x 24).
+// It returns when every problem has its results, which come before the stamp that says so; the rounds behind the last one are then
+// still to run (and find nothing to do).  So the numbers of the rounds go on from call to call: a stamp of an earlier call counts
+// for nothing.
+// ahead: the rounds kept enqueued.  Two where a round takes less than about 20 us (16 MB), for shorter ones the queue would
+// run empty; one otherwise: 1M x 24 with six problems 321 us a solve with two, the last of which keep the stream busy for 18.
 // exact: wait for every round before the next, and tell the launch when no problem asks for function and gradient.
-constexpr int64_t kAhead = 2;
 template <class Launch>
 int drive_rounds(tron_dataset *ds, DriverState &drv, int K, int64_t round_cap, bool exact, Launch launch)
 {
+    const int64_t before = drv.rounds, ahead = exact ? 0 : (double)ds->n * (double)ds->d * 8.0 > 16e6 ? 1 : 2;
     int64_t launched = 0;
     for (unsigned spins = 0;;) {
         int64_t seen = INT64_MAX;
         bool live = false, fg = false;
         for (int k = 0; k < K; ++k) {
-            const int64_t v = __atomic_load_n(&drv.host->stamp[k], __ATOMIC_ACQUIRE);
-            seen = std::min(seen, v >> 2);
-            live |= v == 0 || (v & 3) != MODE_IDLE;
+            const int64_t v = __atomic_load_n(&drv.host->stamp[k], __ATOMIC_ACQUIRE), round = std::max<int64_t>((v >> 2) - before, 0);
+            seen = std::min(seen, round);
+            live |= round == 0 || (v & 3) != MODE_IDLE;
             fg |= (v & 3) == MODE_FG;
         }
         if (!live) return TRON_OK;
-        if (launched < seen + (exact ? 1 : kAhead + 1)) {
-            if (launched > round_cap + kAhead) { set_error("internal: problems still running after the round limit"); return TRON_ESTATE; }
+        if (launched < seen + ahead + 1) {
+            if (launched > round_cap + ahead) { set_error("internal: problems still running after the round limit"); return TRON_ESTATE; }
             ++launched;
-            TRON_TRY(launch(launched, exact && launched > 1 && !fg));
+            drv.rounds += 1;
+            TRON_TRY(launch(drv.rounds, exact && launched > 1 && !fg));
             spins = 0;
             continue;
         }
@@ -813,13 +836,13 @@ int drive_rounds(tron_dataset *ds, DriverState &drv, int K, int64_t round_cap, b
         if (e == hipSuccess) {
             int64_t last = INT64_MAX;
             for (int k = 0; k < K; ++k) last = std::min(last, __atomic_load_n(&drv.host->stamp[k], __ATOMIC_ACQUIRE) >> 2);
-            if (last < launched) { set_error("internal: a round has ended without its stamp"); return TRON_ESTATE; }
+            if (last < drv.rounds) { set_error("internal: a round has ended without its stamp"); return TRON_ESTATE; }
         }
         std::this_thread::yield();
     }
 }
 
-// what problem k's results say, after the stream has drained
+// what problem k's results say
 void fill_result(const DriverState &drv, int k, int cap, tron_result &r)
 {
     const ProbScalars &sc = drv.host->sc[k];
@@ -860,7 +883,7 @@ int one_shot(tron_batch *b, int what, int loss, const double *C_host, const doub
     P.out = OUT;
     TRON_TRY(launch_begin(ds, b->drv, b->K, what, IN, C_host));
     TRON_TRY(launch_pass(b, loss, what == BEGIN_HV));
-    TRON_TRY(launch_advance(b, P, 1));
+    TRON_TRY(launch_advance(b, P, ++b->drv.rounds));
     TRON_HIP(hipStreamSynchronize(ds->stream));
     if (scal_host)
         for (int k = 0; k < b->K; ++k) scal_host[k] = b->drv.host->sc[k].out_scal;
@@ -1062,7 +1085,6 @@ extern "C" int tron_batch_solve(tron_batch *b, const tron_params *params, const 
         TRON_TRY(launch_pass(b, Q.loss, no_fg));
         return launch_advance(b, P, stamp);
     }));
-    TRON_HIP(hipStreamSynchronize(ds->stream));
     int overall = TRON_OK;
     for (int k = 0; k < b->K; ++k) {
         fill_result(b->drv, k, cap, res[k]);
@@ -1085,6 +1107,7 @@ int DriverState::create(int K, hipStream_t stream)
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&st), sizeof(ProbState) * K));
     TRON_HIP(hipHostMalloc(reinterpret_cast<void **>(&host), sizeof(BatchHost), hipHostMallocMapped));
     TRON_HIP(hipHostGetDevicePointer(reinterpret_cast<void **>(&host_dev), host, 0));
+    memset(host, 0, sizeof(BatchHost));
     TRON_HIP(hipMemsetAsync(ctl, 0, sizeof(BatchCtl), stream));
     TRON_HIP(hipMemsetAsync(st, 0, sizeof(ProbState) * K, stream));
     return TRON_OK;
@@ -1132,10 +1155,10 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     const int grid = dense_round_grid(ds->n, ds->d, Q.loss);
     if (resident_possible(ds, grid)) {
         const ResidentShare share(ds->device, grid);
-        drv.host->stamp[0] = 0;
+        drv.host->finished = 0;
         TRON_TRY(dense_solve_launch(ds, P, drv, 0, w_dev, C));
         // With the stamp everything is there that the call returns; the stream's own wait would take some microseconds more.
-        auto ended = [&]() { return __atomic_load_n(&drv.host->stamp[0], __ATOMIC_ACQUIRE) != 0; };
+        auto ended = [&]() { return __atomic_load_n(&drv.host->finished, __ATOMIC_ACQUIRE) != 0; };
         for (unsigned spins = 1; !ended(); ++spins) {
             if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
             __builtin_ia32_pause();
@@ -1149,7 +1172,6 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     if (!done) {
         TRON_TRY(launch_begin(ds, drv, 1, BEGIN_SOLVE, w_dev, &C));
         TRON_TRY(drive_rounds(ds, drv, 1, round_limit(Q), false, [&](int64_t stamp, bool) -> int { return dense_solve_launch(ds, P, drv, stamp, nullptr, C); }));
-        TRON_HIP(hipStreamSynchronize(ds->stream));
     }
     fill_result(drv, 0, cap, *res);
     // D at the final iterate, in the layout of the single-problem calls (one bit per row in 64-bit words for the L2-SVM, fp64 per

@@ -48,6 +48,7 @@ struct BatchC { double v[kBatchMax]; };
 // round it has seen times four plus the mode of its next request, and, once it is idle, its results.
 struct BatchHost {
     int64_t stamp[kBatchMax];
+    int64_t finished;   // a solve in one launch has its results
     ProbScalars sc[kBatchMax];
 };
 
@@ -58,6 +59,7 @@ struct DriverState {
     BatchHost *host = nullptr, *host_dev = nullptr;         // pinned; its device address
     tron_trace_rec *trace = nullptr, *trace_dev = nullptr;  // pinned, K x trace_cap
     int trace_cap = 0;
+    int64_t rounds = 0;   // enqueued so far
     int create(int K, hipStream_t st);
     int ensure_trace(int K, int cap);
     void release();
@@ -261,11 +263,15 @@ __device__ __forceinline__ void advance_problem(const int k, const int mode, con
         ctl->dslot[k] = next.slot;
         S.sc = sc;
         if (host && sc.phase == PH_DONE) host->sc[k] = sc;
-        // running or not, for the host that enqueues rounds meanwhile (see drive_rounds); the results above are read after
-        // the stream has drained
-        if (host) __hip_atomic_store(&host->stamp[k], (stamp << 2) | next.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    if (sc.phase == PH_DONE && in && P.out) P.out[(int64_t)k * d + j] = one_shot ? o : S.w[j];
+    if (sc.phase == PH_DONE && in && P.out) store_shared(P.out + (int64_t)k * d + j, one_shot ? o : S.w[j]);
+    // running or not, for the host that enqueues rounds meanwhile (see drive_rounds); of a problem that is done, after its results
+    if (sc.phase == PH_DONE) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (host && lane == 0) __hip_atomic_store(&host->stamp[k], (stamp << 2) | next.mode, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else if (host && lane == 0) {
+        __hip_atomic_store(&host->stamp[k], (stamp << 2) | next.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // First request of problem k, by one wavefront.  what = BEGIN_SOLVE: state reset, w0 = IN[k]; when w0 is not zero the gradient

@@ -628,12 +628,12 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
     }
     if (whole) {
         if (done && blockIdx.x == 0 && threadIdx.x < kWave) {
-            // the host goes on when it sees the stamp: everything that the call returns has arrived by then
+            // the host goes on when it sees this: everything that the call returns has arrived by then
             const int lane = threadIdx.x;
             if (lane < d) store_shared(out + lane, st.w[lane]);
             if (lane == 0) A.host->sc[0] = st.sc;
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (lane == 0) __hip_atomic_store(&A.host->stamp[0], (int64_t)1 << 2 | MODE_IDLE, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (lane == 0) __hip_atomic_store(&A.host->finished, (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
         grid.leave();
     } else if (blockIdx.x == 0 && threadIdx.x < kWave)   // the solve ended in an earlier round
