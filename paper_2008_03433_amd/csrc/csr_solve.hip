@@ -35,6 +35,7 @@ constexpr int kSegRows = 4096;
 constexpr int kTeamLds = kProdDoubles + kPlainRows;   // (segments: 9/8 kChunk products, later the sums)
 static_assert(kOutOffset + kChunk / 8 * 9 <= kTeamLds, "products of a chunk of segments");
 constexpr int kMaxResidentGrid = 256;
+constexpr int kLine = 16;            // words of 8 bytes
 constexpr int64_t kOutInKernel = 1 << 16;   // the first workgroup copies the result out; longer ones are a copy operation
 constexpr int kStepsPerLaunch = 512;         // some milliseconds; a longer solve goes on in another launch
 
@@ -49,12 +50,12 @@ struct ChunkPlan {
     const int32_t *row_seg;
     const int2 *chunk_long;
     const int4 *long_row;
-    uint64_t *pieces;           // of the rows longer than a chunk, one per chunk and then one per such row; kNoPiece until it is there
+    uint64_t *pieces;           // of the rows longer than a chunk, one per chunk and then one per such row; kEmpty until it is there
     int64_t stored;
     int nchunks, nlong;
 };
 
-constexpr uint64_t kNoPiece = 0x7ff4dead00c0ffeeull;   // a NaN that no arithmetic returns
+constexpr uint64_t kEmpty = 0x7ff4dead00c0ffeeull;   // a NaN that no arithmetic returns
 
 enum { STEP_END = 0, STEP_START, STEP_ZERO, STEP_TRIAL, STEP_CG,   // products with X
        STEP_START_G, STEP_ZERO_G, STEP_TRIAL_G, STEP_HV, STEP_DIAG, STEP_RESTART };   // with X^T, or (the last) none
@@ -74,6 +75,7 @@ __device__ __noinline__ RowTerms row_terms(double z, double y)
 // The state of the solve: every workgroup's own, all the same.
 struct CsrState {
     int step, first_diag, it, onb, cur, dcur, outer, cg_total, n_fun, n_grad, n_hv, status, converged, trace_len;
+    int turn;                // whose lines the step uses
     int na, nb;              // places used so far by the results of products with X, by those with X^T
     int pair_at;             // where the pairs lie
     double f, fnew, gnorm, gnorm0, gscaled, delta, rr, tol, beta, length, ww, pred, snorm, pp, pMp, sMp, ss;   // length: of the step along p
@@ -95,9 +97,10 @@ struct CsrSolveArgs {
     double *pairs[kRing], *u[kRing], *point;
     double *w[2], *g[2], *s, *r, *M;
     double *sums;            // 2 x kSums x kMaxResidentGrid, for even and odd steps
+    uint64_t *lines;         // three turns of kSyncFlat lines, one of a workgroup's sums each
     const double *w0;
     double *out;             // null: the host copies
-    int loss, max_outer, max_cg, trace_cap, resume, steps;
+    int loss, max_outer, max_cg, trace_cap, resume, steps, turn;
     double C, eps, xi, blend;
     GridSync sync;
     CsrState *state;
@@ -119,9 +122,9 @@ struct Chunk {
 // lanes that share a row's sum in the plain layout
 __device__ __forceinline__ int lanes_per_row(int nrows)
 {
-    int g = 1;
-    while (g < kWave && nrows * (g * 2) <= kTeam) g *= 2;
-    return g;
+    // the largest power of two up to 64 of which nrows fit into a team
+    const int most = kTeam / (nrows > 1 ? nrows : 1);
+    return most >= kWave ? kWave : most > 1 ? 1 << (31 - __clz(most)) : 1;
 }
 
 template <bool SEG>
@@ -254,7 +257,15 @@ __device__ __forceinline__ void chunk_sums(const ChunkPlan &P, int chunk, int ti
                 }
             }
             double t = 0.0;
-            for (int k = k0 + sub; k < k1; k += g) t += lds[k];
+            int k = k0 + sub;
+            for (; k + 7 * g < k1; k += 8 * g) {   // eight reads on their way at a time
+                double part[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) part[j] = lds[k + j * g];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) t += part[j];
+            }
+            for (; k < k1; k += g) t += lds[k];
             t = group_sum(t, g);
             if (row < nrows && sub == 0) lds[kProdDoubles + row] = t;
         }
@@ -263,6 +274,7 @@ __device__ __forceinline__ void chunk_sums(const ChunkPlan &P, int chunk, int ti
 }
 
 __device__ __forceinline__ void hand_over(uint64_t *place, double v) { __hip_atomic_store(place, (uint64_t)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void clear(uint64_t *place) { __hip_atomic_store(place, kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // One product, and what is done with every row's sum: aux = load(row) is asked for before the sum is known, apply(row, sum, aux)
 // takes it.  h: the workgroup's first chunks, fetched already.  False: given up.
@@ -318,7 +330,7 @@ __device__ __forceinline__ bool product(const ChunkPlan &P, Chunk &h, int how, c
                 // lane k has the pieces k, k + 64, ...; the row's first one goes with the last of lane 0
                 double z = 0.0;
                 bool there = true;
-                for (int k = lane; k <= R.z && there; k += kWave) there = grid.take(P.pieces + (k < R.z ? R.y + k : P.nchunks + l), kNoPiece, z);
+                for (int k = lane; k <= R.z && there; k += kWave) there = grid.take(P.pieces + (k < R.z ? R.y + k : P.nchunks + l), kEmpty, z);
                 if (__ballot(!there) != 0) {
                     if (lane == 0) *bad = 1;
                     break;
@@ -390,6 +402,7 @@ __device__ __forceinline__ void decide(CsrState &S, const CsrSolveArgs &A, const
 {
     const double eta0 = 1e-4, eta1 = 0.25, eta2 = 0.75, sig2 = 0.5, sig3 = 4.0;
     const int step = S.step;
+    S.turn = S.turn == 2 ? 0 : S.turn + 1;
     if (with_x(step)) S.na += 1;
     else if (step != STEP_ZERO_G) {
         S.pair_at = S.nb % kRing;
@@ -539,12 +552,13 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         if (args.resume) S = *args.state;
         else {
             S = CsrState{};
+            S.turn = args.turn;
             S.step = STEP_START;
             S.status = TRON_EMAXITER;
         }
     }
     __syncthreads();
-    const bool precond = A.blend > 0.0, report = blockIdx.x == 0;
+    const bool precond = A.blend > 0.0, report = blockIdx.x == 0, flat = gridDim.x <= kSyncFlat;
     int step = __builtin_amdgcn_readfirstlane(S.step), left = A.steps;
     Chunk h;
     if (with_x(step)) load_chunk<SEGX>(X, first, tid, h);
@@ -561,6 +575,8 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         const int na = __builtin_amdgcn_readfirstlane(S.na), nb = __builtin_amdgcn_readfirstlane(S.nb);
         double v[kSums] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         bool any = false;   // whether this lane had a row
+        const int turn = __builtin_amdgcn_readfirstlane(S.turn);
+        if (flat && threadIdx.x < kSums) clear(A.lines + ((turn == 2 ? 0 : turn + 1) * kSyncFlat + blockIdx.x) * kLine + threadIdx.x);
         if (with_x(step)) {
             const bool cg = step == STEP_CG, lr = A.loss == TRON_LOSS_LR;
             double *u = A.u[na % kRing];
@@ -666,6 +682,9 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         double *sums = A.sums + (left & 1) * kSums * kMaxResidentGrid;
         if (__ballot(any)) wave_sums(v, nsums, &red[0][threadIdx.x / kWave], kMaxTeams * kWavesPerBlock);
         else if ((int)(threadIdx.x & (kWave - 1)) < nsums) red[threadIdx.x & (kWave - 1)][threadIdx.x / kWave] = 0.0;
+        // Up to 64 workgroups need no barrier beside the sums: each waits until those of all are there, a lane for every workgroup.  (The
+        // lines of the next turn were cleared before; all have read what was in them, or they would not have got here.)
+        if (flat) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // what the others read has arrived
         __syncthreads();
         if ((int)threadIdx.x < nsums) {
             double part[kMaxTeams * kWavesPerBlock], t = 0.0;
@@ -674,26 +693,38 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
 #pragma unroll
             for (int k = 0; k < kMaxTeams * kWavesPerBlock; ++k)
                 if (k < (int)blockDim.x / kWave) t += part[k];
-            store_shared(sums + threadIdx.x * kMaxResidentGrid + blockIdx.x, t);
+            if (flat) hand_over(A.lines + (turn * kSyncFlat + blockIdx.x) * kLine + threadIdx.x, t);
+            else store_shared(sums + threadIdx.x * kMaxResidentGrid + blockIdx.x, t);
         }
-        grid.arrive();
+        if (!flat) grid.arrive();
         // most often a product with the other orientation follows
         if (with_x(step)) load_chunk<SEGT>(T, first, tid, h);
         else load_chunk<SEGX>(X, first, tid, h);
-        ok = grid.wait();
-        if (!ok) break;
-        if (used >= kRing && used % kRing == 0 && threadIdx.x < kWave) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the places are used again
-        if (team == 0) {
-            double t[kSums];
-            const bool mine = tid < (int)gridDim.x;
+        if (!flat) {
+            ok = grid.wait();
+            if (!ok) break;
+            if (team == 0) {
+                double t[kSums];
+                const bool mine = tid < (int)gridDim.x;
 #pragma unroll
-            for (int k = 0; k < kSums; ++k) t[k] = (k < nsums && mine) ? load_shared(sums + k * kMaxResidentGrid + tid) : 0.0;
-            wave_sums(t, nsums, &red[0][tid / kWave], kMaxTeams * kWavesPerBlock);
+                for (int k = 0; k < kSums; ++k) t[k] = (k < nsums && mine) ? load_shared(sums + k * kMaxResidentGrid + tid) : 0.0;
+                wave_sums(t, nsums, &red[0][tid / kWave], kMaxTeams * kWavesPerBlock);
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        if (threadIdx.x < kWave) {   // all of the wavefront the same; lane k adds up sum k
-            const double *part = red[(int)threadIdx.x < nsums ? threadIdx.x : 0];
-            const double total = (part[0] + part[1]) + (part[2] + part[3]);
+        if (threadIdx.x < kWave) {   // all of the wavefront the same; lane k has sum k
+            double total;
+            if (flat) {
+                double t[kSums];
+                ok = grid.collect(A.lines + (turn * kSyncFlat + threadIdx.x) * kLine, nsums, kEmpty, t);
+                wave_sums(t, nsums, &red[0][0], kMaxTeams * kWavesPerBlock);
+                total = red[(int)threadIdx.x < nsums ? threadIdx.x : 0][0];
+                if (!ok && threadIdx.x == 0) bad = 1;
+            } else {
+                const double *part = red[(int)threadIdx.x < nsums ? threadIdx.x : 0];
+                total = (part[0] + part[1]) + (part[2] + part[3]);
+            }
+            if (used >= kRing && used % kRing == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the places are used again
             CsrState next = S;
             double t[kSums];
 #pragma unroll
@@ -702,6 +733,8 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
             if (threadIdx.x == 0) S = next;
         }
         __syncthreads();
+        ok = bad == 0;
+        if (!ok) break;
         const bool was_x = with_x(step);
         step = __builtin_amdgcn_readfirstlane(S.step);
         if (step == STEP_DIAG || step == STEP_TRIAL) {   // they gather from D and the trial point, which lie in the same places every time
@@ -738,8 +771,9 @@ struct CsrSolver {
     tron_trace_rec *trace = nullptr;   // device memory, records past the first kHostRecords
     int trace_cap = 0;
     bool lds_set = false;
-    int64_t npieces = 0;
-    bool pieces_clear = false;   // all of them are kNoPiece between solves
+    int64_t to_clear = 0;        // places from args.lines on that are kEmpty between solves,
+    bool cleared = false;        // unless one was given up (or none was made yet); of the lines, those of the turn `turn`
+    int turn = 0;
     ChunkPlan X, T;
     CsrSolveArgs args;
 };
@@ -759,10 +793,10 @@ void csr_resident_release(tron_dataset *ds)
     ds->csr_solver = nullptr;
 }
 
-__global__ __launch_bounds__(kBlock) void k_no_pieces(uint64_t *pieces, int64_t n)
+__global__ __launch_bounds__(kBlock) void k_clear(uint64_t *places, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) pieces[i] = kNoPiece;
+    if (i < n) places[i] = kEmpty;
 }
 
 // Layouts of large matrices (several column ranges, values left out) stay with a launch per product, whose workgroups keep four times
@@ -793,7 +827,7 @@ static int ensure_space(tron_dataset *ds, int trace_cap)
     if (!W.ready) {
         // one allocation each: up to 2 MB they come from memory that the runtime has already, larger ones take it some 300 us
         const int64_t px = ds->fwd.plain || !ds->fwd.nfix ? 0 : ds->fwd.nblocks + ds->fwd.nfix, pt = ds->bwd.plain || !ds->bwd.nfix ? 0 : ds->bwd.nblocks + ds->bwd.nfix;
-        const int64_t psums = 2 * kSums * kMaxResidentGrid, pstate = (sizeof(CsrState) + 7) / 8;
+        const int64_t psums = 2 * kSums * kMaxResidentGrid, pstate = (sizeof(CsrState) + 7) / 8 / kLine * kLine + kLine, lines = 3 * kSyncFlat * kLine;
         auto get = [&](double *&p, int64_t m) -> int {
             TRON_HIP(hipMalloc(reinterpret_cast<void **>(&p), sizeof(double) * m));
             W.blocks[W.nblocks++] = p;
@@ -805,13 +839,14 @@ static int ensure_space(tron_dataset *ds, int trace_cap)
             TRON_TRY(get(A.u[k], ds->n));
         }
         for (double **v : {&A.point, &A.w[0], &A.w[1], &A.g[0], &A.g[1], &A.s, &A.r, &A.M}) TRON_TRY(get(*v, ds->d));
-        TRON_TRY(get(A.sums, psums + pstate + px + pt));
+        TRON_TRY(get(A.sums, psums + pstate + lines + px + pt));
         A.state = reinterpret_cast<CsrState *>(A.sums + psums);
         W.X = chunk_plan(ds->fwd);
         W.T = chunk_plan(ds->bwd);
-        W.X.pieces = reinterpret_cast<uint64_t *>(A.sums + psums + pstate);
+        A.lines = reinterpret_cast<uint64_t *>(A.sums + psums + pstate);
+        W.X.pieces = A.lines + lines;
         W.T.pieces = W.X.pieces + px;
-        W.npieces = px + pt;
+        W.to_clear = lines + px + pt;
         A.n = ds->n;
         A.d = ds->d;
         A.y = ds->y;
@@ -821,12 +856,12 @@ static int ensure_space(tron_dataset *ds, int trace_cap)
         W.host = reinterpret_cast<CsrHost *>(ds->scal_host + kScalars);
         W.host_dev = reinterpret_cast<CsrHost *>(ds->scal_dev + kScalars);
         W.ready = true;
-        W.pieces_clear = false;
+        W.cleared = false;
     }
-    if (W.npieces > 0 && !W.pieces_clear) {
-        hipLaunchKernelGGL(k_no_pieces, dim3((unsigned)((W.npieces + kBlock - 1) / kBlock)), dim3(kBlock), 0, ds->stream, W.X.pieces, W.npieces);
+    if (!W.cleared) {
+        hipLaunchKernelGGL(k_clear, dim3((unsigned)((W.to_clear + kBlock - 1) / kBlock)), dim3(kBlock), 0, ds->stream, A.lines, W.to_clear);
         TRON_HIP(hipGetLastError());
-        W.pieces_clear = true;
+        W.cleared = true;
     }
     if (trace_cap - kHostRecords > W.trace_cap) {
         TRON_HIP(hipFree(W.trace));
@@ -873,6 +908,7 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     A.sync = grid_sync(ds);
     A.host = W.host_dev;
     A.trace = W.trace;
+    A.turn = W.turn;
     A.steps = kStepsPerLaunch;
     ds->have_D = false;
     {
@@ -892,7 +928,7 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
                 (void)hipGetLastError();
                 TRON_HIP(hipStreamSynchronize(ds->stream));
                 if (!ended()) {   // workgroups gave up waiting for others; w0 is as it was
-                    W.pieces_clear = false;
+                    W.cleared = false;
                     return 0;
                 }
             }
@@ -900,6 +936,7 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
         }
     }
     const CsrState &S = W.host->st;
+    W.turn = S.turn;
     if (!A.out) {
         TRON_HIP(hipMemcpyAsync(w_dev, A.w[S.cur], sizeof(double) * ds->d, hipMemcpyDeviceToDevice, ds->stream));
         TRON_HIP(hipStreamSynchronize(ds->stream));

@@ -82,6 +82,33 @@ public:
         return false;
     }
 
+    // A wavefront waits until the first n words of every workgroup's line are no longer `empty` (a lane's own line, at most kWave
+    // workgroups), and has them in v; 0 beyond.  False: given up, like wait().
+    template <int N>
+    __device__ __forceinline__ bool collect(const uint64_t *line, int n, uint64_t empty, double (&v)[N])
+    {
+        const bool mine = (threadIdx.x & (kWave - 1)) < gridDim.x;
+        if (ticks_ >= 0) {
+            const long long from = wall_clock64();
+            for (unsigned polls = 1;; ++polls) {
+                bool there = true;
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    const uint64_t w = (mine && k < n) ? __hip_atomic_load(line + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+                    there &= w != empty;
+                    v[k] = __longlong_as_double((long long)w);
+                }
+                if (__ballot(!there) == 0) return true;
+                if ((polls & 15u) == 0 && (get(given_up()) != 0 || wall_clock64() - from > ticks_)) break;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = 0.0;
+        }
+        if ((threadIdx.x & (kWave - 1)) == 0) put(given_up(), 1u);
+        return false;
+    }
+
     // the last thing a workgroup does, whether it gave up or not
     __device__ __forceinline__ void leave()
     {
