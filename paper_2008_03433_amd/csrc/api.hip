@@ -114,7 +114,8 @@ static int alloc_common(tron_dataset *ds)
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->partials), sizeof(double) * need));
     // The scalars the host steers by live in pinned host memory that the kernels write directly: they are there when
     // the stream has drained, without a copy operation between the last kernel and the host's wait.
-    TRON_HIP(hipHostMalloc(reinterpret_cast<void **>(&ds->scal_host), sizeof(double) * kScalars + (ds->dense ? 0 : kSolveHostBytes), hipHostMallocMapped));
+    TRON_HIP(hipHostMalloc(reinterpret_cast<void **>(&ds->scal_host), sizeof(double) * kHostWords + (ds->dense ? 0 : kSolveHostBytes), hipHostMallocMapped));
+    memset(ds->scal_host, 0, sizeof(double) * kHostWords);
     TRON_HIP(hipHostGetDevicePointer(reinterpret_cast<void **>(&ds->scal_dev), ds->scal_host, 0));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->scal_copy), sizeof(double) * kScalars));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->ticket), 64));
@@ -632,18 +633,17 @@ int tron_fun_grad(tron_dataset *ds, int loss, double C, const double *w_dev, dou
     const int slot = ds->have_D ? 1 - ds->Dcur : ds->Dcur;
     if (ds->dense) {
         TRON_TRY(dense_fun_grad(ds, loss, C, w_dev, slot, g_dev));
-        TRON_TRY(read_scalars(ds, 4));
+        TRON_TRY(wait_results(ds));
         ds->active_frac[slot] = ds->scal_host[3] / (double)ds->n;
         ds->active_count[slot] = (int64_t)ds->scal_host[3];
         *f_host = 0.5 * ds->scal_host[1] + C * ds->scal_host[0];
         // stand-alone calls: the compacted copy of the active rows only when the knob forces it
         if (g_tuning.dense_compact > 0 && dense_compact_wanted(ds, slot, 0)) TRON_TRY(dense_compact_build(ds, slot));
     } else {
-        TRON_TRY(fun_eval(ds, loss, C, w_dev, slot, f_host));
-        if (g_dev) {
-            double gn;
-            TRON_TRY(grad_eval(ds, C, w_dev, g_dev, &gn));
-        }
+        TRON_TRY(fun_enqueue(ds, loss, w_dev, slot, true));
+        if (g_dev) TRON_TRY(grad_enqueue(ds, C, w_dev, g_dev, 2));
+        TRON_TRY(wait_results(ds));
+        *f_host = 0.5 * ds->scal_host[1] + C * ds->scal_host[0];
     }
     ds->Dcur = slot;
     ds->have_D = true;
@@ -659,7 +659,7 @@ int tron_hv(tron_dataset *ds, double C, const double *v_dev, double *Hv_dev, dou
     if (!ds->have_D) { set_error("tron_hv: no cached D; call tron_fun_grad first"); return TRON_ESTATE; }
     TRON_TRY(hv_enqueue(ds, C, v_dev, Hv_dev));
     if (vHv_host) {
-        TRON_TRY(read_scalars(ds, 1));
+        TRON_TRY(wait_results(ds));
         *vHv_host = ds->scal_host[0];
     }
     return TRON_OK;

@@ -884,7 +884,20 @@ int one_shot(tron_batch *b, int what, int loss, const double *C_host, const doub
     TRON_TRY(launch_begin(ds, b->drv, b->K, what, IN, C_host));
     TRON_TRY(launch_pass(b, loss, what == BEGIN_HV));
     TRON_TRY(launch_advance(b, P, ++b->drv.rounds));
-    TRON_HIP(hipStreamSynchronize(ds->stream));
+    // a problem's stamp comes after its results
+    auto arrived = [&]() {
+        for (int k = 0; k < b->K; ++k)
+            if (__atomic_load_n(&b->drv.host->stamp[k], __ATOMIC_ACQUIRE) >> 2 != b->drv.rounds) return false;
+        return true;
+    };
+    for (unsigned spins = 1; !arrived(); ++spins) {
+        if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) {
+            (void)hipGetLastError();
+            TRON_HIP(hipStreamSynchronize(ds->stream));
+            break;
+        }
+        __builtin_ia32_pause();
+    }
     if (scal_host)
         for (int k = 0; k < b->K; ++k) scal_host[k] = b->drv.host->sc[k].out_scal;
     return TRON_OK;

@@ -67,7 +67,8 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxGrid = 2048;       // 256 CUs x 8 resident workgroups: grid-stride kernels use at most this
 constexpr int kChunk = 2048;         // nonzeros per workgroup in the CSR kernels (256 threads x 8)
 constexpr int kScalars = 16;         // scalar slots shared by the reductions
-constexpr int kSolveHostBytes = 3072;   // pinned memory behind the scalars: what a solve in one launch reports
+constexpr int kHostWords = kScalars + 8;   // pinned memory: the scalars, and a word for HostFlag on a line of its own
+constexpr int kSolveHostBytes = 3072;   // behind it: what a solve in one launch reports
 
 // ---------------------------------------------------------------- profiling slots
 enum Slot {
@@ -295,6 +296,8 @@ struct tron_dataset {
     unsigned *ticket = nullptr;  // counter of finished workgroups for reductions completed inside the producing kernel (zero between kernels)
     unsigned *sync_words = nullptr;  // counters of the launches whose workgroups wait for each other (zero between kernels)
     int cus = 0;                 // compute units of the device
+    int64_t flag_value = 0;      // of the HostFlag given out last
+    bool flagged = false;        // the kernel enqueued last has it (see wait_results)
     bool finish_done = false;    // the last producing kernel did: the next reduce_final call is a no-op
     int dense_grid = 0;          // workgroups of the dense kernels
 
@@ -321,6 +324,14 @@ struct tron_dataset {
 
 namespace tron {
 
+// A word of pinned memory that the last kernel of a call writes when everything that the call returns has arrived: the host sees it
+// 5.5 us before its wait for the stream would end.  next_flag: for the kernel that is enqueued last; wait_results: until it has been
+// written, or the stream has drained where the last kernel has none.
+struct HostFlag {
+    int64_t *word;   // null: none
+    int64_t value;
+};
+
 // Where the kernel that produces first-stage partial sums puts the finished sums when it adds them itself (the workgroup
 // that finishes last does it, see finish_partials): scalar slots first, first + 1, ... of both copies.  ticket == null:
 // a separate k_reduce_final launch adds them.
@@ -333,6 +344,8 @@ struct Finish {
 // the launch is small enough for that to pay (then the reduce_final call that follows does nothing), without otherwise or
 // when first_scalar < 0.
 Finish finish_for(tron_dataset *ds, int first_scalar, int grid);
+HostFlag next_flag(tron_dataset *ds);
+int wait_results(tron_dataset *ds);
 
 // Launches whose workgroups wait for each other (grid_sync.h).  resident_possible: whether `grid` workgroups can be resident
 // together, one per compute unit.  ResidentShare: the call's place among those of this process that run on one device at a time; it
@@ -495,7 +508,6 @@ void csr_resident_release(tron_dataset *ds);
 
 // ---- solver.hip
 int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot, bool ww);               // scalars[0]=sum of loss terms, [1]=w.w if ww, no sync
-int fun_eval(tron_dataset *ds, int loss, double C, const double *w, int Dslot, double *f_out);  // syncs
 int grad_enqueue(tron_dataset *ds, double C, const double *w, double *g, int scalar);           // scalars[scalar]=g.g, no sync
 // out = 1 + C sum_i D_i x_ij^2 with D = Dbuf[Dslot] (the diagonal of the Hessian; C scaled by the caller for a blend). Enqueue only.
 int hess_diag_enqueue(tron_dataset *ds, double C, int Dslot, double *out);

@@ -853,8 +853,8 @@ static int ensure_space(tron_dataset *ds, int trace_cap)
         A.D[0] = ds->Dbuf[0];
         A.D[1] = ds->Dbuf[1];
         static_assert(sizeof(CsrHost) <= kSolveHostBytes, "room behind the scalars");
-        W.host = reinterpret_cast<CsrHost *>(ds->scal_host + kScalars);
-        W.host_dev = reinterpret_cast<CsrHost *>(ds->scal_dev + kScalars);
+        W.host = reinterpret_cast<CsrHost *>(ds->scal_host + kHostWords);
+        W.host_dev = reinterpret_cast<CsrHost *>(ds->scal_dev + kHostWords);
         W.ready = true;
         W.cleared = false;
     }

@@ -176,6 +176,15 @@ __device__ __forceinline__ double block_sum(double v, double *lds)
 __device__ __forceinline__ void store_shared(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ double load_shared(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// For the host: a scalar, and the flag behind what this wavefront has stored (called by all of it; its lane 0 writes)
+__device__ __forceinline__ void store_host(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+__device__ __forceinline__ void post_flag(const HostFlag &f)
+{
+    if (!f.word) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if ((threadIdx.x & (kWave - 1)) == 0) __hip_atomic_store(f.word, f.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // True in every thread of the workgroup that draws the last of the launch's tickets.  Called by all threads; the workgroup's
 // sums were stored by wavefront 0.  The counter is the only thing touched by a read-modify-write; the caller clears it.
 __device__ __forceinline__ bool last_workgroup(unsigned *ticket)

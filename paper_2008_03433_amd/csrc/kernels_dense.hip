@@ -41,6 +41,7 @@ struct DenseFinish {
     const double *dotw;    // null: out itself
     double *scal, *scal_copy;
     bool fun_grad;
+    HostFlag flag;         // with scal
 };
 
 // d <= 32 (at most four lanes per row): the last workgroup completes the sums
@@ -58,12 +59,12 @@ constexpr int kColumnsBlock = 1024, kColumnsPer = 16;
 __device__ __forceinline__ void store_dense_scalars(const DenseFinish &fin, double loss, double ww, double cp, double active)
 {
     if (fin.fun_grad) {
-        fin.scal[0] = loss;
-        fin.scal[1] = ww;
-        fin.scal[2] = cp;
-        fin.scal[3] = active;
+        store_host(fin.scal, loss);
+        store_host(fin.scal + 1, ww);
+        store_host(fin.scal + 2, cp);
+        store_host(fin.scal + 3, active);
     } else {
-        fin.scal[0] = cp;
+        store_host(fin.scal, cp);
         fin.scal_copy[0] = cp;
     }
 }
@@ -147,11 +148,12 @@ __device__ __forceinline__ void dense_outputs(const DenseFinish &fin, int d, dou
         const double o = fma(fin.C, sum, add);
         cp = o * (fin.dotw ? fin.dotw[lane] : o);
         ww = add * add;
-        if (fin.out) fin.out[lane] = o;
+        if (fin.out) store_shared(fin.out + lane, o);
     }
     cp = wave_sum(cp);
     ww = wave_sum(ww);
     if (lane == 0 && fin.scal) store_dense_scalars(fin, loss, ww, cp, active);
+    post_flag(fin.flag);
 }
 
 template <int kWaves>
@@ -679,7 +681,7 @@ __global__ __launch_bounds__(kColumnsBlock) void k_dense_columns(int d, int grid
             const double o = fma(fin.C, t, add);
             cp = o * (fin.dotw ? fin.dotw[c] : o);
             ww = add * add;
-            if (fin.out) fin.out[c] = o;
+            if (fin.out) store_shared(fin.out + c, o);   // on its way before the ticket is drawn
         }
         cp = wave_sum(cp);
         ww = wave_sum(ww);
@@ -712,6 +714,7 @@ __global__ __launch_bounds__(kColumnsBlock) void k_dense_columns(int d, int grid
         store_dense_scalars(fin, t[0], t[1], t[2], t[3]);
         *fin.ticket = 0u;
     }
+    if (threadIdx.x < kWave) post_flag(fin.flag);
 }
 
 // ------------------------------------------------------------------ dispatch
@@ -1180,7 +1183,7 @@ int64_t dense_fun_grad_bytes(const tron_dataset *ds)
 int dense_hv(tron_dataset *ds, double C, int Dslot, const double *v, double *Hv)
 {
     const HvInput in = hv_input(ds, Dslot);
-    const DenseFinish fin{ds->ticket, v, C, Hv, v, ds->scal_dev, ds->scal_copy, false};
+    const DenseFinish fin{ds->ticket, v, C, Hv, v, ds->scal_dev, ds->scal_copy, false, next_flag(ds)};
     {
         ProfScope ps(ds, SLOT_DENSE_HV);
         TRON_TRY(dispatch_hv(ds, in, v, ds->partials, fin));
@@ -1193,7 +1196,7 @@ int dense_hv(tron_dataset *ds, double C, int Dslot, const double *v, double *Hv)
 int dense_hess_diag(tron_dataset *ds, double C, int Dslot, double *out)
 {
     const HvInput in = hv_input(ds, Dslot);
-    const DenseFinish fin{ds->ticket, nullptr, C, out, nullptr, nullptr, nullptr, false};
+    const DenseFinish fin{ds->ticket, nullptr, C, out, nullptr, nullptr, nullptr, false, HostFlag{nullptr, 0}};
     {
         ProfScope ps(ds, SLOT_DENSE_HV);
         TRON_TRY(dispatch_hv(ds, in, nullptr, ds->partials, fin));
@@ -1221,7 +1224,7 @@ int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Ds
     double *loss_partials = ds->partials + ds->d * grid;
     double *col_partials = loss_partials + grid;
     double *active_partials = col_partials + ds->d;
-    const DenseFinish fin{ds->ticket, w, C, g, nullptr, ds->scal_dev, ds->scal_copy, true};
+    const DenseFinish fin{ds->ticket, w, C, g, nullptr, ds->scal_dev, ds->scal_copy, true, next_flag(ds)};
     {
         ProfScope ps(ds, SLOT_DENSE_FUN_GRAD);
         TRON_TRY(dispatch_fg(ds, loss, w, Dout, loss_partials, active_partials, fin));
@@ -1293,7 +1296,7 @@ extern "C" int tron_hv_static(tron_dataset *ds, double C, const double *v_dev, d
     // launch of its own, without a counter, for wider rows the pass clears the counter of k_dense_columns first.  (A counter in
     // the pass needs a launch that clears it: 20,003 x 8 then takes 21.1 us a call, this way 19.1.)
     const bool narrow = ds->d <= kFinishMaxD;
-    const DenseFinish fin{narrow ? nullptr : &g_static_work[dev]->ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false};
+    const DenseFinish fin{narrow ? nullptr : &g_static_work[dev]->ticket, v_dev, C, Hv_dev, v_dev, vHv_dev ? vHv_dev : scalar, scalar, false, HostFlag{nullptr, 0}};
     TRON_TRY(dispatch_hv(ds, in, v_dev, partials, fin));
     if (narrow) hipLaunchKernelGGL(k_dense_finish, dim3(1), dim3(kFinishBlock), 0, ds->stream, (int)ds->d, grid, partials, fin);
     TRON_HIP(hipGetLastError());

@@ -10,7 +10,7 @@ namespace tron {
 // scal[first + s] = sum_{b < count} partials[s*stride + b]; scal is the host's copy (mapped pinned memory), scal_copy the
 // device's
 __global__ __launch_bounds__(kBlock) void k_reduce_final(const double *__restrict__ partials, int count, int stride,
-                                                         double *__restrict__ scal, double *__restrict__ scal_copy, int first)
+                                                         double *__restrict__ scal, double *__restrict__ scal_copy, int first, HostFlag flag)
 {
     __shared__ double lds[kWavesPerBlock];
     const int s = blockIdx.x;
@@ -19,9 +19,10 @@ __global__ __launch_bounds__(kBlock) void k_reduce_final(const double *__restric
     for (int b = threadIdx.x; b < count; b += kBlock) acc += p[b];
     acc = block_sum(acc, lds);
     if (threadIdx.x == 0) {
-        scal[first + s] = acc;
+        store_host(scal + first + s, acc);
         scal_copy[first + s] = acc;
     }
+    if (threadIdx.x < kWave) post_flag(flag);   // (the launches before have written what else there is)
 }
 
 // Automatic rule: launches of up to kFuseMaxGrid workgroups complete their own reduction.  The tickets are drawn one after the
@@ -39,12 +40,34 @@ int reduce_final(tron_dataset *ds, int nslots, int count, int stride, int first_
 {
     if (ds->finish_done) {   // the kernel that produced the partial sums has added them already
         ds->finish_done = false;
+        ds->flagged = false;   // other workgroups' results may still be on their way
         return TRON_OK;
     }
     ProfScope ps(ds, SLOT_REDUCE_FINAL);
     hipLaunchKernelGGL(k_reduce_final, dim3(nslots), dim3(kBlock), 0, ds->stream, ds->partials, count, stride,
-                       ds->scal_dev, ds->scal_copy, first_scalar);
+                       ds->scal_dev, ds->scal_copy, first_scalar, nslots == 1 ? next_flag(ds) : HostFlag{nullptr, 0});
     TRON_HIP(hipGetLastError());
+    return TRON_OK;
+}
+
+HostFlag next_flag(tron_dataset *ds)
+{
+    ds->flagged = true;
+    return HostFlag{reinterpret_cast<int64_t *>(ds->scal_dev + kScalars), ++ds->flag_value};
+}
+
+int wait_results(tron_dataset *ds)
+{
+    if (ds->flagged) {
+        const int64_t *word = reinterpret_cast<const int64_t *>(ds->scal_host + kScalars);
+        for (unsigned spins = 1;; ++spins) {
+            if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == ds->flag_value) return TRON_OK;
+            if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
+            __builtin_ia32_pause();
+        }
+        (void)hipGetLastError();
+    }
+    TRON_HIP(hipStreamSynchronize(ds->stream));
     return TRON_OK;
 }
 

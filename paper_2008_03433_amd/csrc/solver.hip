@@ -24,14 +24,6 @@ int fun_enqueue(tron_dataset *ds, int loss, const double *w, int Dslot, bool ww)
     return TRON_OK;
 }
 
-int fun_eval(tron_dataset *ds, int loss, double C, const double *w, int Dslot, double *f_out)
-{
-    TRON_TRY(fun_enqueue(ds, loss, w, Dslot, true));
-    TRON_TRY(read_scalars(ds, 2));
-    *f_out = 0.5 * ds->scal_host[1] + C * ds->scal_host[0];
-    return TRON_OK;
-}
-
 // g = w + C X^T zhat (zhat from the preceding fun_enqueue); scalar `scalar` = g.g
 int grad_enqueue(tron_dataset *ds, double C, const double *w, double *g, int scalar)
 {
