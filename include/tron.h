@@ -221,7 +221,7 @@ typedef struct {
  * On return the handle caches D at the final iterate (so tron_hv may follow).
  * Dense problems with d <= 32 and no preconditioner -- logistic loss: of any size; L2-SVM: matrices up to 1 GB -- are driven
  * from the device, like tron_batch_solve with one problem over all rows: same rules, same results up to summation order
- * (knob "dense_device_driver").  Sparse problems of up to some four million entries (not partitioned by columns, up to 2048 chunks
+ * (knob "dense_device_driver").  Sparse problems of up to some five million entries (not partitioned by columns, up to 2560 chunks
  * of 2048 entries in either orientation) are solved in one launch, unless the profiler is on: same rules, same results up to
  * summation order (knob "solve_resident").
  */

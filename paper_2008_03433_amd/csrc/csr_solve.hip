@@ -17,7 +17,7 @@
 // sums and stores 1.5, long rows 2, the barrier 1.5 to 2.5, sums over the grid and the next decision 1.5.  Two chunks of 256 threads a
 // workgroup leave 256 registers a thread, which the fetched chunk, the row's vectors and nine sums fill; three chunks (168 registers)
 // are no faster although 513 chunks then need no second round, four spill.  us a solve, driven by the host / here: 100,000 entries
-// 220 / 123, 8,000 x 20,000 with 640,000 entries 300 / 197, 1.05M with Zipf-distributed columns 950 / 860, 3.4M 2345 / 2200.
+// 220 / 115, 8,000 x 20,000 with 640,000 entries 300 / 197, 1.05M with Zipf-distributed columns 950 / 860, 3.4M 2345 / 2200.
 #include <cmath>
 #include <new>
 
@@ -367,6 +367,13 @@ __device__ __forceinline__ void own_rows(const ChunkPlan &P, int tid, const F &f
 }
 
 // ------------------------------------------------------------------ what follows from the sums of a step (one thread of every workgroup)
+__device__ __forceinline__ void finish(CsrState &S, int status)
+{
+    S.status = status;
+    S.converged = status == TRON_OK;
+    S.step = STEP_END;
+}
+
 // zz: z.z at the start, z = -g / M
 __device__ __forceinline__ void begin_cg(CsrState &S, const CsrSolveArgs &A, double zz)
 {
@@ -378,13 +385,7 @@ __device__ __forceinline__ void begin_cg(CsrState &S, const CsrSolveArgs &A, dou
     S.onb = 0;
     S.beta = 0.0;
     S.step = STEP_CG;
-}
-
-__device__ __forceinline__ void finish(CsrState &S, int status)
-{
-    S.status = status;
-    S.converged = status == TRON_OK;
-    S.step = STEP_END;
+    if (sqrt(S.rr) <= S.tol) finish(S, TRON_EMAXITER);   // r.z has underflowed: no step to take
 }
 
 __device__ __forceinline__ void started(CsrState &S, const CsrSolveArgs &A)
@@ -800,10 +801,11 @@ __global__ __launch_bounds__(kBlock) void k_clear(uint64_t *places, int64_t n)
 }
 
 // Layouts of large matrices (several column ranges, values left out) stay with a launch per product, whose workgroups keep four times
-// as many wavefronts on a compute unit: from four rounds of chunks on there is little to gain (a CG iteration of 3.4M entries 68 us
-// against 72, of 1.05M 27 against 34, of 100,000 12 against 25).  So do rows longer than a chunk among the plain layout's, which a launch
-// of their own completes, and chunks of so many rows that the threads would go over them one after the other.
-constexpr int kMaxRounds = 4;
+// as many wavefronts on a compute unit: the more rounds of chunks, the less there is to gain.  us a solve, driven by the host / in one
+// launch: five rounds (3.4M entries) 2345 / 2200, three (2M) 1720 / 1525, two (1M) 950 / 860, less than one 220 / 115.  Rows longer than a
+// chunk among the plain layout's, which a launch of their own completes, and chunks of so many rows that the threads would go over
+// them one after the other are left to the host, too.
+constexpr int kMaxRounds = 5;
 
 static bool plan_fits(const CsrPlan &A)
 {
@@ -892,7 +894,11 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     const int teams = std::min(kMaxTeams, (most + grid - 1) / grid);
     if (most > kMaxRounds * grid * teams || !resident_possible(ds, grid)) return 0;
     const int cap = std::min(res->trace_cap, Q.max_outer);
-    TRON_TRY(ensure_space(ds, cap));
+    if (ensure_space(ds, cap) != TRON_OK) {   // no room beside the matrix: the host-driven solve needs less
+        (void)hipGetLastError();
+        csr_resident_release(ds);
+        return 0;
+    }
     CsrSolver &W = *ds->csr_solver;
     CsrSolveArgs A = W.args;
     A.w0 = w_dev;
