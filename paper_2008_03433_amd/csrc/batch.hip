@@ -891,7 +891,7 @@ int one_shot(tron_batch *b, int what, int loss, const double *C_host, const doub
         return true;
     };
     for (unsigned spins = 1; !arrived(); ++spins) {
-        if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) {
+        if ((spins & kSpinsPerQuery) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) {
             (void)hipGetLastError();
             TRON_HIP(hipStreamSynchronize(ds->stream));
             break;
@@ -1173,7 +1173,7 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
         // With the stamp everything is there that the call returns; the stream's own wait would take some microseconds more.
         auto ended = [&]() { return __atomic_load_n(&drv.host->finished, __ATOMIC_ACQUIRE) != 0; };
         for (unsigned spins = 1; !ended(); ++spins) {
-            if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
+            if ((spins & kSpinsPerQuery) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
             __builtin_ia32_pause();
         }
         if (!ended()) {

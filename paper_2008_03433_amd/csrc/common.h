@@ -344,6 +344,8 @@ struct Finish {
 // the launch is small enough for that to pay (then the reduce_final call that follows does nothing), without otherwise or
 // when first_scalar < 0.
 Finish finish_for(tron_dataset *ds, int first_scalar, int grid);
+// A host that waits for such a word asks every 65,536 looks (a millisecond or two) whether the stream has drained instead.
+constexpr unsigned kSpinsPerQuery = 0xffffu;
 HostFlag next_flag(tron_dataset *ds);
 int wait_results(tron_dataset *ds);
 

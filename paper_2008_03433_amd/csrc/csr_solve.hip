@@ -927,7 +927,7 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
             // With the stamp everything is there that the call returns (the stream's own wait takes some microseconds more)
             auto ended = [&]() { return __atomic_load_n(&W.host->stamp, __ATOMIC_ACQUIRE) == stamp; };
             for (unsigned spins = 1; !ended(); ++spins) {
-                if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
+                if ((spins & kSpinsPerQuery) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
                 __builtin_ia32_pause();
             }
             if (!ended()) {

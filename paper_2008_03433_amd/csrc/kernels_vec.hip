@@ -62,7 +62,7 @@ int wait_results(tron_dataset *ds)
         const int64_t *word = reinterpret_cast<const int64_t *>(ds->scal_host + kScalars);
         for (unsigned spins = 1;; ++spins) {
             if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == ds->flag_value) return TRON_OK;
-            if ((spins & 1023u) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
+            if ((spins & kSpinsPerQuery) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
             __builtin_ia32_pause();
         }
         (void)hipGetLastError();
