@@ -154,7 +154,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
                     if (!mine) { alpha = LossTerm{0.0, 0.0}; zhat = 0.0; Di = 0.0; }
                     LossSum<LOSS> losses{lloss[wv][k][lane], svm ? 0.0 : lprod[svm ? 0 : wv][k][lane]};
                     losses.add(alpha);
-                    if ((it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) losses.scale();
                     lloss[wv][k][lane] = losses.lin;
                     if (!svm) lprod[wv][k][lane] = losses.p;
                     if (svm) {
@@ -169,6 +168,18 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
                 for (int u = 0; u < U; ++u) {
 #pragma unroll
                     for (int e = 0; e < E; ++e) acc[k][e] = fma(c[u], x[u][e], acc[k][e]);
+                }
+            }
+        }
+        if constexpr (!svm) {
+            // by the number of the tile, whichever problems have rows in it: none of them adds more than once a tile
+            if (any_fg && (it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) {
+#pragma unroll
+                for (int k = 0; k < KT; ++k) {
+                    LossSum<LOSS> losses{lloss[wv][k][lane], lprod[wv][k][lane]};
+                    losses.scale();
+                    lloss[wv][k][lane] = losses.lin;
+                    lprod[wv][k][lane] = losses.p;
                 }
             }
         }

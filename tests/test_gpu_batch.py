@@ -119,6 +119,37 @@ def test_batch_pass_with_few_or_many_workgroups(rng, grid):
         tron.tron_tuning_set("batch_grid", 0)
 
 
+@pytest.mark.parametrize("K", [1, 4])
+def test_logistic_losses_of_thousands_of_rows_a_lane(rng, K):
+    """A lane's losses are kept as a product that is scaled every so often (LossSum); at w = 0 every row doubles it.  Four wavefronts of
+    1600 tiles each, 1024 of which would overflow it: problem 0 has rows in all tiles but every 256th, where a scaling by the number of the tile would
+    fall, the others in all.  Bound: two roundings an addition relative to the product, 1600 x 2^-52 / (1600 ln 2), and the sum over 256 lanes."""
+    tron.tron_tuning_set("batch_grid", 1)
+    try:
+        tiles, d = 4 * 1600, 2
+        n = 64 * tiles
+        X = rng.standard_normal((n, d))
+        y = np.where(rng.random(n) < 0.5, 1.0, -1.0)
+        member = np.full(n, (1 << K) - 1, dtype=np.uint32)
+        member[(np.arange(n) // 64) % 1600 % 256 == 255] &= ~np.uint32(1)
+        ds = tron.Dataset.from_dense(X, y)
+        b = tron.Batch(ds, K, member)
+        try:
+            for W in (np.zeros((K, d)), 0.2 * rng.standard_normal((K, d))):
+                G = torch_mod().empty(K, d, dtype=torch_mod().float64, device="cuda")
+                f = b.fun_grad(LOSS_LR, [1.0] * K, dev(W), G)
+                for k in range(K):
+                    rows = _rows(member, k)
+                    t = y[rows] * (X[rows] @ W[k])
+                    assert_scalar_close(f[k], 0.5 * W[k] @ W[k] + np.sum(np.logaddexp(0.0, -t)), rel=1e-13, what=f"f[{k}]")
+                    assert_vec_close(G[k].cpu().numpy(), W[k] - X[rows].T @ (y[rows] / (1.0 + np.exp(t))), what=f"g[{k}]")
+        finally:
+            b.close()
+            ds.close()
+    finally:
+        tron.tron_tuning_set("batch_grid", 0)
+
+
 @pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
 def test_batch_membership_patterns(rng, loss):
     """Empty problems, a problem over everything, long runs of rows that nobody needs, rows used by one problem only."""
