@@ -109,9 +109,13 @@ public:
         return false;
     }
 
-    // the last thing a workgroup does, whether it gave up or not
+    // the last thing a workgroup does, whether it gave up or not.  Every wavefront's additions and stores to the words have arrived before the
+    // workgroup counts itself out: one still on its way (an addition whose result nobody waited for, given_up from take()) would
+    // otherwise land behind the clearing and let the next launch's first barrier pass too early.
     __device__ __forceinline__ void leave()
     {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
         if (threadIdx.x == 0 && add(left()) == gridDim.x - 1)
             for (int k = 0; k < kSyncWords / kSyncLine; ++k) put(w_ + k * kSyncLine, 0u);
     }

@@ -81,6 +81,23 @@ def test_solves_of_several_threads_on_streams_of_their_own(rng):
     assert together == alone
 
 
+# one counter (up to 64 workgroups of 512 rows) and eight groups with one each
+@pytest.mark.parametrize("n", [20_000, 120_000])
+def test_a_launch_behind_one_that_was_given_up_finds_the_counters_at_zero(knob, n):
+    torch = torch_mod()
+    ds = tron.Dataset.from_problem(_dense(np.random.default_rng(n), n, 24))
+    w0 = torch.zeros(24, dtype=torch.float64, device="cuda")
+    try:
+        one = _solve(ds, LOSS_L2SVM, 0.3, w0)
+        for _ in range(40):
+            knob("solve_wait_us", 0)
+            assert _solve(ds, LOSS_L2SVM, 0.3, w0) == one
+            knob("solve_wait_us", -1)
+            assert _solve(ds, LOSS_L2SVM, 0.3, w0) == one
+    finally:
+        ds.close()
+
+
 # ------------------------------------------------------------------ sparse
 def _sparse(rng, n, d, mean, common=(), long_rows=(), zipf=0.0):
     """Rows of about `mean` entries; columns `common` are in every row, the rows `long_rows` have two thirds of all columns, every
