@@ -26,7 +26,11 @@
  *     never retained after the call returns.  "host pointer" = ordinary host memory.
  *   - All GPU work is enqueued on the hipStream_t given at dataset creation (pass the
  *     stream as void*; NULL = the default stream).  A call that returns a host scalar
- *     synchronises that stream before returning; one that does not, does not.
+ *     ("synchronises") returns when all work enqueued on that stream before it has ended and
+ *     its own results have arrived: what it returns, and the D that it leaves in the handle, can
+ *     be read from any stream.  Its last kernel may still be ending, so that a query of the
+ *     stream can find it busy for some microseconds more.  A call that returns no host scalar
+ *     only enqueues.
  *   - A handle is not thread-safe; distinct handles are independent.
  *   - All arithmetic is fp64.  Reductions are two-stage and atomic-free, so repeated
  *     calls with the same inputs return bit-identical results.

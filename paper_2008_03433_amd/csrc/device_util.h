@@ -173,15 +173,19 @@ __device__ __forceinline__ double block_sum(double v, double *lds)
 // them waits for the stores before it draws the ticket; the reader uses loads of device scope.  A fence of device scope
 // (__threadfence) would do as well, but it writes back the XCD's whole L2 for every workgroup: a pass over 1M x 24 rows by 512
 // workgroups took 59 us that way, by 2048 workgroups 119 us.
-__device__ __forceinline__ void store_shared(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ void store_shared(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ double load_shared(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// this wavefront's stores have arrived where they go to
+__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // For the host: a scalar, and the flag behind what this wavefront has stored (called by all of it; its lane 0 writes)
 __device__ __forceinline__ void store_host(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
 __device__ __forceinline__ void post_flag(const HostFlag &f)
 {
     if (!f.word) return;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    stores_arrived();
     if ((threadIdx.x & (kWave - 1)) == 0) __hip_atomic_store(f.word, f.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
@@ -191,7 +195,7 @@ __device__ __forceinline__ bool last_workgroup(unsigned *ticket)
 {
     __shared__ int is_last;
     if (threadIdx.x < kWave) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores of this wavefront have arrived
+        stores_arrived();
         if (threadIdx.x == 0) is_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     }
     __syncthreads();

@@ -196,6 +196,16 @@ struct TileWalk {
     }
 };
 
+// D has arrived when the call that computes it returns, which is some microseconds before the kernel ends that gives the word for
+// it: a captured tron_hv_static may be replayed on another stream from then on.  (Rows of more than four lanes: the word comes from the
+// kernel after the pass.  With these stores 200,003 x 257 would take 340 us instead of 336.)
+template <int L, typename T>
+__device__ __forceinline__ void store_D(T *p, T v)
+{
+    if constexpr (dense_finishes(L)) store_shared(p, v);
+    else *p = v;
+}
+
 // ------------------------------------------------------------------ Hessian-vector pass
 // MASK: D is the active set of the L2-SVM (D_ii = 2 on it, else 0) instead of an fp64 value per row: one bit per row,
 // a 64-bit word per wave tile, when a tile has 64 rows (d <= 32); one byte per row otherwise.
@@ -350,12 +360,12 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
             const uint64_t bits = T::ballot_rows(Di != 0.0, lane);
             if (lane == (it & (kWave - 1))) { held_bits = bits; held_tile = tile; }
             if ((it & (kWave - 1)) == kWave - 1) {
-                Dbits[held_tile] = held_bits;   // every lane holds one: 64 consecutive words
+                store_shared(Dbits + held_tile, held_bits);   // every lane holds one: 64 consecutive words
                 held_tile = -1;
             }
         } else if (mine) {
-            if (LOSS == TRON_LOSS_L2SVM) Dmask[row0 + own] = (Di != 0.0) ? 1 : 0;
-            else Dout[row0 + own] = Di;
+            if (LOSS == TRON_LOSS_L2SVM) store_D<L>(Dmask + row0 + own, (uint8_t)(Di != 0.0 ? 1 : 0));
+            else store_D<L>(Dout + row0 + own, Di);
         }
         if ((it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) losses.scale();
         T::from_row_owner(zhat, c);
@@ -365,7 +375,8 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
             for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[u][e], acc[e]);
         }
     }
-    if (kBits && held_tile >= 0) Dbits[held_tile] = held_bits;
+    if (kBits && held_tile >= 0) store_shared(Dbits + held_tile, held_bits);
+    if (dense_finishes(L)) stores_arrived();   // before the workgroup's ticket: the host goes on when the last one has been drawn
     const double loss_acc = wave_sum(losses.value());
     active_acc = wave_sum(active_acc);
     if (lane == 0) {
@@ -463,9 +474,9 @@ struct OneTile {
             coef = in ? zhat : 0.0;
             if (svm) {
                 const uint64_t word = T::ballot_rows(Di != 0.0, lane);
-                if (lane == 0 && __ballot(in) != 0) static_cast<uint64_t *>(Dv)[tile] = word;
+                if (lane == 0 && __ballot(in) != 0) store_shared(static_cast<uint64_t *>(Dv) + tile, word);
             } else if (in && T::first_owner(lane)) {
-                static_cast<double *>(Dv)[tile * T::RT + T::own_row(lane)] = Di;
+                store_shared(static_cast<double *>(Dv) + tile * T::RT + T::own_row(lane), Di);
             }
             Dreg[0] = slot ? Dreg[0] : Di;
             Dreg[1] = slot ? Di : Dreg[1];
@@ -535,7 +546,7 @@ __device__ __forceinline__ void svm_solve_pass(double *lds, double (*lds_red)[de
             const uint64_t word = T::ballot_rows(in && Di != 0.0, lane);
             if (lane == (it & (kWave - 1))) { held_bits = word; held_tile = tile; }
             if ((it & (kWave - 1)) == kWave - 1) {
-                Dbits[held_tile] = held_bits;   // every lane holds one: 64 consecutive words
+                store_shared(Dbits + held_tile, held_bits);   // every lane holds one: 64 consecutive words
                 held_tile = -1;
             }
             T::from_row_owner(in ? zhat : 0.0, c);
@@ -548,7 +559,8 @@ __device__ __forceinline__ void svm_solve_pass(double *lds, double (*lds_red)[de
             for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[u][e], acc[e]);
         }
     }
-    if (held_tile >= 0) Dbits[held_tile] = held_bits;
+    if (held_tile >= 0) store_shared(Dbits + held_tile, held_bits);
+    stores_arrived();
     const double loss_acc = wave_sum(losses.value());
     if (lane == 0) lds_red[0][wv] = loss_acc;
     T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);

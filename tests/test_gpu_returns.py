@@ -96,3 +96,64 @@ def test_batch_calls_behind_one_another(rng, n):
     finally:
         batch.close()
         ds.close()
+
+
+# the active set as a bit a row and fp64 D; rows in registers, one tile at a time, several (few columns), a launch per round
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("n,d", [(20_000, 24), (400_003, 24), (400_003, 3)])
+def test_D_is_there_for_a_captured_product_on_another_stream(loss, n, d):
+    """A captured tron_hv_static, replayed on another stream as soon as a call has returned that replaced the D it reads."""
+    torch = torch_mod()
+    rng = np.random.default_rng(n + d)
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(own):
+        ds = tron.Dataset.from_problem(_dense(rng, n, d))
+    points = [torch.from_numpy(s * rng.standard_normal(d)).cuda() for s in (0.1, 0.3, 1.0)]
+    v, out = torch.from_numpy(rng.standard_normal(d)).cuda(), torch.empty(d, dtype=torch.float64, device="cuda")
+    w = torch.zeros_like(v)
+
+    def at(k):   # twice: D goes to the handle's two buffers in turn, and the product reads one of them
+        ds.fun_grad(loss, 0.5, points[k - 1])
+        ds.fun_grad(loss, 0.5, points[k])
+
+    def solved(resident):
+        tron.tron_tuning_set("solve_resident", resident)
+        w.zero_()
+        torch.cuda.synchronize()
+        ds.solve(loss, 0.5, 1e-3, w, max_outer=1)
+        tron.tron_tuning_set("solve_resident", -1)
+
+    def product():
+        out.zero_()
+        torch.cuda.synchronize()
+        ds.hv_static(0.5, v, out)
+        torch.cuda.synchronize()
+        return out.cpu().numpy()
+
+    try:
+        for calls in ([lambda k=k: at(k) for k in range(3)], [lambda: solved(-1), lambda: solved(0)]):
+            calls[0]()
+            product()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=own):
+                ds.hv_static(0.5, v, out)
+            expected = []
+            for call in calls:
+                at(0)
+                call()
+                eager = product()
+                graph.replay()
+                torch.cuda.synchronize()
+                expected.append(out.cpu().numpy())   # (the captured call keeps its grid and its rule for rows outside the active set)
+                assert np.linalg.norm(expected[-1] - eager) <= 1e-12 * np.linalg.norm(eager)
+            for k in range(30):
+                at((k + 1) % 3)
+                torch.cuda.synchronize()
+                calls[k % len(calls)]()
+                with torch.cuda.stream(other):
+                    graph.replay()
+                torch.cuda.synchronize()
+                np.testing.assert_array_equal(out.cpu().numpy(), expected[k % len(calls)])
+    finally:
+        torch.cuda.synchronize()
+        ds.close()
