@@ -617,6 +617,8 @@ int tron_dataset_stat(const tron_dataset *ds, const char *name, int64_t *value)
         {"dense_grid", ds->dense ? dense_work_units(ds->n, ds->d) : 0},
         {"dense_compact_rows", (ds->dense && ds->have_D && ds->hat_slot == ds->Dcur) ? ds->hat_rows : 0},
         {"unit_values", (!ds->dense && ds->fwd.unit) ? 1 : 0},
+        {"solves_in_one_launch", ds->resident.done},
+        {"solves_given_up", ds->resident.given_up},
     };
     for (auto &e : tab)
         if (strcmp(e.k, name) == 0) { *value = e.v; return TRON_OK; }

@@ -264,7 +264,16 @@ struct CsrPlan {
 }  // namespace tron
 
 // ---------------------------------------------------------------- the handle
-namespace tron { struct DriverState; struct SolveParams; struct CsrSolver; }
+namespace tron {
+struct DriverState;
+struct SolveParams;
+struct CsrSolver;
+
+// Of a handle's solves in one launch (grid_sync.h): how many have ended that way, and in how many workgroups gave up waiting
+struct ResidentRecord {
+    int64_t done = 0, given_up = 0;
+};
+}  // namespace tron
 struct tron_dataset {
     int64_t n = 0, d = 0;
     bool dense = false;
@@ -314,6 +323,7 @@ struct tron_dataset {
 
     tron::DriverState *driver = nullptr;   // dense: solves driven from the device
     tron::CsrSolver *csr_solver = nullptr;   // sparse: work space of solves in one launch
+    tron::ResidentRecord resident;           // what became of the solves in one launch
 
     // solver vectors (d each), allocated on first tron_solve
     double *sv[9] = {nullptr};

@@ -29,6 +29,11 @@ def _dense(rng, n, d):
     return DenseProblem("resident", n, d, X, y)
 
 
+def _ways(ds):
+    """Solves of the handle that ran as one launch, and those that gave that up."""
+    return tuple(tron.tron_dataset_stat(ds.handle, name) for name in ("solves_in_one_launch", "solves_given_up"))
+
+
 def _solve(ds, loss, C, w0, **kw):
     w = w0.clone()
     r = ds.solve(loss, C, 1e-4, w, **kw)
@@ -45,15 +50,20 @@ def test_dense_solve_in_one_launch_has_the_bits_of_a_launch_per_round(rng, knob,
     w0 = torch.zeros(d, dtype=torch.float64, device="cuda")
     try:
         for start in (w0, w0 + 0.1):
+            before = np.array(_ways(ds))
             one = _solve(ds, loss, 0.3, start)
             assert _solve(ds, loss, 0.3, start) == one
+            assert tuple(_ways(ds) - before) == (2, 0)
             knob("solve_wait_us", 0)    # every workgroup gives up at once, the solve starts again with a launch per round
             assert _solve(ds, loss, 0.3, start) == one
+            assert tuple(_ways(ds) - before) == (2, 1)
             knob("solve_wait_us", -1)
             knob("solve_resident", 0)
             assert _solve(ds, loss, 0.3, start) == one
+            assert tuple(_ways(ds) - before) == (2, 1)
             knob("solve_resident", -1)
             assert _solve(ds, loss, 0.3, start) == one
+            assert tuple(_ways(ds) - before) == (3, 1)
     finally:
         ds.close()
 
@@ -68,7 +78,7 @@ def test_solves_of_several_threads_on_streams_of_their_own(rng):
         with torch.cuda.stream(torch.cuda.Stream()):
             ds = tron.Dataset.from_problem(problems[k])
             w0 = torch.zeros(24, dtype=torch.float64, device="cuda")
-            out[k] = [_solve(ds, LOSS_L2SVM, 0.3, w0) for _ in range(5)]
+            out[k] = [_solve(ds, LOSS_L2SVM, 0.3, w0) for _ in range(5)], _ways(ds)
             ds.close()
 
     for k in range(len(problems)):
@@ -94,6 +104,7 @@ def test_a_launch_behind_one_that_was_given_up_finds_the_counters_at_zero(knob, 
             assert _solve(ds, LOSS_L2SVM, 0.3, w0) == one
             knob("solve_wait_us", -1)
             assert _solve(ds, LOSS_L2SVM, 0.3, w0) == one
+        assert _ways(ds) == (41, 40)
     finally:
         ds.close()
 
@@ -154,8 +165,31 @@ def _same_solve(a, b, rel):
 @pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
 @pytest.mark.parametrize("name", SPARSE)
 def test_sparse_solve_in_one_launch_follows_the_solve_driven_by_the_host(rng, knob, loss, name):
+    _follows_the_host(rng, knob, loss, _sparse(rng, **SPARSE[name]), None)
+
+
+# Shapes that must take the one launch, whatever ran before (their inputs are their own): both orientations plain, one or both as segments
+# (forced, where a chunk of long rows alone would stay plain), two and three rounds of chunks (more than 512 and 1024 of them).  The
+# shapes above take it or leave it, as their rows fall: "rounds" and "wide" have too many empty columns in a chunk.
+ONE_LAUNCH = {
+    "tiny": dict(n=9, d=13, mean=3), "plain": dict(n=3000, d=2500, mean=9), "columns": dict(n=6000, d=3000, mean=12, common=(5, 1700), zipf=1.05),
+    "rows": dict(n=300, d=9000, mean=60, long_rows=(0, 17, 18, 299)), "both": dict(n=5000, d=5000, mean=10, common=(0, 2600), long_rows=(3, 4000)),
+    "two rounds": dict(n=30_000, d=12_000, mean=50), "three rounds": dict(n=60_000, d=16_000, mean=50, long_rows=(3, 40_000)),
+}
+
+
+@pytest.mark.parametrize("loss", [LOSS_LR, LOSS_L2SVM])
+@pytest.mark.parametrize("name", ONE_LAUNCH)
+def test_sparse_solve_takes_the_one_launch(knob, loss, name):
+    rng = np.random.default_rng(len(name))
+    if name in ("rows", "three rounds"):
+        knob("csr_segmented", 1)
+    _follows_the_host(rng, knob, loss, _sparse(rng, **ONE_LAUNCH[name]), True)
+
+
+def _follows_the_host(rng, knob, loss, q, one_launch):
+    """one_launch: whether the solves are known to take it (None: either way)."""
     torch = torch_mod()
-    q = _sparse(rng, **SPARSE[name])
     ds = tron.Dataset.from_problem(q)
     zero = torch.zeros(q.d, dtype=torch.float64, device="cuda")
     far = torch.from_numpy(3.0 * rng.standard_normal(q.d)).cuda()
@@ -173,16 +207,21 @@ def test_sparse_solve_in_one_launch_follows_the_solve_driven_by_the_host(rng, kn
                 ds.hv(C, far, hv)   # with the D that the solve leaves
                 return w.cpu().numpy().tobytes(), r.f, r.gnorm, r.outer_iters, r.cg_iters_total, r.status, r.trace, hv.cpu().numpy()
 
+            before = np.array(_ways(ds))
             one = solve()
+            here = tron.tron_dataset_stat(ds.handle, "solves_in_one_launch") - before[0]
+            assert here == 1 or not one_launch
             again = solve()
             assert one[:7] == again[:7]
             knob("solve_wait_us", 0)    # every workgroup gives up at once, the host drives the solve
             given_up = solve()
             knob("solve_wait_us", -1)
+            assert tuple(_ways(ds) - before) == (2 * here, here)
             assert solve()[:7] == one[:7]
             knob("solve_resident", 0)
             host = solve()
             knob("solve_resident", -1)
+            assert tuple(_ways(ds) - before) == (3 * here, here)
             assert given_up[:7] == host[:7]
             _same_solve(one, host, 5e-9)
             assert np.linalg.norm(one[7] - host[7]) <= 1e-7 * np.linalg.norm(host[7])
@@ -203,6 +242,7 @@ def test_sparse_solve_of_many_steps_goes_on_in_further_launches(rng, knob):
                 return ds.solve(LOSS_LR, 1e3, 1e-7, w, **kw), w
 
             one, w = solve()
+            assert _ways(ds) == (1 if "cg_xi" in kw else 2, 0)
             knob("solve_resident", 0)
             host, v = solve()
             knob("solve_resident", -1)
@@ -226,7 +266,7 @@ def test_sparse_solves_of_several_threads_on_streams_of_their_own(rng):
         with torch.cuda.stream(torch.cuda.Stream()):
             ds = tron.Dataset.from_problem(problems[k])
             w0 = torch.zeros(problems[k].d, dtype=torch.float64, device="cuda")
-            out[k] = [_solve(ds, LOSS_LR, 0.3, w0) for _ in range(5)]
+            out[k] = [_solve(ds, LOSS_LR, 0.3, w0) for _ in range(5)], _ways(ds)
             ds.close()
 
     for k in range(len(problems)):
