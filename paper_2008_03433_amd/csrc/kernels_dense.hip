@@ -72,7 +72,8 @@ __device__ __forceinline__ void store_dense_scalars(const DenseFinish &fin, doub
 // One workgroup adds the rows of partial sums of `grid` workgroups, d <= 32: thread t the elements t, t + T, ... of the
 // d x grid array, T a multiple of d, so all of them belong to column t % d; then over the threads of a column in LDS (col_sum:
 // a double per thread; its earlier contents have been read by wavefront 0 only).  True in wavefront 0: lane c < d then has
-// column c's sum, every lane the loss sum and the number of active rows (zero without loss_partials).
+// column c's sum, every lane the loss sum and the number of active rows (zero without loss_partials; the latter
+// also without active_partials).
 template <int kWaves>
 __device__ __forceinline__ bool dense_add_rows(double *col_sum, int grid, int d, const double *partials, const double *loss_partials,
                                                const double *active_partials, double &col, double &loss, double &active)
@@ -95,7 +96,7 @@ __device__ __forceinline__ bool dense_add_rows(double *col_sum, int grid, int d,
     if (loss_partials) {
         for (int b = t; b < grid; b += kThreads) {
             a += load_shared(loss_partials + b);
-            e += load_shared(active_partials + b);
+            if (active_partials) e += load_shared(active_partials + b);
         }
         a = wave_sum(a);
         e = wave_sum(e);
@@ -384,7 +385,7 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
         lds_red[1][wv] = active_acc;
     }
     T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
-    if (threadIdx.x < 2) {
+    if (threadIdx.x < (active_partials ? 2 : 1)) {   // (a solve does not count them)
         double t = 0.0;
 #pragma unroll
         for (int k = 0; k < kWaves; ++k) t += lds_red[threadIdx.x][k];
@@ -422,7 +423,7 @@ struct SolveArgs {
     const double *X;
     const int8_t *y;
     void *D[2];
-    double *partials, *loss_partials, *active_partials;
+    double *partials, *loss_partials;
     int64_t round_stride;   // doubles between the partial sums of even and odd rounds (a workgroup may be one round ahead)
     unsigned *ticket;
     GridSync sync;
@@ -617,10 +618,10 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
         void *D = __builtin_amdgcn_readfirstlane(ctl.dslot[0]) ? A.D[1] : A.D[0];
         const double *vec = ctl.vec[0];
         const int64_t at = (round & 1) * A.round_stride;
-        double *partials = A.partials + at, *loss_partials = A.loss_partials + at, *active_partials = A.active_partials + at;
+        double *partials = A.partials + at, *loss_partials = A.loss_partials + at;
         if constexpr (ONE) mine.pass(lds, lds_red, mode == MODE_FG, ctl.dslot[0], d, vec, D, partials, loss_partials);
         else if constexpr (kAhead) svm_solve_pass<E, L, U, VEC>(lds, lds_red, mode == MODE_FG, n, d, X, A.y, vec, static_cast<uint64_t *>(D), partials, loss_partials, mine.x, whole);
-        else if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, A.y, vec, D, partials, loss_partials, active_partials);
+        else if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, A.y, vec, D, partials, loss_partials, nullptr);
         else hv_pass<E, L, U, VEC, svm, false, svm, true>(lds, n, d, X, D, vec, partials);
         if (whole) {
             grid.arrive();
@@ -630,7 +631,8 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
             return;
         }
         double col, loss, active;
-        if (dense_add_rows<kWaves>(lds, (int)gridDim.x, (int)d, partials, mode == MODE_FG ? loss_partials : nullptr, active_partials, col, loss, active))
+        // (the rows with D != 0 are not counted here)
+        if (dense_add_rows<kWaves>(lds, (int)gridDim.x, (int)d, partials, mode == MODE_FG ? loss_partials : nullptr, nullptr, col, loss, active))
             advance_problem(0, mode, d, col, loss, &ctl, &st, P, A.trace, whole ? nullptr : A.host, stamp);
         __syncthreads();
         if (!whole) {
@@ -1229,7 +1231,7 @@ int dense_solve_launch(tron_dataset *ds, const SolveParams &P, DriverState &drv,
 {
     const int grid = dense_round_grid(ds->n, ds->d, P.loss);
     double *loss_partials = ds->partials + ds->d * grid;
-    const SolveArgs A{ds->X, ds->y8, {ds->Dbuf[0], ds->Dbuf[1]}, ds->partials, loss_partials, loss_partials + grid, (ds->d + 2) * grid,
+    const SolveArgs A{ds->X, ds->y8, {ds->Dbuf[0], ds->Dbuf[1]}, ds->partials, loss_partials, (ds->d + 1) * grid,
                       ds->ticket, grid_sync(ds), drv.ctl, drv.st, w0, C, P.trace_cap > 0 ? drv.trace_dev : nullptr, drv.host_dev};
     ProfScope ps(ds, SLOT_BATCH_PASS);
     return dispatch_solve(ds, P, A, stamp);
