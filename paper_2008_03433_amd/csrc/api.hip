@@ -137,7 +137,7 @@ GridSync grid_sync(const tron_dataset *ds)
     return GridSync{ds->sync_words, us < 0 ? kResidentWaitUs * kTicksPerUs : us == 0 ? -1 : us * kTicksPerUs};
 }
 
-bool resident_possible(const tron_dataset *ds, int grid) { return g_tuning.solve_resident != 0 && grid <= ds->cus; }
+bool resident_possible(tron_dataset *ds, int grid) { return g_tuning.solve_resident != 0 && grid <= ds->cus && ds->resident.try_it(g_tuning.solve_wait_us); }
 
 namespace {
 struct ResidentPool {

@@ -1192,7 +1192,7 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
             TRON_HIP(hipStreamSynchronize(ds->stream));
         }
         done = ended();   // otherwise workgroups gave up waiting for others before the first of them had the result; w0 is as it was
-        ++(done ? ds->resident.done : ds->resident.given_up);
+        ds->resident.ended(done);
     }
     if (!done) {
         TRON_TRY(launch_begin(ds, drv, 1, BEGIN_SOLVE, w_dev, &C));

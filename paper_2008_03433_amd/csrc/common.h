@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -269,9 +270,30 @@ struct DriverState;
 struct SolveParams;
 struct CsrSolver;
 
-// Of a handle's solves in one launch (grid_sync.h): how many have ended that way, and in how many workgroups gave up waiting
+// Of a handle's solves in one launch (grid_sync.h): how many have ended that way, and in how many workgroups gave up waiting.
+// A give-up costs the wait, a thousand times a small solve, and what held a part of the GPU may go on holding it: after the k-th in a
+// row the next 2^(k-1) solves do not try.  So a handle loses at most some twenty waits over its first million solves, and is back to
+// one launch after at most as many solves as it has been kept from it.  Another wait limit (knob) starts afresh.
 struct ResidentRecord {
-    int64_t done = 0, given_up = 0;
+    int64_t done = 0, given_up = 0, skip = 0, wait_us = -1;
+    int in_a_row = 0;
+    bool try_it(int64_t wait_now)
+    {
+        if (wait_now != wait_us) {
+            wait_us = wait_now;
+            in_a_row = 0;
+            skip = 0;
+        }
+        if (skip == 0) return true;
+        --skip;
+        return false;
+    }
+    void ended(bool well)
+    {
+        ++(well ? done : given_up);
+        in_a_row = well ? 0 : std::min(in_a_row + 1, 40);
+        skip = well ? 0 : (int64_t)1 << (in_a_row - 1);
+    }
 };
 }  // namespace tron
 struct tron_dataset {
@@ -360,12 +382,12 @@ HostFlag next_flag(tron_dataset *ds);
 int wait_results(tron_dataset *ds);
 
 // Launches whose workgroups wait for each other (grid_sync.h).  resident_possible: whether `grid` workgroups can be resident
-// together, one per compute unit.  ResidentShare: the call's place among those of this process that run on one device at a time; it
+// together, one per compute unit, and the handle's last solves have not been given up (asked once a solve).  ResidentShare: the call's place among those of this process that run on one device at a time; it
 // waits until its workgroups and theirs are no more than the compute units, so that two solves on two streams cannot each hold a
 // part of the GPU and wait for the rest.
 struct GridSync;
 GridSync grid_sync(const tron_dataset *ds);
-bool resident_possible(const tron_dataset *ds, int grid);
+bool resident_possible(tron_dataset *ds, int grid);
 class ResidentShare {
 public:
     ResidentShare(int device, int grid);

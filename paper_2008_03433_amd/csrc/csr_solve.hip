@@ -935,14 +935,14 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
                 TRON_HIP(hipStreamSynchronize(ds->stream));
                 if (!ended()) {   // workgroups gave up waiting for others; w0 is as it was
                     W.cleared = false;
-                    ++ds->resident.given_up;
+                    ds->resident.ended(false);
                     return 0;
                 }
             }
             if (W.host->st.step == STEP_END) break;
         }
     }
-    ++ds->resident.done;
+    ds->resident.ended(true);
     const CsrState &S = W.host->st;
     W.turn = S.turn;
     if (!A.out) {

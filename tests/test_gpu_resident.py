@@ -109,6 +109,39 @@ def test_a_launch_behind_one_that_was_given_up_finds_the_counters_at_zero(knob, 
         ds.close()
 
 
+@pytest.mark.parametrize("sparse", [False, True])
+def test_solves_that_were_given_up_are_not_tried_again_at_once(knob, sparse):
+    """What held a part of the GPU may hold it for long: one wait, then one solve the other way, another wait, two solves, four, ..."""
+    torch = torch_mod()
+    rng = np.random.default_rng(5)
+    ds = tron.Dataset.from_problem(_sparse(rng, 500, 400, 9) if sparse else _dense(rng, 5000, 24))
+    w0 = torch.zeros(400 if sparse else 24, dtype=torch.float64, device="cuda")
+    try:
+        one = _solve(ds, LOSS_LR, 0.3, w0)
+        assert _ways(ds) == (1, 0)
+        knob("solve_wait_us", 0)
+        given_up = []
+        for _ in range(20):
+            other = _solve(ds, LOSS_LR, 0.3, w0)
+            assert other[3:6] == one[3:6] and abs(other[1] - one[1]) <= 1e-12 * abs(one[1])
+            given_up.append(_ways(ds)[1])
+        assert given_up == [1, 1, 2, 2, 2] + [3] * 5 + [4] * 9 + [5]
+        knob("solve_wait_us", -1)   # another limit: afresh
+        assert _solve(ds, LOSS_LR, 0.3, w0) == one and _ways(ds) == (2, 5)
+        knob("solve_wait_us", 0)
+        _solve(ds, LOSS_LR, 0.3, w0)
+        assert _ways(ds) == (2, 6)
+        knob("solve_resident", 0)   # not to be tried anyway: no solve counts
+        for _ in range(3):
+            _solve(ds, LOSS_LR, 0.3, w0)
+        knob("solve_resident", -1)
+        _solve(ds, LOSS_LR, 0.3, w0)
+        _solve(ds, LOSS_LR, 0.3, w0)
+        assert _ways(ds) == (2, 7)
+    finally:
+        ds.close()
+
+
 # ------------------------------------------------------------------ sparse
 def _sparse(rng, n, d, mean, common=(), long_rows=(), zipf=0.0):
     """Rows of about `mean` entries; columns `common` are in every row, the rows `long_rows` have two thirds of all columns, every
