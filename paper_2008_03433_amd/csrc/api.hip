@@ -122,7 +122,13 @@ static int alloc_common(tron_dataset *ds)
     TRON_HIP(hipMemset(ds->ticket, 0, 64));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->sync_words), sizeof(unsigned) * kSyncWords));
     TRON_HIP(hipMemset(ds->sync_words, 0, sizeof(unsigned) * kSyncWords));
-    TRON_HIP(hipDeviceGetAttribute(&ds->cus, hipDeviceAttributeMultiprocessorCount, ds->device));
+    TRON_HIP(hipDeviceGetAttribute(&ds->device_cus, hipDeviceAttributeMultiprocessorCount, ds->device));
+    // a stream may be confined to a part of them (hipExtStreamCreateWithCUMask)
+    uint32_t mask[32] = {0};
+    int masked = 0;
+    if (hipExtStreamGetCUMask(ds->stream, 32, mask) != hipSuccess) (void)hipGetLastError();
+    for (uint32_t m : mask) masked += __builtin_popcount(m);
+    ds->cus = masked > 0 ? std::min(masked, ds->device_cus) : ds->device_cus;
     return TRON_OK;
 }
 
@@ -149,13 +155,11 @@ constexpr int kPools = 64;
 ResidentPool g_resident[kPools];
 }  // namespace
 
-ResidentShare::ResidentShare(int device, int grid) : device_(device), grid_(grid)
+ResidentShare::ResidentShare(const tron_dataset *ds, int grid) : device_(ds->device), grid_(ds->cus < ds->device_cus ? ds->device_cus : grid)
 {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 0;
     ResidentPool &p = g_resident[device_ % kPools];
     std::unique_lock<std::mutex> lock(p.m);
-    p.freed.wait(lock, [&] { return p.used == 0 || p.used + grid_ <= cus; });
+    p.freed.wait(lock, [&] { return p.used == 0 || p.used + grid_ <= ds->device_cus; });
     p.used += grid_;
 }
 

@@ -1178,7 +1178,7 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     bool done = false;
     const int grid = dense_round_grid(ds->n, ds->d, Q.loss);
     if (resident_possible(ds, grid)) {
-        const ResidentShare share(ds->device, grid);
+        const ResidentShare share(ds, grid);
         drv.host->finished = 0;
         TRON_TRY(dense_solve_launch(ds, P, drv, 0, w_dev, C));
         // With the stamp everything is there that the call returns; the stream's own wait would take some microseconds more.

@@ -326,7 +326,7 @@ struct tron_dataset {
     double *scal_copy = nullptr; // the same scalars in device memory, for kernels that continue from them without the host
     unsigned *ticket = nullptr;  // counter of finished workgroups for reductions completed inside the producing kernel (zero between kernels)
     unsigned *sync_words = nullptr;  // counters of the launches whose workgroups wait for each other (zero between kernels)
-    int cus = 0;                 // compute units of the device
+    int device_cus = 0, cus = 0; // compute units of the device, and those that the stream may use
     int64_t flag_value = 0;      // of the HostFlag given out last
     bool flagged = false;        // the kernel enqueued last has it (see wait_results)
     bool finish_done = false;    // the last producing kernel did: the next reduce_final call is a no-op
@@ -384,13 +384,13 @@ int wait_results(tron_dataset *ds);
 // Launches whose workgroups wait for each other (grid_sync.h).  resident_possible: whether `grid` workgroups can be resident
 // together, one per compute unit, and the handle's last solves have not been given up (asked once a solve).  ResidentShare: the call's place among those of this process that run on one device at a time; it
 // waits until its workgroups and theirs are no more than the compute units, so that two solves on two streams cannot each hold a
-// part of the GPU and wait for the rest.
+// part of the GPU and wait for the rest.  (A stream with a mask of compute units: it waits until it is alone, as theirs may lie on the same ones.)
 struct GridSync;
 GridSync grid_sync(const tron_dataset *ds);
 bool resident_possible(tron_dataset *ds, int grid);
 class ResidentShare {
 public:
-    ResidentShare(int device, int grid);
+    ResidentShare(const tron_dataset *ds, int grid);
     ~ResidentShare();
     ResidentShare(const ResidentShare &) = delete;
     ResidentShare &operator=(const ResidentShare &) = delete;

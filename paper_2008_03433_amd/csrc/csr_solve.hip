@@ -918,7 +918,7 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     A.steps = kStepsPerLaunch;
     ds->have_D = false;
     {
-        const ResidentShare share(ds->device, grid);
+        const ResidentShare share(ds, grid);
         W.host->stamp = 0;
         for (int64_t stamp = 1;; ++stamp) {
             A.stamp = stamp;

@@ -1,4 +1,5 @@
 """Solves in one launch, whose workgroups wait for each other inside the kernel, against the same solve with a launch per round."""
+import ctypes
 import threading
 
 import numpy as np
@@ -107,6 +108,29 @@ def test_a_launch_behind_one_that_was_given_up_finds_the_counters_at_zero(knob, 
         assert _ways(ds) == (41, 40)
     finally:
         ds.close()
+
+
+def test_solve_on_a_stream_that_may_use_a_quarter_of_the_compute_units():
+    """Workgroups for all of them could not be resident together there: such a solve takes a launch per round and waits for nothing."""
+    torch = torch_mod()
+    hip = tron.load_library()   # its own symbols and those of the runtime that it is linked against
+    w0 = torch.zeros(24, dtype=torch.float64, device="cuda")
+    stream, words = ctypes.c_void_p(), torch.cuda.get_device_properties(0).multi_processor_count // 32
+    mask = (ctypes.c_uint32 * words)(*([0xFFFFFFFF] * (words // 4) + [0] * (words - words // 4)))
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), words, mask) == 0
+    rng = np.random.default_rng(7)
+    for n, here in ((20_000, True), (120_000, False)):   # 40 workgroups, 235
+        p = _dense(rng, n, 24)
+        results = []
+        for masked in (True, False):
+            with torch.cuda.stream(torch.cuda.ExternalStream(stream.value) if masked else torch.cuda.Stream()):
+                ds = tron.Dataset.from_problem(p)
+                results.append([_solve(ds, LOSS_LR, 0.3, w0) for _ in range(3)])
+                assert _ways(ds) == ((3, 0) if here or not masked else (0, 0))
+                ds.close()
+        assert results[0] == results[1]
+    torch.cuda.synchronize()
+    assert hip.hipStreamDestroy(stream) == 0
 
 
 @pytest.mark.parametrize("sparse", [False, True])
