@@ -763,9 +763,10 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
 }
 
 // ------------------------------------------------------------------ host
-// The work space of a handle's solves, kept with the handle
+// The work space of a handle's solves, kept with the handle: 16 d + 4 n doubles and a little
+constexpr int kPieces = 2 * kRing + 9;
 struct CsrSolver {
-    double *blocks[2 * kRing + 9];   // what was allocated
+    double *blocks[kPieces];     // what was allocated
     int nblocks = 0;
     bool ready = false;
     CsrHost *host = nullptr, *host_dev = nullptr;
@@ -818,6 +819,33 @@ static ChunkPlan chunk_plan(const CsrPlan &A)
     return ChunkPlan{A.col, A.val, A.row_lo, A.rowptr, A.chunk_tab, A.flags, A.row_seg, A.chunk_long, A.long_row, nullptr, A.part_nnz[0], A.nblocks, A.plain ? 0 : A.nfix};
 }
 
+struct Piece {
+    double **p;
+    int64_t size;   // doubles
+};
+
+// Up to 2 MB an allocation comes from memory that the runtime has at hand or fetches 2 MB at a time (1 to 40 us), a larger one takes 25 to
+// 500 us each time: the pieces share blocks of up to 2 MB, and where one of them is larger (pairs of more than 131,072 columns) one block.
+// First solve of a handle with 20,000 rows in us (means; single ones differ by 200), an allocation a piece / this / driven by the host: 110,000
+// columns 610 / 580 / 580, 160,000 1130 / 640 / 730, 200,000 1170 / 690 / 690, 300,000 1970 / 730 / 1500 (and freeing them 1290 / 490 / 540).
+static int allocate(CsrSolver &W, const Piece *pieces, int count)
+{
+    constexpr int64_t kSmall = (2 << 20) / sizeof(double), kAlign = 256 / sizeof(double);
+    auto rounded = [&](int k) { return (pieces[k].size + kAlign - 1) / kAlign * kAlign; };
+    int64_t largest = 0;
+    for (int k = 0; k < count; ++k) largest = std::max(largest, rounded(k));
+    csr_resident_free(W);
+    for (int k0 = 0, k1 = 0; k0 < count; k0 = k1) {
+        int64_t total = 0;
+        for (; k1 < count && (k1 == k0 || largest > kSmall || total + rounded(k1) <= kSmall); ++k1) total += rounded(k1);
+        double *block = nullptr;
+        TRON_HIP(hipMalloc(reinterpret_cast<void **>(&block), sizeof(double) * total));
+        W.blocks[W.nblocks++] = block;
+        for (int k = k0; k < k1; block += rounded(k), ++k) *pieces[k].p = block;
+    }
+    return TRON_OK;
+}
+
 static int ensure_space(tron_dataset *ds, int trace_cap)
 {
     if (!ds->csr_solver) {
@@ -827,21 +855,15 @@ static int ensure_space(tron_dataset *ds, int trace_cap)
     CsrSolver &W = *ds->csr_solver;
     CsrSolveArgs &A = W.args;
     if (!W.ready) {
-        // one allocation each: up to 2 MB they come from memory that the runtime has already, larger ones take it some 300 us
         const int64_t px = ds->fwd.plain || !ds->fwd.nfix ? 0 : ds->fwd.nblocks + ds->fwd.nfix, pt = ds->bwd.plain || !ds->bwd.nfix ? 0 : ds->bwd.nblocks + ds->bwd.nfix;
         const int64_t psums = 2 * kSums * kMaxResidentGrid, pstate = (sizeof(CsrState) + 7) / 8 / kLine * kLine + kLine, lines = 3 * kSyncFlat * kLine;
-        auto get = [&](double *&p, int64_t m) -> int {
-            TRON_HIP(hipMalloc(reinterpret_cast<void **>(&p), sizeof(double) * m));
-            W.blocks[W.nblocks++] = p;
-            return TRON_OK;
-        };
-        csr_resident_free(W);
-        for (int k = 0; k < kRing; ++k) {
-            TRON_TRY(get(A.pairs[k], 2 * ds->d));
-            TRON_TRY(get(A.u[k], ds->n));
-        }
-        for (double **v : {&A.point, &A.w[0], &A.w[1], &A.g[0], &A.g[1], &A.s, &A.r, &A.M}) TRON_TRY(get(*v, ds->d));
-        TRON_TRY(get(A.sums, psums + pstate + lines + px + pt));
+        Piece pieces[kPieces];
+        int m = 0;
+        for (int k = 0; k < kRing; ++k) pieces[m++] = Piece{&A.pairs[k], 2 * ds->d};
+        for (int k = 0; k < kRing; ++k) pieces[m++] = Piece{&A.u[k], ds->n};
+        for (double **v : {&A.point, &A.w[0], &A.w[1], &A.g[0], &A.g[1], &A.s, &A.r, &A.M}) pieces[m++] = Piece{v, ds->d};
+        pieces[m++] = Piece{&A.sums, psums + pstate + lines + px + pt};
+        TRON_TRY(allocate(W, pieces, m));
         A.state = reinterpret_cast<CsrState *>(A.sums + psums);
         W.X = chunk_plan(ds->fwd);
         W.T = chunk_plan(ds->bwd);
