@@ -115,7 +115,7 @@ TRON_API int tron_dataset_shape(const tron_dataset *ds, int64_t *n, int64_t *d, 
  *   "dense_compact_rows"       rows of the compacted copy of the active rows the next tron_hv would run over (0: none)
  *   "solves_in_one_launch"     tron_solve calls of this handle so far that ran as one launch (see tron_solve)
  *   "solves_given_up"          those that started as one launch and were done another way, because workgroups had waited for
- *                              others too long
+ *                              others too long, or there was no memory for the work space
  *   "unit_values"              1 when the sparse layouts keep no values (every instance's entries share one value)
  *   "fwd_bytes_gather", "fwd_bytes_head", "fwd_bytes_ranges", "fwd_bytes_combine",
  *   "bwd_bytes_tiles", "bwd_bytes_tile_reduce", "bwd_bytes_ranges", "bwd_bytes_combine"

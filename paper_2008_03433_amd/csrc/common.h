@@ -270,7 +270,8 @@ struct DriverState;
 struct SolveParams;
 struct CsrSolver;
 
-// Of a handle's solves in one launch (grid_sync.h): how many have ended that way, and in how many workgroups gave up waiting.
+// Of a handle's solves in one launch (grid_sync.h): how many have ended that way, and how many were given up: workgroups had
+// waited too long, or the work space found no room.
 // A give-up costs the wait, a thousand times a small solve, and what held a part of the GPU may go on holding it: after the k-th in a
 // row the next 2^(k-1) solves do not try.  So a handle loses at most some twenty waits over its first million solves, and is back to
 // one launch after at most as many solves as it has been kept from it.  Another wait limit (knob) starts afresh.

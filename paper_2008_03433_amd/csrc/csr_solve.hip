@@ -916,11 +916,14 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     const int teams = std::min(kMaxTeams, (most + grid - 1) / grid);
     if (most > kMaxRounds * grid * teams || !resident_possible(ds, grid)) return 0;
     const int cap = std::min(res->trace_cap, Q.max_outer);
-    if (ensure_space(ds, cap) != TRON_OK) {   // no room beside the matrix: the host-driven solve needs less
+    const int space = ensure_space(ds, cap);
+    if (space == TRON_ENOMEM) {   // no room beside the matrix: the host-driven solve needs less
         (void)hipGetLastError();
         csr_resident_release(ds);
+        ds->resident.ended(false);
         return 0;
     }
+    if (space != TRON_OK) return space;
     CsrSolver &W = *ds->csr_solver;
     CsrSolveArgs A = W.args;
     A.w0 = w_dev;
