@@ -230,7 +230,8 @@ typedef struct {
  * from the device, like tron_batch_solve with one problem over all rows: same rules, same results up to summation order
  * (knob "dense_device_driver").  Sparse problems of up to some five million entries (not partitioned by columns, up to 2560 chunks
  * of 2048 entries in either orientation) are solved in one launch, unless the profiler is on: same rules, same results up to
- * summation order (knob "solve_resident").
+ * summation order (knob "solve_resident").  Solves of several threads on streams of their own share the GPU: those that
+ * together need more than all of it run a launch per step instead, with the same results, or wait for room.
  */
 TRON_API int tron_solve(tron_dataset *ds, const tron_params *params, double *w_dev, tron_result *res_host);
 
@@ -360,9 +361,10 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  * "dense_device_driver" (-1/0/1): tron_solve on a dense matrix with d <= 32 and no preconditioner runs its trust-region and
  *   CG steps on the device (as tron_batch_solve does): 0 never, 1 always, -1 (default) for the logistic loss, and for the
  *   L2-SVM on matrices up to 1 GB (larger ones may put their products on a compacted copy, see above).
- * "solve_resident" (-1/0): a tron_solve driven from the device, and that of a small sparse problem, runs as one launch whose
- *   workgroups wait for each other between the steps, where all of them can be resident at once (-1, default), or as a launch per
- *   product (0; sparse problems: driven by the host).
+ * "solve_resident" (-1/0/1): a tron_solve driven from the device, and that of a small sparse problem, runs as one launch whose
+ *   workgroups wait for each other between the steps, where all of them can be resident at once (-1, default; beside solves of
+ *   other threads that leave no room for it, as 1), or as a launch per product (0; sparse problems: driven by the host), or as a
+ *   launch per product with the same bits as one launch (1).
  * "solve_wait_us" (-1..10000000): how long a workgroup of such a launch waits for the others before it gives up and the
  *   solve starts again with a launch per product: microseconds, 0 not at all, -1 (default) a tenth of a second.  After the
  *   k-th give-up in a row a handle's next 2^(k-1) solves do not try one launch.

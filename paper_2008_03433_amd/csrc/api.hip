@@ -149,16 +149,21 @@ namespace {
 struct ResidentPool {
     std::mutex m;
     std::condition_variable freed;
-    int used = 0;   // workgroups of the launches under way
+    int wanted = 0;   // workgroups of the solves under way, whatever their way, and of those that wait for room
+    int used = 0;     // those of the launches whose workgroups wait for each other
 };
 constexpr int kPools = 64;
 ResidentPool g_resident[kPools];
 }  // namespace
 
-ResidentShare::ResidentShare(const tron_dataset *ds, int grid) : device_(ds->device), grid_(ds->cus < ds->device_cus ? ds->device_cus : grid)
+ResidentShare::ResidentShare(const tron_dataset *ds, int grid, int turns)
+    : device_(ds->device), grid_(ds->cus < ds->device_cus ? ds->device_cus : grid)
 {
     ResidentPool &p = g_resident[device_ % kPools];
     std::unique_lock<std::mutex> lock(p.m);
+    p.wanted += grid_;
+    granted_ = g_tuning.solve_resident < 0 && (2 * grid_ <= ds->device_cus || p.wanted <= turns * ds->device_cus);
+    if (!granted_) return;
     p.freed.wait(lock, [&] { return p.used == 0 || p.used + grid_ <= ds->device_cus; });
     p.used += grid_;
 }
@@ -168,9 +173,10 @@ ResidentShare::~ResidentShare()
     ResidentPool &p = g_resident[device_ % kPools];
     {
         std::lock_guard<std::mutex> lock(p.m);
-        p.used -= grid_;
+        p.wanted -= grid_;
+        if (granted_) p.used -= grid_;
     }
-    p.freed.notify_all();
+    if (granted_) p.freed.notify_all();
 }
 
 static int check_labels(const double *y, int64_t n)
@@ -773,7 +779,7 @@ int tron_tuning_set(const char *name, int64_t value)
         g_tuning.dense_device_driver = value;
         return TRON_OK;
     }
-    if (name && strcmp(name, "solve_resident") == 0 && value >= -1 && value <= 0) {
+    if (name && strcmp(name, "solve_resident") == 0 && value >= -1 && value <= 1) {
         g_tuning.solve_resident = value;
         return TRON_OK;
     }

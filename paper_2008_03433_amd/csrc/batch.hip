@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <optional>
 #include <thread>
 
 #include "dense_tile.h"
@@ -1177,8 +1178,9 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     const double C = Q.C;
     bool done = false;
     const int grid = dense_round_grid(ds->n, ds->d, Q.loss);
-    if (resident_possible(ds, grid)) {
-        const ResidentShare share(ds, grid);
+    std::optional<ResidentShare> share;
+    if (resident_possible(ds, grid)) share.emplace(ds, grid, 1);
+    if (share && share->granted()) {
         drv.host->finished = 0;
         TRON_TRY(dense_solve_launch(ds, P, drv, 0, w_dev, C));
         // With the stamp everything is there that the call returns; the stream's own wait would take some microseconds more.
@@ -1193,6 +1195,7 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
         }
         done = ended();   // otherwise workgroups gave up waiting for others before the first of them had the result; w0 is as it was
         ds->resident.ended(done);
+        share.reset();
     }
     if (!done) {
         TRON_TRY(launch_begin(ds, drv, 1, BEGIN_SOLVE, w_dev, &C));

@@ -52,7 +52,8 @@ struct Tuning {
                                    //   -1 automatic (launches of few workgroups, where the extra launch costs more than it does)
     int64_t dense_device_driver = -1;   // tron_solve on dense d <= 32 without preconditioner driven from the device:
                                         //   0 never, 1 always, -1 automatic (all but L2-SVM matrices above 1 GB)
-    int64_t solve_resident = -1;   // solves in one launch whose workgroups wait for each other: 0 never, -1 where they can all be resident
+    int64_t solve_resident = -1;   // solves in one launch whose workgroups wait for each other: 0 never, -1 where they can all be resident,
+                                   //   1 with a launch per step and the same bits
     int64_t solve_wait_us = -1;    // how long such a workgroup waits for the others: -1 automatic, 0 not at all (the launches then end at once)
     int64_t batch_grid = 0;  // workgroups of the multi-problem pass: 0 = as many as are resident at once
     int64_t batch_mfma = -1; // multi-problem pass on the matrix units: 1 = yes, 0 = no, -1 = the library decides
@@ -383,20 +384,32 @@ HostFlag next_flag(tron_dataset *ds);
 int wait_results(tron_dataset *ds);
 
 // Launches whose workgroups wait for each other (grid_sync.h).  resident_possible: whether `grid` workgroups can be resident
-// together, one per compute unit, and the handle's last solves have not been given up (asked once a solve).  ResidentShare: the call's place among those of this process that run on one device at a time; it
-// waits until its workgroups and theirs are no more than the compute units, so that two solves on two streams cannot each hold a
-// part of the GPU and wait for the rest.  (A stream with a mask of compute units: it waits until it is alone, as theirs may lie on the same ones.)
+// together, one per compute unit, and the handle's last solves have not been given up (asked once a solve).
+// ResidentShare: the call's place among the solves of this process on the device.  Granted: the launch and those under way have no
+// more workgroups than there are compute units, so that two solves on two streams cannot each hold a part of the GPU and wait for the
+// rest.  (A stream with a mask of compute units: it has the device to itself, as theirs may lie on the same ones.)  Where there is no room the
+// constructor waits for it; but solves that fill more than half the GPU and together would fill it more than `turns` times go on
+// without (not granted: a launch per step or round, same results), because those of several streams fill each other's gaps.
+// us a solve with 1, 2, 3, 4, 8 threads at it, in turns / this way / (before there was one launch):
+//   dense, 100,000 x 24     54 53 53 53 54   / 55 45 64 40 38    / (108 81 62 39 41)
+//   sparse, 264,000 entries 138 135 136 136 136 / 139 100 74 58 77 / (231 144 98 79 86)
+//   sparse, 480,000         169 167 168 169 169 / 172 107 80 70 77 / (251 150 110 89 85)
+//   sparse, 1.05M, Zipf     847 889 887 877 892 / 850 892 805 778 849 / (950 657 546 490 568)
+// The last one pays for its two rounds of chunks and its long columns in every launch: turns = 2 there, 1 for all others.  Solves of
+// 40 to 49 workgroups: in turns 33 to 37 us with 4 and 8 threads (42 and 60 to 170 before).
 struct GridSync;
 GridSync grid_sync(const tron_dataset *ds);
 bool resident_possible(tron_dataset *ds, int grid);
 class ResidentShare {
 public:
-    ResidentShare(const tron_dataset *ds, int grid);
+    ResidentShare(const tron_dataset *ds, int grid, int turns);
     ~ResidentShare();
+    bool granted() const { return granted_; }
     ResidentShare(const ResidentShare &) = delete;
     ResidentShare &operator=(const ResidentShare &) = delete;
 private:
     int device_, grid_;
+    bool granted_;
 };
 
 // RAII bracket used by the launch helpers

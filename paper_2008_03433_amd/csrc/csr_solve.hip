@@ -18,8 +18,10 @@
 // workgroup leave 256 registers a thread, which the fetched chunk, the row's vectors and nine sums fill; three chunks (168 registers)
 // are no faster although 513 chunks then need no second round, four spill.  us a solve, driven by the host / here: 100,000 entries
 // 220 / 115, 8,000 x 20,000 with 640,000 entries 300 / 197, 1.05M with Zipf-distributed columns 950 / 860, 3.4M 2345 / 2200.
+// (Solves of several threads that together need more than the GPU: see ResidentShare in common.h, and PART_CHUNKS below.)
 #include <cmath>
 #include <new>
+#include <thread>
 
 #include "csr_chunk.h"
 #include "grid_sync.h"
@@ -87,6 +89,7 @@ struct CsrHost {
     CsrState st;
     tron_trace_rec trace[kHostRecords];
     int64_t stamp;   // launches that have ended with all workgroups together
+    int64_t step;    // a launch per step: the last one that has begun
 };
 
 // The rest of what the kernel is told.  It copies this to LDS: kept in registers through all steps it would leave too few of them.
@@ -107,6 +110,7 @@ struct CsrSolveArgs {
     CsrHost *host;
     tron_trace_rec *trace;
     int64_t stamp;
+    double *lanes, *waves;   // a launch per step: what PART_CHUNKS leaves for PART_LONG, see there
 };
 
 // A chunk as a thread holds it before it multiplies: its eight entries, and of the first row it will finish what is needed
@@ -276,9 +280,13 @@ __device__ __forceinline__ void chunk_sums(const ChunkPlan &P, int chunk, int ti
 __device__ __forceinline__ void hand_over(uint64_t *place, double v) { __hip_atomic_store(place, (uint64_t)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void clear(uint64_t *place) { __hip_atomic_store(place, kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// What a launch does: the whole solve, or of one step the rows that fit into a chunk, or those longer than a chunk behind a launch
+// that did the others.
+enum Part { PART_ALL, PART_CHUNKS, PART_LONG };
+
 // One product, and what is done with every row's sum: aux = load(row) is asked for before the sum is known, apply(row, sum, aux)
 // takes it.  h: the workgroup's first chunks, fetched already.  False: given up.
-template <bool SEG, class Load, class Apply>
+template <bool SEG, Part PART, class Load, class Apply>
 __device__ __forceinline__ bool product(const ChunkPlan &P, Chunk &h, int how, const double *x, double beta, bool square, double *lds,
                                         double *piece, int *bad, GridBarrier &grid, int tid, const Load &load, const Apply &apply)
 {
@@ -289,7 +297,7 @@ __device__ __forceinline__ bool product(const ChunkPlan &P, Chunk &h, int how, c
     int4 R = make_int4(0, 0, 0, 0);
     if (SEG && long0 < P.nlong) R = P.long_row[long0];
     Chunk next;
-    for (int c0 = 0; c0 < P.nchunks; c0 += per) {
+    for (int c0 = 0; PART != PART_LONG && c0 < P.nchunks; c0 += per) {
         const int chunk = c0 + team * (int)gridDim.x + (int)blockIdx.x;
         if (c0 > 0) {
             __syncthreads();   // the sums of the chunk before have been read
@@ -322,7 +330,7 @@ __device__ __forceinline__ bool product(const ChunkPlan &P, Chunk &h, int how, c
             aux = load(r);
         }
     }
-    if constexpr (SEG) {
+    if constexpr (SEG && PART != PART_CHUNKS) {
         if (P.nlong > 0) {
             for (int l = long0; l < P.nlong; l += (int)(gridDim.x * blockDim.x / kWave)) {
                 if (l > long0) R = P.long_row[l];
@@ -533,7 +541,45 @@ __device__ __forceinline__ void wave_sums(const double (&v)[kSums], int n, doubl
     }
 }
 
-template <bool SEGX, bool SEGT>
+// lane k has the grid's sum k, of what its workgroups (256 at most, a thread each) have left in `sums`: added up by the first team, the
+// partial sums of its wavefronts behind a barrier in red
+__device__ __forceinline__ void grid_sums(const double *sums, int nsums, int tid, double (*red)[kMaxTeams * kWavesPerBlock])
+{
+    double t[kSums];
+    const bool mine = tid < (int)gridDim.x;
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) t[k] = (k < nsums && mine) ? load_shared(sums + k * kMaxResidentGrid + tid) : 0.0;
+    wave_sums(t, nsums, &red[0][tid / kWave], kMaxTeams * kWavesPerBlock);
+}
+
+__device__ __forceinline__ int sums_of(int step, bool precond) { return step != STEP_HV ? 2 : precond ? kSums : kSums - 2; }
+
+// The first workgroup tells the host: the end of the solve, with the result, or (PART_ALL) that the solve goes on in another launch.
+template <Part PART>
+__device__ __forceinline__ void report_end(const CsrSolveArgs &A, const CsrState &S, int step)
+{
+    if (step == STEP_END && A.out) {
+        const double *w = S.cur ? A.w[1] : A.w[0];
+        for (int64_t j = threadIdx.x; j < A.d; j += blockDim.x) store_shared(A.out + j, load_shared(w + j));
+    }
+    // the host may go on when it sees the stamp: the result has arrived by then
+    stores_arrived();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (PART == PART_ALL) *A.state = S;
+        A.host->st = S;
+        __hip_atomic_store(&A.host->stamp, A.stamp, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// PART_ALL: the whole solve, as described at the top of the file.
+// PART_CHUNKS and PART_LONG: a step in two launches (the second where there are rows longer than a chunk), for solves that find the GPU held
+// by others: nothing waits inside, so that launches of several solves may share the GPU in any way.  Every workgroup has the
+// same rows, and every sum is formed in the same order, as in the one launch, so the results have the same bits.  PART_CHUNKS begins with the
+// sums of the step before and what follows from them; the state lies in one of two places in turn, as late workgroups may still
+// be reading.  Where rows longer than a chunk follow, the wavefronts that will have them leave their lanes' shares of the sums in `lanes`, the
+// others their sums in `waves`.
+template <bool SEGX, bool SEGT, Part PART>
 __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, ChunkPlan T, CsrSolveArgs args)
 {
     extern __shared__ __align__(16) double lds_all[];
@@ -550,7 +596,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
     if (threadIdx.x == 0) {
         bad = 0;
         A = args;
-        if (args.resume) S = *args.state;
+        if (args.resume) S = args.state[PART == PART_ALL ? 0 : PART == PART_LONG ? args.stamp & 1 : ~args.stamp & 1];
         else {
             S = CsrState{};
             S.turn = args.turn;
@@ -559,15 +605,48 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         }
     }
     __syncthreads();
-    const bool precond = A.blend > 0.0, report = blockIdx.x == 0, flat = gridDim.x <= kSyncFlat;
-    int step = __builtin_amdgcn_readfirstlane(S.step), left = A.steps;
+    const bool precond = A.blend > 0.0, report = blockIdx.x == 0, flat = PART == PART_ALL && gridDim.x <= kSyncFlat;
+    int step = __builtin_amdgcn_readfirstlane(S.step), left = PART == PART_ALL ? A.steps : (int)(args.stamp & 1) + 1;   // its parity says which of the two places the sums go to
+    if constexpr (PART == PART_CHUNKS) {
+        if (args.resume && step != STEP_END) {
+            const int nsums = sums_of(step, precond);
+            if (team == 0) grid_sums(A.sums + (~left & 1) * kSums * kMaxResidentGrid, nsums, tid, red);
+            __syncthreads();
+            if (threadIdx.x < kWave) {
+                const double *part = red[(int)threadIdx.x < nsums ? threadIdx.x : 0];
+                const double total = (part[0] + part[1]) + (part[2] + part[3]);
+                CsrState next = S;
+                double t[kSums];
+#pragma unroll
+                for (int k = 0; k < kSums; ++k) t[k] = read_lane(total, k);
+                decide(next, A, t, report && threadIdx.x == 0);
+                if (threadIdx.x == 0) S = next;
+            }
+            __syncthreads();
+            step = __builtin_amdgcn_readfirstlane(S.step);
+            if (step == STEP_END && report) report_end<PART>(A, S, step);
+        }
+        if (report && threadIdx.x == 0) {
+            A.state[args.stamp & 1] = S;
+            if (step != STEP_END) __hip_atomic_store(&A.host->step, A.stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+    // rows longer than a chunk in this step, and the first one of this wavefront
+    int nlong = 0, long0 = 0;
+    if constexpr (PART != PART_ALL) {
+        nlong = step == STEP_RESTART ? 0 : with_x(step) ? (SEGX ? X.nlong : 0) : (SEGT ? T.nlong : 0);
+        long0 = (int)blockIdx.x + (int)gridDim.x * __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+        if (PART == PART_LONG && nlong == 0) return;
+    }
     Chunk h;
-    if (with_x(step)) load_chunk<SEGX>(X, first, tid, h);
-    else load_chunk<SEGT>(T, first, tid, h);
+    if constexpr (PART != PART_LONG) {
+        if (with_x(step)) load_chunk<SEGX>(X, first, tid, h);
+        else load_chunk<SEGT>(T, first, tid, h);
+    }
     bool ok = true;
     for (; step != STEP_END && left > 0; --left) {
         // as if they changed: the addresses of the first chunk are formed again instead of being kept through all steps
-        asm volatile("" : "+v"(tid), "+s"(first));
+        if constexpr (PART == PART_ALL) asm volatile("" : "+v"(tid), "+s"(first));
         const int cur = __builtin_amdgcn_readfirstlane(S.cur), dcur = __builtin_amdgcn_readfirstlane(S.dcur);
         const bool fresh = __builtin_amdgcn_readfirstlane(S.it) == 0;
         const int pair_at = __builtin_amdgcn_readfirstlane(S.pair_at);
@@ -576,6 +655,14 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         const int na = __builtin_amdgcn_readfirstlane(S.na), nb = __builtin_amdgcn_readfirstlane(S.nb);
         double v[kSums] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         bool any = false;   // whether this lane had a row
+        if constexpr (PART == PART_LONG) {
+            if (long0 < nlong) {
+                any = true;
+#pragma unroll
+                for (int k = 0; k < kSums; ++k)
+                    if (k < sums_of(step, precond)) v[k] = A.lanes[((int64_t)long0 * kSums + k) * kWave + (threadIdx.x & (kWave - 1))];
+            }
+        }
         const int turn = __builtin_amdgcn_readfirstlane(S.turn);
         if (flat && threadIdx.x < kSums) clear(A.lines + ((turn == 2 ? 0 : turn + 1) * kSyncFlat + blockIdx.x) * kLine + threadIdx.x);
         if (with_x(step)) {
@@ -584,7 +671,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
             double *D = (dcur ^ (step == STEP_ZERO || step == STEP_TRIAL)) ? A.D[1] : A.D[0];
             const double *row_in = cg ? D : A.y;
             const double beta = S.beta;
-            ok = product<SEGX>(X, h, cg ? GATHER_PAIR : step == STEP_ZERO ? GATHER_NONE : GATHER_ONE, cg ? pair : step == STEP_START ? A.w0 : point, beta, false,
+            ok = product<SEGX, PART>(X, h, cg ? GATHER_PAIR : step == STEP_ZERO ? GATHER_NONE : GATHER_ONE, cg ? pair : step == STEP_START ? A.w0 : point, beta, false,
                                lds, piece, &bad, grid, tid, [&](int r) { return row_in[r]; },
                                [&](int r, double z, double in) {
                                    any = true;
@@ -600,7 +687,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
                                    }
                                    store_shared(u + r, t);
                                });
-            if (step == STEP_START)
+            if (PART != PART_LONG && step == STEP_START)
                 own_rows<SEGT>(T, tid, [&](int j) {
                     any = true;
                     const double x = A.w0[j];
@@ -610,7 +697,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         } else {
             const double *u = step == STEP_DIAG ? (dcur ? A.D[1] : A.D[0]) : A.u[(na + kRing - 1) % kRing];
             double *pair_out = A.pairs[nb % kRing], *point_out = A.point;
-            if (step == STEP_RESTART) {
+            if (PART != PART_LONG && step == STEP_RESTART) {
                 own_rows<SEGT>(T, tid, [&](int j) {
                     any = true;
                     const double z = -g[j] / (precond ? A.M[j] : 1.0);
@@ -624,7 +711,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
                 double *gnew = (trial && cur == 0) ? A.g[1] : A.g[0], *wnew = cur ? A.w[0] : A.w[1];
                 const double *wj = trial ? point : w;
                 struct Aux { double w, g, p, s, r, m; };
-                ok = product<SEGT>(T, h, GATHER_ONE, u, 0.0, diag, lds, piece, &bad, grid, tid,
+                ok = product<SEGT, PART>(T, h, GATHER_ONE, u, 0.0, diag, lds, piece, &bad, grid, tid,
                                    [&](int j) {
                                        Aux a{zero ? 0.0 : wj[j], 0.0, 0.0, 0.0, 0.0, 1.0};
                                        if (hv || diag) a.g = g[j];
@@ -679,14 +766,26 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         const int used = with_x(step) ? na : nb;   // how many places were used before this step's
         if (!ok) break;
         // the workgroup's sums
-        const int nsums = step != STEP_HV ? 2 : precond ? kSums : kSums - 2;
+        const int nsums = sums_of(step, precond);
         double *sums = A.sums + (left & 1) * kSums * kMaxResidentGrid;
-        if (__ballot(any)) wave_sums(v, nsums, &red[0][threadIdx.x / kWave], kMaxTeams * kWavesPerBlock);
+        if (PART == PART_CHUNKS && long0 < nlong) {
+#pragma unroll
+            for (int k = 0; k < kSums; ++k)
+                if (k < nsums) A.lanes[((int64_t)long0 * kSums + k) * kWave + (threadIdx.x & (kWave - 1))] = v[k];
+        } else if (PART == PART_LONG && long0 >= nlong) {
+            if ((int)(threadIdx.x & (kWave - 1)) < nsums)
+                red[threadIdx.x & (kWave - 1)][threadIdx.x / kWave] = A.waves[((int64_t)blockIdx.x * kSums + (threadIdx.x & (kWave - 1))) * kMaxTeams * kWavesPerBlock + threadIdx.x / kWave];
+        } else if (__ballot(any)) wave_sums(v, nsums, &red[0][threadIdx.x / kWave], kMaxTeams * kWavesPerBlock);
         else if ((int)(threadIdx.x & (kWave - 1)) < nsums) red[threadIdx.x & (kWave - 1)][threadIdx.x / kWave] = 0.0;
         // Up to 64 workgroups need no barrier beside the sums: each waits until those of all are there, a lane for every workgroup.  (The
         // lines of the next turn were cleared before; all have read what was in them, or they would not have got here.)
         if (flat) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // what the others read has arrived
         __syncthreads();
+        if (PART == PART_CHUNKS && nlong > 0) {
+            if ((int)threadIdx.x < nsums * kMaxTeams * kWavesPerBlock)   // (those of the wavefronts that have left their lanes' are not read)
+                A.waves[(int64_t)blockIdx.x * kSums * kMaxTeams * kWavesPerBlock + threadIdx.x] = (&red[0][0])[threadIdx.x];
+            return;
+        }
         if ((int)threadIdx.x < nsums) {
             double part[kMaxTeams * kWavesPerBlock], t = 0.0;
 #pragma unroll
@@ -697,6 +796,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
             if (flat) hand_over(A.lines + (turn * kSyncFlat + blockIdx.x) * kLine + threadIdx.x, t);
             else store_shared(sums + threadIdx.x * kMaxResidentGrid + blockIdx.x, t);
         }
+        if (PART != PART_ALL) return;
         if (!flat) grid.arrive();
         // most often a product with the other orientation follows
         if (with_x(step)) load_chunk<SEGT>(T, first, tid, h);
@@ -704,13 +804,7 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         if (!flat) {
             ok = grid.wait();
             if (!ok) break;
-            if (team == 0) {
-                double t[kSums];
-                const bool mine = tid < (int)gridDim.x;
-#pragma unroll
-                for (int k = 0; k < kSums; ++k) t[k] = (k < nsums && mine) ? load_shared(sums + k * kMaxResidentGrid + tid) : 0.0;
-                wave_sums(t, nsums, &red[0][tid / kWave], kMaxTeams * kWavesPerBlock);
-            }
+            if (team == 0) grid_sums(sums, nsums, tid, red);
             __syncthreads();
         }
         if (threadIdx.x < kWave) {   // all of the wavefront the same; lane k has sum k
@@ -745,20 +839,8 @@ __global__ __launch_bounds__(kTeam * kMaxTeams) void k_csr_solve(ChunkPlan X, Ch
         if (!was_x && !with_x(step) && step != STEP_END) load_chunk<SEGT>(T, first, tid, h);   // DIAG, RESTART after a gradient
         // (RESTART and DIAG are followed by a product with X, fetched during the wait like after every other step with X^T)
     }
-    if (ok && report) {
-        if (step == STEP_END && A.out) {
-            const double *w = S.cur ? A.w[1] : A.w[0];
-            for (int64_t j = threadIdx.x; j < A.d; j += blockDim.x) store_shared(A.out + j, load_shared(w + j));
-        }
-        // the host may go on when it sees the stamp: the result has arrived by then
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            *A.state = S;
-            A.host->st = S;
-            __hip_atomic_store(&A.host->stamp, A.stamp, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-    }
+    if (PART != PART_ALL) return;
+    if (ok && report) report_end<PART>(A, S, step);
     grid.leave();
 }
 
@@ -772,10 +854,12 @@ struct CsrSolver {
     CsrHost *host = nullptr, *host_dev = nullptr;
     tron_trace_rec *trace = nullptr;   // device memory, records past the first kHostRecords
     int trace_cap = 0;
-    bool lds_set = false;
+    bool lds_set[3] = {false, false, false};   // by Part
     int64_t to_clear = 0;        // places from args.lines on that are kEmpty between solves,
     bool cleared = false;        // unless one was given up (or none was made yet); of the lines, those of the turn `turn`
     int turn = 0;
+    double *step_block = nullptr;   // what launches per step need beside it
+    int64_t steps = 0;           // such launches so far
     ChunkPlan X, T;
     CsrSolveArgs args;
 };
@@ -791,6 +875,7 @@ void csr_resident_release(tron_dataset *ds)
     if (!ds->csr_solver) return;
     csr_resident_free(*ds->csr_solver);
     hipFree(ds->csr_solver->trace);
+    hipFree(ds->csr_solver->step_block);
     delete ds->csr_solver;
     ds->csr_solver = nullptr;
 }
@@ -879,6 +964,7 @@ static int ensure_space(tron_dataset *ds, int trace_cap)
         static_assert(sizeof(CsrHost) <= kSolveHostBytes, "room behind the scalars");
         W.host = reinterpret_cast<CsrHost *>(ds->scal_host + kHostWords);
         W.host_dev = reinterpret_cast<CsrHost *>(ds->scal_dev + kHostWords);
+        W.host->step = W.steps;
         W.ready = true;
         W.cleared = false;
     }
@@ -897,15 +983,88 @@ static int ensure_space(tron_dataset *ds, int trace_cap)
     return TRON_OK;
 }
 
-template <bool SEGX, bool SEGT>
+template <bool SEGX, bool SEGT, Part PART>
 static int launch(tron_dataset *ds, CsrSolver &W, const CsrSolveArgs &A, int grid, int teams)
 {
     const int lds = teams * kTeamLds * (int)sizeof(double);
-    if (lds > 64 << 10 && !W.lds_set) TRON_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_csr_solve<SEGX, SEGT>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    W.lds_set = true;
-    hipLaunchKernelGGL((k_csr_solve<SEGX, SEGT>), dim3(grid), dim3(teams * kTeam), lds, ds->stream, W.X, W.T, A);
+    if (lds > 64 << 10 && !W.lds_set[PART]) TRON_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_csr_solve<SEGX, SEGT, PART>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    W.lds_set[PART] = true;
+    hipLaunchKernelGGL((k_csr_solve<SEGX, SEGT, PART>), dim3(grid), dim3(teams * kTeam), lds, ds->stream, W.X, W.T, A);
     TRON_HIP(hipGetLastError());
     return TRON_OK;
+}
+
+template <Part PART>
+static int launch_part(tron_dataset *ds, CsrSolver &W, const CsrSolveArgs &A, int grid, int teams)
+{
+    return (ds->fwd.plain ? (ds->bwd.plain ? launch<false, false, PART> : launch<false, true, PART>) : (ds->bwd.plain ? launch<true, false, PART> : launch<true, true, PART>))(ds, W, A, grid, teams);
+}
+
+// The solve in one launch, or in several of kStepsPerLaunch steps: 1 = done, 0 = workgroups gave up waiting for others (w0 is as it was)
+static int solve_resident(tron_dataset *ds, CsrSolver &W, CsrSolveArgs &A, int grid, int teams)
+{
+    for (int64_t stamp = 1;; ++stamp) {
+        A.stamp = stamp;
+        A.resume = stamp > 1;
+        TRON_TRY(launch_part<PART_ALL>(ds, W, A, grid, teams));
+        // With the stamp everything is there that the call returns (the stream's own wait takes some microseconds more)
+        auto ended = [&]() { return __atomic_load_n(&W.host->stamp, __ATOMIC_ACQUIRE) == stamp; };
+        for (unsigned spins = 1; !ended(); ++spins) {
+            if ((spins & kSpinsPerQuery) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
+            __builtin_ia32_pause();
+        }
+        if (!ended()) {
+            (void)hipGetLastError();
+            TRON_HIP(hipStreamSynchronize(ds->stream));
+            if (!ended()) {
+                W.cleared = false;
+                return 0;
+            }
+        }
+        if (W.host->st.step == STEP_END) break;
+    }
+    W.turn = W.host->st.turn;
+    return 1;
+}
+
+// The same solve with a launch or two per step, for solves that do not wait for their turn (ResidentShare): kAhead steps enqueued behind the one that the host has seen begin
+static int solve_in_steps(tron_dataset *ds, CsrSolver &W, CsrSolveArgs &A, int grid, int teams)
+{
+    constexpr int64_t kAhead = 3;
+    const int nlong = std::max(W.X.nlong, W.T.nlong);
+    if (!W.step_block) {
+        const int64_t states = (2 * sizeof(CsrState) + 7) / 8, waves = (int64_t)kMaxResidentGrid * kSums * kMaxTeams * kWavesPerBlock;
+        const int64_t lanes = (int64_t)std::min(nlong, kMaxResidentGrid * kMaxTeams * kWavesPerBlock) * kSums * kWave;
+        TRON_HIP(hipMalloc(reinterpret_cast<void **>(&W.step_block), sizeof(double) * (waves + lanes + states)));
+    }
+    A.waves = W.step_block;
+    A.lanes = A.waves + (int64_t)kMaxResidentGrid * kSums * kMaxTeams * kWavesPerBlock;
+    A.state = reinterpret_cast<CsrState *>(A.lanes + (int64_t)std::min(nlong, kMaxResidentGrid * kMaxTeams * kWavesPerBlock) * kSums * kWave);
+    A.sync.ticks = std::max<long long>(A.sync.ticks, 0);   // (the pieces of a long row are there: nothing is waited for)
+    const int64_t before = W.steps;
+    A.resume = 0;
+    for (unsigned spins = 0;;) {
+        if (__atomic_load_n(&W.host->stamp, __ATOMIC_ACQUIRE) != 0) return 1;
+        const int64_t seen = std::max(__atomic_load_n(&W.host->step, __ATOMIC_ACQUIRE), before);
+        if (W.steps <= seen + kAhead) {
+            A.stamp = ++W.steps;
+            TRON_TRY(launch_part<PART_CHUNKS>(ds, W, A, grid, teams));
+            A.resume = 1;
+            if (nlong > 0) TRON_TRY(launch_part<PART_LONG>(ds, W, A, grid, teams));
+            spins = 0;
+            continue;
+        }
+        if ((++spins & 1023u) != 0) { __builtin_ia32_pause(); continue; }
+        // nothing for a while: make sure that the kernels are still running
+        const hipError_t e = hipStreamQuery(ds->stream);
+        (void)hipGetLastError();
+        if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(e, "hipStreamQuery", __FILE__, __LINE__);
+        if (e == hipSuccess && __atomic_load_n(&W.host->stamp, __ATOMIC_ACQUIRE) == 0 && __atomic_load_n(&W.host->step, __ATOMIC_ACQUIRE) < W.steps) {
+            set_error("internal: a step of a solve has ended without its word");
+            return TRON_ESTATE;
+        }
+        std::this_thread::yield();
+    }
 }
 
 int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tron_result *res, int *status)
@@ -943,33 +1102,18 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     A.steps = kStepsPerLaunch;
     ds->have_D = false;
     {
-        const ResidentShare share(ds, grid);
+        const ResidentShare share(ds, grid, most <= grid * teams ? 1 : 2);
         W.host->stamp = 0;
-        for (int64_t stamp = 1;; ++stamp) {
-            A.stamp = stamp;
-            A.resume = stamp > 1;
-            TRON_TRY((ds->fwd.plain ? (ds->bwd.plain ? launch<false, false> : launch<false, true>) : (ds->bwd.plain ? launch<true, false> : launch<true, true>))(ds, W, A, grid, teams));
-            // With the stamp everything is there that the call returns (the stream's own wait takes some microseconds more)
-            auto ended = [&]() { return __atomic_load_n(&W.host->stamp, __ATOMIC_ACQUIRE) == stamp; };
-            for (unsigned spins = 1; !ended(); ++spins) {
-                if ((spins & kSpinsPerQuery) == 0 && hipStreamQuery(ds->stream) != hipErrorNotReady) break;
-                __builtin_ia32_pause();
-            }
-            if (!ended()) {
-                (void)hipGetLastError();
-                TRON_HIP(hipStreamSynchronize(ds->stream));
-                if (!ended()) {   // workgroups gave up waiting for others; w0 is as it was
-                    W.cleared = false;
-                    ds->resident.ended(false);
-                    return 0;
-                }
-            }
-            if (W.host->st.step == STEP_END) break;
+        const int rc = share.granted() ? solve_resident(ds, W, A, grid, teams) : solve_in_steps(ds, W, A, grid, teams);
+        if (rc == TRON_ENOMEM) {
+            (void)hipGetLastError();
+            return 0;
         }
+        if (rc < 0) return rc;
+        if (share.granted()) ds->resident.ended(rc > 0);
+        if (rc == 0) return 0;
     }
-    ds->resident.ended(true);
     const CsrState &S = W.host->st;
-    W.turn = S.turn;
     if (!A.out) {
         TRON_HIP(hipMemcpyAsync(w_dev, A.w[S.cur], sizeof(double) * ds->d, hipMemcpyDeviceToDevice, ds->stream));
         TRON_HIP(hipStreamSynchronize(ds->stream));

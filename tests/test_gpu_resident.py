@@ -62,6 +62,9 @@ def test_dense_solve_in_one_launch_has_the_bits_of_a_launch_per_round(rng, knob,
             knob("solve_resident", 0)
             assert _solve(ds, loss, 0.3, start) == one
             assert tuple(_ways(ds) - before) == (2, 1)
+            knob("solve_resident", 1)   # as where other solves hold the GPU
+            assert _solve(ds, loss, 0.3, start) == one
+            assert tuple(_ways(ds) - before) == (2, 1)
             knob("solve_resident", -1)
             assert _solve(ds, loss, 0.3, start) == one
             assert tuple(_ways(ds) - before) == (3, 1)
@@ -79,7 +82,7 @@ def test_solves_of_several_threads_on_streams_of_their_own(rng):
         with torch.cuda.stream(torch.cuda.Stream()):
             ds = tron.Dataset.from_problem(problems[k])
             w0 = torch.zeros(24, dtype=torch.float64, device="cuda")
-            out[k] = [_solve(ds, LOSS_L2SVM, 0.3, w0) for _ in range(5)], _ways(ds)
+            out[k] = [_solve(ds, LOSS_L2SVM, 0.3, w0) for _ in range(5)], _ways(ds)[1]   # (some in one launch, some beside others: none given up)
             ds.close()
 
     for k in range(len(problems)):
@@ -268,6 +271,11 @@ def _follows_the_host(rng, knob, loss, q, one_launch):
             one = solve()
             here = tron.tron_dataset_stat(ds.handle, "solves_in_one_launch") - before[0]
             assert here == 1 or not one_launch
+            if here:   # a launch per step, as where other solves hold the GPU: the same rows and sums in the same order
+                knob("solve_resident", 1)
+                assert solve()[:7] == one[:7] and solve()[:7] == one[:7]
+                knob("solve_resident", -1)
+                assert tuple(_ways(ds) - before) == (1, 0)
             again = solve()
             assert one[:7] == again[:7]
             knob("solve_wait_us", 0)    # every workgroup gives up at once, the host drives the solve
@@ -302,7 +310,10 @@ def test_sparse_solve_of_many_steps_goes_on_in_further_launches(rng, knob):
             assert _ways(ds) == (1 if "cg_xi" in kw else 2, 0)
             knob("solve_resident", 0)
             host, v = solve()
+            knob("solve_resident", 1)
+            steps, v1 = solve()
             knob("solve_resident", -1)
+            assert steps == one and torch.equal(v1, w)
             if "cg_xi" in kw:   # the same minimiser: the gradient is 1e-7 of the first one, H >= I
                 assert one.n_hv > 256 and one.status == host.status == 0
                 assert abs(one.f - host.f) <= 1e-9 * host.f
@@ -314,16 +325,26 @@ def test_sparse_solve_of_many_steps_goes_on_in_further_launches(rng, knob):
         ds.close()
 
 
+@pytest.mark.parametrize("shapes", [("two rounds", "columns", "both", "plain"), ("two rounds", "three rounds", "two rounds")])
+def test_sparse_solves_of_threads_that_fill_the_gpu_have_the_bits_they_have_alone(shapes):
+    """Several grids of all compute units, and one of them among small ones."""
+    rng = np.random.default_rng(11)
+    _threads([_sparse(rng, **ONE_LAUNCH[k]) for k in shapes], (1, 3))
+
+
 def test_sparse_solves_of_several_threads_on_streams_of_their_own(rng):
+    _threads([_sparse(rng, **SPARSE[k]) for k in ("columns", "rounds", "both", "short")], (5,))
+
+
+def _threads(problems, solves):
     torch = torch_mod()
-    problems = [_sparse(rng, **SPARSE[k]) for k in ("columns", "rounds", "both", "short")]
     alone, together = {}, {}
 
     def work(k, out):
         with torch.cuda.stream(torch.cuda.Stream()):
             ds = tron.Dataset.from_problem(problems[k])
             w0 = torch.zeros(problems[k].d, dtype=torch.float64, device="cuda")
-            out[k] = [_solve(ds, LOSS_LR, 0.3, w0) for _ in range(5)], _ways(ds)
+            out[k] = [_solve(ds, LOSS_LR, 0.3, w0) for _ in range(sum(solves))], _ways(ds)[1]   # (some in one launch, some beside others: none given up)
             ds.close()
 
     for k in range(len(problems)):
