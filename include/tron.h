@@ -366,8 +366,8 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  *   other threads that leave no room for it, as 1), or as a launch per product (0; sparse problems: driven by the host), or as a
  *   launch per product with the same bits as one launch (1).
  * "solve_wait_us" (-1..10000000): how long a workgroup of such a launch waits for the others before it gives up and the
- *   solve starts again with a launch per product: microseconds, 0 not at all, -1 (default) a tenth of a second.  After the
- *   k-th give-up in a row a handle's next 2^(k-1) solves do not try one launch.
+ *   solve starts again as with "solve_resident" = 1: microseconds, -1 (default) a tenth of a second, 0 not at all (and then as with
+ *   "solve_resident" = 0).  After the k-th give-up in a row a handle's next 2^(k-1) solves do not try one launch.
  * "batch_grid" (0..4096): workgroups of the multi-problem pass (0 = as many as are resident at once).
  * "batch_mfma_rows" (0/32/64): rows of X a wavefront of the matrix-unit pass keeps in LDS at a time (0: 32, except 64
  *                in the L2-SVM's rounds without function / gradient requests).

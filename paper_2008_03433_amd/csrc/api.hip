@@ -143,7 +143,7 @@ GridSync grid_sync(const tron_dataset *ds)
     return GridSync{ds->sync_words, us < 0 ? kResidentWaitUs * kTicksPerUs : us == 0 ? -1 : us * kTicksPerUs};
 }
 
-bool resident_possible(tron_dataset *ds, int grid) { return g_tuning.solve_resident != 0 && grid <= ds->cus && ds->resident.try_it(g_tuning.solve_wait_us); }
+bool resident_possible(const tron_dataset *ds, int grid) { return g_tuning.solve_resident != 0 && grid <= ds->cus; }
 
 namespace {
 struct ResidentPool {
@@ -162,21 +162,30 @@ ResidentShare::ResidentShare(const tron_dataset *ds, int grid, int turns)
     ResidentPool &p = g_resident[device_ % kPools];
     std::unique_lock<std::mutex> lock(p.m);
     p.wanted += grid_;
-    granted_ = g_tuning.solve_resident < 0 && (2 * grid_ <= ds->device_cus || p.wanted <= turns * ds->device_cus);
+    granted_ = turns > 0 && g_tuning.solve_resident < 0 && (2 * grid_ <= ds->device_cus || p.wanted <= turns * ds->device_cus);
     if (!granted_) return;
     p.freed.wait(lock, [&] { return p.used == 0 || p.used + grid_ <= ds->device_cus; });
     p.used += grid_;
 }
 
-ResidentShare::~ResidentShare()
+void ResidentShare::give_back()
 {
+    if (!granted_) return;
     ResidentPool &p = g_resident[device_ % kPools];
     {
         std::lock_guard<std::mutex> lock(p.m);
-        p.wanted -= grid_;
-        if (granted_) p.used -= grid_;
+        p.used -= grid_;
     }
-    if (granted_) p.freed.notify_all();
+    granted_ = false;
+    p.freed.notify_all();
+}
+
+ResidentShare::~ResidentShare()
+{
+    give_back();
+    ResidentPool &p = g_resident[device_ % kPools];
+    std::lock_guard<std::mutex> lock(p.m);
+    p.wanted -= grid_;
 }
 
 static int check_labels(const double *y, int64_t n)

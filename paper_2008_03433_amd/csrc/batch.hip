@@ -1179,7 +1179,7 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     bool done = false;
     const int grid = dense_round_grid(ds->n, ds->d, Q.loss);
     std::optional<ResidentShare> share;
-    if (resident_possible(ds, grid)) share.emplace(ds, grid, 1);
+    if (resident_possible(ds, grid)) share.emplace(ds, grid, ds->resident.try_it(g_tuning.solve_wait_us) ? 1 : 0);
     if (share && share->granted()) {
         drv.host->finished = 0;
         TRON_TRY(dense_solve_launch(ds, P, drv, 0, w_dev, C));
@@ -1195,7 +1195,7 @@ int dense_device_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
         }
         done = ended();   // otherwise workgroups gave up waiting for others before the first of them had the result; w0 is as it was
         ds->resident.ended(done);
-        share.reset();
+        share->give_back();
     }
     if (!done) {
         TRON_TRY(launch_begin(ds, drv, 1, BEGIN_SOLVE, w_dev, &C));

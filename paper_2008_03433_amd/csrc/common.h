@@ -279,6 +279,7 @@ struct CsrSolver;
 struct ResidentRecord {
     int64_t done = 0, given_up = 0, skip = 0, wait_us = -1;
     int in_a_row = 0;
+    bool no_room = false;   // the last work space found none
     bool try_it(int64_t wait_now)
     {
         if (wait_now != wait_us) {
@@ -384,11 +385,11 @@ HostFlag next_flag(tron_dataset *ds);
 int wait_results(tron_dataset *ds);
 
 // Launches whose workgroups wait for each other (grid_sync.h).  resident_possible: whether `grid` workgroups can be resident
-// together, one per compute unit, and the handle's last solves have not been given up (asked once a solve).
+// together, one per compute unit.
 // ResidentShare: the call's place among the solves of this process on the device.  Granted: the launch and those under way have no
 // more workgroups than there are compute units, so that two solves on two streams cannot each hold a part of the GPU and wait for the
 // rest.  (A stream with a mask of compute units: it has the device to itself, as theirs may lie on the same ones.)  Where there is no room the
-// constructor waits for it; but solves that fill more than half the GPU and together would fill it more than `turns` times go on
+// constructor waits for it (turns = 0: the solve wants none); but solves that fill more than half the GPU and together would fill it more than `turns` times go on
 // without (not granted: a launch per step or round, same results), because those of several streams fill each other's gaps.
 // us a solve with 1, 2, 3, 4, 8 threads at it, in turns / this way / (before there was one launch):
 //   dense, 100,000 x 24     54 53 53 53 54   / 55 45 64 40 38    / (108 81 62 39 41)
@@ -399,12 +400,13 @@ int wait_results(tron_dataset *ds);
 // 40 to 49 workgroups: in turns 33 to 37 us with 4 and 8 threads (42 and 60 to 170 before).
 struct GridSync;
 GridSync grid_sync(const tron_dataset *ds);
-bool resident_possible(tron_dataset *ds, int grid);
+bool resident_possible(const tron_dataset *ds, int grid);
 class ResidentShare {
 public:
     ResidentShare(const tron_dataset *ds, int grid, int turns);
     ~ResidentShare();
     bool granted() const { return granted_; }
+    void give_back();   // the room, before the solve goes on another way
     ResidentShare(const ResidentShare &) = delete;
     ResidentShare &operator=(const ResidentShare &) = delete;
 private:

@@ -1074,15 +1074,20 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     const int cus = std::min(ds->cus, kMaxResidentGrid), grid = std::min(most, cus);
     const int teams = std::min(kMaxTeams, (most + grid - 1) / grid);
     if (most > kMaxRounds * grid * teams || !resident_possible(ds, grid)) return 0;
+    // Where one launch is not to be tried, or is given up, the steps are launches of their own: the same bits.  (Without any wait, or without
+    // room for the work space, the host drives the solve.)
+    const bool one = ds->resident.try_it(g_tuning.solve_wait_us), steps = g_tuning.solve_wait_us != 0 || g_tuning.solve_resident > 0;
+    if (!one && (!steps || ds->resident.no_room)) return 0;
     const int cap = std::min(res->trace_cap, Q.max_outer);
-    const int space = ensure_space(ds, cap);
-    if (space == TRON_ENOMEM) {   // no room beside the matrix: the host-driven solve needs less
+    int rc = ensure_space(ds, cap);
+    ds->resident.no_room = rc == TRON_ENOMEM;
+    if (rc == TRON_ENOMEM) {   // the host-driven solve needs less
         (void)hipGetLastError();
         csr_resident_release(ds);
         ds->resident.ended(false);
         return 0;
     }
-    if (space != TRON_OK) return space;
+    if (rc != TRON_OK) return rc;
     CsrSolver &W = *ds->csr_solver;
     CsrSolveArgs A = W.args;
     A.w0 = w_dev;
@@ -1102,16 +1107,25 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     A.steps = kStepsPerLaunch;
     ds->have_D = false;
     {
-        const ResidentShare share(ds, grid, most <= grid * teams ? 1 : 2);
+        ResidentShare share(ds, grid, one ? (most <= grid * teams ? 1 : 2) : 0);
         W.host->stamp = 0;
-        const int rc = share.granted() ? solve_resident(ds, W, A, grid, teams) : solve_in_steps(ds, W, A, grid, teams);
-        if (rc == TRON_ENOMEM) {
-            (void)hipGetLastError();
-            return 0;
+        rc = 0;
+        if (share.granted()) {
+            rc = solve_resident(ds, W, A, grid, teams);
+            if (rc < 0) return rc;
+            ds->resident.ended(rc > 0);
+            share.give_back();
         }
-        if (rc < 0) return rc;
-        if (share.granted()) ds->resident.ended(rc > 0);
-        if (rc == 0) return 0;
+        if (rc == 0) {
+            if (!steps) return 0;
+            TRON_TRY(ensure_space(ds, cap));   // (places of a solve that was given up are cleared)
+            rc = solve_in_steps(ds, W, A, grid, teams);
+            if (rc == TRON_ENOMEM) {
+                (void)hipGetLastError();
+                return 0;
+            }
+            if (rc < 0) return rc;
+        }
     }
     const CsrState &S = W.host->st;
     if (!A.out) {

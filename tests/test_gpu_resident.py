@@ -325,6 +325,28 @@ def test_sparse_solve_of_many_steps_goes_on_in_further_launches(rng, knob):
         ds.close()
 
 
+@pytest.mark.parametrize("name", ["columns", "two rounds", "three rounds"])
+def test_sparse_solves_whose_wait_is_short_have_the_bits_of_one_launch(knob, name):
+    """A limit of a microsecond, which some of the waits exceed and some do not: whether a solve is given up in the middle, is not tried or
+    ends as one launch, its bits are the same."""
+    torch = torch_mod()
+    q = _sparse(np.random.default_rng(3), **ONE_LAUNCH[name])
+    if name == "three rounds":
+        knob("csr_segmented", 1)
+    ds = tron.Dataset.from_problem(q)
+    w0 = torch.zeros(q.d, dtype=torch.float64, device="cuda")
+    try:
+        one = _solve(ds, LOSS_LR, 0.3, w0)
+        for _ in range(3):
+            knob("solve_wait_us", 1)
+            for _ in range(6):
+                assert _solve(ds, LOSS_LR, 0.3, w0) == one
+            knob("solve_wait_us", -1)
+            assert _solve(ds, LOSS_LR, 0.3, w0) == one
+    finally:
+        ds.close()
+
+
 @pytest.mark.parametrize("shapes", [("two rounds", "columns", "both", "plain"), ("two rounds", "three rounds", "two rounds")])
 def test_sparse_solves_of_threads_that_fill_the_gpu_have_the_bits_they_have_alone(shapes):
     """Several grids of all compute units, and one of them among small ones."""
