@@ -1194,18 +1194,10 @@ int64_t dense_fun_grad_bytes(const tron_dataset *ds)
     return 8 * ds->n * ds->d + ds->n + d_bytes(ds->n, ds->d, mask) + 8 * ds->d * grid;
 }
 
-// The flag of a call: up to 2 GB, a pass of 0.33 ms.  Beyond, the 5.5 us that it saves are lost in the spread.
-static HostFlag call_flag(tron_dataset *ds)
-{
-    if ((double)ds->n * (double)ds->d * 8.0 <= 2e9) return next_flag(ds);
-    ds->flagged = false;
-    return HostFlag{nullptr, 0};
-}
-
 int dense_hv(tron_dataset *ds, double C, int Dslot, const double *v, double *Hv)
 {
     const HvInput in = hv_input(ds, Dslot);
-    const DenseFinish fin{ds->ticket, v, C, Hv, v, ds->scal_dev, ds->scal_copy, false, call_flag(ds)};
+    const DenseFinish fin{ds->ticket, v, C, Hv, v, ds->scal_dev, ds->scal_copy, false, next_flag(ds)};
     {
         ProfScope ps(ds, SLOT_DENSE_HV);
         TRON_TRY(dispatch_hv(ds, in, v, ds->partials, fin));
@@ -1246,7 +1238,7 @@ int dense_fun_grad(tron_dataset *ds, int loss, double C, const double *w, int Ds
     double *loss_partials = ds->partials + ds->d * grid;
     double *col_partials = loss_partials + grid;
     double *active_partials = col_partials + ds->d;
-    const DenseFinish fin{ds->ticket, w, C, g, nullptr, ds->scal_dev, ds->scal_copy, true, call_flag(ds)};
+    const DenseFinish fin{ds->ticket, w, C, g, nullptr, ds->scal_dev, ds->scal_copy, true, next_flag(ds)};
     {
         ProfScope ps(ds, SLOT_DENSE_FUN_GRAD);
         TRON_TRY(dispatch_fg(ds, loss, w, Dout, loss_partials, active_partials, fin));
