@@ -38,7 +38,9 @@ constexpr int kTeamLds = kProdDoubles + kPlainRows;   // (segments: 9/8 kChunk p
 static_assert(kOutOffset + kChunk / 8 * 9 <= kTeamLds, "products of a chunk of segments");
 constexpr int kMaxResidentGrid = 256;
 constexpr int kLine = 16;            // words of 8 bytes
-constexpr int64_t kOutInKernel = 1 << 16;   // the first workgroup copies the result out; longer ones are a copy operation
+// Results of up to so many columns are copied out by the first workgroup, longer ones by a copy operation behind the launch.  us a solve of 1M
+// entries, workgroup / operation: 5,000 columns 457 / 464, 12,000 469 / 470, 24,000 492 / 488, 47,000 523 / 503, 100,000 612 / 557.
+constexpr int64_t kOutInKernel = 12'288;
 constexpr int kStepsPerLaunch = 512;         // some milliseconds; a longer solve goes on in another launch
 
 // one orientation of the matrix (see CsrPlan)
@@ -887,8 +889,9 @@ __global__ __launch_bounds__(kBlock) void k_clear(uint64_t *places, int64_t n)
 }
 
 // Layouts of large matrices (several column ranges, values left out) stay with a launch per product, whose workgroups keep four times
-// as many wavefronts on a compute unit: the more rounds of chunks, the less there is to gain.  us a solve, driven by the host / in one
-// launch: five rounds (3.4M entries) 2345 / 2200, three (2M) 1720 / 1525, two (1M) 950 / 860, less than one 220 / 115.  Rows longer than a
+// as many wavefronts on a compute unit: the more rounds of chunks, the less there is to gain.  us a solve (a handle's first one), driven by
+// the host / in one launch, Zipf-distributed columns: 623 chunks 998 / 888 (1026 / 936), 1064 1286 / 1087 (1339 / 1167), 1402 1568 / 1252,
+// 1712 1623 / 1441 (1739 / 1549), 2146 1957 / 1798 (2064 / 1954); uniform ones: 2283 524 / 503 (614 / 587), 2420 483 / 417 (584 / 527).  Rows longer than a
 // chunk among the plain layout's, which a launch of their own completes, and chunks of so many rows that the threads would go over
 // them one after the other are left to the host, too.
 constexpr int kMaxRounds = 5;
