@@ -8,16 +8,21 @@
 // A CG iteration is two steps: the direction p = z + beta p (z = r / M) is formed where it is gathered, from pairs (z, p) of the
 // iteration before, so that nothing waits for beta alone.
 //
-// What is read by other workgroups -- pairs, u -- goes through store_shared to one of kRing places in turn.  A place
-// is read with ordinary loads, which L2 and L1 may keep: no line of it has been read since it was written last, because every time the
-// places have been used up all wavefronts invalidate what their caches hold.  Everything else that changes belongs to one
-// workgroup, the one whose chunk holds the row's first entry (for rows longer than a chunk: workgroup l mod the grid for the l-th).
+// What other workgroups read is written with store_shared and read with ordinary loads, which L1 and L2 may keep: no load may find a line that
+// was filled before the last writing.  Pairs and u go to kRing places in turn: each time the places have been used up, one wavefront
+// of every workgroup invalidates what its caches hold (an acquire of device scope; a barrier of the workgroup behind it covers the other
+// wavefronts), and between two such fences a place is written once and read after that.  The trial point and D (for the
+// preconditioner) lie in the same places every time, with a fence of their own before the product that gathers from them.  A line that a
+// workgroup writes a part of must not come back with old neighbours: see store_shared.  Everything else that changes belongs to one workgroup, the one
+// whose chunk holds the row's first entry (for rows longer than a chunk: workgroup l mod the grid for the l-th), and is its own to read.
 //
 // Latencies bound it: a step is some 6 us with 49 chunks, 13 with 513 -- entries and the first gathers from beyond L2 2 to 5 us, row
 // sums and stores 1.5, long rows 2, the barrier 1.5 to 2.5, sums over the grid and the next decision 1.5.  Two chunks of 256 threads a
 // workgroup leave 256 registers a thread, which the fetched chunk, the row's vectors and nine sums fill; three chunks (168 registers)
 // are no faster although 513 chunks then need no second round, four spill.  us a solve, driven by the host / here: 100,000 entries
-// 220 / 115, 8,000 x 20,000 with 640,000 entries 300 / 197, 1.05M with Zipf-distributed columns 950 / 860, 3.4M 2345 / 2200.
+// 227 / 117, 264,000 230 / 139, 480,000 245 / 172, 1.05M with Zipf-distributed columns 955 / 864 (more at kMaxRounds).  The error of w
+// against sums in extended precision, over 576 solves of six shapes, is 0.95 +- 0.05 of the host-driven solve's (geometric mean of the ratios),
+// although p.p, p.Mp and s.Mp come from recurrences.
 // (Solves of several threads that together need more than the GPU: see ResidentShare in common.h, and PART_CHUNKS below.)
 #include <cmath>
 #include <new>

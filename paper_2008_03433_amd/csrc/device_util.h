@@ -173,6 +173,10 @@ __device__ __forceinline__ double block_sum(double v, double *lds)
 // them waits for the stores before it draws the ticket; the reader uses loads of device scope.  A fence of device scope
 // (__threadfence) would do as well, but it writes back the XCD's whole L2 for every workgroup: a pass over 1M x 24 rows by 512
 // workgroups took 59 us that way, by 2048 workgroups 119 us.
+// Solves of sparse problems in one launch (csr_solve.hip) read what was stored this way with ordinary loads.  They rely on the L2 taking a
+// store to a line that it does not hold without fetching the line's other bytes (a mask says which bytes it has): the next read
+// fetches the line, after all have written.  The memory model does not promise it; were it otherwise, a solve in one launch and the same one with a
+// launch per step, whose caches start empty, would differ, and the tests hold their bits together.
 template <typename T>
 __device__ __forceinline__ void store_shared(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ double load_shared(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -274,8 +278,9 @@ __device__ __forceinline__ double exp_nonpositive(double x)
     return ldexp(1.0 + fma(r * r, q, r), (int)k);
 }
 
-// 1 / x for x in [1, 2]: two Newton steps from the hardware's approximation (24 bits at least), the second of which rounds like
-// the division.  No scaling and no special cases: a division is eleven instructions.
+// 1 / x for x in [1, 2]: two Newton steps from the hardware's approximation (24 bits at least).  The second one corrects a value that is within
+// an ulp or two by a residual known to 2^-52 of itself, so what is rounded is the quotient to 2^-50 of an ulp: the division's result but
+// for quotients that close to the middle between two numbers.  No scaling and no special cases: a division is eleven instructions.
 __device__ __forceinline__ double reciprocal_1_2(double x)
 {
     double r = __builtin_amdgcn_rcp(x);

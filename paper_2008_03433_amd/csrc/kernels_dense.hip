@@ -413,11 +413,11 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_fun_grad(int64_t n, in
 // stamp == 0: the whole solve in one launch of workgroups that are all resident.  Every workgroup keeps the problem's state in LDS,
 // adds all partial sums and takes the step itself (in the same order, so all hold the same bits): between two passes lies one
 // barrier over the grid.  Only the first workgroup reports.  A round of 20,000 x 24 takes 7.6 us (the pass with its tile in registers 2.3, the
-// barrier 2, the sums 1.5, the step 1.5), as a launch of its own 10 and the gaps; whole solves 95 -> 63 us, 1M x 24 229 -> 197,
-// 5M x 18 logistic 748 -> 730.
+// barrier 2, the sums 1.5, the step 1.5), as a launch of its own 10 and the gaps; whole solves 72 us with a launch per round, 50 in
+// one; 1M x 24 215 and 175 (144 to 188 from box to box); 5M x 18 logistic 748 and 706.
 // ONE: no wavefront has more than one tile (stamp == 0 only).
-// stamp > 0: round `stamp` of a solve with a launch per round (grids of more workgroups than CUs, or a part of the GPU
-// busy otherwise): the workgroup that finishes last adds the sums and takes the step, the state lies in device memory.  The
+// stamp > 0: round `stamp` of a solve with a launch per round (grids of more workgroups than CUs, solves of other threads that
+// leave no room, see ResidentShare, or a part of the GPU held otherwise): the workgroup that finishes last adds the sums and takes the step, the state lies in device memory.  The
 // same sums in the same order, the same results.
 struct SolveArgs {
     const double *X;

@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 
 import datagen as dg
+import paper_2008_03433_amd as tron
 from oracle import LOSS_LR, LOSS_L2SVM, Oracle
 
 pytestmark = pytest.mark.gpu
@@ -279,3 +280,32 @@ def test_config5_full_solve_properties():
         assert cosang > 0.999
     finally:
         tron.tron_dataset_destroy(h)
+
+
+def test_logistic_losses_of_more_than_512_tiles_a_wavefront():
+    """A lane's losses are kept as a product that is scaled every 256 tiles where it is large (LossSum); at w = 0 every row doubles it, so
+    that it is scaled from the 512th tile on: 72M rows over 2048 wavefronts have 550.  Bound: as in the multi-problem test of the same, and
+    the reference's sums in chunks of 4M."""
+    torch = torch_mod()
+    n, d, chunk = 72_000_000, 6, 4_000_000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(42)
+    ds = tron.Dataset(tron.tron_dataset_create_dense_empty(n, d))
+    try:
+        points = [torch.zeros(d, dtype=torch.float64, device="cuda"), 0.1 * torch.randn(d, generator=g, dtype=torch.float64, device="cuda")]
+        f = [0.5 * float(w @ w) for w in points]
+        grads = [w.clone() for w in points]
+        for row0 in range(0, n, chunk):
+            X = torch.randn(chunk, d, generator=g, dtype=torch.float64, device="cuda")
+            y = torch.where(torch.rand(chunk, generator=g, dtype=torch.float64, device="cuda") < 0.5, 1.0, -1.0).to(torch.float64)
+            tron.tron_dataset_write_rows(ds.handle, row0, chunk, X, y)
+            for k, w in enumerate(points):
+                t = y * (X @ w)
+                f[k] += float(torch.nn.functional.softplus(-t, threshold=1e9).sum())
+                grads[k] -= (X * (y * torch.sigmoid(-t))[:, None]).sum(0)
+        for k, w in enumerate(points):
+            got = torch.empty_like(w)
+            assert_scalar_close(ds.fun_grad(LOSS_LR, 1.0, w, got), f[k], rel=1e-13, what="f")
+            assert_vec_close(got.cpu().numpy(), grads[k].cpu().numpy(), what="g")
+    finally:
+        ds.close()
