@@ -247,8 +247,8 @@ TRON_API int tron_solve(tron_dataset *ds, const tron_params *params, double *w_d
  * Dense handles with d <= TRON_BATCH_MAX_D only (sparse handles and wider matrices: one tron_solve per problem).
  * Per tile of 64 instances the pass is two skinny matrix products (64 x d by d x K, and d x 64 by 64 x K).  They run
  * on the vector units, or as fp64 matrix instructions with the problems as the sixteen result columns: always above
- * eight problems, below that per loss where measured faster (L2-SVM: eight problems, logistic loss: five and more);
- * knob "batch_mfma".  Same results up to summation order.
+ * eight problems, below that per loss (L2-SVM: eight problems, logistic loss: five and more); knob "batch_mfma".
+ * Same results up to summation order.
  * ------------------------------------------------------------------------------------------ */
 typedef struct tron_batch tron_batch; /* opaque: membership bits, per-problem D, solver state, work space */
 

@@ -955,9 +955,11 @@ static int batch_create_impl(tron_dataset *ds, int K, const uint32_t *member, in
 #define TRON_B(expr) do { hipError_t e__ = (expr); if (e__ != hipSuccess) return fail(hip_fail(e__, #expr, __FILE__, __LINE__)); } while (0)
     if (!b->pass.fn[0]) { set_error("tron_batch_create: internal: no kernel for E=%d L=%d", s.E, s.L); return fail(TRON_EINVAL); }
     // The pass as matrix instructions (8 or 16 problem columns; the tile of X of every wavefront in LDS, and where logistic
-    // function / gradient requests are served the exchange area), chosen per loss: above eight problems always; otherwise
-    // where it is the faster one (measured at 20M x 24: the L2-SVM from eight problems on, the logistic loss -- whose
-    // vector kernel evaluates every problem's terms in every lane and spills -- from five).
+    // function / gradient requests are served the exchange area), chosen per loss: above eight problems always; otherwise by
+    // what was faster when the lines were drawn.  ms a Hessian / function-gradient round of 5, 6, 7, 8 problems over 20M x 24, vector units
+    // against matrix units.  L2-SVM: 0.75 0.76 0.81 0.87 / 0.80 0.87 0.93 1.00 against 0.79 0.80 0.81 0.81 / 1.03 1.04 1.05 1.04.  Logistic: 0.82 0.88
+    // 0.94 1.01 / 1.23 1.32 1.41 1.53 against 0.94 0.97 0.99 1.01 / 1.32 1.37 1.46 1.49 -- and 2.41 with six problems when its line was drawn,
+    // before LossSum: it would lie at eight now.
     const int mfma_from[2] = {5, 8};   // logistic, L2-SVM
     const int dmax = d <= 16 ? 16 : (d <= 24 ? 24 : 32);
     const size_t floor_lds = sizeof(double) * kWavesPerBlock * 32 * 16;   // the final sums of the four wavefronts
