@@ -231,7 +231,7 @@ typedef struct {
  * (knob "dense_device_driver").  Sparse problems of up to some five million entries (not partitioned by columns, up to 2560 chunks
  * of 2048 entries in either orientation) are solved in one launch, unless the profiler is on: same rules, same results up to
  * summation order (knob "solve_resident").  Solves of several threads on streams of their own share the GPU: those that
- * together need more than all of it run a launch per step instead, with the same results, or wait for room.
+ * together need more than all of it run a launch per step instead, with the same results, or wait for room (10 ms at most).
  */
 TRON_API int tron_solve(tron_dataset *ds, const tron_params *params, double *w_dev, tron_result *res_host);
 

@@ -1,5 +1,6 @@
 // C ABI entry points: dataset handles, argument checking, profiling, error text.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <condition_variable>
 #include <cstdarg>
@@ -153,6 +154,9 @@ struct ResidentPool {
     int used = 0;     // those of the launches whose workgroups wait for each other
 };
 constexpr int kPools = 64;
+// Several times what the longest solves in one launch take at a loose tolerance: those that take turns get theirs.  One that holds its room for
+// longer may have it for a launch that waits behind other work on its stream, for however long that takes.
+constexpr std::chrono::milliseconds kRoomWait{10};
 ResidentPool g_resident[kPools];
 }  // namespace
 
@@ -164,8 +168,8 @@ ResidentShare::ResidentShare(const tron_dataset *ds, int grid, int turns)
     p.wanted += grid_;
     granted_ = turns > 0 && g_tuning.solve_resident < 0 && (2 * grid_ <= ds->device_cus || p.wanted <= turns * ds->device_cus);
     if (!granted_) return;
-    p.freed.wait(lock, [&] { return p.used == 0 || p.used + grid_ <= ds->device_cus; });
-    p.used += grid_;
+    granted_ = p.freed.wait_for(lock, kRoomWait, [&] { return p.used == 0 || p.used + grid_ <= ds->device_cus; });
+    if (granted_) p.used += grid_;
 }
 
 void ResidentShare::give_back()

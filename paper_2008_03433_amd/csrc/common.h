@@ -390,7 +390,7 @@ int wait_results(tron_dataset *ds);
 // ResidentShare: the call's place among the solves of this process on the device.  Granted: the launch and those under way have no
 // more workgroups than there are compute units, so that two solves on two streams cannot each hold a part of the GPU and wait for the
 // rest.  (A stream with a mask of compute units: it has the device to itself, as theirs may lie on the same ones.)  Where there is no room the
-// constructor waits for it (turns = 0: the solve wants none); but solves that fill more than half the GPU and together would fill it more than `turns` times go on
+// constructor waits for it, kRoomWait at most (turns = 0: the solve wants none); but solves that fill more than half the GPU and together would fill it more than `turns` times go on
 // without (not granted: a launch per step or round, same results), because those of several streams fill each other's gaps.
 // us a solve with 1, 2, 3, 4, 8 threads at it, in turns / this way / (before there was one launch):
 //   dense, 100,000 x 24     54 53 53 53 54   / 55 45 64 40 38    / (108 81 62 39 41)

@@ -1,6 +1,7 @@
 """Solves in one launch, whose workgroups wait for each other inside the kernel, against the same solve with a launch per round."""
 import ctypes
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -93,6 +94,48 @@ def test_solves_of_several_threads_on_streams_of_their_own(rng):
     for t in threads:
         t.join()
     assert together == alone
+
+
+def test_a_small_solve_does_not_wait_for_what_another_thread_s_stream_is_busy_with():
+    """A solve that fills the GPU has its place from the call on, also while its launch waits behind other work of its stream (here one
+    thread that sleeps).  A small solve of another thread goes on without one launch then, with the same bits."""
+    torch = torch_mod()
+    rng = np.random.default_rng(13)
+    w0 = torch.zeros(24, dtype=torch.float64, device="cuda")
+    busy = torch.cuda.Stream()
+    with torch.cuda.stream(busy):
+        large = tron.Dataset.from_problem(_dense(rng, 120_000, 24))
+    small = tron.Dataset.from_problem(_dense(rng, 20_000, 24))
+    ends = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    try:
+        one = _solve(small, LOSS_LR, 0.3, w0)
+        with torch.cuda.stream(busy):
+            other = _solve(large, LOSS_LR, 0.3, w0)
+            torch.cuda._sleep(1000)   # its first launch takes longer
+            ends[0].record()
+            torch.cuda._sleep(10_000_000)
+            ends[1].record()
+        torch.cuda.synchronize()
+        per_second = 1e10 / ends[0].elapsed_time(ends[1])
+        results = []
+        w = w0.clone()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(int(0.5 * per_second))
+            ends[1].record()
+        thread = threading.Thread(target=lambda: results.append(large.solve(LOSS_LR, 0.3, 1e-4, w)))
+        thread.start()
+        time.sleep(0.1)   # the thread is in its solve
+        assert _solve(small, LOSS_LR, 0.3, w0) == one
+        asleep = not ends[1].query()
+        thread.join()
+        assert asleep
+        assert ends[1].query() and results[0].f == other[1] and w.cpu().numpy().tobytes() == other[0]
+        assert _ways(small) == (1, 0) and _ways(large) == (2, 0)
+    finally:
+        torch.cuda.synchronize()
+        large.close()
+        small.close()
 
 
 # one counter (up to 64 workgroups of 512 rows) and eight groups with one each
