@@ -92,6 +92,9 @@ struct CsrState {
 
 // What the host reads (pinned memory, kept with the scalars)
 constexpr int kHostRecords = 32;
+// The others go to device memory, as many places as the caller has, which stay with the handle: 64 MB at most.  Solves for more records are driven by
+// the host, which writes them to the caller's array itself.
+constexpr int kMaxRecords = 1 << 20;
 struct CsrHost {
     CsrState st;
     tron_trace_rec trace[kHostRecords];
@@ -1082,11 +1085,12 @@ int csr_resident_solve(tron_dataset *ds, const tron_params &Q, double *w_dev, tr
     const int cus = std::min(ds->cus, kMaxResidentGrid), grid = std::min(most, cus);
     const int teams = std::min(kMaxTeams, (most + grid - 1) / grid);
     if (most > kMaxRounds * grid * teams || !resident_possible(ds, grid)) return 0;
+    const int cap = std::min(res->trace_cap, Q.max_outer);
+    if (cap > kMaxRecords) return 0;
     // Where one launch is not to be tried, or is given up, the steps are launches of their own: the same bits.  (Without any wait, or without
     // room for the work space, the host drives the solve.)
     const bool one = ds->resident.try_it(g_tuning.solve_wait_us), steps = g_tuning.solve_wait_us != 0 || g_tuning.solve_resident > 0;
     if (!one && (!steps || ds->resident.no_room)) return 0;
-    const int cap = std::min(res->trace_cap, Q.max_outer);
     int rc = ensure_space(ds, cap);
     ds->resident.no_room = rc == TRON_ENOMEM;
     if (rc == TRON_ENOMEM) {   // the host-driven solve needs less

@@ -390,6 +390,39 @@ def test_sparse_solves_whose_wait_is_short_have_the_bits_of_one_launch(knob, nam
         ds.close()
 
 
+def _solve_with_records(ds, w0, many, records):
+    """A solve that may leave `many` records, few of which it will, in an array of fewer."""
+    from paper_2008_03433_amd import binding
+    w, res = w0.clone(), binding._Result()
+    res.trace_cap, res.trace = many, ctypes.addressof(records)
+    params = binding._Params(LOSS_LR, 0.3, 1e-4, many, 1000, 0.1, 0.0)
+    status = tron.load_library().tron_solve(ds.handle, ctypes.byref(params), w.data_ptr(), ctypes.byref(res))
+    trace = [{name: getattr(records[k], name) for name, _ in binding.TraceRec._fields_} for k in range(res.trace_len)]
+    return w.cpu().numpy().tobytes(), res.f, res.gnorm, res.outer_iters, res.cg_iters_total, status, trace
+
+
+def test_sparse_solve_with_room_for_any_number_of_records(knob):
+    """Up to a million records the work space holds them; for more the host drives the solve, and takes no memory for them."""
+    torch = torch_mod()
+    from paper_2008_03433_amd import binding
+    q = _sparse(np.random.default_rng(17), **ONE_LAUNCH["plain"])
+    ds = tron.Dataset.from_problem(q)
+    w0, records = torch.zeros(q.d, dtype=torch.float64, device="cuda"), (binding.TraceRec * 1000)()
+    try:
+        one = _solve(ds, LOSS_LR, 0.3, w0)
+        assert _solve_with_records(ds, w0, 2**20, records) == one and _ways(ds) == (2, 0)
+        knob("solve_resident", 0)
+        host = _solve(ds, LOSS_LR, 0.3, w0)
+        knob("solve_resident", -1)
+        free = torch.cuda.mem_get_info()[0]
+        for many in (2**20 + 1, 2**31 - 1):
+            assert _solve_with_records(ds, w0, many, records) == host and _ways(ds) == (2, 0)
+        assert torch.cuda.mem_get_info()[0] >= free - 2**27
+        assert _solve(ds, LOSS_LR, 0.3, w0) == one and _ways(ds) == (3, 0)
+    finally:
+        ds.close()
+
+
 @pytest.mark.parametrize("shapes", [("two rounds", "columns", "both", "plain"), ("two rounds", "three rounds", "two rounds")])
 def test_sparse_solves_of_threads_that_fill_the_gpu_have_the_bits_they_have_alone(shapes):
     """Several grids of all compute units, and one of them among small ones."""
