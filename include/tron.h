@@ -229,8 +229,8 @@ typedef struct {
  * Dense problems with d <= 32 and no preconditioner -- logistic loss: of any size; L2-SVM: matrices up to 1 GB -- are driven
  * from the device, like tron_batch_solve with one problem over all rows: same rules, same results up to summation order
  * (knob "dense_device_driver").  Sparse problems of up to some five million entries (not partitioned by columns, up to 2560 chunks
- * of 2048 entries in either orientation) are solved in one launch, unless the profiler is on: same rules, same results up to
- * summation order (knob "solve_resident").  Solves of several threads on streams of their own share the GPU: those that
+ * of 2048 entries in either orientation) are solved in one launch, unless the profiler is on or more than 2^20 records may be left:
+ * same rules, same results up to summation order (knob "solve_resident").  Solves of several threads on streams of their own share the GPU: those that
  * together need more than all of it run a launch per step instead, with the same results, or wait for room (10 ms at most).
  */
 TRON_API int tron_solve(tron_dataset *ds, const tron_params *params, double *w_dev, tron_result *res_host);
