@@ -109,7 +109,7 @@ TRON_API int tron_dataset_shape(const tron_dataset *ds, int64_t *n, int64_t *d, 
  *                              than a chunk of 2048 entries, segments: at most 8192 rows, empty ones included, a chunk)
  *   "fwd_csr_nnz", "bwd_csr_nnz"  nonzeros held in those CSR layouts
  *   "fwd_head_nnz"             of fwd_csr_nnz, the nonzeros of the head partition (the most frequent columns)
- *   "bwd_tile_nnz", "bwd_tile_rows", "bwd_tiles"  nonzeros, features and tiles of the hot-row tiles
+ *   "bwd_tile_nnz", "bwd_tile_rows", "bwd_tiles"  nonzeros and features of the hot rows; their tiles, or without values their pieces
  *   "fwd_lds_columns"          columns served from LDS tables in the forward pass
  *   "dense_grid"               groups of four wave tiles of the matrix, at most 2048 (the unit of tron_hv_static's limit)
  *   "dense_compact_rows"       rows of the compacted copy of the active rows the next tron_hv would run over (0: none)
@@ -335,7 +335,7 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  *   "csr_hot" (0/1): LDS tables of frequent columns in the forward layout;
  *   "csr_head" (0/1): a head partition for the most frequent columns of the whole matrix (needs csr_hot);
  *   "csr_range_slots" (2..4096): LDS table entries per column range;
- *   "csr_tiles" (0/1): hot-row tiles for the transposed product;
+ *   "csr_tiles" (0/1): hot-row tiles (without values: windows) for the transposed product;
  *   "csr_unit" (0/1): layouts without a value stream when every instance's entries share one value;
  *   "csr_sell" (0/1), "csr_sell_blocks" (1..4096): such a layout keeps its head partition as sorted slices of 64 rows,
  *                one row per lane, over the 16384 most frequent columns (0: as chunks like the other partitions, over

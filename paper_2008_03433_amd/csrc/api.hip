@@ -363,14 +363,19 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
     const bool partitioned = bwd_partitioned;
     if (g_tuning.csr_tiles && partitioned) {
         std::vector<std::pair<int64_t, int32_t>> cand;
+        // Without values the entries go to windows (HotWindows), where a feature costs a piece of eight places or more in nearly each of them:
+        // those with two entries a window or more.  us of the kernels of the transposed product of 2M x 3M, 123M entries, 128 windows, features from
+        // one / two / three / four entries a window on: windows 75 / 62 / 57 / 57, their sums 20 / 15 / 13 / 12, the other features 78 / 90 / 99 / 107.
+        const int64_t nwin = unit ? hot_windows_count(n) : 0;
+        const int64_t least = unit ? std::max<int64_t>(kTileMinCount, 2 * nwin) : kTileMinCount;
         for (int64_t j = 0; j < d; ++j)
-            if (t_rowptr[j + 1] >= kTileMinCount) cand.emplace_back(-t_rowptr[j + 1], (int32_t)j);
-        size_t keep = std::min<size_t>(cand.size(), (size_t)kTileSlices * kTileSlots);
+            if (t_rowptr[j + 1] >= least) cand.emplace_back(-t_rowptr[j + 1], (int32_t)j);
+        size_t keep = std::min<size_t>(cand.size(), unit ? std::min<int64_t>(kMaxPieceSlots, (1 << 30) / nwin) : (size_t)kTileSlices * kTileSlots);
         std::partial_sort(cand.begin(), cand.begin() + keep, cand.end());
         // A tile spans at most kTileWindow instances, so a slice has about n / kTileWindow of them however few entries
         // they hold, and a tile costs the kernel about as much as 400 entries cost the range kernels: where there are
         // many tiles they must be at least a quarter full on average, or the features stay in the CSR copy.
-        {
+        if (!unit) {
             int64_t entries = 0;
             for (size_t r = 0; r < keep; ++r) entries -= cand[r].first;
             const int64_t windows = (n + kTileWindow - 1) / kTileWindow * kTileSlices;
@@ -379,7 +384,7 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         if (keep > 0) {
             slot_code.assign((size_t)d, -1);
             for (size_t r = 0; r < keep; ++r) {
-                slot_code[cand[r].second] = (int32_t)((r % kTileSlices) * kTileSlots + r / kTileSlices);
+                slot_code[cand[r].second] = unit ? (int32_t)r : (int32_t)((r % kTileSlices) * kTileSlots + r / kTileSlices);
                 t_rowptr[cand[r].second + 1] = 0;   // no entries of this feature in the CSR copy
             }
             nhot = (int)keep;
@@ -497,7 +502,12 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
             set_error("%s", err_fwd.c_str());
         }
     }
-    if (rc >= 0 && nhot) rc = hot_tiles_build(ds->bwd, h_rowptr, h_col, h_val, slot_code, nhot, ds->stream);
+    if (rc >= 0 && nhot) {
+        try {
+            rc = unit ? hot_windows_build(ds->bwd, h_rowptr, h_col, slot_code, nhot, ds->stream)
+                      : hot_tiles_build(ds->bwd, h_rowptr, h_col, h_val, slot_code, nhot, ds->stream);
+        } catch (const std::bad_alloc &) { set_error("out of host memory building the hot rows"); rc = TRON_ENOMEM; }
+    }
     if (rc >= 0 && unit) {
         hipError_t e = hipMalloc(reinterpret_cast<void **>(&ds->unit_scale), sizeof(double) * (size_t)n);
         if (e == hipSuccess) e = hipMemcpyAsync(ds->unit_scale, row_value.data(), sizeof(double) * (size_t)n, hipMemcpyHostToDevice, ds->stream);

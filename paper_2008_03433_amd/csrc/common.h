@@ -38,7 +38,7 @@ struct Tuning {
     int64_t csr_hot_blocks_per_part = 96;  // persistent workgroups per partition when the LDS table is used
     int64_t csr_blocks_per_part = 128;     // persistent workgroups per column range without LDS tables
     int64_t csr_tiles = 1;   // hot-row tiles for the transposed orientation of partitioned matrices (0 = off)
-    int64_t csr_tile_blocks_per_slice = 0;   // persistent workgroups per slice of hot rows (0 = automatic: 96, or 160 for unit plans)
+    int64_t csr_tile_blocks_per_slice = 0;   // persistent workgroups per slice of hot rows (0 = automatic: 96)
     int64_t csr_sell_blocks = 1024;   // workgroups of the sorted-slice head kernel
     int64_t csr_sell = 1;    // unit plans: the head partition as sorted slices of 64 rows, one row per lane (0 = as chunks)
     int64_t csr_segmented = -1;  // unpartitioned layouts as segments + flag bits instead of plain CSR: 0 never, 1 always, -1 when a
@@ -148,23 +148,51 @@ constexpr int kTileSlots = 2048;    // hot rows per slice = LDS accumulators per
 constexpr int kTileMinCount = 32;   // rows with fewer entries stay in the CSR layout
 constexpr int kTileWindow = 512;    // columns a tile may span (the kernels copy them into LDS, two per thread)
 
+// Hot rows of a unit plan: windows instead of tiles.  A window is a range of up to kSellSlots consecutive columns, whose entries of x
+// fill a workgroup's LDS; a hot row's entries inside it are a piece (longer ones several), kept as 16-bit column offsets in sorted
+// slices of 64 pieces exactly like the head partition's rows (see SellHead): a lane sums a piece.  Every window has the same
+// numbering of pieces, its slots: one after the other those of a hot row, which never lie in two blocks of 64.  Slots are
+// sorted by the length of their pieces in groups of kSlotGroup; the sums lie in that order, and pos says where a slot's sum is.
+constexpr int kPieceEntries = kSellSlots / kWave;   // at most (so that a row has at most 64 of them in a window), unless there would be too
+                                                    // many slots for 16 bits
+constexpr int kMaxPieceSlots = 65535;
+constexpr int kSlotGroup = 1024;
+constexpr int kWindowBlocks = 256;    // workgroups: one per compute unit, shared out to the windows by their entries
+struct HotWindows {
+    bool on = false;
+    int nwin = 0;                 // windows
+    int width = 0;                // columns of a window (the last one has fewer)
+    int nslots = 0;               // slots of a window
+    int nblocks = 0;              // workgroups
+    int64_t ngroups = 0;          // as in SellHead
+    int64_t npieces = 0;          // pieces with entries
+    int32_t *window_of = nullptr; // device, nblocks: the workgroup's window
+    int64_t *wave_off = nullptr;  // device, 16 nblocks + 1
+    uint16_t *data = nullptr;     // device
+    int32_t *row_end = nullptr;   // device, nslots: the hot row whose last slot it is, or -1
+    uint16_t *pos = nullptr;      // device, nwin * nslots: place of the slot's sum in the window, from 1; 0: no entries
+    double *psums = nullptr;      // device, nwin * nslots
+    void release();
+};
+
 struct HotTiles {
-    int64_t nnz = 0;                     // entries held in tiles
-    int nhot = 0;                        // hot rows; row with rank r (by entry count) is slot r / 8 of slice r % 8
-    int64_t ntiles_total = 0;
+    int64_t nnz = 0;                     // entries held in tiles or windows
+    int nhot = 0;                        // hot rows; tiles: row with rank r (by entry count) is slot r / 8 of slice r % 8
+    HotWindows win;                      // unit plans; the members of the tiles are then unused but for slot_of_row and sums
+    int64_t ntiles_total = 0;            // (windows: pieces)
     int64_t tile0[kTileSlices] = {0};    // first tile of slice s
     int64_t ntiles[kTileSlices] = {0};
     int blocks_per_slice = 0;            // persistent workgroups per slice
     int64_t nseg_padded = 0;             // entries of seg_slot (every tile's block padded to a multiple of 8)
     int64_t span_total = 0;              // sum over the tiles of the columns they span (what the kernels copy into LDS)
-    double *val = nullptr;               // device, ntiles_total * kChunk (zero padded); null for a unit plan
+    double *val = nullptr;               // device, ntiles_total * kChunk (zero padded)
     uint16_t *iloc = nullptr;            // device, ntiles_total * kChunk: column minus the tile's first column
     uint8_t *flags = nullptr;            // device, ntiles_total * 256: bit e of byte t = entry 8t + e of the tile is the last of its segment
     int4 *hdr = nullptr;                 // device, per tile: {first column, segments, unused, index into seg_slot}
     uint16_t *seg_slot = nullptr;        // device: slot of every segment, tile by tile (a tile's block starts at a multiple of 8)
-    int32_t *slot_of_row = nullptr;      // device, rows: slice * kTileSlots + slot, or -1
+    int32_t *slot_of_row = nullptr;      // device, rows: where in sums, or -1
     double *wg_acc = nullptr;            // device, kTileSlices * blocks_per_slice * kTileSlots workgroup accumulators
-    double *sums = nullptr;              // device, kTileSlices * kTileSlots: per hot row, sum over its tiles
+    double *sums = nullptr;              // device: sums over the tiles at slice * kTileSlots + slot; over the windows by hot row
     void release();
 };
 
@@ -483,6 +511,9 @@ int csr_plan_build(CsrPlan &P, int64_t rows, int64_t cols, const int64_t *h_rowp
 // t_col = A's row ids).  slot_code[row] = slice * kTileSlots + slot for hot rows, -1 otherwise.
 int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, const double *t_val,
                     const std::vector<int32_t> &slot_code, int nhot, hipStream_t st);
+// The same as windows, for a unit plan: hot_of[row] = 0 .. nhot - 1 or -1.
+int hot_windows_count(int64_t cols);   // windows of a matrix with so many columns
+int hot_windows_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, const std::vector<int32_t> &hot_of, int nhot, hipStream_t st);
 // Products with one orientation; all enqueue on ds->stream.
 //   spmv_loss:  z = A x, then per-instance loss terms: zhat, D; partial slot 0 of ds->partials = sum loss
 //   spmv_scale: out = scale .* (A x)

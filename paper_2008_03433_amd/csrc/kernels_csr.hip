@@ -24,6 +24,7 @@
 // order and apply the epilogue (loss terms, D scaling, v + C * sum) and the first stage of the scalar
 // reductions.
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <exception>
 #include <thread>
@@ -37,8 +38,15 @@ constexpr int64_t kGatherBytesForPartitioning = 3 << 19;  // 1.5 MiB: larger gat
 constexpr int64_t kMinNnzForPartitioning = 1 << 22;
 constexpr int kHotMinCount = 8;   // columns with fewer entries are not worth an LDS slot
 
+void HotWindows::release()
+{
+    hipFree(window_of); hipFree(wave_off); hipFree(data); hipFree(row_end); hipFree(pos); hipFree(psums);
+    *this = HotWindows();
+}
+
 void HotTiles::release()
 {
+    win.release();
     hipFree(val); hipFree(iloc); hipFree(flags); hipFree(hdr); hipFree(seg_slot); hipFree(slot_of_row);
     hipFree(wg_acc); hipFree(sums);
     *this = HotTiles();
@@ -1087,19 +1095,11 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-__global__ __launch_bounds__(kSellBlock) void k_head_sell(int nwaves, const int64_t *__restrict__ wave_off, const uint16_t *__restrict__ data,
-                                                         const double *__restrict__ hot_x, double *__restrict__ sums)
+// the stream of one wavefront: groups g0 .. g1 of data, gathers from the table in LDS
+__device__ __forceinline__ void sell_stream(const double *table, const int64_t *__restrict__ wave_off, int w, const uint16_t *__restrict__ data,
+                                            double *__restrict__ sums)
 {
-    __shared__ __align__(16) double table[kSellSlots + 2];
-    {
-        const double2 *__restrict__ src = reinterpret_cast<const double2 *>(hot_x);
-        for (int k = threadIdx.x; k < kSellSlots / 2; k += kSellBlock) reinterpret_cast<double2 *>(table)[k] = src[k];
-        if (threadIdx.x == 0) table[kSellSlots] = 0.0;   // the padding slot
-        __syncthreads();
-    }
     const int lane = threadIdx.x & (kWave - 1);
-    const int w = blockIdx.x * (kSellBlock / kWave) + threadIdx.x / kWave;
-    if (w >= nwaves) return;
     // everything that steers the loop is kept in scalar registers: a branch on a vector condition would make the compiler
     // wait for every load in flight where the paths join
     const int64_t g0 = uniform64(wave_off[w]);
@@ -1140,6 +1140,75 @@ __global__ __launch_bounds__(kSellBlock) void k_head_sell(int nwaves, const int6
     }
 }
 
+constexpr int kSellWaves = kSellBlock / kWave;
+
+__global__ __launch_bounds__(kSellBlock) void k_head_sell(int nwaves, const int64_t *__restrict__ wave_off, const uint16_t *__restrict__ data,
+                                                         const double *__restrict__ hot_x, double *__restrict__ sums)
+{
+    __shared__ __align__(16) double table[kSellSlots + 2];
+    {
+        const double2 *__restrict__ src = reinterpret_cast<const double2 *>(hot_x);
+        for (int k = threadIdx.x; k < kSellSlots / 2; k += kSellBlock) reinterpret_cast<double2 *>(table)[k] = src[k];
+        if (threadIdx.x == 0) table[kSellSlots] = 0.0;   // the padding slot
+        __syncthreads();
+    }
+    const int w = blockIdx.x * kSellWaves + threadIdx.x / kWave;
+    if (w < nwaves) sell_stream(table, wave_off, w, data, sums);
+}
+
+// Hot rows of a unit plan (see HotWindows): the table is the window of x.  Bound by LDS gathers like the head's kernel: 62 us for 106M entries
+// of 23,000 features over 2M instances in 128 windows.  The tiles that hold such rows in plans with values (k_hot_tiles: segmented scans,
+// accumulators in LDS) took 105 us without values, for 103M entries of 16,384 features.
+__global__ __launch_bounds__(kSellBlock) void k_window_sell(const int32_t *__restrict__ window_of, int width, int64_t cols, const int64_t *__restrict__ wave_off,
+                                                           const uint16_t *__restrict__ data, const double *__restrict__ x, double *__restrict__ psums)
+{
+    __shared__ __align__(16) double table[kSellSlots + 2];
+    const int64_t c0 = (int64_t)window_of[blockIdx.x] * width;   // width is even
+    const int n = (int)(cols - c0 < width ? cols - c0 : width);
+    {
+        const double2 *__restrict__ src = reinterpret_cast<const double2 *>(x + c0);
+        for (int k = threadIdx.x; k < n / 2; k += kSellBlock) reinterpret_cast<double2 *>(table)[k] = src[k];
+        if (threadIdx.x == 0) {
+            if (n & 1) table[n - 1] = x[c0 + n - 1];
+            table[kSellSlots] = 0.0;   // the padding slot
+        }
+        __syncthreads();
+    }
+    sell_stream(table, wave_off, (int)(blockIdx.x * kSellWaves + threadIdx.x / kWave), data, psums);
+}
+
+// sums[h] = sum over the windows and slots of hot row h.  A workgroup has 64 slots: sixteen partial sums each (windows in order inside
+// each), added in order, then the slots of a row.  Some 7 us and the bytes of pos and psums at 4 TB/s (15 us for 128 windows of 25,000 slots; with
+// the sums of a group of slots read coalesced and exchanged in LDS, by 400 workgroups with a ticket a group: the same).
+__global__ __launch_bounds__(kSellBlock) void k_window_reduce(int nwin, int nslots, const int32_t *__restrict__ row_end, const uint16_t *__restrict__ pos,
+                                                             const double *__restrict__ psums, double *__restrict__ sums)
+{
+    __shared__ double part[kSellWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int v = blockIdx.x * kWave + lane;
+    const int per = (nwin + kSellWaves - 1) / kSellWaves;
+    const int w0 = wv * per, w1 = (w0 + per < nwin) ? w0 + per : nwin;
+    double a = 0.0;
+    if (v < nslots) {
+#pragma unroll 8
+        for (int w = w0; w < w1; ++w) {
+            const int p = pos[(int64_t)w * nslots + v];
+            const double t = psums[(int64_t)w * nslots + (p > 0 ? p - 1 : 0)];   // (without entries: whatever is there, not used)
+            a += p > 0 ? t : 0.0;
+        }
+    }
+    part[wv][lane] = a;
+    __syncthreads();
+    if (wv != 0) return;
+    double t = part[0][lane];
+#pragma unroll
+    for (int m = 1; m < kSellWaves; ++m) t += part[m][lane];
+    const int h = v < nslots ? row_end[v] : -1, before = lane_before(h);   // (asked for by all lanes)
+    int first = lane == 0 || before >= 0;
+    wave_seg_scan(t, first);
+    if (h >= 0) sums[h] = t;
+}
+
 template <bool HOT, bool HEAD, bool SQ, bool UNIT>
 __global__ __launch_bounds__(kBlock) void k_csr_spmv_part(PartArgs pa, int64_t rows, PartPtrs pp, const double *__restrict__ x)
 {
@@ -1159,7 +1228,6 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
     struct Entry { uint16_t slot, iloc; double val; };
     std::vector<Entry> cur[kTileSlices];
     int64_t base[kTileSlices] = {0};
-    const bool unit = A.unit;
     std::vector<double> tval[kTileSlices];
     std::vector<uint16_t> tiloc[kTileSlices];
     std::vector<uint8_t> tflags[kTileSlices];
@@ -1183,11 +1251,11 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
         }
         int4 h = make_int4((int)base[s], 0, 0, (int)sslot[s].size());
         const size_t off = tiloc[s].size();
-        if (!unit) tval[s].resize(off + kChunk, 0.0);   // off: a multiple of kChunk
+        tval[s].resize(off + kChunk, 0.0);   // off: a multiple of kChunk
         tiloc[s].resize(off + kChunk, 0);
         tflags[s].resize((off + kChunk) / 8, 0);
         for (size_t k = 0; k < e.size(); ++k) {
-            if (!unit) tval[s][val_pos(off + k)] = e[k].val;
+            tval[s][val_pos(off + k)] = e[k].val;
             tiloc[s][off + k] = e[k].iloc;
             if (k + 1 == e.size() || e[k + 1].slot != e[k].slot) {
                 tflags[s][(off + k) / 8] |= (uint8_t)(1u << (k % 8));
@@ -1235,7 +1303,7 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
                     const int code = ecode[k];
                     if (code == kNoCode || code / kTileSlots != s) continue;
                     ++nnz;
-                    cur[s].push_back({(uint16_t)(code % kTileSlots), (uint16_t)(i - base[s]), unit ? 1.0 : t_val[k]});
+                    cur[s].push_back({(uint16_t)(code % kTileSlots), (uint16_t)(i - base[s]), t_val[k]});
                 }
             }
             close_tile(s);
@@ -1276,7 +1344,7 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
         for (const int4 &h : hdrs[s]) H.span_total += h.z;
     if (ntiles == 0) return TRON_OK;
     if (nseg > 0x7ffffff0 || ntiles > 0x7ffffff0 / kChunk * 1024) { set_error("hot tiles too large"); return TRON_EINVAL; }
-    if (!unit) TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.val), sizeof(double) * ntiles * kChunk));
+    TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.val), sizeof(double) * ntiles * kChunk));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.iloc), sizeof(uint16_t) * ntiles * kChunk));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.flags), ntiles * kBlock));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.hdr), sizeof(int4) * ntiles));
@@ -1285,7 +1353,7 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
     for (int s = 0; s < kTileSlices; ++s) {
         const int64_t t0 = H.tile0[s];
         if (H.ntiles[s] == 0) continue;
-        if (!unit) TRON_HIP(hipMemcpyAsync(H.val + t0 * kChunk, tval[s].data(), sizeof(double) * tval[s].size(), hipMemcpyHostToDevice, st));
+        TRON_HIP(hipMemcpyAsync(H.val + t0 * kChunk, tval[s].data(), sizeof(double) * tval[s].size(), hipMemcpyHostToDevice, st));
         TRON_HIP(hipMemcpyAsync(H.iloc + t0 * kChunk, tiloc[s].data(), sizeof(uint16_t) * tiloc[s].size(), hipMemcpyHostToDevice, st));
         TRON_HIP(hipMemcpyAsync(H.flags + t0 * kBlock, tflags[s].data(), tflags[s].size(), hipMemcpyHostToDevice, st));
         TRON_HIP(hipMemcpyAsync(H.hdr + t0, hdrs[s].data(), sizeof(int4) * hdrs[s].size(), hipMemcpyHostToDevice, st));
@@ -1295,13 +1363,202 @@ int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, c
     TRON_TRY(upload(&H.slot_of_row, slot_code.data(), slot_code.size(), st));
     int64_t maxt = 0;
     for (int s = 0; s < kTileSlices; ++s) maxt = std::max(maxt, H.ntiles[s]);
-    // 0 = automatic: 3 workgroups per CU with values (the kernel is then bound by HBM), 5 without (as many as fit in LDS:
-    // the kernel is bound by instruction issue and LDS latency)
-    const int64_t want_blocks = g_tuning.csr_tile_blocks_per_slice > 0 ? g_tuning.csr_tile_blocks_per_slice : (A.unit ? 160 : 96);
+    // 0 = automatic: 3 workgroups per CU (the kernel is bound by HBM)
+    const int64_t want_blocks = g_tuning.csr_tile_blocks_per_slice > 0 ? g_tuning.csr_tile_blocks_per_slice : 96;
     H.blocks_per_slice = (int)std::max<int64_t>(1, std::min<int64_t>(maxt, std::min<int64_t>(want_blocks, kMaxTileBlocks)));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.wg_acc), sizeof(double) * kTileSlices * H.blocks_per_slice * kTileSlots));
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.sums), sizeof(double) * kTileSlices * kTileSlots));
     TRON_HIP(hipStreamSynchronize(st));
+    return TRON_OK;
+}
+
+// ------------------------------------------------------------------ hot rows of a unit plan as windows (see HotWindows)
+// As many windows as make, with a whole number of workgroups for each, nearly one workgroup per compute unit; beyond that many a
+// multiple, so that no round of workgroups is nearly empty.
+int hot_windows_count(int64_t cols)
+{
+    const int64_t least = std::max<int64_t>(1, (cols + kSellSlots - 1) / kSellSlots);
+    if (least > kWindowBlocks) return (int)((least + kWindowBlocks - 1) / kWindowBlocks * kWindowBlocks);
+    const int64_t most = std::max<int64_t>(1, cols / 2);   // (windows of two columns at least)
+    return (int)std::min<int64_t>(kWindowBlocks / (kWindowBlocks / least), most);
+}
+
+int hot_windows_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, const std::vector<int32_t> &hot_of, int nhot, hipStream_t st)
+{
+    HotTiles &H = A.hot;
+    HotWindows &Q = H.win;
+    const int64_t cols = A.cols;
+    const int width = (int)std::max<int64_t>(2, ((cols + hot_windows_count(cols) - 1) / hot_windows_count(cols) + 1) / 2 * 2);
+    const int nwin = (int)((cols + width - 1) / width);
+    static_assert(kSellSlots % 2 == 0, "an even width of at most kSellSlots");
+    // entries of every hot row in every window
+    std::vector<int32_t> count((size_t)nwin * nhot, 0);
+    std::vector<int64_t> win_nnz((size_t)nwin, 0);
+    const int64_t nnz = t_rowptr[cols];
+    auto for_windows = [&](auto &&fn) { parallel_ranges(nwin, nnz, [&](int64_t w0, int64_t w1) { for (int64_t w = w0; w < w1; ++w) fn(w); }); };
+    auto first_entry = [&](int64_t w) { return t_rowptr[std::min<int64_t>(w * width, cols)]; };
+    for_windows([&](int64_t w) {
+        int32_t *cnt = count.data() + (size_t)w * nhot;
+        int64_t all = 0;
+        for (int64_t k = first_entry(w); k < first_entry(w + 1); ++k) {
+            const int h = hot_of[t_col[k]];
+            if (h >= 0) { ++cnt[h]; ++all; }
+        }
+        win_nnz[(size_t)w] = all;
+    });
+    for (int64_t e : win_nnz) H.nnz += e;
+    if (H.nnz == 0) return TRON_OK;
+    // slots: the pieces of the row's fullest window
+    std::vector<int32_t> fullest((size_t)nhot, 0), slot0((size_t)nhot, 0);
+    for (int w = 0; w < nwin; ++w)
+        for (int h = 0; h < nhot; ++h) fullest[h] = std::max(fullest[h], count[(size_t)w * nhot + h]);
+    int most = kPieceEntries;
+    for (;; most *= 2) {
+        int64_t slots = 0;
+        for (int h = 0; h < nhot; ++h) slots += (fullest[h] + most - 1) / most * (fullest[h] > most ? 2 : 1);   // (half of a block may stay empty)
+        if ((slots <= kMaxPieceSlots && slots * nwin < 0x7ffffff0) || most >= kSellSlots) break;
+    }
+    std::vector<int32_t> row_end;
+    for (int several = 1; several >= 0; --several)
+        for (int h = 0; h < nhot; ++h) {
+            const int m = (fullest[h] + most - 1) / most;
+            if (m == 0 || (m > 1) != (several == 1)) continue;
+            while (row_end.size() % kWave + (size_t)m > kWave) row_end.push_back(-1);
+            slot0[h] = (int32_t)row_end.size();
+            row_end.resize(row_end.size() + (size_t)m, -1);
+            row_end.back() = h;
+        }
+    const int nslots = (int)row_end.size();
+    H.nhot = nhot;
+    if (nslots > kMaxPieceSlots) { set_error("internal: too many pieces of hot rows"); return TRON_EINVAL; }
+    // workgroups: one per window, and what is left of kWindowBlocks always to the window with the most entries per workgroup
+    std::vector<int32_t> blocks((size_t)nwin, 1);
+    {
+        std::vector<std::pair<double, int32_t>> heap;
+        for (int w = 0; w < nwin; ++w) heap.emplace_back((double)win_nnz[w], -w);
+        std::make_heap(heap.begin(), heap.end());
+        for (int left = kWindowBlocks - nwin; left > 0; --left) {
+            std::pop_heap(heap.begin(), heap.end());
+            const int w = -heap.back().second;
+            blocks[w] += 1;
+            heap.back().first = (double)win_nnz[w] / blocks[w];
+            std::push_heap(heap.begin(), heap.end());
+        }
+    }
+    std::vector<int32_t> block0((size_t)nwin + 1, 0), window_of;
+    for (int w = 0; w < nwin; ++w) {
+        block0[w + 1] = block0[w] + blocks[w];
+        window_of.insert(window_of.end(), (size_t)blocks[w], w);
+    }
+    Q.nblocks = block0[nwin];
+    // the slices of a window: its pieces by length (ties: by slot), 64 at a time, dealt to its wavefronts longest first, each to the one
+    // with the least work so far
+    struct Slice { int32_t first, len8, wave; int64_t at; };   // first: of its pieces; at: its header group in the window
+    std::vector<uint16_t> pos((size_t)nwin * nslots, 0);
+    std::vector<std::vector<Slice>> slices((size_t)nwin);
+    std::vector<std::vector<int32_t>> order((size_t)nwin);   // slots of the window's pieces, longest first
+    std::vector<int64_t> wave_len((size_t)Q.nblocks * kSellWaves, 0), win_pieces((size_t)nwin, 0);
+    std::atomic<bool> failed{false};
+    for_windows([&](int64_t w) {
+        try {
+            const int32_t *cnt = count.data() + (size_t)w * nhot;
+            // slots by (group, length); a group's slices begin with a piece of their own
+            std::vector<int32_t> length((size_t)nslots, 0), at((size_t)most + 2);
+            for (int h = 0; h < nhot; ++h)
+                for (int left = cnt[h], v = slot0[h]; left > 0; left -= most, ++v) length[v] = std::min(left, most);
+            std::vector<int32_t> &ord = order[(size_t)w];
+            for (int v0 = 0; v0 < nslots; v0 += kSlotGroup) {
+                const int v1 = std::min(nslots, v0 + kSlotGroup);
+                std::fill(at.begin(), at.end(), 0);
+                for (int v = v0; v < v1; ++v) ++at[(size_t)(most - length[v]) + 1];
+                for (int l = 0; l <= most; ++l) at[(size_t)l + 1] += at[(size_t)l];
+                const int used = at[(size_t)most];   // those with entries
+                ord.resize((size_t)v0 + (size_t)used, -1);
+                for (int v = v0; v < v1; ++v) {
+                    if (length[v] == 0) continue;
+                    const int q = at[(size_t)(most - length[v])]++;
+                    ord[(size_t)(v0 + q)] = v;
+                    pos[(size_t)w * nslots + v] = (uint16_t)(v0 + q + 1);
+                }
+                win_pieces[(size_t)w] += used;
+                ord.resize((size_t)v1, -1);
+            }
+            const int nw = blocks[w] * kSellWaves;
+            std::vector<std::pair<int64_t, int32_t>> heap;   // (-load, -wave)
+            for (int v = 0; v < nw; ++v) heap.emplace_back(0, -v);
+            std::make_heap(heap.begin(), heap.end());
+            std::vector<std::pair<int32_t, int32_t>> by_length;   // (-groups, first piece)
+            static_assert(kSlotGroup % kWave == 0, "a slice belongs to one group");
+            for (int q = 0; q < nslots; q += kWave)
+                if (ord[(size_t)q] >= 0) by_length.emplace_back(-((length[ord[(size_t)q]] + 7) / 8), q);
+            std::sort(by_length.begin(), by_length.end());
+            for (const auto &e : by_length) {
+                std::pop_heap(heap.begin(), heap.end());
+                slices[(size_t)w].push_back({e.second, -e.first, -heap.back().second, -heap.back().first});
+                heap.back().first -= 1 - e.first;
+                std::push_heap(heap.begin(), heap.end());
+            }
+            for (const auto &e : heap) wave_len[(size_t)block0[w] * kSellWaves + (size_t)(-e.second)] = (-e.first + kSellAhead - 1) / kSellAhead * kSellAhead;
+        } catch (const std::exception &) {
+            failed = true;
+        }
+    });
+    if (failed) { set_error("out of host memory building the windows"); return TRON_ENOMEM; }
+    std::vector<int64_t> wave_off(wave_len.size() + 1, 0);
+    for (size_t k = 0; k < wave_len.size(); ++k) wave_off[k + 1] = wave_off[k] + wave_len[k];
+    Q.ngroups = wave_off.back();
+    for (int64_t e : win_pieces) Q.npieces += e;
+    H.ntiles_total = Q.npieces;
+    const HostArray<uint16_t> data((size_t)Q.ngroups * kWave * 8);
+    for_windows([&](int64_t w) {
+        try {
+            const size_t v0 = (size_t)block0[w] * kSellWaves, v1 = (size_t)block0[w + 1] * kSellWaves;
+            std::fill(data.data() + (size_t)wave_off[v0] * kWave * 8, data.data() + (size_t)wave_off[v1] * kWave * 8, (uint16_t)kSellSlots);
+            auto header = [&](int64_t group, int lane, int32_t where, int32_t groups) {
+                const int32_t hdr[4] = {where, groups, 0, 0};
+                std::memcpy(&data[((size_t)group * kWave + lane) * 8], hdr, sizeof(hdr));
+            };
+            std::vector<int64_t> used(v1 - v0, 0), start((size_t)nslots, 0);   // start: of the slot's lane in its slice's first group of entries
+            const std::vector<int32_t> &ord = order[(size_t)w];
+            for (const Slice &s : slices[(size_t)w]) {
+                const int64_t g = wave_off[v0 + (size_t)s.wave] + s.at;
+                used[(size_t)s.wave] = s.at + 1 + s.len8;
+                for (int l = 0; l < kWave; ++l) {
+                    const int q = s.first + l, v = q < nslots ? ord[(size_t)q] : -1;
+                    header(g, l, v >= 0 ? (int32_t)(w * nslots + q) : -1, s.len8);
+                    if (v >= 0) start[(size_t)v] = ((g + 1) * kWave + l) * 8;
+                }
+            }
+            for (size_t v = v0; v < v1; ++v)   // what is left of a stream: headers of slices without groups
+                for (int64_t g = wave_off[v] + used[v - v0]; g < wave_off[v + 1]; ++g)
+                    for (int l = 0; l < kWave; ++l) header(g, l, -1, 0);
+            std::vector<int32_t> done((size_t)nhot, 0);
+            for (int64_t i = w * width; i < std::min<int64_t>(cols, (w + 1) * width); ++i)
+                for (int64_t k = t_rowptr[i]; k < t_rowptr[i + 1]; ++k) {
+                    const int h = hot_of[t_col[k]];
+                    if (h < 0) continue;
+                    const int e = done[h]++, j = e % most;
+                    data[(size_t)start[(size_t)(slot0[h] + e / most)] + (size_t)(j / 8) * kWave * 8 + (size_t)(j % 8)] = (uint16_t)(i - w * width);
+                }
+        } catch (const std::exception &) {
+            failed = true;
+        }
+    });
+    if (failed) { set_error("out of host memory building the windows"); return TRON_ENOMEM; }
+    Q.nwin = nwin;
+    Q.width = width;
+    Q.nslots = nslots;
+    TRON_TRY(upload(&Q.window_of, window_of.data(), window_of.size(), st));
+    TRON_TRY(upload(&Q.wave_off, wave_off.data(), wave_off.size(), st));
+    TRON_TRY(upload(&Q.data, data.data(), (size_t)Q.ngroups * kWave * 8, st));
+    TRON_TRY(upload(&Q.row_end, row_end.data(), row_end.size(), st));
+    TRON_TRY(upload(&Q.pos, pos.data(), pos.size(), st));
+    TRON_TRY(upload(&H.slot_of_row, hot_of.data(), hot_of.size(), st));
+    TRON_HIP(hipMalloc(reinterpret_cast<void **>(&Q.psums), sizeof(double) * (size_t)nwin * nslots));
+    TRON_HIP(hipMalloc(reinterpret_cast<void **>(&H.sums), sizeof(double) * (size_t)nhot));
+    TRON_HIP(hipMemsetAsync(H.sums, 0, sizeof(double) * (size_t)nhot, st));
+    TRON_HIP(hipStreamSynchronize(st));
+    Q.on = true;
     return TRON_OK;
 }
 
@@ -1319,20 +1576,12 @@ struct TilePtrs {
     double *wg_acc;
 };
 
-// An entry of a tile is a 16-bit column offset, and a value unless the plan is a unit plan; thread t loads those of entries
-// 8t .. 8t+7 (see val_pos).  A tile spans at most kTileWindow columns: the workgroup copies them from x into
+// An entry of a tile is a 16-bit column offset and a value; thread t loads those of entries 8t .. 8t+7 (see val_pos).  A tile spans at most kTileWindow columns: the workgroup copies them from x into
 // LDS with two coalesced loads per thread and gathers from the copy -- the gathers of a tile go to a few hundred
 // consecutive doubles, and the vector memory pipeline, which handles about one lane of such a gather per clock, was
 // what bound this kernel when they went to x itself.
-template <bool UNIT>
-struct TileValues {
+struct TileRegs {
     v2d v[4];
-};
-template <>
-struct TileValues<true> {};
-
-template <bool UNIT>
-struct TileRegs : TileValues<UNIT> {
     v4i il;             // eight 16-bit local column offsets
     uint4 slots;        // slots of the segments 8*tid .. 8*tid+7 (16 bits each)
     unsigned flags;     // bit e: entry 8*tid + e is the last of its segment
@@ -1349,16 +1598,13 @@ __device__ __forceinline__ void lds_add(double *a, double v)
 }
 
 // the data of tile T, whose header is h; columns clamped to the tile's last one
-template <bool UNIT>
-__device__ __forceinline__ void load_tile(TileRegs<UNIT> &r, const TilePtrs &tp, const double *__restrict__ x, int4 h, int64_t T)
+__device__ __forceinline__ void load_tile(TileRegs &r, const TilePtrs &tp, const double *__restrict__ x, int4 h, int64_t T)
 {
     const int tid = threadIdx.x;
     r.hdr = h;
     r.il = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(tp.iloc + T * kChunk + 8 * tid));
-    if constexpr (!UNIT) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) r.v[m] = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(tp.val + T * kChunk + m * kQuarter + tid * 2));
-    }
+    for (int m = 0; m < 4; ++m) r.v[m] = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(tp.val + T * kChunk + m * kQuarter + tid * 2));
     r.flags = tp.flags[T * kBlock + tid];
     // slot blocks are padded to a multiple of 8; threads beyond the tile's segments re-read its first block
     const int nseg = h.y;
@@ -1370,8 +1616,7 @@ __device__ __forceinline__ void load_tile(TileRegs<UNIT> &r, const TilePtrs &tp,
     r.w[1] = xt[tid + kBlock < lastc ? tid + kBlock : lastc];
 }
 
-template <bool UNIT>
-__device__ __forceinline__ void store_window(double *window, const TileRegs<UNIT> &r)
+__device__ __forceinline__ void store_window(double *window, const TileRegs &r)
 {
     window[threadIdx.x] = r.w[0];
     window[threadIdx.x + kBlock] = r.w[1];
@@ -1380,9 +1625,9 @@ __device__ __forceinline__ void store_window(double *window, const TileRegs<UNIT
 // One tile: cur is reduced (its columns are in window[BUF]) while the data of the next tile of the workgroup, whose
 // header is ahead, are loaded into nxt; they are not waited for before the end of the step, where the columns go to
 // the other window buffer.  ahead becomes the header of the tile after that.
-template <int BUF, bool SQ, bool UNIT>
-__device__ __forceinline__ void tile_step(double *prod, uint16_t *slots, double *acc, double (*window)[kTileWindow], TileRegs<UNIT> &cur,
-                                          TileRegs<UNIT> &nxt, int4 &ahead, const TilePtrs &tp, const double *__restrict__ x,
+template <int BUF, bool SQ>
+__device__ __forceinline__ void tile_step(double *prod, uint16_t *slots, double *acc, double (*window)[kTileWindow], TileRegs &cur,
+                                          TileRegs &nxt, int4 &ahead, const TilePtrs &tp, const double *__restrict__ x,
                                           const int64_t Tn, const int64_t Tnn)
 {
     const int tid = threadIdx.x;
@@ -1401,12 +1646,10 @@ __device__ __forceinline__ void tile_step(double *prod, uint16_t *slots, double 
         p[2 * m] = window[BUF][two & 0xffffu];
         p[2 * m + 1] = window[BUF][two >> 16];
     }
-    if constexpr (!UNIT) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const double v = cur.v[e / 2][e % 2];
-            p[e] *= SQ ? v * v : v;
-        }
+    for (int e = 0; e < 8; ++e) {
+        const double v = cur.v[e / 2][e % 2];
+        p[e] *= SQ ? v * v : v;
     }
     if (8 * tid < nseg) *reinterpret_cast<uint4 *>(slots + 8 * tid) = cur.slots;
     int idx0;
@@ -1430,7 +1673,7 @@ __device__ __forceinline__ void tile_step(double *prod, uint16_t *slots, double 
 // Persistent workgroup (slice s, q): tiles q, q + B, ... of the slice, LDS accumulators for the slice's hot rows; two steps per
 // iteration so that the two sets of tile registers and the two window buffers swap roles without copies (indices clamped to
 // the last tile, so every step issues the same loads).  SQ: the values are squared.
-template <bool SQ, bool UNIT>
+template <bool SQ>
 __global__ __launch_bounds__(kBlock) void k_hot_tiles(TileArgs ta, int B, TilePtrs tp, const double *__restrict__ x)
 {
     __shared__ __align__(16) double prod[kOutOffset];   // the wavefront totals only
@@ -1446,14 +1689,14 @@ __global__ __launch_bounds__(kBlock) void k_hot_tiles(TileArgs ta, int B, TilePt
         const int64_t T0 = ta.tile0[s];
         const int64_t last = nt - 1;
         auto clampt = [&](int64_t t) { return T0 + (t < last ? t : last); };
-        TileRegs<UNIT> r0, r1;
+        TileRegs r0, r1;
         load_tile(r0, tp, x, load_uniform(tp.hdr + clampt(q)), clampt(q));
         int4 ahead = load_uniform(tp.hdr + clampt(q + B));
         store_window(window[0], r0);
         for (int64_t t = q; t < nt; t += 2 * (int64_t)B) {
-            tile_step<0, SQ, UNIT>(prod, slots, acc, window, r0, r1, ahead, tp, x, clampt(t + B), clampt(t + 2 * (int64_t)B));
+            tile_step<0, SQ>(prod, slots, acc, window, r0, r1, ahead, tp, x, clampt(t + B), clampt(t + 2 * (int64_t)B));
             if (t + B >= nt) break;
-            tile_step<1, SQ, UNIT>(prod, slots, acc, window, r1, r0, ahead, tp, x, clampt(t + 2 * (int64_t)B), clampt(t + 3 * (int64_t)B));
+            tile_step<1, SQ>(prod, slots, acc, window, r1, r0, ahead, tp, x, clampt(t + 2 * (int64_t)B), clampt(t + 3 * (int64_t)B));
         }
     }
     __syncthreads();
@@ -1500,16 +1743,25 @@ static int launch_hot_tiles(tron_dataset *ds, const CsrPlan &A, const double *x,
 {
     const HotTiles &H = A.hot;
     hipStream_t st = ds->stream;
+    if (H.win.on) {   // squares, if any, are in the scaled vector
+        const HotWindows &Q = H.win;
+        {
+            ProfScope ps(ds, SLOT_SPMV_TILES, st);
+            hipLaunchKernelGGL(k_window_sell, dim3(Q.nblocks), dim3(kSellBlock), 0, st, Q.window_of, Q.width, A.cols, Q.wave_off, Q.data, x, Q.psums);
+            TRON_HIP(hipGetLastError());
+        }
+        ProfScope ps(ds, SLOT_SPMV_TILE_REDUCE, st);
+        hipLaunchKernelGGL(k_window_reduce, dim3((Q.nslots + kWave - 1) / kWave), dim3(kSellBlock), 0, st, Q.nwin, Q.nslots, Q.row_end, Q.pos, Q.psums, H.sums);
+        TRON_HIP(hipGetLastError());
+        return TRON_OK;
+    }
     {
         ProfScope ps(ds, SLOT_SPMV_TILES, st);
-        if (A.unit)   // squares, if any, are in the scaled vector
-            hipLaunchKernelGGL((k_hot_tiles<false, true>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
-                               H.blocks_per_slice, tile_ptrs(H), x);
-        else if (square)
-            hipLaunchKernelGGL((k_hot_tiles<true, false>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
+        if (square)
+            hipLaunchKernelGGL(k_hot_tiles<true>, dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
                                H.blocks_per_slice, tile_ptrs(H), x);
         else
-            hipLaunchKernelGGL((k_hot_tiles<false, false>), dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
+            hipLaunchKernelGGL(k_hot_tiles<false>, dim3(kTileSlices * H.blocks_per_slice), dim3(kBlock), 0, st, tile_args(H),
                                H.blocks_per_slice, tile_ptrs(H), x);
         TRON_HIP(hipGetLastError());
     }
@@ -1940,9 +2192,11 @@ PlanBytes plan_bytes(const CsrPlan &A)
                (A.hot_ids ? 8 * (int64_t)A.P * A.range_slots : 0);
     if (A.hot.ntiles_total > 0) {
         const HotTiles &H = A.hot;
-        const int64_t acc = 8 * (int64_t)kTileSlices * H.blocks_per_slice * kTileSlots;
-        b.tiles = H.ntiles_total * (kChunk * (2 + vbytes) + kBlock + (int64_t)sizeof(int4)) + 2 * H.nseg_padded + 8 * H.span_total + acc;
-        b.tile_reduce = acc + 8 * (int64_t)kTileSlices * kTileSlots;
+        const HotWindows &Q = H.win;
+        const int64_t acc = Q.on ? 8 * Q.npieces : 8 * (int64_t)kTileSlices * H.blocks_per_slice * kTileSlots;
+        if (Q.on) b.tiles = Q.ngroups * kWave * 16 + 8 * (int64_t)kSellWaves * Q.nblocks + 8 * (int64_t)Q.width * Q.nblocks + acc;
+        else b.tiles = H.ntiles_total * (kChunk * (2 + vbytes) + kBlock + (int64_t)sizeof(int4)) + 2 * H.nseg_padded + 8 * H.span_total + acc;
+        b.tile_reduce = Q.on ? acc + 2 * (int64_t)Q.nwin * Q.nslots + 8 * (int64_t)H.nhot : acc + 8 * (int64_t)kTileSlices * kTileSlots;
     }
     if (A.direct) {   // row ranges and segment numbers, addend and result, no partial sums
         b.ranges += 4 * A.rows + 16 * A.rows - 8 * nseg_ranges;
