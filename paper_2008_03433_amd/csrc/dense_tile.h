@@ -5,6 +5,21 @@
 
 namespace tron {
 
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+// Matrices that do not fit the 256 MB cache in front of HBM are read with non-temporal loads, at 7.0 instead of 6.2 TB/s; a smaller one gains
+// nothing by it (TB/s of a plain sum over tiles of 12 KiB, ordinary / non-temporal loads: 192 MB 6.4 / 6.4, 256 MB 6.7 / 6.6, 288 MB 6.5 / 6.7, 512 MB
+// 6.0 / 6.9, 2 GB 6.2 / 7.0, 8 GB 6.3 / 7.1), but then a line must be fetched by one instruction as a whole: where an instruction reads pieces of 64 bytes of
+// rows, the same loads lose a quarter (2 GB of rows of 24: 5.5 / 4.8).  So
+//   - rows of 9 to 32 columns (two and four lanes a row) go through LDS, a tile at a time in memory order (TileStream), 6.9 TB/s.  us a
+//     call or solve, straight into registers / through LDS: 230M x 24 Hessian-vector 7110 / 6410; 5M x 18 136 and 128 (logistic and L2-SVM)
+//     / 125 and 118, function/gradient 156 and 135 / 141 and 121, logistic solve 704 / 652; 10M x 9 137 / 126 and 161 / 151;
+//   - rows over 16 lanes or more are loaded as they are, non-temporally: 240,000 x 512 181 / 160 us a Hessian-vector call, 200,003 x 257 82 / 75; but
+//     60,000 x 512 (246 MB) 50 / 53, 40,000 x 127 22 / 24.
+constexpr int64_t kOnceDoubles = 36'000'000;   // 288 MB
+__host__ __device__ inline bool read_once(int64_t n, int64_t d) { return n * d > kOnceDoubles; }
+constexpr bool tiles_stream(int L) { return L == 2 || L == 4; }
+
 // A wave tile of RT = U * 64 / L rows.  A row is covered by L consecutive lanes; lane q of them holds the columns
 // col(q, 0) .. col(q, E - 1): pieces of one or two columns (8 or 16 bytes) dealt to the L lanes in turn, so that one
 // load instruction reads L consecutive pieces of a row and the next one the pieces behind them.  (With E consecutive columns
@@ -41,23 +56,42 @@ struct Tile {
     __device__ static __forceinline__ void load(const double *__restrict__ X, int64_t n, int64_t d, int64_t row0,
                                                 int lane, double (&x)[U][E], uint64_t rows = ~0ull)
     {
+        if constexpr (L >= 16) {
+            if (read_once(n, d)) {   // uniform
+                load_as<true>(X, n, d, row0, lane, x, rows);
+                return;
+            }
+        }
+        load_as<false>(X, n, d, row0, lane, x, rows);
+    }
+
+    template <bool once>
+    __device__ static __forceinline__ void load_as(const double *__restrict__ X, int64_t n, int64_t d, int64_t row0,
+                                                   int lane, double (&x)[U][E], uint64_t rows)
+    {
         const int q = lane % L, rl = lane / L;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t row = row0 + u * RW + rl;
             const bool rok = row < n && ((rows >> (u * RW + rl)) & 1u);
             const double *p = X + row * d;
+            auto pg = (const __attribute__((address_space(1))) double *)p;
+            if constexpr (once) asm volatile("" : "+v"(pg));   // (otherwise the compiler makes one ordinary load of this one and the other instance's)
             if (VEC) {
 #pragma unroll
                 for (int e = 0; e < E; e += 2) {
                     double2 t = make_double2(0.0, 0.0);
-                    if (rok && col(q, e) < d) t = *reinterpret_cast<const double2 *>(p + col(q, e));
+                    if constexpr (once) {
+                        v2d o = v2d{0.0, 0.0};
+                        if (rok && col(q, e) < d) o = __builtin_nontemporal_load((const __attribute__((address_space(1))) v2d *)(pg + col(q, e)));
+                        t = make_double2(o.x, o.y);
+                    } else if (rok && col(q, e) < d) t = *reinterpret_cast<const double2 *>(p + col(q, e));
                     x[u][e] = t.x;
                     x[u][e + 1] = t.y;
                 }
             } else {
 #pragma unroll
-                for (int e = 0; e < E; ++e) x[u][e] = (rok && col(q, e) < d) ? p[col(q, e)] : 0.0;
+                for (int e = 0; e < E; ++e) x[u][e] = !(rok && col(q, e) < d) ? 0.0 : once ? __builtin_nontemporal_load(pg + col(q, e)) : p[col(q, e)];
             }
         }
     }
@@ -121,6 +155,81 @@ struct Tile {
             for (int k = 0; k < waves; ++k) s += lds[k * (E * L) + c];
             store_shared(out + c * stride, s);
         }
+    }
+};
+
+// Tiles of 64 rows through LDS: ask() has the wavefront's next tile copied there by loads that write LDS directly, a kilobyte in memory
+// order each, and take() reads it into the registers of Tile.  A tile of which a part is past the end, or that was not asked for, is
+// loaded as ever.  One buffer a wavefront: it is asked for again as soon as it has been read, so that eight wavefronts a CU
+// have 512 d bytes each on their way all the time, during the arithmetic as well.
+template <int E, int L, int U, bool VEC>
+struct TileStream {
+    using T = Tile<E, L, U, VEC>;
+    double *buf;          // the wavefront's 64 d doubles, 16-byte aligned; null: every tile is loaded straight into registers
+    bool there = false;   // the tile asked for is in LDS or on its way
+
+    static constexpr int64_t bytes(int64_t d, int waves) { return 512 * d * waves; }
+    __device__ __forceinline__ TileStream(double *lds, int64_t d)   // lds: the workgroup's, or null
+        : buf(lds ? lds + 64 * d * __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : nullptr) {}
+
+    // nothing may be on its way but what take() has waited for
+    __device__ __forceinline__ void ask(const double *__restrict__ X, int64_t n, int64_t d, int64_t tile, bool wanted)
+    {
+        if constexpr (tiles_stream(L)) {
+            static_assert(T::RT == kWave, "");
+            there = __builtin_amdgcn_readfirstlane((int)(buf != nullptr && wanted && (tile + 1) * kWave <= n));
+            if (!there) return;
+            const int lane = threadIdx.x & (kWave - 1);
+            const double *src = X + tile * kWave * d + 2 * lane;
+            const int whole = (int)(d / 2);   // kilobytes
+#pragma unroll
+            for (int k = 0; k < (E * L + 1) / 2; ++k)
+                if (k < whole) copy(src + 128 * k, buf + 128 * k);
+            if ((d & 1) && lane < kWave / 2) copy(src + 128 * whole, buf + 128 * whole);
+        }
+    }
+
+    __device__ __forceinline__ void take(const double *__restrict__ X, int64_t n, int64_t d, int64_t tile, int lane, double (&x)[U][E], uint64_t rows = ~0ull)
+    {
+        if (!tiles_stream(L) || !there) {
+            T::load(X, n, d, tile * T::RT, lane, x, rows);
+            wait_loads();   // here, or the compiler waits for these registers where both ways have joined, behind the next ask()
+            return;
+        }
+        wait_loads();
+        const int q = lane % L, rl = lane / L;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double *p = buf + (u * T::RW + rl) * d;
+            if (VEC) {
+#pragma unroll
+                for (int e = 0; e < E; e += 2) {
+                    v2d t = v2d{0.0, 0.0};
+                    if (T::col(q, e) < d) t = *reinterpret_cast<const v2d *>(p + T::col(q, e));
+                    x[u][e] = t.x;
+                    x[u][e + 1] = t.y;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) x[u][e] = T::col(q, e) < d ? p[T::col(q, e)] : 0.0;
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): in registers, before the buffer is asked for again
+        asm volatile("" ::: "memory");
+        there = false;
+    }
+
+    __device__ static __forceinline__ void wait_loads()
+    {
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        asm volatile("" ::: "memory");
+    }
+
+private:
+    __device__ static __forceinline__ void copy(const double *from, double *to)
+    {
+        constexpr int kNonTemporal = 2;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from, (__attribute__((address_space(3))) void *)to, 16, 0, kNonTemporal);
     }
 };
 

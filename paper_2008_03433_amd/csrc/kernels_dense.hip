@@ -19,6 +19,7 @@
 // workgroups of 24 columns.  Wider matrices take a launch of k_dense_columns, one workgroup per 16 columns.  Nothing is added
 // in an order that depends on timing.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include "dense_tile.h"
@@ -213,12 +214,13 @@ __device__ __forceinline__ void store_D(T *p, T v)
 // DIAG: column sums of D_i x_ij^2 instead (the diagonal of X^T D X; v is not read).
 // SKIP (with the bit words only): rows outside the active set are not read.  Chosen by the host when a noticeable
 // part of the rows is inactive; with (almost) every row active the plain loop is about 1% faster.
+// STREAM: X comes through LDS (TileStream; every row is read).
 // SOLVE: the pass is one of several in a launch.  All of them then deal the tiles out alike, so that a wavefront reads the D that
 // it wrote itself.
 // lds: E * L doubles per wavefront
-template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP, bool SOLVE = false>
+template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP, bool STREAM, bool SOLVE = false>
 __device__ __forceinline__ void hv_pass(double *lds, int64_t n, int64_t d, const double *__restrict__ X, const void *__restrict__ Dv,
-                                        const double *__restrict__ v, double *__restrict__ partials)
+                                        const double *__restrict__ v, double *__restrict__ partials, double *stream_lds)
 {
     constexpr int kWaves = dense_block(L) / kWave;
     const double *D = static_cast<const double *>(Dv);
@@ -241,59 +243,84 @@ __device__ __forceinline__ void hv_pass(double *lds, int64_t n, int64_t d, const
     constexpr int G = tiles_at_once(E, L, MASK);
     const TileWalk walk(ntiles, kWaves, SOLVE && kBits);
     const int64_t tile0 = walk.first, last = walk.last, nwaves = walk.step;
-    uint64_t bits_next[G];
+    // the products of a tile whose rows' D are in Drow
+    auto add_tile = [&](const double (&x)[U][E], double Drow) {
+        double c[U];
+        if (DIAG) {
+            T::from_row_owner(Drow, c);
 #pragma unroll
-    for (int g = 0; g < G; ++g) bits_next[g] = (kBits && SKIP && tile0 + g * nwaves < last) ? Dbits[tile0 + g * nwaves] : 0;
-    for (int64_t tile = tile0; tile < last; tile += G * nwaves) {
-        double x[G][U][E], Drow[G], c[U];
-        uint64_t bits[G], any = 0;
-        if (kBits && SKIP) {
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = fma(c[u] * x[u][e], x[u][e], acc[e]);
+            }
+        } else {
+            T::from_row_owner(Drow * T::row_sum(x, vreg, lane), c);   // a1 = D (X v)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[u][e], acc[e]);
+            }
+        }
+    };
+    if constexpr (STREAM) {
+        static_assert(!SKIP, "");
+        TileStream<E, L, U, VEC> stream(stream_lds, d);
+        // D of a tile travels with its rows
+        uint64_t bits = 0;
+        double Drow = 0.0;
+        auto ask = [&](int64_t t) {
+            stream.ask(X, n, d, t, t < last);
+            if (kBits) bits = t < last ? Dbits[t] : 0;
+            else if (t < last && t * T::RT + own < n) Drow = MASK ? (Dm[t * T::RT + own] ? 2.0 : 0.0) : D[t * T::RT + own];
+            else Drow = 0.0;
+        };
+        ask(tile0);
+        for (int64_t tile = tile0; tile < last; tile += nwaves) {
+            double x[U][E];
+            stream.take(X, n, d, tile, lane, x);
+            const double mine = kBits ? (((bits >> own) & 1u) ? 2.0 : 0.0) : Drow;
+            ask(tile + nwaves);
+            add_tile(x, mine);
+        }
+    } else {
+        uint64_t bits_next[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) bits_next[g] = (kBits && SKIP && tile0 + g * nwaves < last) ? Dbits[tile0 + g * nwaves] : 0;
+        for (int64_t tile = tile0; tile < last; tile += G * nwaves) {
+            double x[G][U][E], Drow[G];
+            uint64_t bits[G], any = 0;
+            if (kBits && SKIP) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int64_t ahead = tile + (G + g) * nwaves;
+                    bits[g] = bits_next[g];
+                    any |= bits[g];
+                    bits_next[g] = (ahead < last) ? Dbits[ahead] : 0;
+                }
+                if (any == 0) continue;   // no active row in the tiles
+            }
+            // tiles past the last one: every row is past n
+#pragma unroll
+            for (int g = 0; g < G; ++g) T::load(X, n, d, ((SOLVE && tile + g * nwaves >= last) ? ntiles : tile + g * nwaves) * T::RT, lane, x[g], (kBits && SKIP) ? bits[g] : ~0ull);
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int64_t ahead = tile + (G + g) * nwaves;
-                bits[g] = bits_next[g];
-                any |= bits[g];
-                bits_next[g] = (ahead < last) ? Dbits[ahead] : 0;
-            }
-            if (any == 0) continue;   // no active row in the tiles
-        }
-        // tiles past the last one: every row is past n
-#pragma unroll
-        for (int g = 0; g < G; ++g) T::load(X, n, d, ((SOLVE && tile + g * nwaves >= last) ? ntiles : tile + g * nwaves) * T::RT, lane, x[g], (kBits && SKIP) ? bits[g] : ~0ull);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t t = tile + g * nwaves, row = t * T::RT + own;
-            if (kBits && !SKIP) bits[g] = (t < last) ? Dbits[t] : 0;
-            Drow[g] = 0.0;
-            if (kBits) {
-                Drow[g] = ((bits[g] >> own) & 1u) ? 2.0 : 0.0;
-            } else if (row < n) {
-                Drow[g] = MASK ? (Dm[row] ? 2.0 : 0.0) : D[row];
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (DIAG) {
-                T::from_row_owner(Drow[g], c);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-#pragma unroll
-                    for (int e = 0; e < E; ++e) acc[e] = fma(c[u] * x[g][u][e], x[g][u][e], acc[e]);
-                }
-            } else {
-                T::from_row_owner(Drow[g] * T::row_sum(x[g], vreg, lane), c);   // a1 = D (X v)
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-#pragma unroll
-                    for (int e = 0; e < E; ++e) acc[e] = fma(c[u], x[g][u][e], acc[e]);
+                const int64_t t = tile + g * nwaves, row = t * T::RT + own;
+                if (kBits && !SKIP) bits[g] = (t < last) ? Dbits[t] : 0;
+                Drow[g] = 0.0;
+                if (kBits) {
+                    Drow[g] = ((bits[g] >> own) & 1u) ? 2.0 : 0.0;
+                } else if (row < n) {
+                    Drow[g] = MASK ? (Dm[row] ? 2.0 : 0.0) : D[row];
                 }
             }
+#pragma unroll
+            for (int g = 0; g < G; ++g) add_tile(x[g], Drow[g]);
         }
     }
     T::flush(acc, d, lane, wv, kWaves, lds, partials + (int64_t)blockIdx.x * d, 1);
 }
 
-template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP>
+template <int E, int L, int U, bool VEC, bool MASK, bool DIAG, bool SKIP, bool STREAM>
 __global__ __launch_bounds__(dense_block(L)) void k_dense_hv(int64_t n, int64_t d, const double *__restrict__ X,
                                                                 const void *__restrict__ Dv, const double *__restrict__ v,
                                                                 double *__restrict__ partials, DenseFinish fin)
@@ -302,17 +329,18 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_hv(int64_t n, int64_t 
     __shared__ double lds[dense_lds(E, L)];
     // the counter of k_dense_columns starts at zero whatever an earlier call left in it
     if constexpr (!dense_finishes(L)) { if (blockIdx.x == 0 && threadIdx.x == 0) *fin.ticket = 0u; }
-    hv_pass<E, L, U, VEC, MASK, DIAG, SKIP>(lds, n, d, X, Dv, v, partials);
+    extern __shared__ __align__(16) double stream_lds[];
+    hv_pass<E, L, U, VEC, MASK, DIAG, SKIP, STREAM>(lds, n, d, X, Dv, v, partials, stream_lds);
     if constexpr (dense_finishes(L)) { if (fin.ticket) dense_finish<kWaves>(lds, fin, (int)d, partials, nullptr, nullptr); }
 }
 
 // ------------------------------------------------------------------ function / gradient pass
 // lds as in hv_pass, lds_red: two rows of one double per wavefront
-template <int E, int L, int U, bool VEC, int LOSS>
+template <int E, int L, int U, bool VEC, int LOSS, bool STREAM>
 __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[dense_block(L) / kWave], int64_t n, int64_t d,
                                               const double *__restrict__ X, const int8_t *__restrict__ y, const double *__restrict__ w,
                                               void *__restrict__ Dv, double *__restrict__ partials,
-                                              double *__restrict__ loss_partials, double *__restrict__ active_partials)
+                                              double *__restrict__ loss_partials, double *__restrict__ active_partials, double *stream_lds)
 {
     using T = Tile<E, L, U, VEC>;
     constexpr int kWaves = dense_block(L) / kWave;
@@ -339,12 +367,26 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
     const TileWalk walk(ntiles, kWaves, kBits);
     const int64_t first = walk.first, last = walk.last, step = walk.step;
     int it = 0;
+    TileStream<E, L, U, VEC> stream(STREAM ? stream_lds : nullptr, d);
+    int8_t label = 1;   // of the lane's row of a tile that comes through LDS: travels with it
+    // logistic D of the tile before: stored before the next tile is asked for, as the wait for that one is a wait for the store, too
+    double D_held = 0.0;
+    int64_t D_row = -1;
+    auto ask = [&](int64_t t) {
+        if (!STREAM) return;
+        label = t < last && t * T::RT + own < n ? y[t * T::RT + own] : 1;
+        stream.ask(X, n, d, t, t < last);
+    };
+    ask(first);
     for (int64_t tile = first; tile < last; tile += step, ++it) {
         const int64_t row0 = tile * T::RT;
         double x[U][E], c[U];
-        T::load(X, n, d, row0, lane, x);
+        if (STREAM) stream.take(X, n, d, tile, lane, x);
+        else T::load(X, n, d, row0, lane, x);
         const bool in = row0 + own < n, mine = in && T::first_owner(lane);
-        const double yrow = in ? (double)y[row0 + own] : 1.0;
+        if (STREAM && !kBits && D_row >= 0) store_D<L>(Dout + D_row, D_held);
+        const double yrow = STREAM ? (double)label : in ? (double)y[row0 + own] : 1.0;
+        ask(tile + step);
         const double z = T::row_sum(x, wreg, lane);           // z = X w
         LossTerm alpha;
         double zhat, Di;
@@ -364,6 +406,9 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
                 store_shared(Dbits + held_tile, held_bits);   // every lane holds one: 64 consecutive words
                 held_tile = -1;
             }
+        } else if (STREAM) {
+            D_held = Di;
+            D_row = mine ? row0 + own : -1;
         } else if (mine) {
             if (LOSS == TRON_LOSS_L2SVM) store_D<L>(Dmask + row0 + own, (uint8_t)(Di != 0.0 ? 1 : 0));
             else store_D<L>(Dout + row0 + own, Di);
@@ -377,6 +422,7 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
         }
     }
     if (kBits && held_tile >= 0) store_shared(Dbits + held_tile, held_bits);
+    if (STREAM && !kBits && D_row >= 0) store_D<L>(Dout + D_row, D_held);
     if (dense_finishes(L)) stores_arrived();   // before the workgroup's ticket: the host goes on when the last one has been drawn
     const double loss_acc = wave_sum(losses.value());
     active_acc = wave_sum(active_acc);
@@ -393,7 +439,7 @@ __device__ __forceinline__ void fun_grad_pass(double *lds, double (*lds_red)[den
     }
 }
 
-template <int E, int L, int U, bool VEC, int LOSS>
+template <int E, int L, int U, bool VEC, int LOSS, bool STREAM>
 __global__ __launch_bounds__(dense_block(L)) void k_dense_fun_grad(int64_t n, int64_t d, const double *__restrict__ X,
                                                                       const int8_t *__restrict__ y, const double *__restrict__ w,
                                                                       void *__restrict__ Dv, double *__restrict__ partials,
@@ -403,7 +449,8 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_fun_grad(int64_t n, in
     constexpr int kWaves = dense_block(L) / kWave;
     __shared__ double lds[dense_lds(E, L)];
     __shared__ double lds_red[2][kWaves];
-    fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, y, w, Dv, partials, loss_partials, active_partials);
+    extern __shared__ __align__(16) double stream_lds[];
+    fun_grad_pass<E, L, U, VEC, LOSS, STREAM>(lds, lds_red, n, d, X, y, w, Dv, partials, loss_partials, active_partials, stream_lds);
     if constexpr (dense_finishes(L)) dense_finish<kWaves>(lds, fin, (int)d, partials, loss_partials, active_partials);
 }
 
@@ -415,7 +462,7 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_fun_grad(int64_t n, in
 // barrier over the grid.  Only the first workgroup reports.  A round of 20,000 x 24 takes 7.6 us (the pass with its tile in registers 2.3, the
 // barrier 2, the sums 1.5, the step 1.5), as a launch of its own 10 and the gaps; whole solves 72 us with a launch per round, 50 in
 // one; 1M x 24 215 and 175 (144 to 188 from box to box); 5M x 18 logistic 748 and 706.
-// ONE: no wavefront has more than one tile (stamp == 0 only).
+// ROWS_KEPT: no wavefront has more than one tile (stamp == 0 only).
 // stamp > 0: round `stamp` of a solve with a launch per round (grids of more workgroups than CUs, solves of other threads that
 // leave no room, see ResidentShare, or a part of the GPU held otherwise): the workgroup that finishes last adds the sums and takes the step, the state lies in device memory.  The
 // same sums in the same order, the same results.
@@ -508,10 +555,11 @@ struct OneTile {
 // same order.  x holds the wavefront's first tile already where `loaded` is set: it was asked for before the wait for the other
 // workgroups, which saves 2 us of a pass of 27 (1M x 24).  The logistic loss keeps its two loops: one for both took 730 us a solve of
 // 5M x 18 instead of 718.
-template <int E, int L, int U, bool VEC>
+template <int E, int L, int U, bool VEC, bool STREAM>
 __device__ __forceinline__ void svm_solve_pass(double *lds, double (*lds_red)[dense_block(L) / kWave], const bool fg, int64_t n, int64_t d,
                                                const double *__restrict__ X, const int8_t *__restrict__ y, const double *vec, uint64_t *Dbits,
-                                               double *__restrict__ partials, double *__restrict__ loss_partials, double (&x)[U][E], const bool loaded)
+                                               double *__restrict__ partials, double *__restrict__ loss_partials, double (&x)[U][E], const bool loaded,
+                                               TileStream<E, L, U, VEC> &stream)
 {
     using T = Tile<E, L, U, VEC>;
     constexpr int kWaves = dense_block(L) / kWave;
@@ -530,19 +578,38 @@ __device__ __forceinline__ void svm_solve_pass(double *lds, double (*lds_red)[de
     uint64_t held_bits = 0, bnext = (!fg && walk.first < walk.last) ? Dbits[walk.first] : 0;
     int64_t held_tile = -1;
     int it = 0;
+    constexpr int kLeastActive = 48;
+    // through LDS: the word of the tile after the next one, too, as the next one's says how its rows come
+    uint64_t bnext2 = (STREAM && !fg && walk.first + 1 < walk.last) ? Dbits[walk.first + 1] : 0;
+    int8_t label = STREAM && fg && walk.first < walk.last && walk.first * T::RT + own < n ? y[walk.first * T::RT + own] : 1;
+    auto ask = [&](int64_t t) {
+        if (!STREAM) return;
+        bnext = bnext2;
+        bnext2 = (!fg && t + 1 < walk.last) ? Dbits[t + 1] : 0;
+        if (fg) label = t < walk.last && t * T::RT + own < n ? y[t * T::RT + own] : 1;
+        stream.ask(X, n, d, t, t < walk.last && (fg || __popcll(bnext) >= kLeastActive));
+    };
     for (int64_t tile = walk.first; tile < walk.last; ++tile, ++it) {
         const int64_t row0 = tile * T::RT;
         const uint64_t bits = bnext;   // fetched one step ahead
-        bnext = (!fg && tile + 1 < walk.last) ? Dbits[tile + 1] : 0;
-        if (!fg && bits == 0) continue;   // no active row in the tile
-        if (it > 0 || !loaded) T::load(X, n, d, row0, lane, x, fg ? ~0ull : bits);
+        const int8_t label_there = label;
+        if (!STREAM) bnext = (!fg && tile + 1 < walk.last) ? Dbits[tile + 1] : 0;
+        if (STREAM && stream.there) {
+            stream.take(X, n, d, tile, lane, x);
+            ask(tile + 1);
+        } else {
+            ask(tile + 1);
+            if (!fg && bits == 0) continue;   // no active row in the tile
+            if (STREAM || it > 0 || !loaded) T::load(X, n, d, row0, lane, x, fg ? ~0ull : bits);
+            if (STREAM) stream.wait_loads();
+        }
         double c[U];
         const double z = T::row_sum(x, vreg, lane);
         if (fg) {   // uniform
             const bool in = row0 + own < n;
             LossTerm alpha;
             double zhat, Di;
-            loss_terms_dev<TRON_LOSS_L2SVM>(z, in ? (double)y[row0 + own] : 1.0, alpha, zhat, Di);
+            loss_terms_dev<TRON_LOSS_L2SVM>(z, STREAM ? (double)label_there : in ? (double)y[row0 + own] : 1.0, alpha, zhat, Di);
             if (in && T::first_owner(lane)) losses.add(alpha);
             const uint64_t word = T::ballot_rows(in && Di != 0.0, lane);
             if (lane == (it & (kWave - 1))) { held_bits = word; held_tile = tile; }
@@ -580,11 +647,12 @@ __device__ __forceinline__ void copy_words(T *dst, const T *src)
     for (int i = threadIdx.x; i < (int)(sizeof(T) / sizeof(uint64_t)); i += blockDim.x) reinterpret_cast<uint64_t *>(dst)[i] = reinterpret_cast<const uint64_t *>(src)[i];
 }
 
-template <int E, int L, int U, bool VEC, int LOSS, bool ONE>
+enum Rows { ROWS_LOADED = 0, ROWS_KEPT, ROWS_STREAMED };   // as a pass needs them, in registers (OneTile), through LDS
+template <int E, int L, int U, bool VEC, int LOSS, Rows ROWS>
 __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64_t d, SolveArgs A, SolveParams P, int64_t stamp)
 {
     constexpr int kWaves = dense_block(L) / kWave;
-    constexpr bool svm = LOSS == TRON_LOSS_L2SVM;
+    constexpr bool svm = LOSS == TRON_LOSS_L2SVM, ONE = ROWS == ROWS_KEPT, STREAM = ROWS == ROWS_STREAMED;
     __shared__ double lds[dense_lds(E, L)];
     __shared__ double lds_red[2][kWaves];
     __shared__ BatchCtl ctl;
@@ -607,7 +675,15 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
     const TileWalk walk((n + T::RT - 1) / T::RT, kWaves, true);
     OneTile<E, L, U, VEC, LOSS> mine;
     if constexpr (ONE) mine.load(n, d, X, A.y);
-    if (kAhead && whole && walk.first < walk.last) T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), mine.x);
+    extern __shared__ __align__(16) double stream_lds[];
+    TileStream<E, L, U, VEC> stream(STREAM ? stream_lds : nullptr, d);
+    // the wavefront's first tile, asked for ahead
+    auto first_tile = [&]() {
+        if (!kAhead || walk.first >= walk.last) return;
+        if (STREAM) stream.ask(X, n, d, walk.first, true);
+        else T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), mine.x);
+    };
+    if (whole) first_tile();
     bool done = false;
     for (int64_t round = 1;; ++round) {
         const int mode = __builtin_amdgcn_readfirstlane(ctl.mode[0]);
@@ -620,12 +696,14 @@ __global__ __launch_bounds__(dense_block(L)) void k_dense_solve(int64_t n, int64
         const int64_t at = (round & 1) * A.round_stride;
         double *partials = A.partials + at, *loss_partials = A.loss_partials + at;
         if constexpr (ONE) mine.pass(lds, lds_red, mode == MODE_FG, ctl.dslot[0], d, vec, D, partials, loss_partials);
-        else if constexpr (kAhead) svm_solve_pass<E, L, U, VEC>(lds, lds_red, mode == MODE_FG, n, d, X, A.y, vec, static_cast<uint64_t *>(D), partials, loss_partials, mine.x, whole);
-        else if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS>(lds, lds_red, n, d, X, A.y, vec, D, partials, loss_partials, nullptr);
-        else hv_pass<E, L, U, VEC, svm, false, svm, true>(lds, n, d, X, D, vec, partials);
+        else if constexpr (kAhead) {
+            uint64_t *words = static_cast<uint64_t *>(D);
+            svm_solve_pass<E, L, U, VEC, STREAM>(lds, lds_red, mode == MODE_FG, n, d, X, A.y, vec, words, partials, loss_partials, mine.x, whole, stream);
+        } else if (mode == MODE_FG) fun_grad_pass<E, L, U, VEC, LOSS, STREAM>(lds, lds_red, n, d, X, A.y, vec, D, partials, loss_partials, nullptr, stream_lds);
+        else hv_pass<E, L, U, VEC, svm, false, svm, STREAM, true>(lds, n, d, X, D, vec, partials, stream_lds);
         if (whole) {
             grid.arrive();
-            if (kAhead && walk.first < walk.last) T::load(X, n, d, walk.first * T::RT, threadIdx.x & (kWave - 1), mine.x);
+            first_tile();
             if (!grid.wait()) break;
         } else if (!last_workgroup(A.ticket)) {
             return;
@@ -781,6 +859,25 @@ HvInput hv_input(const tron_dataset *ds, int Dslot)
     return HvInput{ds->X, ds->n, ds->Dbuf[Dslot], mask, skip, few ? dense_grid_few(ds->n, ds->d) : ds->dense_grid};
 }
 
+// Workgroups that read X through LDS want more of it than the 64 KB that a launch has without asking
+template <auto Kernel>
+int allow_lds(int bytes)
+{
+    static std::atomic<uint64_t> asked{0};   // a bit per device
+    int dev = 0;
+    if (bytes <= 64 << 10) return TRON_OK;
+    TRON_HIP(hipGetDevice(&dev));
+    const uint64_t bit = 1ull << (dev & 63);
+    if (asked.load(std::memory_order_relaxed) & bit) return TRON_OK;
+    TRON_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)TileStream<8, 4, 4, true>::bytes(kFinishMaxD, dense_block(4) / kWave)));
+    asked.fetch_or(bit, std::memory_order_relaxed);
+    return TRON_OK;
+}
+
+// bytes of LDS through which a pass reads X
+template <int L>
+int stream_bytes(int64_t n, int64_t d) { return tiles_stream(L) && read_once(n, d) ? (int)(512 * d * (dense_block(L) / kWave)) : 0; }
+
 template <int E, int L>
 int launch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *partials, const DenseFinish &fin)
 {
@@ -789,8 +886,12 @@ int launch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *part
     const int grid = in.grid;
     const void *D = in.D;
     const bool mask = in.mask, skip = in.skip;
-#define TRON_HV(V, M, G, S) \
-    hipLaunchKernelGGL((k_dense_hv<E, L, U, V, M, G, S>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, in.n, ds->d, in.X, D, v, partials, fin)
+    const int through = skip && mask ? 0 : stream_bytes<L>(in.n, ds->d);
+#define TRON_HV_T(V, M, G, S, T) do { \
+        TRON_TRY((allow_lds<k_dense_hv<E, L, U, V, M, G, S, T>>(through))); \
+        hipLaunchKernelGGL((k_dense_hv<E, L, U, V, M, G, S, T>), dim3(grid), dim3(dense_block(L)), through, ds->stream, in.n, ds->d, in.X, D, v, partials, fin); \
+    } while (0)
+#define TRON_HV(V, M, G, S) do { if (through) TRON_HV_T(V, M, G, S, (tiles_stream(L) && !S)); else TRON_HV_T(V, M, G, S, false); } while (0)
 #define TRON_HV_V(M, G, S) do { if (vec) TRON_HV((E % 2 == 0), M, G, S); else TRON_HV(false, M, G, S); } while (0)
     if (v) {
         if (!mask) TRON_HV_V(false, false, false);
@@ -803,6 +904,7 @@ int launch_hv(tron_dataset *ds, const HvInput &in, const double *v, double *part
     }
 #undef TRON_HV_V
 #undef TRON_HV
+#undef TRON_HV_T
     return TRON_OK;
 }
 
@@ -812,14 +914,19 @@ int launch_fg(tron_dataset *ds, int loss, const double *w, void *Dout, double *l
     constexpr int U = pick_U(E, L);
     const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
     const int grid = dense_fun_grad_grid(ds->n, ds->d);
-#define TRON_FG(V, LS) \
-    hipLaunchKernelGGL((k_dense_fun_grad<E, L, U, V, LS>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, ds->X, ds->y8, w, Dout, ds->partials, loss_partials, active_partials, fin)
+    const int through = stream_bytes<L>(ds->n, ds->d);
+#define TRON_FG_T(V, LS, T) do { \
+        TRON_TRY((allow_lds<k_dense_fun_grad<E, L, U, V, LS, T>>(through))); \
+        hipLaunchKernelGGL((k_dense_fun_grad<E, L, U, V, LS, T>), dim3(grid), dim3(dense_block(L)), through, ds->stream, ds->n, ds->d, ds->X, ds->y8, w, Dout, ds->partials, loss_partials, active_partials, fin); \
+    } while (0)
+#define TRON_FG(V, LS) do { if (through) TRON_FG_T(V, LS, tiles_stream(L)); else TRON_FG_T(V, LS, false); } while (0)
     if (loss == TRON_LOSS_LR) {
         if (vec) TRON_FG((E % 2 == 0), TRON_LOSS_LR); else TRON_FG(false, TRON_LOSS_LR);
     } else {
         if (vec) TRON_FG((E % 2 == 0), TRON_LOSS_L2SVM); else TRON_FG(false, TRON_LOSS_L2SVM);
     }
 #undef TRON_FG
+#undef TRON_FG_T
     return TRON_OK;
 }
 
@@ -831,9 +938,15 @@ int launch_solve(tron_dataset *ds, const SolveParams &P, const SolveArgs &A, int
         const bool vec = (E % 2 == 0) && (ds->d % 2 == 0);
         const int grid = dense_round_grid(ds->n, ds->d, P.loss);
         const bool one = stamp == 0 && (ds->n + kWave - 1) / kWave <= (int64_t)grid * (dense_block(L) / kWave);
+        const int through = stream_bytes<L>(ds->n, ds->d);
+#define TRON_SOLVE_T(V, LS, R) do { \
+        TRON_TRY((allow_lds<k_dense_solve<E, L, U, V, LS, R>>(through))); \
+        hipLaunchKernelGGL((k_dense_solve<E, L, U, V, LS, R>), dim3(grid), dim3(dense_block(L)), through, ds->stream, ds->n, ds->d, A, P, stamp); \
+    } while (0)
 #define TRON_SOLVE(V, LS) do { \
-        if (one) hipLaunchKernelGGL((k_dense_solve<E, L, U, V, LS, true>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp); \
-        else hipLaunchKernelGGL((k_dense_solve<E, L, U, V, LS, false>), dim3(grid), dim3(dense_block(L)), 0, ds->stream, ds->n, ds->d, A, P, stamp); \
+        if (one) TRON_SOLVE_T(V, LS, ROWS_KEPT); \
+        else if (through) TRON_SOLVE_T(V, LS, (tiles_stream(L) ? ROWS_STREAMED : ROWS_LOADED)); \
+        else TRON_SOLVE_T(V, LS, ROWS_LOADED); \
     } while (0)
         if (P.loss == TRON_LOSS_LR) {
             if (vec) TRON_SOLVE((E % 2 == 0), TRON_LOSS_LR); else TRON_SOLVE(false, TRON_LOSS_LR);
@@ -841,6 +954,7 @@ int launch_solve(tron_dataset *ds, const SolveParams &P, const SolveArgs &A, int
             if (vec) TRON_SOLVE((E % 2 == 0), TRON_LOSS_L2SVM); else TRON_SOLVE(false, TRON_LOSS_L2SVM);
         }
 #undef TRON_SOLVE
+#undef TRON_SOLVE_T
         TRON_HIP(hipGetLastError());
         return TRON_OK;
     } else {
