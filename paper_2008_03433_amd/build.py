@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtron_hip.so")
-SOURCES = ["api.hip", "solver.hip", "kernels_vec.hip", "kernels_csr.hip", "csr_solve.hip", "kernels_dense.hip", "batch.hip"]
+SOURCES = ["api.hip", "solver.hip", "kernels_vec.hip", "kernels_csr.hip", "csr_build.hip", "csr_solve.hip", "kernels_dense.hip", "batch.hip"]
 HEADERS = ["common.h", "device_util.h", "csr_chunk.h", "dense_tile.h", "device_driver.h", "grid_sync.h", "host_util.h", os.path.join("..", "..", "include", "tron.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

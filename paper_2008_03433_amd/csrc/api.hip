@@ -218,14 +218,58 @@ static int fetch(std::vector<T> &dst, const T *src, size_t count)
 
 // csr_plan_build for either thread: running out of host memory is an error code
 static int plan_build(CsrPlan &P, int64_t rows, int64_t cols, const int64_t *rowptr, const int32_t *col, const double *val, int parts, bool hot,
-                      bool unit, int64_t cols_used, hipStream_t st)
+                      bool unit, int64_t cols_used, hipStream_t st, const CsrFill *fill = nullptr, HostStage *stage = nullptr)
 {
     try {
-        return csr_plan_build(P, rows, cols, rowptr, col, val, parts, hot, unit, cols_used, st);
+        return csr_plan_build(P, rows, cols, rowptr, col, val, parts, hot, unit, cols_used, st, fill, stage);
     } catch (const std::bad_alloc &) {
         set_error("out of host memory building the sparse layout");
         return TRON_ENOMEM;
     }
+}
+
+static int alloc_row_partials(tron_dataset *ds)
+{
+    int64_t need = 0;
+    if (!ds->fwd.plain && !ds->fwd.direct) need = std::max<int64_t>(need, ds->fwd.nseg_total);   // one partial sum per segment
+    if (!ds->bwd.plain && !ds->bwd.direct) need = std::max<int64_t>(need, ds->bwd.nseg_total);
+    if (need > 0) TRON_HIP(hipMalloc(reinterpret_cast<void **>(&ds->row_partials), sizeof(double) * need));
+    return TRON_OK;
+}
+
+// A handle of an unpartitioned matrix, its layouts built on the device: 1 = done, 0 = no room for the work space, < 0 = an error.
+// rowptr and y are on the host and have been checked.
+static int create_on_device(tron_dataset *ds, const int64_t *h_rowptr, const int32_t *col, const double *val, const double *h_y, int mem, int64_t rows_used)
+{
+    const int64_t n = ds->n, d = ds->d, nnz = h_rowptr[n];
+    HostStage stage(ds->stream);
+    struct Build : CsrDeviceBuild { ~Build() { release(); } } B;
+    int rc = B.begin(n, d, nnz, h_rowptr, col, val, mem, stage, ds->stream);
+    if (rc == TRON_ENOMEM) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    TRON_TRY(rc);
+    TRON_TRY(stage.copy(ds->y, h_y, sizeof(double) * (size_t)n, ds->stream));
+    const CsrFill by_row = B.by_row(), by_column = B.by_column();
+    // beside the copies and the sort; what it copies of entries that turn out to be wrong is not used
+    TRON_TRY(plan_build(ds->fwd, n, d, h_rowptr, nullptr, nullptr, 1, false, false, 0, ds->stream, &by_row, &stage));
+    TRON_TRY(B.wait());
+    if (*B.bad != ~0ull) {   // the first in row order
+        const int64_t k = (int64_t)*B.bad, row = std::upper_bound(h_rowptr, h_rowptr + n + 1, k) - h_rowptr - 1;
+        int32_t c[2] = {-1, -1};   // the entry's column and the one before in its row
+        for (int j = 0; j < 2; ++j)
+            if (k - j >= h_rowptr[row]) TRON_HIP(hipMemcpy(&c[j], B.col + k - j, sizeof(int32_t), hipMemcpyDeviceToHost));
+        if (c[0] <= c[1] || c[0] >= d || c[0] < 0)
+            set_error("row %lld: column index %lld out of order or out of range [0,%lld)", (long long)row, (long long)c[0], (long long)d);
+        else set_error("row %lld: non-finite value", (long long)row);
+        return TRON_EINVAL;
+    }
+    int64_t cols_used = 0;
+    for (int64_t j = 0; j < d; ++j) cols_used += B.t_rowptr[j + 1] > B.t_rowptr[j];
+    if (!ds->fwd.plain) ds->fwd.cold_cols = cols_used;
+    TRON_TRY(plan_build(ds->bwd, d, n, B.t_rowptr, nullptr, nullptr, 1, false, false, rows_used, ds->stream, &by_column, &stage));
+    return 1;
 }
 
 }  // namespace tron
@@ -287,14 +331,40 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
     const int64_t nnz = h_rowptr[n];
     if (nnz > 0 && (!col || !val)) { set_error("col/val are null but nnz = %lld", (long long)nnz); return TRON_EINVAL; }
     if (mem == TRON_MEM_DEVICE) {
-        TRON_TRY(fetch(col_copy, col, (size_t)nnz));
-        TRON_TRY(fetch(val_copy, val, (size_t)nnz));
         TRON_TRY(fetch(y_copy, y, (size_t)n));
-        h_col = col_copy.data();
-        h_val = val_copy.data();
         h_y = y_copy.data();
     }
     TRON_TRY(check_labels(h_y, n));
+    const bool fwd_partitioned = g_tuning.csr_parts == kColParts ||
+                                 (g_tuning.csr_parts == 0 && d * (int64_t)sizeof(double) > (3 << 19) && nnz >= (1 << 22));
+    const bool bwd_partitioned = g_tuning.csr_parts == kColParts ||
+                                 (g_tuning.csr_parts == 0 && n * (int64_t)sizeof(double) > (3 << 19) && nnz >= (1 << 22));
+    const bool on_device = !fwd_partitioned && !bwd_partitioned && nnz > 0 && nnz <= INT32_MAX &&
+                           (g_tuning.csr_device_build < 0 ? nnz >= kDeviceBuildNnz : g_tuning.csr_device_build > 0);
+    tron_dataset *ds = new (std::nothrow) tron_dataset();
+    if (!ds) { set_error("out of host memory"); return TRON_ENOMEM; }
+    struct Owner {   // until the handle is the caller's
+        tron_dataset *ds;
+        ~Owner() { tron_dataset_destroy(ds); }
+    } owner{ds};
+    ds->n = n; ds->d = d; ds->dense = false; ds->stream = reinterpret_cast<hipStream_t>(hip_stream);
+    if (on_device) {
+        TRON_TRY(alloc_common(ds));
+        const int rc = create_on_device(ds, h_rowptr, col, val, h_y, mem, rows_used);
+        TRON_TRY(rc);
+        if (rc > 0) TRON_TRY(alloc_row_partials(ds));
+        if (rc > 0) {
+            *out = ds;
+            owner.ds = nullptr;
+            return TRON_OK;
+        }
+    }
+    if (mem == TRON_MEM_DEVICE) {
+        TRON_TRY(fetch(col_copy, col, (size_t)nnz));
+        TRON_TRY(fetch(val_copy, val, (size_t)nnz));
+        h_col = col_copy.data();
+        h_val = val_copy.data();
+    }
     // Columns strictly increasing inside each row and in range; values finite; count per column.  Matrices whose counts fit a
     // cache per thread are walked by several threads, each a block of rows with equal shares of the entries: the blocks' own
     // counts say where each of them places its entries in the transposed copy, instances in ascending order.
@@ -339,10 +409,6 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
     // Unit plans: when both layouts are partitioned and every instance's entries share one value r_i (binary features,
     // optionally scaled per instance, e.g. normalised to unit length), X = diag(r) B with B binary: the layouts keep no
     // values, the row sums of X are multiplied by r afterwards and X^T gathers from r .* (its vector).
-    const bool fwd_partitioned = g_tuning.csr_parts == kColParts ||
-                                 (g_tuning.csr_parts == 0 && d * (int64_t)sizeof(double) > (3 << 19) && nnz >= (1 << 22));
-    const bool bwd_partitioned = g_tuning.csr_parts == kColParts ||
-                                 (g_tuning.csr_parts == 0 && n * (int64_t)sizeof(double) > (3 << 19) && nnz >= (1 << 22));
     bool unit = g_tuning.csr_unit != 0 && fwd_partitioned && bwd_partitioned;
     std::vector<double> row_value;
     if (unit) {
@@ -472,10 +538,7 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         });
     }
 
-    tron_dataset *ds = new (std::nothrow) tron_dataset();
-    if (!ds) { set_error("out of host memory"); return TRON_ENOMEM; }
-    ds->n = n; ds->d = d; ds->dense = false; ds->stream = reinterpret_cast<hipStream_t>(hip_stream);
-    int rc = alloc_common(ds);
+    int rc = on_device ? TRON_OK : alloc_common(ds);
     if (rc >= 0) {
         // the two layouts are independent of each other: the first is built beside the second where a thread can be had
         int rc_fwd = TRON_OK;
@@ -516,22 +579,15 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         ds->fwd.row_scale = ds->unit_scale;
         ds->bwd.col_scale = ds->unit_scale;
     }
-    if (rc >= 0) {
-        int64_t need = 0;
-        if (!ds->fwd.plain && !ds->fwd.direct) need = std::max<int64_t>(need, ds->fwd.nseg_total);   // one partial sum per segment
-        if (!ds->bwd.plain && !ds->bwd.direct) need = std::max<int64_t>(need, ds->bwd.nseg_total);
-        if (need > 0) {
-            hipError_t e = hipMalloc(reinterpret_cast<void **>(&ds->row_partials), sizeof(double) * need);
-            if (e != hipSuccess) rc = hip_fail(e, "allocate row partials", __FILE__, __LINE__);
-        }
-    }
+    if (rc >= 0) rc = alloc_row_partials(ds);
     if (rc >= 0) {
         hipError_t e = hipMemcpyAsync(ds->y, h_y, sizeof(double) * n, hipMemcpyHostToDevice, ds->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ds->stream);
         if (e != hipSuccess) rc = hip_fail(e, "copy y", __FILE__, __LINE__);
     }
-    if (rc < 0) { tron_dataset_destroy(ds); return rc; }
+    if (rc < 0) return rc;
     *out = ds;
+    owner.ds = nullptr;
     return TRON_OK;
 }
 
@@ -780,6 +836,10 @@ int tron_tuning_set(const char *name, int64_t value)
     }
     if (name && strcmp(name, "csr_segmented") == 0 && value >= -1 && value <= 1) {
         g_tuning.csr_segmented = value;
+        return TRON_OK;
+    }
+    if (name && strcmp(name, "csr_device_build") == 0 && value >= -1 && value <= 1) {
+        g_tuning.csr_device_build = value;
         return TRON_OK;
     }
     if (name && strcmp(name, "csr_unit") == 0 && (value == 0 || value == 1)) {

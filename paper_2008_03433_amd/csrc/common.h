@@ -43,6 +43,7 @@ struct Tuning {
     int64_t csr_sell = 1;    // unit plans: the head partition as sorted slices of 64 rows, one row per lane (0 = as chunks)
     int64_t csr_segmented = -1;  // unpartitioned layouts as segments + flag bits instead of plain CSR: 0 never, 1 always, -1 when a
                              //   chunk of the plain layout would leave one thread a long row (see csr_plan_build)
+    int64_t csr_device_build = -1;   // unpartitioned layouts built on the device: 0 never, 1 always, -1 from kDeviceBuildNnz entries on
     int64_t csr_unit = 1;    // partitioned layouts: drop the value stream when every row of X holds one repeated value (0 = off)
     int64_t dense_compact = -1;         // dense L2-SVM: Hessian-vector products on a compacted copy of the active rows:
                                         //   0 never, 1 whenever rows are inactive, -1 automatic (see dense_compact_wanted)
@@ -502,11 +503,59 @@ int copy_norm(tron_dataset *ds, int64_t m, const double *src, double *dst, int f
 int probe_read(const double *src, int64_t count, int reps, hipStream_t st, double *ms, double *checksum);
 int probe_copy(double *dst, const double *src, int64_t count, int reps, hipStream_t st, double *ms);
 
+// ---- csr_build.hip
+constexpr int64_t kDeviceBuildNnz = 1 << 16;   // us of a creation and its end on the host / device: 20,000 entries 290 / 349, 100,000 608 / 503, 300,000 1366 / 678, 1.05M 4553 / 1663
+// Pinned memory for the copies of small host arrays to the device; the destructor waits for the stream and gives it back.
+class HostStage {
+public:
+    explicit HostStage(hipStream_t st) : st_(st) {}
+    ~HostStage();
+    void *take(size_t bytes);   // null: none to be had
+    // src has been read when the call returns, unless it stays: then at the latest when the stream has drained
+    int copy(void *dst, const void *src, size_t bytes, hipStream_t st, bool stays = false);
+    HostStage(const HostStage &) = delete;
+    HostStage &operator=(const HostStage &) = delete;
+private:
+    struct Block { void *p; Block *next; };
+    Block *blocks_ = nullptr;
+    size_t used_ = 0, size_ = 0;
+    hipStream_t st_;
+};
+// Where the entries of a plan come from: entry k of row r, start[r] <= k < start[r + 1], is index[p], val[p] with p = from[k] (null: k).
+struct CsrFill {
+    const int64_t *start;
+    const int32_t *from, *index;
+    const double *val;
+    int64_t *place;   // work space, as many as start
+};
+int csr_fill_plan(const CsrFill &F, bool segments, int64_t rows, int64_t stored, const int64_t *place_dev, int32_t *col, double *val, hipStream_t st);
+// The entries of a matrix on the device, and sorted by column.
+struct CsrDeviceBuild {
+    int64_t n = 0, d = 0, nnz = 0;
+    void *block = nullptr;
+    hipEvent_t sorted = nullptr;
+    int64_t *rowptr = nullptr, *start = nullptr;   // device: of the rows, of the columns
+    int64_t *place = nullptr;
+    const int32_t *col = nullptr;
+    const double *val = nullptr;
+    int32_t *row_of = nullptr;
+    const int32_t *from = nullptr;                 // device: the entries, column by column
+    int64_t *t_rowptr = nullptr;                   // host (the stage's), after wait()
+    unsigned long long *bad = nullptr;             // the same; ~0: every entry is as it has to be
+    int begin(int64_t n, int64_t d, int64_t nnz, const int64_t *h_rowptr, const int32_t *col, const double *val, int mem, HostStage &stage, hipStream_t st);
+    int wait();
+    CsrFill by_row() const { return CsrFill{rowptr, nullptr, col, val, place}; }
+    CsrFill by_column() const { return CsrFill{start, from, row_of, val, place}; }
+    void release();
+};
+
 // ---- kernels_csr.hip
 // parts: 1 = plain CSR, 0 = choose from the size of the gathered vector
 // unit: build a unit plan (see CsrPlan::unit; partitioned layouts only; h_val is not read)
+// cols_used: columns with entries.  fill: the entries lie on the device (unpartitioned plans only; h_col and h_val are not read); then
+// the host's arrays are copied through `stage`, and nothing is waited for.
 int csr_plan_build(CsrPlan &P, int64_t rows, int64_t cols, const int64_t *h_rowptr, const int32_t *h_col,
-                   const double *h_val, int parts, bool hot, bool unit, int64_t cols_used, hipStream_t st);   // cols_used: columns with entries
+                   const double *h_val, int parts, bool hot, bool unit, int64_t cols_used, hipStream_t st, const CsrFill *fill = nullptr, HostStage *stage = nullptr);
 // Hot-row tiles for plan A (rows x cols) from the *other* orientation's CSR (cols x rows: t_rowptr over A's columns,
 // t_col = A's row ids).  slot_code[row] = slice * kTileSlots + slot for hot rows, -1 otherwise.
 int hot_tiles_build(CsrPlan &A, const int64_t *t_rowptr, const int32_t *t_col, const double *t_val,

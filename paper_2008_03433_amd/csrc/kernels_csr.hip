@@ -69,14 +69,19 @@ void CsrPlan::release()
     *this = CsrPlan();
 }
 
+// stage: the array has been read when the call returns
 template <typename T>
-static int upload(T **dst, const T *src, size_t count, hipStream_t st)
+static int upload_array(T **dst, const T *src, size_t count, hipStream_t st, HostStage *stage)
 {
     *dst = nullptr;
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(dst), sizeof(T) * std::max<size_t>(count, 1)));
-    if (count) TRON_HIP(hipMemcpyAsync(*dst, src, sizeof(T) * count, hipMemcpyHostToDevice, st));
+    if (!count) return TRON_OK;
+    if (stage) return stage->copy(*dst, src, sizeof(T) * count, st);
+    TRON_HIP(hipMemcpyAsync(*dst, src, sizeof(T) * count, hipMemcpyHostToDevice, st));
     return TRON_OK;
 }
+template <typename T>
+static int upload(T **dst, const T *src, size_t count, hipStream_t st) { return upload_array(dst, src, count, st, nullptr); }
 
 // row_lo / fix-up lists of the plain layout.  rp[r] = position of row r's first entry, rp[rows] = entries stored.
 static void plan_chunks(const int64_t *rp, int64_t rows, int nchunks, std::vector<int32_t> &row_lo, std::vector<int32_t> &fix_row,
@@ -116,8 +121,14 @@ static inline int64_t col_pos(int64_t q) { const uint32_t e = (uint32_t)q & (kCh
 static inline int64_t val_pos(int64_t q) { const uint32_t e = (uint32_t)q & (kChunk - 1); return q - e + ((e >> 1 & 3) * (kChunk / 4) + (e >> 3) * 2 + (e & 1)); }
 
 int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowptr, const int32_t *h_col,
-                   const double *h_val, int parts, bool hot, bool unit, int64_t cols_used, hipStream_t st)
+                   const double *h_val, int parts, bool hot, bool unit, int64_t cols_used, hipStream_t st, const CsrFill *fill, HostStage *stage)
 {
+    auto upload = [&](auto **dst, const auto *src, size_t count, hipStream_t s) { return upload_array(dst, src, count, s, stage); };
+    // the arrays on the host may go
+    auto arrays_done = [&]() -> int {
+        if (!stage) TRON_HIP(hipStreamSynchronize(st));
+        return TRON_OK;
+    };
     A.rows = rows;
     A.cols = cols;
     A.nnz = h_rowptr[rows];
@@ -168,9 +179,9 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         }
         rp[rows] = at;
         const int64_t stored = at;
-        const HostArray<int32_t> pcol((size_t)stored);
-        const HostArray<double> pval((size_t)stored);
-        parallel_ranges(rows, stored, [&](int64_t r0, int64_t r1) {
+        const HostArray<int32_t> pcol(fill ? 0 : (size_t)stored);
+        const HostArray<double> pval(fill ? 0 : (size_t)stored);
+        if (!fill) parallel_ranges(rows, stored, [&](int64_t r0, int64_t r1) {
             for (int64_t r = r0; r < r1; ++r) {
                 const int64_t k0 = h_rowptr[r], k1 = h_rowptr[r + 1];
                 int64_t q = rp[r];
@@ -188,9 +199,15 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         plan_chunks(rp.data(), rows, A.nblocks, row_lo, fix_row, fix_b0, fix_cnt);
         for (int c = 0; c < A.nblocks; ++c) A.max_rows = std::max(A.max_rows, row_lo[c + 1] - row_lo[c]);
         TRON_TRY(upload(&A.rowptr, rp.data(), (size_t)rows + 1, st));
-        TRON_TRY(upload(&A.col, pcol.data(), (size_t)stored, st));
-        TRON_TRY(upload(&A.val, pval.data(), (size_t)stored, st));
-        TRON_HIP(hipStreamSynchronize(st));   // the staging arrays go out of scope
+        if (fill) {
+            TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.col), sizeof(int32_t) * (size_t)std::max<int64_t>(stored, 1)));
+            TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.val), sizeof(double) * (size_t)std::max<int64_t>(stored, 1)));
+            TRON_TRY(csr_fill_plan(*fill, false, rows, stored, A.rowptr, A.col, A.val, st));
+        } else {
+            TRON_TRY(upload(&A.col, pcol.data(), (size_t)stored, st));
+            TRON_TRY(upload(&A.val, pval.data(), (size_t)stored, st));
+        }
+        TRON_TRY(arrays_done());
     } else {
         const int P = A.P;
         std::vector<int64_t> colcount((size_t)cols + 1, 0);
@@ -279,7 +296,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         // one table for the passes over the entries below: partition in the upper half, LDS slot + 1 (0: none) in the lower
         std::vector<int32_t> code_of(P > 1 ? (size_t)cols : 0);
         for (int64_t j = 0; P > 1 && j < cols; ++j) code_of[j] = ((int32_t)part_of[j] << 16) | ((hot && slot_of[j] >= 0) ? slot_of[j] + 1 : 0);
-        parallel_ranges(rows, A.nnz, [&](int64_t r0, int64_t r1) {
+        parallel_ranges(rows, P == 1 ? rows : A.nnz, [&](int64_t r0, int64_t r1) {
             if (P == 1) {
                 for (int64_t r = r0; r < r1; ++r) len32[(size_t)r] = (int32_t)(h_rowptr[r + 1] - h_rowptr[r]);
                 return;
@@ -328,13 +345,13 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
         if (nseg_total > 0x7ffffff0) { set_error("too many row segments for 32-bit indexing"); return TRON_EINVAL; }
         // entries partition-major; inside a row the entries of one range are contiguous and stay ordered
         size_t stored_cols = (size_t)pos;
-        HostArray<int32_t> pcol((size_t)pos);
-        HostArray<double> pval(A.unit ? 0 : (size_t)pos);
-        parallel_ranges(pos, pos, [&](int64_t q0, int64_t q1) {
+        HostArray<int32_t> pcol(fill ? 0 : (size_t)pos);
+        HostArray<double> pval(A.unit || fill ? 0 : (size_t)pos);
+        if (!fill) parallel_ranges(pos, pos, [&](int64_t q0, int64_t q1) {
             std::fill(pcol.data() + q0, pcol.data() + q1, 0);
             if (!A.unit) std::fill(pval.data() + q0, pval.data() + q1, 0.0);
         });
-        parallel_ranges(rows, A.nnz, [&](int64_t r0, int64_t r1) {   // a row's places belong to that row alone
+        if (!fill) parallel_ranges(rows, A.nnz, [&](int64_t r0, int64_t r1) {   // a row's places belong to that row alone
             int64_t cursor[kMaxParts + 1];
             if (P == 1) {
                 for (int64_t r = r0; r < r1; ++r) {
@@ -510,9 +527,15 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
             TRON_HIP(hipStreamSynchronize(st));
             stored_cols = h0;
         }
-        TRON_TRY(upload(&A.col, pcol.data(), stored_cols, st));
-        if (!A.unit) TRON_TRY(upload(&A.val, pval.data(), (size_t)pos, st));
-        else TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.xs), sizeof(double) * (size_t)(cols + 1)));
+        if (fill) {   // one range
+            std::vector<int64_t> place(rp32.begin(), rp32.begin() + rows + 1);
+            TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.col), sizeof(int32_t) * (size_t)pos));
+            TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.val), sizeof(double) * (size_t)pos));
+            TRON_TRY(stage->copy(fill->place, place.data(), sizeof(int64_t) * place.size(), st));
+            TRON_TRY(csr_fill_plan(*fill, true, rows, pos, fill->place, A.col, A.val, st));
+        } else TRON_TRY(upload(&A.col, pcol.data(), stored_cols, st));
+        if (!fill && !A.unit) TRON_TRY(upload(&A.val, pval.data(), (size_t)pos, st));
+        if (A.unit) TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.xs), sizeof(double) * (size_t)(cols + 1)));
         A.nseg_total = nseg_total;
         // A single range: the kernel applies the epilogue itself where every chunk has a bounded number of rows (the empty ones
         // among them) and the sums it leaves are few enough to be added up by the kernel after it.
@@ -547,7 +570,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
                     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.long_ticket), sizeof(unsigned) * nlong));
                     TRON_HIP(hipMemsetAsync(A.long_ticket, 0, sizeof(unsigned) * nlong, st));
                 }
-                TRON_HIP(hipStreamSynchronize(st));
+                TRON_TRY(arrays_done());
                 A.direct = true;
             }
         }
@@ -566,11 +589,11 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
             }
             TRON_TRY(upload(&A.group_base, gbase.data(), gbase.size(), st));
             TRON_TRY(upload(&A.row_mask, mask.data(), mask.size(), st));
-            TRON_HIP(hipStreamSynchronize(st));   // gbase goes out of scope
+            TRON_TRY(arrays_done());   // gbase goes out of scope
         }
         TRON_TRY(upload(&A.chunk_tab, tab.data(), tab.size(), st));
         TRON_TRY(upload(&A.flags, flags.data(), flags.size(), st));
-        TRON_HIP(hipStreamSynchronize(st));
+        TRON_TRY(arrays_done());
     }
     A.nfix = (int)fix_row.size();
     A.fix_max_cnt = 0;
@@ -583,7 +606,7 @@ int csr_plan_build(CsrPlan &A, int64_t rows, int64_t cols, const int64_t *h_rowp
     }
     TRON_HIP(hipMalloc(reinterpret_cast<void **>(&A.carry), sizeof(double) * A.nblocks));
     TRON_HIP(hipMemsetAsync(A.carry, 0, sizeof(double) * A.nblocks, st));
-    TRON_HIP(hipStreamSynchronize(st));  // the host vectors above go out of scope
+    TRON_TRY(arrays_done());   // the host vectors above go out of scope
     return TRON_OK;
 }
 
