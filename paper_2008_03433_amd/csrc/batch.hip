@@ -15,6 +15,7 @@
 #include <new>
 #include <optional>
 #include <thread>
+#include <type_traits>
 
 #include "dense_tile.h"
 #include "device_driver.h"
@@ -29,11 +30,17 @@ typedef const uint64_t __attribute__((address_space(4))) *ConstWords;
 // range of tiles.  Per tile and problem one 64-bit word says which rows concern the problem: its members
 // (function/gradient pass, logistic Hessian) or its active set I (L2-SVM Hessian: D_ii = 2 on I).  Rows that concern no
 // problem are not read.  The words of the next tile are fetched (scalar loads) while the current one is processed.
-// New active-set words are collected in LDS and stored 64 tiles at a time.
+// New active-set words are collected in LDS and stored kHeld tiles at a time.
+// STREAM: matrices that do not fit the cache come through LDS (TileStream), a tile ahead.  us a function-gradient / Hessian call over 10M x 24: three
+// L2-SVMs 373 / 358 loaded, 333 / 312 streamed, six 448 / 358 and 418 / 333, three logistic problems 549 / 415 and 441 / 331; six L2-SVMs
+// over 1.4M x 24, which fits, 81 / 65 and 82 / 67.
+// What bounds it: instructions and memory in turn, as two wavefronts a SIMD do not cover each other's waits (six L2-SVMs over 1M x 24: vector units
+// 45% busy).  So the loop over the problems asks nothing but whether a problem has rows in the tile (see sweep), and the sums over the
+// lanes at the end are moves between lanes with one barrier for all problems: pass of 56 / 45 us before, 52 / 38 now.
 //   member: [k][tile]     Dbits: [k][slot][tile]     Dval (logistic D): [k][slot][row]
 //   partials: [k][column 0..d-1, then the loss sum][workgroup]
 // Dbits_in and Dbits_out are the same array: a problem's plane is either read (MODE_HV) or written (MODE_FG) by a pass.
-template <int E, int L, int U, bool VEC, int KT, int LOSS>
+template <int E, int L, int U, bool VEC, int KT, int LOSS, bool STREAM>
 __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, const double *__restrict__ X,
                                                        const int8_t *__restrict__ y,
                                                        const BatchCtl *__restrict__ ctl, const uint64_t *__restrict__ member,
@@ -43,35 +50,30 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
     using T = Tile<E, L, U, VEC>;
     static_assert(T::RT == kWave, "one 64-bit word per tile");
     __shared__ double lvec[KT][E * L];
-    __shared__ double lds[kWavesPerBlock * E * L];
-    __shared__ double lds_red[kWavesPerBlock];
+    __shared__ double lcols[STREAM ? 1 : kWavesPerBlock][KT][E * L];
+    __shared__ double lds_red[kWavesPerBlock][KT];
     // function/gradient pass only, kept out of the registers: per wavefront and problem the loss sum of every lane's rows
-    // and the new active-set words of up to 64 tiles
+    // and the new active-set words of up to kHeld tiles
     __shared__ double lloss[kWavesPerBlock][KT][kWave];
     __shared__ double lprod[LOSS == TRON_LOSS_LR ? kWavesPerBlock : 1][KT][kWave];   // and their product, see LossSum
-    __shared__ uint64_t lheld[kWavesPerBlock][KT][kWave];
+    constexpr int kHeld = KT > 4 ? (STREAM ? 16 : 64) : 32;
+    __shared__ uint64_t lheld[kWavesPerBlock][KT][LOSS == TRON_LOSS_LR ? 1 : kHeld];
+    extern __shared__ __align__(16) double dyn[];
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int q = lane % L, own = T::own_row(lane);
     int mode[KT], dslot[KT];
-    bool any = false, any_fg = false;
+    unsigned live = 0, fg = 0, hv = 0;   // problems by what they ask for
 #pragma unroll
     for (int k = 0; k < KT; ++k) {
         mode[k] = ctl->mode[k];
         dslot[k] = ctl->dslot[k];
-        any |= mode[k] != MODE_IDLE;
-        any_fg |= mode[k] == MODE_FG;
+        live |= (unsigned)(mode[k] != MODE_IDLE) << k;
+        fg |= (unsigned)(mode[k] == MODE_FG) << k;
+        hv |= (unsigned)(mode[k] == MODE_HV) << k;
     }
-    if (!any) return;
+    if (live == 0) return;
     constexpr bool svm = LOSS == TRON_LOSS_L2SVM;
-    // L2-SVM Hessian: D_ii = 2 on the active set.  The factor is put into v (exact: a power of two), the product
-    // then only selects rows.
-    for (int i = threadIdx.x; i < KT * E * L; i += kBlock) {
-        const int k = i / (E * L), at = i % (E * L), c = T::col(at / E, at % E);   // lane q's entries lie together
-        const double scale = (svm && ctl->mode[k] == MODE_HV) ? 2.0 : 1.0;
-        lvec[k][at] = (c < d) ? scale * ctl->vec[k][c] : 0.0;
-    }
-    __syncthreads();
     // plane of the words that say which rows concern problem k.  The words are the same for all lanes: read through
     // the constant address space they arrive in scalar registers.  (No plane read here is written by this pass.)
     ConstWords words[KT];
@@ -79,15 +81,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
     for (int k = 0; k < KT; ++k) {
         if ((mode[k] == MODE_HV || mode[k] == MODE_DIAG) && svm) words[k] = (ConstWords)(Dbits_in + ((int64_t)k * 2 + dslot[k]) * ntiles);
         else words[k] = (ConstWords)(member + (int64_t)k * ntiles);
-    }
-    double acc[KT][E];
-#pragma unroll
-    for (int k = 0; k < KT; ++k) {
-        lloss[wv][k][lane] = 0.0;
-        if (!svm) lprod[wv][k][lane] = 0.0;
-        lheld[wv][k][lane] = 0;
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[k][e] = 0.0;
     }
     const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
     const int64_t wave_id = (int64_t)blockIdx.x * kWavesPerBlock + wv;
@@ -97,111 +90,187 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
     uint64_t wnext[KT];
 #pragma unroll
     for (int k = 0; k < KT; ++k) wnext[k] = (mode[k] != MODE_IDLE && first < last) ? words[k][first] : 0;
-    int it = 0;
-    for (int64_t tile = first; tile < last; ++tile, ++it) {
-        const int slotl = it & (kWave - 1);
-        const int64_t row0 = tile * kWave;
-        uint64_t wk[KT], rows = 0;
+    // L2-SVM Hessian: D_ii = 2 on the active set.  The factor is put into v (exact: a power of two), the product
+    // then only selects rows.
+    for (int i = threadIdx.x; i < KT * E * L; i += kBlock) {
+        const int k = i / (E * L), at = i % (E * L), c = T::col(at / E, at % E);   // lane q's entries lie together
+        const double scale = (svm && ctl->mode[k] == MODE_HV) ? 2.0 : 1.0;
+        lvec[k][at] = (c < d) ? scale * ctl->vec[k][c] : 0.0;
+    }
+    __syncthreads();
+    double acc[KT][E];
 #pragma unroll
-        for (int k = 0; k < KT; ++k) {
-            wk[k] = wnext[k];
-            rows |= wk[k];
-            wnext[k] = (mode[k] != MODE_IDLE && tile + 1 < last) ? words[k][tile + 1] : 0;
-        }
-        if (rows != 0) {
-            double x[U][E];
-            T::load(X, n, d, row0, lane, x, rows);
-            const double yrow = (any_fg && row0 + own < n) ? (double)y[row0 + own] : 1.0;
-            // logistic Hessian: D of the tile's rows for every problem, a lane taking the row it owns, fetched together with x
-            double Drow[KT];
+    for (int k = 0; k < KT; ++k) {
+        lloss[wv][k][lane] = 0.0;
+        if (!svm) lprod[wv][k][lane] = 0.0;
+        if (svm && lane < kHeld) lheld[wv][k][lane] = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[k][e] = 0.0;
+    }
+    // The pass over the wavefront's tiles.  M: what every problem that is not idle asks for, or kMixed.  Knowing it takes the questions out of
+    // the loop over the problems: they were 305 scalar instructions a tile beside 845 vector ones (six problems, 24 columns).
+    constexpr int kMixed = -1;
+    auto sweep = [&](auto what) {
+        constexpr int M = decltype(what)::value;
+        const auto mode_of = [&](int k) { return M == kMixed ? mode[k] : M; };
+        const bool any_fg = M == kMixed ? fg != 0 : M == MODE_FG;
+        // What travels with a tile's rows: its labels, and for the logistic Hessian D of every problem, a lane taking the row it owns.
+        TileStream<E, L, U, VEC> stream(STREAM ? dyn : nullptr, d);
+        double ynext = 1.0, Dnext[KT];
+        auto ask = [&](int64_t tile, const uint64_t (&w)[KT]) {
+            uint64_t rows = 0;
+#pragma unroll
+            for (int k = 0; k < KT; ++k) rows |= w[k];
+            stream.ask(X, n, d, tile, tile < last && __popcll(rows) >= kWave / 2);
+            const bool mine = tile < last && tile * kWave + own < n;
+            ynext = (any_fg && mine) ? (double)y[tile * kWave + own] : 1.0;
             if constexpr (!svm) {
 #pragma unroll
                 for (int k = 0; k < KT; ++k) {
-                    Drow[k] = 0.0;
-                    if ((mode[k] == MODE_HV || mode[k] == MODE_DIAG) && wk[k] != 0 && row0 + own < n)
-                        Drow[k] = Dval[((int64_t)k * 2 + dslot[k]) * n + row0 + own];   // zero outside the problem's rows
+                    Dnext[k] = 0.0;
+                    if ((mode_of(k) == MODE_HV || mode_of(k) == MODE_DIAG) && w[k] != 0 && mine)
+                        Dnext[k] = Dval[((int64_t)k * 2 + dslot[k]) * n + tile * kWave + own];   // zero outside the problem's rows
                 }
             }
-            // the vectors are read from LDS again for every tile: hoisted out of the loop they would take KT * E
-            // registers per lane (the empty statement hides the loop invariance from the compiler)
-            int qoff = q * E;
-            asm volatile("" : "+v"(qoff));
+        };
+        ask(first, wnext);
+        int it = 0;
+        for (int64_t tile = first; tile < last; ++tile, ++it) {
+            const int slotl = it & (kHeld - 1);
+            const int64_t row0 = tile * kWave, ahead = tile + 1 < last ? tile + 1 : tile;
+            uint64_t wk[KT], rows = 0;
 #pragma unroll
             for (int k = 0; k < KT; ++k) {
-                if (mode[k] == MODE_IDLE || wk[k] == 0) continue;   // uniform
-                double vk[E], c[U];
-                const bool mine = (wk[k] >> own) & 1u;
-                if (mode[k] == MODE_DIAG) {
-                    // sum_i D_i x_ij^2: the row coefficient is D itself, the entries are squared
-                    T::from_row_owner(svm ? (mine ? 2.0 : 0.0) : Drow[k], c);
+                wk[k] = wnext[k];
+                rows |= wk[k];
+                wnext[k] = (live >> k & 1u) ? words[k][ahead] : 0;
+            }
+            double x[U][E], Drow[KT];
+            if (rows != 0) stream.take(X, n, d, tile, lane, x, rows);
+            const double yrow = ynext;
+            if constexpr (!svm) {
+#pragma unroll
+                for (int k = 0; k < KT; ++k) Drow[k] = Dnext[k];
+            }
+            ask(tile + 1, wnext);
+            if (rows != 0) {
+                if (M == kMixed && live != (fg | hv)) {   // uniform
+#pragma unroll
+                    for (int k = 0; k < KT; ++k) {
+                        if (mode[k] != MODE_DIAG || wk[k] == 0) continue;   // uniform
+                        // sum_i D_i x_ij^2: the row coefficient is D itself, the entries are squared
+                        double c[U];
+                        T::from_row_owner(svm ? (((wk[k] >> own) & 1u) ? 2.0 : 0.0) : Drow[k], c);
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+#pragma unroll
+                            for (int e = 0; e < E; ++e) acc[k][e] = fma(c[u] * x[u][e], x[u][e], acc[k][e]);
+                        }
+                    }
+                }
+                // The vectors are read from LDS again for every tile: hoisted out of the loop they would take KT * E
+                // registers per lane (the empty statement hides the loop invariance from the compiler).  Each is asked for a problem
+                // ahead where there are registers for it.
+                int qoff = q * E;
+                asm volatile("" : "+v"(qoff));
+                constexpr bool kAhead = KT * E <= (svm ? 56 : 32);
+                double vnext[E];
+#pragma unroll
+                for (int e = 0; kAhead && e < E; ++e) vnext[e] = lvec[0][qoff + e];
+#pragma unroll
+                for (int k = 0; k < KT; ++k) {
+                    double vk[E], c[U];
+#pragma unroll
+                    for (int e = 0; kAhead && e < E; ++e) {
+                        vk[e] = vnext[e];
+                        if (k + 1 < KT) vnext[e] = lvec[k + 1][qoff + e];
+                    }
+                    if (wk[k] == 0 || mode_of(k) == MODE_DIAG) continue;   // uniform (no bit: nothing asked for, or no row)
+#pragma unroll
+                    for (int e = 0; !kAhead && e < E; ++e) vk[e] = lvec[k][qoff + e];
+                    const bool mine = (wk[k] >> own) & 1u;
+                    const double z = T::row_sum(x, vk, lane);
+                    double coef;
+                    if (mode_of(k) == MODE_HV) {
+                        coef = svm ? (mine ? z : 0.0) : Drow[k] * z;   // a1 = D (X v) in the row's owner
+                    } else {
+                        // the per-row terms of Table 1 run once per row
+                        LossTerm alpha;
+                        double zhat, Di;
+                        loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
+                        if (!mine) { alpha = LossTerm{0.0, 0.0}; zhat = 0.0; Di = 0.0; }
+                        if constexpr (svm) {
+                            lds_add(&lloss[wv][k][lane], alpha.lin);
+                            const uint64_t nb = __ballot(Di != 0.0);
+                            if (lane == 0) lheld[wv][k][slotl] = nb;   // in the order of the lanes
+                        } else {
+                            LossSum<LOSS> losses{lloss[wv][k][lane], lprod[wv][k][lane]};
+                            losses.add(alpha);
+                            lloss[wv][k][lane] = losses.lin;
+                            lprod[wv][k][lane] = losses.p;
+                            if (mine) Dval[((int64_t)k * 2 + dslot[k]) * n + row0 + own] = Di;
+                        }
+                        coef = zhat;
+                    }
+                    T::from_row_owner(coef, c);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
 #pragma unroll
-                        for (int e = 0; e < E; ++e) acc[k][e] = fma(c[u] * x[u][e], x[u][e], acc[k][e]);
+                        for (int e = 0; e < E; ++e) acc[k][e] = fma(c[u], x[u][e], acc[k][e]);
                     }
-                    continue;
-                }
-#pragma unroll
-                for (int e = 0; e < E; ++e) vk[e] = lvec[k][qoff + e];
-                const double z = T::row_sum(x, vk, lane);
-                if (mode[k] == MODE_HV) {
-                    // a1 = D (X v) in the row's owner
-                    T::from_row_owner(svm ? (mine ? z : 0.0) : Drow[k] * z, c);
-                } else {
-                    // the per-row terms of Table 1 run once per row
-                    LossTerm alpha;
-                    double zhat, Di;
-                    loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
-                    if (!mine) { alpha = LossTerm{0.0, 0.0}; zhat = 0.0; Di = 0.0; }
-                    LossSum<LOSS> losses{lloss[wv][k][lane], svm ? 0.0 : lprod[svm ? 0 : wv][k][lane]};
-                    losses.add(alpha);
-                    lloss[wv][k][lane] = losses.lin;
-                    if (!svm) lprod[wv][k][lane] = losses.p;
-                    if (svm) {
-                        const uint64_t nb = T::ballot_rows(Di != 0.0, lane);
-                        if (lane == 0) lheld[wv][k][slotl] = nb;
-                    } else if (mine) {
-                        Dval[((int64_t)k * 2 + dslot[k]) * n + row0 + own] = Di;
-                    }
-                    T::from_row_owner(zhat, c);
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-#pragma unroll
-                    for (int e = 0; e < E; ++e) acc[k][e] = fma(c[u], x[u][e], acc[k][e]);
                 }
             }
-        }
-        if constexpr (!svm) {
-            // by the number of the tile, whichever problems have rows in it: none of them adds more than once a tile
-            if (any_fg && (it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) {
+            if constexpr (!svm) {
+                // by the number of the tile, whichever problems have rows in it: none of them adds more than once a tile
+                if (any_fg && (it & (LossSum<LOSS>::kAdds - 1)) == LossSum<LOSS>::kAdds - 1) {
+#pragma unroll
+                    for (int k = 0; k < KT; ++k) {
+                        LossSum<LOSS> losses{lloss[wv][k][lane], lprod[wv][k][lane]};
+                        losses.scale();
+                        lloss[wv][k][lane] = losses.lin;
+                        lprod[wv][k][lane] = losses.p;
+                    }
+                }
+            }
+            if (svm && any_fg && (slotl == kHeld - 1 || tile + 1 == last)) {
+                // lane i takes the word of tile (tile - slotl + i): consecutive 8-byte words per problem
 #pragma unroll
                 for (int k = 0; k < KT; ++k) {
-                    LossSum<LOSS> losses{lloss[wv][k][lane], lprod[wv][k][lane]};
-                    losses.scale();
-                    lloss[wv][k][lane] = losses.lin;
-                    lprod[wv][k][lane] = losses.p;
+                    if ((fg >> k & 1u) && lane <= slotl)
+                        Dbits_out[((int64_t)k * 2 + dslot[k]) * ntiles + (tile - slotl) + lane] = T::rows_of_ballot(lheld[wv][k][lane]);
+                    if (lane < kHeld) lheld[wv][k][lane] = 0;
                 }
             }
         }
-        if (svm && any_fg && (slotl == kWave - 1 || tile + 1 == last)) {
-            // lane i takes the word of tile (tile - slotl + i): consecutive 8-byte words per problem
-#pragma unroll
-            for (int k = 0; k < KT; ++k) {
-                if (mode[k] == MODE_FG && lane <= slotl)
-                    Dbits_out[((int64_t)k * 2 + dslot[k]) * ntiles + (tile - slotl) + lane] = lheld[wv][k][lane];
-                lheld[wv][k][lane] = 0;
-            }
-        }
-    }
-    const int64_t cols = d + 1;
+    };
+    if (live == hv) sweep(std::integral_constant<int, MODE_HV>{});
+    else if (live == fg) sweep(std::integral_constant<int, MODE_FG>{});
+    else sweep(std::integral_constant<int, kMixed>{});
+    // columns and loss sums over the wavefronts, in order
+    double *const cols_w = STREAM ? dyn + wv * (kWave * d) : &lcols[STREAM ? 0 : wv][0][0];   // (the rows in the wavefront's part have been read)
 #pragma unroll
     for (int k = 0; k < KT; ++k) {
-        if (mode[k] == MODE_IDLE) continue;   // uniform over the workgroup
-        double *pk = partials + (int64_t)k * cols * gridDim.x;
-        T::flush(acc[k], d, lane, wv, kWavesPerBlock, lds, pk + blockIdx.x, gridDim.x);
-        const double ls = block_sum(LossSum<LOSS>{lloss[wv][k][lane], svm ? 0.0 : lprod[svm ? 0 : wv][k][lane]}.value(), lds_red);   // its barriers also order the reuse of lds
-        if (threadIdx.x == 0) pk[d * (int64_t)gridDim.x + blockIdx.x] = ls;
+        if (!(live >> k & 1u)) continue;   // uniform
+        T::sum_columns(acc[k]);
+        if (lane < L) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) cols_w[k * (E * L) + T::col(lane, e)] = acc[k][e];
+        }
+        if (fg >> k & 1u) {
+            const double ls = wave_sum(LossSum<LOSS>{lloss[wv][k][lane], svm ? 0.0 : lprod[svm ? 0 : wv][k][lane]}.value());
+            if (lane == 0) lds_red[wv][k] = ls;
+        } else if (lane == 0) lds_red[wv][k] = 0.0;
+    }
+    __syncthreads();
+    const int cols = (int)d + 1;
+    for (int i = threadIdx.x; i < KT * cols; i += kBlock) {
+        const int k = i / cols, c = i - k * cols;
+        if (!(live >> k & 1u)) continue;
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w)
+            s += c == (int)d ? lds_red[w][k] : (STREAM ? dyn[w * (kWave * d) + k * (E * L) + c] : lcols[STREAM ? 0 : w][k][c]);
+        partials[(int64_t)i * gridDim.x + blockIdx.x] = s;
     }
 }
 
@@ -678,36 +747,44 @@ using PassFn = void (*)(int64_t, int64_t, const double *, const int8_t *, const 
 
 struct PassPair { PassFn fn[2]; };   // by loss
 
-template <int E, int L, int KT>
+template <int E, int L, int KT, bool STREAM>
 PassPair pass_for(bool vec)
 {
     constexpr int U = pick_U(E, L);
+    constexpr bool S = STREAM && tiles_stream(L);
+    if constexpr (S && KT == 8) {   // (the logistic kernel has no room for the tiles)
+        if constexpr (E % 2 == 0) {
+            if (vec) return {{nullptr, k_batch_pass<E, L, U, true, KT, TRON_LOSS_L2SVM, S>}};
+        }
+        return {{nullptr, k_batch_pass<E, L, U, false, KT, TRON_LOSS_L2SVM, S>}};
+    } else {
     if constexpr (E % 2 == 0) {
-        if (vec) return {{k_batch_pass<E, L, U, true, KT, TRON_LOSS_LR>, k_batch_pass<E, L, U, true, KT, TRON_LOSS_L2SVM>}};
+        if (vec) return {{k_batch_pass<E, L, U, true, KT, TRON_LOSS_LR, S>, k_batch_pass<E, L, U, true, KT, TRON_LOSS_L2SVM, S>}};
     }
-    return {{k_batch_pass<E, L, U, false, KT, TRON_LOSS_LR>, k_batch_pass<E, L, U, false, KT, TRON_LOSS_L2SVM>}};
+    return {{k_batch_pass<E, L, U, false, KT, TRON_LOSS_LR, S>, k_batch_pass<E, L, U, false, KT, TRON_LOSS_L2SVM, S>}};
+    }
 }
 
-template <int KT>
+template <int KT, bool STREAM = false>
 PassPair pass_for_shape(const Shape &s, bool vec)
 {
     switch (s.L * 16 + s.E) {
-    case 16 + 1: return pass_for<1, 1, KT>(vec);
-    case 16 + 2: return pass_for<2, 1, KT>(vec);
-    case 16 + 3: return pass_for<3, 1, KT>(vec);
-    case 16 + 4: return pass_for<4, 1, KT>(vec);
-    case 16 + 5: return pass_for<5, 1, KT>(vec);
-    case 16 + 6: return pass_for<6, 1, KT>(vec);
-    case 16 + 7: return pass_for<7, 1, KT>(vec);
-    case 16 + 8: return pass_for<8, 1, KT>(vec);
-    case 32 + 5: return pass_for<5, 2, KT>(vec);
-    case 32 + 6: return pass_for<6, 2, KT>(vec);
-    case 32 + 7: return pass_for<7, 2, KT>(vec);
-    case 32 + 8: return pass_for<8, 2, KT>(vec);
-    case 64 + 5: return pass_for<5, 4, KT>(vec);
-    case 64 + 6: return pass_for<6, 4, KT>(vec);
-    case 64 + 7: return pass_for<7, 4, KT>(vec);
-    case 64 + 8: return pass_for<8, 4, KT>(vec);
+    case 16 + 1: return pass_for<1, 1, KT, STREAM>(vec);
+    case 16 + 2: return pass_for<2, 1, KT, STREAM>(vec);
+    case 16 + 3: return pass_for<3, 1, KT, STREAM>(vec);
+    case 16 + 4: return pass_for<4, 1, KT, STREAM>(vec);
+    case 16 + 5: return pass_for<5, 1, KT, STREAM>(vec);
+    case 16 + 6: return pass_for<6, 1, KT, STREAM>(vec);
+    case 16 + 7: return pass_for<7, 1, KT, STREAM>(vec);
+    case 16 + 8: return pass_for<8, 1, KT, STREAM>(vec);
+    case 32 + 5: return pass_for<5, 2, KT, STREAM>(vec);
+    case 32 + 6: return pass_for<6, 2, KT, STREAM>(vec);
+    case 32 + 7: return pass_for<7, 2, KT, STREAM>(vec);
+    case 32 + 8: return pass_for<8, 2, KT, STREAM>(vec);
+    case 64 + 5: return pass_for<5, 4, KT, STREAM>(vec);
+    case 64 + 6: return pass_for<6, 4, KT, STREAM>(vec);
+    case 64 + 7: return pass_for<7, 4, KT, STREAM>(vec);
+    case 64 + 8: return pass_for<8, 4, KT, STREAM>(vec);
     default: return {{nullptr, nullptr}};
     }
 }
@@ -715,8 +792,13 @@ PassPair pass_for_shape(const Shape &s, bool vec)
 template <int DMAX, int KT, int RT, bool FG>
 PassPair mfma_pass_pair(bool vec)
 {
-    if (vec) return {{k_batch_pass_mfma<true, DMAX, KT, TRON_LOSS_LR, RT, FG>, k_batch_pass_mfma<true, DMAX, KT, TRON_LOSS_L2SVM, RT, FG>}};
-    return {{k_batch_pass_mfma<false, DMAX, KT, TRON_LOSS_LR, RT, FG>, k_batch_pass_mfma<false, DMAX, KT, TRON_LOSS_L2SVM, RT, FG>}};
+    if constexpr (KT == 8) {   // logistic problems only
+        if (vec) return {{k_batch_pass_mfma<true, DMAX, KT, TRON_LOSS_LR, RT, FG>, nullptr}};
+        return {{k_batch_pass_mfma<false, DMAX, KT, TRON_LOSS_LR, RT, FG>, nullptr}};
+    } else {
+        if (vec) return {{k_batch_pass_mfma<true, DMAX, KT, TRON_LOSS_LR, RT, FG>, k_batch_pass_mfma<true, DMAX, KT, TRON_LOSS_L2SVM, RT, FG>}};
+        return {{k_batch_pass_mfma<false, DMAX, KT, TRON_LOSS_LR, RT, FG>, k_batch_pass_mfma<false, DMAX, KT, TRON_LOSS_L2SVM, RT, FG>}};
+    }
 }
 
 template <int KT, int RT, bool FG>
@@ -955,18 +1037,20 @@ static int batch_create_impl(tron_dataset *ds, int K, const uint32_t *member, in
 #define TRON_B(expr) do { hipError_t e__ = (expr); if (e__ != hipSuccess) return fail(hip_fail(e__, #expr, __FILE__, __LINE__)); } while (0)
     if (!b->pass.fn[0]) { set_error("tron_batch_create: internal: no kernel for E=%d L=%d", s.E, s.L); return fail(TRON_EINVAL); }
     // The pass as matrix instructions (8 or 16 problem columns; the tile of X of every wavefront in LDS, and where logistic
-    // function / gradient requests are served the exchange area), chosen per loss: above eight problems always; otherwise by
-    // what was faster when the lines were drawn.  ms a Hessian / function-gradient round of 5, 6, 7, 8 problems over 20M x 24, vector units
-    // against matrix units.  L2-SVM: 0.75 0.76 0.81 0.87 / 0.80 0.87 0.93 1.00 against 0.79 0.80 0.81 0.81 / 1.03 1.04 1.05 1.04.  Logistic: 0.82 0.88
-    // 0.94 1.01 / 1.23 1.32 1.41 1.53 against 0.94 0.97 0.99 1.01 / 1.32 1.37 1.46 1.49 -- and 2.41 with six problems when its line was drawn,
-    // before LossSum: it would lie at eight now.
-    const int mfma_from[2] = {5, 8};   // logistic, L2-SVM
+    // function / gradient requests are served the exchange area), chosen per loss: above eight problems always, and for logistic problems
+    // from seven on where a lane has eight columns, whose accumulators do not fit the registers of the vector kernel, from eight on over matrices
+    // above 288 MB, where neither is the faster one throughout.  us a function-gradient / Hessian call of 5, 6, 7, 8 problems over 10M rows, vector
+    // units against matrix units.  L2-SVM, 24 columns: 395 418 452 485 / 325 333 346 364 against 531 529 531 535 / 400 404 406 413; 12 columns, 8 problems:
+    // 320 / 200 against 383 / 261.  Logistic, 24 columns: 643 687 737 785 / 436 441 463 483 against 684 701 739 763 / 490 492 498 507; 30 columns: 726 766
+    // 823 991 / 560 564 722 910 against 764 782 820 845 / 562 575 580 584; 8 problems, 12 columns: 563 / 300 against 553 / 338; 4M x 16: 280 / 160 against
+    // 261 / 170; 1M x 24: 93 / 70 against 106 / 75.
+    const int mfma_from[2] = {s.L == 4 && s.E == 8 ? 7 : read_once(n, d) ? 8 : 9, 9};   // logistic, L2-SVM
     const int dmax = d <= 16 ? 16 : (d <= 24 ? 24 : 32);
     const size_t floor_lds = sizeof(double) * kWavesPerBlock * 32 * 16;   // the final sums of the four wavefronts
-    const int KTm = (K <= 8) ? 8 : 16;
     for (int l = 0; l < 2; ++l) {
         b->on_matrix_units[l] = K > 8 || g_tuning.batch_mfma > 0 || (g_tuning.batch_mfma < 0 && K >= mfma_from[l]);
         if (!b->on_matrix_units[l]) continue;
+        const int KTm = l == 0 && K <= 8 ? 8 : 16;
         // half tiles (measured: as fast or faster than whole tiles for both losses, 3 to 12% at 12 problems)
         const int rt = g_tuning.batch_mfma_rows != 0 ? (int)g_tuning.batch_mfma_rows : 32;
         b->pass.fn[l] = mfma_pass_select<true>(KTm, rt, d).fn[l];
@@ -1010,6 +1094,22 @@ static int batch_create_impl(tron_dataset *ds, int K, const uint32_t *member, in
     if (!b->on_matrix_units[0] && !b->on_matrix_units[1]) {
         // the two vector kernels share one grid (the larger residency), as they always have
         b->grid_pass[0] = b->grid_pass[1] = (int)grid_max;
+    }
+    if (tiles_stream(s.L) && read_once(n, d)) {
+        const PassPair streamed = b->KT == 4 ? pass_for_shape<4, true>(s, vec) : pass_for_shape<8, true>(s, vec);
+        const size_t through = TileStream<1, 2, 2, false>::bytes(d, kWavesPerBlock);
+        for (int l = 0; l < 2; ++l) {
+            if (b->on_matrix_units[l] || !streamed.fn[l]) continue;
+            TRON_B(hipFuncSetAttribute(reinterpret_cast<const void *>(streamed.fn[l]), hipFuncAttributeMaxDynamicSharedMemorySize, (int)through));
+            int at_once = 0;
+            TRON_B(hipOccupancyMaxActiveBlocksPerMultiprocessor(&at_once, reinterpret_cast<const void *>(streamed.fn[l]), kBlock, through));
+            if (at_once < 2) continue;   // from 29 (more than four problems) or 31 columns (logistic) on the tiles leave room for one workgroup
+            b->pass.fn[l] = streamed.fn[l];
+            b->pass_lds[l] = through;
+            const int rc = resident(streamed.fn[l], through, &b->grid_pass[l]);
+            if (rc != TRON_OK) return fail(rc);
+            if (b->grid_pass[l] > grid_max) grid_max = b->grid_pass[l];
+        }
     }
     b->grid_used = b->grid_pass[1];
     TRON_B(hipMalloc(reinterpret_cast<void **>(&b->member), sizeof(uint64_t) * (size_t)K * (size_t)b->ntiles));

@@ -51,6 +51,22 @@ struct Tile {
         return __ballot(__shfl((int)pred, (lane % RW) * L + lane / RW, kWave) != 0);
     }
 
+    // the same from the ballot of the owners, whose bits are in the order of the lanes: those of a row's U owners side by side
+    __device__ static __forceinline__ uint64_t rows_of_ballot(uint64_t b)
+    {
+        static_assert(RT == kWave && U == L, "");
+#pragma unroll
+        for (int i = 1; i < U; i *= 2) {   // the even bits to the lower half, the odd ones to the upper half
+            auto swap = [&](int by, uint64_t mask) { const uint64_t t = (b ^ (b >> by)) & mask; b ^= t ^ (t << by); };
+            swap(1, 0x2222222222222222ull);
+            swap(2, 0x0c0c0c0c0c0c0c0cull);
+            swap(4, 0x00f000f000f000f0ull);
+            swap(8, 0x0000ff000000ff00ull);
+            swap(16, 0x00000000ffff0000ull);
+        }
+        return b;
+    }
+
     // load the U x E block of this lane; out-of-range rows / columns read as zero.  rows: bit i clear = row row0 + i
     // is not needed (its coefficient is zero) and is not read at all
     __device__ static __forceinline__ void load(const double *__restrict__ X, int64_t n, int64_t d, int64_t row0,
@@ -131,20 +147,31 @@ struct Tile {
     __device__ static __forceinline__ void from_row_owner(double mine, double (&c)[U])
     {
         if constexpr (U == 1) c[0] = mine;
-        if constexpr (U == 2) { c[0] = dpp_move<0xA0>(mine); c[1] = dpp_move<0xF5>(mine); }   // quad_perm [0,0,2,2], [1,1,3,3]
-        if constexpr (U == 4) { c[0] = dpp_move<0x00>(mine); c[1] = dpp_move<0x55>(mine); c[2] = dpp_move<0xAA>(mine); c[3] = dpp_move<0xFF>(mine); }
+        if constexpr (U == 2) { c[0] = dpp_fetch<0xA0>(mine); c[1] = dpp_fetch<0xF5>(mine); }   // quad_perm [0,0,2,2], [1,1,3,3]
+        if constexpr (U == 4) { c[0] = dpp_fetch<0x00>(mine); c[1] = dpp_fetch<0x55>(mine); c[2] = dpp_fetch<0xAA>(mine); c[3] = dpp_fetch<0xFF>(mine); }
     }
 
-    // acc[e] summed over the lanes that hold the same columns, then over the workgroup's wavefronts (`waves` of them):
-    // column c goes to out[c * stride].  lds: waves * E * L doubles that nothing else uses any more.
-    __device__ static __forceinline__ void flush(double (&acc)[E], int64_t d, int lane, int wv, int waves, double *lds,
-                                                 double *__restrict__ out, int64_t stride)
+    // acc[e] summed over the lanes that hold the same columns, every one of which receives the sum: moves between lanes, no LDS (with
+    // shuffles through LDS a solve over 20,000 x 24 took 49 us instead of 47)
+    __device__ static __forceinline__ void sum_columns(double (&acc)[E])
     {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-#pragma unroll
-            for (int m = L; m < kWave; m <<= 1) acc[e] += __shfl_xor(acc[e], m, kWave);
+            if constexpr (L <= 1) acc[e] += dpp_fetch<0xB1>(acc[e]);
+            if constexpr (L <= 2) acc[e] += dpp_fetch<0x4E>(acc[e]);
+            if constexpr (L <= 4) acc[e] += other_quad_of_8(acc[e]);
+            if constexpr (L <= 8) acc[e] += dpp_fetch<0x128>(acc[e]);
+            if constexpr (L <= 16) acc[e] = add_row_pairs(acc[e]);
+            if constexpr (L <= 32) acc[e] = add_halves(acc[e]);
         }
+    }
+
+    // ... then over the workgroup's wavefronts (`waves` of them): column c goes to out[c * stride].  lds: waves * E * L doubles that
+    // nothing else uses any more.
+    __device__ static __forceinline__ void flush(double (&acc)[E], int64_t d, int lane, int wv, int waves, double *lds,
+                                                 double *__restrict__ out, int64_t stride)
+    {
+        sum_columns(acc);
         if (lane < L) {
 #pragma unroll
             for (int e = 0; e < E; ++e) lds[wv * (E * L) + col(lane, e)] = acc[e];
@@ -217,6 +244,14 @@ struct TileStream {
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): in registers, before the buffer is asked for again
         asm volatile("" ::: "memory");
         there = false;
+        if (rows != ~0ull) {   // uniform; rows that are not needed count as zeros, whatever lies in them
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool needed = (rows >> (u * T::RW + rl)) & 1u;
+#pragma unroll
+                for (int e = 0; e < E; ++e) x[u][e] = needed ? x[u][e] : 0.0;
+            }
+        }
     }
 
     __device__ static __forceinline__ void wait_loads()

@@ -17,6 +17,15 @@ __device__ __forceinline__ double dpp_move(double v)
     return __hiloint2double(hi, lo);
 }
 
+// The same where every lane takes part: nothing has to lie in the result's registers before, which dpp_move copies v to
+template <int CTRL>
+__device__ __forceinline__ double dpp_fetch(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
 __device__ __forceinline__ double read_lane(double v, int lane)
 {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
@@ -93,6 +102,14 @@ __device__ __forceinline__ double group_sum(double v, int g)
     if (g == 16) return v;
     if (g == 32) return v + __shfl_xor(v, 16, kWave);
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+}
+
+// *a += v with the LDS add instruction: one operation instead of a read, an add and a write, and nothing to wait for.
+// Used where no two lanes address the same word between two barriers and a lane's own additions to one word are issued
+// in program order (LDS operations of a wavefront complete in order), so the sum is built in a fixed order.
+__device__ __forceinline__ void lds_add(double *a, double v)
+{
+    (void)__hip_atomic_fetch_add(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // ---- inclusive scans over the 64 lanes of a wavefront, through DPP (no LDS).

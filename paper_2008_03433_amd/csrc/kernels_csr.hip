@@ -1612,14 +1612,6 @@ struct TileRegs {
     int4 hdr;
 };
 
-// *a += v with the LDS add instruction: one operation instead of a read, an add and a write, and nothing to wait for.
-// Used where no two lanes address the same word between two barriers and a lane's own additions to one word are issued
-// in program order (LDS operations of a wavefront complete in order), so the sum is built in a fixed order.
-__device__ __forceinline__ void lds_add(double *a, double v)
-{
-    (void)__hip_atomic_fetch_add(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 // the data of tile T, whose header is h; columns clamped to the tile's last one
 __device__ __forceinline__ void load_tile(TileRegs &r, const TilePtrs &tp, const double *__restrict__ x, int4 h, int64_t T)
 {
