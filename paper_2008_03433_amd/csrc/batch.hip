@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
     // The pass over the wavefront's tiles.  M: what every problem that is not idle asks for, or kMixed.  Knowing it takes the questions out of
     // the loop over the problems: they were 305 scalar instructions a tile beside 845 vector ones (six problems, 24 columns).
     constexpr int kMixed = -1;
-    auto sweep = [&](auto what) {
+    auto sweep = [&](auto what) __attribute__((always_inline)) {
         constexpr int M = decltype(what)::value;
         const auto mode_of = [&](int k) { return M == kMixed ? mode[k] : M; };
         const bool any_fg = M == kMixed ? fg != 0 : M == MODE_FG;
@@ -297,6 +297,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_pass(int64_t n, int64_t d, 
 //     lanes hold in register v are the summation index, so C is used where it lies.  A = X[row][column] read from LDS
 //     along a row: conflict-free.  Problems asking for the Hessian diagonal use the same instructions with A squared and
 //     C = D.
+// What bounds it: a Hessian round 12 logistic problems x 24 columns memory (20M rows: 3.84 GB of X and 1.92 GB of D in 1.0 ms), now that a tile takes
+// 195 vector instructions, 56 of them matrix ones, and 190 scalar ones; it took 503 and 450, and 1.05 ms, with the problems' modes looked up for each
+// element, 32 lane reads for the union of the words, selects for rows and places that are all there, and addresses formed a lane at
+// a time.  A function-gradient round instructions: 1180 vector ones a tile (1420), half of them loss terms, 1.75 ms (1.81).  us a
+// call of 12 problems over 4M rows, before / now, Hessian: 24 columns logistic 246 / 223, L2-SVM 189 / 182; 17 columns 240 / 217, 225 / 189; function-gradient
+// 10 columns 324 / 300, 180 / 155; 30 columns 426 / 429, 277 / 256.
 // Results go to the same partials array, in the same layout, as k_batch_pass writes: the steps after the pass do not
 // know which kernel ran.  Sums are formed in a fixed order (the instruction's, then tiles in order, wavefronts 0..3).
 typedef double mfma4 __attribute__((ext_vector_type(4)));
@@ -352,20 +358,16 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int D = (int)d;
     int mode[KT], dslot[KT];
-    bool any = false, any_fg = false, any_hv = false, any_diag = false, any_mul = false, any_exd = false;
+    unsigned live = 0, fg = 0, hv = 0;   // problems by what they ask for
 #pragma unroll
     for (int k = 0; k < KT; ++k) {
         mode[k] = ctl->mode[k];
         dslot[k] = ctl->dslot[k];
-        any |= mode[k] != MODE_IDLE;
-        any_fg |= mode[k] == MODE_FG;
-        any_hv |= mode[k] == MODE_HV;
-        any_diag |= mode[k] == MODE_DIAG;
-        any_mul |= (FG && mode[k] == MODE_FG) || mode[k] == MODE_HV;
-        any_exd |= !svm && (mode[k] == MODE_HV || mode[k] == MODE_DIAG);
+        live |= (unsigned)(mode[k] != MODE_IDLE) << k;
+        fg |= (unsigned)(mode[k] == MODE_FG) << k;
+        hv |= (unsigned)(mode[k] == MODE_HV) << k;
     }
-    any_fg = FG && any_fg;
-    if (!any) return;
+    if (live == 0) return;
     // The unit in LDS: row r at r S, S = the first length >= d whose rows start in different banks for 16 consecutive rows
     // (16-byte pieces: S = 2 mod 4; 8-byte pieces: S odd).  Every lane copies NP pieces per unit; those past the unit
     // (d < DMAX) are fetched from the first bytes of X and land in the slack behind it.
@@ -384,6 +386,9 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
     const int rowl = lane & (RT - 1), sub = lane / RT;   // row-per-lane layout: row of the unit, problem of a group of PP
     // logistic D of this lane's problem in the slot it reads; lanes without such a problem stay at the start of the array
     const double *const DvalM = (!svm && pk) ? Dval + ((int64_t)p * 2 + dslotM) * n : Dval;
+    // where every problem is in its Hessian product, the other lanes read along with the first problem (their result columns nobody reads)
+    const int pA = __ffs(live) - 1;
+    const double *const DvalH = (!svm && modeM == MODE_IDLE) ? Dval + ((int64_t)pA * 2 + ctl->dslot[pA]) * n : DvalM;
     double Vop[DMAX / 4];
 #pragma unroll
     for (int kk = 0; kk < DMAX / 4; ++kk) {
@@ -405,17 +410,22 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
     const int64_t first = wave_id * per_wave;
     const int64_t last = (first + per_wave < ntiles) ? first + per_wave : ntiles;
     const uint64_t inv_d = (0x100000000ull + (uint64_t)D - 1) / (uint64_t)D;   // row of element e < 2048: (e inv_d) >> 32 (2^32 itself for d = 1)
-    // per piece of this lane, fixed for the whole pass: its row in the unit (RT = past the unit) and where it goes in LDS
-    uint32_t prow[NP], plds[NP];
+    // per piece of this lane, fixed for the whole pass: where it goes in LDS
+    uint32_t plds[NP];
 #pragma unroll
     for (int it = 0; it < NP; ++it) {
         const uint32_t e = (uint32_t)(it * kWave + lane) * PW;
         const uint32_t row = (uint32_t)(((uint64_t)e * inv_d) >> 32);
-        prow[it] = row < (uint32_t)RT ? row : (uint32_t)RT;
         plds[it] = row < (uint32_t)RT ? row * (uint32_t)S + (e - row * (uint32_t)D) : (uint32_t)(xs_len - 2);
     }
 
+    const int pieces = RT * D / PW;   // of a unit
+    const bool once = !FG && read_once(n, d);   // (a round with loss terms is not bound by memory)
     double xr[NP][PW];
+#pragma unroll
+    for (int it = 0; it < NP; ++it)
+#pragma unroll
+        for (int e = 0; e < PW; ++e) xr[it][e] = 0.0;
     double lossM = 0.0;   // L2-SVM: loss terms of this lane's rows of its problem
     LossSum<LOSS> lossK[KT / PP];   // logistic: losses of this lane's row, by problem (PP k + sub)
     int adds = 0;
@@ -428,17 +438,11 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
     // wait for every load in flight where such paths join): a piece of a row that concerns no problem, or past the end, is
     // fetched from the first bytes of X instead -- one cached line for all of them -- and copied like the others; its row
     // coefficient is zero in every problem and X is finite, so what lies there does not matter.
-    auto fetch = [&](int64_t tile, int h, uint64_t urows) {
+    auto fetch = [&](int64_t tile, int h, uint64_t urows) __attribute__((always_inline)) {
         const int64_t row0 = tile * kWave + RT * h;
         const double *base = X + row0 * d;
-        const bool full = urows == (RT == kWave ? ~0ull : 0xffffffffull) && row0 + RT <= n;   // the same for every lane: no per-row questions
-#pragma unroll
-        for (int it = 0; it < NP; ++it) {
-            const uint32_t e = (uint32_t)(it * kWave + lane) * PW;
-            const uint32_t row = prow[it];
-            bool take = row < (uint32_t)RT;
-            if (!full) take = take && ((urows >> (row & (RT - 1))) & 1u) && row0 + row < n;
-            const double *src = take ? base + e : X;
+        const bool full = urows == (RT == kWave ? ~0ull : 0xffffffffull) && row0 + RT <= n;
+        auto load = [&](int it, const double *src) __attribute__((always_inline)) {
             if constexpr (VEC) {
                 const double2 t = *reinterpret_cast<const double2 *>(src);
                 xr[it][0] = t.x;
@@ -446,9 +450,40 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
             } else {
                 xr[it][0] = *src;
             }
+        };
+        if (full) {   // no per-row questions; the same address in every lane but for its own place.  Pieces past the unit keep what they hold.
+            if (once) {   // (see read_once)
+                auto at = (const __attribute__((address_space(1))) double *)(base + lane * PW);
+                asm volatile("" : "+v"(at));   // (otherwise the compiler makes one ordinary load of these and those below)
+#pragma unroll
+                for (int it = 0; it < NP; ++it) {
+                    if (it >= pieces / kWave) {
+                        if (it * kWave < pieces) load(it, it * kWave + lane < pieces ? base + it * kWave * PW + lane * PW : X);
+                    } else if constexpr (VEC) {
+                        const v2d t = __builtin_nontemporal_load((const __attribute__((address_space(1))) v2d *)(at + it * kWave * PW));
+                        xr[it][0] = t.x;
+                        xr[it][1] = t.y;
+                    } else xr[it][0] = __builtin_nontemporal_load(at + it * kWave * PW);
+                }
+                return;
+            }
+#pragma unroll
+            for (int it = 0; it < NP; ++it) {
+                if (it < pieces / kWave) load(it, base + it * kWave * PW + lane * PW);   // uniform
+                else if (it * kWave < pieces) load(it, it * kWave + lane < pieces ? base + it * kWave * PW + lane * PW : X);
+            }
+            return;
+        }
+#pragma unroll
+        for (int it = 0; it < NP; ++it) {
+            uint32_t at = (uint32_t)lane;
+            asm volatile("" : "+v"(at));   // (not to be kept in registers for all units)
+            const uint32_t e = (it * kWave + at) * PW, row = (uint32_t)(((uint64_t)e * inv_d) >> 32);
+            const bool take = row < (uint32_t)RT && ((urows >> (row & (RT - 1))) & 1u) && row0 + row < n;
+            load(it, take ? base + e : X);
         }
     };
-    auto to_lds = [&]() {
+    auto to_lds = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int it = 0; it < NP; ++it) {
             if constexpr (VEC) *reinterpret_cast<double2 *>(Xs + plds[it]) = make_double2(xr[it][0], xr[it][1]);
@@ -474,181 +509,213 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
         w0 = word_ok(first) ? word_raw(first) : 0ull;
         w1 = word_ok(first + 1) ? word_raw(first + 1) : 0ull;
     }
-    uint64_t wk[KT], rows_cur = 0;
+    // Scalar copies of the problems' words (where a row's terms are formed problem by problem), and the rows that concern any of them
+    uint64_t wk[kHasEx ? KT : 1];
+    auto scalar_words = [&](uint64_t w, uint64_t (&each)[kHasEx ? KT : 1]) __attribute__((always_inline)) -> uint64_t {
+        uint64_t rows = 0;
+        if constexpr (kHasEx) {
 #pragma unroll
-    for (int k = 0; k < KT; ++k) {
-        wk[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(w0 >> 32), k) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w0, k);
-        rows_cur |= wk[k];
-    }
-    int ycur = 1;   // the labels travel with the unit: asked for with its loads, first touched after they have all arrived
-    if (first < last && unit_rows(rows_cur, 0) != 0) {
-        if (any_fg) ycur = label_raw(first, 0);
-        fetch(first, 0, unit_rows(rows_cur, 0));
-    }
-    for (int64_t tile = first; tile < last; ++tile) {
-        const uint64_t w2 = word_raw(tile + 2);
-        uint64_t wkn[KT], rows_next = 0;
-#pragma unroll
-        for (int k = 0; k < KT; ++k) {
-            wkn[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(w1 >> 32), k) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w1, k);
-            rows_next |= wkn[k];
-        }
-        // the word of this lane's problem
-        uint64_t wordM = 0;
-        if (svm || any_fg) wordM = lane_value(w0, p);
-#pragma unroll 1
-        for (int h = 0; h < NH; ++h) {
-            const uint64_t urows = unit_rows(rows_cur, h);
-            if (urows != 0) to_lds();
-            // the loads of the unit after this one
-            int ynext = 1;
-            {
-                const bool same_tile = h + 1 < NH;
-                const int64_t nt = same_tile ? tile : tile + 1;
-                const int nh = same_tile ? h + 1 : 0;
-                const uint64_t nrows = unit_rows(same_tile ? rows_cur : rows_next, nh);
-                if (nt < last && nrows != 0) {
-                    if (any_fg) ynext = label_raw(nt, nh);
-                    fetch(nt, nh, nrows);
-                }
+            for (int k = 0; k < KT; ++k) {
+                each[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(w >> 32), k) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w, k);
+                rows |= each[k];
             }
-            if (urows != 0) {
-                wave_lds_fence();
-                // Z = X V for rows 16 s .. 16 s + 15 of the unit
-                auto z_of = [&](int s) {
-                    mfma4 z = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int kk = 0; kk < DMAX / 4; ++kk) {   // columns past d: V is zero there and what A reads is finite
-                        const double a = Xs[(16 * s + p) * S + 4 * kk + g];
-                        z = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Vop[kk], z, 0, 0, 0);
+        } else {   // over the first sixteen lanes
+            int lo = (int)(uint32_t)w, hi = (int)(uint32_t)(w >> 32);
+            auto fold = [](int v) {
+                v |= __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true);   // row_ror:8, 4, 2, 1
+                v |= __builtin_amdgcn_mov_dpp(v, 0x124, 0xf, 0xf, true);
+                v |= __builtin_amdgcn_mov_dpp(v, 0x122, 0xf, 0xf, true);
+                return v | __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, true);
+            };
+            rows = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(fold(hi)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane(fold(lo));
+        }
+        return rows;
+    };
+    uint64_t rows_cur = scalar_words(w0, wk);
+    // The wavefront's tiles.  M: what every problem that is not idle asks for, or kMixed.
+    constexpr int kMixed = -1;
+    auto sweep = [&](auto what) __attribute__((always_inline)) {
+        constexpr int M = decltype(what)::value;
+        const bool any_fg = FG && (M == kMixed ? fg != 0 : M == MODE_FG), any_hv = M == kMixed ? hv != 0 : M == MODE_HV;
+        const bool any_diag = M == kMixed && live != (fg | hv), any_mul = M != kMixed || (FG ? (fg | hv) : hv) != 0;
+        const bool any_exd = !svm && (M == kMixed ? live != fg : M == MODE_HV);
+        const auto mode_of = [&](int k) { return M == kMixed ? mode[k] : (live >> k & 1u) ? M : MODE_IDLE; };
+        // a lane whose problem is idle, or that has none, forms something finite or not that nobody reads
+        const int modeL = M == kMixed ? modeM : M;
+        int ycur = 1;   // the labels travel with the unit: asked for with its loads, first touched after they have all arrived
+        if (first < last && unit_rows(rows_cur, 0) != 0) {
+            if (any_fg) ycur = label_raw(first, 0);
+            fetch(first, 0, unit_rows(rows_cur, 0));
+        }
+        for (int64_t tile = first; tile < last; ++tile) {
+            const uint64_t w2 = word_raw(tile + 2);
+            uint64_t wkn[kHasEx ? KT : 1];
+            const uint64_t rows_next = scalar_words(w1, wkn);
+            // the word of this lane's problem
+            uint64_t wordM = 0;
+            if (svm || any_fg) wordM = lane_value(w0, p);
+#pragma unroll 1
+            for (int h = 0; h < NH; ++h) {
+                const uint64_t urows = unit_rows(rows_cur, h);
+                if (urows != 0) to_lds();
+                // the loads of the unit after this one
+                int ynext = 1;
+                {
+                    const bool same_tile = h + 1 < NH;
+                    const int64_t nt = same_tile ? tile : tile + 1;
+                    const int nh = same_tile ? h + 1 : 0;
+                    const uint64_t nrows = unit_rows(same_tile ? rows_cur : rows_next, nh);
+                    if (nt < last && nrows != 0) {
+                        if (any_fg) ynext = label_raw(nt, nh);
+                        fetch(nt, nh, nrows);
                     }
-                    return z;
-                };
-                if (kHasEx && any_fg) {
-                    // logistic function / gradient requests: Z to the row-per-lane layout, the terms once per row and
-                    // problem that asks (D stored from there), zhat back
+                }
+                if (urows != 0) {
+                    wave_lds_fence();
+                    // Z = X V for rows 16 s .. 16 s + 15 of the unit
+                    auto z_of = [&](int s) {
+                        mfma4 z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                        for (int kk = 0; kk < DMAX / 4; ++kk) {   // columns past d: V is zero there and what A reads is finite
+                            const double a = Xs[(16 * s + p) * S + 4 * kk + g];
+                            z = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Vop[kk], z, 0, 0, 0);
+                        }
+                        return z;
+                    };
+                    if (kHasEx && any_fg) {
+                        // logistic function / gradient requests: Z to the row-per-lane layout, the terms once per row and
+                        // problem that asks (D stored from there), zhat back
+#pragma unroll 1
+                        for (int s = 0; s < NS; ++s) {
+                            const mfma4 z = z_of(s);
+                            if (pk && modeL == MODE_FG) {
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) Ex[p * kExRow + 16 * s + 4 * v + g] = z[v];
+                            }
+                        }
+                        wave_lds_fence();
+                        const double yrow = (double)ycur;
+#pragma unroll
+                        for (int k = 0; k < KT; k += PP) {
+                            bool some = false;
+                            int mk[PP], dk[PP];
+                            uint64_t wq[PP];
+#pragma unroll
+                            for (int j = 0; j < PP; ++j) {
+                                mk[j] = mode_of(k + j);
+                                dk[j] = dslot[k + j];
+                                wq[j] = wk[k + j];
+                                some |= mk[j] == MODE_FG;
+                            }
+                            if (!some) continue;   // uniform
+                            const int kk = k + sub;
+                            const bool act = by_sub_i(mk) == MODE_FG && kk < K;
+                            const double z = Ex[(kk < K ? kk : 0) * kExRow + rowl];
+                            const bool mine = act && ((by_sub_u(wq) >> (RT * h + rowl)) & 1u);
+                            LossTerm alpha;
+                            double zhat, Di;
+                            loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
+                            if (!mine) { alpha = LossTerm{0.0, 0.0}; zhat = 0.0; Di = 0.0; }
+                            lossK[k / PP].add(alpha);
+                            if (mine) Dval[((int64_t)kk * 2 + by_sub_i(dk)) * n + tile * kWave + RT * h + rowl] = Di;
+                            if (act) Ex[kk * kExRow + rowl] = zhat;
+                        }
+                        if ((++adds & (LossSum<LOSS>::kAdds - 1)) == 0) {
+#pragma unroll
+                            for (int k = 0; k < KT / PP; ++k) lossK[k].scale();
+                        }
+                        wave_lds_fence();
+                    }
+                    // labels of the unit's rows as a word (the same in every lane)
+                    const uint64_t yword = (svm && any_fg) ? __ballot(ycur > 0) : 0ull;
+                    // G += X^T C, 16 rows at a time
 #pragma unroll 1
                     for (int s = 0; s < NS; ++s) {
-                        const mfma4 z = z_of(s);
-                        if (modeM == MODE_FG) {
+                        // logistic D of the lane's four elements, asked for before the products that form Z (zero outside the
+                        // problem's rows: never written there); no load sits behind a per-lane branch
+                        double ev[4] = {0.0, 0.0, 0.0, 0.0};
+                        bool evok[4] = {false, false, false, false};
+                        if (M == MODE_HV && any_exd && tile * kWave + kWave <= n) {   // uniform
+                            const double *const at = DvalH + (tile * kWave + RT * h + 16 * s + g);
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) Ex[p * kExRow + 16 * s + 4 * v + g] = z[v];
+                            for (int v = 0; v < 4; ++v) ev[v] = at[4 * v];
+                        } else if (any_exd) {   // uniform
+                            const int64_t r0 = tile * kWave + RT * h + 16 * s + g;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                evok[v] = exM && r0 + 4 * v < n;
+                                ev[v] = *(evok[v] ? DvalM + r0 + 4 * v : Dval);
+                                if (M == MODE_HV && !evok[v]) ev[v] = 0.0;   // rows past n: what lies in LDS in their place is not theirs
+                            }
                         }
-                    }
-                    wave_lds_fence();
-                    const double yrow = (double)ycur;
-#pragma unroll
-                    for (int k = 0; k < KT; k += PP) {
-                        bool some = false;
-                        int mk[PP], dk[PP];
-                        uint64_t wq[PP];
-#pragma unroll
-                        for (int j = 0; j < PP; ++j) {
-                            mk[j] = mode[k + j];
-                            dk[j] = dslot[k + j];
-                            wq[j] = wk[k + j];
-                            some |= mk[j] == MODE_FG;
-                        }
-                        if (!some) continue;   // uniform
-                        const int kk = k + sub;
-                        const bool act = by_sub_i(mk) == MODE_FG && kk < K;
-                        const double z = Ex[(kk < K ? kk : 0) * kExRow + rowl];
-                        const bool mine = act && ((by_sub_u(wq) >> (RT * h + rowl)) & 1u);
-                        LossTerm alpha;
-                        double zhat, Di;
-                        loss_terms_dev<LOSS>(z, yrow, alpha, zhat, Di);
-                        if (!mine) { alpha = LossTerm{0.0, 0.0}; zhat = 0.0; Di = 0.0; }
-                        lossK[k / PP].add(alpha);
-                        if (mine) Dval[((int64_t)kk * 2 + by_sub_i(dk)) * n + tile * kWave + RT * h + rowl] = Di;
-                        if (act) Ex[kk * kExRow + rowl] = zhat;
-                    }
-                    if ((++adds & (LossSum<LOSS>::kAdds - 1)) == 0) {
-#pragma unroll
-                        for (int k = 0; k < KT / PP; ++k) lossK[k].scale();
-                    }
-                    wave_lds_fence();
-                }
-                // labels of the unit's rows as a word (the same in every lane)
-                const uint64_t yword = (svm && any_fg) ? __ballot(ycur > 0) : 0ull;
-                // G += X^T C, 16 rows at a time
-#pragma unroll 1
-                for (int s = 0; s < NS; ++s) {
-                    // logistic D of the lane's four elements, asked for before the products that form Z (zero outside the
-                    // problem's rows: never written there); no load sits behind a per-lane branch
-                    double ev[4] = {0.0, 0.0, 0.0, 0.0};
-                    bool evok[4] = {false, false, false, false};
-                    if (any_exd) {   // uniform
-                        const int64_t r0 = tile * kWave + RT * h + 16 * s + g;
+                        mfma4 z = {0.0, 0.0, 0.0, 0.0};
+                        if (any_hv || (svm && any_fg)) z = z_of(s);
+                        // every LDS read of the 16 rows first (none behind a per-lane condition), then the selects and the products.
+                        // Columns of X past d give result rows that nobody reads: A is used as it lies in LDS.
+                        double a1v[4], a2v[4], ex[4];
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            evok[v] = exM && r0 + 4 * v < n;
-                            ev[v] = *(evok[v] ? DvalM + r0 + 4 * v : Dval);
+                            const int r = 16 * s + 4 * v + g;
+                            ex[v] = kHasEx ? Ex[(pk ? p : 0) * kExRow + r] : 0.0;   // zhat of a logistic function / gradient request
+                            a1v[v] = Xs[r * S + p];
+                            a2v[v] = (DMAX > 16) ? Xs[r * S + 16 + p] : 0.0;
                         }
-                    }
-                    mfma4 z = {0.0, 0.0, 0.0, 0.0};
-                    if (any_hv || (svm && any_fg)) z = z_of(s);
-                    // every LDS read of the 16 rows first (none behind a per-lane condition), then the selects and the products.
-                    // Columns of X past d give result rows that nobody reads: A is used as it lies in LDS.
-                    double a1v[4], a2v[4], ex[4];
+                        const uint32_t bits = (uint32_t)(wordM >> (RT * h + 16 * s + g));   // bit 4 v: row 16 s + 4 v + g of the unit
+                        const uint32_t ybits = (uint32_t)(yword >> (16 * s + g));            // the same rows' labels
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int r = 16 * s + 4 * v + g;
-                        ex[v] = kHasEx ? Ex[(pk ? p : 0) * kExRow + r] : 0.0;   // zhat of a logistic function / gradient request
-                        a1v[v] = Xs[r * S + p];
-                        a2v[v] = (DMAX > 16) ? Xs[r * S + 16 + p] : 0.0;
-                    }
-                    const uint32_t bits = (uint32_t)(wordM >> (RT * h + 16 * s + g));   // bit 4 v: row 16 s + 4 v + g of the unit
-                    const uint32_t ybits = (uint32_t)(yword >> (16 * s + g));            // the same rows' labels
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const double e = evok[v] ? ev[v] : 0.0;
-                        const bool bit = (bits >> (4 * v)) & 1u;
-                        double cfg = 0.0;   // zhat of a function / gradient request
-                        if (kHasEx) cfg = (modeM == MODE_FG) ? ex[v] : 0.0;
-                        if (svm && any_fg) {   // uniform
-                            const double yv = ((ybits >> (4 * v)) & 1u) ? 1.0 : -1.0;
-                            double alpha, zhat, Di;   // L2-SVM only
-                            loss_terms_dev<LOSS>(z[v], yv, alpha, zhat, Di);
-                            const bool mine = modeM == MODE_FG && bit;   // a row of this lane's problem (rows past n have no bit)
-                            lossM += mine ? alpha : 0.0;
-                            cfg = mine ? zhat : 0.0;
-                            const int rt = RT * h + 16 * s + 4 * v + g;   // the row in its tile
-                            nbM |= (uint64_t)(mine && Di != 0.0) << rt;
-                        }
-                        double c;
-                        if (svm) c = (modeM == MODE_HV) ? (bit ? z[v] : 0.0) : cfg;
-                        else c = (modeM == MODE_HV) ? e * z[v] : cfg;
-                        if (any_mul) {
-                            G1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1v[v], c, G1, 0, 0, 0);
-                            if (DMAX > 16) G2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a2v[v], c, G2, 0, 0, 0);
-                        }
-                        if (any_diag) {
-                            double cd;
-                            if (svm) cd = (modeM == MODE_DIAG && bit) ? 2.0 : 0.0;
-                            else cd = (modeM == MODE_DIAG) ? e : 0.0;
-                            G1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1v[v] * a1v[v], cd, G1, 0, 0, 0);
-                            if (DMAX > 16) G2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a2v[v] * a2v[v], cd, G2, 0, 0, 0);
+                        for (int v = 0; v < 4; ++v) {
+                            const double e = M == MODE_HV || evok[v] ? ev[v] : 0.0;
+                            const bool bit = (bits >> (4 * v)) & 1u;
+                            double cfg = 0.0;   // zhat of a function / gradient request
+                            if (kHasEx) cfg = (modeL == MODE_FG) ? ex[v] : 0.0;
+                            if (svm && any_fg) {   // uniform
+                                const double yv = ((ybits >> (4 * v)) & 1u) ? 1.0 : -1.0;
+                                double alpha, zhat, Di;   // L2-SVM only
+                                loss_terms_dev<LOSS>(z[v], yv, alpha, zhat, Di);
+                                const bool mine = modeL == MODE_FG && bit;   // a row of this lane's problem (rows past n have no bit)
+                                lossM += mine ? alpha : 0.0;
+                                cfg = mine ? zhat : 0.0;
+                                const int rt = RT * h + 16 * s + 4 * v + g;   // the row in its tile
+                                nbM |= (uint64_t)(mine && Di != 0.0) << rt;
+                            }
+                            double c;
+                            if (svm) c = (modeL == MODE_HV) ? (bit ? z[v] : 0.0) : cfg;
+                            else c = (modeL == MODE_HV) ? e * z[v] : cfg;
+                            if (any_mul) {
+                                G1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1v[v], c, G1, 0, 0, 0);
+                                if (DMAX > 16) G2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a2v[v], c, G2, 0, 0, 0);
+                            }
+                            if (any_diag) {
+                                double cd;
+                                if (svm) cd = (modeM == MODE_DIAG && bit) ? 2.0 : 0.0;
+                                else cd = (modeM == MODE_DIAG) ? e : 0.0;
+                                G1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1v[v] * a1v[v], cd, G1, 0, 0, 0);
+                                if (DMAX > 16) G2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a2v[v] * a2v[v], cd, G2, 0, 0, 0);
+                            }
                         }
                     }
+                    wave_lds_fence();   // the next unit is written over this one
                 }
-                wave_lds_fence();   // the next unit is written over this one
+                asm volatile("" : "+v"(ynext));   // nothing of the next unit's loads is touched before this point
+                ycur = ynext;
             }
-            asm volatile("" : "+v"(ynext));   // nothing of the next unit's loads is touched before this point
-            ycur = ynext;
-        }
-        if (svm && any_fg) {
-            // the four lanes of a problem hold disjoint rows' bits of its new word; a tile without rows still gets its zero
-            uint64_t word = nbM | lane_value(nbM, lane ^ 16);
-            word |= lane_value(word, lane ^ 32);
-            if (g == 0 && modeM == MODE_FG) Dbits_out[((int64_t)p * 2 + dslotM) * ntiles + tile] = word;
-            nbM = 0;
-        }
-        w0 = w1;
-        w1 = word_ok(tile + 2) ? w2 : 0ull;
-        rows_cur = rows_next;
+            if (svm && any_fg) {
+                // the four lanes of a problem hold disjoint rows' bits of its new word; a tile without rows still gets its zero
+                uint64_t word = nbM | lane_value(nbM, lane ^ 16);
+                word |= lane_value(word, lane ^ 32);
+                if (g == 0 && modeM == MODE_FG) Dbits_out[((int64_t)p * 2 + dslotM) * ntiles + tile] = word;
+                nbM = 0;
+            }
+            w0 = w1;
+            w1 = word_ok(tile + 2) ? w2 : 0ull;
+            rows_cur = rows_next;
 #pragma unroll
-        for (int k = 0; k < KT; ++k) wk[k] = wkn[k];
-    }
+            for (int k = 0; k < (kHasEx ? KT : 1); ++k) wk[k] = wkn[k];
+        }
+    };
+    if (!FG && live == hv) sweep(std::integral_constant<int, MODE_HV>{});
+    else if (FG && live == fg) sweep(std::integral_constant<int, FG ? MODE_FG : kMixed>{});
+    else sweep(std::integral_constant<int, kMixed>{});
     // wavefronts 0..3 added in order; result register v of lane (g, p) is column 4 v + g (G1) / 16 + 4 v + g (G2) of problem p
     __syncthreads();
     double *Gs = dyn;   // [wavefront][column 0..31][problem 0..15]
@@ -1058,9 +1125,9 @@ static int batch_create_impl(tron_dataset *ds, int K, const uint32_t *member, in
         if (b->pass_lds[l] < floor_lds) b->pass_lds[l] = floor_lds;
         TRON_B(hipFuncSetAttribute(reinterpret_cast<const void *>(b->pass.fn[l]), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->pass_lds[l]));
         if (g_tuning.batch_lean != 0) {
-            // rounds without function / gradient requests: three or four wavefronts per SIMD; whole tiles for the L2-SVM,
-            // half tiles for the logistic loss (measured: 3% either way)
-            const int rt_lean = g_tuning.batch_mfma_rows != 0 ? (int)g_tuning.batch_mfma_rows : (l == 1 ? 64 : 32);
+            // rounds without function / gradient requests: three to five wavefronts per SIMD; half tiles here too (with whole ones the L2-SVM
+            // kernel does not fit its registers from 17 columns on: 12 problems over 4M x 17 530 us a call, 189 with half tiles)
+            const int rt_lean = g_tuning.batch_mfma_rows != 0 ? (int)g_tuning.batch_mfma_rows : 32;
             b->pass_nofg.fn[l] = mfma_pass_select<false>(KTm, rt_lean, d).fn[l];
             b->pass_nofg_lds[l] = sizeof(double) * kWavesPerBlock * (size_t)mfma_wave_doubles(dmax, 0, rt_lean);
             if (b->pass_nofg_lds[l] < floor_lds) b->pass_nofg_lds[l] = floor_lds;
