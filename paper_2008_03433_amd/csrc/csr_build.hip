@@ -4,7 +4,7 @@
 //
 // Creating a handle from host arrays was the largest part of a training that runs once: 1.05M entries took 4.2 ms on eight host threads (passes over
 // the entries with random access, starting the threads, copies of some hundred kilobytes at 2 to 3 GB/s), of which 0.4 ms are the
-// transfer of the arrays.  This way: @@ ms.
+// transfer of the arrays.  This way: 1.5 ms (2.2 with arrays that the program has not passed before).
 #include <algorithm>
 #include <cstring>
 #include <new>
