@@ -247,7 +247,7 @@ TRON_API int tron_solve(tron_dataset *ds, const tron_params *params, double *w_d
  * Dense handles with d <= TRON_BATCH_MAX_D only (sparse handles and wider matrices: one tron_solve per problem).
  * Per tile of 64 instances the pass is two skinny matrix products (64 x d by d x K, and d x 64 by 64 x K).  They run
  * on the vector units, or as fp64 matrix instructions with the problems as the sixteen result columns: always above
- * eight problems, below that per loss (L2-SVM: eight problems, logistic loss: five and more); knob "batch_mfma".
+ * eight problems, and for some logistic batches of seven or eight; knob "batch_mfma".
  * Same results up to summation order.
  * ------------------------------------------------------------------------------------------ */
 typedef struct tron_batch tron_batch; /* opaque: membership bits, per-problem D, solver state, work space */
@@ -369,15 +369,14 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  *   solve starts again as with "solve_resident" = 1: microseconds, -1 (default) a tenth of a second, 0 not at all (and then as with
  *   "solve_resident" = 0).  After the k-th give-up in a row a handle's next 2^(k-1) solves do not try one launch.
  * "batch_grid" (0..4096): workgroups of the multi-problem pass (0 = as many as are resident at once).
- * "batch_mfma_rows" (0/32/64): rows of X a wavefront of the matrix-unit pass keeps in LDS at a time (0: 32, except 64
- *                in the L2-SVM's rounds without function / gradient requests).
+ * "batch_mfma_rows" (0/32/64): rows of X a wavefront of the matrix-unit pass keeps in LDS at a time (0: 32).
  * "batch_lean" (0/1, default 1): batches created afterwards run a round of the matrix-unit pass in which no problem asks
  *                for function and gradient (the Hessian-vector calls; inside tron_batch_solve, for matrices of 400 MB
  *                or more, where the host waits for the requests of every round) with a kernel compiled without the loss
  *                terms of such requests: fewer registers, so more wavefronts per SIMD.
  * "batch_mfma" (-1/0/1): batches created afterwards run the multi-problem pass on the fp64 matrix units (1), or on the
- *                vector units where those can hold the batch, i.e. up to eight problems (0); -1 (default): per loss,
- *                the matrix units from eight problems on for the L2-SVM and from five on for the logistic loss.
+ *                vector units where those can hold the batch, i.e. up to eight problems (0); -1 (default): the matrix
+ *                units from nine problems on, and for seven or eight logistic ones over 26 or 28 to 32 columns, eight above 288 MB.
  * Unknown names or values return TRON_EINVAL.
  */
 TRON_API int tron_tuning_set(const char *name, int64_t value);
