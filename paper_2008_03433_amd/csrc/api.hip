@@ -237,19 +237,13 @@ static int alloc_row_partials(tron_dataset *ds)
     return TRON_OK;
 }
 
-// A handle of an unpartitioned matrix, its layouts built on the device: 1 = done, 0 = no room for the work space, < 0 = an error.
-// rowptr and y are on the host and have been checked.
-static int create_on_device(tron_dataset *ds, const int64_t *h_rowptr, const int32_t *col, const double *val, const double *h_y, int mem, int64_t rows_used)
+// The layouts of a handle of an unpartitioned matrix, built on the device.  rowptr and y are on the host and have been checked.
+static int layouts_on_device(tron_dataset *ds, const int64_t *h_rowptr, const int32_t *col, const double *val, const double *h_y, int mem, int64_t rows_used)
 {
     const int64_t n = ds->n, d = ds->d, nnz = h_rowptr[n];
-    HostStage stage(ds->stream);
     struct Build : CsrDeviceBuild { ~Build() { release(); } } B;
-    int rc = B.begin(n, d, nnz, h_rowptr, col, val, mem, stage, ds->stream);
-    if (rc == TRON_ENOMEM) {
-        (void)hipGetLastError();
-        return 0;
-    }
-    TRON_TRY(rc);
+    HostStage stage(ds->stream);   // given back first: it waits for the stream
+    TRON_TRY(B.begin(n, d, nnz, h_rowptr, col, val, mem, stage, ds->stream));
     TRON_TRY(stage.copy(ds->y, h_y, sizeof(double) * (size_t)n, ds->stream));
     const CsrFill by_row = B.by_row(), by_column = B.by_column();
     // beside the copies and the sort; what it copies of entries that turn out to be wrong is not used
@@ -269,7 +263,19 @@ static int create_on_device(tron_dataset *ds, const int64_t *h_rowptr, const int
     for (int64_t j = 0; j < d; ++j) cols_used += B.t_rowptr[j + 1] > B.t_rowptr[j];
     if (!ds->fwd.plain) ds->fwd.cold_cols = cols_used;
     TRON_TRY(plan_build(ds->bwd, d, n, B.t_rowptr, nullptr, nullptr, 1, false, false, rows_used, ds->stream, &by_column, &stage));
-    return 1;
+    return TRON_OK;
+}
+
+// 1 = done, < 0 = an error, 0 = no room: the work space (20 bytes an entry, 32 with host arrays) lies beside the layouts (24 bytes) while they are
+// built.  Then nothing is left of the attempt, and the host's way needs the layouts' room only.
+static int create_on_device(tron_dataset *ds, const int64_t *h_rowptr, const int32_t *col, const double *val, const double *h_y, int mem, int64_t rows_used)
+{
+    const int rc = layouts_on_device(ds, h_rowptr, col, val, h_y, mem, rows_used);
+    if (rc != TRON_ENOMEM) return rc < 0 ? rc : 1;
+    (void)hipGetLastError();
+    ds->fwd.release();
+    ds->bwd.release();
+    return 0;
 }
 
 }  // namespace tron
