@@ -263,6 +263,7 @@ static int layouts_on_device(tron_dataset *ds, const int64_t *h_rowptr, const in
     for (int64_t j = 0; j < d; ++j) cols_used += B.t_rowptr[j + 1] > B.t_rowptr[j];
     if (!ds->fwd.plain) ds->fwd.cold_cols = cols_used;
     TRON_TRY(plan_build(ds->bwd, d, n, B.t_rowptr, nullptr, nullptr, 1, false, false, rows_used, ds->stream, &by_column, &stage));
+    TRON_HIP(hipStreamSynchronize(ds->stream));   // what went wrong in the fills and copies is reported here
     return TRON_OK;
 }
 

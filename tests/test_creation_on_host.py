@@ -96,3 +96,23 @@ hip.host_hip_reset(need[0] - 1)   # and what does not fit either way is an error
 rc, h = create(n, d, arrays)
 assert rc == -2 and not h.value and hip.host_hip_live() == 0, (rc, lib.tron_last_error())
 ''')
+
+
+def test_an_error_of_the_last_wait_is_reported(runtime):
+    run(runtime, r'''
+n, d = 3000, 4000
+arrays = problem(n, d, rng.integers(0, 60, n), rng)
+knob("csr_device_build", 1)
+hip.host_hip_reset(UNLIMITED)
+hip.host_hip_fail_waits_from(1 << 30)   # count them
+rc, h = create(n, d, arrays)
+assert rc == 0
+waits = hip.host_hip_syncs()
+lib.tron_dataset_destroy(h)
+for first in range(waits):
+    hip.host_hip_reset(UNLIMITED)
+    hip.host_hip_fail_waits_from(first)
+    rc, h = create(n, d, arrays)
+    assert rc < 0 and not h.value, (first, waits, rc)
+    assert hip.host_hip_live() == 0
+''')
