@@ -41,7 +41,7 @@ void *HostStage::take(size_t bytes)
 int HostStage::copy(void *dst, const void *src, size_t bytes, hipStream_t st, bool stays)
 {
     constexpr size_t kDirect = 4 << 20;   // from here on pageable memory runs at 30 GB/s, and is read for as long as the copy takes
-    void *p = stays && bytes >= kDirect ? nullptr : take(bytes);
+    void *p = bytes >= kDirect ? nullptr : take(bytes);
     if (p) std::memcpy(p, src, bytes);
     TRON_HIP(hipMemcpyAsync(dst, p ? p : src, bytes, hipMemcpyHostToDevice, st));
     if (!p && !stays) TRON_HIP(hipStreamSynchronize(st));

@@ -116,3 +116,23 @@ for first in range(waits):
     assert rc < 0 and not h.value, (first, waits, rc)
     assert hip.host_hip_live() == 0
 ''')
+
+
+def test_long_arrays_are_not_copied_through_pinned_memory(runtime):
+    """A million rows with few entries: what is copied from a place of 4 MB or more goes the way of ordinary memory."""
+    run(runtime, r'''
+n, d = 1_000_000, 4000
+counts = np.zeros(n, dtype=np.int64)
+counts[rng.integers(0, n, 5000)] = 20
+arrays = problem(n, d, counts, rng)
+held = {}
+for way in (0, 1):
+    knob("csr_device_build", way)
+    hip.host_hip_reset(UNLIMITED)
+    rc, h = create(n, d, arrays)
+    assert rc == 0, lib.tron_last_error()
+    held[way] = hip.host_hip_live()
+    lib.tron_dataset_destroy(h)
+    assert hip.host_hip_pinned_peak() < 8 * n, (way, hip.host_hip_pinned_peak())
+assert held[0] == held[1]
+''')
