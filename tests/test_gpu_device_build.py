@@ -50,6 +50,13 @@ def results(n, d, arrays, on_device):
         ds.close()
 
 
+def ends(n):
+    counts = np.zeros(n, dtype=np.int64)
+    counts[:20] = counts[-20:] = 20
+    counts[n // 2] = 3
+    return counts
+
+
 SHAPES = {
     "one entry": lambda rng: (1, 1, [1], 0),
     "entries in one chunk": lambda rng: (40, 300, rng.integers(0, 30, 40), 0),
@@ -61,6 +68,12 @@ SHAPES = {
     "257 columns: two": lambda rng: (2000, 257, rng.integers(0, 60, 2000), 0),
     "more than 65,536 columns: three": lambda rng: (3000, 70_001, rng.integers(0, 90, 3000), 3),
     "rows longer than a wavefront's share of the sort": lambda rng: (400, 3000, rng.integers(900, 2047, 400), 0),
+    # one chunk of entries between which there are so many empty rows or columns that its positions are looked up: 8 x 2048 rows are the last that are
+    # walked
+    "16,384 rows of which the ends have entries": lambda rng: (16_384, 400, ends(16_384), 0),
+    "16,385 rows of which the ends have entries": lambda rng: (16_385, 400, ends(16_385), 0),
+    "a run of empty rows before a chunk that is full": lambda rng: (40_000, 400, ends(40_000) * 5, 0),
+    "more empty columns than eight chunks": lambda rng: (300, 40_000, rng.integers(0, 6, 300), 3),
 }
 
 
