@@ -327,6 +327,8 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t v, int src)
 // doubles for Z and zhat by problem and row
 __host__ __device__ constexpr int mfma_wave_doubles(int dmax, int kex, int rt) { return rt * (dmax + 2) + 16 + ((kex * (rt + 1) + 1) & ~1); }
 
+__device__ __align__(16) double kNoRow[2] = {0.0, 0.0};   // what is read instead of rows that concern no problem
+
 // RT = rows of X a wavefront keeps in LDS at a time: a whole 64-row tile, or half of one (smaller LDS footprint and
 // fewer registers for the loads in flight, so more wavefronts per SIMD to cover the dependent chains of matrix
 // instructions; the row-per-lane steps then serve 64 / RT problems side by side).
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
     if (live == 0) return;
     // The unit in LDS: row r at r S, S = the first length >= d whose rows start in different banks for 16 consecutive rows
     // (16-byte pieces: S = 2 mod 4; 8-byte pieces: S odd).  Every lane copies NP pieces per unit; those past the unit
-    // (d < DMAX) are fetched from the first bytes of X and land in the slack behind it.
+    // (d < DMAX) are zeros and land in the slack behind it.
     constexpr int xs_len = RT * (DMAX + 2) + 16;
     const int S = VEC ? D + ((6 - D % 4) % 4) : (D | 1);
     const int kex = kHasEx ? K : 0;
@@ -435,9 +437,8 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
     // the rows of unit h of a tile that concern some problem
     auto unit_rows = [&](uint64_t rows, int h) -> uint64_t { return RT == kWave ? rows : ((rows >> (RT * h)) & 0xffffffffull); };
     // Loads of a unit into xr, then xr into LDS.  No load sits behind a branch on a per-lane condition (the compiler would
-    // wait for every load in flight where such paths join): a piece of a row that concerns no problem, or past the end, is
-    // fetched from the first bytes of X instead -- one cached line for all of them -- and copied like the others; its row
-    // coefficient is zero in every problem and X is finite, so what lies there does not matter.
+    // wait for every load in flight where such paths join): for a piece of a row that concerns no problem, or past the end,
+    // zeros are fetched (kNoRow: one cached line for all of them) and copied like the others.  What lies in such a row counts for nothing.
     auto fetch = [&](int64_t tile, int h, uint64_t urows) __attribute__((always_inline)) {
         const int64_t row0 = tile * kWave + RT * h;
         const double *base = X + row0 * d;
@@ -458,7 +459,7 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
 #pragma unroll
                 for (int it = 0; it < NP; ++it) {
                     if (it >= pieces / kWave) {
-                        if (it * kWave < pieces) load(it, it * kWave + lane < pieces ? base + it * kWave * PW + lane * PW : X);
+                        if (it * kWave < pieces) load(it, it * kWave + lane < pieces ? base + it * kWave * PW + lane * PW : kNoRow);
                     } else if constexpr (VEC) {
                         const v2d t = __builtin_nontemporal_load((const __attribute__((address_space(1))) v2d *)(at + it * kWave * PW));
                         xr[it][0] = t.x;
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
 #pragma unroll
             for (int it = 0; it < NP; ++it) {
                 if (it < pieces / kWave) load(it, base + it * kWave * PW + lane * PW);   // uniform
-                else if (it * kWave < pieces) load(it, it * kWave + lane < pieces ? base + it * kWave * PW + lane * PW : X);
+                else if (it * kWave < pieces) load(it, it * kWave + lane < pieces ? base + it * kWave * PW + lane * PW : kNoRow);
             }
             return;
         }
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
             asm volatile("" : "+v"(at));   // (not to be kept in registers for all units)
             const uint32_t e = (it * kWave + at) * PW, row = (uint32_t)(((uint64_t)e * inv_d) >> 32);
             const bool take = row < (uint32_t)RT && ((urows >> (row & (RT - 1))) & 1u) && row0 + row < n;
-            load(it, take ? base + e : X);
+            load(it, take ? base + e : kNoRow);
         }
     };
     auto to_lds = [&]() __attribute__((always_inline)) {
@@ -689,8 +690,10 @@ __global__ __launch_bounds__(kBlock, FG ? 2 : 3) void k_batch_pass_mfma(int64_t 
                                 double cd;
                                 if (svm) cd = (modeM == MODE_DIAG && bit) ? 2.0 : 0.0;
                                 else cd = (modeM == MODE_DIAG) ? e : 0.0;
-                                G1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1v[v] * a1v[v], cd, G1, 0, 0, 0);
-                                if (DMAX > 16) G2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a2v[v] * a2v[v], cd, G2, 0, 0, 0);
+                                // a square that is too large for a number counts as the largest one: infinity times the zero of a problem
+                                // that the row does not concern would be none
+                                G1 = __builtin_amdgcn_mfma_f64_16x16x4f64(fmin(a1v[v] * a1v[v], __DBL_MAX__), cd, G1, 0, 0, 0);
+                                if (DMAX > 16) G2 = __builtin_amdgcn_mfma_f64_16x16x4f64(fmin(a2v[v] * a2v[v], __DBL_MAX__), cd, G2, 0, 0, 0);
                             }
                         }
                     }

@@ -26,12 +26,13 @@ def test_large_batch(n, d, K):
     part = torch.randint(8, (n,), generator=gen, device="cuda", dtype=torch.int32)
     part[n // 2: n // 2 + 6400] = 0          # tiles without a row, tiles with a few
     part[n // 2 + 6400::64][:50] = 1
+    part[0] = 0                              # the matrix' first row among them
     member = torch.zeros(n, dtype=torch.int32, device="cuda")
     for k in range(K):
         member |= ((part != 0) & (part != 1 + k % 7)).to(torch.int32) << k
     handle = tron.tron_dataset_create_dense_empty(n, d)
     held = X.clone()
-    held[part == 0] = 1e100   # (whose squares are numbers, too)
+    held[part == 0] = 1e300   # (whose squares are no numbers)
     tron.tron_dataset_write_rows(handle, 0, n, held, y)
     del held
     ds = tron.Dataset(handle)
