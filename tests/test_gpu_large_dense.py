@@ -16,7 +16,7 @@ def close(got, want, what):
 
 # two lanes a row, four, and 16 to 64 (d > 64); 36 million entries are the first that come this way: just below, at and above it, the last tile
 # with one row, all but one, full
-@pytest.mark.parametrize("n,d", [(4_000_001, 9), (3_600_064, 10), (2_400_063, 15), (2_250_000, 16), (2_250_001, 16), (2_117_648, 17), (2_000_127, 18),
+@pytest.mark.parametrize("n,d", [(4_000_001, 9), (3_599_999, 10), (3_600_064, 10), (2_400_063, 15), (2_249_999, 16), (2_250_000, 16), (2_250_001, 16), (2_117_648, 17), (2_000_127, 18),
                                  (1_500_001, 24), (1_333_376, 27), (1_161_345, 31), (1_125_057, 32), (450_001, 80), (360_003, 101), (200_003, 257), (70_400, 512)])
 def test_large_dense_calls_and_solve(n, d):
     import paper_2008_03433_amd as tron

@@ -247,18 +247,34 @@ def test_csr_one_value_per_instance(rng, loss, force_partitions):
     Bn[:, 11] = 1.0
     pn = _csr_from_dense(Bn / np.sqrt(Bn.sum(axis=1))[:, None], y)
     compare_solves(pn, loss, 1.0, 1e-4, trace_rel=1e-6)
-    # many instances, few features: a tile of the transposed product fills up slowly, so the limit on the columns it may
-    # span (they are copied into LDS) closes it first
+    # many instances, few features.  All of them are hot rows, of which a window holds pieces of at most 256 entries: two windows of 10,000
+    # instances.
     nt, dt = 20000, 300
     Bt = (rng.random((nt, dt)) < 0.05).astype(np.float64)
     Bt[:, 5] = 1.0
-    pt = _csr_from_dense(Bt * np.exp(rng.standard_normal(nt))[:, None], np.where(rng.random(nt) < 0.5, 1.0, -1.0))
+    yt = np.where(rng.random(nt) < 0.5, 1.0, -1.0)
+    pt = _csr_from_dense(Bt * np.exp(rng.standard_normal(nt))[:, None], yt)
     ds = tron.Dataset.from_problem(pt)
     assert tron.tron_dataset_stat(ds.handle, "unit_values") == 1
+    counts = Bt.reshape(2, nt // 2, dt).sum(axis=1)
+    assert counts.sum(axis=0).min() >= 32
+    assert tron.tron_dataset_stat(ds.handle, "bwd_tile_rows") == dt
+    assert tron.tron_dataset_stat(ds.handle, "bwd_tile_nnz") == counts.sum()
+    assert tron.tron_dataset_stat(ds.handle, "bwd_csr_nnz") == 0
+    assert tron.tron_dataset_stat(ds.handle, "bwd_tiles") == np.ceil(counts / 256).sum()
+    ds.close()
+    check_calls(pt, loss, 0.5, rng, w_scale=0.3, n_hv=2)
+    # with values of their own they lie in tiles, which fill up slowly here, so the limit on the columns a tile may span (they are copied into LDS)
+    # closes it first
+    pv = _csr_from_dense(Bt * np.exp(rng.standard_normal((nt, dt))), yt)
+    ds = tron.Dataset.from_problem(pv)
+    assert tron.tron_dataset_stat(ds.handle, "unit_values") == 0
     tiles, tile_nnz = tron.tron_dataset_stat(ds.handle, "bwd_tiles"), tron.tron_dataset_stat(ds.handle, "bwd_tile_nnz")
     ds.close()
-    assert tiles > 0 and tile_nnz / tiles < 0.8 * 2048, (tiles, tile_nnz)   # not filled: closed by the span limit
-    check_calls(pt, loss, 0.5, rng, w_scale=0.3, n_hv=2)
+    assert tile_nnz == counts.sum()
+    # eight slices of features, 512 instances and a few without entries each; closed when full they would be half as many
+    assert 8 * 38 <= tiles <= 8 * 40 and tile_nnz / tiles < 0.8 * 2048, (tiles, tile_nnz)
+    check_calls(pv, loss, 0.5, rng, w_scale=0.3, n_hv=2)
     X2 = B * r[:, None]
     X2[7, 5] *= 1.5
     p2 = _csr_from_dense(X2, y)
