@@ -331,6 +331,10 @@ TRON_API int tron_probe_read_bandwidth(const double *src_dev, int64_t count, int
  *   "csr_segmented" (-1/0/1): unpartitioned layouts as row segments + flag bits (summed by scans) instead of plain CSR
  *                (one lane group per row): 0 never, 1 always, -1 (default) when some chunk of the plain layout would
  *                leave a single thread a row of about a hundred entries or more.
+ *   "csr_device_build" (-1/0/1): unpartitioned layouts built by kernels on the handle's stream: 0 never, 1 always, -1 (default) from
+ *                65,536 entries on.  The same layouts and errors as built on the host; while the call lasts it holds 20 bytes an entry
+ *                (32 with host arrays) of device memory beside the layouts and some pinned memory.  Where that does not fit,
+ *                the host builds them.
  * Partitioned layouts only:
  *   "csr_hot" (0/1): LDS tables of frequent columns in the forward layout;
  *   "csr_head" (0/1): a head partition for the most frequent columns of the whole matrix (needs csr_hot);

@@ -38,6 +38,16 @@ def test_binding_covers_every_declared_symbol():
         assert hasattr(tron, name), f"package does not expose {name}"
 
 
+def test_the_header_describes_every_tuning_knob():
+    src = open(os.path.join(ROOT, "paper_2008_03433_amd", "csrc", "api.hip")).read()
+    body = src[src.index("int tron_tuning_set("):]
+    names = set(re.findall(r'strcmp\(name, "(\w+)"\)', body))
+    assert len(names) >= 20
+    text = open(os.path.join(ROOT, "include", "tron.h")).read()
+    text = text[text.index("Process-wide tuning knobs"):]
+    assert sorted(n for n in names if f'"{n}"' not in text) == []
+
+
 def test_product_package_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2008_03433_amd")
     for dirpath, _, files in os.walk(pkg):
