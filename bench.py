@@ -30,20 +30,21 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published peak
 
 # (workload, library profiler slot) -> (kernel name in rocprofv3 output, profiles/ file that holds its byte counters).
-# The counters were read on exactly that workload at full size; any other run reports traffic = null.
+# The counters were read on exactly that workload at full size; any other run, and a kernel whose bytes in the stored format are no
+# longer those of the summary, reports traffic = null.
 ROCPROF_NAMES = {
-    ("c5", "dense_hv"): ("k_dense_hv<6, 4, 4, true, true, false, false>", "dense_hv_fun_grad_c5.md"),
-    ("c5", "dense_fun_grad"): ("k_dense_fun_grad<6, 4, 4, true, 1>", "dense_hv_fun_grad_c5.md"),
+    ("c5", "dense_hv"): ("k_dense_hv<6, 4, 4, true, true, false, false, true>", "dense_hv_fun_grad_c5.md"),
+    ("c5", "dense_fun_grad"): ("k_dense_fun_grad<6, 4, 4, true, 1, true>", "dense_hv_fun_grad_c5.md"),
     # config 3 has one value per instance: its layouts keep no value stream and run the "unit" kernels
     ("c3", "spmv_head"): ("k_head_sell", "csr_spmv_c3.md"),
     ("c3", "spmv_fwd"): ("k_csr_spmv_part<true, false, false, true>", "csr_spmv_c3.md"),
     ("c3", "spmv_bwd"): ("k_csr_spmv_part<false, false, false, true>", "csr_spmv_c3.md"),
-    ("c3", "spmv_tiles"): ("k_hot_tiles<false, true>", "csr_spmv_c3.md"),
+    ("c3", "spmv_tiles"): ("k_window_sell", "csr_spmv_c3.md"),
     # the same matrix with the general layout forced (csr_unit = 0: 32-bit / 16-bit indices + fp64 values)
     ("c3_values", "spmv_head"): ("k_csr_spmv_part<true, true, false, false>", "csr_spmv_c3_values.md"),
     ("c3_values", "spmv_fwd"): ("k_csr_spmv_part<true, false, false, false>", "csr_spmv_c3_values.md"),
     ("c3_values", "spmv_bwd"): ("k_csr_spmv_part<false, false, false, false>", "csr_spmv_c3_values.md"),
-    ("c3_values", "spmv_tiles"): ("k_hot_tiles<false, false>", "csr_spmv_c3_values.md"),
+    ("c3_values", "spmv_tiles"): ("k_hot_tiles<false>", "csr_spmv_c3_values.md"),
 }
 
 
@@ -143,40 +144,32 @@ def hv_work_bytes(ds) -> float:
     return 24.0 * ds.nnz + 32.0 * ds.n + 32.0 * ds.d
 
 
-def measured_traffic(profile_key, slot: str):
+def measured_traffic(profile_key, slot: str, format_bytes: float):
     """HBM-side bytes per launch from the committed rocprofv3 counter summaries (FETCH_SIZE + WRITE_SIZE, scaled);
-    None unless this run is the workload the summary was taken on."""
+    None unless this run is the workload the summary was taken on and the kernel has the same bytes to move (format_bytes, the
+    library's count, within half a percent of the summary's)."""
     if profile_key is None or (profile_key, slot) not in ROCPROF_NAMES:
         return None
     kname, fname = ROCPROF_NAMES[(profile_key, slot)]
     path = os.path.join(ROOT, "profiles", fname)
     if not os.path.exists(path):
         return None
-    in_traffic = False
-    column = None   # index of the "traffic GB" cell (older summaries: fetched + written)
+    columns = None   # of the table of traffic
     for line in open(path):
         if line.startswith("## "):
-            in_traffic = "traffic" in line
-            column = None
-        if not in_traffic or not line.startswith("|"):
+            columns = None
+        if not line.startswith("|"):
             continue
         cells = [c.strip() for c in line.strip().strip("|").split("|")]
-        if cells and cells[0] == "kernel":
-            column = cells.index("traffic GB") if "traffic GB" in cells else None
-            fetched = cells.index("fetched GB") if "fetched GB" in cells else (cells.index("fetched GB (scaled)") if "fetched GB (scaled)" in cells else None)
-            written = cells.index("written GB") if "written GB" in cells else (cells.index("written GB (scaled)") if "written GB (scaled)" in cells else None)
-            continue
-        if cells and cells[0] == f"`{kname}`":
+        if cells[0] == "kernel":
+            columns = cells if "traffic GB" in cells else None
+        elif columns and cells[0] == f"`{kname}`":
             try:
-                if column is not None:
-                    total = float(cells[column]) * 1e9
-                elif fetched is not None and written is not None:
-                    total = (float(cells[fetched]) + float(cells[written])) * 1e9
-                else:
-                    return None
+                total, stored = (float(cells[columns.index(c)]) * 1e9 for c in ("traffic GB", "format GB"))
             except (ValueError, IndexError):
                 return None
-            return total if total > 0.0 else None    # a row of zeros: the kernel was not in that profile
+            # the summary has three decimals of a GB
+            return total if total > 0.0 and abs(stored - format_bytes) <= 0.005 * stored + 0.5e6 else None
     return None
 
 
@@ -362,7 +355,7 @@ def run_workload(args, wname: str) -> dict:
         if k == "dense_fun_grad":
             fb = fg_fmt
         rec = {"kernel": k, "in": table_name, "bound": "hbm", "achieved": fb / (ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-               "frac": fb / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": measured_traffic(profile_key, k), "ms_per_launch": ms,
+               "frac": fb / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": measured_traffic(profile_key, k, fb), "ms_per_launch": ms,
                "format_bytes_per_launch": fb}
         try:
             rec["work_GB/s"] = work_bytes(ds, stat, k) / (ms * 1e-3) / 1e9

@@ -15,19 +15,47 @@ def _bench():
     return mod
 
 
+def _format_bytes(b, workload, slot):
+    """The bytes in the stored format that the summary was taken with."""
+    kname, fname = b.ROCPROF_NAMES[(workload, slot)]
+    columns = None
+    for line in open(os.path.join(ROOT, "profiles", fname)):
+        cells = [c.strip() for c in line.strip().strip("|").split("|")]
+        if cells[0] == "kernel":
+            columns = cells
+        if cells[0] == f"`{kname}`" and "format GB" in columns:
+            return float(cells[columns.index("format GB")]) * 1e9
+    raise AssertionError((workload, slot, kname))
+
+
 def test_traffic_is_read_from_the_committed_summaries_in_bytes():
     b = _bench()
     # what the kernels of each profiled workload move per launch lies between a few MB and a few tens of GB, and
-    # within a factor of two of known sizes: c5 is 44.2 GB of matrix, the tile kernel of c3 without values reads 0.42 GB
+    # within a factor of two of known sizes: c5 is 44.2 GB of matrix, the hot rows of c3 without values read 0.36 GB
     seen = {}
     for (workload, slot) in b.ROCPROF_NAMES:
-        t = b.measured_traffic(workload, slot)
-        assert t is not None and 1e6 < t < 1e11, (workload, slot, t)
+        stored = _format_bytes(b, workload, slot)
+        t = b.measured_traffic(workload, slot, stored)
+        assert t is not None and 1e6 < t < 1e11 and 0.95 < t / stored < 1.2, (workload, slot, t)
         seen[(workload, slot)] = t
+        # a kernel that has other bytes to move is not the one that was measured
+        assert b.measured_traffic(workload, slot, 0.97 * stored) is None and b.measured_traffic(workload, slot, 1.03 * stored) is None
     assert 0.9 < seen[("c5", "dense_hv")] / (8.0 * 230_000_000 * 24) < 1.1
     assert 0.3e9 < seen[("c3", "spmv_tiles")] < 0.6e9
     assert seen[("c3_values", "spmv_tiles")] > 2.0 * seen[("c3", "spmv_tiles")]   # the value stream triples the bytes
-    assert b.measured_traffic(None, "spmv_tiles") is None and b.measured_traffic("c3", "no_such_kernel") is None
+    assert b.measured_traffic(None, "spmv_tiles", 1e9) is None and b.measured_traffic("c3", "no_such_kernel", 1e9) is None
+
+
+def test_the_measured_kernels_are_in_the_library():
+    import paper_2008_03433_amd as tron
+    b = _bench()
+    lib = open(tron.lib_path(), "rb").read()
+    for kname, _ in b.ROCPROF_NAMES.values():
+        name, _, args = kname.partition("<")
+        mangled = f"{len(name)}{name}"
+        if args:
+            mangled += "I" + "".join({"true": "Lb1E", "false": "Lb0E"}.get(a, f"Li{a}E") for a in args.rstrip(">").split(", ")) + "E"
+        assert mangled.encode() in lib, kname
 
 
 def test_more_than_one_gpu_is_refused_with_a_message():
