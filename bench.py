@@ -144,6 +144,15 @@ def hv_work_bytes(ds) -> float:
     return 24.0 * ds.nnz + 32.0 * ds.n + 32.0 * ds.d
 
 
+def pass_kernel(n: int, d: int, K: int, loss: str) -> str:
+    """What the library runs the pass of K problems on by default: the matrix units from nine problems on, and logistic ones from eight
+    on above 36 million entries and from seven on over 26 or 28 to 32 columns."""
+    first = 9
+    if loss == "lr":
+        first = 7 if d == 26 or 28 <= d <= 32 else 8 if n * d > 36_000_000 else 9
+    return "fp64 matrix instructions" if K >= first else "vector units"
+
+
 def measured_traffic(profile_key, slot: str, format_bytes: float):
     """HBM-side bytes per launch from the committed rocprofv3 counter summaries (FETCH_SIZE + WRITE_SIZE, scaled);
     None unless this run is the workload the summary was taken on and the kernel has the same bytes to move (format_bytes, the
@@ -600,9 +609,7 @@ def cross_validation(X, y, label: str, folds: int = 3, Cs=(0.1, 1.0), eps: float
         torch.cuda.empty_cache()
     agree = max(abs(batch_f[k] - fk) / abs(fk) for k, fk in seq_f)
     return {"workload": label, "n": n, "d": d, "folds": folds, "C": list(Cs), "problems": K, "loss": "l2svm", "eps": eps,
-            # the library's rule per loss: the matrix units from eight problems on (L2-SVM), from five (logistic)
-            "pass_kernel": "fp64 matrix instructions" if K >= 8 else "vector units",
-            "logistic_pass_kernel": "fp64 matrix instructions" if K >= 5 else "vector units",
+            "pass_kernel": pass_kernel(n, d, K, "l2svm"), "logistic_pass_kernel": pass_kernel(n, d, K, "lr"),
             "batched": {"solve_ms": best * 1e3, "rounds": rounds, "hv_pass_ms": hv_pass_ms, "fun_grad_pass_ms": fg_pass_ms,
                         "advance_ms": advance_ms, "logistic_hv_pass_ms": lr_hv_pass_ms, "logistic_fun_grad_pass_ms": lr_fg_pass_ms,
                         "hv_per_second_all_problems": K / ((hv_pass_ms + advance_ms) * 1e-3),

@@ -58,6 +58,17 @@ def test_the_measured_kernels_are_in_the_library():
         assert mangled.encode() in lib, kname
 
 
+def test_the_pass_kernel_named_is_the_one_of_the_library_s_rule():
+    b = _bench()
+    matrix, vector = "fp64 matrix instructions", "vector units"
+    assert [b.pass_kernel(1_000_000, 24, K, "lr") for K in (6, 8, 9)] == [vector, vector, matrix]
+    assert [b.pass_kernel(20_000_000, 24, K, "lr") for K in (7, 8, 12)] == [vector, matrix, matrix]
+    assert [b.pass_kernel(1000, d, 7, "lr") for d in (25, 26, 27, 28, 32)] == [vector, matrix, vector, matrix, matrix]
+    assert [b.pass_kernel(20_000_000, 32, K, "l2svm") for K in (6, 8, 9)] == [vector, vector, matrix]
+    src = open(os.path.join(ROOT, "paper_2008_03433_amd", "csrc", "batch.hip")).read()
+    assert "mfma_from[2] = {s.L == 4 && s.E == 8 ? 7 : read_once(n, d) ? 8 : 9, 9};" in src   # what is said above
+
+
 def test_more_than_one_gpu_is_refused_with_a_message():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
