@@ -50,13 +50,6 @@ def results(n, d, arrays, on_device):
         ds.close()
 
 
-def ends(n):
-    counts = np.zeros(n, dtype=np.int64)
-    counts[:20] = counts[-20:] = 20
-    counts[n // 2] = 3
-    return counts
-
-
 SHAPES = {
     "one entry": lambda rng: (1, 1, [1], 0),
     "entries in one chunk": lambda rng: (40, 300, rng.integers(0, 30, 40), 0),
@@ -68,20 +61,11 @@ SHAPES = {
     "257 columns: two": lambda rng: (2000, 257, rng.integers(0, 60, 2000), 0),
     "more than 65,536 columns: three": lambda rng: (3000, 70_001, rng.integers(0, 90, 3000), 3),
     "rows longer than a wavefront's share of the sort": lambda rng: (400, 3000, rng.integers(900, 2047, 400), 0),
-    # one chunk of entries between which there are so many empty rows or columns that its positions are looked up: 8 x 2048 rows are the last that are
-    # walked
-    "16,384 rows of which the ends have entries": lambda rng: (16_384, 400, ends(16_384), 0),
-    "16,385 rows of which the ends have entries": lambda rng: (16_385, 400, ends(16_385), 0),
-    "a run of empty rows before a chunk that is full": lambda rng: (40_000, 400, ends(40_000) * 5, 0),
-    "more empty columns than eight chunks": lambda rng: (300, 40_000, rng.integers(0, 6, 300), 3),
 }
 
 
-@pytest.mark.parametrize("segmented", [-1, 0, 1])
-@pytest.mark.parametrize("name", SHAPES)
-def test_the_same_layouts_as_on_the_host(rng, name, segmented):
+def compare(rng, n, d, counts, popular, segmented):
     import paper_2008_03433_amd as tron
-    n, d, counts, popular = SHAPES[name](rng)
     arrays = csr(rng, n, d, counts, popular)
     tron.tron_tuning_set("csr_parts", 1)
     tron.tron_tuning_set("csr_segmented", segmented)
@@ -90,6 +74,35 @@ def test_the_same_layouts_as_on_the_host(rng, name, segmented):
     tron.tron_tuning_set("csr_device_build", 1)
     assert results(n, d, arrays, False) == want
     assert results(n, d, arrays, True) == want
+
+
+@pytest.mark.parametrize("segmented", [-1, 0, 1])
+@pytest.mark.parametrize("name", SHAPES)
+def test_the_same_layouts_as_on_the_host(rng, name, segmented):
+    compare(rng, *SHAPES[name](rng), segmented)
+
+
+def ends(n):
+    counts = np.zeros(n, dtype=np.int64)
+    counts[:20] = counts[-20:] = 20
+    counts[n // 2] = 3
+    return counts
+
+
+# A chunk of entries between which there are so many empty rows or columns that its positions are looked up: 8 x 2048 rows are the last that are walked
+EMPTY = {
+    "16,384 rows of which the ends have entries": lambda rng: (16_384, 400, ends(16_384), 0),
+    "16,385 rows of which the ends have entries": lambda rng: (16_385, 400, ends(16_385), 0),
+    "a run of empty rows before a chunk that is full": lambda rng: (40_000, 400, ends(40_000) * 5, 0),
+    "more empty columns than eight chunks": lambda rng: (300, 40_000, rng.integers(0, 6, 300), 3),
+}
+
+
+@pytest.mark.parametrize("segmented", [-1, 0, 1])
+@pytest.mark.parametrize("name", EMPTY)
+def test_the_same_layouts_with_long_runs_of_empty_rows(name, segmented):
+    rng = np.random.default_rng(len(name))
+    compare(rng, *EMPTY[name](rng), segmented)
 
 
 @pytest.mark.parametrize("on_device", [False, True])

@@ -252,8 +252,7 @@ def test_csr_one_value_per_instance(rng, loss, force_partitions):
     nt, dt = 20000, 300
     Bt = (rng.random((nt, dt)) < 0.05).astype(np.float64)
     Bt[:, 5] = 1.0
-    yt = np.where(rng.random(nt) < 0.5, 1.0, -1.0)
-    pt = _csr_from_dense(Bt * np.exp(rng.standard_normal(nt))[:, None], yt)
+    pt = _csr_from_dense(Bt * np.exp(rng.standard_normal(nt))[:, None], np.where(rng.random(nt) < 0.5, 1.0, -1.0))
     ds = tron.Dataset.from_problem(pt)
     assert tron.tron_dataset_stat(ds.handle, "unit_values") == 1
     counts = Bt.reshape(2, nt // 2, dt).sum(axis=1)
@@ -266,7 +265,8 @@ def test_csr_one_value_per_instance(rng, loss, force_partitions):
     check_calls(pt, loss, 0.5, rng, w_scale=0.3, n_hv=2)
     # with values of their own they lie in tiles, which fill up slowly here, so the limit on the columns a tile may span (they are copied into LDS)
     # closes it first
-    pv = _csr_from_dense(Bt * np.exp(rng.standard_normal((nt, dt))), yt)
+    own = np.random.default_rng(7)
+    pv = _csr_from_dense(Bt * np.exp(own.standard_normal((nt, dt))), pt.y)
     ds = tron.Dataset.from_problem(pv)
     assert tron.tron_dataset_stat(ds.handle, "unit_values") == 0
     tiles, tile_nnz = tron.tron_dataset_stat(ds.handle, "bwd_tiles"), tron.tron_dataset_stat(ds.handle, "bwd_tile_nnz")
@@ -274,7 +274,7 @@ def test_csr_one_value_per_instance(rng, loss, force_partitions):
     assert tile_nnz == counts.sum()
     # eight slices of features, 512 instances and a few without entries each; closed when full they would be half as many
     assert 8 * 38 <= tiles <= 8 * 40 and tile_nnz / tiles < 0.8 * 2048, (tiles, tile_nnz)
-    check_calls(pv, loss, 0.5, rng, w_scale=0.3, n_hv=2)
+    check_calls(pv, loss, 0.5, own, w_scale=0.3, n_hv=2)
     X2 = B * r[:, None]
     X2[7, 5] *= 1.5
     p2 = _csr_from_dense(X2, y)
