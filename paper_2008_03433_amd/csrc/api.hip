@@ -430,7 +430,7 @@ int tron_dataset_create_csr(int64_t n, int64_t d, const int64_t *rowptr, const i
         }
     }
     // Hot-row tiles for the transposed product of large matrices: the features with the most entries (rank r by
-    // count -> slice r % 8, slot r / 8) leave the transposed CSR copy and are stored as tiles instead.
+    // count -> slice r % 8, slot r / 8) leave the transposed CSR copy and are stored as tiles instead, or without values in windows.
     std::vector<int32_t> slot_code;
     int nhot = 0;
     const bool partitioned = bwd_partitioned;

@@ -901,7 +901,7 @@ struct tron_batch {
     tron::DriverState drv;
     double *partials = nullptr;           // K x (d+1) x grid
     tron::PassPair pass{{nullptr, nullptr}};
-    size_t pass_lds[2] = {0, 0};          // dynamic LDS of the pass kernel per loss (the matrix-unit pass; 0 otherwise)
+    size_t pass_lds[2] = {0, 0};          // dynamic LDS of the pass kernel per loss (the matrix-unit pass, tiles that come through LDS; 0 otherwise)
     // the matrix-unit pass for rounds in which no problem asks for function and gradient (null: none), with its own
     // dynamic LDS and number of resident workgroups per loss; grid_used = the workgroups of the pass launched last
     tron::PassPair pass_nofg{{nullptr, nullptr}};
@@ -1111,7 +1111,8 @@ static int batch_create_impl(tron_dataset *ds, int K, const uint32_t *member, in
     // from seven on where a lane has eight columns, whose accumulators do not fit the registers of the vector kernel, from eight on over matrices
     // above 288 MB, where neither is the faster one throughout.  us a function-gradient / Hessian call of 5, 6, 7, 8 problems over 10M rows, vector
     // units against matrix units.  L2-SVM, 24 columns: 395 418 452 485 / 325 333 346 364 against 531 529 531 535 / 400 404 406 413; 12 columns, 8 problems:
-    // 320 / 200 against 383 / 261.  Logistic, 24 columns: 643 687 737 785 / 436 441 463 483 against 684 701 739 763 / 490 492 498 507; 30 columns: 726 766
+    // 320 / 200 against 383 / 261; where the tiles have no room in LDS, 8 problems, and a solve with them: 1M x 32 103 / 84, 411 against 99 / 93, 431; 4M x 29
+    // 288 / 217, 1237 against 276 / 231, 1270; 4M x 32, the worst for the vector units, 283 / 218, 1222 against 258 / 217, 1183.  Logistic, 24 columns: 643 687 737 785 / 436 441 463 483 against 684 701 739 763 / 490 492 498 507; 30 columns: 726 766
     // 823 991 / 560 564 722 910 against 764 782 820 845 / 562 575 580 584; 8 problems, 12 columns: 563 / 300 against 553 / 338; 4M x 16: 280 / 160 against
     // 261 / 170; 1M x 24: 93 / 70 against 106 / 75.
     const int mfma_from[2] = {s.L == 4 && s.E == 8 ? 7 : read_once(n, d) ? 8 : 9, 9};   // logistic, L2-SVM

@@ -37,7 +37,7 @@ struct Tuning {
     int64_t csr_head = 1;    // head partition for the matrix' most frequent columns (needs csr_hot; 0 = off)
     int64_t csr_hot_blocks_per_part = 96;  // persistent workgroups per partition when the LDS table is used
     int64_t csr_blocks_per_part = 128;     // persistent workgroups per column range without LDS tables
-    int64_t csr_tiles = 1;   // hot-row tiles for the transposed orientation of partitioned matrices (0 = off)
+    int64_t csr_tiles = 1;   // hot-row tiles or windows for the transposed orientation of partitioned matrices (0 = off)
     int64_t csr_tile_blocks_per_slice = 0;   // persistent workgroups per slice of hot rows (0 = automatic: 96)
     int64_t csr_sell_blocks = 1024;   // workgroups of the sorted-slice head kernel
     int64_t csr_sell = 1;    // unit plans: the head partition as sorted slices of 64 rows, one row per lane (0 = as chunks)
@@ -78,7 +78,7 @@ enum Slot {
     SLOT_SPMV_FWD = 0,     // X times a vector: the chunk kernel (unpartitioned) or the kernel over the column ranges
     SLOT_SPMV_BWD,         // the same for the transposed copy
     SLOT_SPMV_HEAD,        // head partition of X (most frequent columns)
-    SLOT_SPMV_TILES,       // hot-row tiles of the transposed product
+    SLOT_SPMV_TILES,       // hot rows of the transposed product: tiles or windows
     SLOT_SPMV_TILE_REDUCE, // sum of the tiles' workgroup accumulators
     SLOT_SPMV_GATHER,      // vector entries of the LDS-resident columns
     SLOT_SPMV_FIXUP,       // rows split across workgroups
@@ -588,7 +588,7 @@ struct PlanBytes {
     int64_t gather;        // k_gather_hot: ids, the gathered elements, the table copy
     int64_t head;          // head partition (sorted slices or chunks)
     int64_t ranges;        // the column ranges (or the single chunk kernel of an unpartitioned plan)
-    int64_t tiles;         // hot-row tiles incl. the workgroup accumulators
+    int64_t tiles;         // hot-row tiles incl. the workgroup accumulators, or windows incl. the sums of their pieces
     int64_t tile_reduce;
     int64_t combine;       // partial sums in, row vector(s) in, result out
 };

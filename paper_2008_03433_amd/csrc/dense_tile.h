@@ -15,7 +15,11 @@ typedef double v2d __attribute__((ext_vector_type(2)));
 //     call or solve, straight into registers / through LDS: 230M x 24 Hessian-vector 7110 / 6410; 5M x 18 136 and 128 (logistic and L2-SVM)
 //     / 125 and 118, function/gradient 156 and 135 / 141 and 121, logistic solve 704 / 652; 10M x 9 137 / 126 and 161 / 151;
 //   - rows over 16 lanes or more are loaded as they are, non-temporally: 240,000 x 512 181 / 160 us a Hessian-vector call, 200,003 x 257 82 / 75; but
-//     60,000 x 512 (246 MB) 50 / 53, 40,000 x 127 22 / 24.
+//     60,000 x 512 (246 MB) 50 / 53, 40,000 x 127 22 / 24;
+//   - rows of 1 to 8 columns, a lane a row, and of 33 to 64, eight lanes a row, are loaded ordinarily.  us a Hessian-vector call (logistic and L2-SVM),
+//     ordinary / non-temporal loads: 20M x 2 98 and 68 / 113 and 110, 8M x 7 106 and 94 / 222 and 213, 8M x 8 115 and 103 / 163 and 159; 1.5M x 33 91 and 89
+//     / 126 and 125, 1M x 57 102 and 101 / 142 and 142.  Not so even numbers from 40 on, whose 16-byte pieces make whole lines: 1.3M x 40 93 and
+//     92 / 88 and 88, 1.2M x 48 101 and 100 / 91 and 91, 5M x 64 454 and 447 / 404 and 400; they are loaded like the others of eight lanes.
 constexpr int64_t kOnceDoubles = 36'000'000;   // 288 MB
 __host__ __device__ inline bool read_once(int64_t n, int64_t d) { return n * d > kOnceDoubles; }
 constexpr bool tiles_stream(int L) { return L == 2 || L == 4; }
@@ -28,8 +32,8 @@ constexpr bool tiles_stream(int L) { return L == 2 || L == 4; }
 // rows u * RW + lane / L; steps of rows that lie U apart, which would make lane i the owner of row i, took 192 us
 // against 162 us on 5M x 18.  The sum over a row's lanes is folded so that step u's total ends up in the lanes with
 // lane % U == u (row_sum), which own the row: no exchange through LDS between the sums, the per-row work and the way back.
-// Staging whole tiles through LDS, 16 bytes per lane in memory order, was measured too: 227 us on 5M x 18, since the room
-// for the tiles leaves two wavefronts per SIMD.
+// (Tiles of matrices above 288 MB come through LDS by loads that write it directly, see TileStream: 118 to 125 us on 5M x 18.  Copied
+// there through registers, a tile at a time and nothing under way meanwhile, they took 227 us.)
 template <int E, int L, int U, bool VEC>
 struct Tile {
     static constexpr int RW = kWave / L;     // rows per step

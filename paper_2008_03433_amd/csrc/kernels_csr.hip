@@ -10,7 +10,7 @@
 // into a chunk are stored so that they never cross a chunk boundary; one longer than a chunk receives the rest
 // from the `carry` of the following chunks in a small fix-up kernel, in a fixed order -- nothing is ever added in
 // an order that depends on timing, so results are bit-reproducible (the one atomic instruction in use, the LDS
-// add of the unit tile kernel, has a fixed order too).
+// add of the tile kernel, has a fixed order too).
 //
 // The gathers decide the speed.  A gather that misses the vector L1 costs an L2 request of its own, and
 // a CU keeps only ~100 of them in flight; one that misses L2 as well pulls a 64-byte sector for 8 useful
@@ -19,7 +19,7 @@
 //     one LDS table, 16-bit slots, whole rows) and 8 column ranges, workgroup b on range b % 8 so that
 //     each XCD's L2 gathers from its own slice of the vector; each range has an LDS table of its own;
 //   - transposed orientation: hot-row tiles (see HotTiles: LDS accumulators, gathers from a copy of the tile's
-//     columns in LDS) and 8 column ranges for the rest.
+//     columns in LDS), or without values windows of the vector in LDS (see HotWindows), and 8 column ranges for the rest.
 // Partitions write one partial sum per segment; combine kernels add a row's partial sums in a fixed
 // order and apply the epilogue (loss terms, D scaling, v + C * sum) and the first stage of the scalar
 // reductions.
